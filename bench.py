@@ -54,9 +54,9 @@ def kernel_algorithmic_bytes(name, d, n, r, c, k, pa=False):
         "k_est_median": 4 * d + 4 * d,          # vhat read, estimates written
         "k_reduce": (n + 1) * rc4,
         "k_estimate": rc4 + 4 * d + 4 * d,
-        "k_sel_hist": 4 * d,
-        "k_sel_count": 4 * d,
-        "k_sel_write": 4 * d + 4 * k,
+        "k_sel_hist": None,                     # works on the listed keys (or takes one histogram over d values)
+        "k_sel_filter": 4 * d,
+        "k_sel_write": 4 * k,
         "k_gather": k * (4 + 8 * n + 8),
         "k_tail_x": k * 16,
         "k_fill_u32": None,

@@ -56,7 +56,8 @@ typedef struct sams_ctx sams_ctx;
  * Ranges: 1 <= d < 2^31-1, 1 <= n <= 1024, 1 <= r <= SAMS_MAX_ROWS, 1 <= c < 2^31-1, 1 <= k <= d.
  * Allocates the context's device scratch: about 4d bytes for the estimates, d/8 for the index bitmap,
  * small selection state and, when c exceeds one LDS window, the sketch plan and its staging buffer
- * (4*r*d bytes of plan + 4*n*r*d bytes of staging); sams_scratch_bytes reports the total.  The plan is
+ * (4*r*d bytes of plan + 4*n*r*d bytes of staging; the selection's lists live in the staging buffer, without one they take
+ * another 6d bytes); sams_scratch_bytes reports the total.  The plan is
  * built on the stream by this call.
  * For an even r the median of Sec. II-C is the lower middle element.
  */
@@ -251,7 +252,7 @@ int gather_topk(sams_ctx *ctx, const float *u, const float *vhat, const int32_t 
  *   idx_in   [k] int32 in, ascending (unsketch_topk's output)     delta_in  [k] in (gather_topk's output)
  *   k_out    1 <= k_out <= k
  *   idx_out  [k_out] int32 out      delta_out [k_out] out
- * The results feed amsgrad_ef_update with k_sel = k_out.  Uses the context's estimate scratch.
+ * The results feed amsgrad_ef_update with k_sel = k_out.
  */
 int topk_refine(sams_ctx *ctx, const int32_t *idx_in, const float *delta_in, int64_t k_out, int32_t *idx_out,
                 float *delta_out);
@@ -259,8 +260,8 @@ int topk_refine(sams_ctx *ctx, const int32_t *idx_in, const float *delta_in, int
 /*
  * topk_refine for callers that cannot allocate device memory or create a context: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same selection, same kernels, same results as
- * topk_refine(ctx, ...) with ctx->k = k_in, but context-free: the scratch of the selection (k_out positions, a radix
- * histogram, per-tile counts and prefixes; about 4*SAMS_STATIC_MAX_CANDIDATES + 64 KiB bytes) is a static device
+ * topk_refine(ctx, ...) with ctx->k = k_in, but context-free: the scratch of the selection (the listed keys, radix
+ * histograms, per-tile counts and ranks; about 6*SAMS_STATIC_MAX_CANDIDATES + 32 KiB bytes) is a static device
  * array inside the library, which every GPU the library runs on holds until the process ends.  The call allocates
  * and frees nothing and records no memset (every clear is a kernel).
  *   idx_in   [k_in] int32 in, ascending     delta_in [k_in] in      1 <= k_out <= k_in <= SAMS_STATIC_MAX_CANDIDATES

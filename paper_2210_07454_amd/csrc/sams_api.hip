@@ -15,9 +15,9 @@ static std::mutex g_tun_mutex;      // sams_configure against the copy sams_crea
 
 static const char *const kKernelNames[KID_COUNT] = {
     "k_fill_u32", "k_hash_dump", "k_tail_x", "k_tail_zero_e", "k_head", "k_sketch_atomic", "k_reduce",
-    "k_estimate", "k_sel_init", "k_sel_hist", "k_sel_pick", "k_sel_count", "k_sel_scan", "k_sel_write",
+    "k_estimate", "k_sel_hist", "k_sel_filter", "k_sel_count", "k_sel_write",
     "k_gather", "k_plan_build", "k_bin_scatter", "k_bin_accumulate", "k_sketch_lds", "k_bin_lookup",
-    "k_bin_collect", "k_est_median", "k_head_scatter", "k_refine_map", "k_head_pa", "k_head_sparse_v", "k_sel_small"};
+    "k_bin_collect", "k_est_median", "k_head_scatter", "k_head_pa", "k_head_sparse_v", "k_sel_small"};
 
 const char *kernel_name(int kid) { return (kid >= 0 && kid < KID_COUNT) ? kKernelNames[kid] : ""; }
 
@@ -107,15 +107,12 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
         ctx->hp.row[j].as = hash_host[4 * j + 2];
         ctx->hp.row[j].bs = hash_host[4 * j + 3];
     }
-    ctx->ntile = (d + kSelTile - 1) / kSelTile;
     const int64_t words = (d + 31) / 32;
     struct { void **p; int64_t bytes; } allocs[] = {
         {(void **)&ctx->est, d * 4},
         {(void **)&ctx->bitmap, words * 4},
-        {(void **)&ctx->hist, kHistBins * 4},
-        {(void **)&ctx->sel, (int64_t)sizeof(SelState)},
-        {(void **)&ctx->cnt, 2 * ctx->ntile * 4},
-        {(void **)&ctx->base, 2 * ctx->ntile * 4},
+        {(void **)&ctx->sel, (kSelStateWords + 2 * kHistBins) * 4},
+        {(void **)&ctx->sel_tile, 3 * sel_tiles(d) * 4},
     };
     for (auto &a : allocs) {
         hipError_t e = hipMalloc(a.p, (size_t)a.bytes);
@@ -143,7 +140,18 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
     }
     int rc = static_scratch_ptr(&static_scratch);                    // resolved here so that topk_refine_static never has to
     if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, ctx->bitmap, words, 0u);
+    if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, ctx->sel, kSelStateWords + 2 * kHistBins, 0u);
     if (rc == SAMS_OK && ctx->tun.sketch_path != 1) rc = plan_create(ctx, ctx->tun);
+    if (rc == SAMS_OK && plan_staging_words(ctx) < sel_list_words(d)) {
+        hipError_t e = hipMalloc((void **)&ctx->sel_list, (size_t)sel_list_words(d) * 4);
+        if (e != hipSuccess) {
+            g_last_hip_error = (int)e;
+            (void)hipGetLastError();
+            rc = SAMS_ENOMEM;
+        } else {
+            ctx->scratch_bytes += sel_list_words(d) * 4;
+        }
+    }
     if (rc != SAMS_OK) {
         sams_destroy(ctx);
         return rc;
@@ -158,7 +166,7 @@ int sams_destroy(sams_ctx *ctx)
     int rc = SAMS_OK;
     hipError_t e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) { g_last_hip_error = (int)e; rc = SAMS_EHIP; }
-    void *ptrs[] = {ctx->est, ctx->bitmap, ctx->wordrank, ctx->gsel, ctx->hist, ctx->sel, ctx->cnt, ctx->base};
+    void *ptrs[] = {ctx->est, ctx->bitmap, ctx->wordrank, ctx->gsel, ctx->sel, ctx->sel_tile, ctx->sel_list};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     plan_destroy(ctx);
@@ -345,13 +353,11 @@ int unsketch_topk(sams_ctx *ctx, const float *S_mean, const float *vhat, int32_t
     if (!ctx || !S_mean || !idx || !aligned16(S_mean) || !aligned16(idx) || !aligned16(vhat) ||
         !aligned16(est_sel))
         return SAMS_EINVAL;
-    // the selection's state is reset first, so that the estimate kernel can already take the first histogram
     const SelScratch sc = ctx_sel_scratch(ctx);
-    const bool passes = select_uses_passes(ctx->d);
-    bool hist0_done = false;
-    if (passes) SAMS_TRY(enqueue_select_begin(ctx, ctx->stream, sc, ctx->k));
-    SAMS_TRY(enqueue_estimate(ctx, S_mean, vhat, ctx->est, passes ? sc.hist : nullptr, &hist0_done));
-    return enqueue_select(ctx, ctx->stream, sc, ctx->est, ctx->d, ctx->k, idx, est_sel, passes, hist0_done);
+    bool hist_done = false;
+    SAMS_TRY(enqueue_estimate(ctx, S_mean, vhat, ctx->est, &sc, &hist_done));
+    if (sel_list_in_staging(ctx)) ctx->plan.staged_u = nullptr;      // the lists overwrite any staged vector
+    return enqueue_select(ctx, ctx->stream, sc, ctx->est, ctx->d, ctx->k, nullptr, idx, est_sel, hist_done);
 }
 
 int topk_refine(sams_ctx *ctx, const int32_t *idx_in, const float *delta_in, int64_t k_out, int32_t *idx_out,
@@ -359,9 +365,8 @@ int topk_refine(sams_ctx *ctx, const int32_t *idx_in, const float *delta_in, int
 {
     if (!ctx || !idx_in || !delta_in || !idx_out || !delta_out || k_out < 1 || k_out > ctx->k) return SAMS_EINVAL;
     if (!aligned16(idx_in) || !aligned16(delta_in) || !aligned16(idx_out) || !aligned16(delta_out)) return SAMS_EINVAL;
-    // the estimate scratch is free at this point: it holds the positions among the candidates
-    return enqueue_refine(ctx, ctx->stream, ctx_sel_scratch(ctx), reinterpret_cast<int32_t *>(ctx->est), idx_in, delta_in,
-                          ctx->k, k_out, idx_out, delta_out);
+    if (sel_list_in_staging(ctx)) ctx->plan.staged_u = nullptr;      // the lists overwrite any staged vector
+    return enqueue_select(ctx, ctx->stream, ctx_sel_scratch(ctx), delta_in, ctx->k, k_out, idx_in, idx_out, delta_out, false);
 }
 
 int gather_topk(sams_ctx *ctx, const float *u, const float *vhat, const int32_t *idx, float *U_workers,

@@ -27,26 +27,23 @@ extern int g_last_hip_error;
     } while (0)
 
 constexpr int kWave = 64;
-constexpr int kSelTile = 8192;      // coordinates one wavefront compacts in the selection
-constexpr int kHistBins = 2048;     // first radix digit: 11 bits, then 10 and 10
-constexpr int kSelPasses = 3;
-constexpr int kSelSmallSeg = 4096;   // keys per wavefront of the one-workgroup selection ...
-constexpr int kSelSmallMax = 16 * kSelSmallSeg;   // ... which handles up to this many keys
+constexpr int kHistBins = 2048;     // first radix digit of the selection: 11 bits, then 10 and 10 (kHistBins / 2 bins)
+constexpr int64_t kSelSmallMax = 1 << 16;   // keys up to which the selection is one launch after the first histogram
 
-// device-resident state of the radix selection (no host round trip inside a step)
+// device-resident state of the radix selection (no host round trip inside a step); all zero between two selections
+// as far as the next one reads it before writing it: the histograms and `done` are cleared by whoever uses them
 struct SelState {
-    uint32_t prefix;   // key bits decided so far (top bits of the k-th largest |est| pattern)
-    uint32_t k_rem;    // how many keys to take among those matching the prefix
-    uint32_t tau;      // final: the 31-bit pattern of the k-th largest |est|
-    uint32_t k_eq;     // final: how many coordinates with |est| == tau are selected (smallest indices)
+    uint32_t prefix[3];   // key bits decided after each digit: the top bits of the k-th largest |key| pattern (prefix[2]: all 31)
+    uint32_t k_rem[3];    // how many keys to take among those that match the prefix (k_rem[2]: how many equal to the k-th largest)
+    uint32_t done[4];     // workgroups that have finished, per launch of the selection that asks for the last one
 };
 
 // kernels, for the optional per-kernel timing (sams_profile_*)
 enum KernelId {
     KID_FILL = 0, KID_HASH_DUMP, KID_TAIL_X, KID_TAIL_ZERO_E, KID_HEAD, KID_SKETCH_ATOMIC, KID_REDUCE,
-    KID_ESTIMATE, KID_SEL_INIT, KID_SEL_HIST, KID_SEL_PICK, KID_SEL_COUNT, KID_SEL_SCAN, KID_SEL_WRITE,
+    KID_ESTIMATE, KID_SEL_HIST, KID_SEL_FILTER, KID_SEL_COUNT, KID_SEL_WRITE,
     KID_GATHER, KID_PLAN_BUILD, KID_BIN_SCATTER, KID_BIN_ACCUMULATE, KID_SKETCH_LDS, KID_BIN_LOOKUP,
-    KID_BIN_COLLECT, KID_EST_MEDIAN, KID_HEAD_SCATTER, KID_REFINE_MAP, KID_HEAD_PA, KID_HEAD_SPARSE_V, KID_SEL_SMALL, KID_COUNT
+    KID_BIN_COLLECT, KID_EST_MEDIAN, KID_HEAD_SCATTER, KID_HEAD_PA, KID_HEAD_SPARSE_V, KID_SEL_SMALL, KID_COUNT
 };
 const char *kernel_name(int kid);
 
@@ -108,14 +105,25 @@ struct Tunables {
 };
 extern Tunables g_tun;
 
+// the keys a selection has listed (k_sel_filter), and what is known per tile of keys
+struct SelList {
+    uint32_t *val;           // [len + 64]  a listed key's bits (sign included), tile after tile, each from the tile's first position on
+    uint16_t *loc;           // [len + 64]  its position inside the tile
+    uint32_t *cnt;           // [ntile_cap]  listed keys per tile
+    uint2 *group;            // [ntile_cap]  per workgroup of k_sel_count: keys above the threshold, keys equal to it
+};
+
 // scratch of one radix selection (enqueue_select): the context's, or the static one of topk_refine_static
 struct SelScratch {
-    uint32_t *hist;          // [kHistBins]
-    SelState *sel;           // [1]
-    uint32_t *cnt;           // [2][ntile_cap]  per-wavefront-tile counts: greater, equal
-    uint32_t *base;          // [2][ntile_cap]  exclusive prefix: selected before, equal before
-    int64_t ntile_cap;       // tiles of kSelTile keys the arrays have room for
+    SelState *st;
+    uint32_t *hist;          // [2 * kHistBins]  first digit, then second, then third
+    SelList list;
+    int64_t ntile_cap;
 };
+constexpr int64_t kSelStateWords = 64;                               // words of SelState, rounded up; the histograms follow it
+static_assert(sizeof(SelState) <= kSelStateWords * 4, "selection state");
+// tiles for which the per-tile arrays need room when up to len keys are selected from: of 4096 keys, at least 256
+static inline int64_t sel_tiles(int64_t len) { return (len >> 12) + 1 > 256 ? (len >> 12) + 1 : 256; }
 
 }  // namespace sams
 
@@ -130,11 +138,9 @@ struct sams_ctx {
     uint32_t *wordrank;      // [ceil(d/32)]  for a bitmap word with a bit set: the rank (position in idx) of its first set bit;
                              //               with gsel, only where the head is fused per worker (fuse_head = 2), else null
     float *gsel;             // [n][k]        g of every worker at the coordinates of the most recent index set, by rank
-    uint32_t *hist;          // [kHistBins]
-    sams::SelState *sel;     // [1]
-    uint32_t *cnt;           // [2][ntile]  per-wavefront-tile counts: greater, equal
-    uint32_t *base;          // [2][ntile]  exclusive prefix: selected before, equal before
-    int64_t ntile;
+    uint32_t *sel;           // SelState, then the histograms [2 * kHistBins]
+    uint32_t *sel_tile;      // [3][sel_tiles(d)]  SelList::group, cnt
+    uint32_t *sel_list;      // SelList::val and loc when the staging buffer is absent or too small to hold them, else null
     int64_t scratch_bytes;
     sams::Plan plan;
     sams::Tunables tun;      // the tunables as they were when the context was created
@@ -208,24 +214,106 @@ __device__ __forceinline__ float median_of(float (&a)[R])
     return a[(R - 1) / 2];
 }
 
-// exclusive prefix sum over the 1024 threads of a block (part: at least 16 words of LDS; all threads call it):
-// a shuffle scan inside every wavefront, then the 16 wavefront totals through LDS
-__device__ __forceinline__ uint32_t block_exclusive_scan_1024(uint32_t val, uint32_t *part)
+// inclusive prefix sum over the 64 lanes, in registers: six adds through the data-parallel primitives (row shifts by 1, 2,
+// 4, 8 inside rows of 16, then the row totals broadcast), where shuffles would each cost a trip through the LDS crossbar
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x)
 {
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    uint32_t incl = val;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const uint32_t x = __shfl_up(incl, off);
-        if (lane >= off) incl += x;
-    }
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);
+    return x;
+}
+
+// exclusive prefix sum over the N threads of a block (part: at least N / 64 words of LDS; all threads call it):
+// a scan inside every wavefront, then the wavefronts' totals through LDS
+template <int N>
+__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t val, uint32_t *part)
+{
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t incl = wave_inclusive_scan(val);
     if (lane == kWave - 1) part[wave] = incl;
     __syncthreads();
-    uint32_t before = 0;
-#pragma unroll
-    for (int q = 0; q < 1024 / kWave; ++q) before += q < wave ? part[q] : 0u;
+    const uint32_t upto = wave_inclusive_scan(lane < N / kWave ? part[lane] : 0u);
+    const uint32_t before = wave ? (uint32_t)__builtin_amdgcn_readlane((int)upto, wave - 1) : 0u;
     __syncthreads();
     return before + incl - val;
+}
+
+// accesses to data that other workgroups of the same launch write or read (AGENT: coherent across the XCDs' L2s)
+template <bool AGENT, typename T>
+__device__ __forceinline__ T get(const T *p)
+{
+    if constexpr (AGENT) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return *p;
+}
+template <bool AGENT, typename T>
+__device__ __forceinline__ void put(T *p, T v)
+{
+    if constexpr (AGENT) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *p = v;
+}
+
+// True in every thread of the workgroup that comes here last of the nblk of its launch; nobody waits.  The agent-scope
+// accesses and atomics that the workgroups have issued before are complete by then.  *done goes back to 0.
+// sh: a word of LDS.
+__device__ __forceinline__ bool last_workgroup(uint32_t *done, uint32_t nblk, uint32_t *sh)
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                 // this wavefront's stores and atomics have been performed
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t before = atomicAdd(done, 1u);
+        if (before == nblk - 1) put<true>(done, 0u);
+        *sh = before;
+    }
+    __syncthreads();
+    return *sh == nblk - 1;
+}
+
+// The digit in which the k_rem-th largest key lies, from the histogram count(bin) of NB bins: exactly one thread calls
+// sink(digit, number of keys in higher bins), since k_rem <= the number of keys.  Thread t looks at NB / THREADS
+// consecutive bins counted from the top.
+template <int THREADS, int NB, typename C, typename S>
+__device__ __forceinline__ void pick_digit(C count, uint32_t k_rem, S sink, uint32_t *part)
+{
+    constexpr int PER = NB / THREADS;
+    const int top = NB - 1 - (int)threadIdx.x * PER;
+    uint32_t v[PER], sum = 0;
+#pragma unroll
+    for (int z = 0; z < PER; ++z) v[z] = count(top - z);
+#pragma unroll
+    for (int z = 0; z < PER; ++z) sum += v[z];
+    uint32_t above = block_exclusive_scan<THREADS>(sum, part);
+#pragma unroll
+    for (int z = 0; z < PER; ++z) {
+        if (above < k_rem && k_rem <= above + v[z]) sink((uint32_t)(top - z), above);
+        above += v[z];
+    }
+}
+
+// One workgroup picks a digit from its complete global histogram, clears that histogram and leaves the prefix and the
+// remaining count in the state, and in picked[2] (LDS; complete after the next barrier).  k: for digit 0, the number of
+// keys to select.  part: THREADS / 64 words of LDS.
+template <int THREADS>
+__device__ __forceinline__ void sel_pick(SelState *st, uint32_t *hist, int digit, uint32_t k, uint32_t *part, uint32_t *picked)
+{
+    const uint32_t prefix_in = digit == 0 ? 0u : st->prefix[digit - 1];
+    const uint32_t k_rem = digit == 0 ? k : st->k_rem[digit - 1];
+    auto count = [&](int b) {
+        const uint32_t x = get<true>(hist + b);
+        hist[b] = 0u;
+        return x;
+    };
+    const int width = digit == 0 ? 11 : 10;
+    auto sink = [&](uint32_t b, uint32_t above) {
+        const uint32_t prefix = (prefix_in << width) | b;
+        st->prefix[digit] = picked[0] = prefix;
+        st->k_rem[digit] = picked[1] = k_rem - above;
+    };
+    if (digit == 0) pick_digit<THREADS, kHistBins>(count, k_rem, sink, part);
+    else pick_digit<THREADS, kHistBins / 2>(count, k_rem, sink, part);
 }
 
 // ---- enqueue functions (all asynchronous on ctx->stream; return SAMS_OK or SAMS_EHIP) ----
@@ -246,11 +334,12 @@ int enqueue_sketch(sams_ctx *ctx, const float *u, float *S_workers);
 // sams_plan.hip
 int plan_create(sams_ctx *ctx, const Tunables &tun);
 void plan_destroy(sams_ctx *ctx);
+int64_t plan_staging_words(const sams_ctx *ctx);     // size of the staging buffer in floats, 0 without one
 int enqueue_sketch_planned(sams_ctx *ctx, const float *u, float *S_workers);
 int enqueue_row_estimates_planned(sams_ctx *ctx, const float *S_mean, float *rowest);
 // whole recovery through the plan when the fused collect+median kernel applies; *done says whether it ran
 int enqueue_estimates_planned_fused(sams_ctx *ctx, const float *S_mean, const float *vhat, float *est, bool *done,
-                                    uint32_t *hist);   // hist: null, or where to add the first-digit histogram of |est|
+                                    const SelScratch *sc);   // see enqueue_estimate; *done implies the histogram
 bool head_can_fuse(const sams_ctx *ctx);
 // wordrank and gsel exist for this context (sams_create decides): the per-worker fused head then leaves the
 // gradients of the selected coordinates in gsel and the second moments on I_{t-1} need no gathers
@@ -259,15 +348,21 @@ int enqueue_head_scatter(sams_ctx *ctx, const float *g, float *m, float *e_u, fl
                          float beta1, float beta2, float rho, bool pa,   // pa: v, vhat are [n][d] (Alg. 1)
                          const int32_t *idx_prev, int64_t k_prev);       // I_{t-1}, as handed to the tail
 // sams_select.hip
-int enqueue_estimate(sams_ctx *ctx, const float *S_mean, const float *vhat, float *est, uint32_t *hist, bool *hist_done);
-bool select_uses_passes(int64_t len);
-int enqueue_select_begin(sams_ctx *ctx, hipStream_t stream, const SelScratch &sc, int64_t k);
-// ctx may be null (no per-kernel timing); the work goes to `stream`, the scratch is the caller's
+// whether the kernel that takes the first digit's histogram over len keys also picks the digit (the filter does otherwise)
+bool sel_hist_picks(int64_t len);
+// sc != null: a selection of ctx->k from est follows with this scratch; *hist_done tells whether the estimate kernel has
+// also taken the histogram of the first radix digit (see sel_hist_picks)
+int enqueue_estimate(sams_ctx *ctx, const float *S_mean, const float *vhat, float *est, const SelScratch *sc, bool *hist_done);
+// The k of keys[0..len) with the largest magnitude, ties to the smaller position, positions ascending: idx = position, or
+// map[position]; val_sel (or null) = the key.  hist_done: see enqueue_estimate.  ctx may be null (no per-kernel timing);
+// the work goes to `stream`, the scratch is the caller's.
 int enqueue_select(sams_ctx *ctx, hipStream_t stream, const SelScratch &sc, const float *keys, int64_t len, int64_t k,
-                   int32_t *idx, float *val_sel, bool begun, bool hist0_done);
-int enqueue_refine(sams_ctx *ctx, hipStream_t stream, const SelScratch &sc, int32_t *pos, const int32_t *idx_in,
-                   const float *delta_in, int64_t k_in, int64_t k_out, int32_t *idx_out, float *delta_out);
+                   const int32_t *map, int32_t *idx, float *val_sel, bool hist_done);
 SelScratch ctx_sel_scratch(const sams_ctx *ctx);
+// words of SelList::val and loc together for len keys
+static inline int64_t sel_list_words(int64_t len) { return (len + 64) + (len + 64 + 1) / 2; }
+// whether the lists of a selection from d keys live in the staging buffer (idle between two sketches)
+bool sel_list_in_staging(const sams_ctx *ctx);
 // sams_noalloc.hip: device address of the static scratch of topk_refine_static on the current device
 int static_scratch_ptr(void **out);
 

@@ -1,7 +1,7 @@
 // topk_refine_static: the second round's final selection (topk_refine of sams.h) for callers that cannot
 // allocate device memory -- code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
-// It needs no context: the scratch the selection kernels use (positions among the candidates, radix histogram,
-// selection state, per-tile counts and prefixes) lives in a file-scope __device__ array that every GPU the
+// It needs no context: the scratch the selection kernels use (listed keys, radix histograms,
+// selection state, per-tile counts and ranks) lives in a file-scope __device__ array that every GPU the
 // library runs on holds until the process ends.  The kernels are the ones topk_refine launches; they receive the
 // array's device address as an ordinary argument.
 #include <mutex>
@@ -11,18 +11,16 @@
 namespace sams {
 
 constexpr int64_t kStaticMaxCand = SAMS_STATIC_MAX_CANDIDATES;
-constexpr int64_t kStaticTiles = (kStaticMaxCand + kSelTile - 1) / kSelTile;
+constexpr int64_t kStaticTiles = (kStaticMaxCand >> 12) + 1;         // sel_tiles(kStaticMaxCand)
 constexpr int kStaticMaxDevices = 64;
 
 // layout of the scratch, in bytes from its start (every part 256-byte aligned)
-constexpr size_t kOffPos = 0;                                                   // int32 [kStaticMaxCand]
-constexpr size_t kOffHist = kOffPos + (size_t)kStaticMaxCand * 4;               // uint32 [kHistBins]
-constexpr size_t kOffCnt = kOffHist + (size_t)kHistBins * 4;                    // uint32 [2][kStaticTiles]
-constexpr size_t kOffBase = kOffCnt + (size_t)2 * kStaticTiles * 4;             // uint32 [2][kStaticTiles]
-constexpr size_t kOffSel = kOffBase + (size_t)2 * kStaticTiles * 4;             // SelState
-constexpr size_t kStaticBytes = kOffSel + 256;
-static_assert(kOffHist % 256 == 0 && kOffCnt % 256 == 0 && kOffBase % 256 == 0 && kOffSel % 256 == 0, "alignment");
-static_assert(sizeof(SelState) <= 256, "selection state");
+constexpr size_t align256(size_t x) { return (x + 255) / 256 * 256; }
+constexpr size_t kOffVal = 0;                                                        // SelList::val
+constexpr size_t kOffLoc = align256(kOffVal + (size_t)(kStaticMaxCand + 64) * 4);    // SelList::loc
+constexpr size_t kOffTile = align256(kOffLoc + (size_t)(kStaticMaxCand + 64) * 2);   // SelList::group, cnt
+constexpr size_t kOffSel = align256(kOffTile + (size_t)3 * kStaticTiles * 4);        // SelState, then the histograms
+constexpr size_t kStaticBytes = kOffSel + (size_t)(kSelStateWords + 2 * kHistBins) * 4;
 
 // In host code this name is only a handle for hipGetSymbolAddress, never a device address.
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
@@ -64,14 +62,14 @@ int topk_refine_static(const int32_t *idx_in, const float *delta_in, int64_t k_i
     void *p = nullptr;
     SAMS_TRY(static_scratch_ptr(&p));
     unsigned char *b = static_cast<unsigned char *>(p);
-    const SelScratch sc = {reinterpret_cast<uint32_t *>(b + kOffHist), reinterpret_cast<SelState *>(b + kOffSel),
-                           reinterpret_cast<uint32_t *>(b + kOffCnt), reinterpret_cast<uint32_t *>(b + kOffBase),
+    uint32_t *tile = reinterpret_cast<uint32_t *>(b + kOffTile), *sel = reinterpret_cast<uint32_t *>(b + kOffSel);
+    const SelScratch sc = {reinterpret_cast<SelState *>(sel), sel + kSelStateWords,
+                           {reinterpret_cast<uint32_t *>(b + kOffVal), reinterpret_cast<uint16_t *>(b + kOffLoc),
+                            tile + 2 * kStaticTiles, reinterpret_cast<uint2 *>(tile)},
                            kStaticTiles};
-    // Nothing here needs clearing by the host: the selection's first kernel resets the histogram and the state, the
-    // counts and prefixes are written for every tile of this call before they are read, and only the first k_out
-    // positions are read back.
-    return enqueue_refine(nullptr, (hipStream_t)hip_stream, sc, reinterpret_cast<int32_t *>(b + kOffPos), idx_in,
-                          delta_in, k_in, k_out, idx_out, delta_out);
+    // Nothing here needs clearing by the host: a device array starts as zeros, and a selection leaves its histograms and
+    // counters as zeros for the next one; everything else is written before it is read.
+    return enqueue_select(nullptr, (hipStream_t)hip_stream, sc, delta_in, k_in, k_out, idx_in, idx_out, delta_out, false);
 }
 
 }  // extern "C"

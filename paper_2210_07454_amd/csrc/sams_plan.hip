@@ -386,8 +386,8 @@ k_plan_records(const uint32_t *__restrict__ meta, uint32_t *__restrict__ rec, in
         n_in += inchain[z] ? 1u : 0u;
         n_cs += cstart[z] ? 1u : 0u;
     }
-    uint32_t rank = block_exclusive_scan_1024(n_in, part);
-    uint32_t e = block_exclusive_scan_1024(n_cs, part);
+    uint32_t rank = block_exclusive_scan<1024>(n_in, part);
+    uint32_t e = block_exclusive_scan<1024>(n_cs, part);
     bool too_long = false;
 #pragma unroll
     for (int z = 0; z < 4; ++z) {
@@ -1218,7 +1218,8 @@ __global__ void __launch_bounds__(kFusedThreads)
 k_bin_collect_median(const float *__restrict__ lk, const uint16_t *__restrict__ srcp,
                      const uint32_t *__restrict__ dst16, const uint32_t *__restrict__ pbase,
                      const float *__restrict__ vhat, float *__restrict__ est, int64_t d, int tile_log2,
-                     int64_t ntile, int64_t rowlen, int gl, uint32_t *__restrict__ hist)
+                     int64_t ntile, int64_t rowlen, int gl, uint32_t k, SelState *__restrict__ st,
+                     uint32_t *__restrict__ hist)
 {
     extern __shared__ float rowbuf[];                                // [2][L], at least kHistBins words in all
     const int L = 1 << tile_log2;
@@ -1316,6 +1317,8 @@ k_bin_collect_median(const float *__restrict__ lk, const uint16_t *__restrict__ 
         __syncthreads();
         for (int b = threadIdx.x; b < kHistBins; b += kFusedThreads)
             if (lh[b]) atomicAdd(&hist[b], lh[b]);
+        __syncthreads();                                             // lh is free again: a few words for the last workgroup
+        if (st && last_workgroup(&st->done[0], gridDim.x, lh)) sel_pick<kFusedThreads>(st, hist, 0, k, lh + 32, lh + 2);
     }
 }
 
@@ -1345,7 +1348,7 @@ static int32_t lookup_split(const Plan &pl, int32_t rows)
 }
 
 int enqueue_estimates_planned_fused(sams_ctx *ctx, const float *S_mean, const float *vhat, float *est, bool *done,
-                                    uint32_t *hist)
+                                    const SelScratch *sc)
 {
     Plan &pl = ctx->plan;
     *done = false;
@@ -1362,12 +1365,14 @@ int enqueue_estimates_planned_fused(sams_ctx *ctx, const float *S_mean, const fl
     }
     {
         ProfScope ps(ctx, KID_BIN_COLLECT);
+        const bool pick = sc && sel_hist_picks(ctx->d);
         const size_t lds = (size_t)(2 * L * 4) > (size_t)kHistBins * 4 ? (size_t)(2 * L * 4) : (size_t)kHistBins * 4;
 #define SAMS_CM(RR, IT)                                                                                   \
     case RR:                                                                                              \
         hipLaunchKernelGGL((k_bin_collect_median<RR, IT>), dim3((unsigned)pl.ntile), dim3(kFusedThreads), \
                            lds, ctx->stream, lk, pl.srcp, pl.dst16, pl.pbase, vhat, est,                   \
-                           ctx->d, pl.tile_log2, pl.ntile, pl.rowlen, pl.grp_log2, hist);                 \
+                           ctx->d, pl.tile_log2, pl.ntile, pl.rowlen, pl.grp_log2, (uint32_t)ctx->k,      \
+                           pick ? sc->st : nullptr, sc ? sc->hist : nullptr);                             \
         break;
         switch (ctx->r) {
             SAMS_FUSED_MEDIAN_VARIANTS(SAMS_CM)
@@ -1849,6 +1854,11 @@ void plan_destroy(sams_ctx *ctx)
     pl.dst16 = pl.pbase = pl.binbase = pl.meta = pl.rec = nullptr;
     pl.wlow = nullptr;
     pl.stg = pl.rowest = nullptr;
+}
+
+int64_t plan_staging_words(const sams_ctx *ctx)
+{
+    return ctx->plan.stg ? (int64_t)ctx->n * ctx->plan.stage_rows * ctx->plan.rowlen : 0;
 }
 
 bool head_compacts_g(const sams_ctx *ctx) { return ctx->wordrank != nullptr && ctx->gsel != nullptr; }

@@ -12,22 +12,40 @@ namespace sams {
 // ------------------------------------------------------------------------------------------
 // stage 3a: per-coordinate estimates (Sec. II-C median, Alg. 3 scaling)
 // ------------------------------------------------------------------------------------------
-template <int R>
+__device__ __forceinline__ uint32_t mag_key(float x) { return __float_as_uint(x) & 0x7fffffffu; }
+
+// HIST: a selection follows, and the histogram of the first digit of |est| is taken here (as in k_bin_collect_median).
+template <int R, bool HIST>
 __global__ void __launch_bounds__(256)
 k_estimate(const float *__restrict__ S, const float *__restrict__ vhat, float *__restrict__ est,
-           HashParams hp, int64_t d, int64_t c)
+           HashParams hp, int64_t d, int64_t c, uint32_t *__restrict__ hist)
 {
-    int64_t l = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (l >= d) return;
-    float a[R];
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-        uint32_t b = bucket_of(hp, j, (uint32_t)l);
-        float q = S[(int64_t)j * c + b];
-        a[j] = sign_neg(hp, j, (uint32_t)l) ? -q : q;
+    __shared__ uint32_t lh[HIST ? kHistBins : 1];
+    const int64_t l = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if constexpr (HIST) {
+        for (int b = threadIdx.x; b < kHistBins; b += 256) lh[b] = 0;
+        __syncthreads();
+    } else {
+        if (l >= d) return;
     }
-    float med = median_of<R>(a);
-    est[l] = vhat ? (med / sqrtf(vhat[l])) : med;
+    if (l < d) {
+        float a[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            uint32_t b = bucket_of(hp, j, (uint32_t)l);
+            float q = S[(int64_t)j * c + b];
+            a[j] = sign_neg(hp, j, (uint32_t)l) ? -q : q;
+        }
+        const float med = median_of<R>(a);
+        const float e = vhat ? (med / sqrtf(vhat[l])) : med;
+        est[l] = e;
+        if constexpr (HIST) atomicAdd(&lh[mag_key(e) >> 20], 1u);
+    }
+    if constexpr (HIST) {
+        __syncthreads();
+        for (int b = threadIdx.x; b < kHistBins; b += 256)
+            if (lh[b]) atomicAdd(&hist[b], lh[b]);
+    }
 }
 
 // est[l] = median_j(rowest[j][l]) / sqrt(vhat[l]) from row estimates already in coordinate order
@@ -48,21 +66,22 @@ k_est_median(const float *__restrict__ rowest, const float *__restrict__ vhat, f
 // ------------------------------------------------------------------------------------------
 // stage 3b: exact top-k of |est| by radix selection on the 31-bit magnitude pattern
 // ------------------------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t mag_key(float x) { return __float_as_uint(x) & 0x7fffffffu; }
-
-__device__ __forceinline__ int sel_shift(int pass) { return pass == 0 ? 20 : (pass == 1 ? 10 : 0); }
-__device__ __forceinline__ int sel_width(int pass) { return pass == 0 ? 11 : 10; }
-
-__global__ void k_sel_init(SelState *st, uint32_t k, uint32_t *hist)
-{
-    for (int t = threadIdx.x; t < kHistBins; t += blockDim.x) hist[t] = 0;
-    if (threadIdx.x == 0) {
-        st->prefix = 0;
-        st->k_rem = k;
-        st->tau = 0;
-        st->k_eq = 0;
-    }
-}
+// Digits of 11, 10 and 10 bits.  The histogram of the first digit needs every key (an estimate kernel often takes it).
+// A filter then reads the keys once more and lists those whose first digit is not below that of the k-th largest key --
+// the selected ones and the candidates, about 1.5 k of them unless many keys are equal -- in coordinate order, every
+// tile of keys in a region of its own.  Everything after that works on the listed keys only.
+//   up to 2^16 keys: k_sel_small filters, and its last workgroup finishes the selection
+//   more: k_sel_filter, two histograms of the listed keys, k_sel_count, k_sel_write
+// Up to 2^20 keys every filter workgroup picks the first digit from the histogram for itself (8 KiB, in every L2); above,
+// the last workgroup of the histogram does it once.
+// Code that one workgroup runs once is bound by its chain of latencies, fetching the instructions among them: it is kept
+// short (rolled loops; 16 KB of unrolled code took 5 us longer).
+// "Last workgroup" (last_workgroup) never waits: whoever draws the last number goes on, the others end.  Data that it
+// reads from other workgroups of the same launch goes through agent-scope atomic accesses, since the L2s of the eight
+// XCDs are not coherent with each other inside a launch.
+// Measured on MI355X: 65,536 keys 8 us (one workgroup with three sweeps over the keys: 28); 431,003 keys 29 us (ten
+// launches: 84), 11.2 million keys 35 us after the fused histogram (111), 4.96 million keys of which a quarter is kept
+// 63 us (136), 124 million keys 0.18 ms (0.41): what is left is the filter's pass over the keys and launches of 5 us.
 
 // The streaming passes of the selection read four consecutive keys per lane with one 16-byte load
 // (the entry points accept 16-byte aligned arrays only; the last, partial group of four is read key by key).  Absent keys
@@ -104,391 +123,396 @@ __device__ __forceinline__ void wave_prefix3(uint32_t cnt, uint64_t below, uint3
     *total = t;
 }
 
-// histogram of the current digit over the keys whose higher digits equal the prefix
-__global__ void __launch_bounds__(256)
-k_sel_hist(const float *__restrict__ est, int64_t d, int pass, const SelState *__restrict__ st,
-           uint32_t *__restrict__ hist)
+// Histogram of the first digit over all keys, by a grid of at most kHistMaxGrid workgroups; PICK: the last one picks the
+// digit.
+constexpr int kHistMaxGrid = 512;
+template <bool PICK>
+__global__ void __launch_bounds__(1024)
+k_sel_hist(const float *__restrict__ keys, int64_t len, uint32_t k, SelState *__restrict__ st, uint32_t *__restrict__ hist)
 {
-    __shared__ uint32_t lh[kHistBins];
-    for (int t = threadIdx.x; t < kHistBins; t += blockDim.x) lh[t] = 0;
+    __shared__ uint32_t lh[kHistBins], part[16], sh[2];
+    for (int t = threadIdx.x; t < kHistBins; t += 1024) lh[t] = 0;
     __syncthreads();
-    const int shift = sel_shift(pass), width = sel_width(pass);
-    const uint32_t prefix = st->prefix;
-    const uint32_t dmask = (1u << width) - 1u;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x * 4;
-    for (int64_t l = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) * 4; l < d; l += stride) {
-        const Keys4 q = load_keys4(est, l, d);
+    const int64_t stride = (int64_t)gridDim.x * 4096;
+    for (int64_t l = (blockIdx.x * (int64_t)1024 + threadIdx.x) * 4; l < len; l += stride) {
+        const Keys4 q = load_keys4(keys, l, len);
 #pragma unroll
-        for (int z = 0; z < 4; ++z) {
-            const uint32_t key = mag_key(q.v[z]);
-            if (((q.have >> z) & 1u) && (key >> (shift + width)) == prefix)
-                atomicAdd(&lh[(key >> shift) & dmask], 1u);
-        }
+        for (int z = 0; z < 4; ++z)
+            if ((q.have >> z) & 1u) atomicAdd(&lh[mag_key(q.v[z]) >> 20], 1u);
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < kHistBins; t += blockDim.x)
+    for (int t = threadIdx.x; t < kHistBins; t += 1024)
         if (lh[t]) atomicAdd(&hist[t], lh[t]);
+    if constexpr (PICK) {
+        if (last_workgroup(&st->done[0], gridDim.x, sh)) sel_pick<1024>(st, hist, 0, k, part, sh);
+    }
 }
 
-// choose the digit in which the k_rem-th largest key lies; clear the histogram for the next pass.
-// 1024 threads; thread t looks at the two bins 2t and 2t+1 counted from the top.
-__global__ void __launch_bounds__(1024)
-k_sel_pick(SelState *st, uint32_t *hist, int pass)
+constexpr int kSelTileLog2 = 12;                                     // keys per tile of the filters: 1024 threads, 4 each
+// A tile of keys per workgroup: lists the keys whose first digit is at or above the k-th largest key's, in
+// coordinate order, at val / loc [tile * tile size], their number at cnt[tile].
+// PICK: the workgroup picks that digit from hist0 (the prefix and the number of keys to take among those that match it
+// are left in picked[2], LDS); otherwise it is *prefix_in.  AGENT: the list is read again in this launch.
+template <bool PICK, bool AGENT>
+__device__ __forceinline__ void filter_tile(const float *__restrict__ keys, int64_t len, int64_t tile,
+                                            const uint32_t *__restrict__ prefix_in, const uint32_t *__restrict__ hist0, uint32_t k,
+                                            const SelList &ls, uint32_t *picked)
 {
-    __shared__ uint32_t part[16];
-    const int nb = 1 << sel_width(pass);
+    __shared__ uint32_t part[16], wsum[16];
+    const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
+    const int64_t base = tile << kSelTileLog2;
+    const Keys4 q = load_keys4(keys, base + t * 4, len);
+    uint32_t prefix;
+    if constexpr (PICK) {
+        pick_digit<1024, kHistBins>([&](int b) { return hist0[b]; }, k, [&](uint32_t b, uint32_t above) {
+            picked[0] = b;
+            picked[1] = k - above;
+        }, part);
+        __syncthreads();
+        prefix = picked[0];
+    } else {
+        prefix = *prefix_in;
+    }
+    uint32_t keep = 0, before = 0, total = 0;
+#pragma unroll
+    for (int z = 0; z < 4; ++z)
+        keep |= ((mag_key(q.v[z]) >> 20) >= prefix ? (q.have >> z) & 1u : 0u) << z;
+    if (__ballot(keep != 0u)) wave_prefix3((uint32_t)__popc(keep), ((uint64_t)1 << lane) - 1, &before, &total);
+    if (lane == 0) wsum[wave] = total;
+    __syncthreads();
+    const uint32_t upto = wave_inclusive_scan(lane < 16 ? wsum[lane] : 0u);   // lane w: listed by wavefronts 0 .. w
+    uint32_t pos = before + (uint32_t)__shfl((int)upto, wave) - total;
+#pragma unroll
+    for (int z = 0; z < 4; ++z)
+        if ((keep >> z) & 1u) {
+            put<AGENT>(ls.val + base + pos, __float_as_uint(q.v[z]));
+            put<AGENT>(ls.loc + base + pos, (uint16_t)(t * 4 + z));
+            ++pos;
+        }
+    if (t == 15) put<AGENT>(ls.cnt + tile, upto);
+}
+
+// The listed keys of at most 16 tiles as one sequence in coordinate order, for one workgroup of 1024 threads: entry e is
+// number e - start[tile] of its tile's list; the first kFlatMax entries are copied to LDS.
+constexpr int kSelMaxTiles = 16;                                     // kSelSmallMax keys
+constexpr uint32_t kFlatMax = 4096;
+struct Flat {
+    uint32_t start[2 * kSelMaxTiles];
+    uint32_t val[kFlatMax], pos[kFlatMax];
+    uint32_t part[16], picked[4], hist[2048];
+};
+
+// entries e[0..N), each below the number of entries: tile by bisection, N searches side by side
+template <bool AGENT, int N>
+__device__ __forceinline__ void flat_fetch(const SelList &ls, const Flat &f, const uint32_t (&e)[N], uint2 (&x)[N])
+{
+    uint32_t tile[N];
+#pragma unroll
+    for (int z = 0; z < N; ++z) tile[z] = 0;
+#pragma unroll 1
+    for (uint32_t step = kSelMaxTiles; step; step >>= 1) {
+#pragma unroll
+        for (int z = 0; z < N; ++z)
+            if (f.start[tile[z] + step] <= e[z]) tile[z] += step;
+    }
+#pragma unroll
+    for (int z = 0; z < N; ++z) {
+        const uint32_t base = tile[z] << kSelTileLog2, at = base + e[z] - f.start[tile[z]];
+        x[z] = make_uint2(get<AGENT>(ls.val + at), base + get<AGENT>(ls.loc + at));
+    }
+}
+template <bool AGENT>
+__device__ __forceinline__ uint2 flat_get(const SelList &ls, const Flat &f, uint32_t e)
+{
+    if (e < kFlatMax) return make_uint2(f.val[e], f.pos[e]);
+    uint2 x[1];
+    flat_fetch<AGENT, 1>(ls, f, {e}, x);
+    return x[0];
+}
+
+// the number of entries; complete for all threads
+template <bool AGENT>
+__device__ __forceinline__ uint32_t flat_load(const SelList &ls, Flat &f, int ntile)
+{
     const int t = threadIdx.x;
-    const int b0 = nb - 1 - 2 * t, b1 = nb - 2 - 2 * t;             // descending bins
-    const uint32_t v0 = b0 >= 0 ? hist[b0] : 0u, v1 = b1 >= 0 ? hist[b1] : 0u;
-    const uint32_t k_rem = st->k_rem, prefix_in = st->prefix;
-    const uint32_t above0 = block_exclusive_scan_1024(v0 + v1, part), above1 = above0 + v0;
-    hist[2 * t] = 0;
-    hist[2 * t + 1] = 0;
-    int b = -1;
-    uint32_t above = 0;
-    if (b0 >= 0 && above0 < k_rem && k_rem <= above0 + v0) { b = b0; above = above0; }
-    if (b1 >= 0 && above1 < k_rem && k_rem <= above1 + v1) { b = b1; above = above1; }
-    if (b >= 0) {                                                    // exactly one thread, since k_rem <= total
-        const uint32_t prefix = (prefix_in << sel_width(pass)) | (uint32_t)b;
-        st->prefix = prefix;
-        st->k_rem = k_rem - above;
-        if (pass == kSelPasses - 1) {
-            st->tau = prefix;
-            st->k_eq = k_rem - above;
+    const uint32_t before = block_exclusive_scan<1024>(t < ntile ? get<AGENT>(ls.cnt + t) : 0u, f.part);
+    if (t < 2 * kSelMaxTiles) f.start[t] = before;                   // from ntile on: the number of entries
+    for (int b = t; b < 2048; b += 1024) f.hist[b] = 0;
+    __syncthreads();
+    const uint32_t m = f.start[ntile], mm = m < kFlatMax ? m : kFlatMax;
+#pragma unroll 1
+    for (uint32_t e0 = t; e0 < mm; e0 += 4 * 1024) {
+        uint32_t e[4];
+        uint2 x[4];
+#pragma unroll
+        for (int z = 0; z < 4; ++z) e[z] = e0 + z * 1024 < mm ? e0 + z * 1024 : mm - 1;
+        flat_fetch<AGENT, 4>(ls, f, e, x);
+#pragma unroll
+        for (int z = 0; z < 4; ++z) {                                // (the last entry may be stored twice, alike)
+            f.val[e[z]] = x[z].x;
+            f.pos[e[z]] = x[z].y;
         }
     }
+    __syncthreads();
+    return m;
 }
 
-// a lane's four keys against the threshold: adds to its counts of keys above tau and equal to it
-__device__ __forceinline__ void count_keys4(const Keys4 &q, uint32_t tau, uint32_t &ngt, uint32_t &neq)
+// the last two digits: prefix (the first digit) and k_rem (keys to take among those that match it) become the threshold
+// and how many keys equal to it to take
+template <bool AGENT>
+__device__ __forceinline__ void flat_digits(const SelList &ls, Flat &f, uint32_t m, uint32_t &prefix, uint32_t &k_rem)
 {
-#pragma unroll
-    for (int z = 0; z < 4; ++z) {
-        const uint32_t key = mag_key(q.v[z]);
-        const bool have = (q.have >> z) & 1u;
-        ngt += (have && key > tau) ? 1u : 0u;
-        neq += (have && key == tau) ? 1u : 0u;
+    const int t = threadIdx.x;
+#pragma unroll 1
+    for (int digit = 1; digit <= 2; ++digit) {
+        uint32_t *h = f.hist + (digit - 1) * 1024, *p = f.picked + (digit - 1) * 2;
+        const int up = 30 - 10 * digit;
+        for (uint32_t e = t; e < m; e += 1024) {
+            const uint32_t key = flat_get<AGENT>(ls, f, e).x & 0x7fffffffu;
+            if ((key >> up) == prefix) atomicAdd(&h[(key >> (up - 10)) & 1023u], 1u);
+        }
+        __syncthreads();
+        pick_digit<1024, 1024>([&](int b) { return h[b]; }, k_rem, [&](uint32_t b, uint32_t above) {
+            p[0] = (prefix << 10) | b;
+            p[1] = k_rem - above;
+        }, f.part);
+        __syncthreads();
+        prefix = p[0];
+        k_rem = p[1];
     }
 }
 
-// sums of the lanes' counts over the wavefront (in every lane)
-__device__ __forceinline__ void wave_sum2(uint32_t &a, uint32_t &b)
+// writes the selected entries at their rank: key > tau, or key == tau and among the first k_eq such keys.
+// map != null: the output is map[position] instead of the position.
+template <bool AGENT>
+__device__ __forceinline__ void flat_write(const SelList &ls, Flat &f, uint32_t m, uint32_t tau, uint32_t k_eq, int64_t k,
+                                           const int32_t *__restrict__ map, int32_t *__restrict__ idx,
+                                           float *__restrict__ val_sel)
 {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        a += __shfl_xor(a, off);
-        b += __shfl_xor(b, off);
+    uint32_t gt_run = 0, eq_run = 0;
+#pragma unroll 1
+    for (uint32_t e0 = 0; e0 < m; e0 += 1024) {
+        const uint32_t e = e0 + threadIdx.x;
+        uint2 x = make_uint2(0u, 0u);
+        if (e < m) x = flat_get<AGENT>(ls, f, e);
+        const uint32_t key = x.x & 0x7fffffffu;
+        const bool gt = e < m && key > tau, eq = e < m && key == tau;
+        const uint32_t own = (gt ? 1u : 0u) | (eq ? 0x10000u : 0u);  // both prefixes (at most 1024) in one scan
+        const uint32_t before = block_exclusive_scan<1024>(own, f.part);
+        if (threadIdx.x == 1023) f.picked[0] = before + own;
+        const uint32_t eqb = eq_run + (before >> 16), gtb = gt_run + (before & 0xffffu);
+        if (gt || (eq && eqb < k_eq)) {
+            const int64_t pos = (int64_t)gtb + (eqb < k_eq ? eqb : k_eq);
+            if (pos < k) {
+                idx[pos] = map ? map[x.y] : (int32_t)x.y;
+                if (val_sel) val_sel[pos] = __uint_as_float(x.x);
+            }
+        }
+        __syncthreads();
+        gt_run += f.picked[0] & 0xffffu;
+        eq_run += f.picked[0] >> 16;
+        __syncthreads();
     }
 }
 
-// one wavefront over the keys [base, base + span): how many exceed tau, how many equal it (in every lane)
-__device__ __forceinline__ void wave_count(const float *__restrict__ est, int64_t d, int64_t base, int span,
-                                           uint32_t tau, int lane, uint32_t *gt_out, uint32_t *eq_out)
+// tiles of 4096 keys, one per workgroup
+__global__ void __launch_bounds__(1024)
+k_sel_small(const float *__restrict__ keys, int64_t len, SelState *__restrict__ st, uint32_t *__restrict__ hist, SelList ls,
+            int64_t k, const int32_t *__restrict__ map, int32_t *__restrict__ idx, float *__restrict__ val_sel)
 {
-    uint32_t ngt = 0, neq = 0;                                       // this lane's counts
-    for (int s = 0; s < span; s += kWave * 4) count_keys4(load_keys4(est, base + s + lane * 4, d), tau, ngt, neq);
-    wave_sum2(ngt, neq);
-    *gt_out = ngt;
-    *eq_out = neq;
+    __shared__ Flat f;
+    filter_tile<true, true>(keys, len, blockIdx.x, nullptr, hist, (uint32_t)k, ls, f.picked);
+    uint32_t prefix = f.picked[0], k_rem = f.picked[1];
+    if (!last_workgroup(&st->done[1], gridDim.x, f.part)) return;
+    for (int b = threadIdx.x; b < kHistBins; b += 1024) hist[b] = 0u; // every workgroup has read it
+    __syncthreads();
+    const uint32_t m = flat_load<true>(ls, f, (int)gridDim.x);
+    flat_digits<true>(ls, f, m, prefix, k_rem);
+    flat_write<true>(ls, f, m, prefix, k_rem, k, map, idx, val_sel);
 }
 
-// per wavefront tile of kSelTile consecutive coordinates: how many keys exceed tau, how many equal it
-__global__ void __launch_bounds__(256)
-k_sel_count(const float *__restrict__ est, int64_t d, const SelState *__restrict__ st,
-            uint32_t *__restrict__ cnt_gt, uint32_t *__restrict__ cnt_eq, int64_t ntile)
+// PICK: the filter picks the first digit (and leaves it in the state), see above
+template <bool PICK>
+__global__ void __launch_bounds__(1024)
+k_sel_filter(const float *__restrict__ keys, int64_t len, SelState *__restrict__ st, const uint32_t *__restrict__ hist,
+             SelList ls, uint32_t k)
+{
+    __shared__ uint32_t picked[2];
+    filter_tile<PICK, false>(keys, len, blockIdx.x, st->prefix, hist, k, ls, picked);
+    if (PICK && blockIdx.x == 0 && threadIdx.x == 0) {
+        st->prefix[0] = picked[0];
+        st->k_rem[0] = picked[1];
+    }
+}
+
+constexpr int kSelWriteMaxTpw = 4;
+// f(have, bits) for the listed keys of a tile, 64 at a time by one wavefront; four groups of 64 are fetched
+// together (clamped to the tile's count: in bounds)
+template <typename F>
+__device__ __forceinline__ void each_listed(const SelList &ls, int64_t tile, uint32_t cnt, F f)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    int64_t tile = blockIdx.x * (int64_t)(blockDim.x / kWave) + (threadIdx.x / kWave);
-    if (tile >= ntile) return;
-    uint32_t ngt, neq;
-    wave_count(est, d, tile * kSelTile, kSelTile, st->tau, lane, &ngt, &neq);
-    if (lane == 0) {
-        cnt_gt[tile] = ngt;
-        cnt_eq[tile] = neq;
-    }
-}
-
-// single block: exclusive prefixes over the tiles.  eq_base = equal keys before the tile;
-// sel_base = selected coordinates before the tile, where a tile contributes all its greater keys
-// and as many of its equal keys as are still wanted (k_eq counted from the smallest index).
-// Rounds of 1024 x kScanItems consecutive tiles; a thread owns kScanItems consecutive tiles of a round.
-constexpr int kScanItems = 8;
-
-__global__ void __launch_bounds__(1024)
-k_sel_scan(const uint32_t *__restrict__ cnt_gt, const uint32_t *__restrict__ cnt_eq, int64_t ntile,
-           const SelState *__restrict__ st, uint32_t *__restrict__ sel_base,
-           uint32_t *__restrict__ eq_base)
-{
-    __shared__ uint32_t part[16];
-    __shared__ uint32_t carry[2];
-    const int t = threadIdx.x;
-    const uint32_t k_eq = st->k_eq;
-    uint32_t eq_run = 0, sel_run = 0;                                // totals of the rounds already done
-    for (int64_t q0 = 0; q0 < ntile; q0 += 1024 * kScanItems) {
-        const int64_t lo = q0 + (int64_t)t * kScanItems;
-        uint32_t ce[kScanItems], cg[kScanItems];
-        uint32_t eq_sum = 0;
-#pragma unroll
-        for (int z = 0; z < kScanItems; ++z) {
-            ce[z] = lo + z < ntile ? cnt_eq[lo + z] : 0u;
-            cg[z] = lo + z < ntile ? cnt_gt[lo + z] : 0u;
-            eq_sum += ce[z];
-        }
-        const uint32_t eb0 = eq_run + block_exclusive_scan_1024(eq_sum, part);
-        uint32_t eb = eb0, take_sum = 0;
-#pragma unroll
-        for (int z = 0; z < kScanItems; ++z) {
-            const uint32_t want = eb < k_eq ? k_eq - eb : 0u;
-            take_sum += cg[z] + (ce[z] < want ? ce[z] : want);
-            eb += ce[z];
-        }
-        uint32_t sb = sel_run + block_exclusive_scan_1024(take_sum, part);
-        if (t == 1023) {
-            carry[0] = eb;
-            carry[1] = sb + take_sum;
-        }
-        eb = eb0;
-#pragma unroll
-        for (int z = 0; z < kScanItems; ++z) {
-            const uint32_t want = eb < k_eq ? k_eq - eb : 0u;
-            if (lo + z < ntile) {
-                eq_base[lo + z] = eb;
-                sel_base[lo + z] = sb;
-            }
-            sb += cg[z] + (ce[z] < want ? ce[z] : want);
-            eb += ce[z];
-        }
-        __syncthreads();
-        eq_run = carry[0];
-        sel_run = carry[1];
-        __syncthreads();
-    }
-}
-
-// One sweep of the ordered compaction: the wavefront's lanes hold four consecutive keys each, starting at coordinate
-// l0 in this lane; the selected ones (key > tau, or key == tau and among the first k_eq such keys) are written at
-// their rank.  out, eqr: selected and equal keys before this sweep, updated for the next one.
-__device__ __forceinline__ void compact_keys4(const Keys4 &q, int64_t l0, uint32_t tau, uint32_t k_eq, uint64_t below,
-                                              uint32_t &out, uint32_t &eqr, int64_t k, int32_t *__restrict__ idx,
-                                              float *__restrict__ est_sel)
-{
-    uint32_t gt = 0, eq = 0;                                         // bit z: key z is above / at the threshold
-#pragma unroll
-    for (int z = 0; z < 4; ++z) {
-        const uint32_t key = mag_key(q.v[z]);
-        const bool have = (q.have >> z) & 1u;
-        gt |= (have && key > tau) ? (1u << z) : 0u;
-        eq |= (have && key == tau) ? (1u << z) : 0u;
-    }
-    // Most sweeps hold no key at the threshold and at most one selected key per lane: both prefixes then come from
-    // one ballot instead of three (the branches are uniform over the wavefront).
-    uint32_t take = gt;
-    if (__ballot(eq != 0u) != 0) {
-        uint32_t eq_before, eq_total;
-        wave_prefix3((uint32_t)__popc(eq), below, &eq_before, &eq_total);
+    const uint32_t *val = ls.val + (tile << kSelTileLog2);
+#pragma unroll 1
+    for (uint32_t e0 = 0; e0 < cnt; e0 += 4 * kWave) {
+        uint32_t w[4];
 #pragma unroll
         for (int z = 0; z < 4; ++z) {
-            const uint32_t rank = eqr + eq_before + (uint32_t)__popc(eq & ((1u << z) - 1u));
-            if (((eq >> z) & 1u) && rank < k_eq) take |= 1u << z;
+            const uint32_t e = e0 + z * kWave + lane;
+            w[z] = val[e < cnt ? e : cnt - 1];
         }
-        eqr += eq_total;
-    }
-    const uint64_t any = __ballot(take != 0u);
-    if (any == 0) return;
-    uint32_t take_before, take_total;
-    if (__ballot((take & (take - 1u)) != 0u) == 0) {                 // no lane selects two of its keys
-        take_before = (uint32_t)__popcll(any & below);
-        take_total = (uint32_t)__popcll(any);
-    } else {
-        wave_prefix3((uint32_t)__popc(take), below, &take_before, &take_total);
-    }
 #pragma unroll
-    for (int z = 0; z < 4; ++z) {
-        if ((take >> z) & 1u) {
-            const int64_t pos = (int64_t)out + take_before + __popc(take & ((1u << z) - 1u));
-            if (pos < k) {
-                idx[pos] = (int32_t)(l0 + z);
-                if (est_sel) est_sel[pos] = q.v[z];
-            }
-        }
-    }
-    out += take_total;
-}
-
-// one wavefront walks the keys [base, base + span) in index order and writes the selected ones at their rank;
-// out, eqr: selected and equal keys before base
-__device__ __forceinline__ void wave_compact(const float *__restrict__ est, int64_t d, int64_t base, int span,
-                                             uint32_t tau, uint32_t k_eq, int lane, uint32_t out, uint32_t eqr,
-                                             int64_t k, int32_t *__restrict__ idx, float *__restrict__ est_sel)
-{
-    const uint64_t below = ((uint64_t)1 << lane) - 1;
-    for (int s = 0; s < span; s += kWave * 4) {
-        const int64_t l0 = base + s + lane * 4;                      // this lane's four consecutive keys
-        compact_keys4(load_keys4(est, l0, d), l0, tau, k_eq, below, out, eqr, k, idx, est_sel);
+        for (int z = 0; z < 4; ++z)
+            if (e0 + z * kWave < cnt) f(e0 + z * kWave + lane < cnt, w[z]);
     }
 }
 
-// ordered compaction: every wavefront walks its tile in index order and writes the selected
-// coordinates (key > tau, or key == tau and among the first k_eq such coordinates) at their rank
-__global__ void __launch_bounds__(256)
-k_sel_write(const float *__restrict__ est, int64_t d, const SelState *__restrict__ st,
-            const uint32_t *__restrict__ sel_base, const uint32_t *__restrict__ eq_base,
-            int64_t ntile, int64_t k, int32_t *__restrict__ idx, float *__restrict__ est_sel)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    int64_t tile = blockIdx.x * (int64_t)(blockDim.x / kWave) + (threadIdx.x / kWave);
-    if (tile >= ntile) return;
-    wave_compact(est, d, tile * kSelTile, kSelTile, st->tau, st->k_eq, lane, sel_base[tile], eq_base[tile], k, idx,
-                 est_sel);
-}
-
-// The whole selection in one workgroup of 1024 threads for len <= kSelSmallMax keys: the histogram of the first
-// digit with its pick, one sweep that lists the keys sharing that digit in LDS (the later digits, and the counts at
-// the threshold per segment of kSelSmallSeg keys, then come from the list), prefixes, and the ordered compaction (one
-// wavefront per segment).  Same arithmetic as the kernels above; replaces ten launches, which is most of the step's
-// time when the vector has only tens of thousands of coordinates.  Its time is the instruction issue of one compute
-// unit, about 5 us per sweep over 65,536 keys plus 10 us for the compaction: three sweeps instead of five brought it
-// from 40 to 32 us; four counters per histogram bin, the keys kept in registers across the phases, or the loads of
-// eight sweeps issued together each changed nothing.
-constexpr int kSmallCand = 8192;             // keys sharing the threshold's first digit that the one-workgroup selection can list in LDS
+// histogram of digit 1 or 2 over the listed keys whose higher digits are the picked ones
 __global__ void __launch_bounds__(1024)
-k_sel_small(const float *__restrict__ keys, int64_t len, uint32_t k, int32_t *__restrict__ idx,
-            float *__restrict__ val_sel)
+k_sel_list_hist(SelState *__restrict__ st, uint32_t *__restrict__ hist, SelList ls, int64_t ntile, int digit,
+                uint32_t *__restrict__ clear)   // null, or the first digit's histogram, which the filter has read
 {
-    __shared__ uint32_t lh[kHistBins];
-    __shared__ uint32_t cand[kSmallCand];                            // (segment << 20) | low 20 bits of a listed key
-    __shared__ uint32_t ncand;
-    __shared__ uint32_t part[16];
-    __shared__ uint32_t sh[2];                                       // prefix, k_rem after a pick
-    __shared__ uint32_t seg_gt[16], seg_eq[16], seg_sel_base[16], seg_eq_base[16];
+    __shared__ uint32_t lh[1024], part[16], sh[2];
     const int t = threadIdx.x;
-    const int lane = t & (kWave - 1), seg = t / kWave;               // 16 wavefronts, one segment of the keys each
-    const int64_t base = (int64_t)seg * kSelSmallSeg;
-    uint32_t prefix = 0, k_rem = k;
-    // lh holds the histogram of the next `width` bits over the keys whose higher bits equal prefix: find the bin of
-    // the k_rem-th largest, extend the prefix by it
-    auto pick = [&](int width) {
-        const int nb = 1 << width;
-        const int b0 = nb - 1 - 2 * t, b1 = nb - 2 - 2 * t;          // descending bins, two per thread
-        const uint32_t v0 = b0 >= 0 ? lh[b0] : 0u, v1 = b1 >= 0 ? lh[b1] : 0u;
-        const uint32_t above0 = block_exclusive_scan_1024(v0 + v1, part), above1 = above0 + v0;
-        int b = -1;
-        uint32_t above = 0;
-        if (b0 >= 0 && above0 < k_rem && k_rem <= above0 + v0) { b = b0; above = above0; }
-        if (b1 >= 0 && above1 < k_rem && k_rem <= above1 + v1) { b = b1; above = above1; }
-        if (b >= 0) {                                                // exactly one thread, since k_rem <= total
-            sh[0] = (prefix << width) | (uint32_t)b;
-            sh[1] = k_rem - above;
+    lh[t] = 0;
+    if (clear && blockIdx.x == 0)
+        for (int b = t; b < kHistBins; b += 1024) clear[b] = 0u;
+    __syncthreads();
+    const uint32_t prefix = st->prefix[digit - 1];
+    const int up = 30 - 10 * digit;
+    const int64_t waves = (int64_t)gridDim.x * 16;
+    for (int64_t tile = (int64_t)blockIdx.x * 16 + t / kWave; tile < ntile; tile += waves)
+        each_listed(ls, tile, ls.cnt[tile], [&](bool have, uint32_t bits) {
+            const uint32_t key = bits & 0x7fffffffu;
+            if (have && (key >> up) == prefix) atomicAdd(&lh[(key >> (up - 10)) & 1023u], 1u);
+        });
+    __syncthreads();
+    if (lh[t]) atomicAdd(&hist[t], lh[t]);
+    if (last_workgroup(&st->done[digit], gridDim.x, sh)) sel_pick<1024>(st, hist, digit, 0, part, sh);
+}
+
+// keys of a tile's list that exceed the threshold, and that equal it (uniform over the wavefront)
+__device__ __forceinline__ uint2 count_listed(const SelList &ls, int64_t tile, uint32_t cnt, uint32_t tau)
+{
+    uint2 n = make_uint2(0u, 0u);
+    each_listed(ls, tile, cnt, [&](bool have, uint32_t bits) {
+        n.x += (uint32_t)__popcll(__ballot(have && (bits & 0x7fffffffu) > tau));
+        n.y += (uint32_t)__popcll(__ballot(have && (bits & 0x7fffffffu) == tau));
+    });
+    return n;
+}
+
+// A workgroup has 16 * tpw consecutive tiles, wavefront w the tiles tpw w ... tpw w + tpw - 1 of them.
+// k_sel_count: keys above and at the threshold per workgroup, to group[].
+__global__ void __launch_bounds__(1024)
+k_sel_count(const SelState *__restrict__ st, SelList ls, int64_t ntile, int tpw)
+{
+    __shared__ uint32_t sum[2];
+    const uint32_t tau = st->prefix[2];
+    const int wave = threadIdx.x / kWave;
+    if (threadIdx.x < 2) sum[threadIdx.x] = 0;
+    __syncthreads();
+    uint2 n = make_uint2(0u, 0u);
+    for (int q = 0; q < tpw; ++q) {
+        const int64_t tile = ((int64_t)blockIdx.x * 16 + wave) * tpw + q;
+        if (tile >= ntile) break;
+        const uint2 x = count_listed(ls, tile, ls.cnt[tile], tau);
+        n.x += x.x;
+        n.y += x.y;
+    }
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        atomicAdd(&sum[0], n.x);
+        atomicAdd(&sum[1], n.y);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) ls.group[blockIdx.x] = make_uint2(sum[0], sum[1]);
+}
+
+// k_sel_write: a workgroup adds up what the groups before it hold (every one for itself: a few hundred to two thousand pairs,
+// in place of a scan by one workgroup in between), counts its own tiles and writes their selected keys at their rank:
+// key > tau, or key == tau and among the first k_eq such keys.  map != null: the output is map[position].
+__global__ void __launch_bounds__(1024)
+k_sel_write(const SelState *__restrict__ st, SelList ls, int64_t ntile, int tpw, int64_t k, const int32_t *__restrict__ map,
+            int32_t *__restrict__ idx, float *__restrict__ val_sel)
+{
+    __shared__ uint32_t part[16], sum[2];
+    __shared__ uint32_t tile_gt[16 * kSelWriteMaxTpw], tile_eq[16 * kSelWriteMaxTpw];
+    const uint32_t tau = st->prefix[2], k_eq = st->k_rem[2];
+    const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
+    const uint64_t below = ((uint64_t)1 << lane) - 1;
+    if (t < 2) sum[t] = 0;
+    if (t < 16 * kSelWriteMaxTpw) tile_gt[t] = tile_eq[t] = 0;
+    __syncthreads();
+    uint32_t g = 0, e = 0;
+    for (uint32_t q = t; q < blockIdx.x; q += 1024) {
+        const uint2 x = ls.group[q];
+        g += x.x;
+        e += x.y;
+    }
+    g = wave_inclusive_scan(g);
+    e = wave_inclusive_scan(e);
+    if (lane == kWave - 1) {
+        atomicAdd(&sum[0], g);
+        atomicAdd(&sum[1], e);
+    }
+    const int64_t first = ((int64_t)blockIdx.x * 16 + wave) * tpw;
+    for (int q = 0; q < tpw && first + q < ntile; ++q) {
+        const uint2 n = count_listed(ls, first + q, ls.cnt[first + q], tau);
+        if (lane == 0) {
+            tile_gt[wave * tpw + q] = n.x;
+            tile_eq[wave * tpw + q] = n.y;
         }
-        __syncthreads();
-        prefix = sh[0];
-        k_rem = sh[1];
-        __syncthreads();
-    };
-    auto clear_hist = [&]() {
-        for (int b = t; b < kHistBins; b += 1024) lh[b] = 0;
-        __syncthreads();
-    };
-    auto hist_over_keys = [&](int pass) {
-        const int shift = sel_shift(pass), width = sel_width(pass);
-        const uint32_t dmask = (1u << width) - 1u;
-        clear_hist();
-        for (int64_t l = (int64_t)t * 4; l < len; l += 4096) {
-            const Keys4 q = load_keys4(keys, l, len);
+    }
+    __syncthreads();
+    const int nt = 16 * tpw;
+    const uint32_t own_g = t < nt ? tile_gt[t] : 0u, own_e = t < nt ? tile_eq[t] : 0u;
+    const uint32_t before_g = block_exclusive_scan<1024>(own_g, part), before_e = block_exclusive_scan<1024>(own_e, part);
+    if (t < nt) {
+        tile_gt[t] = sum[0] + before_g;
+        tile_eq[t] = sum[1] + before_e;
+    }
+    __syncthreads();
+    for (int q = 0; q < tpw && first + q < ntile; ++q) {
+        const int64_t base = (first + q) << kSelTileLog2;
+        const uint32_t cnt = ls.cnt[first + q];
+        uint32_t gtr = tile_gt[wave * tpw + q], eqr = tile_eq[wave * tpw + q];
+#pragma unroll 1
+        for (uint32_t e0 = 0; e0 < cnt; e0 += 4 * kWave) {
+            uint32_t bits[4];
+            int32_t l[4];
 #pragma unroll
             for (int z = 0; z < 4; ++z) {
-                const uint32_t key = mag_key(q.v[z]);
-                if (((q.have >> z) & 1u) && (key >> (shift + width)) == prefix)
-                    atomicAdd(&lh[(key >> shift) & dmask], 1u);
+                const uint32_t en = e0 + z * kWave + lane, at = en < cnt ? en : cnt - 1;
+                bits[z] = ls.val[base + at];
+                l[z] = (int32_t)(base + ls.loc[base + at]);
             }
-        }
-        __syncthreads();
-    };
-    hist_over_keys(0);
-    if (t == 0) ncand = 0;
-    pick(sel_width(0));                                              // its barriers also publish ncand = 0
-    // One sweep lists the keys that share the threshold's first digit (few, unless many keys are equal) and counts, per
-    // segment, the keys above that digit; the last two digits and the counts at the threshold then come from the
-    // list instead of from three more sweeps over all keys.
-    {
-        uint32_t ngt = 0;
-        for (int s = 0; s < kSelSmallSeg; s += kWave * 4) {
-            const Keys4 q = load_keys4(keys, base + s + lane * 4, len);
+            if (map) {
+#pragma unroll
+                for (int z = 0; z < 4; ++z) l[z] = map[l[z]];
+            }
 #pragma unroll
             for (int z = 0; z < 4; ++z) {
-                const uint32_t key = mag_key(q.v[z]);
-                if ((q.have >> z) & 1u) {
-                    const uint32_t top = key >> sel_shift(0);
-                    ngt += top > prefix ? 1u : 0u;
-                    if (top == prefix) {
-                        const uint32_t slot = atomicAdd(&ncand, 1u);
-                        if (slot < (uint32_t)kSmallCand) cand[slot] = ((uint32_t)seg << 20) | (key & 0xFFFFFu);
+                if (e0 + z * kWave >= cnt) break;                    // uniform over the wavefront
+                const bool have = e0 + z * kWave + lane < cnt;
+                const uint32_t key = bits[z] & 0x7fffffffu;
+                const uint64_t gtm = __ballot(have && key > tau), eqm = __ballot(have && key == tau);
+                const uint32_t eqb = eqr + (uint32_t)__popcll(eqm & below);
+                if (have && (key > tau || (key == tau && eqb < k_eq))) {
+                    const int64_t pos = (int64_t)gtr + __popcll(gtm & below) + (eqb < k_eq ? eqb : k_eq);
+                    if (pos < k) {
+                        idx[pos] = l[z];
+                        if (val_sel) val_sel[pos] = __uint_as_float(bits[z]);
                     }
                 }
+                gtr += (uint32_t)__popcll(gtm);
+                eqr += (uint32_t)__popcll(eqm);
             }
         }
-        uint32_t zero = 0;
-        wave_sum2(ngt, zero);
-        if (lane == 0) {
-            seg_gt[seg] = ngt;
-            seg_eq[seg] = 0;
-        }
     }
-    __syncthreads();
-    const uint32_t listed = ncand;
-    if (listed <= (uint32_t)kSmallCand) {
-        clear_hist();
-        for (uint32_t q = t; q < listed; q += 1024) atomicAdd(&lh[(cand[q] >> 10) & 1023u], 1u);
-        __syncthreads();
-        pick(sel_width(1));
-        const uint32_t digit1 = prefix & 1023u;
-        clear_hist();
-        for (uint32_t q = t; q < listed; q += 1024) {
-            const uint32_t e = cand[q];
-            if (((e >> 10) & 1023u) == digit1) atomicAdd(&lh[e & 1023u], 1u);
-        }
-        __syncthreads();
-        pick(sel_width(2));
-        const uint32_t tau20 = prefix & 0xFFFFFu;
-        for (uint32_t q = t; q < listed; q += 1024) {
-            const uint32_t e = cand[q], low = e & 0xFFFFFu;
-            if (low > tau20) atomicAdd(&seg_gt[e >> 20], 1u);
-            if (low == tau20) atomicAdd(&seg_eq[e >> 20], 1u);
-        }
-    } else {                                                         // too many to list: sweeps over all keys
-        hist_over_keys(1);
-        pick(sel_width(1));
-        hist_over_keys(2);
-        pick(sel_width(2));
-        uint32_t ngt = 0, neq = 0;
-        if (base < len) wave_count(keys, len, base, kSelSmallSeg, prefix, lane, &ngt, &neq);
-        if (lane == 0) {
-            seg_gt[seg] = ngt;
-            seg_eq[seg] = neq;
-        }
-    }
-    const uint32_t tau = prefix, k_eq = k_rem;
-    __syncthreads();
-    if (t == 0) {
-        uint32_t eb = 0, sb = 0;
-        for (int q = 0; q < 16; ++q) {
-            seg_eq_base[q] = eb;
-            seg_sel_base[q] = sb;
-            const uint32_t want = eb < k_eq ? k_eq - eb : 0u;
-            sb += seg_gt[q] + (seg_eq[q] < want ? seg_eq[q] : want);
-            eb += seg_eq[q];
-        }
-    }
-    __syncthreads();
-    if (base < len)
-        wave_compact(keys, len, base, kSelSmallSeg, tau, k_eq, lane, seg_sel_base[seg], seg_eq_base[seg], (int64_t)k, idx,
-                     val_sel);
 }
 
-// hist != null: the caller is about to select over est and has reset the selection state (enqueue_select_begin);
-// *hist_done tells whether the estimate kernel also took the histogram of the first radix digit
 constexpr int64_t kGatherEstimateMaxTableBytes = 1 << 20, kGatherEstimateMaxD = (int64_t)1 << 22;
-int enqueue_estimate(sams_ctx *ctx, const float *S_mean, const float *vhat, float *est, uint32_t *hist, bool *hist_done)
+int enqueue_estimate(sams_ctx *ctx, const float *S_mean, const float *vhat, float *est, const SelScratch *sc, bool *hist_done)
 {
     if (hist_done) *hist_done = false;
     const int block = 256;
@@ -498,9 +522,9 @@ int enqueue_estimate(sams_ctx *ctx, const float *S_mean, const float *vhat, floa
     const bool small = (int64_t)ctx->r * ctx->c * 4 <= kGatherEstimateMaxTableBytes && ctx->d <= kGatherEstimateMaxD;
     if (ctx->plan.mode == PLAN_BINNED && (ctx->tun.estimate_path == 2 || (ctx->tun.estimate_path == 0 && !small))) {
         bool done = false;
-        SAMS_TRY(enqueue_estimates_planned_fused(ctx, S_mean, vhat, est, &done, hist));
+        SAMS_TRY(enqueue_estimates_planned_fused(ctx, S_mean, vhat, est, &done, sc));
         if (done) {
-            if (hist_done) *hist_done = hist != nullptr;
+            if (hist_done) *hist_done = sc != nullptr;
             return SAMS_OK;
         }
         SAMS_TRY(enqueue_row_estimates_planned(ctx, S_mean, ctx->plan.rowest));
@@ -520,11 +544,18 @@ int enqueue_estimate(sams_ctx *ctx, const float *S_mean, const float *vhat, floa
         SAMS_HIP(hipGetLastError());
         return SAMS_OK;
     }
+    // the histogram with every estimate kernel of up to 2^16 coordinates: two launches do estimate and selection there;
+    // above, several times as many workgroups would each flush theirs
+    const bool with_hist = sc && ctx->d <= kSelSmallMax;
     switch (ctx->r) {
-#define SAMS_CASE(R)                                                                             \
-    case R:                                                                                      \
-        SAMS_LAUNCH(ctx, KID_ESTIMATE, (k_estimate<R>), grid, block, S_mean, vhat, est, ctx->hp, \
-                    ctx->d, ctx->c);                                                             \
+#define SAMS_CASE(R)                                                                                       \
+    case R:                                                                                                \
+        if (with_hist)                                                                                     \
+            SAMS_LAUNCH(ctx, KID_ESTIMATE, (k_estimate<R, true>), grid, block, S_mean, vhat, est, ctx->hp, \
+                        ctx->d, ctx->c, sc->hist);                                                         \
+        else                                                                                               \
+            SAMS_LAUNCH(ctx, KID_ESTIMATE, (k_estimate<R, false>), grid, block, S_mean, vhat, est, ctx->hp, \
+                        ctx->d, ctx->c, nullptr);                                                          \
         break;
         SAMS_CASE(1) SAMS_CASE(2) SAMS_CASE(3) SAMS_CASE(4) SAMS_CASE(5) SAMS_CASE(6) SAMS_CASE(7)
         SAMS_CASE(8) SAMS_CASE(9) SAMS_CASE(10) SAMS_CASE(11) SAMS_CASE(12) SAMS_CASE(13)
@@ -533,74 +564,58 @@ int enqueue_estimate(sams_ctx *ctx, const float *S_mean, const float *vhat, floa
     default:
         return SAMS_EINVAL;
     }
+    if (hist_done) *hist_done = with_hist;
     SAMS_HIP(hipGetLastError());
     return SAMS_OK;
 }
 
-// idx_out[q] = idx_in[pos[q]]: positions among the candidates back to coordinates
-__global__ void __launch_bounds__(256)
-k_refine_map(const int32_t *__restrict__ idx_in, const int32_t *__restrict__ pos, int64_t k_out,
-             int32_t *__restrict__ idx_out)
-{
-    int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (q < k_out) idx_out[q] = idx_in[pos[q]];
-}
+bool sel_list_in_staging(const sams_ctx *ctx) { return ctx->sel_list == nullptr; }
 
 SelScratch ctx_sel_scratch(const sams_ctx *ctx)
 {
-    return SelScratch{ctx->hist, ctx->sel, ctx->cnt, ctx->base, ctx->ntile};
+    uint32_t *list = sel_list_in_staging(ctx) ? reinterpret_cast<uint32_t *>(ctx->plan.stg) : ctx->sel_list;
+    const int64_t nt = sel_tiles(ctx->d);
+    const SelList ls = {list, reinterpret_cast<uint16_t *>(list + ctx->d + 64), ctx->sel_tile + 2 * nt,
+                        reinterpret_cast<uint2 *>(ctx->sel_tile)};
+    return SelScratch{reinterpret_cast<SelState *>(ctx->sel), ctx->sel + kSelStateWords, ls, nt};
 }
 
-// resets the selection state and the histogram for a selection of k out of len keys; nothing to do for the
-// one-workgroup selection of short vectors (returns false)
-bool select_uses_passes(int64_t len) { return len > kSelSmallMax; }
+bool sel_hist_picks(int64_t len) { return len > ((int64_t)1 << 20); }
 
-int enqueue_select_begin(sams_ctx *ctx, hipStream_t stream, const SelScratch &sc, int64_t k)
-{
-    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_INIT, k_sel_init, 1, 256, sc.sel, (uint32_t)k, sc.hist);
-    SAMS_HIP(hipGetLastError());
-    return SAMS_OK;
-}
-
-// the k entries of keys[0..len) with the largest magnitude, ties to the smaller position; positions ascending.
-// begun: enqueue_select_begin has been called for this selection (otherwise it is called here);
-// hist0_done: the histogram of the first digit has been accumulated into sc.hist since then
 int enqueue_select(sams_ctx *ctx, hipStream_t stream, const SelScratch &sc, const float *keys, int64_t len, int64_t k,
-                   int32_t *idx, float *val_sel, bool begun, bool hist0_done)
+                   const int32_t *map, int32_t *idx, float *val_sel, bool hist_done)
 {
+    uint32_t *hist1 = sc.hist + kHistBins, *hist2 = hist1 + kHistBins / 2;
+    if (!hist_done) {
+        if (sel_hist_picks(len))
+            SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, k_sel_hist<true>, grid_for(len, 4096, kHistMaxGrid), 1024, keys, len,
+                           (uint32_t)k, sc.st, sc.hist);
+        else
+            SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, k_sel_hist<false>, grid_for(len, 4096, kHistMaxGrid), 1024, keys, len,
+                           (uint32_t)k, sc.st, sc.hist);
+    }
     if (len <= kSelSmallMax) {
-        SAMS_LAUNCH_ON(ctx, stream, KID_SEL_SMALL, k_sel_small, 1, 1024, keys, len, (uint32_t)k, idx, val_sel);
+        SAMS_LAUNCH_ON(ctx, stream, KID_SEL_SMALL, k_sel_small, grid_for(len, 1 << kSelTileLog2), 1024, keys, len, sc.st,
+                       sc.hist, sc.list, k, map, idx, val_sel);
         SAMS_HIP(hipGetLastError());
         return SAMS_OK;
     }
-    const int64_t nt = (len + kSelTile - 1) / kSelTile;
+    const int64_t nt = (len + (1 << kSelTileLog2) - 1) >> kSelTileLog2;
     if (nt > sc.ntile_cap) return SAMS_EINVAL;
-    uint32_t *cnt_gt = sc.cnt, *cnt_eq = sc.cnt + sc.ntile_cap;
-    uint32_t *sel_base = sc.base, *eq_base = sc.base + sc.ntile_cap;
-    if (!begun) SAMS_TRY(enqueue_select_begin(ctx, stream, sc, k));
-    for (int pass = 0; pass < kSelPasses; ++pass) {
-        if (pass > 0 || !(begun && hist0_done))
-            SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, k_sel_hist, grid_for(len, 256 * 16, 4096), 256, keys, len, pass,
-                           sc.sel, sc.hist);
-        SAMS_LAUNCH_ON(ctx, stream, KID_SEL_PICK, k_sel_pick, 1, 1024, sc.sel, sc.hist, pass);
-    }
-    const int waves_per_block = 256 / kWave;
-    const int tgrid = (int)((nt + waves_per_block - 1) / waves_per_block);
-    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_COUNT, k_sel_count, tgrid, 256, keys, len, sc.sel, cnt_gt, cnt_eq, nt);
-    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_SCAN, k_sel_scan, 1, 1024, cnt_gt, cnt_eq, nt, sc.sel, sel_base, eq_base);
-    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_WRITE, k_sel_write, tgrid, 256, keys, len, sc.sel, sel_base, eq_base, nt, k,
-                   idx, val_sel);
-    SAMS_HIP(hipGetLastError());
-    return SAMS_OK;
-}
-
-// Second round with over-selection (Sec. III-A): the k_out candidates with the largest |delta_in|.  pos: k_out
-// int32 of scratch (positions among the candidates).
-int enqueue_refine(sams_ctx *ctx, hipStream_t stream, const SelScratch &sc, int32_t *pos, const int32_t *idx_in,
-                   const float *delta_in, int64_t k_in, int64_t k_out, int32_t *idx_out, float *delta_out)
-{
-    SAMS_TRY(enqueue_select(ctx, stream, sc, delta_in, k_in, k_out, pos, delta_out, false, false));
-    SAMS_LAUNCH_ON(ctx, stream, KID_REFINE_MAP, k_refine_map, grid_for(k_out, 256), 256, idx_in, pos, k_out, idx_out);
+    const int lgrid = grid_for(nt, 16, 128);
+    const int tpw = nt > 16384 ? kSelWriteMaxTpw : 1;                // at most a few thousand groups for a workgroup to add up
+    const int wgrid = grid_for(nt, 16 * tpw);
+    if (sel_hist_picks(len))
+        SAMS_LAUNCH_ON(ctx, stream, KID_SEL_FILTER, k_sel_filter<false>, (unsigned)nt, 1024, keys, len, sc.st, sc.hist, sc.list,
+                       (uint32_t)k);
+    else
+        SAMS_LAUNCH_ON(ctx, stream, KID_SEL_FILTER, k_sel_filter<true>, (unsigned)nt, 1024, keys, len, sc.st, sc.hist, sc.list,
+                       (uint32_t)k);
+    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, k_sel_list_hist, lgrid, 1024, sc.st, hist1, sc.list, nt, 1,
+                   sel_hist_picks(len) ? nullptr : sc.hist);
+    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, k_sel_list_hist, lgrid, 1024, sc.st, hist2, sc.list, nt, 2, nullptr);
+    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_COUNT, k_sel_count, wgrid, 1024, sc.st, sc.list, nt, tpw);
+    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_WRITE, k_sel_write, wgrid, 1024, sc.st, sc.list, nt, tpw, k, map, idx, val_sel);
     SAMS_HIP(hipGetLastError());
     return SAMS_OK;
 }
