@@ -55,7 +55,8 @@ typedef struct sams_ctx sams_ctx;
  *              the default stream.
  * Ranges: 1 <= d < 2^31-1, 1 <= n <= 1024, 1 <= r <= SAMS_MAX_ROWS, 1 <= c < 2^31-1, 1 <= k <= d.
  * Allocates the context's device scratch: about 4d bytes for the estimates, d/8 for the index bitmap,
- * small selection state and, when c exceeds one LDS window, the sketch plan and its staging buffer
+ * small selection state and, when c exceeds one LDS window, the sketch plan and its staging buffer (for a table of 128 to
+ * 16384 buckets and d <= 2^26, instead, lists of about 4 to 8 bytes per row and coordinate; see "sketch_path")
  * (4*r*d bytes of plan + 4*n*r*d bytes of staging; the selection's lists live in the staging buffer, without one they take
  * another 6d bytes); sams_scratch_bytes reports the total.  The plan is
  * built on the stream by this call.
@@ -124,9 +125,12 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
  *   "estimate_path" 0 (default): stage 3 reads the mean table through the same plan, run backwards, unless the
  *                 table is at most 1 MiB and d <= 2^22 (then as with 1: such a table stays in cache);
  *                 1: one gather per (row, coordinate) straight from the table; 2: through the plan whenever there is one
- *   "sketch_path" 0 (default): the binned, order-preserving path whenever c exceeds one LDS window, and
+ *   "sketch_path" 0 (default): the order-preserving path whenever c exceeds one LDS window, and
  *                 also for smaller tables while d <= 2^22 (one bin; one workgroup per (worker, row) walks the
- *                 vector); LDS atomics for small tables with larger d; 1: one global atomic add per term
+ *                 vector); LDS atomics for small tables with larger d.  A table of 128 to 16384 buckets under a vector of
+ *                 up to 2^26 coordinates keeps the order in another way, without staging, unless "tile_log2", "win_log2",
+ *                 "chunk_log2", "acc_threads", "stage_rows" or "estimate_path" 2 ask for the binned path ("fuse_head"
+ *                 then has nothing to stage and changes nothing); 1: one global atomic add per term
  *                 (no plan memory); 2: the order-preserving path always; 3: LDS atomics whenever c fits one
  *                 window
  * Returns SAMS_EINVAL for an unknown key or a value out of range.
@@ -137,7 +141,7 @@ int sams_configure(const char *key, int value);
 int sams_destroy(sams_ctx *ctx);
 
 /* How this context carries out sketch_accumulate: 0 = one global atomic add per term, 1 = row by row in LDS
- * (c fits one window), 2 = the binned, order-preserving path.  -1 for a NULL context. */
+ * (c fits one window), 2 = the order-preserving path (binned, or by lists for narrow tables).  -1 for a NULL context. */
 int sams_sketch_mode(const sams_ctx *ctx);
 
 /* How the second pass of the binned path reads its metadata in this context (see "acc_wide"): 2 = every row through
@@ -202,7 +206,8 @@ int sams_hash_dump(sams_ctx *ctx, int32_t *bucket, int8_t *sign);
  *     S_workers[i][j][h_j(l)] += s_j(l) * u[i][l]      for all workers i, rows j, coordinates l.
  *   u          [n][d] in    the vectors to sketch (what amsgrad_ef_update leaves in e_u)
  *   S_workers  [n][r][c] out, overwritten (zeroed by the call, then accumulated)
- * On the binned path (sams_sketch_mode() == 2: the default unless c fits one LDS window and d > 2^22)
+ * On the order-preserving path (sams_sketch_mode() == 2: the default unless c fits one LDS window and d > 2^22, and then
+ * too for tables of 128 to 16384 buckets up to d = 2^26)
  * the terms of a bucket are added in ascending coordinate order, i.e. the result equals a sequential
  * loop over l bit for bit and is reproducible.
  * On the other paths (LDS atomics, or "sketch_path" = 1) the order is

@@ -17,7 +17,8 @@ static const char *const kKernelNames[KID_COUNT] = {
     "k_fill_u32", "k_hash_dump", "k_tail_x", "k_tail_zero_e", "k_head", "k_sketch_atomic", "k_reduce",
     "k_estimate", "k_sel_hist", "k_sel_filter", "k_sel_count", "k_sel_write",
     "k_gather", "k_plan_build", "k_bin_scatter", "k_bin_accumulate", "k_sketch_lds", "k_bin_lookup",
-    "k_bin_collect", "k_est_median", "k_head_scatter", "k_head_pa", "k_head_sparse_v", "k_sel_small"};
+    "k_bin_collect", "k_est_median", "k_head_scatter", "k_head_pa", "k_head_sparse_v", "k_sel_small",
+    "k_sketch_pull"};
 
 const char *kernel_name(int kid) { return (kid >= 0 && kid < KID_COUNT) ? kKernelNames[kid] : ""; }
 
@@ -141,7 +142,9 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
     int rc = static_scratch_ptr(&static_scratch);                    // resolved here so that topk_refine_static never has to
     if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, ctx->bitmap, words, 0u);
     if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, ctx->sel, kSelStateWords + 2 * kHistBins, 0u);
-    if (rc == SAMS_OK && ctx->tun.sketch_path != 1) rc = plan_create(ctx, ctx->tun);
+    bool pulls = false;
+    if (rc == SAMS_OK) rc = pull_create(ctx, ctx->tun, &pulls);
+    if (rc == SAMS_OK && !pulls && ctx->tun.sketch_path != 1) rc = plan_create(ctx, ctx->tun);
     if (rc == SAMS_OK && plan_staging_words(ctx) < sel_list_words(d)) {
         hipError_t e = hipMalloc((void **)&ctx->sel_list, (size_t)sel_list_words(d) * 4);
         if (e != hipSuccess) {
@@ -170,6 +173,7 @@ int sams_destroy(sams_ctx *ctx)
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     plan_destroy(ctx);
+    pull_destroy(ctx);
     if (ctx->prof) {
         for (int s = 0; s < kProfPool; ++s) {
             if (ctx->prof[s].a) (void)hipEventDestroy(ctx->prof[s].a);

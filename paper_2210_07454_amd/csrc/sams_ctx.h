@@ -43,7 +43,7 @@ enum KernelId {
     KID_FILL = 0, KID_HASH_DUMP, KID_TAIL_X, KID_TAIL_ZERO_E, KID_HEAD, KID_SKETCH_ATOMIC, KID_REDUCE,
     KID_ESTIMATE, KID_SEL_HIST, KID_SEL_FILTER, KID_SEL_COUNT, KID_SEL_WRITE,
     KID_GATHER, KID_PLAN_BUILD, KID_BIN_SCATTER, KID_BIN_ACCUMULATE, KID_SKETCH_LDS, KID_BIN_LOOKUP,
-    KID_BIN_COLLECT, KID_EST_MEDIAN, KID_HEAD_SCATTER, KID_HEAD_PA, KID_HEAD_SPARSE_V, KID_SEL_SMALL, KID_COUNT
+    KID_BIN_COLLECT, KID_EST_MEDIAN, KID_HEAD_SCATTER, KID_HEAD_PA, KID_HEAD_SPARSE_V, KID_SEL_SMALL, KID_SKETCH_PULL, KID_COUNT
 };
 const char *kernel_name(int kid);
 
@@ -82,6 +82,17 @@ struct Plan {
     float *rowest;      // [r][d]               per-step: signed row estimates in coordinate order (stage 3);
                         //                      absent when the median is fused (fused_median)
     bool fused_median;  // stage 3 keeps the row estimates in registers (decided when the plan is built)
+};
+
+// the lists of the pulling form of the order-preserving path (see sams_pull.hip); kernel == null: this context does not pull
+struct PullPlan {
+    const void *kernel;
+    int32_t ntile;                // tiles of the vector
+    int32_t nslice;               // slices of 64 buckets in a row
+    int32_t per_win, nwin;        // slices per window, windows per row (a workgroup has one)
+    uint32_t *first;              // [streams + 1]       first group of words of a wavefront's lists
+    uint32_t *lists;              // [groups][64][2 or 4]  words of two entries
+    int64_t list_bytes;
 };
 
 // tunables: sams_configure edits the process-wide set, sams_create copies it into the context, and every
@@ -143,6 +154,7 @@ struct sams_ctx {
     uint32_t *sel_list;      // SelList::val and loc when the staging buffer is absent or too small to hold them, else null
     int64_t scratch_bytes;
     sams::Plan plan;
+    sams::PullPlan pull;
     sams::Tunables tun;      // the tunables as they were when the context was created
     // per-kernel timing (host)
     int prof_on;
@@ -331,6 +343,10 @@ int enqueue_gather(sams_ctx *ctx, const float *u, const float *vhat, const int32
                    float *U_workers, float *delta);
 // sams_sketch.hip
 int enqueue_sketch(sams_ctx *ctx, const float *u, float *S_workers);
+// sams_pull.hip
+int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done);
+void pull_destroy(sams_ctx *ctx);
+int enqueue_sketch_pull(sams_ctx *ctx, const float *u, float *S_workers);
 // sams_plan.hip
 int plan_create(sams_ctx *ctx, const Tunables &tun);
 void plan_destroy(sams_ctx *ctx);

@@ -1865,7 +1865,7 @@ bool head_compacts_g(const sams_ctx *ctx) { return ctx->wordrank != nullptr && c
 
 bool head_can_fuse(const sams_ctx *ctx)
 {
-    return ctx->tun.fuse_head && ctx->plan.mode == PLAN_BINNED && (ctx->d & 3) == 0 && ctx->plan.tile_log2 <= 14;
+    return ctx->tun.fuse_head && ctx->plan.mode == PLAN_BINNED && !ctx->pull.kernel && (ctx->d & 3) == 0 && ctx->plan.tile_log2 <= 14;
 }
 
 int enqueue_head_scatter(sams_ctx *ctx, const float *g, float *m, float *e_u, float *v, float *vhat,

@@ -520,7 +520,7 @@ int enqueue_estimate(sams_ctx *ctx, const float *S_mean, const float *vhat, floa
     // A small table under a short vector stays in every L2: r gathers per coordinate in one launch then beat the two
     // launches of the plan-driven recovery (C1: 6 us against 23), which is made for tables far larger than any cache.
     const bool small = (int64_t)ctx->r * ctx->c * 4 <= kGatherEstimateMaxTableBytes && ctx->d <= kGatherEstimateMaxD;
-    if (ctx->plan.mode == PLAN_BINNED && (ctx->tun.estimate_path == 2 || (ctx->tun.estimate_path == 0 && !small))) {
+    if (ctx->plan.mode == PLAN_BINNED && !ctx->pull.kernel && (ctx->tun.estimate_path == 2 || (ctx->tun.estimate_path == 0 && !small))) {
         bool done = false;
         SAMS_TRY(enqueue_estimates_planned_fused(ctx, S_mean, vhat, est, &done, sc));
         if (done) {

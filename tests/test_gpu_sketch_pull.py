@@ -1,0 +1,54 @@
+"""sketch_accumulate of narrow tables (128 to 2^14 buckets), where the workgroups pull their coordinates from tiles of the
+vector: tables bit for bit those of a sequential loop, at the edges of tiles (13,308 coordinates), slices (64 buckets)
+and windows, for workers that start off a 16-byte boundary, and where the path has to step back."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import Oracle
+from paper_2210_07454_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [  # d, n, r, c
+    (13_308, 2, 3, 128), (13_309, 3, 2, 129), (13_307, 3, 2, 191), (26_617, 5, 1, 16_384), (79_851, 3, 3, 10_007),
+    (1, 5, 2, 128), (2, 4, 1, 200), (63, 5, 3, 4_096), (13_310, 90, 3, 400), (13_311, 130, 2, 1_999), (39_927, 67, 4, 2_040),
+    (30_001, 70, 8, 9_000), (100_000, 2, 16, 5_000), (130_563, 1, 1, 16_383), (20_011, 300, 1, 700), (12_345, 150, 2, 16_000),
+]
+
+
+def check(d, n, r, c, hp, seed):
+    from paper_2210_07454_amd import sams
+    rng = np.random.default_rng(seed)
+    u = (rng.standard_normal((n, d)) * 10.0 ** rng.uniform(-3, 1, d)).astype(np.float32)
+    u[:, ::7] *= np.float32(0.0)                                     # zeros of both signs
+    S = torch.full((n, r, c), 9.0, device="cuda")
+    with sams.Context(d, n, r, c, 1, hp) as ctx:
+        assert ctx.sketch_mode == 2
+        ctx.sketch_accumulate(torch.from_numpy(u).cuda(), S)
+        got = S.cpu().numpy()
+        ctx.sams_profile_enable(True)
+        ctx.sketch_accumulate(torch.from_numpy(u).cuda(), S)
+        ctx.sams_profile_enable(False)
+        kernels = set(ctx.sams_profile_read())
+    o = Oracle("f32")
+    for i in range(n):
+        assert np.array_equal(got[i].view(np.uint32), o.sketch(u[i], hp, c).view(np.uint32)), i
+    return kernels
+
+
+@pytest.mark.parametrize("d,n,r,c", SHAPES)
+def test_narrow_tables_bit_exact(d, n, r, c):
+    assert check(d, n, r, c, inputs.hash_params(r, seed=d % 89), d) == {"k_sketch_pull"}
+
+
+def test_a_hash_that_crowds_the_buckets_takes_the_binned_path():
+    """a = c: every coordinate whose product stays below the modulus falls into one bucket."""
+    hp = inputs.hash_params(2, seed=1)
+    hp[0, 0] = 1_000
+    assert "k_sketch_pull" not in check(40_000, 2, 2, 1_000, hp, 3)
+
+
+@pytest.mark.parametrize("c", [127, 16_385])
+def test_tables_outside_the_range_take_the_binned_path(c):
+    assert "k_sketch_pull" not in check(33_000, 2, 2, c, inputs.hash_params(2, seed=4), 5)
