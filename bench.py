@@ -58,7 +58,7 @@ def kernel_algorithmic_bytes(name, d, n, r, c, k, pa=False):
         "k_sel_filter": 4 * d,
         "k_sel_write": 4 * k,
         "k_gather": k * (4 + 8 * n + 8),
-        "k_tail_x": k * 16,
+        "k_tail": k * 16,
         "k_fill_u32": None,
     }
     return table.get(name)

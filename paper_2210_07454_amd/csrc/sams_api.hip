@@ -14,7 +14,7 @@ Tunables g_tun = {0, 0, 0, 0, 0, 1024, 0, 0, 1, 0, 16, 0, 0, 2};
 static std::mutex g_tun_mutex;      // sams_configure against the copy sams_create takes
 
 static const char *const kKernelNames[KID_COUNT] = {
-    "k_fill_u32", "k_hash_dump", "k_tail_x", "k_tail_zero_e", "k_head", "k_sketch_atomic", "k_reduce",
+    "k_fill_u32", "k_hash_dump", "k_tail", "k_tail_zero_e", "k_head", "k_sketch_atomic", "k_reduce",
     "k_estimate", "k_sel_hist", "k_sel_filter", "k_sel_count", "k_sel_write",
     "k_gather", "k_plan_build", "k_bin_scatter", "k_bin_accumulate", "k_sketch_lds", "k_bin_lookup",
     "k_bin_collect", "k_est_median", "k_head_scatter", "k_head_pa", "k_head_sparse_v", "k_sel_small",
@@ -392,13 +392,11 @@ int amsgrad_ef_update(sams_ctx *ctx, const float *g_next, float *m, float *e_u, 
         !aligned16(x) || !aligned16(idx) || !aligned16(delta))
         return SAMS_EINVAL;
     ctx->plan.staged_u = nullptr;                                    // e_u is about to change
-    SAMS_TRY(enqueue_tail(ctx, e_u, x, idx, delta, k_sel, lr, g_next == nullptr));
-    if (g_next) {
-        if (head_can_fuse(ctx))
-            SAMS_TRY(enqueue_head_scatter(ctx, g_next, m, e_u, v, vhat, beta1, beta2, ef_ratio, false, idx, k_sel));
-        else
-            SAMS_TRY(enqueue_head(ctx, g_next, m, e_u, v, vhat, beta1, beta2, ef_ratio));
-    }
+    if (!g_next) return enqueue_tail_only(ctx, e_u, x, idx, delta, k_sel, lr);
+    if (!head_can_fuse(ctx))
+        return enqueue_update(ctx, g_next, m, e_u, v, vhat, x, idx, delta, k_sel, beta1, beta2, lr, ef_ratio, false);
+    SAMS_TRY(enqueue_tail(ctx, x, idx, delta, k_sel, lr));
+    SAMS_TRY(enqueue_head_scatter(ctx, g_next, m, e_u, v, vhat, beta1, beta2, ef_ratio, false, idx, k_sel));
     return SAMS_OK;
 }
 
@@ -412,13 +410,11 @@ int amsgrad_ef_update_pa(sams_ctx *ctx, const float *g_next, float *m, float *e_
         !aligned16(vhat_workers) || !aligned16(x) || !aligned16(idx) || !aligned16(delta))
         return SAMS_EINVAL;
     ctx->plan.staged_u = nullptr;                                    // e_u is about to change
-    SAMS_TRY(enqueue_tail(ctx, e_u, x, idx, delta, k_sel, lr, g_next == nullptr));
-    if (g_next) {
-        if (head_can_fuse(ctx))
-            SAMS_TRY(enqueue_head_scatter(ctx, g_next, m, e_u, v_workers, vhat_workers, beta1, beta2, ef_ratio, true, idx, k_sel));
-        else
-            SAMS_TRY(enqueue_head_pa(ctx, g_next, m, e_u, v_workers, vhat_workers, beta1, beta2, ef_ratio));
-    }
+    if (!g_next) return enqueue_tail_only(ctx, e_u, x, idx, delta, k_sel, lr);
+    if (!head_can_fuse(ctx))
+        return enqueue_update(ctx, g_next, m, e_u, v_workers, vhat_workers, x, idx, delta, k_sel, beta1, beta2, lr, ef_ratio, true);
+    SAMS_TRY(enqueue_tail(ctx, x, idx, delta, k_sel, lr));
+    SAMS_TRY(enqueue_head_scatter(ctx, g_next, m, e_u, v_workers, vhat_workers, beta1, beta2, ef_ratio, true, idx, k_sel));
     return SAMS_OK;
 }
 

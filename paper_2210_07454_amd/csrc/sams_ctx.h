@@ -40,7 +40,7 @@ struct SelState {
 
 // kernels, for the optional per-kernel timing (sams_profile_*)
 enum KernelId {
-    KID_FILL = 0, KID_HASH_DUMP, KID_TAIL_X, KID_TAIL_ZERO_E, KID_HEAD, KID_SKETCH_ATOMIC, KID_REDUCE,
+    KID_FILL = 0, KID_HASH_DUMP, KID_TAIL, KID_TAIL_ZERO_E, KID_HEAD, KID_SKETCH_ATOMIC, KID_REDUCE,
     KID_ESTIMATE, KID_SEL_HIST, KID_SEL_FILTER, KID_SEL_COUNT, KID_SEL_WRITE,
     KID_GATHER, KID_PLAN_BUILD, KID_BIN_SCATTER, KID_BIN_ACCUMULATE, KID_SKETCH_LDS, KID_BIN_LOOKUP,
     KID_BIN_COLLECT, KID_EST_MEDIAN, KID_HEAD_SCATTER, KID_HEAD_PA, KID_HEAD_SPARSE_V, KID_SEL_SMALL, KID_SKETCH_PULL, KID_COUNT
@@ -332,12 +332,12 @@ __device__ __forceinline__ void sel_pick(SelState *st, uint32_t *hist, int digit
 int enqueue_fill_u32(sams_ctx *ctx, uint32_t *p, int64_t n, uint32_t val);
 int enqueue_hash_dump(sams_ctx *ctx, int32_t *bucket, int8_t *sign);
 // sams_update.hip
-int enqueue_tail(sams_ctx *ctx, float *e_u, float *x, const int32_t *idx, const float *delta,
-                 int64_t k_sel, float lr, bool zero_e);
-int enqueue_head(sams_ctx *ctx, const float *g, float *m, float *e_u, float *v, float *vhat,
-                 float beta1, float beta2, float rho);
-int enqueue_head_pa(sams_ctx *ctx, const float *g, float *m, float *e_u, float *v_w, float *vhat_w, float beta1,
-                    float beta2, float rho);
+// the whole update when the head is not fused with the first sketch pass (pa: Alg. 1, v and vhat are [n][d])
+int enqueue_update(sams_ctx *ctx, const float *g, float *m, float *e_u, float *v, float *vhat, float *x, const int32_t *idx,
+                   const float *delta, int64_t k_sel, float beta1, float beta2, float lr, float rho, bool pa);
+// the tail alone: with the bitmap of the index set for a fused head, and with e zeroed there when no head follows
+int enqueue_tail(sams_ctx *ctx, float *x, const int32_t *idx, const float *delta, int64_t k_sel, float lr);
+int enqueue_tail_only(sams_ctx *ctx, float *e_u, float *x, const int32_t *idx, const float *delta, int64_t k_sel, float lr);
 int enqueue_reduce(sams_ctx *ctx, const float *S_workers, float *S_mean);
 int enqueue_gather(sams_ctx *ctx, const float *u, const float *vhat, const int32_t *idx,
                    float *U_workers, float *delta);

@@ -16,14 +16,14 @@ __device__ __forceinline__ uint32_t mag_key(float x) { return __float_as_uint(x)
 
 // HIST: a selection follows, and the histogram of the first digit of |est| is taken here (as in k_bin_collect_median).
 template <int R, bool HIST>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(HIST ? 1024 : 256)
 k_estimate(const float *__restrict__ S, const float *__restrict__ vhat, float *__restrict__ est,
            HashParams hp, int64_t d, int64_t c, uint32_t *__restrict__ hist)
 {
     __shared__ uint32_t lh[HIST ? kHistBins : 1];
     const int64_t l = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if constexpr (HIST) {
-        for (int b = threadIdx.x; b < kHistBins; b += 256) lh[b] = 0;
+        for (int b = threadIdx.x; b < kHistBins; b += 1024) lh[b] = 0;
         __syncthreads();
     } else {
         if (l >= d) return;
@@ -43,7 +43,7 @@ k_estimate(const float *__restrict__ S, const float *__restrict__ vhat, float *_
     }
     if constexpr (HIST) {
         __syncthreads();
-        for (int b = threadIdx.x; b < kHistBins; b += 256)
+        for (int b = threadIdx.x; b < kHistBins; b += 1024)
             if (lh[b]) atomicAdd(&hist[b], lh[b]);
     }
 }
@@ -551,7 +551,7 @@ int enqueue_estimate(sams_ctx *ctx, const float *S_mean, const float *vhat, floa
 #define SAMS_CASE(R)                                                                                       \
     case R:                                                                                                \
         if (with_hist)                                                                                     \
-            SAMS_LAUNCH(ctx, KID_ESTIMATE, (k_estimate<R, true>), grid, block, S_mean, vhat, est, ctx->hp, \
+            SAMS_LAUNCH(ctx, KID_ESTIMATE, (k_estimate<R, true>), grid_for(ctx->d, 1024), 1024, S_mean, vhat, est, ctx->hp, \
                         ctx->d, ctx->c, sc->hist);                                                         \
         else                                                                                               \
             SAMS_LAUNCH(ctx, KID_ESTIMATE, (k_estimate<R, false>), grid, block, S_mean, vhat, est, ctx->hp, \

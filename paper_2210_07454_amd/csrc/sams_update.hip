@@ -12,81 +12,251 @@ namespace sams {
 // ------------------------------------------------------------------------------------------
 // stage 5: tail (finish iteration t) and head (start iteration t+1) of Alg. 2
 // ------------------------------------------------------------------------------------------
-// x[idx[q]] -= lr * delta[q]; mark idx[q] in the bitmap (I_t for the next head).  wordrank != null: idx is ascending
-// (as amsgrad_ef_update requires), so the rank of the first coordinate of every bitmap word that has one is its q
-__global__ void k_tail_x(const int32_t *__restrict__ idx, const float *__restrict__ delta, int64_t k,
-                         float lr, float *__restrict__ x, uint32_t *__restrict__ bitmap, uint32_t *__restrict__ wordrank)
+// The first position of the ascending idx[0..k) whose value is at least `want`, by one wavefront: 64 probes at a time, so
+// two to four dependent loads for up to 2^24 entries.
+__device__ __forceinline__ int64_t wave_lower_bound(const int32_t *__restrict__ idx, int64_t k, int64_t want)
 {
-    int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (q >= k) return;
-    uint32_t l = (uint32_t)idx[q];
-    x[l] = (x[l] - (lr * delta[q]));
-    atomicOr(&bitmap[l >> 5], 1u << (l & 31));
-    if (wordrank && (q == 0 || ((uint32_t)idx[q - 1] >> 5) != (l >> 5))) wordrank[l >> 5] = (uint32_t)q;
+    const int lane = threadIdx.x & (kWave - 1);
+    int64_t lo = 0, hi = k;                                          // the answer is in [lo, hi]
+    while (hi > lo) {
+        const int64_t step = (hi - lo + kWave - 1) / kWave, p = lo + lane * step;
+        const int below = __popcll(__ballot(p < hi && (int64_t)idx[p < hi ? p : hi - 1] < want));   // a prefix of the probes
+        if (below == 0) return lo;
+        const int64_t next = lo + below * step;                      // the first probe that is not below, if any
+        lo = lo + (below - 1) * step + 1;
+        hi = next < hi ? next : hi;
+    }
+    return lo;
 }
 
-// e[i][idx[q]] = 0 (only needed when no head follows; otherwise the head reads the bitmap)
-__global__ void k_tail_zero_e(const int32_t *__restrict__ idx, int64_t k, int32_t n, int64_t d,
-                              float *__restrict__ e)
+// range[0..2) (LDS) = positions of the index set's members in [l0, l1); complete after the next barrier.  The first two
+// wavefronts search, one bound each.
+__device__ __forceinline__ void member_range(const int32_t *__restrict__ idx, int64_t k, int64_t l0, int64_t l1, int64_t *range)
+{
+    const int wave = threadIdx.x / kWave;
+    if (wave < 2) {
+        const int64_t at = wave_lower_bound(idx, k, wave == 0 ? l0 : l1);
+        if ((threadIdx.x & (kWave - 1)) == 0) range[wave] = at;
+    }
+}
+
+// The tail for a head that reads the bitmap of I_t (the fused ones): a workgroup has 256 bitmap words, finds their
+// members in the ascending idx, updates x there and writes the words whole -- no clearing pass, no atomics on memory.
+// wordrank != null: also the rank in idx of the first member of every word that has one.
+__global__ void __launch_bounds__(256)
+k_tail(const int32_t *__restrict__ idx, const float *__restrict__ delta, int64_t k, int64_t words, float lr,
+       float *__restrict__ x, uint32_t *__restrict__ bitmap, uint32_t *__restrict__ wordrank)
+{
+    __shared__ uint32_t bits[256];
+    __shared__ int64_t range[2];
+    const int t = threadIdx.x;
+    const int64_t w0 = blockIdx.x * (int64_t)256;
+    bits[t] = 0;
+    member_range(idx, k, w0 * 32, (w0 + 256) * 32, range);
+    __syncthreads();
+    for (int64_t q = range[0] + t; q < range[1]; q += 256) {
+        const int32_t l = idx[q];
+        x[l] = (x[l] - (lr * delta[q]));
+        atomicOr(&bits[(l >> 5) - (int)w0], 1u << (l & 31));
+        if (wordrank && (q == 0 || (idx[q - 1] >> 5) != (l >> 5))) wordrank[l >> 5] = (uint32_t)q;
+    }
+    __syncthreads();
+    if (w0 + t < words) bitmap[w0 + t] = bits[t];
+}
+
+// the tail when no head follows: x, and e[i][idx[q]] = 0
+__global__ void k_tail_zero_e(const int32_t *__restrict__ idx, const float *__restrict__ delta, int64_t k, int32_t n, int64_t d,
+                              float lr, float *__restrict__ x, float *__restrict__ e)
 {
     int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (q >= k) return;
     int64_t l = idx[q];
+    x[l] = (x[l] - (lr * delta[q]));
     for (int32_t i = 0; i < n; ++i) e[(int64_t)i * d + l] = 0.0f;
 }
 
-// Dense head.  One thread owns VEC consecutive coordinates and walks the n workers, so that the
-// worker sum of g needed for h (only on I_t) comes for free and in ascending worker order.
-template <int VEC>
-__global__ void __launch_bounds__(256)
-k_head(const float *__restrict__ g, float *__restrict__ m, float *__restrict__ e,
-       float *__restrict__ v, float *__restrict__ vhat, const uint32_t *__restrict__ bitmap,
-       int32_t n, int64_t d, float beta1, float omb1, float beta2, float omb2, float rho)
+// Tail and dense head in one launch, when the head is not fused with the first sketch pass.  Two kinds of workgroups:
+//   dense   1024 coordinates of `wchunk` workers: m and u (over e), e taken as zero on I_t, whose members it finds in the
+//           ascending idx; the workgroups of the first workers also have v and vhat off I_t.  Alg. 1 (PA): v and
+//           vhat are per worker, and u = m / sqrt(vhat) + rho e.
+//   sparse  the members of I_t: x, and (Alg. 2) h from all workers' g in ascending worker order, v, vhat; 32 lanes
+//           share a member from kWideMinWorkers workers on (a chain of n memory latencies otherwise)
+// Nothing that one workgroup writes is read by another.  VEC: 4 = 16-byte accesses (d a multiple of 4), 1 = a thread's
+// four coordinates lie 256 apart.  The next worker's values are fetched while one is computed; the first ones while
+// the members are searched for.
+struct UpdateArgs {
+    const float *g;
+    float *m, *e, *v, *vhat, *x;
+    const int32_t *idx;
+    const float *delta;
+    int64_t k, d, ntile;
+    int32_t n, wchunk, ny;
+    float beta1, omb1, beta2, omb2, rho, lr;
+};
+
+__device__ __forceinline__ void update_members(const UpdateArgs &a, int64_t block, bool pa, float *vals)
 {
-    int64_t l0 = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) * VEC;
-    if (l0 >= d) return;
-    uint32_t selbits;
-    if (VEC == 4) {
-        selbits = (bitmap[l0 >> 5] >> (l0 & 31)) & 0xFu;
-    } else {
-        selbits = (bitmap[l0 >> 5] >> (l0 & 31)) & 1u;
+    const int t = threadIdx.x;
+    if (pa || a.n < kWideMinWorkers) {
+        const int64_t q = block * 256 + t;
+        if (q >= a.k) return;
+        const int64_t l = a.idx[q];
+        a.x[l] = (a.x[l] - (a.lr * a.delta[q]));
+        if (pa) return;
+        float gs = 0.0f;
+        for (int32_t i0 = 0; i0 < a.n; i0 += 8) {                    // eight loads in flight, added in worker order
+            float val[8];
+#pragma unroll
+            for (int z = 0; z < 8; ++z) val[z] = a.g[(int64_t)(i0 + z < a.n ? i0 + z : a.n - 1) * a.d + l];
+#pragma unroll
+            for (int z = 0; z < 8; ++z)
+                if (i0 + z < a.n) gs = (i0 + z == 0) ? val[z] : (gs + val[z]);
+        }
+        const float h = (gs / (float)a.n);
+        const float vv = ((a.beta2 * a.v[l]) + (a.omb2 * (h * h)));
+        a.v[l] = vv;
+        if (vv > a.vhat[l]) a.vhat[l] = vv;
+        return;
     }
-    float gs[VEC];
-    for (int32_t i = 0; i < n; ++i) {
-        int64_t off = (int64_t)i * d + l0;
-        float gv[VEC], mv[VEC], ev[VEC];
+    const int ql = t >> 5, wl = t & 31;
+    const int64_t q = block * kWideCoords + ql;
+    const int64_t l = q < a.k ? a.idx[q] : 0;
+    float gs = 0.0f;
+    for (int32_t i0 = 0; i0 < a.n; i0 += 256) {                      // 256 workers at a time through LDS [8][256]
+        const int32_t lim = a.n - i0 < 256 ? a.n - i0 : 256;
+        if (q < a.k)
+            for (int32_t i = wl; i < lim; i += 32) vals[ql * 256 + i] = a.g[(int64_t)(i0 + i) * a.d + l];
+        __syncthreads();
+        if (wl == 0)
+            for (int32_t i = 0; i < lim; ++i) gs = (i0 + i == 0) ? vals[ql * 256] : (gs + vals[ql * 256 + i]);
+        __syncthreads();
+    }
+    if (q < a.k && wl == 0) {
+        a.x[l] = (a.x[l] - (a.lr * a.delta[q]));
+        const float h = (gs / (float)a.n);
+        const float vv = ((a.beta2 * a.v[l]) + (a.omb2 * (h * h)));
+        a.v[l] = vv;
+        if (vv > a.vhat[l]) a.vhat[l] = vv;
+    }
+}
+
+template <int VEC, bool PA>
+__global__ void __launch_bounds__(256)
+k_update(UpdateArgs a)
+{
+    __shared__ float vals[kWideCoords * 256];
+    __shared__ uint32_t bits[32];
+    __shared__ int64_t range[2];
+    const int t = threadIdx.x;
+    const int64_t dense = a.ntile * a.ny;
+    if (blockIdx.x >= dense) {
+        update_members(a, (int64_t)blockIdx.x - dense, PA, vals);
+        return;
+    }
+    const int64_t l0 = (blockIdx.x % a.ntile) * 1024;
+    const int32_t y = (int32_t)(blockIdx.x / a.ntile);
+    const int32_t i0 = y * a.wchunk, i1 = i0 + a.wchunk < a.n ? i0 + a.wchunk : a.n;
+    // this thread's coordinates: l0 + at(z), z < 4
+    auto at = [&](int z) { return VEC == 4 ? t * 4 + z : t + 256 * z; };
+    auto in = [&](int z) { return l0 + at(z) < a.d; };
+    auto load = [&](const float *p, float *o) {
         if (VEC == 4) {
-            float4 a = *reinterpret_cast<const float4 *>(g + off);
-            float4 b = *reinterpret_cast<const float4 *>(m + off);
-            float4 cc = *reinterpret_cast<const float4 *>(e + off);
-            gv[0] = a.x; gv[1] = a.y; gv[2] = a.z; gv[3] = a.w;
-            mv[0] = b.x; mv[1] = b.y; mv[2] = b.z; mv[3] = b.w;
-            ev[0] = cc.x; ev[1] = cc.y; ev[2] = cc.z; ev[3] = cc.w;
+            float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (in(0)) q = *reinterpret_cast<const float4 *>(p + t * 4);
+            o[0] = q.x; o[1] = q.y; o[2] = q.z; o[3] = q.w;
         } else {
-            gv[0] = g[off]; mv[0] = m[off]; ev[0] = e[off];
+#pragma unroll
+            for (int z = 0; z < 4; ++z) o[z] = in(z) ? p[t + 256 * z] : 0.f;
+        }
+    };
+    auto store = [&](float *p, const float *o) {
+        if (VEC == 4) {
+            if (in(0)) *reinterpret_cast<float4 *>(p + t * 4) = make_float4(o[0], o[1], o[2], o[3]);
+        } else {
+#pragma unroll
+            for (int z = 0; z < 4; ++z)
+                if (in(z)) p[t + 256 * z] = o[z];
+        }
+    };
+    constexpr int A = PA ? 5 : 3;                                    // g, m, e (v, vhat) of the worker at hand and of the next
+    float cur[A][4], nxt[A][4];
+    auto load_worker = [&](int32_t i, float (&o)[A][4]) {
+        const int64_t off = (int64_t)i * a.d + l0;
+        load(a.g + off, o[0]);
+        load(a.m + off, o[1]);
+        load(a.e + off, o[2]);
+        if constexpr (PA) {
+            load(a.v + off, o[3]);
+            load(a.vhat + off, o[4]);
+        }
+    };
+    load_worker(i0, cur);
+    uint32_t sel = 0;                                                // bit z: the thread's coordinate z is in I_t
+    if (a.k > 0) {                                                   // uniform over the launch
+        if (t < 32) bits[t] = 0;
+        member_range(a.idx, a.k, l0, l0 + 1024, range);
+        __syncthreads();
+        for (int64_t q = range[0] + t; q < range[1]; q += 256) {
+            const int p = (int)(a.idx[q] - l0);
+            atomicOr(&bits[p >> 5], 1u << (p & 31));
+        }
+        __syncthreads();
+#pragma unroll
+        for (int z = 0; z < 4; ++z) sel |= ((bits[at(z) >> 5] >> (at(z) & 31)) & 1u) << z;
+    }
+    for (int32_t i = i0; i < i1; ++i) {
+        if (i + 1 < i1) load_worker(i + 1, nxt);
+        float mo[4], uo[4];
+#pragma unroll
+        for (int z = 0; z < 4; ++z) {
+            const float gv = cur[0][z];
+            const float mm = ((a.beta1 * cur[1][z]) + (a.omb1 * gv));
+            const float ein = ((sel >> z) & 1u) ? 0.0f : cur[2][z];  // e_t is zero on I_t
+            mo[z] = mm;
+            if constexpr (PA) {
+                const float v2 = ((a.beta2 * cur[3][z]) + (a.omb2 * (gv * gv)));
+                cur[3][z] = v2;
+                if (v2 > cur[4][z]) cur[4][z] = v2;
+                uo[z] = ((mm / sqrtf(cur[4][z])) + (a.rho * ein));
+            } else {
+                uo[z] = (mm + (a.rho * ein));
+            }
+        }
+        const int64_t off = (int64_t)i * a.d + l0;
+        store(a.m + off, mo);
+        store(a.e + off, uo);
+        if constexpr (PA) {
+            store(a.v + off, cur[3]);
+            store(a.vhat + off, cur[4]);
         }
 #pragma unroll
-        for (int t = 0; t < VEC; ++t) {
-            float mm = ((beta1 * mv[t]) + (omb1 * gv[t]));
-            float ein = ((selbits >> t) & 1u) ? 0.0f : ev[t];       // e_t is zero on I_t
-            mv[t] = mm;
-            ev[t] = (mm + (rho * ein));
-            gs[t] = (i == 0) ? gv[t] : (gs[t] + gv[t]);
-        }
-        if (VEC == 4) {
-            *reinterpret_cast<float4 *>(m + off) = make_float4(mv[0], mv[1], mv[2], mv[3]);
-            *reinterpret_cast<float4 *>(e + off) = make_float4(ev[0], ev[1], ev[2], ev[3]);
-        } else {
-            m[off] = mv[0]; e[off] = ev[0];
-        }
-    }
-    float fn = (float)n;
+        for (int q = 0; q < A; ++q)
 #pragma unroll
-    for (int t = 0; t < VEC; ++t) {
-        float h = ((selbits >> t) & 1u) ? (gs[t] / fn) : 0.0f;
-        float vv = (beta2 * v[l0 + t]) + (omb2 * (h * h));
-        v[l0 + t] = vv;
-        if (vv > vhat[l0 + t]) vhat[l0 + t] = vv;
+            for (int z = 0; z < 4; ++z) cur[q][z] = nxt[q][z];
+    }
+    if constexpr (!PA) {
+        if (y == 0) {                                                // v and vhat off I_t, where h = 0
+            float vv[4], vh[4];
+            load(a.v + l0, vv);
+            load(a.vhat + l0, vh);
+            bool moved = false;
+#pragma unroll
+            for (int z = 0; z < 4; ++z) {
+                vv[z] = ((a.beta2 * vv[z]) + (a.omb2 * (0.0f * 0.0f)));
+                if (vv[z] > vh[z]) { vh[z] = vv[z]; moved = true; }
+            }
+            if (sel == 0u) {
+                store(a.v + l0, vv);
+                if (moved) store(a.vhat + l0, vh);
+            } else {                                                 // the members belong to a sparse workgroup
+#pragma unroll
+                for (int z = 0; z < 4; ++z)
+                    if (in(z) && !((sel >> z) & 1u)) {
+                        a.v[l0 + at(z)] = vv[z];
+                        a.vhat[l0 + at(z)] = vh[z];
+                    }
+            }
+        }
     }
 }
 
@@ -102,7 +272,8 @@ __device__ __forceinline__ float4 ld4_stream(const float *p)
     return make_float4(t.x, t.y, t.z, t.w);
 }
 
-template <int VEC>
+// AHEAD: tables whose loads a thread has in flight
+template <int VEC, int AHEAD>
 __global__ void __launch_bounds__(256)
 k_reduce(const float *__restrict__ S_w, float *__restrict__ S_mean, int32_t n, int64_t rc)
 {
@@ -115,12 +286,12 @@ k_reduce(const float *__restrict__ S_w, float *__restrict__ S_mean, int32_t n, i
             for (int32_t i0 = 1; i0 < n; i0 += 8) {                  // eight tables' loads in flight, added in worker order
                 float4 b[8];
 #pragma unroll
-                for (int z = 0; z < 8; ++z) {
+                for (int z = 0; z < AHEAD; ++z) {
                     const int32_t i = (i0 + z < n) ? (i0 + z) : (n - 1);
                     b[z] = ld4_stream(S_w + (int64_t)i * rc + t);
                 }
 #pragma unroll
-                for (int z = 0; z < 8; ++z) {
+                for (int z = 0; z < AHEAD; ++z) {
                     if (i0 + z < n) {
                         acc.x = (acc.x + b[z].x);
                         acc.y = (acc.y + b[z].y);
@@ -132,7 +303,14 @@ k_reduce(const float *__restrict__ S_w, float *__restrict__ S_mean, int32_t n, i
             *reinterpret_cast<float4 *>(S_mean + t) = make_float4((acc.x / fn), (acc.y / fn), (acc.z / fn), (acc.w / fn));
         } else {
             float acc = S_w[t];
-            for (int32_t i = 1; i < n; ++i) acc = (acc + S_w[(int64_t)i * rc + t]);
+            for (int32_t i0 = 1; i0 < n; i0 += AHEAD) {
+                float b[AHEAD];
+#pragma unroll
+                for (int z = 0; z < AHEAD; ++z) b[z] = S_w[(int64_t)(i0 + z < n ? i0 + z : n - 1) * rc + t];
+#pragma unroll
+                for (int z = 0; z < AHEAD; ++z)
+                    if (i0 + z < n) acc = (acc + b[z]);
+            }
             S_mean[t] = (acc / fn);
         }
     }
@@ -197,97 +375,41 @@ k_gather_wide(const float *__restrict__ u, const float *__restrict__ vhat, const
     }
 }
 
-// Head of Alg. 1 (parameter averaging): per-worker second moments, u = m / sqrt(vhat) + rho * e.
-// Purely elementwise over the n*d entries; e is taken as zero on the recorded index set (bitmap over d).
-template <int VEC>
-__global__ void __launch_bounds__(256)
-k_head_pa(const float *__restrict__ g, float *__restrict__ m, float *__restrict__ e, float *__restrict__ vw,
-          float *__restrict__ vhw, const uint32_t *__restrict__ bitmap, int64_t d, float beta1, float omb1,
-          float beta2, float omb2, float rho)
+int enqueue_tail_only(sams_ctx *ctx, float *e_u, float *x, const int32_t *idx, const float *delta, int64_t k_sel, float lr)
 {
-    const int64_t l0 = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) * VEC;
-    if (l0 >= d) return;
-    const int64_t off = (int64_t)blockIdx.y * d + l0;
-    const uint32_t selbits = (bitmap[l0 >> 5] >> (l0 & 31)) & (VEC == 4 ? 0xFu : 1u);
-    float gv[VEC], mv[VEC], ev[VEC], vv[VEC], vh[VEC];
-    if (VEC == 4) {
-        const float4 a = *reinterpret_cast<const float4 *>(g + off), b = *reinterpret_cast<const float4 *>(m + off),
-                     cc = *reinterpret_cast<const float4 *>(e + off), p = *reinterpret_cast<const float4 *>(vw + off),
-                     q = *reinterpret_cast<const float4 *>(vhw + off);
-        gv[0] = a.x; gv[1] = a.y; gv[2] = a.z; gv[3] = a.w;
-        mv[0] = b.x; mv[1] = b.y; mv[2] = b.z; mv[3] = b.w;
-        ev[0] = cc.x; ev[1] = cc.y; ev[2] = cc.z; ev[3] = cc.w;
-        vv[0] = p.x; vv[1] = p.y; vv[2] = p.z; vv[3] = p.w;
-        vh[0] = q.x; vh[1] = q.y; vh[2] = q.z; vh[3] = q.w;
-    } else {
-        gv[0] = g[off]; mv[0] = m[off]; ev[0] = e[off]; vv[0] = vw[off]; vh[0] = vhw[off];
-    }
-#pragma unroll
-    for (int t = 0; t < VEC; ++t) {
-        const float mm = (beta1 * mv[t]) + (omb1 * gv[t]);
-        const float v2 = (beta2 * vv[t]) + (omb2 * (gv[t] * gv[t]));
-        const float ein = ((selbits >> t) & 1u) ? 0.0f : ev[t];
-        mv[t] = mm;
-        vv[t] = v2;
-        if (v2 > vh[t]) vh[t] = v2;
-        ev[t] = (mm / sqrtf(vh[t])) + (rho * ein);
-    }
-    if (VEC == 4) {
-        *reinterpret_cast<float4 *>(m + off) = make_float4(mv[0], mv[1], mv[2], mv[3]);
-        *reinterpret_cast<float4 *>(e + off) = make_float4(ev[0], ev[1], ev[2], ev[3]);
-        *reinterpret_cast<float4 *>(vw + off) = make_float4(vv[0], vv[1], vv[2], vv[3]);
-        *reinterpret_cast<float4 *>(vhw + off) = make_float4(vh[0], vh[1], vh[2], vh[3]);
-    } else {
-        m[off] = mv[0]; e[off] = ev[0]; vw[off] = vv[0]; vhw[off] = vh[0];
-    }
-}
-
-int enqueue_head_pa(sams_ctx *ctx, const float *g, float *m, float *e_u, float *v_w, float *vhat_w, float beta1,
-                    float beta2, float rho)
-{
-    const int64_t d = ctx->d;
-    const float omb1 = 1.0f - beta1, omb2 = 1.0f - beta2;
-    if ((d & 3) == 0) {
-        ProfScope ps(ctx, KID_HEAD_PA);
-        hipLaunchKernelGGL(k_head_pa<4>, dim3((unsigned)grid_for(d / 4, 256), (unsigned)ctx->n), dim3(256), 0,
-                           ctx->stream, g, m, e_u, v_w, vhat_w, ctx->bitmap, d, beta1, omb1, beta2, omb2, rho);
-    } else {
-        ProfScope ps(ctx, KID_HEAD_PA);
-        hipLaunchKernelGGL(k_head_pa<1>, dim3((unsigned)grid_for(d, 256), (unsigned)ctx->n), dim3(256), 0,
-                           ctx->stream, g, m, e_u, v_w, vhat_w, ctx->bitmap, d, beta1, omb1, beta2, omb2, rho);
-    }
+    if (k_sel == 0) return SAMS_OK;
+    SAMS_LAUNCH(ctx, KID_TAIL_ZERO_E, k_tail_zero_e, grid_for(k_sel, 256), 256, idx, delta, k_sel, ctx->n, ctx->d, lr, x, e_u);
     SAMS_HIP(hipGetLastError());
     return SAMS_OK;
 }
 
-int enqueue_tail(sams_ctx *ctx, float *e_u, float *x, const int32_t *idx, const float *delta,
-                 int64_t k_sel, float lr, bool zero_e)
+int enqueue_tail(sams_ctx *ctx, float *x, const int32_t *idx, const float *delta, int64_t k_sel, float lr)
 {
     const int64_t words = (ctx->d + 31) / 32;
-    SAMS_TRY(enqueue_fill_u32(ctx, ctx->bitmap, words, 0u));
-    if (k_sel > 0) {
-        SAMS_LAUNCH(ctx, KID_TAIL_X, k_tail_x, grid_for(k_sel, 256), 256, idx, delta, k_sel, lr, x,
-                    ctx->bitmap, ctx->wordrank);
-        if (zero_e)
-            SAMS_LAUNCH(ctx, KID_TAIL_ZERO_E, k_tail_zero_e, grid_for(k_sel, 256), 256, idx, k_sel,
-                        ctx->n, ctx->d, e_u);
-    }
+    SAMS_LAUNCH(ctx, KID_TAIL, k_tail, grid_for(words, 256), 256, idx, delta, k_sel, words, lr, x, ctx->bitmap, ctx->wordrank);
     SAMS_HIP(hipGetLastError());
     return SAMS_OK;
 }
 
-int enqueue_head(sams_ctx *ctx, const float *g, float *m, float *e_u, float *v, float *vhat,
-                 float beta1, float beta2, float rho)
+int enqueue_update(sams_ctx *ctx, const float *g, float *m, float *e_u, float *v, float *vhat, float *x, const int32_t *idx,
+                   const float *delta, int64_t k_sel, float beta1, float beta2, float lr, float rho, bool pa)
 {
-    const int64_t d = ctx->d;
-    const float omb1 = 1.0f - beta1, omb2 = 1.0f - beta2;
-    if ((d & 3) == 0) {
-        SAMS_LAUNCH(ctx, KID_HEAD, (k_head<4>), grid_for(d / 4, 256), 256, g, m, e_u, v, vhat,
-                    ctx->bitmap, ctx->n, d, beta1, omb1, beta2, omb2, rho);
-    } else {
-        SAMS_LAUNCH(ctx, KID_HEAD, (k_head<1>), grid_for(d, 256), 256, g, m, e_u, v, vhat, ctx->bitmap,
-                    ctx->n, d, beta1, omb1, beta2, omb2, rho);
-    }
+    const int64_t ntile = (ctx->d + 1023) / 1024;
+    // Enough workgroups for a few per compute unit: the workers of a tile are shared out when there are few tiles.  With
+    // per-worker second moments a worker is traffic enough for the search to be hidden (n = 8, d = 11.2 million: 589 us,
+    // 635 with all workers of a tile in one workgroup; the other way round without them, 107 and 96 us at 3 million).
+    int64_t ny = (2048 + ntile - 1) / ntile;
+    if (ny > ctx->n || pa) ny = ctx->n;
+    const int32_t wchunk = (int32_t)((ctx->n + ny - 1) / ny);
+    ny = (ctx->n + wchunk - 1) / wchunk;
+    const int64_t per_sparse = pa || ctx->n < kWideMinWorkers ? 256 : kWideCoords;
+    const int64_t blocks = ntile * ny + (k_sel + per_sparse - 1) / per_sparse;
+    const UpdateArgs a = {g, m, e_u, v, vhat, x, idx, delta, k_sel, ctx->d, ntile, ctx->n, wchunk, (int32_t)ny, beta1, 1.0f - beta1,
+                          beta2, 1.0f - beta2, rho, lr};
+    const bool vec = (ctx->d & 3) == 0;
+    ProfScope ps(ctx, pa ? KID_HEAD_PA : KID_HEAD);
+    const auto kernel = pa ? (vec ? k_update<4, true> : k_update<1, true>) : (vec ? k_update<4, false> : k_update<1, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, ctx->stream, a);
     SAMS_HIP(hipGetLastError());
     return SAMS_OK;
 }
@@ -295,10 +417,14 @@ int enqueue_head(sams_ctx *ctx, const float *g, float *m, float *e_u, float *v, 
 int enqueue_reduce(sams_ctx *ctx, const float *S_workers, float *S_mean)
 {
     const int64_t rc = (int64_t)ctx->r * ctx->c;
-    if ((rc & 3) == 0)
-        SAMS_LAUNCH(ctx, KID_REDUCE, k_reduce<4>, grid_for(rc / 4, 256, 1 << 16), 256, S_workers, S_mean, ctx->n, rc);
+    // one cell per thread for small tables: with four, a table of 2,000 cells would be two workgroups, each a chain of n / 8
+    // memory latencies (n = 100: 14 us)
+    if ((rc & 3) == 0 && rc >= 4 * 256 * 256)
+        SAMS_LAUNCH(ctx, KID_REDUCE, (k_reduce<4, 8>), grid_for(rc / 4, 256, 1 << 16), 256, S_workers, S_mean, ctx->n, rc);
+    else if (ctx->n <= 9)
+        SAMS_LAUNCH(ctx, KID_REDUCE, (k_reduce<1, 8>), grid_for(rc, 256, 1 << 16), 256, S_workers, S_mean, ctx->n, rc);
     else
-        SAMS_LAUNCH(ctx, KID_REDUCE, k_reduce<1>, grid_for(rc, 256, 1 << 16), 256, S_workers, S_mean, ctx->n, rc);
+        SAMS_LAUNCH(ctx, KID_REDUCE, (k_reduce<1, 32>), grid_for(rc, 256, 1 << 16), 256, S_workers, S_mean, ctx->n, rc);
     SAMS_HIP(hipGetLastError());
     return SAMS_OK;
 }
