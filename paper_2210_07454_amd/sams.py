@@ -26,6 +26,7 @@ EXPORTS = ["sams_create", "sams_destroy", "sams_scratch_bytes", "sams_preconditi
            "amsgrad_ef_update", "amsgrad_ef_update_pa", "topk_refine_static", "topk_refine_static_max_candidates"]
 
 _lib = None
+_F32, _I32 = torch.float32, torch.int32
 
 
 class SamsError(RuntimeError):
@@ -100,15 +101,20 @@ def sams_precondition_device_memory(fraction: float = 0.995) -> int:
 
 
 def _ptr(t, dtype=None, shape=None, name="tensor"):
+    """Device address of a tensor after the checks the C side cannot make (every call of a step goes through here for
+    each of its tensors, so the good case comes first and costs a few attribute look-ups)."""
     if t is None:
         return None
+    try:
+        if (t.dtype is dtype or dtype is None) and (shape is None or t.shape == shape) and t.is_cuda and t.is_contiguous():
+            return t.data_ptr()
+    except AttributeError:
+        pass
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous()):
         raise TypeError(f"{name}: expected a contiguous CUDA tensor")
     if dtype is not None and t.dtype != dtype:
         raise TypeError(f"{name}: expected {dtype}, got {t.dtype}")
-    if shape is not None and tuple(t.shape) != tuple(shape):
-        raise ValueError(f"{name}: expected shape {tuple(shape)}, got {tuple(t.shape)}")
-    return ctypes.c_void_p(t.data_ptr())
+    raise ValueError(f"{name}: expected shape {tuple(shape)}, got {tuple(t.shape)}")
 
 
 def _check(code, where):
@@ -139,6 +145,8 @@ class Context:
         if hp.shape != (r, 4):
             raise ValueError(f"hash_params: expected shape ({r}, 4)")
         self.d, self.n, self.r, self.c, self.k = d, n, r, c, k
+        self._nd, self._d, self._k, self._nk = (n, d), (d,), (k,), (n, k)      # the shapes the calls check
+        self._nrc, self._rc = (n, r, c), (r, c)
         self.stream = stream if stream is not None else torch.cuda.current_stream()
         self._h = ctypes.c_void_p()
         self._lib = lib
@@ -203,66 +211,64 @@ class Context:
                                         _ptr(sign, torch.int8, (self.r, self.d), "sign")), "sams_hash_dump")
 
     def sketch_accumulate(self, u, S_workers):
-        _check(self._lib.sketch_accumulate(
-            self._h, _ptr(u, torch.float32, (self.n, self.d), "u"),
-            _ptr(S_workers, torch.float32, (self.n, self.r, self.c), "S_workers")), "sketch_accumulate")
+        code = self._lib.sketch_accumulate(self._h, _ptr(u, _F32, self._nd, "u"), _ptr(S_workers, _F32, self._nrc, "S_workers"))
+        if code:
+            _check(code, "sketch_accumulate")
 
     def sketch_reduce(self, S_workers, S_mean):
-        _check(self._lib.sketch_reduce(
-            self._h, _ptr(S_workers, torch.float32, (self.n, self.r, self.c), "S_workers"),
-            _ptr(S_mean, torch.float32, (self.r, self.c), "S_mean")), "sketch_reduce")
+        code = self._lib.sketch_reduce(self._h, _ptr(S_workers, _F32, self._nrc, "S_workers"),
+                                       _ptr(S_mean, _F32, self._rc, "S_mean"))
+        if code:
+            _check(code, "sketch_reduce")
 
     def unsketch_topk(self, S_mean, vhat, idx, est_sel=None):
-        _check(self._lib.unsketch_topk(
-            self._h, _ptr(S_mean, torch.float32, (self.r, self.c), "S_mean"),
-            _ptr(vhat, torch.float32, (self.d,), "vhat"), _ptr(idx, torch.int32, (self.k,), "idx"),
-            _ptr(est_sel, torch.float32, (self.k,), "est_sel")), "unsketch_topk")
+        code = self._lib.unsketch_topk(self._h, _ptr(S_mean, _F32, self._rc, "S_mean"), _ptr(vhat, _F32, self._d, "vhat"),
+                                       _ptr(idx, _I32, self._k, "idx"), _ptr(est_sel, _F32, self._k, "est_sel"))
+        if code:
+            _check(code, "unsketch_topk")
 
     def unsketch_estimates(self, S_mean, vhat, est):
-        _check(self._lib.unsketch_estimates(
-            self._h, _ptr(S_mean, torch.float32, (self.r, self.c), "S_mean"),
-            _ptr(vhat, torch.float32, (self.d,), "vhat"), _ptr(est, torch.float32, (self.d,), "est")),
-            "unsketch_estimates")
+        code = self._lib.unsketch_estimates(self._h, _ptr(S_mean, _F32, self._rc, "S_mean"), _ptr(vhat, _F32, self._d, "vhat"),
+                                            _ptr(est, _F32, self._d, "est"))
+        if code:
+            _check(code, "unsketch_estimates")
 
     def gather_topk(self, u, vhat, idx, U_workers, delta):
-        _check(self._lib.gather_topk(
-            self._h, _ptr(u, torch.float32, (self.n, self.d), "u"), _ptr(vhat, torch.float32, (self.d,), "vhat"),
-            _ptr(idx, torch.int32, (self.k,), "idx"), _ptr(U_workers, torch.float32, (self.n, self.k), "U_workers"),
-            _ptr(delta, torch.float32, (self.k,), "delta")), "gather_topk")
+        code = self._lib.gather_topk(self._h, _ptr(u, _F32, self._nd, "u"), _ptr(vhat, _F32, self._d, "vhat"),
+                                     _ptr(idx, _I32, self._k, "idx"), _ptr(U_workers, _F32, self._nk, "U_workers"),
+                                     _ptr(delta, _F32, self._k, "delta"))
+        if code:
+            _check(code, "gather_topk")
 
     def topk_refine(self, idx_in, delta_in, k_out, idx_out, delta_out):
-        _check(self._lib.topk_refine(
-            self._h, _ptr(idx_in, torch.int32, (self.k,), "idx_in"), _ptr(delta_in, torch.float32, (self.k,), "delta_in"),
-            int(k_out), _ptr(idx_out, torch.int32, (k_out,), "idx_out"),
-            _ptr(delta_out, torch.float32, (k_out,), "delta_out")), "topk_refine")
+        code = self._lib.topk_refine(self._h, _ptr(idx_in, _I32, self._k, "idx_in"), _ptr(delta_in, _F32, self._k, "delta_in"),
+                                     int(k_out), _ptr(idx_out, _I32, (k_out,), "idx_out"),
+                                     _ptr(delta_out, _F32, (k_out,), "delta_out"))
+        if code:
+            _check(code, "topk_refine")
 
     def amsgrad_ef_update(self, g_next, m, e_u, v, vhat, x, idx, delta, k_sel, beta1, beta2, lr, ef_ratio=1.0):
-        nd = (self.n, self.d)
-        if k_sel:
-            if idx is None or delta is None or idx.numel() < k_sel or delta.numel() < k_sel:
-                raise ValueError("idx/delta shorter than k_sel")
-        _check(self._lib.amsgrad_ef_update(
-            self._h, _ptr(g_next, torch.float32, nd, "g_next"), _ptr(m, torch.float32, nd, "m"),
-            _ptr(e_u, torch.float32, nd, "e_u"), _ptr(v, torch.float32, (self.d,), "v"),
-            _ptr(vhat, torch.float32, (self.d,), "vhat"), _ptr(x, torch.float32, (self.d,), "x"),
-            _ptr(idx, torch.int32, None, "idx"), _ptr(delta, torch.float32, None, "delta"), int(k_sel),
-            float(beta1), float(beta2), float(lr), float(ef_ratio)), "amsgrad_ef_update")
-
-
-    def _update_pa(self, g_next, m, e_u, v_w, vhat_w, x, idx, delta, k_sel, beta1, beta2, lr, ef_ratio):
-        nd = (self.n, self.d)
-        _check(self._lib.amsgrad_ef_update_pa(
-            self._h, _ptr(g_next, torch.float32, nd, "g_next"), _ptr(m, torch.float32, nd, "m"),
-            _ptr(e_u, torch.float32, nd, "e_u"), _ptr(v_w, torch.float32, nd, "v_workers"),
-            _ptr(vhat_w, torch.float32, nd, "vhat_workers"), _ptr(x, torch.float32, (self.d,), "x"),
-            _ptr(idx, torch.int32, None, "idx"), _ptr(delta, torch.float32, None, "delta"), int(k_sel),
-            float(beta1), float(beta2), float(lr), float(ef_ratio)), "amsgrad_ef_update_pa")
+        if k_sel and (idx is None or delta is None or idx.numel() < k_sel or delta.numel() < k_sel):
+            raise ValueError("idx/delta shorter than k_sel")
+        nd, d = self._nd, self._d
+        code = self._lib.amsgrad_ef_update(
+            self._h, _ptr(g_next, _F32, nd, "g_next"), _ptr(m, _F32, nd, "m"), _ptr(e_u, _F32, nd, "e_u"),
+            _ptr(v, _F32, d, "v"), _ptr(vhat, _F32, d, "vhat"), _ptr(x, _F32, d, "x"), _ptr(idx, _I32, None, "idx"),
+            _ptr(delta, _F32, None, "delta"), int(k_sel), beta1, beta2, lr, ef_ratio)
+        if code:
+            _check(code, "amsgrad_ef_update")
 
     def amsgrad_ef_update_pa(self, g_next, m, e_u, v_workers, vhat_workers, x, idx, delta, k_sel, beta1, beta2, lr,
                              ef_ratio=1.0):
         if k_sel and (idx is None or delta is None or idx.numel() < k_sel or delta.numel() < k_sel):
             raise ValueError("idx/delta shorter than k_sel")
-        self._update_pa(g_next, m, e_u, v_workers, vhat_workers, x, idx, delta, k_sel, beta1, beta2, lr, ef_ratio)
+        nd = self._nd
+        code = self._lib.amsgrad_ef_update_pa(
+            self._h, _ptr(g_next, _F32, nd, "g_next"), _ptr(m, _F32, nd, "m"), _ptr(e_u, _F32, nd, "e_u"),
+            _ptr(v_workers, _F32, nd, "v_workers"), _ptr(vhat_workers, _F32, nd, "vhat_workers"), _ptr(x, _F32, self._d, "x"),
+            _ptr(idx, _I32, None, "idx"), _ptr(delta, _F32, None, "delta"), int(k_sel), beta1, beta2, lr, ef_ratio)
+        if code:
+            _check(code, "amsgrad_ef_update_pa")
 
 
 class Buffers:
