@@ -439,17 +439,26 @@ k_bin_scatter(const float *__restrict__ u, const uint16_t *__restrict__ srcp, co
     const int64_t tile = (int64_t)(blockIdx.x % kNumXcd) * per + slot / n;
     if (tile >= ntile) return;
     const int64_t l0 = tile << tile_log2;
-    const bool vec = (d & 3) == 0;
     {
-        const float *ui = u + (int64_t)i * d;
-        if (vec) {
-            for (int p = threadIdx.x * 4; p < L; p += blockDim.x * 4) {
-                float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (l0 + p < d) q = load_stream(reinterpret_cast<const float4 *>(ui + l0 + p));
-                *reinterpret_cast<float4 *>(tilebuf + p) = q;
+        // The worker's tile starts `mis` floats past a 16-byte boundary (not 0 when d is no multiple of 4): it is read from
+        // that boundary on, coordinate l0 + p to tile0[p].  The values around it belong to the tile's or the worker's
+        // neighbours; no slot names them.
+        const int64_t flat = (int64_t)i * d + l0;
+        const int mis = (int)(flat & 3);
+        const float *src = u + (flat - mis);
+        const int64_t lim = (int64_t)n * d - (flat - mis);           // floats of u from src on
+        const float *tile0 = tilebuf + mis;
+        const int top = (int)(L < d - l0 ? L : d - l0) + mis;
+        for (int p = threadIdx.x * 4; p < top; p += blockDim.x * 4) {
+            float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (p + 4 <= lim) {
+                q = load_stream(reinterpret_cast<const float4 *>(src + p));
+            } else {                                                 // the last, partial group of u
+                q.x = src[p];
+                if (p + 1 < lim) q.y = src[p + 1];
+                if (p + 2 < lim) q.z = src[p + 2];
             }
-        } else {
-            for (int p = threadIdx.x; p < L; p += blockDim.x) tilebuf[p] = (l0 + p < d) ? ui[l0 + p] : 0.f;
+            *reinterpret_cast<float4 *>(tilebuf + p) = q;
         }
         __syncthreads();
         for (int32_t j = rg.j0; j < rg.j0 + rg.rj; ++j) {
@@ -475,10 +484,10 @@ k_bin_scatter(const float *__restrict__ u, const uint16_t *__restrict__ srcp, co
                         const uint32_t s0 = packed.x & 0xffffu, s1 = packed.x >> 16, s2 = packed.y & 0xffffu,
                                        s3 = packed.y >> 16;
                         float4 v;
-                        v.x = (s0 == kSrcPad) ? 0.f : tilebuf[s0 & 0x7fffu]; v.x = (s0 & 0x8000u) ? -v.x : v.x;
-                        v.y = (s1 == kSrcPad) ? 0.f : tilebuf[s1 & 0x7fffu]; v.y = (s1 & 0x8000u) ? -v.y : v.y;
-                        v.z = (s2 == kSrcPad) ? 0.f : tilebuf[s2 & 0x7fffu]; v.z = (s2 & 0x8000u) ? -v.z : v.z;
-                        v.w = (s3 == kSrcPad) ? 0.f : tilebuf[s3 & 0x7fffu]; v.w = (s3 & 0x8000u) ? -v.w : v.w;
+                        v.x = (s0 == kSrcPad) ? 0.f : tile0[s0 & 0x7fffu]; v.x = (s0 & 0x8000u) ? -v.x : v.x;
+                        v.y = (s1 == kSrcPad) ? 0.f : tile0[s1 & 0x7fffu]; v.y = (s1 & 0x8000u) ? -v.y : v.y;
+                        v.z = (s2 == kSrcPad) ? 0.f : tile0[s2 & 0x7fffu]; v.z = (s2 & 0x8000u) ? -v.z : v.z;
+                        v.w = (s3 == kSrcPad) ? 0.f : tile0[s3 & 0x7fffu]; v.w = (s3 & 0x8000u) ? -v.w : v.w;
                         store_stream(reinterpret_cast<float4 *>(oj + at4[uu]), v);
                     }
                 }
@@ -621,7 +630,9 @@ k_head_scatter(HeadArgs ha, const uint16_t *__restrict__ srcp, const uint32_t *_
 // v' = beta2 v (+ 0), then v = v' + (1 - beta2) h^2; vhat = max(max(vhat, v'), v) = max(vhat, v) since v >= v'.
 // (Fetching the other workers' g for those coordinates inside worker 0's workgroup instead was tried: its
 // divergent, dependent gathers made the kernel 1.5x slower.)
-template <bool PA>
+// VEC: 4 = 16-byte accesses (d a multiple of 4); 1 = 4-byte accesses, a thread's coordinates kFusedThreads apart (the workers'
+// vectors start at any alignment then).
+template <bool PA, int VEC>
 __global__ void __launch_bounds__(kFusedThreads)
 k_head_scatter_w(HeadArgs ha, const uint16_t *__restrict__ srcp, const uint32_t *__restrict__ dst16,
                  const uint32_t *__restrict__ pbase, float *__restrict__ stg, int32_t n, RowGroup rg, int64_t d,
@@ -636,88 +647,162 @@ k_head_scatter_w(HeadArgs ha, const uint16_t *__restrict__ srcp, const uint32_t 
     if (slot / n >= per || tile >= ntile) return;
     const int64_t l0 = tile << tile_log2;
     const int64_t wbase = (int64_t)i * d + l0;
-    float4 gkeep[kFusedIters];                                       // g and the bitmap word of the positions with a
-    uint32_t wkeep[kFusedIters];                                     // member of I_{t-1}, for the compaction below
+    if constexpr (VEC == 4) {
+        float4 gkeep[kFusedIters];                                       // g and the bitmap word of the positions with a
+        uint32_t wkeep[kFusedIters];                                     // member of I_{t-1}, for the compaction below
 #pragma unroll
-    for (int it = 0; it < kFusedIters; ++it) { gkeep[it] = make_float4(0.f, 0.f, 0.f, 0.f); wkeep[it] = 0u; }
+        for (int it = 0; it < kFusedIters; ++it) { gkeep[it] = make_float4(0.f, 0.f, 0.f, 0.f); wkeep[it] = 0u; }
 #pragma unroll
-    for (int it = 0; it < kFusedIters; ++it) {
-        const int p = (it * kFusedThreads + (int)threadIdx.x) * 4;
-        if (p < L) {
-            float uv[4] = {0.f, 0.f, 0.f, 0.f};
-            if (l0 + p < d) {
-                const uint32_t bword = ha.bitmap[(l0 + p) >> 5];
-                const uint32_t selbits = (bword >> ((l0 + p) & 31)) & 0xFu;
-                const float4 a = load_stream(reinterpret_cast<const float4 *>(ha.g + wbase + p));
-                const float4 b = load_stream(reinterpret_cast<const float4 *>(ha.m + wbase + p));
-                const float4 cc = load_stream(reinterpret_cast<const float4 *>(ha.e + wbase + p));
-                const float gv[4] = {a.x, a.y, a.z, a.w}, mv[4] = {b.x, b.y, b.z, b.w}, ev[4] = {cc.x, cc.y, cc.z, cc.w};
-                float mo[4];
-                if constexpr (PA) {
-                    const float4 pv = load_stream(reinterpret_cast<const float4 *>(ha.v + wbase + p));
-                    const float4 ph = load_stream(reinterpret_cast<const float4 *>(ha.vhat + wbase + p));
-                    float vv[4] = {pv.x, pv.y, pv.z, pv.w}, vh[4] = {ph.x, ph.y, ph.z, ph.w};
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        const float mm = (ha.beta1 * mv[t]) + (ha.omb1 * gv[t]);
-                        const float v2 = (ha.beta2 * vv[t]) + (ha.omb2 * (gv[t] * gv[t]));
-                        const float ein = ((selbits >> t) & 1u) ? 0.0f : ev[t];          // e_t is zero on I_t
-                        mo[t] = mm;
-                        vv[t] = v2;
-                        if (v2 > vh[t]) vh[t] = v2;
-                        uv[t] = (mm / sqrtf(vh[t])) + (ha.rho * ein);
-                    }
-                    store_stream(reinterpret_cast<float4 *>(ha.v + wbase + p), make_float4(vv[0], vv[1], vv[2], vv[3]));
-                    store_stream(reinterpret_cast<float4 *>(ha.vhat + wbase + p), make_float4(vh[0], vh[1], vh[2], vh[3]));
-                } else {
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        const float mm = (ha.beta1 * mv[t]) + (ha.omb1 * gv[t]);
-                        const float ein = ((selbits >> t) & 1u) ? 0.0f : ev[t];          // e_t is zero on I_t
-                        mo[t] = mm;
-                        uv[t] = mm + (ha.rho * ein);
-                    }
-                    gkeep[it] = a;
-                    wkeep[it] = selbits ? bword : 0u;
-                    if (i == 0) {                                    // the decay of v, once per coordinate
-                        const float4 vin = *reinterpret_cast<const float4 *>(ha.v + l0 + p);
-                        const float4 hin = *reinterpret_cast<const float4 *>(ha.vhat + l0 + p);
-                        float vv[4] = {vin.x, vin.y, vin.z, vin.w}, vh[4] = {hin.x, hin.y, hin.z, hin.w};
-                        bool moved = false;
+        for (int it = 0; it < kFusedIters; ++it) {
+            const int p = (it * kFusedThreads + (int)threadIdx.x) * 4;
+            if (p < L) {
+                float uv[4] = {0.f, 0.f, 0.f, 0.f};
+                if (l0 + p < d) {
+                    const uint32_t bword = ha.bitmap[(l0 + p) >> 5];
+                    const uint32_t selbits = (bword >> ((l0 + p) & 31)) & 0xFu;
+                    const float4 a = load_stream(reinterpret_cast<const float4 *>(ha.g + wbase + p));
+                    const float4 b = load_stream(reinterpret_cast<const float4 *>(ha.m + wbase + p));
+                    const float4 cc = load_stream(reinterpret_cast<const float4 *>(ha.e + wbase + p));
+                    const float gv[4] = {a.x, a.y, a.z, a.w}, mv[4] = {b.x, b.y, b.z, b.w}, ev[4] = {cc.x, cc.y, cc.z, cc.w};
+                    float mo[4];
+                    if constexpr (PA) {
+                        const float4 pv = load_stream(reinterpret_cast<const float4 *>(ha.v + wbase + p));
+                        const float4 ph = load_stream(reinterpret_cast<const float4 *>(ha.vhat + wbase + p));
+                        float vv[4] = {pv.x, pv.y, pv.z, pv.w}, vh[4] = {ph.x, ph.y, ph.z, ph.w};
 #pragma unroll
                         for (int t = 0; t < 4; ++t) {
-                            vv[t] = (ha.beta2 * vv[t]);              // + (1 - beta2) * 0^2, exactly
-                            if (vv[t] > vh[t]) { vh[t] = vv[t]; moved = true; }
+                            const float mm = (ha.beta1 * mv[t]) + (ha.omb1 * gv[t]);
+                            const float v2 = (ha.beta2 * vv[t]) + (ha.omb2 * (gv[t] * gv[t]));
+                            const float ein = ((selbits >> t) & 1u) ? 0.0f : ev[t];          // e_t is zero on I_t
+                            mo[t] = mm;
+                            vv[t] = v2;
+                            if (v2 > vh[t]) vh[t] = v2;
+                            uv[t] = (mm / sqrtf(vh[t])) + (ha.rho * ein);
                         }
-                        *reinterpret_cast<float4 *>(ha.v + l0 + p) = make_float4(vv[0], vv[1], vv[2], vv[3]);
-                        if (moved) *reinterpret_cast<float4 *>(ha.vhat + l0 + p) = make_float4(vh[0], vh[1], vh[2], vh[3]);
+                        store_stream(reinterpret_cast<float4 *>(ha.v + wbase + p), make_float4(vv[0], vv[1], vv[2], vv[3]));
+                        store_stream(reinterpret_cast<float4 *>(ha.vhat + wbase + p), make_float4(vh[0], vh[1], vh[2], vh[3]));
+                    } else {
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+                            const float mm = (ha.beta1 * mv[t]) + (ha.omb1 * gv[t]);
+                            const float ein = ((selbits >> t) & 1u) ? 0.0f : ev[t];          // e_t is zero on I_t
+                            mo[t] = mm;
+                            uv[t] = mm + (ha.rho * ein);
+                        }
+                        gkeep[it] = a;
+                        wkeep[it] = selbits ? bword : 0u;
+                        if (i == 0) {                                    // the decay of v, once per coordinate
+                            const float4 vin = *reinterpret_cast<const float4 *>(ha.v + l0 + p);
+                            const float4 hin = *reinterpret_cast<const float4 *>(ha.vhat + l0 + p);
+                            float vv[4] = {vin.x, vin.y, vin.z, vin.w}, vh[4] = {hin.x, hin.y, hin.z, hin.w};
+                            bool moved = false;
+#pragma unroll
+                            for (int t = 0; t < 4; ++t) {
+                                vv[t] = (ha.beta2 * vv[t]);              // + (1 - beta2) * 0^2, exactly
+                                if (vv[t] > vh[t]) { vh[t] = vv[t]; moved = true; }
+                            }
+                            *reinterpret_cast<float4 *>(ha.v + l0 + p) = make_float4(vv[0], vv[1], vv[2], vv[3]);
+                            if (moved) *reinterpret_cast<float4 *>(ha.vhat + l0 + p) = make_float4(vh[0], vh[1], vh[2], vh[3]);
+                        }
+                    }
+                    store_stream(reinterpret_cast<float4 *>(ha.m + wbase + p), make_float4(mo[0], mo[1], mo[2], mo[3]));
+                    store_stream(reinterpret_cast<float4 *>(ha.e + wbase + p), make_float4(uv[0], uv[1], uv[2], uv[3]));
+                }
+                *reinterpret_cast<float4 *>(tilebuf + p) = make_float4(uv[0], uv[1], uv[2], uv[3]);
+            }
+        }
+        if constexpr (!PA) {
+            // g of this worker at the coordinates of I_{t-1}, at their rank in the index set: the rank of the word's
+            // first member plus the members of the word below the coordinate.  Kept out of the streaming loop above,
+            // whose loads a wait for the rank would hold up.
+            if (ha.gsel) {
+#pragma unroll
+                for (int it = 0; it < kFusedIters; ++it) {
+                    const uint32_t selbits4 = (wkeep[it] >> ((uint32_t)((it * kFusedThreads + (int)threadIdx.x) * 4) & 31u)) & 0xFu;
+                    if (selbits4) {
+                        const int p = (it * kFusedThreads + (int)threadIdx.x) * 4;
+                        const uint32_t r0 = ha.wordrank[(l0 + p) >> 5];
+                        const float gv[4] = {gkeep[it].x, gkeep[it].y, gkeep[it].z, gkeep[it].w};
+#pragma unroll
+                        for (int t = 0; t < 4; ++t)
+                            if ((selbits4 >> t) & 1u) {
+                                const uint32_t below = wkeep[it] & ((1u << (((uint32_t)p & 31u) + t)) - 1u);
+                                ha.gsel[(int64_t)i * ha.k_prev + r0 + __popc(below)] = gv[t];
+                            }
                     }
                 }
-                store_stream(reinterpret_cast<float4 *>(ha.m + wbase + p), make_float4(mo[0], mo[1], mo[2], mo[3]));
-                store_stream(reinterpret_cast<float4 *>(ha.e + wbase + p), make_float4(uv[0], uv[1], uv[2], uv[3]));
             }
-            *reinterpret_cast<float4 *>(tilebuf + p) = make_float4(uv[0], uv[1], uv[2], uv[3]);
         }
-    }
-    if constexpr (!PA) {
-        // g of this worker at the coordinates of I_{t-1}, at their rank in the index set: the rank of the word's
-        // first member plus the members of the word below the coordinate.  Kept out of the streaming loop above,
-        // whose loads a wait for the rank would hold up.
-        if (ha.gsel) {
+    } else {
+        constexpr int kIters = kFusedIters * 4, kBatch = 4;          // kBatch turns' loads are in flight together
+        const int lim = (int)(L < d - l0 ? L : d - l0);              // (addresses clamped into the tile: read, not used)
+        float gkeep[kIters];
+        uint32_t selm = 0;                                           // bit it: the thread's coordinate of that turn is in I_{t-1}
 #pragma unroll
-            for (int it = 0; it < kFusedIters; ++it) {
-                const uint32_t selbits4 = (wkeep[it] >> ((uint32_t)((it * kFusedThreads + (int)threadIdx.x) * 4) & 31u)) & 0xFu;
-                if (selbits4) {
-                    const int p = (it * kFusedThreads + (int)threadIdx.x) * 4;
-                    const uint32_t r0 = ha.wordrank[(l0 + p) >> 5];
-                    const float gv[4] = {gkeep[it].x, gkeep[it].y, gkeep[it].z, gkeep[it].w};
+        for (int it0 = 0; it0 < kIters; it0 += kBatch) {
+            float gv[kBatch], mv[kBatch], ev[kBatch], vv[kBatch], vh[kBatch];
+            uint32_t sel[kBatch];
 #pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        if ((selbits4 >> t) & 1u) {
-                            const uint32_t below = wkeep[it] & ((1u << (((uint32_t)p & 31u) + t)) - 1u);
-                            ha.gsel[(int64_t)i * ha.k_prev + r0 + __popc(below)] = gv[t];
-                        }
+            for (int z = 0; z < kBatch; ++z) {
+                const int p = (it0 + z) * kFusedThreads + (int)threadIdx.x;
+                const int64_t q = wbase + (p < lim ? p : lim - 1), l = l0 + (p < lim ? p : lim - 1);
+                gv[z] = __builtin_nontemporal_load(ha.g + q);
+                mv[z] = __builtin_nontemporal_load(ha.m + q);
+                ev[z] = __builtin_nontemporal_load(ha.e + q);
+                if constexpr (PA) {
+                    vv[z] = __builtin_nontemporal_load(ha.v + q);
+                    vh[z] = __builtin_nontemporal_load(ha.vhat + q);
+                } else if (i == 0) {
+                    vv[z] = ha.v[l];
+                    vh[z] = ha.vhat[l];
                 }
+                sel[z] = (ha.bitmap[l >> 5] >> (l & 31)) & 1u;
+            }
+#pragma unroll
+            for (int z = 0; z < kBatch; ++z) {
+                const int p = (it0 + z) * kFusedThreads + (int)threadIdx.x;
+                const float mm = (ha.beta1 * mv[z]) + (ha.omb1 * gv[z]);
+                const float ein = sel[z] ? 0.0f : ev[z];             // e_t is zero on I_t
+                float uv;
+                bool moved = PA;
+                if constexpr (PA) {
+                    vv[z] = (ha.beta2 * vv[z]) + (ha.omb2 * (gv[z] * gv[z]));
+                    if (vv[z] > vh[z]) vh[z] = vv[z];
+                    uv = (mm / sqrtf(vh[z])) + (ha.rho * ein);
+                } else {
+                    uv = mm + (ha.rho * ein);
+                    gkeep[it0 + z] = gv[z];
+                    if (i == 0) {                                    // the decay of v, once per coordinate
+                        vv[z] = ha.beta2 * vv[z];                    // + (1 - beta2) * 0^2, exactly
+                        if (vv[z] > vh[z]) { vh[z] = vv[z]; moved = true; }
+                    }
+                }
+                if (p < lim) {
+                    if constexpr (PA) {
+                        __builtin_nontemporal_store(vv[z], ha.v + wbase + p);
+                        __builtin_nontemporal_store(vh[z], ha.vhat + wbase + p);
+                    } else {
+                        selm |= sel[z] << (it0 + z);
+                        if (i == 0) {
+                            ha.v[l0 + p] = vv[z];
+                            if (moved) ha.vhat[l0 + p] = vh[z];
+                        }
+                    }
+                    __builtin_nontemporal_store(mm, ha.m + wbase + p);
+                    __builtin_nontemporal_store(uv, ha.e + wbase + p);
+                    tilebuf[p] = uv;
+                }
+            }
+        }
+        if constexpr (!PA) {
+            if (ha.gsel && selm) {
+#pragma unroll
+                for (int it = 0; it < kIters; ++it)
+                    if ((selm >> it) & 1u) {
+                        const int64_t l = l0 + it * kFusedThreads + (int)threadIdx.x;
+                        const uint32_t below = ha.bitmap[l >> 5] & ((1u << (l & 31)) - 1u);
+                        ha.gsel[(int64_t)i * ha.k_prev + ha.wordrank[l >> 5] + __popc(below)] = gkeep[it];
+                    }
             }
         }
     }
@@ -1295,10 +1380,15 @@ k_bin_collect_median(const float *__restrict__ lk, const uint16_t *__restrict__ 
     for (int it = 0; it < ITERS; ++it) {
         const int p = (it * kFusedThreads + (int)threadIdx.x) * 4;
         if (p < L && l0 + p < d) {
+            const bool whole = l0 + p + 3 < d;                       // not the last, partial group of the vector
             float vh[4] = {1.f, 1.f, 1.f, 1.f};
-            if (vhat) {
+            if (vhat && whole) {
                 const float4 q = *reinterpret_cast<const float4 *>(vhat + l0 + p);
                 vh[0] = q.x; vh[1] = q.y; vh[2] = q.z; vh[3] = q.w;
+            } else if (vhat) {
+#pragma unroll
+                for (int t = 0; t < 3; ++t)
+                    if (l0 + p + t < d) vh[t] = vhat[l0 + p + t];
             }
             float o[4];
 #pragma unroll
@@ -1308,9 +1398,15 @@ k_bin_collect_median(const float *__restrict__ lk, const uint16_t *__restrict__ 
                 for (int j = 0; j < R; ++j) col[j] = a[j][it][t];
                 const float med = median_of<R>(col);
                 o[t] = vhat ? (med / sqrtf(vh[t])) : med;
-                if (hist) atomicAdd(&lh[(__float_as_uint(o[t]) & 0x7fffffffu) >> 20], 1u);
+                if (hist && (whole || l0 + p + t < d)) atomicAdd(&lh[(__float_as_uint(o[t]) & 0x7fffffffu) >> 20], 1u);
             }
-            *reinterpret_cast<float4 *>(est + l0 + p) = make_float4(o[0], o[1], o[2], o[3]);
+            if (whole) {
+                *reinterpret_cast<float4 *>(est + l0 + p) = make_float4(o[0], o[1], o[2], o[3]);
+            } else {
+#pragma unroll
+                for (int t = 0; t < 3; ++t)
+                    if (l0 + p + t < d) est[l0 + p + t] = o[t];
+            }
         }
     }
     if (hist) {
@@ -1700,8 +1796,10 @@ int plan_create(sams_ctx *ctx, const Tunables &tun)
         if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_bin_scatter, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
         if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_head_scatter<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
         if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_head_scatter<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_head_scatter_w<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_head_scatter_w<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_head_scatter_w<false, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_head_scatter_w<true, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_head_scatter_w<false, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_head_scatter_w<true, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
 #define SAMS_CM(RR, IT)                                                                            \
     if (e == hipSuccess)                                                                           \
         e = hipFuncSetAttribute((const void *)k_bin_collect_median<RR, IT>,                        \
@@ -1830,8 +1928,7 @@ int plan_create(sams_ctx *ctx, const Tunables &tun)
         if (rc != SAMS_OK) rc = dev_alloc(ctx, (void **)&pl.stg, stg_bytes);
         // the median is fused when a thread can hold the row estimates of its coordinates and the staging
         // buffer can hold the looked-up values of all r rows; otherwise they go through rowest
-        pl.fused_median = tun.fuse_median && fused_median_iters(ctx->r, pl.tile_log2) > 0 && (ctx->d & 3) == 0 &&
-                          n * pl.stage_rows >= r;
+        pl.fused_median = tun.fuse_median && fused_median_iters(ctx->r, pl.tile_log2) > 0 && n * pl.stage_rows >= r;
         if (rc == SAMS_OK && !pl.fused_median) rc = dev_alloc(ctx, (void **)&pl.rowest, r * ctx->d * 4);
         if (rc != SAMS_OK) break;
     } while (0);
@@ -1865,7 +1962,7 @@ bool head_compacts_g(const sams_ctx *ctx) { return ctx->wordrank != nullptr && c
 
 bool head_can_fuse(const sams_ctx *ctx)
 {
-    return ctx->tun.fuse_head && ctx->plan.mode == PLAN_BINNED && !ctx->pull.kernel && (ctx->d & 3) == 0 && ctx->plan.tile_log2 <= 14;
+    return ctx->tun.fuse_head && ctx->plan.mode == PLAN_BINNED && !ctx->pull.kernel && (ctx->tun.fuse_head == 2 || (ctx->d & 3) == 0);
 }
 
 int enqueue_head_scatter(sams_ctx *ctx, const float *g, float *m, float *e_u, float *v, float *vhat,
@@ -1883,14 +1980,11 @@ int enqueue_head_scatter(sams_ctx *ctx, const float *g, float *m, float *e_u, fl
         const RowGroup rg = {0, pl.stage_rows, pl.stage_rows, ctx->r, pl.stage_ilv};
         if (ctx->tun.fuse_head == 2) {                                  // one workgroup per (tile, worker)
             const dim3 wgrid((unsigned)(per * kNumXcd * ctx->n));
-            if (pa)
-                hipLaunchKernelGGL(k_head_scatter_w<true>, wgrid, dim3(kFusedThreads), (size_t)(L * 4), ctx->stream,
-                                   ha, pl.srcp, pl.dst16, pl.pbase, pl.stg, ctx->n, rg, ctx->d, pl.tile_log2,
-                                   pl.ntile, pl.rowlen, pl.grp_log2);
-            else
-                hipLaunchKernelGGL(k_head_scatter_w<false>, wgrid, dim3(kFusedThreads), (size_t)(L * 4), ctx->stream,
-                                   ha, pl.srcp, pl.dst16, pl.pbase, pl.stg, ctx->n, rg, ctx->d, pl.tile_log2,
-                                   pl.ntile, pl.rowlen, pl.grp_log2);
+            const bool vec = (ctx->d & 3) == 0;
+            const auto kernel = pa ? (vec ? k_head_scatter_w<true, 4> : k_head_scatter_w<true, 1>)
+                                   : (vec ? k_head_scatter_w<false, 4> : k_head_scatter_w<false, 1>);
+            hipLaunchKernelGGL(kernel, wgrid, dim3(kFusedThreads), (size_t)(L * 4), ctx->stream, ha, pl.srcp, pl.dst16, pl.pbase,
+                               pl.stg, ctx->n, rg, ctx->d, pl.tile_log2, pl.ntile, pl.rowlen, pl.grp_log2);
         } else if (pa)
             hipLaunchKernelGGL(k_head_scatter<true>, grid, dim3(kFusedThreads), (size_t)(L * 4), ctx->stream, ha,
                                pl.srcp, pl.dst16, pl.pbase, pl.stg, ctx->n, rg, ctx->d, pl.tile_log2, pl.ntile,
@@ -1946,7 +2040,7 @@ int enqueue_sketch_planned(sams_ctx *ctx, const float *u, float *S_workers)
         if (j0 > 0 || pl.staged_u != u) {                            // not staged by a fused head: pass 1 now
             ProfScope ps(ctx, KID_BIN_SCATTER);
             hipLaunchKernelGGL(k_bin_scatter, dim3((unsigned)(per * kNumXcd * ctx->n)), dim3((unsigned)ctx->tun.scatter_threads),
-                               (size_t)(L * 4), ctx->stream, u, pl.srcp, pl.dst16, pl.pbase, pl.stg, ctx->n, rg,
+                               (size_t)(L * 4 + 16), ctx->stream, u, pl.srcp, pl.dst16, pl.pbase, pl.stg, ctx->n, rg,
                                ctx->d, pl.tile_log2, pl.ntile, pl.rowlen, pl.grp_log2);
         }
         SAMS_HIP(hipGetLastError());
