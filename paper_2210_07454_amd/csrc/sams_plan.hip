@@ -420,23 +420,34 @@ k_plan_records(const uint32_t *__restrict__ meta, uint32_t *__restrict__ rec, in
 // ------------------------------------------------------------------------------------------
 // pass 1: per tile, every worker's values to their positions in the row streams
 // ------------------------------------------------------------------------------------------
-// One workgroup per (tile, worker).  Workgroup ids are dealt round-robin to the 8 XCDs; consecutive tiles are
-// given to the same XCD so that neighbouring runs of a bin are written through one L2, and the n workers of
-// a tile sit there in consecutive slots so that the tile's plan metadata crosses the fabric once and comes
-// from that L2 for the other workers.  A thread owns 4 consecutive slots (always inside
+// One workgroup per (tile, worker), in this order: the tiles are dealt round-robin to the 8 XCDs, as the workgroups are;
+// an XCD takes its tiles in groups of `group`, and a group worker by worker.  At any time a few hundred consecutive tiles of
+// one or two workers are then being written, so that in each of a worker's row streams the runs under way lie next to each
+// other (with all workers of a tile side by side there are n times as many places under way, and the memory is slower:
+// pass 1 at d = 11.2 million, n = 8 0.59 -> 0.51 ms, fused with the head at 25.6 million, n = 16 3.87 -> 3.36 ms), and the
+// group's plan metadata is still in the XCD's L2 when the next worker needs it (see scatter_group).
+__device__ __forceinline__ void tile_and_worker(int64_t per, int32_t n, int32_t group, int64_t *tile, int32_t *worker)
+{
+    const int64_t slot = blockIdx.x / kNumXcd, g = slot / ((int64_t)group * n), in = slot % ((int64_t)group * n);
+    const int64_t size = per - g * group < group ? per - g * group : group;   // the last group may be smaller
+    *worker = (int32_t)(in / size);
+    *tile = (int64_t)(blockIdx.x % kNumXcd) + kNumXcd * (g * group + in % size);
+}
+
+// A thread owns 4 consecutive slots (always inside
 // one group of G >= 4 slots, hence one run): one 8-byte load of their sources, one 4-byte load of the group's
 // stream position, 4 LDS reads and one 16-byte store -- nothing depends on another global load.
 __global__ void __launch_bounds__(1024)
 k_bin_scatter(const float *__restrict__ u, const uint16_t *__restrict__ srcp, const uint32_t *__restrict__ dst16,
               const uint32_t *__restrict__ pbase, float *__restrict__ stg, int32_t n, RowGroup rg, int64_t d,
-              int tile_log2, int64_t ntile, int64_t rowlen, int gl)
+              int tile_log2, int64_t ntile, int64_t rowlen, int gl, int32_t group)
 {
     extern __shared__ float tilebuf[];
     const int L = 1 << tile_log2;
     const int64_t per = (ntile + kNumXcd - 1) / kNumXcd;
-    const int64_t slot = blockIdx.x / kNumXcd;
-    const int32_t i = (int32_t)(slot % n);
-    const int64_t tile = (int64_t)(blockIdx.x % kNumXcd) * per + slot / n;
+    int64_t tile;
+    int32_t i;
+    tile_and_worker(per, n, group, &tile, &i);
     if (tile >= ntile) return;
     const int64_t l0 = tile << tile_log2;
     {
@@ -621,9 +632,8 @@ k_head_scatter(HeadArgs ha, const uint16_t *__restrict__ srcp, const uint32_t *_
     }
 }
 
-// The same work with one workgroup per (tile, worker): the n workgroups of a tile sit on the same XCD in
-// consecutive slots and walk the tile's plan metadata at about the same time, so that it comes from HBM once
-// and from that XCD's L2 for the others, instead of being re-read through the fabric once per worker.
+// The same work with one workgroup per (tile, worker), in the order of k_bin_scatter: the plan metadata of a tile comes from
+// HBM for its first worker and from that XCD's L2 for the others, instead of through the fabric once per worker.
 // The second moments of Alg. 2 need the mean gradient over the workers, but only on I_{t-1}: worker 0's
 // workgroup decays v everywhere (the update with h = 0, which is what every other coordinate gets) and
 // k_head_sparse_v then adds the (1 - beta2) h^2 term on I_{t-1}.  Rounding is that of the one-step formula:
@@ -636,15 +646,15 @@ template <bool PA, int VEC>
 __global__ void __launch_bounds__(kFusedThreads)
 k_head_scatter_w(HeadArgs ha, const uint16_t *__restrict__ srcp, const uint32_t *__restrict__ dst16,
                  const uint32_t *__restrict__ pbase, float *__restrict__ stg, int32_t n, RowGroup rg, int64_t d,
-                 int tile_log2, int64_t ntile, int64_t rowlen, int gl)
+                 int tile_log2, int64_t ntile, int64_t rowlen, int gl, int32_t group)
 {
     extern __shared__ float tilebuf[];
     const int L = 1 << tile_log2;
     const int64_t per = (ntile + kNumXcd - 1) / kNumXcd;
-    const int64_t slot = blockIdx.x / kNumXcd;
-    const int32_t i = (int32_t)(slot % n);
-    const int64_t tile = (int64_t)(blockIdx.x % kNumXcd) * per + slot / n;
-    if (slot / n >= per || tile >= ntile) return;
+    int64_t tile;
+    int32_t i;
+    tile_and_worker(per, n, group, &tile, &i);
+    if (tile >= ntile) return;
     const int64_t l0 = tile << tile_log2;
     const int64_t wbase = (int64_t)i * d + l0;
     if constexpr (VEC == 4) {
@@ -1773,6 +1783,7 @@ int plan_create(sams_ctx *ctx, const Tunables &tun)
     pl.ntile = (ctx->d + L - 1) / L;
     pl.dpad = pl.ntile * L;
     const int64_t r = ctx->r, n = ctx->n, NB = pl.nbins;
+    pl.rows = ctx->r;
     if (pl.tile_log2 > 14 || NB > 8192) return SAMS_EINVAL;          // kSrcPad; LDS prefix in k_plan_place
     SAMS_TRY(dev_alloc(ctx, (void **)&pl.binbase, r * (NB + 1) * 4));
     SAMS_TRY(dev_alloc(ctx, (void **)&pl.pbase, r * (pl.ntile + 1) * 4));
@@ -1958,6 +1969,18 @@ int64_t plan_staging_words(const sams_ctx *ctx)
     return ctx->plan.stg ? (int64_t)ctx->n * ctx->plan.stage_rows * ctx->plan.rowlen : 0;
 }
 
+// Tiles of an XCD that pass 1 takes worker by worker (tile_and_worker): as many as have their plan metadata (2.25 bytes per
+// slot and row) in 3 MB, three quarters of the XCD's L2, but no more than 16 -- for 2^14 coordinates and five rows; with 64,
+// pass 1 with the head takes 8.0 instead of 7.2 ms at d = 124 million, with 24 of 2^13 3.40 instead of 3.36 at 25.6 million.  When the whole plan's metadata fits in half the 256 MB
+// Infinity Cache it comes from there, and groups of 64 are better (0.73 and 0.79 ms at 11.2 million).
+static int32_t scatter_group(const Plan &pl)
+{
+    const int64_t row_bytes = pl.rowlen * 2 + (pl.rowlen >> pl.grp_log2) * 4, all = row_bytes * pl.rows;
+    const int64_t per_tile = all / pl.ntile + 1, cached = all <= ((int64_t)128 << 20);
+    const int64_t want = (cached ? 12 : 3) * 1000000 / per_tile, most = cached ? 4096 : 16;
+    return (int32_t)(want < 1 ? 1 : (want > most ? most : want));
+}
+
 bool head_compacts_g(const sams_ctx *ctx) { return ctx->wordrank != nullptr && ctx->gsel != nullptr; }
 
 bool head_can_fuse(const sams_ctx *ctx)
@@ -1984,7 +2007,7 @@ int enqueue_head_scatter(sams_ctx *ctx, const float *g, float *m, float *e_u, fl
             const auto kernel = pa ? (vec ? k_head_scatter_w<true, 4> : k_head_scatter_w<true, 1>)
                                    : (vec ? k_head_scatter_w<false, 4> : k_head_scatter_w<false, 1>);
             hipLaunchKernelGGL(kernel, wgrid, dim3(kFusedThreads), (size_t)(L * 4), ctx->stream, ha, pl.srcp, pl.dst16, pl.pbase,
-                               pl.stg, ctx->n, rg, ctx->d, pl.tile_log2, pl.ntile, pl.rowlen, pl.grp_log2);
+                               pl.stg, ctx->n, rg, ctx->d, pl.tile_log2, pl.ntile, pl.rowlen, pl.grp_log2, scatter_group(pl));
         } else if (pa)
             hipLaunchKernelGGL(k_head_scatter<true>, grid, dim3(kFusedThreads), (size_t)(L * 4), ctx->stream, ha,
                                pl.srcp, pl.dst16, pl.pbase, pl.stg, ctx->n, rg, ctx->d, pl.tile_log2, pl.ntile,
@@ -2041,7 +2064,7 @@ int enqueue_sketch_planned(sams_ctx *ctx, const float *u, float *S_workers)
             ProfScope ps(ctx, KID_BIN_SCATTER);
             hipLaunchKernelGGL(k_bin_scatter, dim3((unsigned)(per * kNumXcd * ctx->n)), dim3((unsigned)ctx->tun.scatter_threads),
                                (size_t)(L * 4 + 16), ctx->stream, u, pl.srcp, pl.dst16, pl.pbase, pl.stg, ctx->n, rg,
-                               ctx->d, pl.tile_log2, pl.ntile, pl.rowlen, pl.grp_log2);
+                               ctx->d, pl.tile_log2, pl.ntile, pl.rowlen, pl.grp_log2, scatter_group(pl));
         }
         SAMS_HIP(hipGetLastError());
         SAMS_TRY(dispatch_acc(ctx, S_workers, rg, false));
