@@ -128,7 +128,8 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
  *   "sketch_path" 0 (default): the order-preserving path whenever c exceeds one LDS window, and
  *                 also for smaller tables while d <= 2^22 (one bin; one workgroup per (worker, row) walks the
  *                 vector); LDS atomics for small tables with larger d.  A table of 128 to 16384 buckets under a vector of
- *                 up to 2^26 coordinates keeps the order in another way, without staging, unless "tile_log2", "win_log2",
+ *                 up to 2^26 coordinates goes another way, by lists and without staging, which keeps the order up to d = 2^22
+ *                 (above, the vector may be cut into parts whose sums are added up, always in the same way), unless "tile_log2", "win_log2",
  *                 "chunk_log2", "acc_threads", "stage_rows" or "estimate_path" 2 ask for the binned path ("fuse_head"
  *                 then has nothing to stage and changes nothing); 1: one global atomic add per term
  *                 (no plan memory); 2: the order-preserving path always; 3: LDS atomics whenever c fits one
@@ -141,7 +142,7 @@ int sams_configure(const char *key, int value);
 int sams_destroy(sams_ctx *ctx);
 
 /* How this context carries out sketch_accumulate: 0 = one global atomic add per term, 1 = row by row in LDS
- * (c fits one window), 2 = the order-preserving path (binned, or by lists for narrow tables).  -1 for a NULL context. */
+ * (c fits one window) or by lists for parts of a long vector, 2 = the order-preserving path (binned, or by lists for narrow tables).  -1 for a NULL context. */
 int sams_sketch_mode(const sams_ctx *ctx);
 
 /* How the second pass of the binned path reads its metadata in this context (see "acc_wide"): 2 = every row through
@@ -206,8 +207,7 @@ int sams_hash_dump(sams_ctx *ctx, int32_t *bucket, int8_t *sign);
  *     S_workers[i][j][h_j(l)] += s_j(l) * u[i][l]      for all workers i, rows j, coordinates l.
  *   u          [n][d] in    the vectors to sketch (what amsgrad_ef_update leaves in e_u)
  *   S_workers  [n][r][c] out, overwritten (zeroed by the call, then accumulated)
- * On the order-preserving path (sams_sketch_mode() == 2: the default unless c fits one LDS window and d > 2^22, and then
- * too for tables of 128 to 16384 buckets up to d = 2^26)
+ * On the order-preserving path (sams_sketch_mode() == 2: the default unless c fits one LDS window and d > 2^22)
  * the terms of a bucket are added in ascending coordinate order, i.e. the result equals a sequential
  * loop over l bit for bit and is reproducible.
  * On the other paths (LDS atomics, or "sketch_path" = 1) the order is

@@ -18,7 +18,7 @@ static const char *const kKernelNames[KID_COUNT] = {
     "k_estimate", "k_sel_hist", "k_sel_filter", "k_sel_count", "k_sel_write",
     "k_gather", "k_plan_build", "k_bin_scatter", "k_bin_accumulate", "k_sketch_lds", "k_bin_lookup",
     "k_bin_collect", "k_est_median", "k_head_scatter", "k_head_pa", "k_head_sparse_v", "k_sel_small",
-    "k_sketch_pull"};
+    "k_sketch_pull", "k_pull_sum"};
 
 const char *kernel_name(int kid) { return (kid >= 0 && kid < KID_COUNT) ? kKernelNames[kid] : ""; }
 

@@ -27,6 +27,7 @@ extern int g_last_hip_error;
     } while (0)
 
 constexpr int kWave = 64;
+constexpr int64_t kOrderedSingleBinMaxD = (int64_t)1 << 22;     // largest d sketched in order when c fits one window
 constexpr int kHistBins = 2048;     // first radix digit of the selection: 11 bits, then 10 and 10 (kHistBins / 2 bins)
 constexpr int64_t kSelSmallMax = 1 << 16;   // keys up to which the selection is one launch after the first histogram
 
@@ -43,7 +44,7 @@ enum KernelId {
     KID_FILL = 0, KID_HASH_DUMP, KID_TAIL, KID_TAIL_ZERO_E, KID_HEAD, KID_SKETCH_ATOMIC, KID_REDUCE,
     KID_ESTIMATE, KID_SEL_HIST, KID_SEL_FILTER, KID_SEL_COUNT, KID_SEL_WRITE,
     KID_GATHER, KID_PLAN_BUILD, KID_BIN_SCATTER, KID_BIN_ACCUMULATE, KID_SKETCH_LDS, KID_BIN_LOOKUP,
-    KID_BIN_COLLECT, KID_EST_MEDIAN, KID_HEAD_SCATTER, KID_HEAD_PA, KID_HEAD_SPARSE_V, KID_SEL_SMALL, KID_SKETCH_PULL, KID_COUNT
+    KID_BIN_COLLECT, KID_EST_MEDIAN, KID_HEAD_SCATTER, KID_HEAD_PA, KID_HEAD_SPARSE_V, KID_SEL_SMALL, KID_SKETCH_PULL, KID_PULL_SUM, KID_COUNT
 };
 const char *kernel_name(int kid);
 
@@ -90,8 +91,11 @@ struct PullPlan {
     int32_t ntile;                // tiles of the vector
     int32_t nslice;               // slices of 64 buckets in a row
     int32_t per_win, nwin;        // slices per window, windows per row (a workgroup has one)
+    int32_t per_wave, group;      // slices per wavefront; words that a lane reads with one load
+    int32_t parts, per_part;      // parts of the vector that workgroups share out, tiles per part
     uint32_t *first;              // [streams + 1]       first group of words of a wavefront's lists
     uint32_t *lists;              // [groups][64][2 or 4]  words of two entries
+    float *part_sums;             // [parts][n][r][c], with more than one part
     int64_t list_bytes;
 };
 

@@ -38,7 +38,6 @@ constexpr int kAccDepth = 8;                // chunks in flight per workgroup of
 constexpr int kFusedThreads = 1024;          // kernels whose threads own the same 4-coordinate groups throughout
 constexpr int kFusedIters = 4;              // tiles of at most 2^14 coordinates = 4 float4 per thread
 constexpr int kMaxLdsBytes = 160 * 1024;      // LDS of one compute unit; the dynamic-LDS cap of every kernel here
-constexpr int64_t kOrderedSingleBinMaxD = (int64_t)1 << 22;     // largest d sketched in order when c fits one window
 
 constexpr uint16_t kSrcPad = 0x7fffu;          // slot source meaning "padding": tiles hold at most 2^14 coordinates
 constexpr uint32_t kMetaNextShift = 15;

@@ -3,22 +3,25 @@
 // The binned path (sams_plan.hip) writes every signed value to where its bucket's window will read it and reads it
 // back: 8 bytes of memory traffic per (worker, row, coordinate), and a window that few workgroups share when the table
 // is small.  A narrow table turns that round: the workgroups pull.  The vector is cut into tiles that fit in LDS; a
-// workgroup has one worker, one row and a range of up to 14 slices of 64 buckets (a window), walks the worker's tiles in
-// order, and every lane of a wavefront owns one bucket of its slice, with the bucket's sum in a register.  Which
+// workgroup has one worker, one row and a range of up to 56 slices of 64 buckets (a window), walks the worker's tiles in
+// order, and every lane of a wavefront owns one bucket of each of its one, two or four slices, with the sum in a register.  Which
 // coordinates of a tile a bucket takes is worked out once, at context creation: per (row, tile, slice) a list of steps,
 // each of 64 entries, one per lane -- the coordinate inside the tile and its sign --, padded with an entry that points at a
 // zero; the lists of a wavefront lie one after the other, as one stream.  A lane takes its entries in ascending
 // coordinate order, so the sums are those of a sequential loop over the coordinates, bit for bit (adding the padding's
 // zero changes nothing: a sum that starts at +0 is never -0; a value is added as fma(value, +-1, sum), which rounds
 // once, like the addition).  No atomics, no exchange between lanes, one barrier per tile.
+// Vectors of more than 2^22 coordinates, whose sums need not be in that order, may be cut into parts: workgroups of their
+// own make a table of every part, and the tables are added up part after part, always the same way.
 //
-// Cost: every workgroup reads its worker's whole vector (through the L2: the workgroups of one worker sit on one XCD and
-// walk in step), so the vector is read rows x windows times; the lists, which all workers share, once per worker.
+// Cost: every workgroup reads its worker's whole vector, or part (through the L2: the workgroups of one worker sit on one XCD
+// and walk in step), so the vector is read rows x windows times; the lists, which all workers share, once per worker.
 // Bound by what one compute unit takes in from the L2, 45 GB/s whether the lines hit or not (the same with two or four
 // loading wavefronts, one or two tiles ahead, always the same tiles); the adding alone takes a third of that time.
 // Measured on MI355X, both passes of the binned path before and this kernel now: d = 60,000, n = 50, 5 x 400: 98 and 11 us;
 // n = 100: 130 and 21 us; d = 65,536, n = 4, 5 x 2,048: 21 and 9 us; d = 431,003, n = 5, 4 x 9,001: 103 and 39 us;
-// d = 25.6 million, n = 4, 5 x 10,000: 8.5 and 2.4 ms.
+// d = 25.6 million, n = 4, 5 x 10,000: 8.5 and 1.14 ms (2.4 with one slice per wavefront and the vector in one part: twelve
+// windows that read it instead of three).
 #include <stdlib.h>
 
 #include "sams_ctx.h"
@@ -46,14 +49,25 @@ constexpr int kPullMaxList = 512;             // longest list of one bucket in o
 // ------------------------------------------------------------------------------------------
 // plan
 // ------------------------------------------------------------------------------------------
-// Where the lists are: wavefront w of the workgroup for (row, window) has slice win * per_win + w; its lists, one per tile,
-// are one stream.
+// Where the lists are: wavefront w of the workgroup for (row, window, part of the tiles) has the per_wave slices from
+// win * per_win + w * per_wave on; its lists, tile by tile and in a tile slice by slice, are one stream.
 struct PullOrder {
-    int32_t ntile, nslice, per_win, nwin, group;
+    int32_t ntile, nslice, per_win, nwin, group, per_wave, parts, per_part;
 };
+__host__ __device__ __forceinline__ int64_t stream_number(const PullOrder &po, int j, int win, int part, int wave)
+{
+    return (((int64_t)j * po.nwin + win) * po.parts + part) * (po.per_win / po.per_wave) + wave;
+}
 __device__ __forceinline__ int64_t list_number(const PullOrder &po, int j, int tile, int s)
 {
-    return (((int64_t)j * po.nwin + s / po.per_win) * po.per_win + s % po.per_win) * po.ntile + tile;
+    const int in = s % po.per_win;
+    return (stream_number(po, j, s / po.per_win, tile / po.per_part, in / po.per_wave) * po.per_part + tile % po.per_part) *
+               po.per_wave + in % po.per_wave;
+}
+// slices that have lists: those of every wavefront that has a slice at all (its others are empty: one group of padding)
+__host__ __device__ __forceinline__ int listed_slices(const PullOrder &po)
+{
+    return (po.nslice + po.per_wave - 1) / po.per_wave * po.per_wave;
 }
 
 // per (tile, row): groups of words of every list (the longest of its 64 columns, at least one group); *longest: the
@@ -62,7 +76,7 @@ __global__ void __launch_bounds__(1024)
 k_pull_count(HashParams hp, int64_t d, PullOrder po, uint32_t *__restrict__ len, uint32_t *__restrict__ longest)
 {
     extern __shared__ uint32_t cnt[];                                // [nslice * 64]
-    const int j = blockIdx.y, nslice = po.nslice;
+    const int j = blockIdx.y, nslice = listed_slices(po);
     const int64_t l0 = (int64_t)blockIdx.x * kPullTile;
     const int lim = d - l0 < kPullTile ? (int)(d - l0) : kPullTile;
     for (int b = threadIdx.x; b < nslice * kWave; b += 1024) cnt[b] = 0;
@@ -88,7 +102,7 @@ k_pull_count(HashParams hp, int64_t d, PullOrder po, uint32_t *__restrict__ len,
 __global__ void __launch_bounds__(1024)
 k_pull_place(HashParams hp, int64_t d, PullOrder po, const uint32_t *__restrict__ off, uint32_t *__restrict__ lists)
 {
-    const int nslice = po.nslice;
+    const int nslice = listed_slices(po);
     extern __shared__ uint32_t end[];                                // [nslice * 64] list ends, then kPullTile 16-bit entries
     __shared__ uint32_t part[16];
     uint16_t *ent = reinterpret_cast<uint16_t *>(end + nslice * kWave);
@@ -152,9 +166,10 @@ k_pull_place(HashParams hp, int64_t d, PullOrder po, const uint32_t *__restrict_
 struct PullArgs {
     const float *u;
     const uint32_t *lists, *first;    // first[stream]: the stream's first group of words; [streams]: the end
-    float *S;
+    float *S;                         // [parts][n][r][c]
     int64_t d, c, total;              // total = n * d
-    int32_t n, r, ntile, nslice, per_win, nwin;
+    int32_t n, r;
+    PullOrder po;
 };
 
 // 16 bytes per lane from memory straight to LDS: lane x's go to dst + 16 x bytes.  src: this lane's.
@@ -176,7 +191,8 @@ __device__ __forceinline__ void load_to_lds4(const float *src, float *dst)
 // tile before each list).  The adders' loop is a stream of groups: one load is issued per group, unconditionally and
 // straight into the registers that the loop carries, so that the compiler waits for exactly the oldest; the eight (four)
 // values of a group are read from LDS together and added in order.
-template <int W, int D>
+// PW: slices per wavefront, whose sums take turns in x[0].
+template <int W, int D, int PW>
 __global__ void __launch_bounds__(kPullThreads)
 k_sketch_pull(PullArgs a)
 {
@@ -184,9 +200,12 @@ k_sketch_pull(PullArgs a)
     const int t = threadIdx.x, lane = t & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(t / kWave);
     // workgroups are dealt round-robin to the 8 XCDs: consecutive (worker, row, window) triples to one XCD
     const int64_t per = (int64_t)gridDim.x / 8, q = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
-    const int32_t rw = a.r * a.nwin;
-    if (q >= (int64_t)a.n * rw) return;
-    const int32_t i = (int32_t)(q / rw), j = (int32_t)(q % rw) / a.nwin, win = (int32_t)(q % rw) % a.nwin;
+    const PullOrder &po = a.po;
+    const int32_t rw = a.r * po.nwin;                                // workgroups that walk the same tiles
+    if (q >= (int64_t)a.n * po.parts * rw) return;
+    const int32_t i = (int32_t)(q / rw) / po.parts, part = (int32_t)(q / rw) % po.parts;
+    const int32_t j = (int32_t)(q % rw) / po.nwin, win = (int32_t)(q % rw) % po.nwin;
+    const int32_t t0 = part * po.per_part, ntile = po.ntile - t0 < po.per_part ? po.ntile - t0 : po.per_part;
     // worker i's vector starts `mis` floats past a 16-byte boundary; the tiles are loaded from that boundary on
     const int64_t row0 = (int64_t)i * a.d;
     const int mis = (int)(row0 & 3);
@@ -205,7 +224,7 @@ k_sketch_pull(PullArgs a)
         // read by an adder, except for the up to three values put right below.
         auto load = [&](int32_t tl) {
             float *dst = buf + (tl % kPullBufs) * kPullBuf;
-            const int64_t at = row0 - mis + (int64_t)tl * kPullTile; // flat position in u of the buffer's start
+            const int64_t at = row0 - mis + (int64_t)(t0 + tl) * kPullTile;   // flat position in u of the buffer's start
 #pragma unroll
             for (int g = 0; g < kPullLoads; ++g) {
                 const int chunk = g * kPullLoaders + w;
@@ -216,30 +235,30 @@ k_sketch_pull(PullArgs a)
             load_to_lds4(a.u + (fa < last4 ? fa : last4), buf + kPullBufs * kPullBuf);
         };
         load(0);
-        if (a.ntile > 1) load(1);
-        for (int32_t tl = 0; tl < a.ntile; ++tl) {
+        if (ntile > 1) load(1);
+        for (int32_t tl = 0; tl < ntile; ++tl) {
             // tile tl is there; its share of a later tile, and tile tl + 1, may be under way
-            if (tl + 1 < a.ntile) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kPullLoads + 2) : "memory");
+            if (tl + 1 < ntile) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kPullLoads + 2) : "memory");
             else asm volatile("s_waitcnt vmcnt(1)" ::: "memory");
-            const int64_t at = row0 - mis + (int64_t)tl * kPullTile, f = a.total & ~(int64_t)3;
+            const int64_t at = row0 - mis + (int64_t)(t0 + tl) * kPullTile, f = a.total & ~(int64_t)3;
             if (f - at < kPullZero) {                                // u's last, partial group: in the last worker's last tile or
                 const int p = (int)(f - at);                         // the one before it, by the wavefront that loaded its chunk
                 if (p / 4 / kWave % kPullLoaders == w && lane < (int)(a.total & 3))
                     buf[(tl % kPullBufs) * kPullBuf + p + lane] = a.u[f + lane];
             }
             __syncthreads();                                         // the adders have done with tile tl - 1, whose buffer tl + 2 takes
-            if (tl + 2 < a.ntile) load(tl + 2);
+            if (tl + 2 < ntile) load(tl + 2);
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // the LDS is given back with nothing under way
         return;
     }
-    const int32_t s = win * a.per_win + wave;
-    if (wave >= a.per_win || s >= a.nslice) {                        // no slice: only the barriers
-        for (int32_t tl = 0; tl < a.ntile; ++tl) __syncthreads();
+    const int32_t s = win * po.per_win + wave * PW;
+    if (wave * PW >= po.per_win || s >= po.nslice) {                 // no slice: only the barriers
+        for (int32_t tl = 0; tl < ntile; ++tl) __syncthreads();
         return;
     }
     typedef uint32_t vecw __attribute__((ext_vector_type(W)));
-    const int64_t stream = ((int64_t)j * a.nwin + win) * a.per_win + wave;
+    const int64_t stream = stream_number(po, j, win, part, wave);
     const uint32_t g0 = a.first[stream], g1 = a.first[stream + 1];
     const vecw *src = reinterpret_cast<const vecw *>(a.lists) + (int64_t)g0 * kWave + lane;
     const int32_t ng = (int32_t)(g1 - g0);
@@ -250,7 +269,10 @@ k_sketch_pull(PullArgs a)
         __builtin_amdgcn_sched_barrier(0);
     }
     src += (int64_t)D * kWave;
-    float x = 0.f;
+    float x[PW];
+#pragma unroll
+    for (int p = 0; p < PW; ++p) x[p] = 0.f;
+    int32_t lists_left = PW;                                         // of the tile
     const char *base = reinterpret_cast<const char *>(buf + mis);
     int32_t left = kPullBufs;                                        // buffers until the first one again
     __syncthreads();                                                 // tile 0 is there
@@ -268,13 +290,20 @@ k_sketch_pull(PullArgs a)
                     sg[2 * p + 1] = __uint_as_float(0x3f800000u | (w[p] & 0x80000000u));
                 }
 #pragma unroll
-                for (int p = 0; p < 2 * W; ++p) x = __builtin_fmaf(v[p], sg[p], x);
-                if (__builtin_amdgcn_readfirstlane((int)w[0]) & 2) { // the tile's list ends
-                    if (m0 + z + 1 < ng) __syncthreads();            // the next tile is there
-                    base += kPullBuf * 4;
-                    if (--left == 0) {
-                        base -= kPullBufs * kPullBuf * 4;
-                        left = kPullBufs;
+                for (int p = 0; p < 2 * W; ++p) x[0] = __builtin_fmaf(v[p], sg[p], x[0]);
+                if (__builtin_amdgcn_readfirstlane((int)w[0]) & 2) { // the list ends
+                    const float y = x[0];                            // after a tile's PW lists x[0] is the first slice's again
+#pragma unroll
+                    for (int p = 0; p + 1 < PW; ++p) x[p] = x[p + 1];
+                    x[PW - 1] = y;
+                    if (--lists_left == 0) {
+                        lists_left = PW;
+                        if (m0 + z + 1 < ng) __syncthreads();        // the next tile is there
+                        base += kPullBuf * 4;
+                        if (--left == 0) {
+                            base -= kPullBufs * kPullBuf * 4;
+                            left = kPullBufs;
+                        }
                     }
                 }
             }
@@ -284,7 +313,28 @@ k_sketch_pull(PullArgs a)
         }
         src += (int64_t)D * kWave;
     }
-    if (s * kWave + lane < a.c) a.S[((int64_t)i * a.r + j) * a.c + s * kWave + lane] = x;
+    float *out = a.S + (((int64_t)part * a.n + i) * a.r + j) * a.c;
+#pragma unroll
+    for (int p = 0; p < PW; ++p)
+        if ((s + p) * kWave + lane < a.c) out[(s + p) * kWave + lane] = x[p];
+}
+
+// the parts' tables added up, part after part
+__global__ void __launch_bounds__(256)
+k_pull_sum(const float *__restrict__ part, float *__restrict__ S, int64_t cells, int32_t parts)
+{
+    const int64_t q = blockIdx.x * (int64_t)256 + threadIdx.x;
+    if (q >= cells) return;
+    float x = 0.f;
+    for (int32_t p0 = 0; p0 < parts; p0 += 8) {                      // eight loads in flight
+        float v[8];
+#pragma unroll
+        for (int z = 0; z < 8; ++z) v[z] = part[(int64_t)(p0 + z < parts ? p0 + z : parts - 1) * cells + q];
+#pragma unroll
+        for (int z = 0; z < 8; ++z)
+            if (p0 + z < parts) x = (x + v[z]);
+    }
+    S[q] = x;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -301,16 +351,37 @@ static bool pull_shape(const sams_ctx *ctx, const Tunables &tun, PullPlan &pp)
         return false;                                                // the caller asks for the binned path or for a shape of it
     if (ctx->c < 128 || ctx->c > (1 << 14) || ctx->d > ((int64_t)1 << 26) || (int64_t)ctx->n * ctx->d < 4) return false;
     pp.nslice = (int32_t)((ctx->c + kWave - 1) / kWave);
-    // Windows per row: at most one slice per adder, and as many as fit into the rounds (of one workgroup per compute unit, 256
-    // of them) that this takes; every round is as long as reading the whole vector.
+    pp.ntile = (int32_t)((ctx->d + kPullTile - 1) / kPullTile);
+    // A workgroup takes in a tile per `step`, one workgroup per compute unit: the cost is tiles per workgroup (and about
+    // twelve that starting and ending takes) times rounds of 256 workgroups.  Two or four slices per wavefront are fewer windows, and
+    // so fewer rounds; the vector is cut into parts where the order of the additions is not promised (d > 2^22).  Ties
+    // go to fewer slices and parts.
     const int64_t pairs = (int64_t)ctx->n * ctx->r;
-    const int64_t least = (pp.nslice + kPullAdders - 1) / kPullAdders, rounds = (pairs * least + 255) / 256;
-    int64_t nwin = rounds * 256 / pairs;
+    const int32_t most_parts = ctx->d > kOrderedSingleBinMaxD ? 128 : 1;
+    int64_t best = INT64_MAX, nwin = 1;
+    for (int32_t pw = 1; pw <= 4; pw *= 2) {
+        const int64_t least = (pp.nslice + kPullAdders * pw - 1) / (kPullAdders * pw);
+        for (int32_t parts = 1; parts <= most_parts; ++parts) {
+            const int64_t rounds = (pairs * least * parts + 255) / 256, cost = rounds * ((pp.ntile + parts - 1) / parts + 12);
+            if (cost >= best) continue;
+            best = cost;
+            pp.per_wave = pw;
+            pp.parts = parts;
+            nwin = parts == 1 ? rounds * 256 / pairs : least;        // as many windows as the rounds have room for
+        }
+    }
     if (nwin > pp.nslice) nwin = pp.nslice;
     pp.per_win = (int32_t)((pp.nslice + nwin - 1) / nwin);
+    pp.per_win = (pp.per_win + pp.per_wave - 1) / pp.per_wave * pp.per_wave;
     pp.nwin = (pp.nslice + pp.per_win - 1) / pp.per_win;
-    pp.ntile = (int32_t)((ctx->d + kPullTile - 1) / kPullTile);
+    pp.per_part = (pp.ntile + pp.parts - 1) / pp.parts;
+    pp.parts = (pp.ntile + pp.per_part - 1) / pp.per_part;           // none is empty
     return true;
+}
+
+static PullOrder pull_order(const PullPlan &pp)
+{
+    return {pp.ntile, pp.nslice, pp.per_win, pp.nwin, pp.group, pp.per_wave, pp.parts, pp.per_part};
 }
 
 // SAMS_OK with *done saying whether the context pulls; device memory that cannot be had means it does not
@@ -321,9 +392,15 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
     if (!pull_shape(ctx, tun, pp)) return SAMS_OK;
     // groups of eight steps where the lists of a tile are long (13308 / c entries on average, the longest of 64 decides)
     const int32_t group = ctx->c <= 4096 ? 4 : 2;
-    pp.kernel = group == 4 ? (const void *)k_sketch_pull<4, 6> : (const void *)k_sketch_pull<2, 8>;
-    const PullOrder po = {pp.ntile, pp.nslice, pp.per_win, pp.nwin, group};
-    const int64_t streams = (int64_t)ctx->r * pp.nwin * pp.per_win, lists = streams * pp.ntile;
+    pp.group = group;
+    const void *const kernels[2][3] = {
+        {(const void *)k_sketch_pull<2, 8, 1>, (const void *)k_sketch_pull<2, 8, 2>, (const void *)k_sketch_pull<2, 8, 4>},
+        {(const void *)k_sketch_pull<4, 6, 1>, (const void *)k_sketch_pull<4, 6, 2>, (const void *)k_sketch_pull<4, 6, 4>}};
+    pp.kernel = kernels[group == 4][pp.per_wave / 2];
+    const PullOrder po = pull_order(pp);
+    const int64_t streams = stream_number(po, ctx->r, 0, 0, 0), per_stream = (int64_t)pp.per_part * pp.per_wave,
+                  lists = streams * per_stream;
+    const int64_t part_bytes = pp.parts > 1 ? (int64_t)pp.parts * ctx->n * ctx->r * ctx->c * 4 : 0;
     uint32_t *longest = nullptr, *off = nullptr;                     // build-time only
     uint32_t *h_off = (uint32_t *)malloc((size_t)(lists + 1) * 4), *h_first = (uint32_t *)malloc((size_t)(streams + 1) * 4);
     int rc = SAMS_OK;
@@ -332,7 +409,7 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
             hipMalloc((void **)&pp.first, (size_t)(streams + 1) * 4) != hipSuccess)
             break;
         const dim3 grid((unsigned)pp.ntile, (unsigned)ctx->r);
-        const int lds_count = pp.nslice * kWave * 4, lds_place = lds_count + kPullTile * 2;
+        const int lds_count = listed_slices(po) * kWave * 4, lds_place = lds_count + kPullTile * 2;
         const int lds_max = kPullLds;                                // more than the other two kernels need
         hipError_t e = hipFuncSetAttribute((const void *)k_pull_count, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
         if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_pull_place, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
@@ -353,7 +430,7 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
         uint64_t run = 0;
         for (int64_t q = 0; q < lists; ++q) {
             const uint32_t len = h_off[q];
-            if (q % pp.ntile == 0) h_first[q / pp.ntile] = (uint32_t)run;
+            if (q % per_stream == 0) h_first[q / per_stream] = (uint32_t)run;
             h_off[q] = (uint32_t)run;
             run += len;
         }
@@ -364,6 +441,7 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
         h_off[lists] = (uint32_t)run;
         pp.list_bytes = (int64_t)(run * group + kPullSpare) * kWave * 4;
         if (hipMalloc((void **)&pp.lists, (size_t)pp.list_bytes) != hipSuccess) break;
+        if (part_bytes && hipMalloc((void **)&pp.part_sums, (size_t)part_bytes) != hipSuccess) break;
         e = hipMemcpyAsync(off, h_off, (size_t)(lists + 1) * 4, hipMemcpyHostToDevice, ctx->stream);
         if (e == hipSuccess) e = hipMemcpyAsync(pp.first, h_first, (size_t)(streams + 1) * 4, hipMemcpyHostToDevice, ctx->stream);
         if (e != hipSuccess) { g_last_hip_error = (int)e; rc = SAMS_EHIP; break; }
@@ -383,8 +461,8 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
     if (off) (void)hipFree(off);
     ctx->pull = pp;
     if (*done) {
-        ctx->plan.mode = PLAN_BINNED;                                // to the caller: the order-preserving path
-        ctx->scratch_bytes += pp.list_bytes + (streams + 1) * 4;
+        ctx->plan.mode = pp.parts == 1 ? PLAN_BINNED : PLAN_LDS_ROW; // to the caller: whether the order is the coordinates'
+        ctx->scratch_bytes += pp.list_bytes + (streams + 1) * 4 + part_bytes;
     } else {
         pull_destroy(ctx);
     }
@@ -395,19 +473,26 @@ void pull_destroy(sams_ctx *ctx)
 {
     if (ctx->pull.first) (void)hipFree(ctx->pull.first);
     if (ctx->pull.lists) (void)hipFree(ctx->pull.lists);
+    if (ctx->pull.part_sums) (void)hipFree(ctx->pull.part_sums);
     ctx->pull = PullPlan{};
 }
 
 int enqueue_sketch_pull(sams_ctx *ctx, const float *u, float *S_workers)
 {
     const PullPlan &pp = ctx->pull;
-    PullArgs a = {u, pp.lists, pp.first, S_workers, ctx->d, ctx->c, (int64_t)ctx->n * ctx->d, ctx->n, ctx->r, pp.ntile, pp.nslice,
-                  pp.per_win, pp.nwin};
-    const int64_t wgs = (int64_t)ctx->n * ctx->r * pp.nwin;
+    const int64_t cells = (int64_t)ctx->n * ctx->r * ctx->c;
+    PullArgs a = {u, pp.lists, pp.first, pp.parts > 1 ? pp.part_sums : S_workers, ctx->d, ctx->c, (int64_t)ctx->n * ctx->d, ctx->n,
+                  ctx->r, pull_order(pp)};
+    const int64_t wgs = (int64_t)ctx->n * ctx->r * pp.nwin * pp.parts;
     void *args[] = {&a};
-    ProfScope ps(ctx, KID_SKETCH_PULL);
-    SAMS_HIP(hipLaunchKernel(pp.kernel, dim3((unsigned)((wgs + 7) / 8 * 8)), dim3(kPullThreads), args,
-                             (size_t)kPullLds, ctx->stream));
+    {
+        ProfScope ps(ctx, KID_SKETCH_PULL);
+        SAMS_HIP(hipLaunchKernel(pp.kernel, dim3((unsigned)((wgs + 7) / 8 * 8)), dim3(kPullThreads), args,
+                                 (size_t)kPullLds, ctx->stream));
+    }
+    if (pp.parts > 1)
+        SAMS_LAUNCH(ctx, KID_PULL_SUM, k_pull_sum, grid_for(cells, 256), 256, pp.part_sums, S_workers, cells, pp.parts);
+    SAMS_HIP(hipGetLastError());
     return SAMS_OK;
 }
 

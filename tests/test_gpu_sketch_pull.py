@@ -14,6 +14,7 @@ SHAPES = [  # d, n, r, c
     (13_308, 2, 3, 128), (13_309, 3, 2, 129), (13_307, 3, 2, 191), (26_617, 5, 1, 16_384), (79_851, 3, 3, 10_007),
     (1, 5, 2, 128), (2, 4, 1, 200), (63, 5, 3, 4_096), (13_310, 90, 3, 400), (13_311, 130, 2, 1_999), (39_927, 67, 4, 2_040),
     (30_001, 70, 8, 9_000), (100_000, 2, 16, 5_000), (130_563, 1, 1, 16_383), (20_011, 300, 1, 700), (12_345, 150, 2, 16_000),
+    (40_001, 20, 16, 3_457), (53_231, 100, 3, 8_003), (26_615, 87, 3, 14_337),   # several slices per wavefront, ragged ones too
 ]
 
 
@@ -52,3 +53,35 @@ def test_a_hash_that_crowds_the_buckets_takes_the_binned_path():
 @pytest.mark.parametrize("c", [127, 16_385])
 def test_tables_outside_the_range_take_the_binned_path(c):
     assert "k_sketch_pull" not in check(33_000, 2, 2, c, inputs.hash_params(2, seed=4), 5)
+
+
+@pytest.mark.parametrize("d,n,r,c", [((1 << 22) + 1, 3, 2, 130), ((1 << 22) + 3, 1, 3, 4_097), (4_205_329, 2, 1, 16_384),
+                                     (4_205_327, 5, 4, 10_007), (8_516_119, 1, 1, 897)])
+def test_long_vectors_in_parts(d, n, r, c):
+    """Above 2^22 coordinates the vector may be cut into parts: exact where the partial sums are, reproducible, and within
+    the bound of sums in another order (a bucket of q terms: (q - 1) 2^-24 of the sum of their magnitudes, q about d / c)."""
+    from paper_2210_07454_amd import sams
+    rng = np.random.default_rng(d)
+    hp = inputs.hash_params(r, seed=d % 89)
+    whole = rng.integers(-3, 4, (n, d)).astype(np.float32)
+    u = (rng.standard_normal((n, d)) * 10.0 ** rng.uniform(-3, 1, d)).astype(np.float32)
+    S = torch.full((n, r, c), 9.0, device="cuda")
+    with sams.Context(d, n, r, c, 1, hp) as ctx:
+        ctx.sams_profile_enable(True)
+        ctx.sketch_accumulate(torch.from_numpy(whole).cuda(), S)
+        ctx.sams_profile_enable(False)
+        assert "k_sketch_pull" in ctx.sams_profile_read()
+        got = S.cpu().numpy()
+        o = Oracle("f32")
+        for i in range(n):
+            assert np.array_equal(got[i], o.sketch(whole[i], hp, c)), i
+        ctx.sketch_accumulate(torch.from_numpy(u).cuda(), S)
+        got = S.cpu().numpy()
+        ctx.sketch_accumulate(torch.from_numpy(u).cuda(), S)
+        assert np.array_equal(got.view(np.uint32), S.cpu().numpy().view(np.uint32))
+    o64 = Oracle("f64")
+    plus = np.stack([hp[:, 0], hp[:, 1], np.full(r, 2, np.uint32), np.zeros(r, np.uint32)], axis=1).astype(np.uint32)   # every sign +1
+    for i in range(n):
+        mass = o64.sketch(np.abs(u[i]).astype(np.float64), plus, c)
+        bound = 2.0 * d / c * 2.0 ** -24 * mass + 1e-37              # twice the average number of terms
+        assert np.all(np.abs(got[i] - o64.sketch(u[i].astype(np.float64), hp, c)) <= bound), i
