@@ -1,0 +1,30 @@
+"""One iteration on vectors whose length sits at the edges of the kernels' pieces -- a tile of pass 1 (2^14 coordinates),
+a tile of the update (1024), a workgroup of the tail (8192), groups of four --, so that most workers start off a 16-byte
+boundary; with as many workers as the update shares out over workgroups, and with tiles in more than one group."""
+import pytest
+
+from tests.test_gpu_random_shapes import DEFAULTS, one_iteration
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [  # d, n, r, c, k
+    (16_381, 3, 5, 40_000, 300), (16_383, 5, 4, 40_000, 16_383), (16_385, 4, 3, 40_000, 1), (16_386, 3, 2, 40_000, 4_000),
+    (32_771, 5, 1, 33_000, 8_192), (49_155, 2, 6, 50_000, 49_155),
+    (1_023, 17, 2, 20_000, 5), (1_025, 16, 3, 20_000, 1_025), (8_193, 33, 2, 17_000, 70), (7, 40, 2, 17_000, 3),
+    (2_900_003, 2, 16, 70_001, 900),                                 # tiles of 2^12: two groups per XCD, the last a small one
+]
+
+
+@pytest.mark.parametrize("fuse_head", [0, 2], ids=["separate-head", "fused-head-per-worker"])
+@pytest.mark.parametrize("d,n,r,c,k", SHAPES)
+def test_lengths_at_the_edges_of_tiles(d, n, r, c, k, fuse_head):
+    from paper_2210_07454_amd import sams
+    sams.load()
+    tun = dict(DEFAULTS, fuse_head=fuse_head, tile_log2=14 if 16_000 < d < 50_000 else 0)
+    try:
+        for key, val in tun.items():
+            sams.sams_configure(key, val)
+        assert one_iteration(sams, (d, n, r, c, k), seed=d % 97)
+    finally:
+        for key, val in DEFAULTS.items():
+            sams.sams_configure(key, val)
