@@ -48,6 +48,68 @@ k_estimate(const float *__restrict__ S, const float *__restrict__ vhat, float *_
     }
 }
 
+// The same for long vectors and tables that LDS holds at least a row of: a workgroup per compute unit keeps the first
+// `held` rows in LDS (the others are gathered as above) and walks the vector with a fixed step, so that a hash value follows
+// from the one before: y(l + step) = y(l) + (a step mod p), less p if that is not below it.  The bucket is y less
+// floor(y m / 2^32) c, and less c once more if that is not below c, with m = floor(2^32 / c): the quotient is at most one too
+// small for y < 2^31.
+constexpr int kEstLdsUnroll = 4;
+template <int R>
+__global__ void __launch_bounds__(1024)
+k_estimate_lds(const float *__restrict__ S, const float *__restrict__ vhat, float *__restrict__ est, HashParams hp, int64_t d,
+               int32_t c, uint32_t m, int32_t held)
+{
+    extern __shared__ float rows[];
+    const int t = threadIdx.x;
+    for (int q = t; q < held * c; q += 1024) rows[q] = S[q];
+    __syncthreads();
+    const int64_t step = (int64_t)gridDim.x * 1024;
+    uint32_t yb[R], ys[R], ab[R], as[R];
+    int64_t l = blockIdx.x * (int64_t)1024 + t;
+    if (l >= d) return;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        yb[j] = hash_y(hp.row[j].ah, hp.row[j].bh, (uint32_t)l);
+        ys[j] = hash_y(hp.row[j].as, hp.row[j].bs, (uint32_t)l);
+        ab[j] = hash_y(hp.row[j].ah, 0u, (uint32_t)step);
+        as[j] = hash_y(hp.row[j].as, 0u, (uint32_t)step);
+    }
+    auto less = [](uint32_t y, uint32_t by) { return y - by < y ? y - by : y; };   // y mod by for y < 2 by
+    for (; l < d; l += step * kEstLdsUnroll) {
+        float a[kEstLdsUnroll][R], vh[kEstLdsUnroll];
+#pragma unroll
+        for (int z = 0; z < kEstLdsUnroll; ++z) vh[z] = vhat ? vhat[l + z * step < d ? l + z * step : l] : 1.f;
+        uint32_t neg[kEstLdsUnroll] = {};                            // bit j: the row's sign; applied once all loads are under way
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            uint32_t b[kEstLdsUnroll];
+#pragma unroll
+            for (int z = 0; z < kEstLdsUnroll; ++z) {
+                b[z] = less(yb[j] - __umulhi(yb[j], m) * (uint32_t)c, (uint32_t)c);
+                neg[z] |= (ys[j] & 1u) << j;
+                yb[j] = less(yb[j] + ab[j], kP31);
+                ys[j] = less(ys[j] + as[j], kP31);
+            }
+            if (j < held) {                                          // uniform
+#pragma unroll
+                for (int z = 0; z < kEstLdsUnroll; ++z) a[z][j] = rows[j * c + (int)b[z]];
+            } else {
+#pragma unroll
+                for (int z = 0; z < kEstLdsUnroll; ++z) a[z][j] = S[(int64_t)j * c + b[z]];
+            }
+        }
+#pragma unroll
+        for (int z = 0; z < kEstLdsUnroll; ++z)
+#pragma unroll
+            for (int j = 0; j < R; ++j) a[z][j] = __uint_as_float(__float_as_uint(a[z][j]) ^ (((neg[z] >> j) & 1u) << 31));
+#pragma unroll
+        for (int z = 0; z < kEstLdsUnroll; ++z) {
+            const float med = median_of<R>(a[z]);
+            if (l + z * step < d) est[l + z * step] = vhat ? (med / sqrtf(vh[z])) : med;
+        }
+    }
+}
+
 // est[l] = median_j(rowest[j][l]) / sqrt(vhat[l]) from row estimates already in coordinate order
 template <int R>
 __global__ void __launch_bounds__(256)
@@ -511,6 +573,12 @@ k_sel_write(const SelState *__restrict__ st, SelList ls, int64_t ntile, int tpw,
     }
 }
 
+// k_estimate_lds where it pays for filling the LDS, against gathers of all rows: d = 25.6 million, 5 x 10,000 432 and 129 us,
+// 10 x 4,000 604 and 250 us, 5 x 32,000 (one row held) 440 and 402 us; d = 4 million, 5 x 10,000 72 and 30 us, 5 x 40,000
+// (one row held) 76 us both; d = 1 million, 5 x 400 8 us both, 5 x 10,000 20 and 12 us; d = 431,003, 4 x 9,001 7 and 10 us.
+constexpr int kEstLdsBytes = 160 * 1024;
+constexpr int64_t kEstLdsMinD = (int64_t)1 << 20;
+constexpr int kEstLdsMinShare = 5;                                   // at least a fifth of the rows held
 constexpr int64_t kGatherEstimateMaxTableBytes = 1 << 20, kGatherEstimateMaxD = (int64_t)1 << 22;
 int enqueue_estimate(sams_ctx *ctx, const float *S_mean, const float *vhat, float *est, const SelScratch *sc, bool *hist_done)
 {
@@ -534,6 +602,29 @@ int enqueue_estimate(sams_ctx *ctx, const float *S_mean, const float *vhat, floa
         SAMS_LAUNCH(ctx, KID_EST_MEDIAN, (k_est_median<R>), grid, block, ctx->plan.rowest, vhat, est, \
                     ctx->d);                                                                          \
         break;
+            SAMS_CASE(1) SAMS_CASE(2) SAMS_CASE(3) SAMS_CASE(4) SAMS_CASE(5) SAMS_CASE(6) SAMS_CASE(7)
+            SAMS_CASE(8) SAMS_CASE(9) SAMS_CASE(10) SAMS_CASE(11) SAMS_CASE(12) SAMS_CASE(13)
+            SAMS_CASE(14) SAMS_CASE(15) SAMS_CASE(16)
+#undef SAMS_CASE
+        default:
+            return SAMS_EINVAL;
+        }
+        SAMS_HIP(hipGetLastError());
+        return SAMS_OK;
+    }
+    const int64_t row_bytes = ctx->c * 4;
+    const int32_t held = (int32_t)(kEstLdsBytes / row_bytes < ctx->r ? kEstLdsBytes / row_bytes : ctx->r);
+    if (ctx->d >= kEstLdsMinD && ctx->c >= 2 && held * kEstLdsMinShare >= ctx->r && ctx->tun.estimate_path != 1) {
+        const uint32_t m = (uint32_t)(((uint64_t)1 << 32) / (uint64_t)ctx->c);
+        switch (ctx->r) {
+#define SAMS_CASE(R)                                                                                                             \
+    case R: {                                                                                                                    \
+        SAMS_HIP(hipFuncSetAttribute((const void *)k_estimate_lds<R>, hipFuncAttributeMaxDynamicSharedMemorySize, kEstLdsBytes)); \
+        ProfScope ps(ctx, KID_ESTIMATE);                                                                                         \
+        hipLaunchKernelGGL(k_estimate_lds<R>, dim3(grid_for(ctx->d, 1024, 256)), dim3(1024), (size_t)(held * row_bytes),        \
+                           ctx->stream, S_mean, vhat, est, ctx->hp, ctx->d, (int32_t)ctx->c, m, held);                           \
+        break;                                                                                                                   \
+    }
             SAMS_CASE(1) SAMS_CASE(2) SAMS_CASE(3) SAMS_CASE(4) SAMS_CASE(5) SAMS_CASE(6) SAMS_CASE(7)
             SAMS_CASE(8) SAMS_CASE(9) SAMS_CASE(10) SAMS_CASE(11) SAMS_CASE(12) SAMS_CASE(13)
             SAMS_CASE(14) SAMS_CASE(15) SAMS_CASE(16)
