@@ -94,7 +94,7 @@ struct PullPlan {
     int32_t per_wave, group;      // slices per wavefront; words that a lane reads with one load
     int32_t parts, per_part;      // parts of the vector that workgroups share out, tiles per part
     uint32_t *first;              // [streams + 1]       first group of words of a wavefront's lists
-    uint32_t *lists;              // [groups][64][2 or 4]  words of two entries
+    uint32_t *lists;              // [groups][64][group]  words of two entries, in groups of PullOrder::group
     float *part_sums;             // [parts][n][r][c], with more than one part
     int64_t list_bytes;
 };

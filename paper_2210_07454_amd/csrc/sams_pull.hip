@@ -20,7 +20,7 @@
 // loading wavefronts, one or two tiles ahead, always the same tiles); the adding alone takes a third of that time.
 // Measured on MI355X, both passes of the binned path before and this kernel now: d = 60,000, n = 50, 5 x 400: 98 and 11 us;
 // n = 100: 130 and 21 us; d = 65,536, n = 4, 5 x 2,048: 21 and 9 us; d = 431,003, n = 5, 4 x 9,001: 103 and 39 us;
-// d = 25.6 million, n = 4, 5 x 10,000: 8.5 and 1.14 ms (2.4 with one slice per wavefront and the vector in one part: twelve
+// d = 25.6 million, n = 4, 5 x 10,000: 8.5 and 1.00 ms (2.4 with one slice per wavefront and the vector in one part: twelve
 // windows that read it instead of three).
 #include <stdlib.h>
 
@@ -43,7 +43,7 @@ constexpr int kPullAhead = 4;                 // tiles that the loaders are ahea
 constexpr int kPullSpare = 64;                // words behind the last list, read ahead but not used
 constexpr int kPullMaxList = 512;             // longest list of one bucket in one tile
 // A word holds two consecutive steps of a lane: the first step's coordinate in bits 2-15 (so that it is a byte offset) and
-// its sign in bit 0, the second's in bits 17-30 and 31.  Words come in groups of 2 or 4 (PullOrder::group), which a lane
+// its sign in bit 0, the second's in bits 17-30 and 31.  Words come in groups of 1, 2 or 4 (PullOrder::group), which a lane
 // reads with one load; bit 1 of a group's first word, in every lane: this group ends a tile's list.
 
 // ------------------------------------------------------------------------------------------
@@ -189,7 +189,7 @@ __device__ __forceinline__ void load_to_lds4(const float *src, float *dst)
 // Three tile buffers: the loaders bring the next two tiles in while the adders work on the third.  The two kinds wait for
 // their own loads only (a wavefront's loads come back in order: one that fetched both would wait for the whole next
 // tile before each list).  The adders' loop is a stream of groups: one load is issued per group, unconditionally and
-// straight into the registers that the loop carries, so that the compiler waits for exactly the oldest; the eight (four)
+// straight into the registers that the loop carries, so that the compiler waits for exactly the oldest; the two to eight
 // values of a group are read from LDS together and added in order.
 // PW: slices per wavefront, whose sums take turns in x[0].
 template <int W, int D, int PW>
@@ -390,11 +390,13 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
     *done = false;
     PullPlan pp = {};
     if (!pull_shape(ctx, tun, pp)) return SAMS_OK;
-    // groups of eight steps where the lists of a tile are long (13308 / c entries on average, the longest of 64 decides)
-    const int32_t group = ctx->c <= 4096 ? 4 : 2;
+    // Groups of eight steps where the lists of a tile are long (13308 / c entries on average, the longest of 64 decides),
+    // else of four; of two where a wavefront has four lists per tile and the steps, padding among them, are what
+    // bounds the kernel (5 x 10,000, n = 4, 25.6 million coordinates: 1.13 -> 1.00 ms)
+    const int32_t group = ctx->c <= 4096 ? 4 : (pp.per_wave == 4 ? 1 : 2);
     pp.group = group;
     const void *const kernels[2][3] = {
-        {(const void *)k_sketch_pull<2, 8, 1>, (const void *)k_sketch_pull<2, 8, 2>, (const void *)k_sketch_pull<2, 8, 4>},
+        {(const void *)k_sketch_pull<2, 8, 1>, (const void *)k_sketch_pull<2, 8, 2>, (const void *)k_sketch_pull<1, 16, 4>},
         {(const void *)k_sketch_pull<4, 6, 1>, (const void *)k_sketch_pull<4, 6, 2>, (const void *)k_sketch_pull<4, 6, 4>}};
     pp.kernel = kernels[group == 4][pp.per_wave / 2];
     const PullOrder po = pull_order(pp);
