@@ -239,15 +239,12 @@ int sams_configure(const char *key, int value)
 
 int sams_sketch_mode(const sams_ctx *ctx) { return ctx ? ctx->plan.mode : -1; }
 
-int sams_accumulate_variant(const sams_ctx *ctx)
-{
-    return (ctx && ctx->plan.mode == PLAN_BINNED) ? ctx->plan.acc_variant : -1;
-}
+// (a context that pulls has PLAN_BINNED or PLAN_LDS_ROW for the order of its additions, and no plan)
+static bool uses_plan(const sams_ctx *ctx) { return ctx && ctx->plan.mode == PLAN_BINNED && !ctx->pull.kernel; }
 
-int64_t sams_record_rows(const sams_ctx *ctx)
-{
-    return (ctx && ctx->plan.mode == PLAN_BINNED) ? (int64_t)ctx->plan.rec_mask : -1;
-}
+int sams_accumulate_variant(const sams_ctx *ctx) { return uses_plan(ctx) ? ctx->plan.acc_variant : -1; }
+
+int64_t sams_record_rows(const sams_ctx *ctx) { return uses_plan(ctx) ? (int64_t)ctx->plan.rec_mask : -1; }
 
 int64_t sams_scratch_bytes(const sams_ctx *ctx) { return ctx ? ctx->scratch_bytes : 0; }
 

@@ -85,3 +85,12 @@ def test_long_vectors_in_parts(d, n, r, c):
         mass = o64.sketch(np.abs(u[i]).astype(np.float64), plus, c)
         bound = 2.0 * d / c * 2.0 ** -24 * mass + 1e-37              # twice the average number of terms
         assert np.all(np.abs(got[i] - o64.sketch(u[i].astype(np.float64), hp, c)) <= bound), i
+
+
+@pytest.mark.parametrize("d,c,pulls", [(40_000, 1_000, True), ((1 << 22) + 5, 500, True), (40_000, 127, False), (40_000, 40_000, False)])
+def test_second_pass_variant_is_reported_where_there_is_one(d, c, pulls):
+    """-1 from both where no second pass reads metadata: a context that pulls has no binned path."""
+    from paper_2210_07454_amd import sams
+    with sams.Context(d, 2, 2, c, 1, inputs.hash_params(2, seed=4)) as ctx:
+        assert (ctx.accumulate_variant == -1) == pulls
+        assert (ctx.record_rows == -1) == pulls
