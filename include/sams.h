@@ -275,9 +275,9 @@ int topk_refine(sams_ctx *ctx, const int32_t *idx_in, const float *delta_in, int
  * Returns SAMS_EINVAL for a null or misaligned pointer or a size outside the range above (nothing enqueued),
  * SAMS_EHIP for a runtime error.  The first call on a device looks up the array's address (hipGetSymbolAddress;
  * sams_create does the same look-up, so a process that has created a context on the device has it already) and
- * should be made outside stream capture.  All calls on one GPU share the one array, which keeps the previous call's
- * contents: calls that overlap in time on the same GPU (different streams, or graphs replayed concurrently) race; calls
- * ordered by a stream or by events do not.
+ * should be made outside stream capture.  All calls on one GPU share the one array: calls that overlap in time on the same
+ * GPU (different streams, or graphs replayed concurrently) spoil each other's outputs; calls ordered by a stream or by events
+ * do not, and no call depends on what an earlier one left behind.
  * topk_refine_static_max_candidates() returns SAMS_STATIC_MAX_CANDIDATES as the library was built.
  */
 int topk_refine_static(const int32_t *idx_in, const float *delta_in, int64_t k_in, int64_t k_out, int32_t *idx_out,

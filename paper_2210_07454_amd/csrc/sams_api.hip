@@ -39,11 +39,16 @@ __global__ void k_hash_dump(HashParams hp, int64_t d, int32_t *bucket, int8_t *s
     }
 }
 
-int enqueue_fill_u32(sams_ctx *ctx, uint32_t *p, int64_t n, uint32_t val)
+int enqueue_fill_u32_on(sams_ctx *ctx, hipStream_t stream, uint32_t *p, int64_t n, uint32_t val)
 {
-    SAMS_LAUNCH(ctx, KID_FILL, k_fill_u32, grid_for(n, 256 * 4, 1 << 16), 256, p, n, val);
+    SAMS_LAUNCH_ON(ctx, stream, KID_FILL, k_fill_u32, grid_for(n, 256 * 4, 1 << 16), 256, p, n, val);
     SAMS_HIP(hipGetLastError());
     return SAMS_OK;
+}
+
+int enqueue_fill_u32(sams_ctx *ctx, uint32_t *p, int64_t n, uint32_t val)
+{
+    return enqueue_fill_u32_on(ctx, ctx->stream, p, n, val);
 }
 
 int enqueue_hash_dump(sams_ctx *ctx, int32_t *bucket, int8_t *sign)

@@ -31,8 +31,8 @@ constexpr int64_t kOrderedSingleBinMaxD = (int64_t)1 << 22;     // largest d ske
 constexpr int kHistBins = 2048;     // first radix digit of the selection: 11 bits, then 10 and 10 (kHistBins / 2 bins)
 constexpr int64_t kSelSmallMax = 1 << 16;   // keys up to which the selection is one launch after the first histogram
 
-// device-resident state of the radix selection (no host round trip inside a step); all zero between two selections
-// as far as the next one reads it before writing it: the histograms and `done` are cleared by whoever uses them
+// device-resident state of the radix selection (no host round trip inside a step).  A selection starts from histograms and
+// `done` of zeros and leaves them so; topk_refine_static clears them first all the same
 struct SelState {
     uint32_t prefix[3];   // key bits decided after each digit: the top bits of the k-th largest |key| pattern (prefix[2]: all 31)
     uint32_t k_rem[3];    // how many keys to take among those that match the prefix (k_rem[2]: how many equal to the k-th largest)
@@ -334,6 +334,7 @@ __device__ __forceinline__ void sel_pick(SelState *st, uint32_t *hist, int digit
 
 // ---- enqueue functions (all asynchronous on ctx->stream; return SAMS_OK or SAMS_EHIP) ----
 int enqueue_fill_u32(sams_ctx *ctx, uint32_t *p, int64_t n, uint32_t val);
+int enqueue_fill_u32_on(sams_ctx *ctx, hipStream_t stream, uint32_t *p, int64_t n, uint32_t val);   // ctx may be null: no timing then
 int enqueue_hash_dump(sams_ctx *ctx, int32_t *bucket, int8_t *sign);
 // sams_update.hip
 // the whole update when the head is not fused with the first sketch pass (pa: Alg. 1, v and vhat are [n][d])

@@ -1,0 +1,68 @@
+"""A selection that ends half-way, or that another one runs into, spoils no later one: the histograms and counters that it
+leaves are cleared before they are used again."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import Oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def candidates(k_in, seed):
+    rng = np.random.default_rng(seed)
+    vals = (rng.integers(-4000, 4001, k_in) / 8.0).astype(np.float32)
+    return np.cumsum(rng.integers(1, 9, k_in)).astype(np.int32), vals
+
+
+def hip():
+    return ctypes.CDLL("libamdhip64.so.7")                           # the runtime that torch has loaded
+
+
+def cut_chain(graph, keep):
+    """Takes the nodes of a captured chain away behind the first `keep`; how many it had."""
+    lib, raw = hip(), ctypes.c_void_p(graph.raw_cuda_graph())
+    chain, cnt = [], ctypes.c_size_t(1)
+    node = ctypes.c_void_p()
+    assert lib.hipGraphGetRootNodes(raw, ctypes.byref(node), ctypes.byref(cnt)) == 0 and cnt.value == 1
+    while True:
+        chain.append(ctypes.c_void_p(node.value))
+        cnt = ctypes.c_size_t(0)
+        assert lib.hipGraphNodeGetDependentNodes(chain[-1], None, ctypes.byref(cnt)) == 0
+        if cnt.value == 0:
+            break
+        assert cnt.value == 1
+        assert lib.hipGraphNodeGetDependentNodes(chain[-1], ctypes.byref(node), ctypes.byref(cnt)) == 0
+    for n in reversed(chain[keep:]):
+        assert lib.hipGraphDestroyNode(n) == 0
+    return len(chain)
+
+
+@pytest.mark.parametrize("k_in", [5_000, 70_000, 300_000, 1_300_000])   # every route of the selection
+def test_static_refine_after_one_that_ended_half_way(k_in):
+    """The kernels of a call up to the first, second, ... one alone (a captured call whose later nodes are taken away), each
+    time followed by a whole call."""
+    from paper_2210_07454_amd import sams
+    k_out = k_in // 3
+    cand, vals = candidates(k_in, k_in)
+    ci, vi = torch.from_numpy(cand).cuda(), torch.from_numpy(vals).cuda()
+    io, do = torch.empty(k_out, device="cuda", dtype=torch.int32), torch.empty(k_out, device="cuda")
+    want_idx, want_delta = Oracle("f32").refine(cand, vals, k_out)
+    sams.topk_refine_static(ci, vi, k_out, io, do)
+    torch.cuda.synchronize()
+    keep, nodes = 1, 2
+    while keep < nodes:
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(graph):
+            sams.topk_refine_static(ci, vi, k_out, io, do)
+        nodes = cut_chain(graph, keep)
+        graph.instantiate()
+        graph.replay()
+        torch.cuda.synchronize()
+        io.fill_(-1)
+        sams.topk_refine_static(ci, vi, k_out, io, do)
+        assert np.array_equal(io.cpu().numpy(), want_idx), (k_in, keep)
+        assert np.array_equal(do.cpu().numpy(), want_delta), (k_in, keep)
+        keep += 1
