@@ -73,6 +73,24 @@ static int prof_drain(sams_ctx *ctx)
     return SAMS_OK;
 }
 
+// Brackets the enqueueing of a selection by body().  A failure between its kernels (a launch that is refused, or an error that an
+// earlier call of the thread has left for the next check) would leave the first digit's histogram to be counted twice.
+template <typename F>
+static int selection(sams_ctx *ctx, F body)
+{
+    const bool clear = ctx->sel_open;
+    ctx->sel_open = true;
+    if (clear) SAMS_TRY(enqueue_fill_u32(ctx, ctx->sel, kSelStateWords + 2 * kHistBins, 0u));
+    SAMS_TRY(body());
+    if (clear) {                                                     // recorded into a graph, it has not happened yet
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        SAMS_HIP(hipStreamIsCapturing(ctx->stream, &st));
+        if (st != hipStreamCaptureStatusNone) return SAMS_OK;
+    }
+    ctx->sel_open = false;
+    return SAMS_OK;
+}
+
 }  // namespace sams
 
 using namespace sams;
@@ -359,11 +377,13 @@ int unsketch_topk(sams_ctx *ctx, const float *S_mean, const float *vhat, int32_t
     if (!ctx || !S_mean || !idx || !aligned16(S_mean) || !aligned16(idx) || !aligned16(vhat) ||
         !aligned16(est_sel))
         return SAMS_EINVAL;
-    const SelScratch sc = ctx_sel_scratch(ctx);
-    bool hist_done = false;
-    SAMS_TRY(enqueue_estimate(ctx, S_mean, vhat, ctx->est, &sc, &hist_done));
-    if (sel_list_in_staging(ctx)) ctx->plan.staged_u = nullptr;      // the lists overwrite any staged vector
-    return enqueue_select(ctx, ctx->stream, sc, ctx->est, ctx->d, ctx->k, nullptr, idx, est_sel, hist_done);
+    return selection(ctx, [&]() -> int {
+        const SelScratch sc = ctx_sel_scratch(ctx);
+        bool hist_done = false;
+        SAMS_TRY(enqueue_estimate(ctx, S_mean, vhat, ctx->est, &sc, &hist_done));
+        if (sel_list_in_staging(ctx)) ctx->plan.staged_u = nullptr;  // the lists overwrite any staged vector
+        return enqueue_select(ctx, ctx->stream, sc, ctx->est, ctx->d, ctx->k, nullptr, idx, est_sel, hist_done);
+    });
 }
 
 int topk_refine(sams_ctx *ctx, const int32_t *idx_in, const float *delta_in, int64_t k_out, int32_t *idx_out,
@@ -372,7 +392,9 @@ int topk_refine(sams_ctx *ctx, const int32_t *idx_in, const float *delta_in, int
     if (!ctx || !idx_in || !delta_in || !idx_out || !delta_out || k_out < 1 || k_out > ctx->k) return SAMS_EINVAL;
     if (!aligned16(idx_in) || !aligned16(delta_in) || !aligned16(idx_out) || !aligned16(delta_out)) return SAMS_EINVAL;
     if (sel_list_in_staging(ctx)) ctx->plan.staged_u = nullptr;      // the lists overwrite any staged vector
-    return enqueue_select(ctx, ctx->stream, ctx_sel_scratch(ctx), delta_in, ctx->k, k_out, idx_in, idx_out, delta_out, false);
+    return selection(ctx, [&]() -> int {
+        return enqueue_select(ctx, ctx->stream, ctx_sel_scratch(ctx), delta_in, ctx->k, k_out, idx_in, idx_out, delta_out, false);
+    });
 }
 
 int gather_topk(sams_ctx *ctx, const float *u, const float *vhat, const int32_t *idx, float *U_workers,

@@ -32,7 +32,8 @@ constexpr int kHistBins = 2048;     // first radix digit of the selection: 11 bi
 constexpr int64_t kSelSmallMax = 1 << 16;   // keys up to which the selection is one launch after the first histogram
 
 // device-resident state of the radix selection (no host round trip inside a step).  A selection starts from histograms and
-// `done` of zeros and leaves them so; topk_refine_static clears them first all the same
+// `done` of zeros and leaves them so; the next one clears them first where one failed half-way (sams_ctx::sel_open), and
+// topk_refine_static always does
 struct SelState {
     uint32_t prefix[3];   // key bits decided after each digit: the top bits of the k-th largest |key| pattern (prefix[2]: all 31)
     uint32_t k_rem[3];    // how many keys to take among those that match the prefix (k_rem[2]: how many equal to the k-th largest)
@@ -154,6 +155,7 @@ struct sams_ctx {
                              //               with gsel, only where the head is fused per worker (fuse_head = 2), else null
     float *gsel;             // [n][k]        g of every worker at the coordinates of the most recent index set, by rank
     uint32_t *sel;           // SelState, then the histograms [2 * kHistBins]
+    bool sel_open;           // a selection was begun and not enqueued whole: the next one clears `sel` first
     uint32_t *sel_tile;      // [3][sel_tiles(d)]  SelList::group, cnt
     uint32_t *sel_list;      // SelList::val and loc when the staging buffer is absent or too small to hold them, else null
     int64_t scratch_bytes;

@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from oracle import Oracle
+from paper_2210_07454_amd import inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -66,3 +67,32 @@ def test_static_refine_after_one_that_ended_half_way(k_in):
         assert np.array_equal(io.cpu().numpy(), want_idx), (k_in, keep)
         assert np.array_equal(do.cpu().numpy(), want_delta), (k_in, keep)
         keep += 1
+
+
+# the first digit's histogram comes from the gathering estimates, from the plan's recovery below and above 2^20
+# coordinates, or from a pass over the keys
+@pytest.mark.parametrize("d,r,c", [(60_000, 5, 400), (300_001, 3, 120_000), (1_300_003, 3, 120_000), (431_003, 4, 9_001)])
+def test_topk_after_a_call_that_failed_half_way(d, r, c):
+    """An error that an earlier HIP call of the thread has left behind is reported by the first check of a call, after its
+    estimates have been enqueued: the selection behind them never runs."""
+    from paper_2210_07454_amd import sams
+    k = d // 50
+    rng = np.random.default_rng(d)
+    hp = inputs.hash_params(r)
+    S = rng.standard_normal((r, c)).astype(np.float32)
+    vhat = (rng.random(d) + 0.1).astype(np.float32)
+    o = Oracle("f32")
+    want = o.topk(o.unsketch(S, vhat, d, hp), k)
+    Sd, vd = torch.from_numpy(S).cuda(), torch.from_numpy(vhat).cuda()
+    idx = torch.empty(k, device="cuda", dtype=torch.int32)
+    lib = hip()
+    with sams.Context(d, 2, r, c, k, hp) as ctx:
+        for _ in range(2):
+            assert lib.hipSetDevice(4096) != 0                       # no such device: leaves its error behind
+            with pytest.raises(sams.SamsError):
+                ctx.unsketch_topk(Sd, vd, idx)
+            lib.hipGetLastError()
+            idx.fill_(-1)
+            for _ in range(2):
+                ctx.unsketch_topk(Sd, vd, idx)
+                assert np.array_equal(idx.cpu().numpy(), want)
