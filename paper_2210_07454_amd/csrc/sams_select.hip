@@ -345,10 +345,11 @@ __device__ __forceinline__ void flat_digits(const SelList &ls, Flat &f, uint32_t
 }
 
 // writes the selected entries at their rank: key > tau, or key == tau and among the first k_eq such keys.
-// map != null: the output is map[position] instead of the position.
+// map != null: the output is map[position] instead of the position, which a call on another stream with the same scratch
+// may have put there: it is held below len.
 template <bool AGENT>
 __device__ __forceinline__ void flat_write(const SelList &ls, Flat &f, uint32_t m, uint32_t tau, uint32_t k_eq, int64_t k,
-                                           const int32_t *__restrict__ map, int32_t *__restrict__ idx,
+                                           int64_t len, const int32_t *__restrict__ map, int32_t *__restrict__ idx,
                                            float *__restrict__ val_sel)
 {
     uint32_t gt_run = 0, eq_run = 0;
@@ -366,7 +367,7 @@ __device__ __forceinline__ void flat_write(const SelList &ls, Flat &f, uint32_t 
         if (gt || (eq && eqb < k_eq)) {
             const int64_t pos = (int64_t)gtb + (eqb < k_eq ? eqb : k_eq);
             if (pos < k) {
-                idx[pos] = map ? map[x.y] : (int32_t)x.y;
+                idx[pos] = map ? map[x.y < (uint32_t)len ? x.y : (uint32_t)len - 1u] : (int32_t)x.y;
                 if (val_sel) val_sel[pos] = __uint_as_float(x.x);
             }
         }
@@ -390,7 +391,7 @@ k_sel_small(const float *__restrict__ keys, int64_t len, SelState *__restrict__ 
     __syncthreads();
     const uint32_t m = flat_load<true>(ls, f, (int)gridDim.x);
     flat_digits<true>(ls, f, m, prefix, k_rem);
-    flat_write<true>(ls, f, m, prefix, k_rem, k, map, idx, val_sel);
+    flat_write<true>(ls, f, m, prefix, k_rem, k, len, map, idx, val_sel);
 }
 
 // PICK: the filter picks the first digit (and leaves it in the state), see above
@@ -492,10 +493,11 @@ k_sel_count(const SelState *__restrict__ st, SelList ls, int64_t ntile, int tpw)
 
 // k_sel_write: a workgroup adds up what the groups before it hold (every one for itself: a few hundred to two thousand pairs,
 // in place of a scan by one workgroup in between), counts its own tiles and writes their selected keys at their rank:
-// key > tau, or key == tau and among the first k_eq such keys.  map != null: the output is map[position].
+// key > tau, or key == tau and among the first k_eq such keys.  map != null: the output is map[position] (below len, see
+// flat_write).
 __global__ void __launch_bounds__(1024)
-k_sel_write(const SelState *__restrict__ st, SelList ls, int64_t ntile, int tpw, int64_t k, const int32_t *__restrict__ map,
-            int32_t *__restrict__ idx, float *__restrict__ val_sel)
+k_sel_write(const SelState *__restrict__ st, SelList ls, int64_t len, int64_t ntile, int tpw, int64_t k,
+            const int32_t *__restrict__ map, int32_t *__restrict__ idx, float *__restrict__ val_sel)
 {
     __shared__ uint32_t part[16], sum[2];
     __shared__ uint32_t tile_gt[16 * kSelWriteMaxTpw], tile_eq[16 * kSelWriteMaxTpw];
@@ -550,7 +552,7 @@ k_sel_write(const SelState *__restrict__ st, SelList ls, int64_t ntile, int tpw,
             }
             if (map) {
 #pragma unroll
-                for (int z = 0; z < 4; ++z) l[z] = map[l[z]];
+                for (int z = 0; z < 4; ++z) l[z] = map[l[z] < len ? l[z] : len - 1];
             }
 #pragma unroll
             for (int z = 0; z < 4; ++z) {
@@ -706,7 +708,7 @@ int enqueue_select(sams_ctx *ctx, hipStream_t stream, const SelScratch &sc, cons
                    sel_hist_picks(len) ? nullptr : sc.hist);
     SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, k_sel_list_hist, lgrid, 1024, sc.st, hist2, sc.list, nt, 2, nullptr);
     SAMS_LAUNCH_ON(ctx, stream, KID_SEL_COUNT, k_sel_count, wgrid, 1024, sc.st, sc.list, nt, tpw);
-    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_WRITE, k_sel_write, wgrid, 1024, sc.st, sc.list, nt, tpw, k, map, idx, val_sel);
+    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_WRITE, k_sel_write, wgrid, 1024, sc.st, sc.list, len, nt, tpw, k, map, idx, val_sel);
     SAMS_HIP(hipGetLastError());
     return SAMS_OK;
 }

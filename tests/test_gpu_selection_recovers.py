@@ -69,6 +69,29 @@ def test_static_refine_after_one_that_ended_half_way(k_in):
         keep += 1
 
 
+@pytest.mark.parametrize("sizes", [(5_000, 61_000), (70_001, 1_300_000), (3_000, 300_007)])
+def test_static_refine_after_calls_that_overlapped(sizes):
+    """Calls of two sizes on two streams: their own outputs are undefined, but no position that the larger one has listed may
+    lead the smaller one past its candidates, and the next call by itself is right."""
+    from paper_2210_07454_amd import sams
+    calls = []
+    for k_in in sizes:
+        cand, vals = candidates(k_in, k_in)
+        ci, vi = torch.from_numpy(cand).cuda(), torch.from_numpy(vals).cuda()
+        k_out = k_in // 3
+        io, do = torch.empty(k_out, device="cuda", dtype=torch.int32), torch.empty(k_out, device="cuda")
+        calls.append((ci, vi, k_out, io, do, torch.cuda.Stream(), Oracle("f32").refine(cand, vals, k_out)))
+    torch.cuda.synchronize()
+    for _ in range(10):
+        for ci, vi, k_out, io, do, stream, _ in calls:
+            sams.topk_refine_static(ci, vi, k_out, io, do, stream)
+    torch.cuda.synchronize()
+    for ci, vi, k_out, io, do, _, want in calls:
+        io.fill_(-1)
+        sams.topk_refine_static(ci, vi, k_out, io, do)
+        assert np.array_equal(io.cpu().numpy(), want[0]) and np.array_equal(do.cpu().numpy(), want[1])
+
+
 # the first digit's histogram comes from the gathering estimates, from the plan's recovery below and above 2^20
 # coordinates, or from a pass over the keys
 @pytest.mark.parametrize("d,r,c", [(60_000, 5, 400), (300_001, 3, 120_000), (1_300_003, 3, 120_000), (431_003, 4, 9_001)])
