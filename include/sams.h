@@ -97,6 +97,8 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
  *                 1: one workgroup per tile loops over the workers; 2: one workgroup per (tile, worker), the
  *                 workers of a tile sharing the plan's metadata through one L2, and the (1 - beta2) h^2 term of
  *                 v on I_{t-1} added by a small kernel of its own (same results bit for bit).
+ *                 Where d is no multiple of 4, 1 fuses nothing, and 2 only amsgrad_ef_update from d = 2^24 on (the separate
+ *                 head is faster otherwise).
  *   "stage_rows"  0..16 (default 0 = all r rows): rows of the sketch staged at once on the binned path; the
  *                 staging buffer holds 4*n*stage_rows*(1.1 to 1.5)*d bytes and stage 1 runs row group after
  *                 row group (each group after the first re-reads u)

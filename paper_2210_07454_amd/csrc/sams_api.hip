@@ -417,7 +417,7 @@ int amsgrad_ef_update(sams_ctx *ctx, const float *g_next, float *m, float *e_u, 
         return SAMS_EINVAL;
     ctx->plan.staged_u = nullptr;                                    // e_u is about to change
     if (!g_next) return enqueue_tail_only(ctx, e_u, x, idx, delta, k_sel, lr);
-    if (!head_can_fuse(ctx))
+    if (!head_can_fuse(ctx, false))
         return enqueue_update(ctx, g_next, m, e_u, v, vhat, x, idx, delta, k_sel, beta1, beta2, lr, ef_ratio, false);
     SAMS_TRY(enqueue_tail(ctx, x, idx, delta, k_sel, lr));
     SAMS_TRY(enqueue_head_scatter(ctx, g_next, m, e_u, v, vhat, beta1, beta2, ef_ratio, false, idx, k_sel));
@@ -435,7 +435,7 @@ int amsgrad_ef_update_pa(sams_ctx *ctx, const float *g_next, float *m, float *e_
         return SAMS_EINVAL;
     ctx->plan.staged_u = nullptr;                                    // e_u is about to change
     if (!g_next) return enqueue_tail_only(ctx, e_u, x, idx, delta, k_sel, lr);
-    if (!head_can_fuse(ctx))
+    if (!head_can_fuse(ctx, true))
         return enqueue_update(ctx, g_next, m, e_u, v_workers, vhat_workers, x, idx, delta, k_sel, beta1, beta2, lr, ef_ratio, true);
     SAMS_TRY(enqueue_tail(ctx, x, idx, delta, k_sel, lr));
     SAMS_TRY(enqueue_head_scatter(ctx, g_next, m, e_u, v_workers, vhat_workers, beta1, beta2, ef_ratio, true, idx, k_sel));

@@ -363,7 +363,7 @@ int enqueue_row_estimates_planned(sams_ctx *ctx, const float *S_mean, float *row
 // whole recovery through the plan when the fused collect+median kernel applies; *done says whether it ran
 int enqueue_estimates_planned_fused(sams_ctx *ctx, const float *S_mean, const float *vhat, float *est, bool *done,
                                     const SelScratch *sc);   // see enqueue_estimate; *done implies the histogram
-bool head_can_fuse(const sams_ctx *ctx);
+bool head_can_fuse(const sams_ctx *ctx, bool pa);
 // wordrank and gsel exist for this context (sams_create decides): the per-worker fused head then leaves the
 // gradients of the selected coordinates in gsel and the second moments on I_{t-1} need no gathers
 bool head_compacts_g(const sams_ctx *ctx);

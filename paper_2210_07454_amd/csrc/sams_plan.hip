@@ -640,7 +640,7 @@ k_head_scatter(HeadArgs ha, const uint16_t *__restrict__ srcp, const uint32_t *_
 // (Fetching the other workers' g for those coordinates inside worker 0's workgroup instead was tried: its
 // divergent, dependent gathers made the kernel 1.5x slower.)
 // VEC: 4 = 16-byte accesses (d a multiple of 4); 1 = 4-byte accesses, a thread's coordinates kFusedThreads apart (the workers'
-// vectors start at any alignment then).
+// vectors start at any alignment then), for Alg. 2 alone and long vectors (head_can_fuse).
 template <bool PA, int VEC>
 __global__ void __launch_bounds__(kFusedThreads)
 k_head_scatter_w(HeadArgs ha, const uint16_t *__restrict__ srcp, const uint32_t *__restrict__ dst16,
@@ -743,13 +743,15 @@ k_head_scatter_w(HeadArgs ha, const uint16_t *__restrict__ srcp, const uint32_t 
             }
         }
     } else {
+        static_assert(!PA, "separate head and pass 1 are faster");
         constexpr int kIters = kFusedIters * 4, kBatch = 4;          // kBatch turns' loads are in flight together
         const int lim = (int)(L < d - l0 ? L : d - l0);              // (addresses clamped into the tile: read, not used)
         float gkeep[kIters];
         uint32_t selm = 0;                                           // bit it: the thread's coordinate of that turn is in I_{t-1}
 #pragma unroll
         for (int it0 = 0; it0 < kIters; it0 += kBatch) {
-            float gv[kBatch], mv[kBatch], ev[kBatch], vv[kBatch], vh[kBatch];
+            if (it0 * kFusedThreads >= lim) break;                   // uniform: tiles of 2^13 are half of the turns (25.6 million, 7 rows,
+            float gv[kBatch], mv[kBatch], ev[kBatch], vv[kBatch], vh[kBatch];   // n = 16: 4.57 ms with all of them, 4.12 without)
             uint32_t sel[kBatch];
 #pragma unroll
             for (int z = 0; z < kBatch; ++z) {
@@ -758,10 +760,7 @@ k_head_scatter_w(HeadArgs ha, const uint16_t *__restrict__ srcp, const uint32_t 
                 gv[z] = __builtin_nontemporal_load(ha.g + q);
                 mv[z] = __builtin_nontemporal_load(ha.m + q);
                 ev[z] = __builtin_nontemporal_load(ha.e + q);
-                if constexpr (PA) {
-                    vv[z] = __builtin_nontemporal_load(ha.v + q);
-                    vh[z] = __builtin_nontemporal_load(ha.vhat + q);
-                } else if (i == 0) {
+                if (i == 0) {
                     vv[z] = ha.v[l];
                     vh[z] = ha.vhat[l];
                 }
@@ -772,30 +771,14 @@ k_head_scatter_w(HeadArgs ha, const uint16_t *__restrict__ srcp, const uint32_t 
                 const int p = (it0 + z) * kFusedThreads + (int)threadIdx.x;
                 const float mm = (ha.beta1 * mv[z]) + (ha.omb1 * gv[z]);
                 const float ein = sel[z] ? 0.0f : ev[z];             // e_t is zero on I_t
-                float uv;
-                bool moved = PA;
-                if constexpr (PA) {
-                    vv[z] = (ha.beta2 * vv[z]) + (ha.omb2 * (gv[z] * gv[z]));
-                    if (vv[z] > vh[z]) vh[z] = vv[z];
-                    uv = (mm / sqrtf(vh[z])) + (ha.rho * ein);
-                } else {
-                    uv = mm + (ha.rho * ein);
-                    gkeep[it0 + z] = gv[z];
-                    if (i == 0) {                                    // the decay of v, once per coordinate
-                        vv[z] = ha.beta2 * vv[z];                    // + (1 - beta2) * 0^2, exactly
-                        if (vv[z] > vh[z]) { vh[z] = vv[z]; moved = true; }
-                    }
-                }
+                const float uv = mm + (ha.rho * ein);
+                gkeep[it0 + z] = gv[z];
                 if (p < lim) {
-                    if constexpr (PA) {
-                        __builtin_nontemporal_store(vv[z], ha.v + wbase + p);
-                        __builtin_nontemporal_store(vh[z], ha.vhat + wbase + p);
-                    } else {
-                        selm |= sel[z] << (it0 + z);
-                        if (i == 0) {
-                            ha.v[l0 + p] = vv[z];
-                            if (moved) ha.vhat[l0 + p] = vh[z];
-                        }
+                    selm |= sel[z] << (it0 + z);
+                    if (i == 0) {                                    // the decay of v, once per coordinate
+                        const float v0 = ha.beta2 * vv[z];           // + (1 - beta2) * 0^2, exactly
+                        ha.v[l0 + p] = v0;
+                        if (v0 > vh[z]) ha.vhat[l0 + p] = v0;
                     }
                     __builtin_nontemporal_store(mm, ha.m + wbase + p);
                     __builtin_nontemporal_store(uv, ha.e + wbase + p);
@@ -803,16 +786,14 @@ k_head_scatter_w(HeadArgs ha, const uint16_t *__restrict__ srcp, const uint32_t 
                 }
             }
         }
-        if constexpr (!PA) {
-            if (ha.gsel && selm) {
+        if (ha.gsel && selm) {
 #pragma unroll
-                for (int it = 0; it < kIters; ++it)
-                    if ((selm >> it) & 1u) {
-                        const int64_t l = l0 + it * kFusedThreads + (int)threadIdx.x;
-                        const uint32_t below = ha.bitmap[l >> 5] & ((1u << (l & 31)) - 1u);
-                        ha.gsel[(int64_t)i * ha.k_prev + ha.wordrank[l >> 5] + __popc(below)] = gkeep[it];
-                    }
-            }
+            for (int it = 0; it < kIters; ++it)
+                if ((selm >> it) & 1u) {
+                    const int64_t l = l0 + it * kFusedThreads + (int)threadIdx.x;
+                    const uint32_t below = ha.bitmap[l >> 5] & ((1u << (l & 31)) - 1u);
+                    ha.gsel[(int64_t)i * ha.k_prev + ha.wordrank[l >> 5] + __popc(below)] = gkeep[it];
+                }
         }
     }
     __syncthreads();
@@ -1809,7 +1790,6 @@ int plan_create(sams_ctx *ctx, const Tunables &tun)
         if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_head_scatter_w<false, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
         if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_head_scatter_w<true, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
         if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_head_scatter_w<false, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_head_scatter_w<true, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
 #define SAMS_CM(RR, IT)                                                                            \
     if (e == hipSuccess)                                                                           \
         e = hipFuncSetAttribute((const void *)k_bin_collect_median<RR, IT>,                        \
@@ -1982,9 +1962,16 @@ static int32_t scatter_group(const Plan &pl)
 
 bool head_compacts_g(const sams_ctx *ctx) { return ctx->wordrank != nullptr && ctx->gsel != nullptr; }
 
-bool head_can_fuse(const sams_ctx *ctx)
+// Where d is no multiple of four the workgroup per (tile, worker) has 4-byte accesses to pay for the copy of u that it saves.
+// Update and first sketch pass, fused and separate (n = 8, five rows; d one more than a multiple of four): 11.2 million 0.93
+// and 0.91 ms, 16.8 million 1.22 and 1.29 ms, 60 million 3.9 and 4.1 ms, 124 million 8.0 and 8.5 ms; below, at one million
+// with n = 4, 53 and 58 us but a step of 119 and 113 us, with the tail and the second moments on I_{t-1} in launches of their
+// own.  Alg. 1: 1.44 and 1.12 ms at 11.2 million, 6.0 and 5.7 at 60 million, 4.6 and 4.3 at 100 million (three rows).
+constexpr int64_t kFuseOddMinD = (int64_t)1 << 24;
+bool head_can_fuse(const sams_ctx *ctx, bool pa)
 {
-    return ctx->tun.fuse_head && ctx->plan.mode == PLAN_BINNED && !ctx->pull.kernel && (ctx->tun.fuse_head == 2 || (ctx->d & 3) == 0);
+    if (!ctx->tun.fuse_head || ctx->plan.mode != PLAN_BINNED || ctx->pull.kernel) return false;
+    return (ctx->d & 3) == 0 || (ctx->tun.fuse_head == 2 && !pa && ctx->d >= kFuseOddMinD);
 }
 
 int enqueue_head_scatter(sams_ctx *ctx, const float *g, float *m, float *e_u, float *v, float *vhat,
@@ -2003,8 +1990,7 @@ int enqueue_head_scatter(sams_ctx *ctx, const float *g, float *m, float *e_u, fl
         if (ctx->tun.fuse_head == 2) {                                  // one workgroup per (tile, worker)
             const dim3 wgrid((unsigned)(per * kNumXcd * ctx->n));
             const bool vec = (ctx->d & 3) == 0;
-            const auto kernel = pa ? (vec ? k_head_scatter_w<true, 4> : k_head_scatter_w<true, 1>)
-                                   : (vec ? k_head_scatter_w<false, 4> : k_head_scatter_w<false, 1>);
+            const auto kernel = pa ? k_head_scatter_w<true, 4> : (vec ? k_head_scatter_w<false, 4> : k_head_scatter_w<false, 1>);
             hipLaunchKernelGGL(kernel, wgrid, dim3(kFusedThreads), (size_t)(L * 4), ctx->stream, ha, pl.srcp, pl.dst16, pl.pbase,
                                pl.stg, ctx->n, rg, ctx->d, pl.tile_log2, pl.ntile, pl.rowlen, pl.grp_log2, scatter_group(pl));
         } else if (pa)

@@ -28,3 +28,40 @@ def test_lengths_at_the_edges_of_tiles(d, n, r, c, k, fuse_head):
     finally:
         for key, val in DEFAULTS.items():
             sams.sams_configure(key, val)
+
+
+def fused(d, n, r, c, pa):
+    """whether the update also stages its vector, by the kernels that it launches"""
+    import torch
+    from paper_2210_07454_amd import inputs, sams
+    sams.sams_configure("fuse_head", 2)
+    try:
+        with sams.Context(d, n, r, c, 4, inputs.hash_params(r)) as ctx:
+            g, m, e = (torch.zeros(n, d, device="cuda") for _ in range(3))
+            v, vhat = (torch.ones((n, d) if pa else (d,), device="cuda") for _ in range(2))
+            update = ctx.amsgrad_ef_update_pa if pa else ctx.amsgrad_ef_update
+            ctx.sams_profile_enable(True)
+            update(g, m, e, v, vhat, torch.zeros(d, device="cuda"), None, None, 0, 0.9, 0.99, 1e-3)
+            ctx.sams_profile_enable(False)
+            return "k_head_scatter" in ctx.sams_profile_read()
+    finally:
+        sams.sams_configure("fuse_head", 0)
+
+
+def test_ragged_vectors_fuse_the_head_only_where_that_is_faster():
+    long = 1 << 24
+    assert fused(300_000, 2, 3, 40_000, False) and fused(300_000, 2, 3, 40_000, True)
+    assert fused(long + 1, 1, 2, 40_000, False) and fused(long + 4, 1, 2, 40_000, True)
+    assert not fused(300_001, 2, 3, 40_000, False) and not fused(300_001, 2, 3, 40_000, True)
+    assert not fused(long - 1, 1, 2, 40_000, False) and not fused(long + 1, 1, 2, 40_000, True)
+
+
+@pytest.mark.parametrize("d,n,r,c,k", [((1 << 24) + 1, 3, 2, 70_001, 20_000), ((1 << 24) + 8_195, 2, 7, 200_003, 3_000)])
+def test_long_ragged_vectors_with_the_fused_head(d, n, r, c, k):
+    """tiles of 2^14 and of 2^13 (half of the fused head's turns), a last tile of one coordinate and of three"""
+    from paper_2210_07454_amd import sams
+    try:
+        sams.sams_configure("fuse_head", 2)
+        assert one_iteration(sams, (d, n, r, c, k), seed=d % 97)
+    finally:
+        sams.sams_configure("fuse_head", 0)
