@@ -149,7 +149,13 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
         ctx->scratch_bytes += a.bytes;
     }
     void *static_scratch = nullptr;
-    if (ctx->tun.fuse_head == 2 && ctx->tun.sketch_path != 1) {      // the per-worker fused head compacts g on I_{t-1}
+    int rc = static_scratch_ptr(&static_scratch);                    // resolved here so that topk_refine_static never has to
+    if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, ctx->bitmap, words, 0u);
+    if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, ctx->sel, kSelStateWords + 2 * kHistBins, 0u);
+    bool pulls = false;
+    if (rc == SAMS_OK) rc = pull_create(ctx, ctx->tun, &pulls);
+    if (rc == SAMS_OK && !pulls && ctx->tun.sketch_path != 1) rc = plan_create(ctx, ctx->tun);
+    if (rc == SAMS_OK && ctx->tun.fuse_head == 2 && head_can_fuse(ctx, false)) {   // the per-worker fused head compacts g on I_{t-1}
         struct { void **p; int64_t bytes; } extra[] = {{(void **)&ctx->wordrank, words * 4}, {(void **)&ctx->gsel, (int64_t)n * k * 4}};
         for (auto &a : extra) {
             hipError_t e = hipMalloc(a.p, (size_t)a.bytes);
@@ -162,12 +168,6 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
             ctx->scratch_bytes += a.bytes;
         }
     }
-    int rc = static_scratch_ptr(&static_scratch);                    // resolved here so that topk_refine_static never has to
-    if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, ctx->bitmap, words, 0u);
-    if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, ctx->sel, kSelStateWords + 2 * kHistBins, 0u);
-    bool pulls = false;
-    if (rc == SAMS_OK) rc = pull_create(ctx, ctx->tun, &pulls);
-    if (rc == SAMS_OK && !pulls && ctx->tun.sketch_path != 1) rc = plan_create(ctx, ctx->tun);
     if (rc == SAMS_OK && plan_staging_words(ctx) < sel_list_words(d)) {
         hipError_t e = hipMalloc((void **)&ctx->sel_list, (size_t)sel_list_words(d) * 4);
         if (e != hipSuccess) {

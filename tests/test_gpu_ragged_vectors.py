@@ -65,3 +65,20 @@ def test_long_ragged_vectors_with_the_fused_head(d, n, r, c, k):
         assert one_iteration(sams, (d, n, r, c, k), seed=d % 97)
     finally:
         sams.sams_configure("fuse_head", 0)
+
+
+@pytest.mark.parametrize("d,c,extra", [(60_000, 40_000, True), (60_000, 400, False), (60_001, 40_000, False), (6_000_000, 500, False)])
+def test_room_for_the_compacted_gradients_only_where_the_head_fuses(d, c, extra):
+    """g of every worker on the index set and the ranks of its bitmap words: not for a context that pulls, adds up rows in LDS
+    or has its head apart"""
+    from paper_2210_07454_amd import inputs, sams
+    n, r, k = 3, 2, d // 10
+    size = {}
+    try:
+        for fuse_head in (0, 2):
+            sams.sams_configure("fuse_head", fuse_head)
+            with sams.Context(d, n, r, c, k, inputs.hash_params(r)) as ctx:
+                size[fuse_head] = ctx.scratch_bytes
+    finally:
+        sams.sams_configure("fuse_head", 0)
+    assert size[2] - size[0] == (4 * n * k + (d + 31) // 32 * 4 if extra else 0)
