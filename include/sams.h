@@ -54,12 +54,16 @@ typedef struct sams_ctx sams_ctx;
  *   hip_stream the hipStream_t (as void*) every later call on this context is enqueued on; NULL =
  *              the default stream.
  * Ranges: 1 <= d < 2^31-1, 1 <= n <= 1024, 1 <= r <= SAMS_MAX_ROWS, 1 <= c < 2^31-1, 1 <= k <= d.
- * Allocates the context's device scratch: about 4d bytes for the estimates, d/8 for the index bitmap,
- * small selection state and, when c exceeds one LDS window, the sketch plan and its staging buffer (for a table of 128 to
- * 16384 buckets and d <= 2^26, instead, lists of about 4 to 8 bytes per row and coordinate; see "sketch_path")
- * (4*r*d bytes of plan + 4*n*r*d bytes of staging; the selection's lists live in the staging buffer, without one they take
- * another 6d bytes); sams_scratch_bytes reports the total.  The plan is
- * built on the stream by this call.
+ * Allocates the context's device scratch; sams_scratch_bytes reports the total:
+ *   always            4d bytes for the estimates, d/8 for the index bitmap, small selection state
+ *   c above one LDS window, or d <= 2^22: the sketch plan and its staging buffer, 4*r*d + 4*n*r*d bytes and their padding
+ *   128 <= c <= 16384 and d <= 2^26, in their place: lists, 3 to 12 bytes per row and coordinate (24 at most: a hash that needs
+ *                     more goes the other way), and above d = 2^22 up to 128 tables of n*r*c floats; where these find no
+ *                     room, the context does without them (see "sketch_path")
+ *   no staging buffer of 6d bytes: that much for the lists of the selection ("sketch_path" 1 too), or, where it is not to be
+ *                     had, 6 MiB (selections from more than 2^20 keys then read every key in four passes instead of two)
+ *   "fuse_head" 2, where it fuses: 4*n*k + d/8 bytes
+ * The plan or the lists are built on the stream by this call, which waits for them.
  * For an even r the median of Sec. II-C is the lower middle element.
  */
 int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int64_t k,
@@ -91,7 +95,7 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
  *                 following sketch_accumulate called with that same e_u pointer skips its first pass.
  *                 The caller must then not write to e_u between the two calls (the algorithm never does).
  *                 The sorted copy lives in the context's staging buffer and is forgotten as soon as anything else
- *                 uses that buffer (unsketch_topk, unsketch_estimates, a sketch_accumulate that stages row groups)
+ *                 uses that buffer (unsketch_topk, unsketch_estimates, topk_refine, a sketch_accumulate that stages row groups)
  *                 or e_u changes through this library (any amsgrad_ef_update*): a later sketch_accumulate of the
  *                 same pointer then runs both passes again.
  *                 1: one workgroup per tile loops over the workers; 2: one workgroup per (tile, worker), the
@@ -134,7 +138,7 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
  *                 (above, the vector may be cut into parts whose sums are added up, always in the same way), unless "tile_log2", "win_log2",
  *                 "chunk_log2", "acc_threads", "stage_rows" or "estimate_path" 2 ask for the binned path ("fuse_head"
  *                 then has nothing to stage and changes nothing); 1: one global atomic add per term
- *                 (no plan memory); 2: the order-preserving path always; 3: LDS atomics whenever c fits one
+ *                 (no plan and no staging); 2: the order-preserving path always; 3: LDS atomics whenever c fits one
  *                 window
  * Returns SAMS_EINVAL for an unknown key or a value out of range.
  */

@@ -119,6 +119,7 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
     ctx->d = d; ctx->n = n; ctx->r = r; ctx->c = c; ctx->k = k;
     ctx->stream = (hipStream_t)hip_stream;
     ctx->prof_only = -1;
+    ctx->sel_cap = d;
     {
         std::lock_guard<std::mutex> lock(g_tun_mutex);
         ctx->tun = g_tun;                                            // every later call reads this copy only
@@ -170,12 +171,18 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
     }
     if (rc == SAMS_OK && plan_staging_words(ctx) < sel_list_words(d)) {
         hipError_t e = hipMalloc((void **)&ctx->sel_list, (size_t)sel_list_words(d) * 4);
+        if (e != hipSuccess && d > kSelHistPickMin) {                // longer selections work on the keys themselves
+            (void)hipGetLastError();
+            ctx->sel_list = nullptr;
+            ctx->sel_cap = kSelHistPickMin;
+            e = hipMalloc((void **)&ctx->sel_list, (size_t)sel_list_words(ctx->sel_cap) * 4);
+        }
         if (e != hipSuccess) {
             g_last_hip_error = (int)e;
             (void)hipGetLastError();
             rc = SAMS_ENOMEM;
         } else {
-            ctx->scratch_bytes += sel_list_words(d) * 4;
+            ctx->scratch_bytes += sel_list_words(ctx->sel_cap) * 4;
         }
     }
     if (rc != SAMS_OK) {

@@ -121,10 +121,11 @@ struct Tunables {
 };
 extern Tunables g_tun;
 
-// the keys a selection has listed (k_sel_filter), and what is known per tile of keys
+// the keys a selection has listed (k_sel_filter), and what is known per tile of keys.  Without room for lists the keys
+// themselves take their place: cnt and loc null, every key of a tile listed
 struct SelList {
-    uint32_t *val;           // [len + 64]  a listed key's bits (sign included), tile after tile, each from the tile's first position on
-    uint16_t *loc;           // [len + 64]  its position inside the tile
+    uint32_t *val;           // [cap + 64]  a listed key's bits (sign included), tile after tile, each from the tile's first position on
+    uint16_t *loc;           // [cap + 64]  its position inside the tile
     uint32_t *cnt;           // [ntile_cap]  listed keys per tile
     uint2 *group;            // [ntile_cap]  per workgroup of k_sel_count: keys above the threshold, keys equal to it
 };
@@ -134,8 +135,9 @@ struct SelScratch {
     SelState *st;
     uint32_t *hist;          // [2 * kHistBins]  first digit, then second, then third
     SelList list;
-    int64_t ntile_cap;
+    int64_t ntile_cap, cap;  // tiles, and keys that the lists have room for
 };
+constexpr int64_t kSelHistPickMin = (int64_t)1 << 20;                // above, the kernel that takes the first histogram picks its digit
 constexpr int64_t kSelStateWords = 64;                               // words of SelState, rounded up; the histograms follow it
 static_assert(sizeof(SelState) <= kSelStateWords * 4, "selection state");
 // tiles for which the per-tile arrays need room when up to len keys are selected from: of 4096 keys, at least 256
@@ -158,6 +160,7 @@ struct sams_ctx {
     bool sel_open;           // a selection was begun and not enqueued whole: the next one clears `sel` first
     uint32_t *sel_tile;      // [3][sel_tiles(d)]  SelList::group, cnt
     uint32_t *sel_list;      // SelList::val and loc when the staging buffer is absent or too small to hold them, else null
+    int64_t sel_cap;         // keys that the lists have room for: d, or less where device memory was short
     int64_t scratch_bytes;
     sams::Plan plan;
     sams::PullPlan pull;

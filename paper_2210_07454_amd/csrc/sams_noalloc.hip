@@ -66,7 +66,7 @@ int topk_refine_static(const int32_t *idx_in, const float *delta_in, int64_t k_i
     const SelScratch sc = {reinterpret_cast<SelState *>(sel), sel + kSelStateWords,
                            {reinterpret_cast<uint32_t *>(b + kOffVal), reinterpret_cast<uint16_t *>(b + kOffLoc),
                             tile + 2 * kStaticTiles, reinterpret_cast<uint2 *>(tile)},
-                           kStaticTiles};
+                           kStaticTiles, kStaticMaxCand};
     // Calls on several streams share this scratch, so what the one before has left is not relied on (inside a context the
     // stream orders the selections): one that overlapped another, or ended half-way, would spoil every later call.  Costs a
     // launch of 2 us (4.96 million candidates: 64 -> 66 us).

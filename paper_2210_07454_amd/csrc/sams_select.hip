@@ -131,7 +131,8 @@ k_est_median(const float *__restrict__ rowest, const float *__restrict__ vhat, f
 // Digits of 11, 10 and 10 bits.  The histogram of the first digit needs every key (an estimate kernel often takes it).
 // A filter then reads the keys once more and lists those whose first digit is not below that of the k-th largest key --
 // the selected ones and the candidates, about 1.5 k of them unless many keys are equal -- in coordinate order, every
-// tile of keys in a region of its own.  Everything after that works on the listed keys only.
+// tile of keys in a region of its own.  Everything after that works on the listed keys only (on all keys, without the filter,
+// where a context of more than 2^20 coordinates found no room for lists).
 //   up to 2^16 keys: k_sel_small filters, and its last workgroup finishes the selection
 //   more: k_sel_filter, two histograms of the listed keys, k_sel_count, k_sel_write
 // Up to 2^20 keys every filter workgroup picks the first digit from the histogram for itself (8 KiB, in every L2); above,
@@ -409,6 +410,13 @@ k_sel_filter(const float *__restrict__ keys, int64_t len, SelState *__restrict__
 }
 
 constexpr int kSelWriteMaxTpw = 4;
+__device__ __forceinline__ uint32_t listed(const SelList &ls, int64_t len, int64_t tile)
+{
+    if (ls.cnt) return ls.cnt[tile];
+    const int64_t rest = len - (tile << kSelTileLog2);
+    return rest < (1 << kSelTileLog2) ? (uint32_t)rest : 1u << kSelTileLog2;
+}
+
 // f(have, bits) for the listed keys of a tile, 64 at a time by one wavefront; four groups of 64 are fetched
 // together (clamped to the tile's count: in bounds)
 template <typename F>
@@ -432,7 +440,7 @@ __device__ __forceinline__ void each_listed(const SelList &ls, int64_t tile, uin
 
 // histogram of digit 1 or 2 over the listed keys whose higher digits are the picked ones
 __global__ void __launch_bounds__(1024)
-k_sel_list_hist(SelState *__restrict__ st, uint32_t *__restrict__ hist, SelList ls, int64_t ntile, int digit,
+k_sel_list_hist(SelState *__restrict__ st, uint32_t *__restrict__ hist, SelList ls, int64_t len, int64_t ntile, int digit,
                 uint32_t *__restrict__ clear)   // null, or the first digit's histogram, which the filter has read
 {
     __shared__ uint32_t lh[1024], part[16], sh[2];
@@ -445,7 +453,7 @@ k_sel_list_hist(SelState *__restrict__ st, uint32_t *__restrict__ hist, SelList 
     const int up = 30 - 10 * digit;
     const int64_t waves = (int64_t)gridDim.x * 16;
     for (int64_t tile = (int64_t)blockIdx.x * 16 + t / kWave; tile < ntile; tile += waves)
-        each_listed(ls, tile, ls.cnt[tile], [&](bool have, uint32_t bits) {
+        each_listed(ls, tile, listed(ls, len, tile), [&](bool have, uint32_t bits) {
             const uint32_t key = bits & 0x7fffffffu;
             if (have && (key >> up) == prefix) atomicAdd(&lh[(key >> (up - 10)) & 1023u], 1u);
         });
@@ -468,7 +476,7 @@ __device__ __forceinline__ uint2 count_listed(const SelList &ls, int64_t tile, u
 // A workgroup has 16 * tpw consecutive tiles, wavefront w the tiles tpw w ... tpw w + tpw - 1 of them.
 // k_sel_count: keys above and at the threshold per workgroup, to group[].
 __global__ void __launch_bounds__(1024)
-k_sel_count(const SelState *__restrict__ st, SelList ls, int64_t ntile, int tpw)
+k_sel_count(const SelState *__restrict__ st, SelList ls, int64_t len, int64_t ntile, int tpw)
 {
     __shared__ uint32_t sum[2];
     const uint32_t tau = st->prefix[2];
@@ -479,7 +487,7 @@ k_sel_count(const SelState *__restrict__ st, SelList ls, int64_t ntile, int tpw)
     for (int q = 0; q < tpw; ++q) {
         const int64_t tile = ((int64_t)blockIdx.x * 16 + wave) * tpw + q;
         if (tile >= ntile) break;
-        const uint2 x = count_listed(ls, tile, ls.cnt[tile], tau);
+        const uint2 x = count_listed(ls, tile, listed(ls, len, tile), tau);
         n.x += x.x;
         n.y += x.y;
     }
@@ -521,7 +529,7 @@ k_sel_write(const SelState *__restrict__ st, SelList ls, int64_t len, int64_t nt
     }
     const int64_t first = ((int64_t)blockIdx.x * 16 + wave) * tpw;
     for (int q = 0; q < tpw && first + q < ntile; ++q) {
-        const uint2 n = count_listed(ls, first + q, ls.cnt[first + q], tau);
+        const uint2 n = count_listed(ls, first + q, listed(ls, len, first + q), tau);
         if (lane == 0) {
             tile_gt[wave * tpw + q] = n.x;
             tile_eq[wave * tpw + q] = n.y;
@@ -538,7 +546,7 @@ k_sel_write(const SelState *__restrict__ st, SelList ls, int64_t len, int64_t nt
     __syncthreads();
     for (int q = 0; q < tpw && first + q < ntile; ++q) {
         const int64_t base = (first + q) << kSelTileLog2;
-        const uint32_t cnt = ls.cnt[first + q];
+        const uint32_t cnt = listed(ls, len, first + q);
         uint32_t gtr = tile_gt[wave * tpw + q], eqr = tile_eq[wave * tpw + q];
 #pragma unroll 1
         for (uint32_t e0 = 0; e0 < cnt; e0 += 4 * kWave) {
@@ -548,7 +556,7 @@ k_sel_write(const SelState *__restrict__ st, SelList ls, int64_t len, int64_t nt
             for (int z = 0; z < 4; ++z) {
                 const uint32_t en = e0 + z * kWave + lane, at = en < cnt ? en : cnt - 1;
                 bits[z] = ls.val[base + at];
-                l[z] = (int32_t)(base + ls.loc[base + at]);
+                l[z] = (int32_t)(base + (ls.loc ? (uint32_t)ls.loc[base + at] : at));
             }
             if (map) {
 #pragma unroll
@@ -668,12 +676,12 @@ SelScratch ctx_sel_scratch(const sams_ctx *ctx)
 {
     uint32_t *list = sel_list_in_staging(ctx) ? reinterpret_cast<uint32_t *>(ctx->plan.stg) : ctx->sel_list;
     const int64_t nt = sel_tiles(ctx->d);
-    const SelList ls = {list, reinterpret_cast<uint16_t *>(list + ctx->d + 64), ctx->sel_tile + 2 * nt,
+    const SelList ls = {list, reinterpret_cast<uint16_t *>(list + ctx->sel_cap + 64), ctx->sel_tile + 2 * nt,
                         reinterpret_cast<uint2 *>(ctx->sel_tile)};
-    return SelScratch{reinterpret_cast<SelState *>(ctx->sel), ctx->sel + kSelStateWords, ls, nt};
+    return SelScratch{reinterpret_cast<SelState *>(ctx->sel), ctx->sel + kSelStateWords, ls, nt, ctx->sel_cap};
 }
 
-bool sel_hist_picks(int64_t len) { return len > ((int64_t)1 << 20); }
+bool sel_hist_picks(int64_t len) { return len > kSelHistPickMin; }
 
 int enqueue_select(sams_ctx *ctx, hipStream_t stream, const SelScratch &sc, const float *keys, int64_t len, int64_t k,
                    const int32_t *map, int32_t *idx, float *val_sel, bool hist_done)
@@ -698,17 +706,20 @@ int enqueue_select(sams_ctx *ctx, hipStream_t stream, const SelScratch &sc, cons
     const int lgrid = grid_for(nt, 16, 128);
     const int tpw = nt > 16384 ? kSelWriteMaxTpw : 1;                // at most a few thousand groups for a workgroup to add up
     const int wgrid = grid_for(nt, 16 * tpw);
-    if (sel_hist_picks(len))
+    SelList ls = sc.list;
+    if (len > sc.cap)                                                // above kSelHistPickMin, so the digit has been picked
+        ls = {reinterpret_cast<uint32_t *>(const_cast<float *>(keys)), nullptr, nullptr, sc.list.group};   // read only
+    else if (sel_hist_picks(len))
         SAMS_LAUNCH_ON(ctx, stream, KID_SEL_FILTER, k_sel_filter<false>, (unsigned)nt, 1024, keys, len, sc.st, sc.hist, sc.list,
                        (uint32_t)k);
     else
         SAMS_LAUNCH_ON(ctx, stream, KID_SEL_FILTER, k_sel_filter<true>, (unsigned)nt, 1024, keys, len, sc.st, sc.hist, sc.list,
                        (uint32_t)k);
-    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, k_sel_list_hist, lgrid, 1024, sc.st, hist1, sc.list, nt, 1,
+    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, k_sel_list_hist, lgrid, 1024, sc.st, hist1, ls, len, nt, 1,
                    sel_hist_picks(len) ? nullptr : sc.hist);
-    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, k_sel_list_hist, lgrid, 1024, sc.st, hist2, sc.list, nt, 2, nullptr);
-    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_COUNT, k_sel_count, wgrid, 1024, sc.st, sc.list, nt, tpw);
-    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_WRITE, k_sel_write, wgrid, 1024, sc.st, sc.list, len, nt, tpw, k, map, idx, val_sel);
+    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, k_sel_list_hist, lgrid, 1024, sc.st, hist2, ls, len, nt, 2, nullptr);
+    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_COUNT, k_sel_count, wgrid, 1024, sc.st, ls, len, nt, tpw);
+    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_WRITE, k_sel_write, wgrid, 1024, sc.st, ls, len, nt, tpw, k, map, idx, val_sel);
     SAMS_HIP(hipGetLastError());
     return SAMS_OK;
 }
