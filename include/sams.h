@@ -61,7 +61,7 @@ typedef struct sams_ctx sams_ctx;
  *                     more goes the other way), and above d = 2^22 up to 128 tables of n*r*c floats; where these find no
  *                     room, the context does without them (see "sketch_path")
  *   no staging buffer of 6d bytes: that much for the lists of the selection ("sketch_path" 1 too), or, where it is not to be
- *                     had, 6 MiB (selections from more than 2^20 keys then read every key in four passes instead of two)
+ *                     had, 6 MiB (every pass of a selection from more than 2^20 keys is then over all of them)
  *   "fuse_head" 2, where it fuses: 4*n*k + d/8 bytes
  * The plan or the lists are built on the stream by this call, which waits for them.
  * For an even r the median of Sec. II-C is the lower middle element.

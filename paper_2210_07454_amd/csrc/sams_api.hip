@@ -156,6 +156,7 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
     bool pulls = false;
     if (rc == SAMS_OK) rc = pull_create(ctx, ctx->tun, &pulls);
     if (rc == SAMS_OK && !pulls && ctx->tun.sketch_path != 1) rc = plan_create(ctx, ctx->tun);
+    if (rc == SAMS_OK) rc = estimate_prepare(ctx);
     if (rc == SAMS_OK && ctx->tun.fuse_head == 2 && head_can_fuse(ctx, false)) {   // the per-worker fused head compacts g on I_{t-1}
         struct { void **p; int64_t bytes; } extra[] = {{(void **)&ctx->wordrank, words * 4}, {(void **)&ctx->gsel, (int64_t)n * k * 4}};
         for (auto &a : extra) {

@@ -376,6 +376,8 @@ int enqueue_head_scatter(sams_ctx *ctx, const float *g, float *m, float *e_u, fl
 // sams_select.hip
 // whether the kernel that takes the first digit's histogram over len keys also picks the digit (the filter does otherwise)
 bool sel_hist_picks(int64_t len);
+// at creation, once it is known whether there is a plan: what the kernels of enqueue_estimate need set
+int estimate_prepare(const sams_ctx *ctx);
 // sc != null: a selection of ctx->k from est follows with this scratch; *hist_done tells whether the estimate kernel has
 // also taken the histogram of the first radix digit (see sel_hist_picks)
 int enqueue_estimate(sams_ctx *ctx, const float *S_mean, const float *vhat, float *est, const SelScratch *sc, bool *hist_done);

@@ -590,15 +590,42 @@ constexpr int kEstLdsBytes = 160 * 1024;
 constexpr int64_t kEstLdsMinD = (int64_t)1 << 20;
 constexpr int kEstLdsMinShare = 5;                                   // at least a fifth of the rows held
 constexpr int64_t kGatherEstimateMaxTableBytes = 1 << 20, kGatherEstimateMaxD = (int64_t)1 << 22;
+
+// Whether stage 3 goes through the plan.  A small table under a short vector stays in every L2: r gathers per coordinate in
+// one launch then beat the two launches of the plan-driven recovery (C1: 6 us against 23), which is made for tables far
+// larger than any cache.
+static bool estimate_by_plan(const sams_ctx *ctx)
+{
+    const bool small = (int64_t)ctx->r * ctx->c * 4 <= kGatherEstimateMaxTableBytes && ctx->d <= kGatherEstimateMaxD;
+    return ctx->plan.mode == PLAN_BINNED && !ctx->pull.kernel && (ctx->tun.estimate_path == 2 || (ctx->tun.estimate_path == 0 && !small));
+}
+
+// rows that k_estimate_lds holds, 0 = it is not used
+static int32_t estimate_held_rows(const sams_ctx *ctx)
+{
+    const int32_t held = (int32_t)(kEstLdsBytes / (ctx->c * 4) < ctx->r ? kEstLdsBytes / (ctx->c * 4) : ctx->r);
+    const bool used = ctx->d >= kEstLdsMinD && ctx->c >= 2 && held * kEstLdsMinShare >= ctx->r && ctx->tun.estimate_path != 1;
+    return used && !estimate_by_plan(ctx) ? held : 0;
+}
+
+int estimate_prepare(const sams_ctx *ctx)
+{
+    if (!estimate_held_rows(ctx)) return SAMS_OK;
+#define SAMS_CASE(R) (const void *)k_estimate_lds<R>
+    const void *const kernels[SAMS_MAX_ROWS] = {SAMS_CASE(1),  SAMS_CASE(2),  SAMS_CASE(3),  SAMS_CASE(4), SAMS_CASE(5),  SAMS_CASE(6),
+                                                SAMS_CASE(7),  SAMS_CASE(8),  SAMS_CASE(9),  SAMS_CASE(10), SAMS_CASE(11), SAMS_CASE(12),
+                                                SAMS_CASE(13), SAMS_CASE(14), SAMS_CASE(15), SAMS_CASE(16)};
+#undef SAMS_CASE
+    SAMS_HIP(hipFuncSetAttribute(kernels[ctx->r - 1], hipFuncAttributeMaxDynamicSharedMemorySize, kEstLdsBytes));
+    return SAMS_OK;
+}
+
 int enqueue_estimate(sams_ctx *ctx, const float *S_mean, const float *vhat, float *est, const SelScratch *sc, bool *hist_done)
 {
     if (hist_done) *hist_done = false;
     const int block = 256;
     const int grid = grid_for(ctx->d, block);
-    // A small table under a short vector stays in every L2: r gathers per coordinate in one launch then beat the two
-    // launches of the plan-driven recovery (C1: 6 us against 23), which is made for tables far larger than any cache.
-    const bool small = (int64_t)ctx->r * ctx->c * 4 <= kGatherEstimateMaxTableBytes && ctx->d <= kGatherEstimateMaxD;
-    if (ctx->plan.mode == PLAN_BINNED && !ctx->pull.kernel && (ctx->tun.estimate_path == 2 || (ctx->tun.estimate_path == 0 && !small))) {
+    if (estimate_by_plan(ctx)) {
         bool done = false;
         SAMS_TRY(enqueue_estimates_planned_fused(ctx, S_mean, vhat, est, &done, sc));
         if (done) {
@@ -622,16 +649,13 @@ int enqueue_estimate(sams_ctx *ctx, const float *S_mean, const float *vhat, floa
         SAMS_HIP(hipGetLastError());
         return SAMS_OK;
     }
-    const int64_t row_bytes = ctx->c * 4;
-    const int32_t held = (int32_t)(kEstLdsBytes / row_bytes < ctx->r ? kEstLdsBytes / row_bytes : ctx->r);
-    if (ctx->d >= kEstLdsMinD && ctx->c >= 2 && held * kEstLdsMinShare >= ctx->r && ctx->tun.estimate_path != 1) {
+    if (const int32_t held = estimate_held_rows(ctx)) {
         const uint32_t m = (uint32_t)(((uint64_t)1 << 32) / (uint64_t)ctx->c);
         switch (ctx->r) {
 #define SAMS_CASE(R)                                                                                                             \
     case R: {                                                                                                                    \
-        SAMS_HIP(hipFuncSetAttribute((const void *)k_estimate_lds<R>, hipFuncAttributeMaxDynamicSharedMemorySize, kEstLdsBytes)); \
         ProfScope ps(ctx, KID_ESTIMATE);                                                                                         \
-        hipLaunchKernelGGL(k_estimate_lds<R>, dim3(grid_for(ctx->d, 1024, 256)), dim3(1024), (size_t)(held * row_bytes),        \
+        hipLaunchKernelGGL(k_estimate_lds<R>, dim3(grid_for(ctx->d, 1024, 256)), dim3(1024), (size_t)(held * ctx->c * 4),       \
                            ctx->stream, S_mean, vhat, est, ctx->hp, ctx->d, (int32_t)ctx->c, m, held);                           \
         break;                                                                                                                   \
     }
