@@ -29,7 +29,7 @@ extern int g_last_hip_error;
 constexpr int kWave = 64;
 constexpr int64_t kOrderedSingleBinMaxD = (int64_t)1 << 22;     // largest d sketched in order when c fits one window
 constexpr int kHistBins = 2048;     // first radix digit of the selection: 11 bits, then 10 and 10 (kHistBins / 2 bins)
-constexpr int64_t kSelSmallMax = 1 << 16;   // keys up to which the selection is one launch after the first histogram
+constexpr int64_t kSelSmallMax = 1 << 16;   // keys up to which the selection is one launch after the first histogram (for small k)
 
 // device-resident state of the radix selection (no host round trip inside a step).  A selection starts from histograms and
 // `done` of zeros and leaves them so; the next one clears them first where one failed half-way (sams_ctx::sel_open), and

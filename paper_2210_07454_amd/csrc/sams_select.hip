@@ -133,8 +133,8 @@ k_est_median(const float *__restrict__ rowest, const float *__restrict__ vhat, f
 // the selected ones and the candidates, about 1.5 k of them unless many keys are equal -- in coordinate order, every
 // tile of keys in a region of its own.  Everything after that works on the listed keys only (on all keys, without the filter,
 // where a context of more than 2^20 coordinates found no room for lists).
-//   up to 2^16 keys: k_sel_small filters, and its last workgroup finishes the selection
-//   more: k_sel_filter, two histograms of the listed keys, k_sel_count, k_sel_write
+//   up to 2^16 keys and small k (kSelSmallMaxK): k_sel_small filters, and its last workgroup finishes the selection
+//   else: k_sel_filter, two histograms of the listed keys, k_sel_count, k_sel_write
 // Up to 2^20 keys every filter workgroup picks the first digit from the histogram for itself (8 KiB, in every L2); above,
 // the last workgroup of the histogram does it once.
 // Code that one workgroup runs once is bound by its chain of latencies, fetching the instructions among them: it is kept
@@ -142,9 +142,11 @@ k_est_median(const float *__restrict__ rowest, const float *__restrict__ vhat, f
 // "Last workgroup" (last_workgroup) never waits: whoever draws the last number goes on, the others end.  Data that it
 // reads from other workgroups of the same launch goes through agent-scope atomic accesses, since the L2s of the eight
 // XCDs are not coherent with each other inside a launch.
-// Measured on MI355X: 65,536 keys 8 us (one workgroup with three sweeps over the keys: 28); 431,003 keys 29 us (ten
-// launches: 84), 11.2 million keys 35 us after the fused histogram (111), 4.96 million keys of which a quarter is kept
-// 63 us (136), 124 million keys 0.18 ms (0.41): what is left is the filter's pass over the keys and launches of 5 us.
+// Measured on MI355X, without the first histogram's pass where an estimate kernel takes it, in brackets ten launches over all
+// keys (up to 2^16 keys three sweeps by one workgroup): k = 1 % of 65,536 keys 8 us (28), of 431,003 29 us with the
+// histogram (84), of 11.2 million 35 us (111), of 124 million 0.18 ms (0.41): what is left is the filter's pass over the keys and
+// launches of 5 us.  By topk_refine, with the histogram: 65,536 keys, half of them kept 26 us (44); 431,003, half 30 us (63);
+// 4.96 million, a quarter 61 us (134), half 72 us (137), all 87 us (126).
 
 // The streaming passes of the selection read four consecutive keys per lane with one 16-byte load
 // (the entry points accept 16-byte aligned arrays only; the last, partial group of four is read key by key).  Absent keys
@@ -409,7 +411,7 @@ k_sel_filter(const float *__restrict__ keys, int64_t len, SelState *__restrict__
     }
 }
 
-constexpr int kSelWriteMaxTpw = 4;
+constexpr int kSelWriteMaxPpw = 4;
 __device__ __forceinline__ uint32_t listed(const SelList &ls, int64_t len, int64_t tile)
 {
     if (ls.cnt) return ls.cnt[tile];
@@ -417,31 +419,49 @@ __device__ __forceinline__ uint32_t listed(const SelList &ls, int64_t len, int64
     return rest < (1 << kSelTileLog2) ? (uint32_t)rest : 1u << kSelTileLog2;
 }
 
-// f(have, bits) for the listed keys of a tile, 64 at a time by one wavefront; four groups of 64 are fetched
-// together (clamped to the tile's count: in bounds)
+// What a wavefront takes at a time: a tile's list, or (SPLIT) one of 2^split pieces of it, whole groups of 64 but for the last
+// one's end.
+struct Piece {
+    int64_t at;    // first entry, in val and loc
+    uint32_t cnt;
+};
+template <bool SPLIT>
+__device__ __forceinline__ Piece piece_of(const SelList &ls, int64_t len, int64_t piece, int split)
+{
+    if constexpr (!SPLIT) return {piece << kSelTileLog2, listed(ls, len, piece)};
+    const int64_t tile = piece >> split;
+    const uint32_t sub = (uint32_t)piece & ((1u << split) - 1u), all = listed(ls, len, tile);
+    const uint32_t size = (((all + (1u << split) - 1u) >> split) + kWave - 1u) & ~(uint32_t)(kWave - 1);
+    const uint32_t lo = sub * size < all ? sub * size : all, hi = lo + size < all ? lo + size : all;
+    return {(tile << kSelTileLog2) + lo, hi - lo};
+}
+
+// f(have, bits) for the listed keys of a piece, 64 at a time by one wavefront; four groups of 64 are fetched
+// together (clamped to the piece's count: in bounds)
 template <typename F>
-__device__ __forceinline__ void each_listed(const SelList &ls, int64_t tile, uint32_t cnt, F f)
+__device__ __forceinline__ void each_listed(const SelList &ls, const Piece &pc, F f)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    const uint32_t *val = ls.val + (tile << kSelTileLog2);
+    const uint32_t *val = ls.val + pc.at;
 #pragma unroll 1
-    for (uint32_t e0 = 0; e0 < cnt; e0 += 4 * kWave) {
+    for (uint32_t e0 = 0; e0 < pc.cnt; e0 += 4 * kWave) {
         uint32_t w[4];
 #pragma unroll
         for (int z = 0; z < 4; ++z) {
             const uint32_t e = e0 + z * kWave + lane;
-            w[z] = val[e < cnt ? e : cnt - 1];
+            w[z] = val[e < pc.cnt ? e : pc.cnt - 1];
         }
 #pragma unroll
         for (int z = 0; z < 4; ++z)
-            if (e0 + z * kWave < cnt) f(e0 + z * kWave + lane < cnt, w[z]);
+            if (e0 + z * kWave < pc.cnt) f(e0 + z * kWave + lane < pc.cnt, w[z]);
     }
 }
 
 // histogram of digit 1 or 2 over the listed keys whose higher digits are the picked ones
+template <bool SPLIT>
 __global__ void __launch_bounds__(1024)
-k_sel_list_hist(SelState *__restrict__ st, uint32_t *__restrict__ hist, SelList ls, int64_t len, int64_t ntile, int digit,
-                uint32_t *__restrict__ clear)   // null, or the first digit's histogram, which the filter has read
+k_sel_list_hist(SelState *__restrict__ st, uint32_t *__restrict__ hist, SelList ls, int64_t len, int64_t pieces, int split,
+                int digit, uint32_t *__restrict__ clear)   // null, or the first digit's histogram, which the filter has read
 {
     __shared__ uint32_t lh[1024], part[16], sh[2];
     const int t = threadIdx.x;
@@ -452,8 +472,8 @@ k_sel_list_hist(SelState *__restrict__ st, uint32_t *__restrict__ hist, SelList 
     const uint32_t prefix = st->prefix[digit - 1];
     const int up = 30 - 10 * digit;
     const int64_t waves = (int64_t)gridDim.x * 16;
-    for (int64_t tile = (int64_t)blockIdx.x * 16 + t / kWave; tile < ntile; tile += waves)
-        each_listed(ls, tile, listed(ls, len, tile), [&](bool have, uint32_t bits) {
+    for (int64_t piece = (int64_t)blockIdx.x * 16 + t / kWave; piece < pieces; piece += waves)
+        each_listed(ls, piece_of<SPLIT>(ls, len, piece, split), [&](bool have, uint32_t bits) {
             const uint32_t key = bits & 0x7fffffffu;
             if (have && (key >> up) == prefix) atomicAdd(&lh[(key >> (up - 10)) & 1023u], 1u);
         });
@@ -462,21 +482,22 @@ k_sel_list_hist(SelState *__restrict__ st, uint32_t *__restrict__ hist, SelList 
     if (last_workgroup(&st->done[digit], gridDim.x, sh)) sel_pick<1024>(st, hist, digit, 0, part, sh);
 }
 
-// keys of a tile's list that exceed the threshold, and that equal it (uniform over the wavefront)
-__device__ __forceinline__ uint2 count_listed(const SelList &ls, int64_t tile, uint32_t cnt, uint32_t tau)
+// keys of a piece that exceed the threshold, and that equal it (uniform over the wavefront)
+__device__ __forceinline__ uint2 count_listed(const SelList &ls, const Piece &pc, uint32_t tau)
 {
     uint2 n = make_uint2(0u, 0u);
-    each_listed(ls, tile, cnt, [&](bool have, uint32_t bits) {
+    each_listed(ls, pc, [&](bool have, uint32_t bits) {
         n.x += (uint32_t)__popcll(__ballot(have && (bits & 0x7fffffffu) > tau));
         n.y += (uint32_t)__popcll(__ballot(have && (bits & 0x7fffffffu) == tau));
     });
     return n;
 }
 
-// A workgroup has 16 * tpw consecutive tiles, wavefront w the tiles tpw w ... tpw w + tpw - 1 of them.
+// A workgroup has 16 * ppw consecutive pieces, wavefront w the pieces ppw w ... ppw w + ppw - 1 of them.
 // k_sel_count: keys above and at the threshold per workgroup, to group[].
+template <bool SPLIT>
 __global__ void __launch_bounds__(1024)
-k_sel_count(const SelState *__restrict__ st, SelList ls, int64_t len, int64_t ntile, int tpw)
+k_sel_count(const SelState *__restrict__ st, SelList ls, int64_t len, int64_t pieces, int split, int ppw)
 {
     __shared__ uint32_t sum[2];
     const uint32_t tau = st->prefix[2];
@@ -484,10 +505,10 @@ k_sel_count(const SelState *__restrict__ st, SelList ls, int64_t len, int64_t nt
     if (threadIdx.x < 2) sum[threadIdx.x] = 0;
     __syncthreads();
     uint2 n = make_uint2(0u, 0u);
-    for (int q = 0; q < tpw; ++q) {
-        const int64_t tile = ((int64_t)blockIdx.x * 16 + wave) * tpw + q;
-        if (tile >= ntile) break;
-        const uint2 x = count_listed(ls, tile, listed(ls, len, tile), tau);
+    for (int q = 0; q < ppw; ++q) {
+        const int64_t piece = ((int64_t)blockIdx.x * 16 + wave) * ppw + q;
+        if (piece >= pieces) break;
+        const uint2 x = count_listed(ls, piece_of<SPLIT>(ls, len, piece, split), tau);
         n.x += x.x;
         n.y += x.y;
     }
@@ -500,20 +521,21 @@ k_sel_count(const SelState *__restrict__ st, SelList ls, int64_t len, int64_t nt
 }
 
 // k_sel_write: a workgroup adds up what the groups before it hold (every one for itself: a few hundred to two thousand pairs,
-// in place of a scan by one workgroup in between), counts its own tiles and writes their selected keys at their rank:
+// in place of a scan by one workgroup in between), counts its own pieces and writes their selected keys at their rank:
 // key > tau, or key == tau and among the first k_eq such keys.  map != null: the output is map[position] (below len, see
 // flat_write).
+template <bool SPLIT>
 __global__ void __launch_bounds__(1024)
-k_sel_write(const SelState *__restrict__ st, SelList ls, int64_t len, int64_t ntile, int tpw, int64_t k,
+k_sel_write(const SelState *__restrict__ st, SelList ls, int64_t len, int64_t pieces, int split, int ppw, int64_t k,
             const int32_t *__restrict__ map, int32_t *__restrict__ idx, float *__restrict__ val_sel)
 {
     __shared__ uint32_t part[16], sum[2];
-    __shared__ uint32_t tile_gt[16 * kSelWriteMaxTpw], tile_eq[16 * kSelWriteMaxTpw];
+    __shared__ uint32_t piece_gt[16 * kSelWriteMaxPpw], piece_eq[16 * kSelWriteMaxPpw];
     const uint32_t tau = st->prefix[2], k_eq = st->k_rem[2];
     const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
     const uint64_t below = ((uint64_t)1 << lane) - 1;
     if (t < 2) sum[t] = 0;
-    if (t < 16 * kSelWriteMaxTpw) tile_gt[t] = tile_eq[t] = 0;
+    if (t < 16 * kSelWriteMaxPpw) piece_gt[t] = piece_eq[t] = 0;
     __syncthreads();
     uint32_t g = 0, e = 0;
     for (uint32_t q = t; q < blockIdx.x; q += 1024) {
@@ -527,36 +549,44 @@ k_sel_write(const SelState *__restrict__ st, SelList ls, int64_t len, int64_t nt
         atomicAdd(&sum[0], g);
         atomicAdd(&sum[1], e);
     }
-    const int64_t first = ((int64_t)blockIdx.x * 16 + wave) * tpw;
-    for (int q = 0; q < tpw && first + q < ntile; ++q) {
-        const uint2 n = count_listed(ls, first + q, listed(ls, len, first + q), tau);
+    const int64_t first = ((int64_t)blockIdx.x * 16 + wave) * ppw;
+    for (int q = 0; q < ppw && first + q < pieces; ++q) {
+        const uint2 n = count_listed(ls, piece_of<SPLIT>(ls, len, first + q, split), tau);
         if (lane == 0) {
-            tile_gt[wave * tpw + q] = n.x;
-            tile_eq[wave * tpw + q] = n.y;
+            piece_gt[wave * ppw + q] = n.x;
+            piece_eq[wave * ppw + q] = n.y;
         }
     }
     __syncthreads();
-    const int nt = 16 * tpw;
-    const uint32_t own_g = t < nt ? tile_gt[t] : 0u, own_e = t < nt ? tile_eq[t] : 0u;
+    const int np = 16 * ppw;
+    const uint32_t own_g = t < np ? piece_gt[t] : 0u, own_e = t < np ? piece_eq[t] : 0u;
     const uint32_t before_g = block_exclusive_scan<1024>(own_g, part), before_e = block_exclusive_scan<1024>(own_e, part);
-    if (t < nt) {
-        tile_gt[t] = sum[0] + before_g;
-        tile_eq[t] = sum[1] + before_e;
+    if (t < np) {
+        piece_gt[t] = sum[0] + before_g;
+        piece_eq[t] = sum[1] + before_e;
     }
     __syncthreads();
-    for (int q = 0; q < tpw && first + q < ntile; ++q) {
-        const int64_t base = (first + q) << kSelTileLog2;
-        const uint32_t cnt = listed(ls, len, first + q);
-        uint32_t gtr = tile_gt[wave * tpw + q], eqr = tile_eq[wave * tpw + q];
+    for (int q = 0; q < ppw && first + q < pieces; ++q) {
+        const Piece pc = piece_of<SPLIT>(ls, len, first + q, split);
+        const int64_t base = (SPLIT ? (first + q) >> split : first + q) << kSelTileLog2;
+        const uint32_t cnt = pc.cnt;
+        uint32_t gtr = piece_gt[wave * ppw + q], eqr = piece_eq[wave * ppw + q];
 #pragma unroll 1
         for (uint32_t e0 = 0; e0 < cnt; e0 += 4 * kWave) {
-            uint32_t bits[4];
+            uint32_t bits[4], at[4];
             int32_t l[4];
 #pragma unroll
             for (int z = 0; z < 4; ++z) {
-                const uint32_t en = e0 + z * kWave + lane, at = en < cnt ? en : cnt - 1;
-                bits[z] = ls.val[base + at];
-                l[z] = (int32_t)(base + (ls.loc ? (uint32_t)ls.loc[base + at] : at));
+                const uint32_t en = e0 + z * kWave + lane;
+                at[z] = en < cnt ? en : cnt - 1;
+                bits[z] = ls.val[pc.at + at[z]];
+            }
+            if (ls.loc) {
+#pragma unroll
+                for (int z = 0; z < 4; ++z) l[z] = (int32_t)(base + ls.loc[pc.at + at[z]]);
+            } else {
+#pragma unroll
+                for (int z = 0; z < 4; ++z) l[z] = (int32_t)(pc.at + at[z]);
             }
             if (map) {
 #pragma unroll
@@ -705,6 +735,15 @@ SelScratch ctx_sel_scratch(const sams_ctx *ctx)
     return SelScratch{reinterpret_cast<SelState *>(ctx->sel), ctx->sel + kSelStateWords, ls, nt, ctx->sel_cap};
 }
 
+// Up to 2^16 keys, the largest k for which k_sel_small's last workgroup finishes by itself: it takes 2 us per thousand listed
+// keys, where the other kernels take 26 us whatever the lists hold.  Both (topk_refine): 20,000 keys, k = 5,000 17 and 26 us,
+// 10,000 30 and 26 us; 65,536 keys, k = 8,192 25 and 26 us, 16,384 43 and 26 us, 65,536 142 and 26 us.
+constexpr int64_t kSelSmallMaxK = 1 << 13;
+// Tiles' lists are cut into pieces of at least 256 entries (about 1.5 k are listed) while there are fewer than 16 wavefronts for
+// each of the 256 compute units.  Whole lists and pieces: 100,000 keys, k = 50,000 54 and 26 us; a million, half of them 62 and
+// 33 us, an eighth 36 and 31 us; 4.96 million, half 82 and 72 us; with more pieces than that 30 million keys, half, take 350
+// instead of 235 us.
+constexpr int64_t kSelMaxPieces = 4096;
 bool sel_hist_picks(int64_t len) { return len > kSelHistPickMin; }
 
 int enqueue_select(sams_ctx *ctx, hipStream_t stream, const SelScratch &sc, const float *keys, int64_t len, int64_t k,
@@ -719,7 +758,7 @@ int enqueue_select(sams_ctx *ctx, hipStream_t stream, const SelScratch &sc, cons
             SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, k_sel_hist<false>, grid_for(len, 4096, kHistMaxGrid), 1024, keys, len,
                            (uint32_t)k, sc.st, sc.hist);
     }
-    if (len <= kSelSmallMax) {
+    if (len <= kSelSmallMax && k <= kSelSmallMaxK) {
         SAMS_LAUNCH_ON(ctx, stream, KID_SEL_SMALL, k_sel_small, grid_for(len, 1 << kSelTileLog2), 1024, keys, len, sc.st,
                        sc.hist, sc.list, k, map, idx, val_sel);
         SAMS_HIP(hipGetLastError());
@@ -727,9 +766,12 @@ int enqueue_select(sams_ctx *ctx, hipStream_t stream, const SelScratch &sc, cons
     }
     const int64_t nt = (len + (1 << kSelTileLog2) - 1) >> kSelTileLog2;
     if (nt > sc.ntile_cap) return SAMS_EINVAL;
-    const int lgrid = grid_for(nt, 16, 128);
-    const int tpw = nt > 16384 ? kSelWriteMaxTpw : 1;                // at most a few thousand groups for a workgroup to add up
-    const int wgrid = grid_for(nt, 16 * tpw);
+    int split = 0;
+    while (split < 4 && (3 * k / 2 / nt >> split) > 4 * kWave && nt << split < kSelMaxPieces) ++split;
+    const int64_t pieces = nt << split;
+    const int lgrid = grid_for(pieces, 16, 128);
+    const int ppw = pieces > 16384 ? kSelWriteMaxPpw : 1;            // at most a few thousand groups for a workgroup to add up
+    const int wgrid = grid_for(pieces, 16 * ppw);
     SelList ls = sc.list;
     if (len > sc.cap)                                                // above kSelHistPickMin, so the digit has been picked
         ls = {reinterpret_cast<uint32_t *>(const_cast<float *>(keys)), nullptr, nullptr, sc.list.group};   // read only
@@ -739,11 +781,14 @@ int enqueue_select(sams_ctx *ctx, hipStream_t stream, const SelScratch &sc, cons
     else
         SAMS_LAUNCH_ON(ctx, stream, KID_SEL_FILTER, k_sel_filter<true>, (unsigned)nt, 1024, keys, len, sc.st, sc.hist, sc.list,
                        (uint32_t)k);
-    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, k_sel_list_hist, lgrid, 1024, sc.st, hist1, ls, len, nt, 1,
-                   sel_hist_picks(len) ? nullptr : sc.hist);
-    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, k_sel_list_hist, lgrid, 1024, sc.st, hist2, ls, len, nt, 2, nullptr);
-    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_COUNT, k_sel_count, wgrid, 1024, sc.st, ls, len, nt, tpw);
-    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_WRITE, k_sel_write, wgrid, 1024, sc.st, ls, len, nt, tpw, k, map, idx, val_sel);
+    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, (split ? k_sel_list_hist<true> : k_sel_list_hist<false>), lgrid, 1024, sc.st, hist1, ls, len,
+                   pieces, split, 1, sel_hist_picks(len) ? nullptr : sc.hist);
+    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, (split ? k_sel_list_hist<true> : k_sel_list_hist<false>), lgrid, 1024, sc.st, hist2, ls, len,
+                   pieces, split, 2, nullptr);
+    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_COUNT, (split ? k_sel_count<true> : k_sel_count<false>), wgrid, 1024, sc.st, ls, len, pieces, split,
+                   ppw);
+    SAMS_LAUNCH_ON(ctx, stream, KID_SEL_WRITE, (split ? k_sel_write<true> : k_sel_write<false>), wgrid, 1024, sc.st, ls, len, pieces, split,
+                   ppw, k, map, idx, val_sel);
     SAMS_HIP(hipGetLastError());
     return SAMS_OK;
 }
