@@ -340,10 +340,11 @@ k_pull_sum(const float *__restrict__ part, float *__restrict__ S, int64_t cells,
 // ------------------------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------------------------
-// Whether this shape pulls, and into how many windows.  Tables of 128 to 2^14 buckets under vectors of up to 2^26
+// Whether this shape pulls (if its lists turn out short enough, see pull_slower), and into how many windows.  Tables of 128 to 2^14 buckets under vectors of up to 2^26
 // coordinates.  With fewer buckets a bucket's list gets too long to sort by insertion at creation, with more the lists of a
 // tile's 64 buckets get too uneven (on average one entry with 2^14 buckets, the longest of 64 four); the lists of
 // longer vectors take gigabytes.
+constexpr int64_t kPullLongD = 1000000;       // shorter vectors always pull: both paths are launches and latencies
 static bool pull_shape(const sams_ctx *ctx, const Tunables &tun, PullPlan &pp)
 {
     if (tun.sketch_path != 0 || tun.estimate_path == 2 || tun.win_log2 || tun.tile_log2 || tun.chunk_log2 || tun.acc_threads ||
@@ -352,10 +353,11 @@ static bool pull_shape(const sams_ctx *ctx, const Tunables &tun, PullPlan &pp)
     if (ctx->c < 128 || ctx->c > (1 << 14) || ctx->d > ((int64_t)1 << 26) || (int64_t)ctx->n * ctx->d < 4) return false;
     pp.nslice = (int32_t)((ctx->c + kWave - 1) / kWave);
     pp.ntile = (int32_t)((ctx->d + kPullTile - 1) / kPullTile);
-    // A workgroup takes in a tile per `step`, one workgroup per compute unit: the cost is tiles per workgroup (and about
-    // twelve that starting and ending takes) times rounds of 256 workgroups.  Two or four slices per wavefront are fewer windows, and
-    // so fewer rounds; the vector is cut into parts where the order of the additions is not promised (d > 2^22).  Ties
-    // go to fewer slices and parts.
+    // One workgroup per compute unit: the cost is taken to be tiles per workgroup (and about twelve that starting and ending takes)
+    // times rounds of 256 workgroups.  Two or four slices per wavefront are fewer windows, and so fewer rounds; the vector is
+    // cut into parts where the order of the additions is not promised (d > 2^22).  Ties go to fewer slices and parts.
+    // The steps of the lists, whose number no choice here changes but which a workgroup with more slices has more of, are not
+    // in it.
     const int64_t pairs = (int64_t)ctx->n * ctx->r;
     const int32_t most_parts = ctx->d > kOrderedSingleBinMaxD ? 128 : 1;
     int64_t best = INT64_MAX, nwin = 1;
@@ -376,7 +378,30 @@ static bool pull_shape(const sams_ctx *ctx, const Tunables &tun, PullPlan &pp)
     pp.nwin = (pp.nslice + pp.per_win - 1) / pp.per_win;
     pp.per_part = (pp.ntile + pp.parts - 1) / pp.parts;
     pp.parts = (pp.ntile + pp.per_part - 1) / pp.per_part;           // none is empty
+    // The binned path cuts a table of up to 2^12 buckets into windows of 2^7 until it has 1024 workgroups: with few pairs under
+    // a long vector many short streams, where every puller has to take in the whole vector.  In ns: 820 per tile here; there a
+    // base, 0.67 per position of a window's stream, 1.6 per thousand terms through staging.  Lists and bins (us), one pair of 4,096
+    // buckets: d = 431,003 25 and 28, a million 67 and 40, four million 257 and 109; 2 x 3 of 3,000, four million 256 and
+    // 174; 4 x 5 of 4,096, four million 290 and 256, a million 76 and 85; 2 x 5 of 2,000, four million 264 and 263.
+    if (ctx->d >= kPullLongD && ctx->d <= kOrderedSingleBinMaxD && ctx->c <= (1 << 12)) {
+        const int64_t bins = 25000 + 86 * ctx->d / ctx->c + pairs * ctx->d * 16 / 10000, here = best * 820;
+        if (pairs * ((ctx->c + 127) / 128) < 2048 && bins < here) return false;
+    }
     return true;
+}
+
+// Whether the other path is faster with lists of this many steps.  A tile takes a workgroup 0.64 us and 5.1 ns per step; with many
+// pairs and more than 2^13 buckets, several rounds of workgroups with up to 56 slices each, that can exceed the 2 us per
+// million terms of the binned path (or, above 2^22 coordinates, of LDS atomics).  Both (ms): 5 x 16,384, n = 50, d = four
+// million 2.39 and 1.93, ten million 7.2 and 4.9; 5 x 9,001 (a row whose lists are half padding), n = 32, five million
+// 2.79 and 2.21; 5 x 12,000, n = 50, four million 1.78 and 1.94.
+static bool pull_slower(const sams_ctx *ctx, const PullPlan &pp, int64_t steps)
+{
+    const int64_t pairs = (int64_t)ctx->n * ctx->r;
+    if (ctx->d < kPullLongD || ctx->c <= (1 << 13) || pairs < 160) return false;
+    const int64_t rounds = (pairs * pp.nwin * pp.parts + 255) / 256;
+    const int64_t here = rounds * pp.per_part * 640 + rounds * pp.per_part * 51 / 10 * steps / ((int64_t)ctx->r * pp.nwin * pp.ntile);
+    return here > 25000 + 2 * pairs * ctx->d / 1000;
 }
 
 static PullOrder pull_order(const PullPlan &pp)
@@ -438,7 +463,7 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
         }
         // A hash that crowds a tile's coordinates into few buckets makes long or mostly empty lists: not for this path.
         const uint64_t steps = run * 2 * group * kWave, fair = 12ull * (uint64_t)ctx->r * (uint64_t)ctx->d + 8ull * kWave * lists;
-        if (h_longest > kPullMaxList || steps > fair || run >= (1ull << 31)) break;
+        if (h_longest > kPullMaxList || steps > fair || run >= (1ull << 31) || pull_slower(ctx, pp, (int64_t)(run * 2 * group))) break;
         h_first[streams] = (uint32_t)run;
         h_off[lists] = (uint32_t)run;
         pp.list_bytes = (int64_t)(run * group + kPullSpare) * kWave * 4;
