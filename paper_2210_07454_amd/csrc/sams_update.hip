@@ -391,15 +391,18 @@ int enqueue_tail(sams_ctx *ctx, float *x, const int32_t *idx, const float *delta
     return SAMS_OK;
 }
 
+constexpr int64_t kUpdateLong = (int64_t)1 << 25;    // entries of g
 int enqueue_update(sams_ctx *ctx, const float *g, float *m, float *e_u, float *v, float *vhat, float *x, const int32_t *idx,
                    const float *delta, int64_t k_sel, float beta1, float beta2, float lr, float rho, bool pa)
 {
     const int64_t ntile = (ctx->d + 1023) / 1024;
-    // Enough workgroups for a few per compute unit: the workers of a tile are shared out when there are few tiles.  With
-    // per-worker second moments a worker is traffic enough for the search to be hidden (n = 8, d = 11.2 million: 589 us,
-    // 635 with all workers of a tile in one workgroup; the other way round without them, 107 and 96 us at 3 million).
+    // Enough workgroups for a few per compute unit: the workers of a tile are shared out when there are few tiles.  A worker is
+    // also traffic enough for the search to be hidden with per-worker second moments (n = 8, d = 11.2 million: 589 us, 635 with all
+    // workers of a tile in one workgroup), and once g, m and e are more than the 256 MB Infinity Cache: the workgroups under
+    // way then go through one worker's arrays instead of all (n = 8: 11.2 million 380 and 440 us, 124 million 4.2 and 4.8 ms;
+    // n = 33, three million 376 and 416 us; n = 3, 11.2 million 182 and 189 us; below, n = 8, 103 and 95 us at three million).
     int64_t ny = (2048 + ntile - 1) / ntile;
-    if (ny > ctx->n || pa) ny = ctx->n;
+    if (ny > ctx->n || pa || ctx->n * ctx->d >= kUpdateLong) ny = ctx->n;
     const int32_t wchunk = (int32_t)((ctx->n + ny - 1) / ny);
     ny = (ctx->n + wchunk - 1) / wchunk;
     const int64_t per_sparse = pa || ctx->n < kWideMinWorkers ? 256 : kWideCoords;

@@ -56,12 +56,15 @@ def test_ragged_vectors_fuse_the_head_only_where_that_is_faster():
     assert not fused(long - 1, 1, 2, 40_000, False) and not fused(long + 1, 1, 2, 40_000, True)
 
 
-@pytest.mark.parametrize("d,n,r,c,k", [((1 << 24) + 1, 3, 2, 70_001, 20_000), ((1 << 24) + 8_195, 2, 7, 200_003, 3_000)])
-def test_long_ragged_vectors_with_the_fused_head(d, n, r, c, k):
-    """tiles of 2^14 and of 2^13 (half of the fused head's turns), a last tile of one coordinate and of three"""
+@pytest.mark.parametrize("d,n,r,c,k,fuse_head", [
+    ((1 << 24) + 1, 3, 2, 70_001, 20_000, 2), ((1 << 24) + 8_195, 2, 7, 200_003, 3_000, 2),
+    ((1 << 24) + 1, 2, 1, 70_001, 20_000, 0), (1 << 23, 4, 1, 70_001, 20_000, 0), ((1 << 23) - 1, 4, 1, 70_001, 20_000, 0)])
+def test_long_ragged_vectors(d, n, r, c, k, fuse_head):
+    """the fused head: tiles of 2^14 and of 2^13 (half of its turns), a last tile of one coordinate and of three; the separate
+    one: a worker per workgroup, and all workers"""
     from paper_2210_07454_amd import sams
     try:
-        sams.sams_configure("fuse_head", 2)
+        sams.sams_configure("fuse_head", fuse_head)
         assert one_iteration(sams, (d, n, r, c, k), seed=d % 97)
     finally:
         sams.sams_configure("fuse_head", 0)
