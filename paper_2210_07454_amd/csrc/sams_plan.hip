@@ -427,15 +427,18 @@ k_plan_records(const uint32_t *__restrict__ meta, uint32_t *__restrict__ rec, in
 // group's plan metadata is still in the XCD's L2 when the next worker needs it (see scatter_group).
 __device__ __forceinline__ void tile_and_worker(int64_t per, int32_t n, int32_t group, int64_t *tile, int32_t *worker)
 {
-    const int64_t slot = blockIdx.x / kNumXcd, g = slot / ((int64_t)group * n), in = slot % ((int64_t)group * n);
-    const int64_t size = per - g * group < group ? per - g * group : group;   // the last group may be smaller
-    *worker = (int32_t)(in / size);
-    *tile = (int64_t)(blockIdx.x % kNumXcd) + kNumXcd * (g * group + in % size);
+    const uint32_t slot = blockIdx.x / kNumXcd, all = (uint32_t)group * (uint32_t)n, g = slot / all, in = slot - g * all;
+    const uint32_t first = g * (uint32_t)group, rest = (uint32_t)per - first;
+    const uint32_t size = rest < (uint32_t)group ? rest : (uint32_t)group, w = in / size;   // the last group may be smaller
+    *worker = (int32_t)w;
+    *tile = (int64_t)(blockIdx.x % kNumXcd) + kNumXcd * (int64_t)(first + (in - w * size));
 }
 
 // A thread owns 4 consecutive slots (always inside
 // one group of G >= 4 slots, hence one run): one 8-byte load of their sources, one 4-byte load of the group's
 // stream position, 4 LDS reads and one 16-byte store -- nothing depends on another global load.
+// STREAM: u is read with streaming loads (see scatter_streams).
+template <bool STREAM>
 __global__ void __launch_bounds__(1024)
 k_bin_scatter(const float *__restrict__ u, const uint16_t *__restrict__ srcp, const uint32_t *__restrict__ dst16,
               const uint32_t *__restrict__ pbase, float *__restrict__ stg, int32_t n, RowGroup rg, int64_t d,
@@ -462,7 +465,8 @@ k_bin_scatter(const float *__restrict__ u, const uint16_t *__restrict__ srcp, co
         for (int p = threadIdx.x * 4; p < top; p += blockDim.x * 4) {
             float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
             if (p + 4 <= lim) {
-                q = load_stream(reinterpret_cast<const float4 *>(src + p));
+                const float4 *at = reinterpret_cast<const float4 *>(src + p);
+                q = STREAM ? load_stream(at) : *at;
             } else {                                                 // the last, partial group of u
                 q.x = src[p];
                 if (p + 1 < lim) q.y = src[p + 1];
@@ -1784,7 +1788,8 @@ int plan_create(sams_ctx *ctx, const Tunables &tun)
         if (!h_total || !h_base || !h_tile) { rc = SAMS_ENOMEM; break; }
         hipError_t e = hipFuncSetAttribute((const void *)k_plan_sort, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
         if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_plan_chain, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_bin_scatter, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_bin_scatter<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_bin_scatter<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
         if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_head_scatter<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
         if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_head_scatter<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
         if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_head_scatter_w<false, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
@@ -1948,16 +1953,28 @@ int64_t plan_staging_words(const sams_ctx *ctx)
     return ctx->plan.stg ? (int64_t)ctx->n * ctx->plan.stage_rows * ctx->plan.rowlen : 0;
 }
 
+static int64_t plan_metadata_bytes(const Plan &pl) { return (pl.rowlen * 2 + (pl.rowlen >> pl.grp_log2) * 4) * pl.rows; }
+
 // Tiles of an XCD that pass 1 takes worker by worker (tile_and_worker): as many as have their plan metadata (2.25 bytes per
 // slot and row) in 3 MB, three quarters of the XCD's L2, but no more than 16 -- for 2^14 coordinates and five rows; with 64,
 // pass 1 with the head takes 8.0 instead of 7.2 ms at d = 124 million, with 24 of 2^13 3.40 instead of 3.36 at 25.6 million.  When the whole plan's metadata fits in half the 256 MB
 // Infinity Cache it comes from there, and groups of 64 are better (0.73 and 0.79 ms at 11.2 million).
 static int32_t scatter_group(const Plan &pl)
 {
-    const int64_t row_bytes = pl.rowlen * 2 + (pl.rowlen >> pl.grp_log2) * 4, all = row_bytes * pl.rows;
+    const int64_t all = plan_metadata_bytes(pl);
     const int64_t per_tile = all / pl.ntile + 1, cached = all <= ((int64_t)128 << 20);
     const int64_t want = (cached ? 12 : 3) * 1000000 / per_tile, most = cached ? 4096 : 16;
     return (int32_t)(want < 1 ? 1 : (want > most ? most : want));
+}
+
+// Whether pass 1 by itself reads u with streaming loads.  A vector that the update has left in the Infinity Cache is better read
+// through the L2s, as long as it does not push out the plan's metadata: the line lies where u and four times the metadata
+// fill the 256 MB.  Streaming and plain (pass 1, us): d = 222,390, n = 27 38 and 30; a million, n = 8 55 and 43, n = 33 166 and
+// 137, n = 45 224 and 193, n = 60 291 and 289; three million, n = 8 124 and 105 (in groups of 16 tiles; 115 in groups of 64),
+// n = 16 240 and 244; six million, n = 5 166 and 171.
+static bool scatter_streams(const sams_ctx *ctx)
+{
+    return (int64_t)ctx->n * ctx->d * 4 + 4 * plan_metadata_bytes(ctx->plan) > ((int64_t)256 << 20);
 }
 
 bool head_compacts_g(const sams_ctx *ctx) { return ctx->wordrank != nullptr && ctx->gsel != nullptr; }
@@ -2047,9 +2064,11 @@ int enqueue_sketch_planned(sams_ctx *ctx, const float *u, float *S_workers)
         const RowGroup rg = {j0, (ctx->r - j0) < pl.stage_rows ? (ctx->r - j0) : pl.stage_rows, pl.stage_rows, ctx->r, pl.stage_ilv};
         if (j0 > 0 || pl.staged_u != u) {                            // not staged by a fused head: pass 1 now
             ProfScope ps(ctx, KID_BIN_SCATTER);
-            hipLaunchKernelGGL(k_bin_scatter, dim3((unsigned)(per * kNumXcd * ctx->n)), dim3((unsigned)ctx->tun.scatter_threads),
+            const bool stream = scatter_streams(ctx);
+            const int32_t group = scatter_group(pl);
+            hipLaunchKernelGGL((stream ? k_bin_scatter<true> : k_bin_scatter<false>), dim3((unsigned)(per * kNumXcd * ctx->n)), dim3((unsigned)ctx->tun.scatter_threads),
                                (size_t)(L * 4 + 16), ctx->stream, u, pl.srcp, pl.dst16, pl.pbase, pl.stg, ctx->n, rg,
-                               ctx->d, pl.tile_log2, pl.ntile, pl.rowlen, pl.grp_log2, scatter_group(pl));
+                               ctx->d, pl.tile_log2, pl.ntile, pl.rowlen, pl.grp_log2, stream || group < 16 ? group : 16);
         }
         SAMS_HIP(hipGetLastError());
         SAMS_TRY(dispatch_acc(ctx, S_workers, rg, false));
