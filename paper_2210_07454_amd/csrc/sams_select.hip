@@ -613,12 +613,7 @@ k_sel_write(const SelState *__restrict__ st, SelList ls, int64_t len, int64_t pi
     }
 }
 
-// k_estimate_lds where it pays for filling the LDS, against gathers of all rows: d = 25.6 million, 5 x 10,000 432 and 129 us,
-// 10 x 4,000 604 and 250 us, 5 x 32,000 (one row held) 440 and 402 us; d = 4 million, 5 x 10,000 72 and 30 us, 5 x 40,000
-// (one row held) 76 us both; d = 1 million, 5 x 400 8 us both, 5 x 10,000 20 and 12 us; d = 431,003, 4 x 9,001 7 and 10 us.
 constexpr int kEstLdsBytes = 160 * 1024;
-constexpr int64_t kEstLdsMinD = (int64_t)1 << 20;
-constexpr int kEstLdsMinShare = 5;                                   // at least a fifth of the rows held
 constexpr int64_t kGatherEstimateMaxTableBytes = 1 << 20, kGatherEstimateMaxD = (int64_t)1 << 22;
 
 // Whether stage 3 goes through the plan.  A small table under a short vector stays in every L2: r gathers per coordinate in
@@ -630,11 +625,23 @@ static bool estimate_by_plan(const sams_ctx *ctx)
     return ctx->plan.mode == PLAN_BINNED && !ctx->pull.kernel && (ctx->tun.estimate_path == 2 || (ctx->tun.estimate_path == 0 && !small));
 }
 
-// rows that k_estimate_lds holds, 0 = it is not used
+// Rows that k_estimate_lds holds, 0 = it is not used.  It has to fill its LDS and to compute more per coordinate than the
+// gathers wait for while their table stays in the 32 KB L1s; rows that it has no room for cost it more than the gathers.
+// k_estimate_lds and gathers (us):
+//   whole table held, d = 1 million (6 million): 5 x 9,001 11 and 19 (41 and 105), 3 x 5,000 7 and 8 (27 and 39), 5 x 2,406 8 and 8 (33 and 46),
+//     5 x 1,000 8 and 8 (32 and 35), at two million 15 and 14; 7 x 2,406 at 1.1 million 16 and 14, at 1.5 17 and 18; 16 x 1,000
+//     26 and 23 (119 and 125); 1 x 5,000 5 and 5 (18 and 16), 1 x 16,384 6 and 6 (21 and 28), 1 x 40,000 8 and 5 (36 and 22)
+//   two rows held: 5 x 16,384 18 and 22 (78 and 118), 10 x 16,384 at 1.5 million 59 and 50, at three million 89 and 101
+//   one: 3 x 32,768 16 and 15 (96 and 72), at 25.6 million 249 and 283
 static int32_t estimate_held_rows(const sams_ctx *ctx)
 {
+    const int64_t table = ctx->r * ctx->c * 4, million = 1000000;
     const int32_t held = (int32_t)(kEstLdsBytes / (ctx->c * 4) < ctx->r ? kEstLdsBytes / (ctx->c * 4) : ctx->r);
-    const bool used = ctx->d >= kEstLdsMinD && ctx->c >= 2 && held * kEstLdsMinShare >= ctx->r && ctx->tun.estimate_path != 1;
+    int64_t least;                                                   // the shortest vector
+    if (held == ctx->r) least = table > 56 * 1024 && ctx->c > 2000 ? (ctx->c > 4096 ? million : 3 * million / 2) : 6 * million;
+    else if (held >= 2) least = held * 3 >= ctx->r ? million : 3 * million;
+    else least = 12 * million;
+    const bool used = ctx->d >= least && ctx->c >= 2 && held * 5 >= ctx->r && (ctx->r > 1 || (ctx->c > 8192 && ctx->c <= 24576)) && ctx->tun.estimate_path != 1;
     return used && !estimate_by_plan(ctx) ? held : 0;
 }
 
