@@ -1421,6 +1421,15 @@ static int fused_median_iters(int32_t r, int tile_log2)
     if (r <= SAMS_MAX_ROWS && tile_log2 <= 12) return 1;
     return 0;
 }
+// Vectors of a length that is no multiple of four, whose recovery has the choice (the others' contexts have no room for the row
+// estimates): many workgroups with small tiles leave most of the 1024 threads of the fused kernel idle, row after row.  Fused
+// and apart, with the selection that follows (us): 586 tiles of 2^9 (d = 300,001, n = 2) 5 rows 71 and 54; 537 of 2^11 (1.1 million)
+// 79 and 72; 910 of 2^12 (3.7 million) 137 and 130, 1 row 63 and 71; 171 of 2^12 (700,001, n = 8) 52 and 61; 134 of 2^13
+// (1.1 million) 58 and 75; 16 rows, 269 of 2^12 161 and 131, 171 of 2^12 96 and 102.
+static bool collect_apart(int32_t r, int tile_log2, int64_t ntile)
+{
+    return r > 1 && tile_log2 <= 12 && ntile > 256;
+}
 // (rows, ITERS) pairs that are instantiated: the ITERS fused_median_iters gives for that many rows
 #define SAMS_FUSED_MEDIAN_VARIANTS(X)                                                              \
     X(1, 4) X(2, 4) X(3, 4) X(4, 4) X(5, 4) X(6, 4) X(7, 2) X(8, 2) X(9, 2) X(10, 2) X(11, 2) X(12, 2) \
@@ -1923,7 +1932,8 @@ int plan_create(sams_ctx *ctx, const Tunables &tun)
         if (rc != SAMS_OK) rc = dev_alloc(ctx, (void **)&pl.stg, stg_bytes);
         // the median is fused when a thread can hold the row estimates of its coordinates and the staging
         // buffer can hold the looked-up values of all r rows; otherwise they go through rowest
-        pl.fused_median = tun.fuse_median && fused_median_iters(ctx->r, pl.tile_log2) > 0 && n * pl.stage_rows >= r;
+        pl.fused_median = tun.fuse_median && fused_median_iters(ctx->r, pl.tile_log2) > 0 && n * pl.stage_rows >= r &&
+                          !((ctx->d & 3) != 0 && collect_apart(ctx->r, pl.tile_log2, pl.ntile));
         if (rc == SAMS_OK && !pl.fused_median) rc = dev_alloc(ctx, (void **)&pl.rowest, r * ctx->d * 4);
         if (rc != SAMS_OK) break;
     } while (0);

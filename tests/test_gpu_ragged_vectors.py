@@ -85,3 +85,21 @@ def test_room_for_the_compacted_gradients_only_where_the_head_fuses(d, c, extra)
     finally:
         sams.sams_configure("fuse_head", 0)
     assert size[2] - size[0] == (4 * n * k + (d + 31) // 32 * 4 if extra else 0)
+
+
+@pytest.mark.parametrize("d,n,r,c,k,apart", [(300_001, 2, 3, 40_000, 700, True), (300_003, 2, 16, 40_000, 3_000, True),
+                                             (1_100_001, 5, 4, 90_000, 11_000, False)])
+def test_recovery_of_ragged_vectors(d, n, r, c, k, apart):
+    """row estimates through memory where the tiles are many and small, in registers elsewhere: one iteration bit for bit"""
+    import torch
+    from paper_2210_07454_amd import inputs, sams
+    try:
+        sams.sams_configure("estimate_path", 2)
+        assert one_iteration(sams, (d, n, r, c, k), seed=d % 97)
+        with sams.Context(d, n, r, c, k, inputs.hash_params(r)) as ctx:
+            ctx.sams_profile_enable(True)
+            ctx.unsketch_estimates(torch.ones(r, c, device="cuda"), None, torch.empty(d, device="cuda"))
+            ctx.sams_profile_enable(False)
+            assert ("k_est_median" in ctx.sams_profile_read()) == apart
+    finally:
+        sams.sams_configure("estimate_path", 0)
