@@ -88,7 +88,7 @@ def test_room_for_the_compacted_gradients_only_where_the_head_fuses(d, c, extra)
 
 
 @pytest.mark.parametrize("d,n,r,c,k,apart", [(300_001, 2, 3, 40_000, 700, True), (300_003, 2, 16, 40_000, 3_000, True),
-                                             (1_100_001, 5, 4, 90_000, 11_000, False)])
+                                             (1_100_001, 8, 4, 90_000, 11_000, False)])
 def test_recovery_of_ragged_vectors(d, n, r, c, k, apart):
     """row estimates through memory where the tiles are many and small, in registers elsewhere: one iteration bit for bit"""
     import torch
