@@ -424,10 +424,13 @@ int enqueue_reduce(sams_ctx *ctx, const float *S_workers, float *S_mean)
     // memory latencies (n = 100: 14 us)
     if ((rc & 3) == 0 && rc >= 4 * 256 * 256)
         SAMS_LAUNCH(ctx, KID_REDUCE, (k_reduce<4, 8>), grid_for(rc / 4, 256, 1 << 16), 256, S_workers, S_mean, ctx->n, rc);
-    else if (ctx->n <= 9)
-        SAMS_LAUNCH(ctx, KID_REDUCE, (k_reduce<1, 8>), grid_for(rc, 256, 1 << 16), 256, S_workers, S_mean, ctx->n, rc);
-    else
-        SAMS_LAUNCH(ctx, KID_REDUCE, (k_reduce<1, 32>), grid_for(rc, 256, 1 << 16), 256, S_workers, S_mean, ctx->n, rc);
+    else {
+        // about as many tables in flight as there are: in place of those past the last one it is read again (n = 2, 7 x 262,143 4.2
+        // and 7.7 us with one and eight, n = 10, 5 x 1,048,577 37 and 54 us with 16 and 32)
+        const auto kernel = ctx->n <= 2 ? k_reduce<1, 1> : ctx->n <= 3 ? k_reduce<1, 2> : ctx->n <= 9 ? k_reduce<1, 8>
+                            : ctx->n <= 17 ? k_reduce<1, 16> : k_reduce<1, 32>;
+        SAMS_LAUNCH(ctx, KID_REDUCE, kernel, grid_for(rc, 256, 1 << 16), 256, S_workers, S_mean, ctx->n, rc);
+    }
     SAMS_HIP(hipGetLastError());
     return SAMS_OK;
 }

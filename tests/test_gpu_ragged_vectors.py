@@ -103,3 +103,17 @@ def test_recovery_of_ragged_vectors(d, n, r, c, k, apart):
             assert ("k_est_median" in ctx.sams_profile_read()) == apart
     finally:
         sams.sams_configure("estimate_path", 0)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 9, 10, 17, 18, 33])
+@pytest.mark.parametrize("r,c", [(3, 333), (3, 100_001), (4, 70_001)])
+def test_mean_of_any_number_of_tables(n, r, c):
+    import numpy as np
+    import torch
+    from oracle import Oracle
+    from paper_2210_07454_amd import inputs, sams
+    S = np.random.default_rng(n).standard_normal((n, r, c)).astype(np.float32)
+    mean = torch.empty(r, c, device="cuda")
+    with sams.Context(1_000, n, r, c, 1, inputs.hash_params(r)) as ctx:
+        ctx.sketch_reduce(torch.from_numpy(S).cuda(), mean)
+    assert np.array_equal(mean.cpu().numpy(), Oracle("f32").sketch_mean(S))
