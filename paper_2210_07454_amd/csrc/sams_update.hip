@@ -77,9 +77,9 @@ __global__ void k_tail_zero_e(const int32_t *__restrict__ idx, const float *__re
 
 // Tail and dense head in one launch, when the head is not fused with the first sketch pass.  Two kinds of workgroups:
 //   dense   1024 coordinates of `wchunk` workers: m and u (over e), e taken as zero on I_t, whose members it finds in the
-//           ascending idx; the workgroups of the first workers also have v and vhat off I_t.  Alg. 1 (PA): v and
-//           vhat are per worker, and u = m / sqrt(vhat) + rho e.
-//   sparse  the members of I_t: x, and (Alg. 2) h from all workers' g in ascending worker order, v, vhat; 32 lanes
+//           ascending idx; the workgroups of the first workers also have v and vhat off I_t, and on I_t if they have all
+//           workers (ny = 1).  Alg. 1 (PA): v and vhat are per worker, and u = m / sqrt(vhat) + rho e.
+//   sparse  the members of I_t: x, and (Alg. 2, ny > 1) h from all workers' g in ascending worker order, v, vhat; 32 lanes
 //           share a member from kWideMinWorkers workers on (a chain of n memory latencies otherwise)
 // Nothing that one workgroup writes is read by another.  VEC: 4 = 16-byte accesses (d a multiple of 4), 1 = a thread's
 // four coordinates lie 256 apart.  The next worker's values are fetched while one is computed; the first ones while
@@ -97,12 +97,13 @@ struct UpdateArgs {
 __device__ __forceinline__ void update_members(const UpdateArgs &a, int64_t block, bool pa, float *vals)
 {
     const int t = threadIdx.x;
-    if (pa || a.n < kWideMinWorkers) {
+    const bool only_x = pa || a.ny == 1;
+    if (only_x || a.n < kWideMinWorkers) {
         const int64_t q = block * 256 + t;
         if (q >= a.k) return;
         const int64_t l = a.idx[q];
         a.x[l] = (a.x[l] - (a.lr * a.delta[q]));
-        if (pa) return;
+        if (only_x) return;
         float gs = 0.0f;
         for (int32_t i0 = 0; i0 < a.n; i0 += 8) {                    // eight loads in flight, added in worker order
             float val[8];
@@ -204,9 +205,14 @@ k_update(UpdateArgs a)
 #pragma unroll
         for (int z = 0; z < 4; ++z) sel |= ((bits[at(z) >> 5] >> (at(z) & 31)) & 1u) << z;
     }
+    float gs[4];
     for (int32_t i = i0; i < i1; ++i) {
         if (i + 1 < i1) load_worker(i + 1, nxt);
         float mo[4], uo[4];
+        if constexpr (!PA) {
+#pragma unroll
+            for (int z = 0; z < 4; ++z) gs[z] = i == i0 ? cur[0][z] : (gs[z] + cur[0][z]);
+        }
 #pragma unroll
         for (int z = 0; z < 4; ++z) {
             const float gv = cur[0][z];
@@ -240,12 +246,14 @@ k_update(UpdateArgs a)
             load(a.v + l0, vv);
             load(a.vhat + l0, vh);
             bool moved = false;
+            const bool all = a.ny == 1;                              // of the workers have been here: members as well
 #pragma unroll
             for (int z = 0; z < 4; ++z) {
-                vv[z] = ((a.beta2 * vv[z]) + (a.omb2 * (0.0f * 0.0f)));
+                const float h = all && ((sel >> z) & 1u) ? (gs[z] / (float)a.n) : 0.0f;
+                vv[z] = ((a.beta2 * vv[z]) + (a.omb2 * (h * h)));
                 if (vv[z] > vh[z]) { vh[z] = vv[z]; moved = true; }
             }
-            if (sel == 0u) {
+            if (all || sel == 0u) {
                 store(a.v + l0, vv);
                 if (moved) store(a.vhat + l0, vh);
             } else {                                                 // the members belong to a sparse workgroup
@@ -403,9 +411,14 @@ int enqueue_update(sams_ctx *ctx, const float *g, float *m, float *e_u, float *v
     // n = 33, three million 376 and 416 us; n = 3, 11.2 million 182 and 189 us; below, n = 8, 103 and 95 us at three million).
     int64_t ny = (2048 + ntile - 1) / ntile;
     if (ny > ctx->n || pa || ctx->n * ctx->d >= kUpdateLong) ny = ctx->n;
+    // With more than 1 in 64 coordinates in I_t the sparse workgroups' gathers of g, a memory line per value, cost more than that:
+    // all workers in one workgroup, which has h of its members by itself.  Shared out and by itself: n = 8, d = 11.2 million, 1 % of
+    // the coordinates 414 and 422 us, 2 % 449 and 441, 10 % 515 and 449; n = 4, 60 million, 2 % 1.38 and 1.30 ms; n = 16, 200,001
+    // (196 tiles), 2 % 13 and 15 us.
+    if (!pa && k_sel > ctx->d / 64 && ntile >= 256) ny = 1;
     const int32_t wchunk = (int32_t)((ctx->n + ny - 1) / ny);
     ny = (ctx->n + wchunk - 1) / wchunk;
-    const int64_t per_sparse = pa || ctx->n < kWideMinWorkers ? 256 : kWideCoords;
+    const int64_t per_sparse = pa || ny == 1 || ctx->n < kWideMinWorkers ? 256 : kWideCoords;
     const int64_t blocks = ntile * ny + (k_sel + per_sparse - 1) / per_sparse;
     const UpdateArgs a = {g, m, e_u, v, vhat, x, idx, delta, k_sel, ctx->d, ntile, ctx->n, wchunk, (int32_t)ny, beta1, 1.0f - beta1,
                           beta2, 1.0f - beta2, rho, lr};

@@ -117,3 +117,12 @@ def test_mean_of_any_number_of_tables(n, r, c):
     with sams.Context(1_000, n, r, c, 1, inputs.hash_params(r)) as ctx:
         ctx.sketch_reduce(torch.from_numpy(S).cuda(), mean)
     assert np.array_equal(mean.cpu().numpy(), Oracle("f32").sketch_mean(S))
+
+
+@pytest.mark.parametrize("d,n,r,c,k", [(300_001, 17, 2, 40_000, 4_687), (300_001, 17, 2, 40_000, 4_688), (261_121, 3, 1, 40_000, 261_121),
+                                       (261_120, 3, 1, 40_000, 9_000), (2_200_000, 5, 1, 40_000, 500)])
+def test_update_with_many_members(d, n, r, c, k):
+    """the second moments on the index set by workgroups of their own, and (from 256 tiles on, more than 1 in 64 coordinates; or
+    enough tiles for all workers of one to be together) by those that have all workers"""
+    from paper_2210_07454_amd import sams
+    assert one_iteration(sams, (d, n, r, c, k), seed=d % 97)
