@@ -1977,14 +1977,13 @@ static int32_t scatter_group(const Plan &pl)
     return (int32_t)(want < 1 ? 1 : (want > most ? most : want));
 }
 
-// Whether pass 1 by itself reads u with streaming loads.  A vector that the update has left in the Infinity Cache is better read
-// through the L2s, as long as it does not push out the plan's metadata: the line lies where u and four times the metadata
-// fill the 256 MB.  Streaming and plain (pass 1, us): d = 222,390, n = 27 38 and 30; a million, n = 8 55 and 43, n = 33 166 and
-// 137, n = 45 224 and 193, n = 60 291 and 289; three million, n = 8 124 and 105 (in groups of 16 tiles; 115 in groups of 64),
-// n = 16 240 and 244; six million, n = 5 166 and 171.
+// Whether pass 1 by itself reads u with streaming loads.  A short vector that the update has left in the caches is better read
+// through the L2s, as long as it does not push the plan's metadata out of them.  Whole steps, streaming and plain (us): d = 222,390,
+// n = 27 130 and 120; 447,001, n = 20 172 and 163; 688,050, n = 44 519 and 518; a million, n = 8 243 and 238, n = 33 569 and 575, n = 45 727 and
+// 750; three million, n = 4 237 and 246, n = 8 443 and 460.
 static bool scatter_streams(const sams_ctx *ctx)
 {
-    return (int64_t)ctx->n * ctx->d * 4 + 4 * plan_metadata_bytes(ctx->plan) > ((int64_t)256 << 20);
+    return (int64_t)ctx->n * ctx->d * 4 > ((int64_t)96 << 20) || plan_metadata_bytes(ctx->plan) > ((int64_t)12 << 20);
 }
 
 bool head_compacts_g(const sams_ctx *ctx) { return ctx->wordrank != nullptr && ctx->gsel != nullptr; }
@@ -2074,11 +2073,9 @@ int enqueue_sketch_planned(sams_ctx *ctx, const float *u, float *S_workers)
         const RowGroup rg = {j0, (ctx->r - j0) < pl.stage_rows ? (ctx->r - j0) : pl.stage_rows, pl.stage_rows, ctx->r, pl.stage_ilv};
         if (j0 > 0 || pl.staged_u != u) {                            // not staged by a fused head: pass 1 now
             ProfScope ps(ctx, KID_BIN_SCATTER);
-            const bool stream = scatter_streams(ctx);
-            const int32_t group = scatter_group(pl);
-            hipLaunchKernelGGL((stream ? k_bin_scatter<true> : k_bin_scatter<false>), dim3((unsigned)(per * kNumXcd * ctx->n)), dim3((unsigned)ctx->tun.scatter_threads),
+            hipLaunchKernelGGL((scatter_streams(ctx) ? k_bin_scatter<true> : k_bin_scatter<false>), dim3((unsigned)(per * kNumXcd * ctx->n)), dim3((unsigned)ctx->tun.scatter_threads),
                                (size_t)(L * 4 + 16), ctx->stream, u, pl.srcp, pl.dst16, pl.pbase, pl.stg, ctx->n, rg,
-                               ctx->d, pl.tile_log2, pl.ntile, pl.rowlen, pl.grp_log2, stream || group < 16 ? group : 16);
+                               ctx->d, pl.tile_log2, pl.ntile, pl.rowlen, pl.grp_log2, scatter_group(pl));
         }
         SAMS_HIP(hipGetLastError());
         SAMS_TRY(dispatch_acc(ctx, S_workers, rg, false));
