@@ -57,7 +57,7 @@ typedef struct sams_ctx sams_ctx;
  * Allocates the context's device scratch; sams_scratch_bytes reports the total:
  *   always            4d bytes for the estimates, d/8 for the index bitmap, small selection state
  *   c above one LDS window, or d <= 2^22: the sketch plan and its staging buffer, 4*r*d + 4*n*r*d bytes and their padding
- *   128 <= c <= 16384 and d <= 2^26, in their place: lists, 3 to 12 bytes per row and coordinate (24 at most: a hash that needs
+ *   128 <= c <= 16384 and d <= 2^26, in their place: lists, 3 to 15 bytes per row and coordinate (24 at most: a hash that needs
  *                     more goes the other way), and above d = 2^22 up to 128 tables of n*r*c floats; where these find no
  *                     room, the context does without them (see "sketch_path")
  *   no staging buffer of 6d bytes: that much for the lists of the selection ("sketch_path" 1 too), or, where it is not to be

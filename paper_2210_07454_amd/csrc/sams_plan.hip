@@ -1966,9 +1966,15 @@ int64_t plan_staging_words(const sams_ctx *ctx)
 static int64_t plan_metadata_bytes(const Plan &pl) { return (pl.rowlen * 2 + (pl.rowlen >> pl.grp_log2) * 4) * pl.rows; }
 
 // Tiles of an XCD that pass 1 takes worker by worker (tile_and_worker): as many as have their plan metadata (2.25 bytes per
-// slot and row) in 3 MB, three quarters of the XCD's L2, but no more than 16 -- for 2^14 coordinates and five rows; with 64,
-// pass 1 with the head takes 8.0 instead of 7.2 ms at d = 124 million, with 24 of 2^13 3.40 instead of 3.36 at 25.6 million.  When the whole plan's metadata fits in half the 256 MB
-// Infinity Cache it comes from there, and groups of 64 are better (0.73 and 0.79 ms at 11.2 million).
+// slot and row) in 3 MB, three quarters of the XCD's L2, but no more than 16.  Pass 1 with the head (ms) and what it fetches
+// (GB) in groups of
+//                                                  1           4           6     8           12          16          24
+//   124 million, n = 8, 5 rows (automatic: 15)     7.29  14.4  7.40  14.4  7.19  7.45  14.4  7.32  15.1  7.31  16.5  7.44
+//   25 million, n = 16, 10 rows (16)               4.79   5.6  4.65   5.6  4.30  4.27   5.6  4.21   5.8  4.24   6.8  4.46
+//   25.6 million, n = 16, 7 rows (16)              3.64        3.62        3.43  3.42        3.38        3.36        3.41
+// so that the larger groups gain by the order of the writes, at the two shorter vectors, and pay with metadata that leaves
+// the L2 before the last worker has read it; with 64, 8.0 ms at 124 million.  When the whole plan's metadata fits in half
+// the 256 MB Infinity Cache it comes from there, and groups of 64 are better (0.73 and 0.79 ms at 11.2 million).
 static int32_t scatter_group(const Plan &pl)
 {
     const int64_t all = plan_metadata_bytes(pl);

@@ -16,12 +16,18 @@
 //
 // Cost: every workgroup reads its worker's whole vector, or part (through the L2: the workgroups of one worker sit on one XCD
 // and walk in step), so the vector is read rows x windows times; the lists, which all workers share, once per worker.
-// Bound by what one compute unit takes in from the L2, 45 GB/s whether the lines hit or not (the same with two or four
-// loading wavefronts, one or two tiles ahead, always the same tiles); the adding alone takes a third of that time.
-// Measured on MI355X, both passes of the binned path before and this kernel now: d = 60,000, n = 50, 5 x 400: 98 and 11 us;
-// n = 100: 130 and 21 us; d = 65,536, n = 4, 5 x 2,048: 21 and 9 us; d = 431,003, n = 5, 4 x 9,001: 103 and 39 us;
-// d = 25.6 million, n = 4, 5 x 10,000: 8.5 and 1.00 ms (2.4 with one slice per wavefront and the vector in one part: twelve
-// windows that read it instead of three).
+// Bound by two things that hardly overlap: what one compute unit takes in from the L2, 50 GB/s or so whether the lines hit or
+// not (the same with two or four loading wavefronts, one or two tiles ahead, always the same tiles), and the steps of the lists,
+// 5 ns each (a wavefront's read of 64 scattered values of the tile).  The kernel, its loads alone and its adding alone (us):
+//   d = 60,000, n = 50, 5 x 400 10, 6.5 and 10; n = 100 20, 12 and 19; 431,003, n = 5, 4 x 9,001 39, 26 and 18; 25.6 million, n = 4,
+//   5 x 400 353, 187 and 195, 5 x 4,096 608, 345 and 375, 5 x 10,000 825, 508 and 409, 5 x 16,384 1,294, 920 and 626
+// What a list holds beyond its coordinates is by the row's hash: 1.5 to 3.1 entries per coordinate in 28 of 30 rows of 10,000
+// buckets, 5.5 and 5.8 in the others; 2.7 with 9,001, 1.35 with 400.  A launch waits for its worst row.
+// Measured on MI355X, both passes of the binned path before and this kernel: d = 60,000, n = 50, 5 x 400: 98 and 10 us; n = 100:
+// 130 and 20 us; d = 65,536, n = 4, 5 x 2,048: 21 and 8 us; d = 431,003, n = 5, 4 x 9,001: 103 and 39 us; d = 25.6 million,
+// n = 4, 5 x 10,000: 8.5 and 0.83 to 1.0 ms by the hash (2.4 with one slice per wavefront and the vector in one part: twelve
+// windows that read it instead of three).  The lists are made in half the time of the plan: 0.13 ms at 65,536, 0.33 at
+// 431,003, 5.3 at 25.6 million (0.26, 0.43 and 10); two waits for the stream and a sum over their lengths on the host are in it.
 #include <stdlib.h>
 
 #include "sams_ctx.h"
