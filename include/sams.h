@@ -273,7 +273,7 @@ int topk_refine(sams_ctx *ctx, const int32_t *idx_in, const float *delta_in, int
  * topk_refine for callers that cannot allocate device memory or create a context: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same selection, same kernels, same results as
  * topk_refine(ctx, ...) with ctx->k = k_in, but context-free: the scratch of the selection (the listed keys, radix
- * histograms, per-tile counts and ranks; about 6*SAMS_STATIC_MAX_CANDIDATES + 32 KiB bytes) is a static device
+ * histograms, per-tile counts and ranks; about 6*SAMS_STATIC_MAX_CANDIDATES + 112 KiB bytes) is a static device
  * array inside the library, which every GPU the library runs on holds until the process ends.  The call allocates
  * and frees nothing and records no memset (every clear is a kernel).
  *   idx_in   [k_in] int32 in, ascending     delta_in [k_in] in      1 <= k_out <= k_in <= SAMS_STATIC_MAX_CANDIDATES

@@ -80,12 +80,13 @@ static int selection(sams_ctx *ctx, F body)
 {
     const bool clear = ctx->sel_open;
     ctx->sel_open = true;
-    if (clear) SAMS_TRY(enqueue_fill_u32(ctx, ctx->sel, kSelStateWords + 2 * kHistBins, 0u));
+    if (clear) SAMS_TRY(enqueue_fill_u32(ctx, ctx->sel, kSelClearWords, 0u));
     SAMS_TRY(body());
     if (clear) {                                                     // recorded into a graph, it has not happened yet
         hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-        SAMS_HIP(hipStreamIsCapturing(ctx->stream, &st));
-        if (st != hipStreamCaptureStatusNone) return SAMS_OK;
+        if (hipStreamIsCapturing(ctx->stream, &st) != hipSuccess) (void)hipGetLastError();   // (the default stream beside a capture)
+        else if (st == hipStreamCaptureStatusNone) ctx->sel_open = false;
+        return SAMS_OK;
     }
     ctx->sel_open = false;
     return SAMS_OK;
@@ -136,7 +137,7 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
     struct { void **p; int64_t bytes; } allocs[] = {
         {(void **)&ctx->est, d * 4},
         {(void **)&ctx->bitmap, words * 4},
-        {(void **)&ctx->sel, (kSelStateWords + 2 * kHistBins) * 4},
+        {(void **)&ctx->sel, kSelWords * 4},
         {(void **)&ctx->sel_tile, 3 * sel_tiles(d) * 4},
     };
     for (auto &a : allocs) {
@@ -152,7 +153,7 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
     void *static_scratch = nullptr;
     int rc = static_scratch_ptr(&static_scratch);                    // resolved here so that topk_refine_static never has to
     if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, ctx->bitmap, words, 0u);
-    if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, ctx->sel, kSelStateWords + 2 * kHistBins, 0u);
+    if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, ctx->sel, kSelClearWords, 0u);
     bool pulls = false;
     if (rc == SAMS_OK) rc = pull_create(ctx, ctx->tun, &pulls);
     if (rc == SAMS_OK && !pulls && ctx->tun.sketch_path != 1) rc = plan_create(ctx, ctx->tun);

@@ -29,11 +29,13 @@ extern int g_last_hip_error;
 constexpr int kWave = 64;
 constexpr int64_t kOrderedSingleBinMaxD = (int64_t)1 << 22;     // largest d sketched in order when c fits one window
 constexpr int kHistBins = 2048;     // first radix digit of the selection: 11 bits, then 10 and 10 (kHistBins / 2 bins)
+constexpr int kSelTileLog2 = 12;    // keys per tile of the filters: 1024 threads, 4 each
+constexpr int kSelMaxTiles = 16;    // kSelSmallMax keys
 constexpr int64_t kSelSmallMax = 1 << 16;   // keys up to which the selection is one launch after the first histogram (for small k)
 
 // device-resident state of the radix selection (no host round trip inside a step).  A selection starts from histograms and
-// `done` of zeros and leaves them so; the next one clears them first where one failed half-way (sams_ctx::sel_open), and
-// topk_refine_static always does
+// `done` of zeros and leaves them so (up to 2^16 keys, after a pass of its own over the keys, it needs none); the next one
+// clears them first where one failed half-way (sams_ctx::sel_open), and topk_refine_static always does
 struct SelState {
     uint32_t prefix[3];   // key bits decided after each digit: the top bits of the k-th largest |key| pattern (prefix[2]: all 31)
     uint32_t k_rem[3];    // how many keys to take among those that match the prefix (k_rem[2]: how many equal to the k-th largest)
@@ -134,11 +136,15 @@ struct SelList {
 struct SelScratch {
     SelState *st;
     uint32_t *hist;          // [2 * kHistBins]  first digit, then second, then third
+    uint32_t *tile_hist;     // [kSelMaxTiles][kHistBins / 2]  up to 2^16 keys: first digit tile by tile, two bins of 16 bits a word
     SelList list;
     int64_t ntile_cap, cap;  // tiles, and keys that the lists have room for
+    bool shared;             // by several streams: what the selection before has left in st and hist is not relied on
 };
 constexpr int64_t kSelHistPickMin = (int64_t)1 << 20;                // above, the kernel that takes the first histogram picks its digit
 constexpr int64_t kSelStateWords = 64;                               // words of SelState, rounded up; the histograms follow it
+constexpr int64_t kSelClearWords = kSelStateWords + 2 * kHistBins;   // what a selection starts from as zeros
+constexpr int64_t kSelWords = kSelClearWords + kSelMaxTiles * kHistBins / 2;   // the tiles' histograms after it
 static_assert(sizeof(SelState) <= kSelStateWords * 4, "selection state");
 // tiles for which the per-tile arrays need room when up to len keys are selected from: of 4096 keys, at least 256
 static inline int64_t sel_tiles(int64_t len) { return (len >> 12) + 1 > 256 ? (len >> 12) + 1 : 256; }
@@ -156,7 +162,7 @@ struct sams_ctx {
     uint32_t *wordrank;      // [ceil(d/32)]  for a bitmap word with a bit set: the rank (position in idx) of its first set bit;
                              //               with gsel, only where the head is fused per worker (fuse_head = 2), else null
     float *gsel;             // [n][k]        g of every worker at the coordinates of the most recent index set, by rank
-    uint32_t *sel;           // SelState, then the histograms [2 * kHistBins]
+    uint32_t *sel;           // [kSelWords]  SelState, then SelScratch::hist and tile_hist
     bool sel_open;           // a selection was begun and not enqueued whole: the next one clears `sel` first
     uint32_t *sel_tile;      // [3][sel_tiles(d)]  SelList::group, cnt
     uint32_t *sel_list;      // SelList::val and loc when the staging buffer is absent or too small to hold them, else null

@@ -20,7 +20,7 @@ constexpr size_t kOffVal = 0;                                                   
 constexpr size_t kOffLoc = align256(kOffVal + (size_t)(kStaticMaxCand + 64) * 4);    // SelList::loc
 constexpr size_t kOffTile = align256(kOffLoc + (size_t)(kStaticMaxCand + 64) * 2);   // SelList::group, cnt
 constexpr size_t kOffSel = align256(kOffTile + (size_t)3 * kStaticTiles * 4);        // SelState, then the histograms
-constexpr size_t kStaticBytes = kOffSel + (size_t)(kSelStateWords + 2 * kHistBins) * 4;
+constexpr size_t kStaticBytes = kOffSel + (size_t)kSelWords * 4;
 
 // In host code this name is only a handle for hipGetSymbolAddress, never a device address.
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
@@ -63,14 +63,10 @@ int topk_refine_static(const int32_t *idx_in, const float *delta_in, int64_t k_i
     SAMS_TRY(static_scratch_ptr(&p));
     unsigned char *b = static_cast<unsigned char *>(p);
     uint32_t *tile = reinterpret_cast<uint32_t *>(b + kOffTile), *sel = reinterpret_cast<uint32_t *>(b + kOffSel);
-    const SelScratch sc = {reinterpret_cast<SelState *>(sel), sel + kSelStateWords,
+    const SelScratch sc = {reinterpret_cast<SelState *>(sel), sel + kSelStateWords, sel + kSelClearWords,
                            {reinterpret_cast<uint32_t *>(b + kOffVal), reinterpret_cast<uint16_t *>(b + kOffLoc),
                             tile + 2 * kStaticTiles, reinterpret_cast<uint2 *>(tile)},
-                           kStaticTiles, kStaticMaxCand};
-    // Calls on several streams share this scratch, so what the one before has left is not relied on (inside a context the
-    // stream orders the selections): one that overlapped another, or ended half-way, would spoil every later call.  Costs a
-    // launch of 2 us (4.96 million candidates: 64 -> 66 us).
-    SAMS_TRY(enqueue_fill_u32_on(nullptr, (hipStream_t)hip_stream, sel, kSelStateWords + 2 * kHistBins, 0u));
+                           kStaticTiles, kStaticMaxCand, true};
     return enqueue_select(nullptr, (hipStream_t)hip_stream, sc, delta_in, k_in, k_out, idx_in, idx_out, delta_out, false);
 }
 
