@@ -16,11 +16,12 @@
 //
 // Cost: every workgroup reads its worker's whole vector, or part (through the L2: the workgroups of one worker sit on one XCD
 // and walk in step), so the vector is read rows x windows times; the lists, which all workers share, once per worker.
-// Bound by two things that hardly overlap: what one compute unit takes in from the L2, 50 GB/s or so whether the lines hit or
-// not (the same with two or four loading wavefronts, one or two tiles ahead, always the same tiles), and the steps of the lists,
-// 5 ns each (a wavefront's read of 64 scattered values of the tile).  The kernel, its loads alone and its adding alone (us):
-//   d = 60,000, n = 50, 5 x 400 10, 6.5 and 10; n = 100 20, 12 and 19; 431,003, n = 5, 4 x 9,001 39, 26 and 18; 25.6 million, n = 4,
-//   5 x 400 353, 187 and 195, 5 x 4,096 608, 345 and 375, 5 x 10,000 825, 508 and 409, 5 x 16,384 1,294, 920 and 626
+// Bound by what one compute unit takes in from the L2 (a tile of 52 KB in 0.5 us, 105 GB/s, whether the lines hit or not) and by the
+// steps of the lists, 5 ns each (a wavefront's read of 64 scattered values of the tile).  Two tiles are under way while a third is
+// added: that takes a barrier of its own (tile_barrier), since __syncthreads lets the loaders wait for all they have asked for,
+// and one tile then took 0.65 us (in this kernel, 431,003 coordinates, n = 5, 4 x 9,001: 37.5 -> 29 us; 65,536, n = 4, 5 x 2,048: 9.0 ->
+// 7.8; 25.6 million, n = 4, 5 x 10,000 with its sums and estimates: 0.99 -> 0.85 ms).  Counters in LDS in place of the barrier, so
+// that the wavefronts need not walk in step, cost more than they give (29 -> 48 us: their latency is in every tile).
 // What a list holds beyond its coordinates is by the row's hash: 1.5 to 3.1 entries per coordinate in 28 of 30 rows of 10,000
 // buckets, 5.5 and 5.8 in the others; 2.7 with 9,001, 1.35 with 400.  A launch waits for its worst row.
 // Measured on MI355X, both passes of the binned path before and this kernel: d = 60,000, n = 50, 5 x 400: 98 and 10 us; n = 100:
@@ -191,6 +192,11 @@ __device__ __forceinline__ void load_to_lds4(const float *src, float *dst)
                                      (__attribute__((address_space(3))) void *)dst, 4, 0, 0);
 }
 
+// The barrier between two tiles.  Not __syncthreads: the compiler puts a wait for every load that is under way in front of
+// that, the next tile's among them.  LDS accesses of a wavefront happen in order, an adder's values have been used when it gets
+// here, and a loader has waited for its part of the tile; the LDS writes before the first tile are waited for.
+__device__ __forceinline__ void tile_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // W: words per group; D: groups of words on their way ahead of the one being added.
 // Three tile buffers: the loaders bring the next two tiles in while the adders work on the third.  The two kinds wait for
 // their own loads only (a wavefront's loads come back in order: one that fetched both would wait for the whole next
@@ -231,11 +237,18 @@ k_sketch_pull(PullArgs a)
         auto load = [&](int32_t tl) {
             float *dst = buf + (tl % kPullBufs) * kPullBuf;
             const int64_t at = row0 - mis + (int64_t)(t0 + tl) * kPullTile;   // flat position in u of the buffer's start
+            if (at + kPullZero <= last4) {                           // uniform; without the limit on the address half the instructions
+                const float *src = a.u + at + (w * kWave + lane) * 4;
 #pragma unroll
-            for (int g = 0; g < kPullLoads; ++g) {
-                const int chunk = g * kPullLoaders + w;
-                const int64_t f = at + (chunk * kWave + lane) * 4;
-                load_to_lds16(a.u + (f < last4 ? f : last4), dst + chunk * kWave * 4);
+                for (int g = 0; g < kPullLoads; ++g)
+                    load_to_lds16(src + g * kPullLoaders * kWave * 4, dst + (g * kPullLoaders + w) * kWave * 4);
+            } else {
+#pragma unroll
+                for (int g = 0; g < kPullLoads; ++g) {
+                    const int chunk = g * kPullLoaders + w;
+                    const int64_t f = at + (chunk * kWave + lane) * 4;
+                    load_to_lds16(a.u + (f < last4 ? f : last4), dst + chunk * kWave * 4);
+                }
             }
             const int64_t fa = at + ahead;
             load_to_lds4(a.u + (fa < last4 ? fa : last4), buf + kPullBufs * kPullBuf);
@@ -252,7 +265,7 @@ k_sketch_pull(PullArgs a)
                 if (p / 4 / kWave % kPullLoaders == w && lane < (int)(a.total & 3))
                     buf[(tl % kPullBufs) * kPullBuf + p + lane] = a.u[f + lane];
             }
-            __syncthreads();                                         // the adders have done with tile tl - 1, whose buffer tl + 2 takes
+            tile_barrier();                                          // the adders have done with tile tl - 1, whose buffer tl + 2 takes
             if (tl + 2 < ntile) load(tl + 2);
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // the LDS is given back with nothing under way
@@ -260,7 +273,7 @@ k_sketch_pull(PullArgs a)
     }
     const int32_t s = win * po.per_win + wave * PW;
     if (wave * PW >= po.per_win || s >= po.nslice) {                 // no slice: only the barriers
-        for (int32_t tl = 0; tl < ntile; ++tl) __syncthreads();
+        for (int32_t tl = 0; tl < ntile; ++tl) tile_barrier();
         return;
     }
     typedef uint32_t vecw __attribute__((ext_vector_type(W)));
@@ -281,7 +294,7 @@ k_sketch_pull(PullArgs a)
     int32_t lists_left = PW;                                         // of the tile
     const char *base = reinterpret_cast<const char *>(buf + mis);
     int32_t left = kPullBufs;                                        // buffers until the first one again
-    __syncthreads();                                                 // tile 0 is there
+    tile_barrier();                                                  // tile 0 is there
     for (int32_t m0 = 0; m0 < ng; m0 += D) {
 #pragma unroll
         for (int z = 0; z < D; ++z) {
@@ -304,7 +317,7 @@ k_sketch_pull(PullArgs a)
                     x[PW - 1] = y;
                     if (--lists_left == 0) {
                         lists_left = PW;
-                        if (m0 + z + 1 < ng) __syncthreads();        // the next tile is there
+                        if (m0 + z + 1 < ng) tile_barrier();         // the next tile is there
                         base += kPullBuf * 4;
                         if (--left == 0) {
                             base -= kPullBufs * kPullBuf * 4;
