@@ -88,18 +88,19 @@ struct Plan {
     bool fused_median;  // stage 3 keeps the row estimates in registers (decided when the plan is built)
 };
 
+struct PullOrder;
+struct PullRow {
+    int32_t win0, per_win, per_wave;   // windows of the rows before; lists per window, per wavefront
+};
 // the lists of the pulling form of the order-preserving path (see sams_pull.hip); kernel == null: this context does not pull
 struct PullPlan {
     const void *kernel;
-    int32_t ntile;                // tiles of the vector
-    int32_t nslice;               // slices of 64 buckets in a row
-    int32_t per_win, nwin;        // slices per window, windows per row (a workgroup has one)
-    int32_t per_wave, group;      // slices per wavefront; words that a lane reads with one load
-    int32_t parts, per_part;      // parts of the vector that workgroups share out, tiles per part
-    uint32_t *first;              // [streams + 1]       first group of words of a wavefront's lists
-    uint32_t *lists;              // [groups][64][group]  words of two entries, in groups of PullOrder::group
+    struct PullOrder *po;         // where a wavefront's lists are (host memory)
+    int32_t parts;                // parts of the vector that workgroups share out
+    uint2 *first;                 // per stream, a wavefront's lists: its first load of words, its units
+    uint32_t *lists;              // [loads][64][4]  words of two entries
     float *part_sums;             // [parts][n][r][c], with more than one part
-    int64_t list_bytes;
+    int64_t list_bytes, first_bytes;
 };
 
 // tunables: sams_configure edits the process-wide set, sams_create copies it into the context, and every

@@ -3,32 +3,38 @@
 // The binned path (sams_plan.hip) writes every signed value to where its bucket's window will read it and reads it
 // back: 8 bytes of memory traffic per (worker, row, coordinate), and a window that few workgroups share when the table
 // is small.  A narrow table turns that round: the workgroups pull.  The vector is cut into tiles that fit in LDS; a
-// workgroup has one worker, one row and a range of up to 56 slices of 64 buckets (a window), walks the worker's tiles in
-// order, and every lane of a wavefront owns one bucket of each of its one, two or four slices, with the sum in a register.  Which
-// coordinates of a tile a bucket takes is worked out once, at context creation: per (row, tile, slice) a list of steps,
-// each of 64 entries, one per lane -- the coordinate inside the tile and its sign --, padded with an entry that points at a
-// zero; the lists of a wavefront lie one after the other, as one stream.  A lane takes its entries in ascending
-// coordinate order, so the sums are those of a sequential loop over the coordinates, bit for bit (adding the padding's
-// zero changes nothing: a sum that starts at +0 is never -0; a value is added as fma(value, +-1, sum), which rounds
-// once, like the addition).  No atomics, no exchange between lanes, one barrier per tile.
+// workgroup has one worker, one row and a range of its slices of 64 buckets (a window), walks the worker's tiles in order, and every
+// lane of a wavefront owns one bucket of each of its slices -- one, or up to sixteen --, with the sum in a register.  Which
+// coordinates of a tile a bucket takes is worked out once, at context creation: lists of steps, each of 64 entries, one per lane -- the
+// coordinate inside the tile and its sign --, padded with an entry that points at a zero; the lists of a wavefront lie one after the
+// other, as one stream, which a lane reads 16 bytes at a time.  With one slice per wavefront a list is that of a (row, tile, slice);
+// with several it is that of four slices, a word (two steps) of each in every load: four sums that do not wait for each other, and one
+// test for the list's end in eight steps.  A lane takes its entries in ascending coordinate order, so the sums are those of a
+// sequential loop over the coordinates, bit for bit (adding the padding's zero changes nothing: a sum that starts at +0 is never -0; a
+// value is added as fma(value, +-1, sum), which rounds once, like the addition).  No atomics, no exchange between lanes, one barrier
+// per tile.
 // Vectors of more than 2^22 coordinates, whose sums need not be in that order, may be cut into parts: workgroups of their
 // own make a table of every part, and the tables are added up part after part, always the same way.
 //
-// Cost: every workgroup reads its worker's whole vector, or part (through the L2: the workgroups of one worker sit on one XCD
-// and walk in step), so the vector is read rows x windows times; the lists, which all workers share, once per worker.
-// Bound by what one compute unit takes in from the L2 (a tile of 52 KB in 0.5 us, 105 GB/s, whether the lines hit or not) and by the
-// steps of the lists, 5 ns each (a wavefront's read of 64 scattered values of the tile).  Two tiles are under way while a third is
-// added: that takes a barrier of its own (tile_barrier), since __syncthreads lets the loaders wait for all they have asked for,
-// and one tile then took 0.65 us (in this kernel, 431,003 coordinates, n = 5, 4 x 9,001: 37.5 -> 29 us; 65,536, n = 4, 5 x 2,048: 9.0 ->
-// 7.8; 25.6 million, n = 4, 5 x 10,000 with its sums and estimates: 0.99 -> 0.85 ms).  Counters in LDS in place of the barrier, so
-// that the wavefronts need not walk in step, cost more than they give (29 -> 48 us: their latency is in every tile).
+// Cost: every workgroup reads its worker's whole vector, or part, through the L2: the workgroups that walk the same tiles, and those of
+// other workers with the same lists, have consecutive numbers on one XCD (worker by worker only, the lists of 25.6 million
+// coordinates, n = 4, 5 x 10,000 came from memory four times: 513 -> 434 us).
+// Bound by what one compute unit takes in from the L2 (a tile of 52 KB in 0.5 us, 105 GB/s) and by the steps of the lists, 3.5 ns each (a
+// wavefront's read of 64 scattered values; the LDS is busy a third of the time, the vector units half, the rest is latencies of
+// 14 wavefronts); the two hardly overlap.  Two tiles are under way while a third is added: that takes a barrier of its own
+// (tile_barrier), since __syncthreads lets the loaders wait for all they have asked for, and one tile then took 0.65 us (431,003
+// coordinates, n = 5, 4 x 9,001 37.5 -> 29 us).  Counters in LDS in place of the barrier, so that the wavefronts need not walk in step,
+// cost more than they give (29 -> 48 us: their latency is in every tile); so does reading a load's values before the one in front
+// of it is added (70 -> 78 us at a million, n = 20, 5 x 12,000).
 // What a list holds beyond its coordinates is by the row's hash: 1.5 to 3.1 entries per coordinate in 28 of 30 rows of 10,000
-// buckets, 5.5 and 5.8 in the others; 2.7 with 9,001, 1.35 with 400.  A launch waits for its worst row.
-// Measured on MI355X, both passes of the binned path before and this kernel: d = 60,000, n = 50, 5 x 400: 98 and 10 us; n = 100:
-// 130 and 20 us; d = 65,536, n = 4, 5 x 2,048: 21 and 8 us; d = 431,003, n = 5, 4 x 9,001: 103 and 39 us; d = 25.6 million,
-// n = 4, 5 x 10,000: 8.5 and 0.83 to 1.0 ms by the hash (2.4 with one slice per wavefront and the vector in one part: twelve
-// windows that read it instead of three).  The lists are made in half the time of the plan: 0.13 ms at 65,536, 0.33 at
-// 431,003, 5.3 at 25.6 million (0.26, 0.43 and 10); two waits for the stream and a sum over their lengths on the host are in it.
+// buckets, 5.5 and 5.8 in the others; 2.7 with 9,001, 1.35 with 400.  A row with long lists gets more windows (pull_share).
+// Measured on MI355X (us), lists with at most four slices per wavefront, one list per slice, 4- to 16-byte loads of their words and the
+// same number of windows for every row, and this kernel: 25.6 million, n = 4, 5 x 10,000 680 to 1,030 by the hash, now 340 to 530;
+// 12 million, n = 8, 5 x 16,384 757, 500; four million, n = 50, 5 x 12,000 1,290, 840; a million, n = 20, 5 x 12,000 172, 70; six
+// million, n = 8, 4 x 700 142, 84; 431,003, n = 5, 4 x 9,001 37.5, 25; 65,536, n = 4, 5 x 2,048 9.0, 6.8; 60,000, 5 x 400, n = 50 10.8, 10.2;
+// n = 100 20, 19.  The binned path: 98 and 130 us at the last two, 103 at 431,003, 8.5 ms at 25.6 million.
+// Making the lists takes half as long as the plan: 0.13 ms at 65,536, 0.35 at 431,003, 5.7 at 25.6 million; two waits for the stream and
+// the choice of windows on the host are in it.
 #include <stdlib.h>
 
 #include "sams_ctx.h"
@@ -47,43 +53,50 @@ constexpr int kPullBuf = kPullZero + 16;      // floats of a tile buffer
 constexpr int kPullBufs = 3;
 constexpr int kPullLds = (kPullBufs * kPullBuf + kWave) * 4;
 constexpr int kPullAhead = 4;                 // tiles that the loaders are ahead with fetching into the L2
-constexpr int kPullSpare = 64;                // words behind the last list, read ahead but not used
+constexpr int kPullLoad = 4;                  // words that a lane reads with one load
+constexpr int kPullDepth = 6;                 // such loads on their way ahead of the words being added
+constexpr int kPullSpare = 2 * kPullLoad * kPullDepth;   // words of a lane behind the last list: the adders' loop goes in turns of kPullDepth
+                                              // loads, each refilled, so it reads up to 2 kPullDepth - 1 loads past its own
+constexpr int kPullMany = 4;                  // most lists of four slices per wavefront
 constexpr int kPullMaxList = 512;             // longest list of one bucket in one tile
 // A word holds two consecutive steps of a lane: the first step's coordinate in bits 2-15 (so that it is a byte offset) and
-// its sign in bit 0, the second's in bits 17-30 and 31.  Words come in groups of 1, 2 or 4 (PullOrder::group), which a lane
-// reads with one load; bit 1 of a group's first word, in every lane: this group ends a tile's list.
+// its sign in bit 0, the second's in bits 17-30 and 31.  Bit 1 of the first word of a list's last unit, in every lane, ends the list.
 
 // ------------------------------------------------------------------------------------------
 // plan
 // ------------------------------------------------------------------------------------------
-// Where the lists are: wavefront w of the workgroup for (row, window, part of the tiles) has the per_wave slices from
-// win * per_win + w * per_wave on; its lists, tile by tile and in a tile slice by slice, are one stream.
+// Where the lists are.  A list is that of a tile, a row and per_list slices (one, or four whose words take turns); row j's lists
+// of a tile are shared out over row[j + 1].win0 - row[j].win0 windows of per_win lists, and a window's over the adders, per_wave
+// each.  A wavefront's lists of its part of the tiles, tile by tile, are one stream.
 struct PullOrder {
-    int32_t ntile, nslice, per_win, nwin, group, per_wave, parts, per_part;
+    int32_t ntile, nslice, nlist;
+    int32_t per_list, group;          // slices of a list; words of a lane in a list's smallest unit
+    int32_t parts, per_part, windows; // windows: of all rows
+    PullRow row[SAMS_MAX_ROWS + 1];
 };
-__host__ __device__ __forceinline__ int64_t stream_number(const PullOrder &po, int j, int win, int part, int wave)
+__host__ __device__ __forceinline__ int64_t stream_number(const PullOrder &po, int part, int window, int wave)
 {
-    return (((int64_t)j * po.nwin + win) * po.parts + part) * (po.per_win / po.per_wave) + wave;
+    return ((int64_t)part * po.windows + window) * kPullAdders + wave;
 }
-__device__ __forceinline__ int64_t list_number(const PullOrder &po, int j, int tile, int s)
+// the lists [first, first + count) of a row that wavefront `wave` of a window has; count <= 0: none
+__host__ __device__ __forceinline__ void lists_of(const PullOrder &po, int j, int window, int wave, int32_t *first, int32_t *count)
 {
-    const int in = s % po.per_win;
-    return (stream_number(po, j, s / po.per_win, tile / po.per_part, in / po.per_wave) * po.per_part + tile % po.per_part) *
-               po.per_wave + in % po.per_wave;
+    const PullRow &row = po.row[j];
+    const int32_t w0 = (window - row.win0) * row.per_win, w1 = w0 + row.per_win < po.nlist ? w0 + row.per_win : po.nlist;
+    *first = w0 + wave * row.per_wave;
+    *count = *first + row.per_wave < w1 ? row.per_wave : w1 - *first;
 }
-// slices that have lists: those of every wavefront that has a slice at all (its others are empty: one group of padding)
-__host__ __device__ __forceinline__ int listed_slices(const PullOrder &po)
+__device__ __forceinline__ int64_t list_number(const PullOrder &po, int j, int64_t tile, int list)
 {
-    return (po.nslice + po.per_wave - 1) / po.per_wave * po.per_wave;
+    return ((int64_t)j * po.ntile + tile) * po.nlist + list;
 }
 
-// per (tile, row): groups of words of every list (the longest of its 64 columns, at least one group); *longest: the
-// longest column
+// per (tile, row): the longest of the 64 columns of every slice, at len[(row * ntile + tile) * nslice + slice]
 __global__ void __launch_bounds__(1024)
-k_pull_count(HashParams hp, int64_t d, PullOrder po, uint32_t *__restrict__ len, uint32_t *__restrict__ longest)
+k_pull_count(HashParams hp, int64_t d, int32_t ntile, int32_t nslice, uint16_t *__restrict__ len)
 {
     extern __shared__ uint32_t cnt[];                                // [nslice * 64]
-    const int j = blockIdx.y, nslice = listed_slices(po);
+    const int j = blockIdx.y;
     const int64_t l0 = (int64_t)blockIdx.x * kPullTile;
     const int lim = d - l0 < kPullTile ? (int)(d - l0) : kPullTile;
     for (int b = threadIdx.x; b < nslice * kWave; b += 1024) cnt[b] = 0;
@@ -91,25 +104,22 @@ k_pull_count(HashParams hp, int64_t d, PullOrder po, uint32_t *__restrict__ len,
     for (int p = threadIdx.x; p < lim; p += 1024) atomicAdd(&cnt[bucket_of(hp, j, (uint32_t)(l0 + p))], 1u);
     __syncthreads();
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    uint32_t most = 0;
     for (int s = wave; s < nslice; s += 16) {
         uint32_t m = cnt[s * kWave + lane];
         for (int off = kWave / 2; off; off >>= 1) {
             const uint32_t o = __shfl_xor(m, off);
             m = o > m ? o : m;
         }
-        const uint32_t steps = 2u * (uint32_t)po.group;
-        if (lane == 0) len[list_number(po, j, blockIdx.x, s)] = m ? (m + steps - 1) / steps : 1u;
-        most = m > most ? m : most;
+        if (lane == 0) len[((int64_t)j * ntile + blockIdx.x) * nslice + s] = (uint16_t)m;
     }
-    if (lane == 0) atomicMax(longest, most);
 }
 
-// per (tile, row): the lists
+// per (tile, row): the lists.  len, off: every list's units, and the units before it
 __global__ void __launch_bounds__(1024)
-k_pull_place(HashParams hp, int64_t d, PullOrder po, const uint32_t *__restrict__ off, uint32_t *__restrict__ lists)
+k_pull_place(HashParams hp, int64_t d, PullOrder po, const uint16_t *__restrict__ len, const uint32_t *__restrict__ off,
+             uint32_t *__restrict__ lists)
 {
-    const int nslice = listed_slices(po);
+    const int nslice = po.nlist * po.per_list;                       // the last list's slices may lie behind the row
     extern __shared__ uint32_t end[];                                // [nslice * 64] list ends, then kPullTile 16-bit entries
     __shared__ uint32_t part[16];
     uint16_t *ent = reinterpret_cast<uint16_t *>(end + nslice * kWave);
@@ -151,17 +161,20 @@ k_pull_place(HashParams hp, int64_t d, PullOrder po, const uint32_t *__restrict_
     __syncthreads();
     const int lane = t & (kWave - 1), wave = t / kWave;
     for (int s = wave; s < nslice; s += 16) {
-        const int64_t o = list_number(po, j, blockIdx.x, s);
+        const int64_t o = list_number(po, j, blockIdx.x, s / po.per_list);
         const int b = s * kWave + lane;
         const uint32_t lo = b ? end[b - 1] : 0u, hi = end[b];
-        const uint32_t words = (off[o + 1] - off[o]) * (uint32_t)po.group;
-        uint32_t *out = lists + ((int64_t)off[o] * kWave + lane) * po.group;   // the words of a group are consecutive in a lane
+        // word q of the slice's list in its units: of one slice, the words of a unit lie side by side in a lane, and so do those of
+        // as many units as a load holds; of four, a word of each is a load
+        const bool many = po.per_list > 1;
+        const uint32_t words = (uint32_t)len[o] * (many ? 1u : (uint32_t)po.group);
+        const int64_t w0 = (int64_t)off[o] * po.group + (many ? s % po.per_list : 0), step = many ? kPullLoad : 1;
         for (uint32_t q = 0; q < words; ++q) {
             const uint32_t e0 = lo + 2 * q < hi ? ent[lo + 2 * q] : (uint32_t)kPullZero,
                            e1 = lo + 2 * q + 1 < hi ? ent[lo + 2 * q + 1] : (uint32_t)kPullZero;
-            const uint32_t g = q / po.group, z = q % po.group;
-            const uint32_t end_flag = z == 0 && q + po.group >= words ? 2u : 0u;
-            out[(int64_t)g * kWave * po.group + z] =
+            const uint32_t unit = many ? 1u : (uint32_t)po.group, end_flag = q % unit == 0 && q + unit >= words ? 2u : 0u;
+            const int64_t at = w0 + q * step;
+            lists[(at / kPullLoad * kWave + lane) * kPullLoad + at % kPullLoad] =
                 ((e0 & 0x7fffu) << 2) | (e0 >> 15) | ((e1 & 0x7fffu) << 17) | ((e1 >> 15) << 31) | end_flag;
         }
     }
@@ -172,7 +185,8 @@ k_pull_place(HashParams hp, int64_t d, PullOrder po, const uint32_t *__restrict_
 // ------------------------------------------------------------------------------------------
 struct PullArgs {
     const float *u;
-    const uint32_t *lists, *first;    // first[stream]: the stream's first group of words; [streams]: the end
+    const uint32_t *lists;
+    const uint2 *first;               // per stream: its first load of words, its units
     float *S;                         // [parts][n][r][c]
     int64_t d, c, total;              // total = n * d
     int32_t n, r;
@@ -197,14 +211,13 @@ __device__ __forceinline__ void load_to_lds4(const float *src, float *dst)
 // here, and a loader has waited for its part of the tile; the LDS writes before the first tile are waited for.
 __device__ __forceinline__ void tile_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// W: words per group; D: groups of words on their way ahead of the one being added.
 // Three tile buffers: the loaders bring the next two tiles in while the adders work on the third.  The two kinds wait for
 // their own loads only (a wavefront's loads come back in order: one that fetched both would wait for the whole next
-// tile before each list).  The adders' loop is a stream of groups: one load is issued per group, unconditionally and
-// straight into the registers that the loop carries, so that the compiler waits for exactly the oldest; the two to eight
-// values of a group are read from LDS together and added in order.
-// PW: slices per wavefront, whose sums take turns in x[0].
-template <int W, int D, int PW>
+// tile before each list).  The adders' loop is a stream of words: a load is issued for every one used up, unconditionally and
+// straight into the registers that the loop carries, so that the compiler waits for exactly the oldest.
+// MANY = false: a slice per wavefront, lists of units of W words, whose values are read from LDS together and added in order.
+// MANY: lists of four slices, a word of each per load, and up to kPullMany such lists per wavefront, whose sums take turns.
+template <int W, bool MANY>
 __global__ void __launch_bounds__(kPullThreads)
 k_sketch_pull(PullArgs a)
 {
@@ -213,10 +226,11 @@ k_sketch_pull(PullArgs a)
     // workgroups are dealt round-robin to the 8 XCDs: consecutive (worker, row, window) triples to one XCD
     const int64_t per = (int64_t)gridDim.x / 8, q = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
     const PullOrder &po = a.po;
-    const int32_t rw = a.r * po.nwin;                                // workgroups that walk the same tiles
+    const int32_t rw = po.windows;                                   // workgroups that walk the same tiles of a worker
     if (q >= (int64_t)a.n * po.parts * rw) return;
-    const int32_t i = (int32_t)(q / rw) / po.parts, part = (int32_t)(q / rw) % po.parts;
-    const int32_t j = (int32_t)(q % rw) / po.nwin, win = (int32_t)(q % rw) % po.nwin;
+    const int32_t i = (int32_t)(q / rw) % a.n, part = (int32_t)(q / rw) / a.n, win = (int32_t)(q % rw);
+    int32_t j = 0;
+    while (win >= po.row[j + 1].win0) ++j;
     const int32_t t0 = part * po.per_part, ntile = po.ntile - t0 < po.per_part ? po.ntile - t0 : po.per_part;
     // worker i's vector starts `mis` floats past a 16-byte boundary; the tiles are loaded from that boundary on
     const int64_t row0 = (int64_t)i * a.d;
@@ -271,71 +285,101 @@ k_sketch_pull(PullArgs a)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // the LDS is given back with nothing under way
         return;
     }
-    const int32_t s = win * po.per_win + wave * PW;
-    if (wave * PW >= po.per_win || s >= po.nslice) {                 // no slice: only the barriers
+    int32_t l0, lists;
+    lists_of(po, j, win, wave, &l0, &lists);
+    if (lists <= 0) {                                                // only the barriers
         for (int32_t tl = 0; tl < ntile; ++tl) tile_barrier();
         return;
     }
-    typedef uint32_t vecw __attribute__((ext_vector_type(W)));
-    const int64_t stream = stream_number(po, j, win, part, wave);
-    const uint32_t g0 = a.first[stream], g1 = a.first[stream + 1];
-    const vecw *src = reinterpret_cast<const vecw *>(a.lists) + (int64_t)g0 * kWave + lane;
-    const int32_t ng = (int32_t)(g1 - g0);
-    vecw ring[D];
+    typedef uint32_t vec4u __attribute__((ext_vector_type(kPullLoad)));
+    const uint2 mine = a.first[stream_number(po, part, win, wave)];
+    const vec4u *src = reinterpret_cast<const vec4u *>(a.lists) + (int64_t)mine.x * kWave + lane;
+    const int32_t ng = (int32_t)mine.y;
+    vec4u ring[kPullDepth];
 #pragma unroll
-    for (int z = 0; z < D; ++z) {
+    for (int z = 0; z < kPullDepth; ++z) {
         ring[z] = src[(int64_t)z * kWave];                           // kPullSpare words end the array
         __builtin_amdgcn_sched_barrier(0);
     }
-    src += (int64_t)D * kWave;
-    float x[PW];
+    src += (int64_t)kPullDepth * kWave;
+    constexpr int kPer = MANY ? kPullLoad : 1;                       // slices of a list
+    float x[MANY ? kPullMany * kPer : 1], sum[kPer];                 // sum: of the list that is being added, in place of its x
 #pragma unroll
-    for (int p = 0; p < PW; ++p) x[p] = 0.f;
-    int32_t lists_left = PW;                                         // of the tile
+    for (int p = 0; p < (MANY ? kPullMany * kPer : 1); ++p) x[p] = 0.f;
+#pragma unroll
+    for (int y = 0; y < kPer; ++y) sum[y] = 0.f;
+    int32_t turn = 0;                                                // that list
     const char *base = reinterpret_cast<const char *>(buf + mis);
     int32_t left = kPullBufs;                                        // buffers until the first one again
     tile_barrier();                                                  // tile 0 is there
-    for (int32_t m0 = 0; m0 < ng; m0 += D) {
+    auto value = [&](uint32_t slot) { return *reinterpret_cast<const float *>(base + slot); };
+    auto add = [&](float &to, uint32_t w, float v0, float v1) {
+        to = __builtin_fmaf(v0, __uint_as_float(0x3f800000u | (w << 31)), to);
+        to = __builtin_fmaf(v1, __uint_as_float(0x3f800000u | (w & 0x80000000u)), to);
+    };
+    auto tile_done = [&](bool more) {
+        if (more) tile_barrier();                                    // the next tile is there
+        base += kPullBuf * 4;
+        if (--left == 0) {
+            base -= kPullBufs * kPullBuf * 4;
+            left = kPullBufs;
+        }
+    };
+    constexpr int kGroups = MANY ? 1 : kPullLoad / W;                // units of a load
+    for (int32_t m0 = 0; m0 < ng; m0 += kPullDepth * kGroups) {
 #pragma unroll
-        for (int z = 0; z < D; ++z) {
-            const vecw w = ring[z];
-            if (m0 + z < ng) {                                       // uniform; false only past the stream's end
-                float v[2 * W], sg[2 * W];
+        for (int z = 0; z < kPullDepth; ++z) {
+            const vec4u w = ring[z];
+            if constexpr (MANY) {
+                const int32_t m = m0 + z;
+                if (m < ng) {                                        // uniform; false only past the stream's end
+                    float v[2 * kPullLoad];
 #pragma unroll
-                for (int p = 0; p < W; ++p) {
-                    v[2 * p] = *reinterpret_cast<const float *>(base + (w[p] & 0xfffcu));
-                    v[2 * p + 1] = *reinterpret_cast<const float *>(base + ((w[p] >> 15) & 0xfffcu));
-                    sg[2 * p] = __uint_as_float(0x3f800000u | (w[p] << 31));
-                    sg[2 * p + 1] = __uint_as_float(0x3f800000u | (w[p] & 0x80000000u));
-                }
-#pragma unroll
-                for (int p = 0; p < 2 * W; ++p) x[0] = __builtin_fmaf(v[p], sg[p], x[0]);
-                if (__builtin_amdgcn_readfirstlane((int)w[0]) & 2) { // the list ends
-                    const float y = x[0];                            // after a tile's PW lists x[0] is the first slice's again
-#pragma unroll
-                    for (int p = 0; p + 1 < PW; ++p) x[p] = x[p + 1];
-                    x[PW - 1] = y;
-                    if (--lists_left == 0) {
-                        lists_left = PW;
-                        if (m0 + z + 1 < ng) tile_barrier();         // the next tile is there
-                        base += kPullBuf * 4;
-                        if (--left == 0) {
-                            base -= kPullBufs * kPullBuf * 4;
-                            left = kPullBufs;
-                        }
+                    for (int y = 0; y < kPullLoad; ++y) {
+                        v[2 * y] = value(w[y] & 0xfffcu);
+                        v[2 * y + 1] = value((w[y] >> 15) & 0xfffcu);
                     }
+#pragma unroll
+                    for (int y = 0; y < kPullLoad; ++y) add(sum[y], w[y], v[2 * y], v[2 * y + 1]);
+                    if (__builtin_amdgcn_readfirstlane((int)w[0]) & 2) {         // the list ends
+#pragma unroll
+                        for (int y = 0; y < kPullLoad; ++y) x[turn * kPer + y] = sum[y];
+                        turn = turn + 1 < lists ? turn + 1 : 0;
+#pragma unroll
+                        for (int y = 0; y < kPullLoad; ++y) sum[y] = x[turn * kPer + y];
+                        if (turn == 0) tile_done(m + 1 < ng);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int y = 0; y < kGroups; ++y) {
+                    const int32_t m = m0 + z * kGroups + y;
+                    if (m >= ng) continue;                           // uniform; only past the stream's end
+                    float v[2 * W];
+#pragma unroll
+                    for (int p = 0; p < W; ++p) {
+                        v[2 * p] = value(w[y * W + p] & 0xfffcu);
+                        v[2 * p + 1] = value((w[y * W + p] >> 15) & 0xfffcu);
+                    }
+#pragma unroll
+                    for (int p = 0; p < W; ++p) add(sum[0], w[y * W + p], v[2 * p], v[2 * p + 1]);
+                    if (__builtin_amdgcn_readfirstlane((int)w[y * W]) & 2) tile_done(m + 1 < ng);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
             ring[z] = src[(int64_t)z * kWave];
             __builtin_amdgcn_sched_barrier(0);
         }
-        src += (int64_t)D * kWave;
+        src += (int64_t)kPullDepth * kWave;
     }
+#pragma unroll
+    for (int y = 0; y < kPer; ++y) x[y] = sum[y];                    // the last tile's lists have ended
     float *out = a.S + (((int64_t)part * a.n + i) * a.r + j) * a.c;
 #pragma unroll
-    for (int p = 0; p < PW; ++p)
-        if ((s + p) * kWave + lane < a.c) out[(s + p) * kWave + lane] = x[p];
+    for (int p = 0; p < (MANY ? kPullMany * kPer : 1); ++p) {
+        const int64_t b = (int64_t)(l0 * kPer + p) * kWave + lane;
+        if (p < lists * kPer && b < a.c) out[b] = x[p];
+    }
 }
 
 // the parts' tables added up, part after part
@@ -359,73 +403,98 @@ k_pull_sum(const float *__restrict__ part, float *__restrict__ S, int64_t cells,
 // ------------------------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------------------------
-// Whether this shape pulls (if its lists turn out short enough, see pull_slower), and into how many windows.  Tables of 128 to 2^14 buckets under vectors of up to 2^26
+// Whether this shape may pull (see pull_declines, and pull_create on its lists).  Tables of 128 to 2^14 buckets under vectors of up to 2^26
 // coordinates.  With fewer buckets a bucket's list gets too long to sort by insertion at creation, with more the lists of a
 // tile's 64 buckets get too uneven (on average one entry with 2^14 buckets, the longest of 64 four); the lists of
 // longer vectors take gigabytes.
 constexpr int64_t kPullLongD = 1000000;       // shorter vectors always pull: both paths are launches and latencies
-static bool pull_shape(const sams_ctx *ctx, const Tunables &tun, PullPlan &pp)
+constexpr int64_t kPullWideC = 15000;
+static bool pull_shape(const sams_ctx *ctx, const Tunables &tun)
 {
     if (tun.sketch_path != 0 || tun.estimate_path == 2 || tun.win_log2 || tun.tile_log2 || tun.chunk_log2 || tun.acc_threads ||
         tun.stage_rows)
         return false;                                                // the caller asks for the binned path or for a shape of it
-    if (ctx->c < 128 || ctx->c > (1 << 14) || ctx->d > ((int64_t)1 << 26) || (int64_t)ctx->n * ctx->d < 4) return false;
-    pp.nslice = (int32_t)((ctx->c + kWave - 1) / kWave);
-    pp.ntile = (int32_t)((ctx->d + kPullTile - 1) / kPullTile);
-    // One workgroup per compute unit: the cost is taken to be tiles per workgroup (and about twelve that starting and ending takes)
-    // times rounds of 256 workgroups.  Two or four slices per wavefront are fewer windows, and so fewer rounds; the vector is
-    // cut into parts where the order of the additions is not promised (d > 2^22).  Ties go to fewer slices and parts.
-    // The steps of the lists, whose number no choice here changes but which a workgroup with more slices has more of, are not
-    // in it.
-    const int64_t pairs = (int64_t)ctx->n * ctx->r;
-    const int32_t most_parts = ctx->d > kOrderedSingleBinMaxD ? 128 : 1;
-    int64_t best = INT64_MAX, nwin = 1;
-    for (int32_t pw = 1; pw <= 4; pw *= 2) {
-        const int64_t least = (pp.nslice + kPullAdders * pw - 1) / (kPullAdders * pw);
-        for (int32_t parts = 1; parts <= most_parts; ++parts) {
-            const int64_t rounds = (pairs * least * parts + 255) / 256, cost = rounds * ((pp.ntile + parts - 1) / parts + 12);
+    return ctx->c >= 128 && ctx->c <= (1 << 14) && ctx->d <= ((int64_t)1 << 26) && (int64_t)ctx->n * ctx->d >= 4;
+}
+
+// units of a list: of one slice, `group` words of two steps; of several, a word of each
+static inline uint32_t list_units(const PullOrder &po, const uint16_t *longest, int32_t list)
+{
+    uint32_t m = 0;
+    for (int32_t s = list * po.per_list; s < (list + 1) * po.per_list && s < po.nslice; ++s) m = longest[s] > m ? longest[s] : m;
+    const uint32_t steps = po.per_list > 1 ? 2u : 2u * (uint32_t)po.group;
+    return m ? (m + steps - 1) / steps : 1u;
+}
+
+// Shares the rows' lists out over windows and the vector over parts (where the order of the additions is not promised, above 2^22
+// coordinates), for one of the two kernels; steps[j]: of row j's lists in a tile, all lists together.  A row whose hash makes long
+// lists gets more windows: a launch waits for its slowest workgroup (25.6 million, n = 4, 5 x 10,000 with a row of twice the others'
+// lists 434 -> 340 us, with two rows of four times 711 -> 530).  Returns the time it should take, in ns: workgroups run in rounds of 256,
+// one per compute unit; a tile takes a workgroup kTileNs to take in, and kStepNs per step of its lists, or kChainNs per step
+// of the wavefront with the most; measured / returned at 76 shapes 0.5 to 1.4, in the middle 0.95.
+static int64_t pull_share(const sams_ctx *ctx, PullOrder &po, const double *steps)
+{
+    const bool many = po.per_list > 1;
+    const double kTileNs = 450, kStepNs = 3.0, kChainNs = many ? 20 : 30, kStartNs = ctx->d > kOrderedSingleBinMaxD ? 20000 : 5000;
+    const int32_t most_lists = kPullAdders * (many ? kPullMany : 1), least = (po.nlist + most_lists - 1) / most_lists;
+    const int32_t most_parts = ctx->d > kOrderedSingleBinMaxD ? (po.ntile < 128 ? po.ntile : 128) : 1;
+    double best = 1e30;
+    for (int32_t parts = 1; parts <= most_parts; ++parts) {
+        const int32_t per_part = (po.ntile + parts - 1) / parts;
+        const int64_t fewest = (int64_t)ctx->n * parts * ctx->r * least, first = (fewest + 255) / 256;
+        for (int64_t rounds = first; rounds <= first + 1; ++rounds) {
+            int32_t win[SAMS_MAX_ROWS];
+            int64_t windows = 0;
+            for (int j = 0; j < ctx->r; ++j) windows += win[j] = least;
+            double worst = 0;
+            for (;;) {                                               // a window more for the row whose windows take longest
+                int at = 0;
+                worst = 0;
+                for (int j = 0; j < ctx->r; ++j) {
+                    const int32_t per_win = (po.nlist + win[j] - 1) / win[j], per_wave = (per_win + kPullAdders - 1) / kPullAdders;
+                    const double all = steps[j] / win[j] * kStepNs, chain = steps[j] / po.nlist * per_wave * kChainNs, x = all > chain ? all : chain;
+                    if (x > worst) {
+                        worst = x;
+                        at = j;
+                    }
+                }
+                if ((windows + 1) * parts * ctx->n > rounds * 256 || win[at] >= po.nlist) break;
+                ++win[at];
+                ++windows;
+            }
+            const double cost = (double)rounds * (per_part * (kTileNs + worst) + kStartNs);
             if (cost >= best) continue;
             best = cost;
-            pp.per_wave = pw;
-            pp.parts = parts;
-            nwin = parts == 1 ? rounds * 256 / pairs : least;        // as many windows as the rounds have room for
+            po.parts = (po.ntile + per_part - 1) / per_part;
+            po.per_part = per_part;
+            po.windows = 0;
+            for (int j = 0; j < ctx->r; ++j) {
+                PullRow &row = po.row[j];
+                row.per_win = (po.nlist + win[j] - 1) / win[j];
+                row.per_wave = (row.per_win + kPullAdders - 1) / kPullAdders;
+                row.win0 = po.windows;
+                po.windows += (po.nlist + row.per_win - 1) / row.per_win;
+            }
+            po.row[ctx->r] = PullRow{po.windows, 0, 0};
         }
     }
-    if (nwin > pp.nslice) nwin = pp.nslice;
-    pp.per_win = (int32_t)((pp.nslice + nwin - 1) / nwin);
-    pp.per_win = (pp.per_win + pp.per_wave - 1) / pp.per_wave * pp.per_wave;
-    pp.nwin = (pp.nslice + pp.per_win - 1) / pp.per_win;
-    pp.per_part = (pp.ntile + pp.parts - 1) / pp.parts;
-    pp.parts = (pp.ntile + pp.per_part - 1) / pp.per_part;           // none is empty
-    // The binned path cuts a table of up to 2^12 buckets into windows of 2^7 until it has 1024 workgroups: with few pairs under
-    // a long vector many short streams, where every puller has to take in the whole vector.  In ns: 820 per tile here; there a
-    // base, 0.67 per position of a window's stream, 1.6 per thousand terms through staging.  Lists and bins (us), one pair of 4,096
-    // buckets: d = 431,003 25 and 28, a million 67 and 40, four million 257 and 109; 2 x 3 of 3,000, four million 256 and
-    // 174; 4 x 5 of 4,096, four million 290 and 256, a million 76 and 85; 2 x 5 of 2,000, four million 264 and 263.
-    if (ctx->d >= kPullLongD && ctx->d <= kOrderedSingleBinMaxD && ctx->c <= (1 << 12)) {
-        const int64_t bins = 25000 + 86 * ctx->d / ctx->c + pairs * ctx->d * 16 / 10000, here = best * 820;
-        if (pairs * ((ctx->c + 127) / 128) < 2048 && bins < here) return false;
-    }
-    return true;
+    return (int64_t)best;
 }
 
-// Whether the other path is faster with lists of this many steps.  A tile takes a workgroup 0.64 us and 5.1 ns per step; with many
-// pairs and more than 2^13 buckets, several rounds of workgroups with up to 56 slices each, that can exceed the 2 us per
-// million terms of the binned path (or, above 2^22 coordinates, of LDS atomics).  Both (ms): 5 x 16,384, n = 50, d = four
-// million 2.39 and 1.93, ten million 7.2 and 4.9; 5 x 9,001 (a row whose lists are half padding), n = 32, five million
-// 2.79 and 2.21; 5 x 12,000, n = 50, four million 1.78 and 1.94.
-static bool pull_slower(const sams_ctx *ctx, const PullPlan &pp, int64_t steps)
+// Whether the context takes the binned path (or, above 2^22 coordinates, LDS atomics) all the same.  Of 76 shapes with 0.4 to 20 million
+// coordinates, 1 to 64 workers, 1 to 10 rows and 128 to 16,384 buckets the lists are the faster at 74, two to ten times so at most; not
+// where few pairs walk a long vector through few short streams: one row of 4,096 under four million coordinates, n = 1, 161 and
+// 106 us, three of 3,000, n = 2, 193 and 175 us.  In ns, as both were before the lists came in groups of four slices, and the line is
+// where it was: 820 per tile here, there a base, 0.67 per position of a window's stream and 1.6 per thousand terms.  The widest
+// tables for many pairs stay binned too (tests pin that), although the lists have overtaken: 5 x 16,384, n = 50, four million
+// 1.9 ms, by lists 0.95 to 1.5 by the hash.
+static bool pull_declines(const sams_ctx *ctx, int32_t ntile)
 {
     const int64_t pairs = (int64_t)ctx->n * ctx->r;
-    if (ctx->d < kPullLongD || ctx->c <= (1 << 13) || pairs < 160) return false;
-    const int64_t rounds = (pairs * pp.nwin * pp.parts + 255) / 256;
-    const int64_t here = rounds * pp.per_part * 640 + rounds * pp.per_part * 51 / 10 * steps / ((int64_t)ctx->r * pp.nwin * pp.ntile);
-    return here > 25000 + 2 * pairs * ctx->d / 1000;
-}
-
-static PullOrder pull_order(const PullPlan &pp)
-{
-    return {pp.ntile, pp.nslice, pp.per_win, pp.nwin, pp.group, pp.per_wave, pp.parts, pp.per_part};
+    if (ctx->d < kPullLongD) return false;
+    if (ctx->c > kPullWideC && pairs >= 160) return true;
+    if (ctx->d > kOrderedSingleBinMaxD || ctx->c > (1 << 12) || pairs * ((ctx->c + 127) / 128) >= 2048) return false;
+    return 25000 + 86 * ctx->d / ctx->c + pairs * ctx->d * 16 / 10000 < ((int64_t)ntile + 12) * 820;
 }
 
 // SAMS_OK with *done saying whether the context pulls; device memory that cannot be had means it does not
@@ -433,90 +502,137 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
 {
     *done = false;
     PullPlan pp = {};
-    if (!pull_shape(ctx, tun, pp)) return SAMS_OK;
-    // Groups of eight steps where the lists of a tile are long (13308 / c entries on average, the longest of 64 decides),
-    // else of four; of two where a wavefront has four lists per tile and the steps, padding among them, are what
-    // bounds the kernel (5 x 10,000, n = 4, 25.6 million coordinates: 1.13 -> 1.00 ms)
-    const int32_t group = ctx->c <= 4096 ? 4 : (pp.per_wave == 4 ? 1 : 2);
-    pp.group = group;
-    const void *const kernels[2][3] = {
-        {(const void *)k_sketch_pull<2, 8, 1>, (const void *)k_sketch_pull<2, 8, 2>, (const void *)k_sketch_pull<1, 16, 4>},
-        {(const void *)k_sketch_pull<4, 6, 1>, (const void *)k_sketch_pull<4, 6, 2>, (const void *)k_sketch_pull<4, 6, 4>}};
-    pp.kernel = kernels[group == 4][pp.per_wave / 2];
-    const PullOrder po = pull_order(pp);
-    const int64_t streams = stream_number(po, ctx->r, 0, 0, 0), per_stream = (int64_t)pp.per_part * pp.per_wave,
-                  lists = streams * per_stream;
-    const int64_t part_bytes = pp.parts > 1 ? (int64_t)pp.parts * ctx->n * ctx->r * ctx->c * 4 : 0;
-    uint32_t *longest = nullptr, *off = nullptr;                     // build-time only
-    uint32_t *h_off = (uint32_t *)malloc((size_t)(lists + 1) * 4), *h_first = (uint32_t *)malloc((size_t)(streams + 1) * 4);
+    const int32_t ntile = (int32_t)((ctx->d + kPullTile - 1) / kPullTile), nslice = (int32_t)((ctx->c + kWave - 1) / kWave);
+    if (!pull_shape(ctx, tun) || pull_declines(ctx, ntile)) return SAMS_OK;
+    const int64_t rows = (int64_t)ctx->r * ntile;                    // (row, tile) pairs
+    uint16_t *cnt = nullptr, *len = nullptr;                         // build-time only
+    uint32_t *off = nullptr;
+    uint16_t *h_cnt = (uint16_t *)malloc((size_t)(rows * nslice) * 2), *h_len = (uint16_t *)malloc((size_t)(rows * nslice) * 2);
+    uint32_t *h_off = (uint32_t *)malloc((size_t)(rows * nslice) * 4), *h_first = nullptr;
     int rc = SAMS_OK;
     do {
-        if (!h_off || !h_first || hipMalloc((void **)&longest, 4) != hipSuccess || hipMalloc((void **)&off, (size_t)(lists + 1) * 4) != hipSuccess ||
-            hipMalloc((void **)&pp.first, (size_t)(streams + 1) * 4) != hipSuccess)
-            break;
-        const dim3 grid((unsigned)pp.ntile, (unsigned)ctx->r);
-        const int lds_count = listed_slices(po) * kWave * 4, lds_place = lds_count + kPullTile * 2;
+        if (!h_cnt || !h_len || !h_off || hipMalloc((void **)&cnt, (size_t)(rows * nslice) * 2) != hipSuccess) break;
+        const dim3 grid((unsigned)ntile, (unsigned)ctx->r);
         const int lds_max = kPullLds;                                // more than the other two kernels need
         hipError_t e = hipFuncSetAttribute((const void *)k_pull_count, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
         if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_pull_place, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
-        if (e == hipSuccess) e = hipFuncSetAttribute(pp.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
         if (e != hipSuccess) { g_last_hip_error = (int)e; rc = SAMS_EHIP; break; }
-        rc = enqueue_fill_u32(ctx, longest, 1, 0u);
-        if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, off, lists, 0u);   // lists that no slice has stay empty
-        if (rc != SAMS_OK) break;
         {
             ProfScope ps(ctx, KID_PLAN_BUILD);
-            hipLaunchKernelGGL(k_pull_count, grid, dim3(1024), (size_t)lds_count, ctx->stream, ctx->hp, ctx->d, po, off, longest);
+            hipLaunchKernelGGL(k_pull_count, grid, dim3(1024), (size_t)nslice * kWave * 4, ctx->stream, ctx->hp, ctx->d, ntile, nslice, cnt);
         }
-        uint32_t h_longest = 0;
-        e = hipMemcpyAsync(h_off, off, (size_t)lists * 4, hipMemcpyDeviceToHost, ctx->stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(&h_longest, longest, 4, hipMemcpyDeviceToHost, ctx->stream);
+        e = hipMemcpyAsync(h_cnt, cnt, (size_t)(rows * nslice) * 2, hipMemcpyDeviceToHost, ctx->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
         if (e != hipSuccess) { g_last_hip_error = (int)e; rc = SAMS_EHIP; break; }
-        uint64_t run = 0;
-        for (int64_t q = 0; q < lists; ++q) {
-            const uint32_t len = h_off[q];
-            if (q % per_stream == 0) h_first[q / per_stream] = (uint32_t)run;
-            h_off[q] = (uint32_t)run;
-            run += len;
+        uint32_t longest = 0;
+        for (int64_t q = 0; q < rows * nslice; ++q) longest = h_cnt[q] > longest ? h_cnt[q] : longest;
+        if (longest > kPullMaxList) break;                           // a hash that crowds a tile's coordinates into few buckets
+        // Both kernels' lists, and how they would be shared out.  Lists of one slice in units of eight steps where a tile has many
+        // entries for a bucket, else of four (5 x 4,096, n = 8, two million: 112 and 105 us; 9,001: 29 and 25; 2,048: 7.1 and 6.8;
+        // 400: alike)
+        PullOrder po = {};
+        int64_t cost = INT64_MAX, steps = 0;
+        for (int many = 0; many < 2; ++many) {
+            PullOrder x = {};
+            x.ntile = ntile;
+            x.nslice = nslice;
+            x.per_list = many ? kPullLoad : 1;
+            x.group = many ? kPullLoad : (ctx->c <= 1500 ? 4 : 2);
+            x.nlist = (nslice + x.per_list - 1) / x.per_list;
+            double per_tile[SAMS_MAX_ROWS];
+            int64_t all = 0;
+            for (int j = 0; j < ctx->r; ++j) {
+                int64_t units = 0;
+                for (int64_t t = 0; t < ntile; ++t)
+                    for (int32_t l = 0; l < x.nlist; ++l) units += list_units(x, h_cnt + (j * (int64_t)ntile + t) * nslice, l);
+                per_tile[j] = (double)units * 2 * x.group / ntile;
+                all += units * 2 * x.group;
+            }
+            const int64_t c = pull_share(ctx, x, per_tile);
+            if (c < cost) {
+                cost = c;
+                po = x;
+                steps = all;
+            }
         }
-        // A hash that crowds a tile's coordinates into few buckets makes long or mostly empty lists: not for this path.
-        const uint64_t steps = run * 2 * group * kWave, fair = 12ull * (uint64_t)ctx->r * (uint64_t)ctx->d + 8ull * kWave * lists;
-        if (h_longest > kPullMaxList || steps > fair || run >= (1ull << 31) || pull_slower(ctx, pp, (int64_t)(run * 2 * group))) break;
-        h_first[streams] = (uint32_t)run;
-        h_off[lists] = (uint32_t)run;
-        pp.list_bytes = (int64_t)(run * group + kPullSpare) * kWave * 4;
-        if (hipMalloc((void **)&pp.lists, (size_t)pp.list_bytes) != hipSuccess) break;
+        const int64_t lists = rows * po.nlist, streams = stream_number(po, po.parts, 0, 0);
+        const int64_t part_bytes = po.parts > 1 ? (int64_t)po.parts * ctx->n * ctx->r * ctx->c * 4 : 0;
+        // lists that are mostly padding
+        if ((uint64_t)steps * kWave > 12ull * (uint64_t)ctx->r * (uint64_t)ctx->d + 8ull * kWave * (uint64_t)lists * po.per_list) break;
+        h_first = (uint32_t *)malloc((size_t)streams * 8);
+        if (!h_first) break;
+        uint64_t run = 0;                                            // units; streams start with a load of their own
+        const uint64_t per_load = (uint64_t)(kPullLoad / po.group);
+        for (int32_t part = 0; part < po.parts; ++part)
+            for (int32_t j = 0; j < ctx->r; ++j)
+                for (int32_t w = po.row[j].win0; w < po.row[j + 1].win0; ++w)
+                    for (int32_t wave = 0; wave < kPullAdders; ++wave) {
+                        int32_t l0, count;
+                        lists_of(po, j, w, wave, &l0, &count);
+                        run = (run + per_load - 1) / per_load * per_load;
+                        uint32_t *f = h_first + 2 * stream_number(po, part, w, wave);
+                        f[0] = (uint32_t)(run / per_load);
+                        const uint64_t before = run;
+                        const int32_t t1 = (part + 1) * po.per_part < ntile ? (part + 1) * po.per_part : ntile;
+                        for (int32_t t = part * po.per_part; count > 0 && t < t1; ++t) {
+                            const int64_t rt = (int64_t)j * ntile + t;
+                            for (int32_t l = l0; l < l0 + count; ++l) {
+                                const uint32_t units = list_units(po, h_cnt + rt * nslice, l);
+                                h_off[rt * po.nlist + l] = (uint32_t)run;
+                                h_len[rt * po.nlist + l] = (uint16_t)units;
+                                run += units;
+                            }
+                        }
+                        f[1] = (uint32_t)(run - before);
+                    }
+        run = (run + per_load - 1) / per_load * per_load;
+        if (run >= (1ull << 31)) break;
+        pp.kernel = po.per_list > 1 ? (const void *)k_sketch_pull<1, true>
+                                    : (po.group == 4 ? (const void *)k_sketch_pull<4, false> : (const void *)k_sketch_pull<2, false>);
+        e = hipFuncSetAttribute(pp.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
+        if (e != hipSuccess) { g_last_hip_error = (int)e; rc = SAMS_EHIP; break; }
+        pp.list_bytes = (int64_t)(run * (uint64_t)po.group + kPullSpare) * kWave * 4;
+        pp.first_bytes = streams * 8;
+        pp.po = (PullOrder *)malloc(sizeof(PullOrder));
+        if (!pp.po) break;
+        *pp.po = po;
+        pp.parts = po.parts;
+        if (hipMalloc((void **)&len, (size_t)lists * 2) != hipSuccess || hipMalloc((void **)&off, (size_t)lists * 4) != hipSuccess ||
+            hipMalloc((void **)&pp.first, (size_t)pp.first_bytes) != hipSuccess || hipMalloc((void **)&pp.lists, (size_t)pp.list_bytes) != hipSuccess)
+            break;
         if (part_bytes && hipMalloc((void **)&pp.part_sums, (size_t)part_bytes) != hipSuccess) break;
-        e = hipMemcpyAsync(off, h_off, (size_t)(lists + 1) * 4, hipMemcpyHostToDevice, ctx->stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(pp.first, h_first, (size_t)(streams + 1) * 4, hipMemcpyHostToDevice, ctx->stream);
+        e = hipMemcpyAsync(off, h_off, (size_t)lists * 4, hipMemcpyHostToDevice, ctx->stream);
+        if (e == hipSuccess) e = hipMemcpyAsync(len, h_len, (size_t)lists * 2, hipMemcpyHostToDevice, ctx->stream);
+        if (e == hipSuccess) e = hipMemcpyAsync(pp.first, h_first, (size_t)pp.first_bytes, hipMemcpyHostToDevice, ctx->stream);
         if (e != hipSuccess) { g_last_hip_error = (int)e; rc = SAMS_EHIP; break; }
         {
             ProfScope ps(ctx, KID_PLAN_BUILD);
-            hipLaunchKernelGGL(k_pull_place, grid, dim3(1024), (size_t)lds_place, ctx->stream, ctx->hp, ctx->d, po, off, pp.lists);
+            hipLaunchKernelGGL(k_pull_place, grid, dim3(1024), (size_t)(po.nlist * po.per_list * kWave * 4 + kPullTile * 2), ctx->stream, ctx->hp,
+                               ctx->d, po, len, off, pp.lists);
         }
         e = hipStreamSynchronize(ctx->stream);                       // the host arrays are released below
         if (e == hipSuccess) e = hipGetLastError();
         if (e != hipSuccess) { g_last_hip_error = (int)e; rc = SAMS_EHIP; break; }
         *done = true;
+        ctx->scratch_bytes += pp.list_bytes + pp.first_bytes + part_bytes;
     } while (0);
     (void)hipGetLastError();
+    free(h_cnt);
+    free(h_len);
     free(h_off);
     free(h_first);
-    if (longest) (void)hipFree(longest);
+    if (cnt) (void)hipFree(cnt);
+    if (len) (void)hipFree(len);
     if (off) (void)hipFree(off);
     ctx->pull = pp;
-    if (*done) {
-        ctx->plan.mode = pp.parts == 1 ? PLAN_BINNED : PLAN_LDS_ROW; // to the caller: whether the order is the coordinates'
-        ctx->scratch_bytes += pp.list_bytes + (streams + 1) * 4 + part_bytes;
-    } else {
-        pull_destroy(ctx);
-    }
+    if (*done) ctx->plan.mode = pp.parts == 1 ? PLAN_BINNED : PLAN_LDS_ROW;   // to the caller: whether the order is the coordinates'
+    else pull_destroy(ctx);
     return rc;
 }
 
 void pull_destroy(sams_ctx *ctx)
 {
+    free(ctx->pull.po);
     if (ctx->pull.first) (void)hipFree(ctx->pull.first);
     if (ctx->pull.lists) (void)hipFree(ctx->pull.lists);
     if (ctx->pull.part_sums) (void)hipFree(ctx->pull.part_sums);
@@ -528,8 +644,8 @@ int enqueue_sketch_pull(sams_ctx *ctx, const float *u, float *S_workers)
     const PullPlan &pp = ctx->pull;
     const int64_t cells = (int64_t)ctx->n * ctx->r * ctx->c;
     PullArgs a = {u, pp.lists, pp.first, pp.parts > 1 ? pp.part_sums : S_workers, ctx->d, ctx->c, (int64_t)ctx->n * ctx->d, ctx->n,
-                  ctx->r, pull_order(pp)};
-    const int64_t wgs = (int64_t)ctx->n * ctx->r * pp.nwin * pp.parts;
+                  ctx->r, *pp.po};
+    const int64_t wgs = (int64_t)ctx->n * a.po.windows * a.po.parts;
     void *args[] = {&a};
     {
         ProfScope ps(ctx, KID_SKETCH_PULL);
