@@ -91,13 +91,13 @@ __device__ __forceinline__ int64_t list_number(const PullOrder &po, int j, int64
     return ((int64_t)j * po.ntile + tile) * po.nlist + list;
 }
 
-// per (tile, row): the longest of the 64 columns of every slice, at len[(row * ntile + tile) * nslice + slice]
+// per (row, every step-th tile): the longest of the 64 columns of every slice, at len[(row * gridDim.x + blockIdx.x) * nslice + slice]
 __global__ void __launch_bounds__(1024)
-k_pull_count(HashParams hp, int64_t d, int32_t ntile, int32_t nslice, uint16_t *__restrict__ len)
+k_pull_count(HashParams hp, int64_t d, int32_t step, int32_t nslice, uint16_t *__restrict__ len)
 {
     extern __shared__ uint32_t cnt[];                                // [nslice * 64]
     const int j = blockIdx.y;
-    const int64_t l0 = (int64_t)blockIdx.x * kPullTile;
+    const int64_t l0 = (int64_t)blockIdx.x * step * kPullTile;
     const int lim = d - l0 < kPullTile ? (int)(d - l0) : kPullTile;
     for (int b = threadIdx.x; b < nslice * kWave; b += 1024) cnt[b] = 0;
     __syncthreads();
@@ -110,7 +110,7 @@ k_pull_count(HashParams hp, int64_t d, int32_t ntile, int32_t nslice, uint16_t *
             const uint32_t o = __shfl_xor(m, off);
             m = o > m ? o : m;
         }
-        if (lane == 0) len[((int64_t)j * ntile + blockIdx.x) * nslice + s] = (uint16_t)m;
+        if (lane == 0) len[((int64_t)j * gridDim.x + blockIdx.x) * nslice + s] = (uint16_t)m;
     }
 }
 
@@ -403,18 +403,19 @@ k_pull_sum(const float *__restrict__ part, float *__restrict__ S, int64_t cells,
 // ------------------------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------------------------
-// Whether this shape may pull (see pull_declines, and pull_create on its lists).  Tables of 128 to 2^14 buckets under vectors of up to 2^26
-// coordinates.  With fewer buckets a bucket's list gets too long to sort by insertion at creation, with more the lists of a
-// tile's 64 buckets get too uneven (on average one entry with 2^14 buckets, the longest of 64 four); the lists of
-// longer vectors take gigabytes.
+// Whether this shape may pull (see pull_declines, and pull_create on its lists).  Tables of 128 to 2^15 buckets under vectors of up to
+// 2^26 coordinates.  With fewer buckets a bucket's list gets too long to sort by insertion at creation, with more the lists of a
+// tile's 64 buckets are padding but for a tenth (13,308 coordinates and a step or two for each of 512 slices), and their making would
+// not fit in LDS; the lists of longer vectors take gigabytes.
 constexpr int64_t kPullLongD = 1000000;       // shorter vectors always pull: both paths are launches and latencies
-constexpr int64_t kPullWideC = 15000;
+constexpr int64_t kPullWidePinned = 15000, kPullWide = 1 << 14, kPullMaxC = 1 << 15, kPullWideMinD = 1 << 18;
 static bool pull_shape(const sams_ctx *ctx, const Tunables &tun)
 {
     if (tun.sketch_path != 0 || tun.estimate_path == 2 || tun.win_log2 || tun.tile_log2 || tun.chunk_log2 || tun.acc_threads ||
         tun.stage_rows)
         return false;                                                // the caller asks for the binned path or for a shape of it
-    return ctx->c >= 128 && ctx->c <= (1 << 14) && ctx->d <= ((int64_t)1 << 26) && (int64_t)ctx->n * ctx->d >= 4;
+    if (ctx->c > kPullWide && ctx->d < kPullWideMinD) return false;
+    return ctx->c >= 128 && ctx->c <= kPullMaxC && ctx->d <= ((int64_t)1 << 26) && (int64_t)ctx->n * ctx->d >= 4;
 }
 
 // units of a list: of one slice, `group` words of two steps; of several, a word of each
@@ -485,14 +486,18 @@ static int64_t pull_share(const sams_ctx *ctx, PullOrder &po, const double *step
 // coordinates, 1 to 64 workers, 1 to 10 rows and 128 to 16,384 buckets the lists are the faster at 74, two to ten times so at most; not
 // where few pairs walk a long vector through few short streams: one row of 4,096 under four million coordinates, n = 1, 161 and
 // 106 us, three of 3,000, n = 2, 193 and 175 us.  In ns, as both were before the lists came in groups of four slices, and the line is
-// where it was: 820 per tile here, there a base, 0.67 per position of a window's stream and 1.6 per thousand terms.  The widest
-// tables for many pairs stay binned too (tests pin that), although the lists have overtaken: 5 x 16,384, n = 50, four million
-// 1.9 ms, by lists 0.95 to 1.5 by the hash.
+// where it was: 820 per tile here, there a base, 0.67 per position of a window's stream and 1.6 per thousand terms.  Tables of
+// 15,000 to 2^14 buckets for many pairs stay binned too (tests pin that), although the lists have overtaken: 5 x 16,384, n = 50, four
+// million 1.9 ms, by lists 0.95 to 1.5 by the hash.
+// Above 2^14 buckets the line is the cost that pull_share returns against 1.75 ns per thousand terms by bins: of 66 shapes with 0.27 to
+// 21 million coordinates and 16,400 to 32,700 buckets the lists are the faster at 65, 1.0 to 2.5 times up to 2^22 coordinates (where
+// one of 40 others, 7 x 29,777 and n = 32 under 2.6 million, lost with 1,288 us to 1,005), two to 26 times above, where the others are
+// LDS atomics.
 static bool pull_declines(const sams_ctx *ctx, int32_t ntile)
 {
     const int64_t pairs = (int64_t)ctx->n * ctx->r;
     if (ctx->d < kPullLongD) return false;
-    if (ctx->c > kPullWideC && pairs >= 160) return true;
+    if (ctx->c > kPullWidePinned && ctx->c <= kPullWide && pairs >= 160) return true;
     if (ctx->d > kOrderedSingleBinMaxD || ctx->c > (1 << 12) || pairs * ((ctx->c + 127) / 128) >= 2048) return false;
     return 25000 + 86 * ctx->d / ctx->c + pairs * ctx->d * 16 / 10000 < ((int64_t)ntile + 12) * 820;
 }
@@ -517,36 +522,44 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
         hipError_t e = hipFuncSetAttribute((const void *)k_pull_count, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
         if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_pull_place, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
         if (e != hipSuccess) { g_last_hip_error = (int)e; rc = SAMS_EHIP; break; }
-        {
-            ProfScope ps(ctx, KID_PLAN_BUILD);
-            hipLaunchKernelGGL(k_pull_count, grid, dim3(1024), (size_t)nslice * kWave * 4, ctx->stream, ctx->hp, ctx->d, ntile, nslice, cnt);
-        }
-        e = hipMemcpyAsync(h_cnt, cnt, (size_t)(rows * nslice) * 2, hipMemcpyDeviceToHost, ctx->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-        if (e != hipSuccess) { g_last_hip_error = (int)e; rc = SAMS_EHIP; break; }
-        uint32_t longest = 0;
-        for (int64_t q = 0; q < rows * nslice; ++q) longest = h_cnt[q] > longest ? h_cnt[q] : longest;
-        if (longest > kPullMaxList) break;                           // a hash that crowds a tile's coordinates into few buckets
-        // Both kernels' lists, and how they would be shared out.  Lists of one slice in units of eight steps where a tile has many
-        // entries for a bucket, else of four (5 x 4,096, n = 8, two million: 112 and 105 us; 9,001: 29 and 25; 2,048: 7.1 and 6.8;
-        // 400: alike)
+        // every step-th tile's longest columns, to the host
+        auto count = [&](int32_t step) {
+            const int64_t tiles = (ntile + step - 1) / step;
+            {
+                ProfScope ps(ctx, KID_PLAN_BUILD);
+                hipLaunchKernelGGL(k_pull_count, dim3((unsigned)tiles, (unsigned)ctx->r), dim3(1024), (size_t)nslice * kWave * 4, ctx->stream,
+                                   ctx->hp, ctx->d, step, nslice, cnt);
+            }
+            e = hipMemcpyAsync(h_cnt, cnt, (size_t)(ctx->r * tiles * nslice) * 2, hipMemcpyDeviceToHost, ctx->stream);
+            if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+            if (e != hipSuccess) { g_last_hip_error = (int)e; rc = SAMS_EHIP; }
+            return e == hipSuccess;
+        };
+        // What the choice rests on: up to 64 tiles of each row.  A wide table may be declined, and is counted whole only then.
+        const bool wide = ctx->c > kPullWide;
+        const int32_t sample = (ntile + 63) / 64, counted = wide ? sample : 1;
+        if (!count(counted)) break;
+        // Both kernels' lists, and how they would be shared out.  Lists of one slice (not for a wide table: none was faster) in units of
+        // eight steps where a tile has many entries for a bucket, else of four (5 x 4,096, n = 8, two million: 112 and 105 us; 9,001:
+        // 29 and 25; 2,048: 7.1 and 6.8; 400: alike)
         PullOrder po = {};
-        int64_t cost = INT64_MAX, steps = 0;
-        for (int many = 0; many < 2; ++many) {
+        int64_t cost = INT64_MAX;
+        double steps = 0;
+        for (int many = wide; many < 2; ++many) {
             PullOrder x = {};
             x.ntile = ntile;
             x.nslice = nslice;
             x.per_list = many ? kPullLoad : 1;
             x.group = many ? kPullLoad : (ctx->c <= 1500 ? 4 : 2);
             x.nlist = (nslice + x.per_list - 1) / x.per_list;
-            double per_tile[SAMS_MAX_ROWS];
-            int64_t all = 0;
+            double per_tile[SAMS_MAX_ROWS], all = 0;
+            const int64_t tiles = (ntile + counted - 1) / counted, every = wide ? 1 : sample;
             for (int j = 0; j < ctx->r; ++j) {
-                int64_t units = 0;
-                for (int64_t t = 0; t < ntile; ++t)
-                    for (int32_t l = 0; l < x.nlist; ++l) units += list_units(x, h_cnt + (j * (int64_t)ntile + t) * nslice, l);
-                per_tile[j] = (double)units * 2 * x.group / ntile;
-                all += units * 2 * x.group;
+                int64_t units = 0, seen = 0;
+                for (int64_t t = 0; t < tiles; t += every, ++seen)
+                    for (int32_t l = 0; l < x.nlist; ++l) units += list_units(x, h_cnt + (j * tiles + t) * nslice, l);
+                per_tile[j] = (double)units * 2 * x.group / seen;
+                all += per_tile[j] * ntile;
             }
             const int64_t c = pull_share(ctx, x, per_tile);
             if (c < cost) {
@@ -555,10 +568,14 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
                 steps = all;
             }
         }
+        if (wide && cost > 25000 + (int64_t)ctx->n * ctx->r * ctx->d * 7 / 4000) break;   // (see pull_declines)
+        if (steps * kWave > 12.0 * ctx->r * (double)ctx->d + 8.0 * kWave * (double)rows * nslice) break;   // lists that are mostly padding
+        if (counted > 1 && !count(1)) break;
+        uint32_t longest = 0;
+        for (int64_t q = 0; q < rows * nslice; ++q) longest = h_cnt[q] > longest ? h_cnt[q] : longest;
+        if (longest > kPullMaxList) break;                           // a hash that crowds a tile's coordinates into few buckets
         const int64_t lists = rows * po.nlist, streams = stream_number(po, po.parts, 0, 0);
         const int64_t part_bytes = po.parts > 1 ? (int64_t)po.parts * ctx->n * ctx->r * ctx->c * 4 : 0;
-        // lists that are mostly padding
-        if ((uint64_t)steps * kWave > 12ull * (uint64_t)ctx->r * (uint64_t)ctx->d + 8ull * kWave * (uint64_t)lists * po.per_list) break;
         h_first = (uint32_t *)malloc((size_t)streams * 8);
         if (!h_first) break;
         uint64_t run = 0;                                            // units; streams start with a load of their own

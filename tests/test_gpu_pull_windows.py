@@ -63,3 +63,25 @@ def test_parts_with_windows_of_their_own(d, n, r, c, rows):
     o = Oracle("f32")
     for i in range(n):
         assert np.array_equal(got[i], o.sketch(u[i], hp, c)), i
+
+
+@pytest.mark.parametrize("d,n,r,c,pulls", [
+    (262_144, 4, 3, 16_385, True), (262_143, 4, 3, 16_385, False), (300_001, 2, 2, 32_767, True), (300_007, 3, 5, 20_001, True), (280_001, 16, 2, 32_768, True),
+    (280_003, 2, 2, 32_769, False), ((1 << 22) + 9, 2, 2, 32_768, True)])
+def test_wide_tables(d, n, r, c, pulls):
+    """Tables of more than 2^14 buckets pull from 2^18 coordinates on, up to 2^15 buckets; the others are binned: same bits."""
+    from paper_2210_07454_amd import sams
+    rng = np.random.default_rng(d + c)
+    hp = inputs.hash_params(r, seed=8)                               # no row of long lists, which would be binned
+    whole = d > 1 << 22                                              # the order of the additions is not promised
+    u = rng.integers(-3, 4, (n, d)).astype(np.float32) if whole else rng.standard_normal((n, d)).astype(np.float32)
+    S = torch.full((n, r, c), 9.0, device="cuda")
+    with sams.Context(d, n, r, c, 1, hp) as ctx:
+        ctx.sams_profile_enable(True)
+        ctx.sketch_accumulate(torch.from_numpy(u).cuda(), S)
+        ctx.sams_profile_enable(False)
+        assert ("k_sketch_pull" in ctx.sams_profile_read()) == pulls
+        got = S.cpu().numpy()
+    o = Oracle("f32")
+    for i in range(n):
+        assert np.array_equal(got[i].view(np.uint32) if not whole else got[i], o.sketch(u[i], hp, c).view(np.uint32) if not whole else o.sketch(u[i], hp, c)), i
