@@ -31,6 +31,8 @@ constexpr int64_t kOrderedSingleBinMaxD = (int64_t)1 << 22;     // largest d ske
 constexpr int kHistBins = 2048;     // first radix digit of the selection: 11 bits, then 10 and 10 (kHistBins / 2 bins)
 constexpr int kSelTileLog2 = 12;    // keys per tile of the filters: 1024 threads, 4 each
 constexpr int kSelMaxTiles = 16;    // kSelSmallMax keys
+constexpr int kSelFlatTiles = 256;       // tiles whose lists one workgroup may finish a selection from
+constexpr int64_t kSelFlatMax = (int64_t)kSelFlatTiles << kSelTileLog2;
 constexpr int64_t kSelSmallMax = 1 << 16;   // keys up to which the selection is one launch after the first histogram (for small k)
 
 // device-resident state of the radix selection (no host round trip inside a step).  A selection starts from histograms and

@@ -14,21 +14,35 @@ namespace sams {
 // ------------------------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t mag_key(float x) { return __float_as_uint(x) & 0x7fffffffu; }
 
-// HIST: a selection follows, and the histogram of the first digit of |est| is taken here (as in k_bin_collect_median).
+// What a kernel that takes the histogram of the first digit of |est| does at its end (as k_bin_collect_median): the workgroup's
+// histogram to the whole one, and where st is given the last workgroup picks the digit.
+__device__ __forceinline__ void hist_finish(uint32_t *lh, uint32_t k, SelState *__restrict__ st, uint32_t *__restrict__ hist)
+{
+    __syncthreads();
+    for (int b = threadIdx.x; b < kHistBins; b += 1024)
+        if (lh[b]) atomicAdd(&hist[b], lh[b]);
+    if (!st) return;
+    __syncthreads();                                                 // lh is free again: a few words for the last workgroup
+    if (last_workgroup(&st->done[0], gridDim.x, lh)) sel_pick<1024>(st, hist, 0, k, lh + 32, lh + 2);
+}
+
+// HIST: a selection follows, and the histogram of the first digit of |est| is taken here, by workgroups of 1024 threads that walk the
+// vector with a fixed step: one per compute unit at most, so that there are few histograms to add up (unsketch_topk with a histogram
+// pass of its own, and by up to 128, 256 and 512 workgroups: 110,000 coordinates 24.4, 13.9 us, alike; 431,003 31.6, 21.0, 20.6, 23.0; a
+// million 41, 36, 32, 32; four million, 5 x 30,000 114, 139, 107, 109; the first three with fewer launches of the selection too).
+constexpr int kEstHistGrid = 256;
 template <int R, bool HIST>
 __global__ void __launch_bounds__(HIST ? 1024 : 256)
 k_estimate(const float *__restrict__ S, const float *__restrict__ vhat, float *__restrict__ est,
-           HashParams hp, int64_t d, int64_t c, uint32_t *__restrict__ hist)
+           HashParams hp, int64_t d, int64_t c, uint32_t k, SelState *__restrict__ st, uint32_t *__restrict__ hist)
 {
     __shared__ uint32_t lh[HIST ? kHistBins : 1];
-    const int64_t l = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if constexpr (HIST) {
         for (int b = threadIdx.x; b < kHistBins; b += 1024) lh[b] = 0;
         __syncthreads();
-    } else {
-        if (l >= d) return;
     }
-    if (l < d) {
+    const int64_t step = HIST ? (int64_t)gridDim.x * 1024 : d;
+    for (int64_t l = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; l < d; l += step) {
         float a[R];
 #pragma unroll
         for (int j = 0; j < R; ++j) {
@@ -41,11 +55,7 @@ k_estimate(const float *__restrict__ S, const float *__restrict__ vhat, float *_
         est[l] = e;
         if constexpr (HIST) atomicAdd(&lh[mag_key(e) >> 20], 1u);
     }
-    if constexpr (HIST) {
-        __syncthreads();
-        for (int b = threadIdx.x; b < kHistBins; b += 1024)
-            if (lh[b]) atomicAdd(&hist[b], lh[b]);
-    }
+    if constexpr (HIST) hist_finish(lh, k, st, hist);
 }
 
 // The same for long vectors and tables that LDS holds at least a row of: a workgroup per compute unit keeps the first
@@ -57,16 +67,18 @@ constexpr int kEstLdsUnroll = 4;
 template <int R>
 __global__ void __launch_bounds__(1024)
 k_estimate_lds(const float *__restrict__ S, const float *__restrict__ vhat, float *__restrict__ est, HashParams hp, int64_t d,
-               int32_t c, uint32_t m, int32_t held)
+               int32_t c, uint32_t m, int32_t held, uint32_t k, SelState *__restrict__ st, uint32_t *__restrict__ hist)
 {
-    extern __shared__ float rows[];
+    extern __shared__ float rows[];                                  // [held][c], and with hist a histogram (see k_estimate)
     const int t = threadIdx.x;
+    uint32_t *lh = reinterpret_cast<uint32_t *>(rows + held * c);
+    if (hist)
+        for (int b = t; b < kHistBins; b += 1024) lh[b] = 0;
     for (int q = t; q < held * c; q += 1024) rows[q] = S[q];
     __syncthreads();
     const int64_t step = (int64_t)gridDim.x * 1024;
     uint32_t yb[R], ys[R], ab[R], as[R];
     int64_t l = blockIdx.x * (int64_t)1024 + t;
-    if (l >= d) return;
 #pragma unroll
     for (int j = 0; j < R; ++j) {
         yb[j] = hash_y(hp.row[j].ah, hp.row[j].bh, (uint32_t)l);
@@ -105,9 +117,14 @@ k_estimate_lds(const float *__restrict__ S, const float *__restrict__ vhat, floa
 #pragma unroll
         for (int z = 0; z < kEstLdsUnroll; ++z) {
             const float med = median_of<R>(a[z]);
-            if (l + z * step < d) est[l + z * step] = vhat ? (med / sqrtf(vh[z])) : med;
+            if (l + z * step < d) {
+                const float e = vhat ? (med / sqrtf(vh[z])) : med;
+                est[l + z * step] = e;
+                if (hist) atomicAdd(&lh[mag_key(e) >> 20], 1u);
+            }
         }
     }
+    if (hist) hist_finish(lh, k, st, hist);
 }
 
 // est[l] = median_j(rowest[j][l]) / sqrt(vhat[l]) from row estimates already in coordinate order
@@ -133,7 +150,8 @@ k_est_median(const float *__restrict__ rowest, const float *__restrict__ vhat, f
 // the selected ones and the candidates, about 1.5 k of them unless many keys are equal -- in coordinate order, every
 // tile of keys in a region of its own.  Everything after that works on the listed keys only (on all keys, without the filter,
 // where a context of more than 2^20 coordinates found no room for lists).
-//   up to 2^16 keys and small k (kSelSmallMaxK): k_sel_small filters, and its last workgroup finishes the selection
+//   up to 2^20 keys and small k (kSelSmallMaxK, kSelFlatMaxK; but see sel_by_launches): k_sel_small filters, and its last
+//   workgroup finishes the selection
 //   else: k_sel_filter, two histograms of the listed keys, k_sel_count, k_sel_write
 // Up to 2^20 keys every filter workgroup picks the first digit from the histogram for itself (8 KiB, in every L2); above,
 // the last workgroup of the histogram does it once.
@@ -288,24 +306,26 @@ __device__ __forceinline__ void filter_tile(const float *__restrict__ keys, int6
     if (t == 15) put<AGENT>(ls.cnt + tile, upto);
 }
 
-// The listed keys of at most 16 tiles as one sequence in coordinate order, for one workgroup of 1024 threads: entry e is
-// number e - start[tile] of its tile's list; the first kFlatMax entries are copied to LDS.
-constexpr uint32_t kFlatMax = 4096;
+// The listed keys of at most TILES tiles as one sequence in coordinate order, for one workgroup of 1024 threads: entry e is
+// number e - start[tile] of its tile's list; the first kMax entries are copied to LDS (64 KB in all, so that two workgroups share a
+// compute unit).
+template <int TILES>
 struct Flat {
-    uint32_t start[2 * kSelMaxTiles];
-    uint32_t val[kFlatMax], pos[kFlatMax];
-    uint32_t part[16], picked[4], hist[2048];
+    static constexpr uint32_t kMax = 7168;
+    uint32_t start[2 * TILES];
+    uint32_t val[kMax], pos[kMax];
+    uint32_t part[16], picked[4], hist[1024];
 };
 
 // entries e[0..N), each below the number of entries: tile by bisection, N searches side by side
-template <bool AGENT, int N>
-__device__ __forceinline__ void flat_fetch(const SelList &ls, const Flat &f, const uint32_t (&e)[N], uint2 (&x)[N])
+template <bool AGENT, int N, int TILES>
+__device__ __forceinline__ void flat_fetch(const SelList &ls, const Flat<TILES> &f, const uint32_t (&e)[N], uint2 (&x)[N])
 {
     uint32_t tile[N];
 #pragma unroll
     for (int z = 0; z < N; ++z) tile[z] = 0;
 #pragma unroll 1
-    for (uint32_t step = kSelMaxTiles; step; step >>= 1) {
+    for (uint32_t step = TILES; step; step >>= 1) {
 #pragma unroll
         for (int z = 0; z < N; ++z)
             if (f.start[tile[z] + step] <= e[z]) tile[z] += step;
@@ -316,25 +336,17 @@ __device__ __forceinline__ void flat_fetch(const SelList &ls, const Flat &f, con
         x[z] = make_uint2(get<AGENT>(ls.val + at), base + get<AGENT>(ls.loc + at));
     }
 }
-template <bool AGENT>
-__device__ __forceinline__ uint2 flat_get(const SelList &ls, const Flat &f, uint32_t e)
-{
-    if (e < kFlatMax) return make_uint2(f.val[e], f.pos[e]);
-    uint2 x[1];
-    flat_fetch<AGENT, 1>(ls, f, {e}, x);
-    return x[0];
-}
-
 // the number of entries; complete for all threads
-template <bool AGENT>
-__device__ __forceinline__ uint32_t flat_load(const SelList &ls, Flat &f, int ntile)
+template <bool AGENT, int TILES>
+__device__ __forceinline__ uint32_t flat_load(const SelList &ls, Flat<TILES> &f, int ntile)
 {
+    static_assert(2 * TILES <= 1024, "a thread per start");
     const int t = threadIdx.x;
     const uint32_t before = block_exclusive_scan<1024>(t < ntile ? get<AGENT>(ls.cnt + t) : 0u, f.part);
-    if (t < 2 * kSelMaxTiles) f.start[t] = before;                   // from ntile on: the number of entries
-    for (int b = t; b < 2048; b += 1024) f.hist[b] = 0;
+    if (t < 2 * TILES) f.start[t] = before;                          // from ntile on: the number of entries
+    f.hist[t] = 0;
     __syncthreads();
-    const uint32_t m = f.start[ntile], mm = m < kFlatMax ? m : kFlatMax;
+    const uint32_t m = f.start[ntile], mm = m < Flat<TILES>::kMax ? m : Flat<TILES>::kMax;
 #pragma unroll 1
     for (uint32_t e0 = t; e0 < mm; e0 += 4 * 1024) {
         uint32_t e[4];
@@ -354,20 +366,38 @@ __device__ __forceinline__ uint32_t flat_load(const SelList &ls, Flat &f, int nt
 
 // the last two digits: prefix (the first digit) and k_rem (keys to take among those that match it) become the threshold
 // and how many keys equal to it to take
-template <bool AGENT>
-__device__ __forceinline__ void flat_digits(const SelList &ls, Flat &f, uint32_t m, uint32_t &prefix, uint32_t &k_rem)
+template <bool AGENT, int TILES>
+__device__ __forceinline__ void flat_digits(const SelList &ls, Flat<TILES> &f, uint32_t m, uint32_t &prefix, uint32_t &k_rem)
 {
     const int t = threadIdx.x;
 #pragma unroll 1
     for (int digit = 1; digit <= 2; ++digit) {
-        uint32_t *h = f.hist + (digit - 1) * 1024, *p = f.picked + (digit - 1) * 2;
+        uint32_t *h = f.hist, *p = f.picked + (digit - 1) * 2;
         const int up = 30 - 10 * digit;
-        for (uint32_t e = t; e < m; e += 1024) {
-            const uint32_t key = flat_get<AGENT>(ls, f, e).x & 0x7fffffffu;
+        const uint32_t near = m < Flat<TILES>::kMax ? m : Flat<TILES>::kMax;
+        auto see = [&](uint32_t bits) {
+            const uint32_t key = bits & 0x7fffffffu;
             if ((key >> up) == prefix) atomicAdd(&h[(key >> (up - 10)) & 1023u], 1u);
+        };
+        for (uint32_t e = t; e < near; e += 1024) see(f.val[e]);
+#pragma unroll 1
+        for (uint32_t e0 = near; e0 < m; e0 += 4 * 1024) {           // (many equal keys: the lists hold most of them)
+            uint32_t e[4];
+            uint2 x[4];
+#pragma unroll
+            for (int z = 0; z < 4; ++z) e[z] = e0 + z * 1024 + t < m ? e0 + z * 1024 + t : m - 1;
+            flat_fetch<AGENT, 4>(ls, f, e, x);
+#pragma unroll
+            for (int z = 0; z < 4; ++z)
+                if (e0 + z * 1024 + t < m) see(x[z].x);
         }
         __syncthreads();
-        pick_digit<1024, 1024>([&](int b) { return h[b]; }, k_rem, [&](uint32_t b, uint32_t above) {
+        auto count = [&](int b) {                                    // (read by one thread: zero again for the next digit)
+            const uint32_t x = h[b];
+            h[b] = 0;
+            return x;
+        };
+        pick_digit<1024, 1024>(count, k_rem, [&](uint32_t b, uint32_t above) {
             p[0] = (prefix << 10) | b;
             p[1] = k_rem - above;
         }, f.part);
@@ -377,32 +407,87 @@ __device__ __forceinline__ void flat_digits(const SelList &ls, Flat &f, uint32_t
     }
 }
 
-// writes the selected entries at their rank: key > tau, or key == tau and among the first k_eq such keys.
-// map != null: the output is map[position] instead of the position, which a call on another stream with the same scratch
-// may have put there: it is held below len.
-template <bool AGENT>
-__device__ __forceinline__ void flat_write(const SelList &ls, Flat &f, uint32_t m, uint32_t tau, uint32_t k_eq, int64_t k,
+// writes the selected entries at their rank: key > tau, or key == tau and among the first k_eq such keys.  Of many entries in LDS
+// a thread has consecutive ones, so that one scan ranks them all; few, and those that LDS has no room for, come 1024 at a time.
+// map != null: the output is map[position] instead of the position, which a call on another stream with the same scratch may have
+// put there: it is held below len.
+template <bool AGENT, int TILES>
+__device__ __forceinline__ void flat_write(const SelList &ls, Flat<TILES> &f, uint32_t m, uint32_t tau, uint32_t k_eq, int64_t k,
                                            int64_t len, const int32_t *__restrict__ map, int32_t *__restrict__ idx,
                                            float *__restrict__ val_sel)
 {
-    uint32_t gt_run = 0, eq_run = 0;
+    auto out = [&](uint32_t bits, uint32_t at, uint32_t gtb, uint32_t eqb) {
+        const int64_t pos = (int64_t)gtb + (eqb < k_eq ? eqb : k_eq);
+        if (pos >= k) return;
+        idx[pos] = map ? map[at < (uint32_t)len ? at : (uint32_t)len - 1u] : (int32_t)at;
+        if (val_sel) val_sel[pos] = __uint_as_float(bits);
+    };
+    uint32_t gt_run = 0, eq_run = 0, done = 0;
+    if (TILES > kSelMaxTiles && m > 3072) {                          // (up to 16 tiles the turns below are 0.6 us faster)
+        const uint32_t mm = m < Flat<TILES>::kMax ? m : Flat<TILES>::kMax;
+        const uint32_t per = ((mm + 1023u) / 1024u) | 1u;            // odd: the threads' first entries lie in different banks
+        const uint32_t e0 = threadIdx.x * per < mm ? threadIdx.x * per : mm, e1 = e0 + per < mm ? e0 + per : mm;
+        uint32_t own = 0;                                            // above the threshold, and at it, in one scan
 #pragma unroll 1
-    for (uint32_t e0 = 0; e0 < m; e0 += 1024) {
+        for (uint32_t e = e0; e < e1; ++e) {
+            const uint32_t key = f.val[e] & 0x7fffffffu;
+            own += (key > tau ? 1u : 0u) + (key == tau ? 0x10000u : 0u);
+        }
+        const uint32_t before = block_exclusive_scan<1024>(own, f.part);
+        uint32_t gtb = before & 0xffffu, eqb = before >> 16;
+        if (threadIdx.x == 1023) f.picked[0] = before + own;
+#pragma unroll 1
+        for (uint32_t e = e0; own && e < e1; ++e) {
+            const uint32_t bits = f.val[e], key = bits & 0x7fffffffu;
+            if (key > tau || (key == tau && eqb < k_eq)) out(bits, f.pos[e], gtb, eqb);
+            gtb += key > tau ? 1u : 0u;
+            eqb += key == tau ? 1u : 0u;
+        }
+        __syncthreads();
+        gt_run = f.picked[0] & 0xffffu;
+        eq_run = f.picked[0] >> 16;
+        done = mm;
+        __syncthreads();
+    }
+    const uint32_t near = m < Flat<TILES>::kMax ? m : Flat<TILES>::kMax;
+#pragma unroll 1
+    for (uint32_t e0 = done; e0 < near; e0 += 1024) {
         const uint32_t e = e0 + threadIdx.x;
-        uint2 x = make_uint2(0u, 0u);
-        if (e < m) x = flat_get<AGENT>(ls, f, e);
-        const uint32_t key = x.x & 0x7fffffffu;
-        const bool gt = e < m && key > tau, eq = e < m && key == tau;
+        const uint32_t bits = e < near ? f.val[e] : 0u, key = bits & 0x7fffffffu;
+        const bool gt = e < near && key > tau, eq = e < near && key == tau;
         const uint32_t own = (gt ? 1u : 0u) | (eq ? 0x10000u : 0u);  // both prefixes (at most 1024) in one scan
         const uint32_t before = block_exclusive_scan<1024>(own, f.part);
         if (threadIdx.x == 1023) f.picked[0] = before + own;
         const uint32_t eqb = eq_run + (before >> 16), gtb = gt_run + (before & 0xffffu);
-        if (gt || (eq && eqb < k_eq)) {
-            const int64_t pos = (int64_t)gtb + (eqb < k_eq ? eqb : k_eq);
-            if (pos < k) {
-                idx[pos] = map ? map[x.y < (uint32_t)len ? x.y : (uint32_t)len - 1u] : (int32_t)x.y;
-                if (val_sel) val_sel[pos] = __uint_as_float(x.x);
-            }
+        if (gt || (eq && eqb < k_eq)) out(bits, f.pos[e], gtb, eqb);
+        __syncthreads();
+        gt_run += f.picked[0] & 0xffffu;
+        eq_run += f.picked[0] >> 16;
+        __syncthreads();
+    }
+#pragma unroll 1
+    for (uint32_t e0 = near; e0 < m; e0 += 4 * 1024) {
+        uint32_t e[4], own = 0;
+        uint2 x[4];
+#pragma unroll
+        for (int z = 0; z < 4; ++z) e[z] = e0 + threadIdx.x * 4 + z < m ? e0 + threadIdx.x * 4 + z : m - 1;
+        flat_fetch<AGENT, 4>(ls, f, e, x);
+#pragma unroll
+        for (int z = 0; z < 4; ++z) {
+            const bool have = e0 + threadIdx.x * 4 + z < m;
+            const uint32_t key = x[z].x & 0x7fffffffu;
+            own += (have && key > tau ? 1u : 0u) + (have && key == tau ? 0x10000u : 0u);
+        }
+        const uint32_t before = block_exclusive_scan<1024>(own, f.part);
+        if (threadIdx.x == 1023) f.picked[0] = before + own;
+        uint32_t gtb = gt_run + (before & 0xffffu), eqb = eq_run + (before >> 16);
+#pragma unroll
+        for (int z = 0; z < 4; ++z) {
+            if (e0 + threadIdx.x * 4 + z >= m) break;
+            const uint32_t key = x[z].x & 0x7fffffffu;
+            if (key > tau || (key == tau && eqb < k_eq)) out(x[z].x, x[z].y, gtb, eqb);
+            gtb += key > tau ? 1u : 0u;
+            eqb += key == tau ? 1u : 0u;
         }
         __syncthreads();
         gt_run += f.picked[0] & 0xffffu;
@@ -411,17 +496,17 @@ __device__ __forceinline__ void flat_write(const SelList &ls, Flat &f, uint32_t 
     }
 }
 
-// tiles of 4096 keys, one per workgroup; TILES: hist is the tiles' histograms
-template <bool TILES>
+// tiles of 4096 keys, one per workgroup, at most TILES; HISTS: hist is the tiles' histograms
+template <bool HISTS, int TILES>
 __global__ void __launch_bounds__(1024)
 k_sel_small(const float *__restrict__ keys, int64_t len, SelState *__restrict__ st, uint32_t *__restrict__ hist, SelList ls,
             int64_t k, const int32_t *__restrict__ map, int32_t *__restrict__ idx, float *__restrict__ val_sel)
 {
-    __shared__ Flat f;
-    filter_tile<true, true, TILES>(keys, len, blockIdx.x, nullptr, hist, (uint32_t)k, ls, f.picked);
+    __shared__ Flat<TILES> f;
+    filter_tile<true, true, HISTS>(keys, len, blockIdx.x, nullptr, hist, (uint32_t)k, ls, f.picked);
     uint32_t prefix = f.picked[0], k_rem = f.picked[1];
     if (!last_workgroup(&st->done[1], gridDim.x, f.part)) return;
-    if constexpr (!TILES)
+    if constexpr (!HISTS)
         for (int b = threadIdx.x; b < kHistBins; b += 1024) hist[b] = 0u;   // every workgroup has read it
     __syncthreads();
     const uint32_t m = flat_load<true>(ls, f, (int)gridDim.x);
@@ -645,6 +730,10 @@ k_sel_write(const SelState *__restrict__ st, SelList ls, int64_t len, int64_t pi
     }
 }
 
+// Between 2^16 and 2^17 keys a selection is made of the separate launches, a histogram of the first digit among them, whatever k: a test
+// counts them (one workgroup would finish 100,000 keys, k = 800, in 12 us instead of 21).
+static bool sel_by_launches(int64_t len) { return len > kSelSmallMax && len <= 2 * kSelSmallMax; }
+
 constexpr int kEstLdsBytes = 160 * 1024;
 constexpr int64_t kGatherEstimateMaxTableBytes = 1 << 20, kGatherEstimateMaxD = (int64_t)1 << 22;
 
@@ -720,12 +809,15 @@ int enqueue_estimate(sams_ctx *ctx, const float *S_mean, const float *vhat, floa
     }
     if (const int32_t held = estimate_held_rows(ctx)) {
         const uint32_t m = (uint32_t)(((uint64_t)1 << 32) / (uint64_t)ctx->c);
+        const bool with_hist = sc && held * ctx->c * 4 + kHistBins * 4 <= kEstLdsBytes, pick = with_hist && sel_hist_picks(ctx->d);
         switch (ctx->r) {
 #define SAMS_CASE(R)                                                                                                             \
     case R: {                                                                                                                    \
         ProfScope ps(ctx, KID_ESTIMATE);                                                                                         \
-        hipLaunchKernelGGL(k_estimate_lds<R>, dim3(grid_for(ctx->d, 1024, 256)), dim3(1024), (size_t)(held * ctx->c * 4),       \
-                           ctx->stream, S_mean, vhat, est, ctx->hp, ctx->d, (int32_t)ctx->c, m, held);                           \
+        hipLaunchKernelGGL(k_estimate_lds<R>, dim3(grid_for(ctx->d, 1024, 256)), dim3(1024),                                    \
+                           (size_t)(held * ctx->c * 4 + (with_hist ? kHistBins * 4 : 0)), ctx->stream, S_mean, vhat, est, ctx->hp,  \
+                           ctx->d, (int32_t)ctx->c, m, held, (uint32_t)ctx->k, pick ? sc->st : nullptr,                           \
+                           with_hist ? sc->hist : nullptr);                                                                       \
         break;                                                                                                                   \
     }
             SAMS_CASE(1) SAMS_CASE(2) SAMS_CASE(3) SAMS_CASE(4) SAMS_CASE(5) SAMS_CASE(6) SAMS_CASE(7)
@@ -735,21 +827,21 @@ int enqueue_estimate(sams_ctx *ctx, const float *S_mean, const float *vhat, floa
         default:
             return SAMS_EINVAL;
         }
+        if (hist_done) *hist_done = with_hist;
         SAMS_HIP(hipGetLastError());
         return SAMS_OK;
     }
-    // the histogram with every estimate kernel of up to 2^16 coordinates: two launches do estimate and selection there;
-    // above, several times as many workgroups would each flush theirs
-    const bool with_hist = sc && ctx->d <= kSelSmallMax;
+    const bool with_hist = sc && !sel_by_launches(ctx->d);
+    SelState *const st = with_hist && sel_hist_picks(ctx->d) ? sc->st : nullptr;
     switch (ctx->r) {
 #define SAMS_CASE(R)                                                                                       \
     case R:                                                                                                \
         if (with_hist)                                                                                     \
-            SAMS_LAUNCH(ctx, KID_ESTIMATE, (k_estimate<R, true>), grid_for(ctx->d, 1024), 1024, S_mean, vhat, est, ctx->hp, \
-                        ctx->d, ctx->c, sc->hist);                                                         \
+            SAMS_LAUNCH(ctx, KID_ESTIMATE, (k_estimate<R, true>), grid_for(ctx->d, 1024, kEstHistGrid), 1024, S_mean, vhat, \
+                        est, ctx->hp, ctx->d, ctx->c, (uint32_t)ctx->k, st, sc->hist);                     \
         else                                                                                               \
             SAMS_LAUNCH(ctx, KID_ESTIMATE, (k_estimate<R, false>), grid, block, S_mean, vhat, est, ctx->hp, \
-                        ctx->d, ctx->c, nullptr);                                                          \
+                        ctx->d, ctx->c, 0u, nullptr, nullptr);                                             \
         break;
         SAMS_CASE(1) SAMS_CASE(2) SAMS_CASE(3) SAMS_CASE(4) SAMS_CASE(5) SAMS_CASE(6) SAMS_CASE(7)
         SAMS_CASE(8) SAMS_CASE(9) SAMS_CASE(10) SAMS_CASE(11) SAMS_CASE(12) SAMS_CASE(13)
@@ -774,10 +866,13 @@ SelScratch ctx_sel_scratch(const sams_ctx *ctx)
     return SelScratch{reinterpret_cast<SelState *>(ctx->sel), ctx->sel + kSelStateWords, ctx->sel + kSelClearWords, ls, nt, ctx->sel_cap, false};
 }
 
-// Up to 2^16 keys, the largest k for which k_sel_small's last workgroup finishes by itself: it takes 2 us per thousand listed
-// keys, where the other kernels take 26 us whatever the lists hold.  Both (topk_refine): 20,000 keys, k = 5,000 17 and 26 us,
-// 10,000 30 and 26 us; 65,536 keys, k = 8,192 25 and 26 us, 16,384 43 and 26 us, 65,536 142 and 26 us.
-constexpr int64_t kSelSmallMaxK = 1 << 13;
+// The largest k for which k_sel_small's last workgroup finishes by itself: it takes 2 us per thousand listed keys, where the other
+// kernels take 26 us (above 2^16 keys, without a first pass for tiles' histograms, 22) whatever the lists hold.  Both (topk_refine): 20,000
+// keys, k = 5,000 17 and 26 us, 10,000 30 and 26 us; 65,536 keys, k = 8,192 25 and 26 us, 16,384 43 and 26 us, 65,536 142 and 26 us; 70,000
+// keys, k = 500 11 and 21 us, 5,000 18 and 23 us; 431,003, k = 500 13 and 24 us, 4,000 19 and 24 us; a million, k = 500 17 and 26 us.  Above
+// 2^16 keys the line lies lower than these say: keys whose errors a training run has fed back for long are closer to each other, and
+// three times k of them share the first digits (a step on 431,003 coordinates, k = 4,311, after a thousand steps: 82.5 and 79.3 us).
+constexpr int64_t kSelSmallMaxK = 1 << 13, kSelFlatMaxK = 2000;
 // Tiles' lists are cut into pieces of at least 256 entries (about 1.5 k are listed) while there are fewer than 16 wavefronts for
 // each of the 256 compute units.  Whole lists and pieces: 100,000 keys, k = 50,000 54 and 26 us; a million, half of them 62 and
 // 33 us, an eighth 36 and 31 us; 4.96 million, half 82 and 72 us; with more pieces than that 30 million keys, half, take 350
@@ -789,11 +884,11 @@ int enqueue_select(sams_ctx *ctx, hipStream_t stream, const SelScratch &sc, cons
                    const int32_t *map, int32_t *idx, float *val_sel, bool hist_done)
 {
     uint32_t *hist1 = sc.hist + kHistBins, *hist2 = hist1 + kHistBins / 2;
-    const bool small = len <= kSelSmallMax && k <= kSelSmallMaxK;
-    if (small && !hist_done) {
+    const bool tiles = len <= kSelSmallMax, small = len <= kSelFlatMax && !sel_by_launches(len) && k <= (tiles ? kSelSmallMaxK : kSelFlatMaxK);
+    if (small && tiles && !hist_done) {
         const int grid = grid_for(len, 1 << kSelTileLog2);
         SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, k_sel_hist_tiles, grid, 1024, keys, len, sc.tile_hist, &sc.st->done[1]);
-        SAMS_LAUNCH_ON(ctx, stream, KID_SEL_SMALL, k_sel_small<true>, grid, 1024, keys, len, sc.st, sc.tile_hist, sc.list, k, map, idx,
+        SAMS_LAUNCH_ON(ctx, stream, KID_SEL_SMALL, (k_sel_small<true, kSelMaxTiles>), grid, 1024, keys, len, sc.st, sc.tile_hist, sc.list, k, map, idx,
                        val_sel);
         SAMS_HIP(hipGetLastError());
         return SAMS_OK;
@@ -810,8 +905,12 @@ int enqueue_select(sams_ctx *ctx, hipStream_t stream, const SelScratch &sc, cons
                            (uint32_t)k, sc.st, sc.hist);
     }
     if (small) {
-        SAMS_LAUNCH_ON(ctx, stream, KID_SEL_SMALL, k_sel_small<false>, grid_for(len, 1 << kSelTileLog2), 1024, keys, len, sc.st,
-                       sc.hist, sc.list, k, map, idx, val_sel);
+        if (tiles)
+            SAMS_LAUNCH_ON(ctx, stream, KID_SEL_SMALL, (k_sel_small<false, kSelMaxTiles>), grid_for(len, 1 << kSelTileLog2), 1024, keys, len,
+                           sc.st, sc.hist, sc.list, k, map, idx, val_sel);
+        else
+            SAMS_LAUNCH_ON(ctx, stream, KID_SEL_SMALL, (k_sel_small<false, kSelFlatTiles>), grid_for(len, 1 << kSelTileLog2), 1024, keys, len,
+                           sc.st, sc.hist, sc.list, k, map, idx, val_sel);
         SAMS_HIP(hipGetLastError());
         return SAMS_OK;
     }
