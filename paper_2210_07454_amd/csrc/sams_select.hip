@@ -150,7 +150,7 @@ k_est_median(const float *__restrict__ rowest, const float *__restrict__ vhat, f
 // the selected ones and the candidates, about 1.5 k of them unless many keys are equal -- in coordinate order, every
 // tile of keys in a region of its own.  Everything after that works on the listed keys only (on all keys, without the filter,
 // where a context of more than 2^20 coordinates found no room for lists).
-//   up to 2^20 keys and small k (kSelSmallMaxK, kSelFlatMaxK; but see sel_by_launches): k_sel_small filters, and its last
+//   up to 2^20 keys and small k (kSelSmallMaxK, kSelFlatMaxK, kSelFlatShortMaxK; but see sel_by_launches): k_sel_small filters, and its last
 //   workgroup finishes the selection
 //   else: k_sel_filter, two histograms of the listed keys, k_sel_count, k_sel_write
 // Up to 2^20 keys every filter workgroup picks the first digit from the histogram for itself (8 KiB, in every L2); above,
@@ -307,11 +307,12 @@ __device__ __forceinline__ void filter_tile(const float *__restrict__ keys, int6
 }
 
 // The listed keys of at most TILES tiles as one sequence in coordinate order, for one workgroup of 1024 threads: entry e is
-// number e - start[tile] of its tile's list; the first kMax entries are copied to LDS (64 KB in all, so that two workgroups share a
-// compute unit).
+// number e - start[tile] of its tile's list; the first kMax entries are copied to LDS.  Up to 16 tiles that is 64 KB in all; more
+// tiles (at most a workgroup per compute unit) list more keys for the same k, and the entries beyond kMax are fetched for every digit
+// again: with 7,168 and with 15,360 entries a step on 200,000 coordinates, k = 1,500 after 600 steps 54.3 and 52.0 us.
 template <int TILES>
 struct Flat {
-    static constexpr uint32_t kMax = 7168;
+    static constexpr uint32_t kMax = TILES > kSelMaxTiles ? 15360 : 7168;
     uint32_t start[2 * TILES];
     uint32_t val[kMax], pos[kMax];
     uint32_t part[16], picked[4], hist[1024];
@@ -868,11 +869,12 @@ SelScratch ctx_sel_scratch(const sams_ctx *ctx)
 
 // The largest k for which k_sel_small's last workgroup finishes by itself: it takes 2 us per thousand listed keys, where the other
 // kernels take 26 us (above 2^16 keys, without a first pass for tiles' histograms, 22) whatever the lists hold.  Both (topk_refine): 20,000
-// keys, k = 5,000 17 and 26 us, 10,000 30 and 26 us; 65,536 keys, k = 8,192 25 and 26 us, 16,384 43 and 26 us, 65,536 142 and 26 us; 70,000
-// keys, k = 500 11 and 21 us, 5,000 18 and 23 us; 431,003, k = 500 13 and 24 us, 4,000 19 and 24 us; a million, k = 500 17 and 26 us.  Above
-// 2^16 keys the line lies lower than these say: keys whose errors a training run has fed back for long are closer to each other, and
-// three times k of them share the first digits (a step on 431,003 coordinates, k = 4,311, after a thousand steps: 82.5 and 79.3 us).
-constexpr int64_t kSelSmallMaxK = 1 << 13, kSelFlatMaxK = 2000;
+// keys, k = 5,000 17 and 26 us, 10,000 30 and 26 us; 65,536 keys, k = 8,192 25 and 26 us, 16,384 43 and 26 us, 65,536 142 and 26 us; 431,003,
+// k = 500 16 and 30 us, 2,500 18 and 30 us, 4,311 22 and 30 us; a million, k = 3,000 23 and 32 us.  Above 2^16 keys the line lies lower
+// than these say: keys whose errors a training run has fed back for long are closer to each other, and three times k of them share
+// the first digits (whole steps after 600 to 1,000: 200,000 coordinates, k = 2,500 53 and 63 us; 300,000, 3,000 68.7 and 71; 431,003,
+// 3,000 76.3 and 78.3, 4,311 83.1 and 80.4; 800,000, 2,500 114 and 117; a million, 2,000 136 and 141, 3,000 141 and 137).
+constexpr int64_t kSelSmallMaxK = 1 << 13, kSelFlatMaxK = 2500, kSelFlatShortMaxK = 3000, kSelFlatShort = (int64_t)1 << 19;
 // Tiles' lists are cut into pieces of at least 256 entries (about 1.5 k are listed) while there are fewer than 16 wavefronts for
 // each of the 256 compute units.  Whole lists and pieces: 100,000 keys, k = 50,000 54 and 26 us; a million, half of them 62 and
 // 33 us, an eighth 36 and 31 us; 4.96 million, half 82 and 72 us; with more pieces than that 30 million keys, half, take 350
@@ -884,7 +886,9 @@ int enqueue_select(sams_ctx *ctx, hipStream_t stream, const SelScratch &sc, cons
                    const int32_t *map, int32_t *idx, float *val_sel, bool hist_done)
 {
     uint32_t *hist1 = sc.hist + kHistBins, *hist2 = hist1 + kHistBins / 2;
-    const bool tiles = len <= kSelSmallMax, small = len <= kSelFlatMax && !sel_by_launches(len) && k <= (tiles ? kSelSmallMaxK : kSelFlatMaxK);
+    const bool tiles = len <= kSelSmallMax;
+    const int64_t small_k = tiles ? kSelSmallMaxK : len <= kSelFlatShort ? kSelFlatShortMaxK : kSelFlatMaxK;
+    const bool small = len <= kSelFlatMax && !sel_by_launches(len) && k <= small_k;
     if (small && tiles && !hist_done) {
         const int grid = grid_for(len, 1 << kSelTileLog2);
         SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, k_sel_hist_tiles, grid, 1024, keys, len, sc.tile_hist, &sc.st->done[1]);

@@ -1,4 +1,4 @@
-"""Selections that one workgroup finishes from up to 256 tiles' lists: around the entries its LDS holds (7,168) and writes in turns
+"""Selections that one workgroup finishes from up to 256 tiles' lists: around the entries its LDS holds (15,360; 7,168 up to 16 tiles) and writes in turns
 (3,072), with the lists full of equal keys, and first histograms taken by the kernels that make the estimates."""
 import numpy as np
 import pytest
@@ -12,7 +12,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("k_in,listed,k_out", [(131_073, 3_071, 2_000), (131_073, 3_073, 1_999), (140_000, 7_168, 2_000), (140_000, 7_169, 2_000),
                                                (131_072, 7_168, 2_000), (300_001, 11_265, 17), (300_001, 60_000, 2_000), (1 << 20, 1 << 20, 1),
-                                               ((1 << 20) - 4095, 7_167, 2_001), (40_000, 4_097, 4_000)])
+                                               ((1 << 20) - 4095, 7_167, 2_001), (40_000, 4_097, 4_000),
+                                               (200_000, 15_360, 3_000), (200_000, 15_361, 2_999), (1 << 19, 19_457, 3_000), ((1 << 19) + 1, 15_361, 2_500),
+                                               (1 << 20, 15_359, 2_500), (900_000, 40_000, 2_500)])
 @pytest.mark.parametrize("equal", [False, True], ids=["distinct", "equal"])
 def test_lists_around_what_lds_holds(k_in, listed, k_out, equal):
     """`listed` keys share the first digit of the threshold, all others lie below."""
