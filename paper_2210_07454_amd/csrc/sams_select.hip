@@ -164,7 +164,7 @@ k_est_median(const float *__restrict__ rowest, const float *__restrict__ vhat, f
 // keys (up to 2^16 keys three sweeps by one workgroup): k = 1 % of 65,536 keys 8 us (28), of 431,003 29 us with the
 // histogram (84), of 11.2 million 35 us (111), of 124 million 0.18 ms (0.41): what is left is the filter's pass over the keys and
 // launches of 5 us.  By topk_refine, with the histogram: 65,536 keys, half of them kept 26 us (44); 431,003, half 30 us (63);
-// 4.96 million, a quarter 61 us (134), half 72 us (137), all 87 us (126).
+// 4.96 million, a quarter 56 us (134), all 84 us (126).
 
 // The streaming passes of the selection read four consecutive keys per lane with one 16-byte load
 // (the entry points accept 16-byte aligned arrays only; the last, partial group of four is read key by key).  Absent keys
@@ -206,9 +206,17 @@ __device__ __forceinline__ void wave_prefix3(uint32_t cnt, uint64_t below, uint3
     *total = t;
 }
 
-// Histogram of the first digit over all keys, by a grid of at most kHistMaxGrid workgroups; PICK: the last one picks the
-// digit.
-constexpr int kHistMaxGrid = 512;
+// Histogram of the first digit over all keys; PICK: the last workgroup picks the digit.  A workgroup has at least four tiles of 4096 keys
+// where that leaves kHistMinGrid of them, and there are no more than compute units: what a workgroup costs is the adding of its
+// histogram to the whole one.  Selections (topk_refine) with up to 512 and so: a million keys 32.5 and 31.3 us, three million 40 and
+// 36.5, 4.96 million, a quarter 58.5 and 55.7, seven million, an eighth 58 and 55;
+// two loads of keys are under way per thread, for the long ones.
+constexpr int kHistMinGrid = 128, kHistMaxGrid = 256;
+static int hist_grid(int64_t len)
+{
+    const int by_four = grid_for(len, 4 << kSelTileLog2, kHistMaxGrid);
+    return by_four > kHistMinGrid ? by_four : grid_for(len, 1 << kSelTileLog2, kHistMinGrid);
+}
 template <bool PICK>
 __global__ void __launch_bounds__(1024)
 k_sel_hist(const float *__restrict__ keys, int64_t len, uint32_t k, SelState *__restrict__ st, uint32_t *__restrict__ hist)
@@ -217,11 +225,13 @@ k_sel_hist(const float *__restrict__ keys, int64_t len, uint32_t k, SelState *__
     for (int t = threadIdx.x; t < kHistBins; t += 1024) lh[t] = 0;
     __syncthreads();
     const int64_t stride = (int64_t)gridDim.x * 4096;
-    for (int64_t l = (blockIdx.x * (int64_t)1024 + threadIdx.x) * 4; l < len; l += stride) {
-        const Keys4 q = load_keys4(keys, l, len);
+    for (int64_t l = (blockIdx.x * (int64_t)1024 + threadIdx.x) * 4; l < len; l += 2 * stride) {
+        const Keys4 q[2] = {load_keys4(keys, l, len), load_keys4(keys, l + stride, len)};
 #pragma unroll
-        for (int z = 0; z < 4; ++z)
-            if ((q.have >> z) & 1u) atomicAdd(&lh[mag_key(q.v[z]) >> 20], 1u);
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int z = 0; z < 4; ++z)
+                if ((q[y].have >> z) & 1u) atomicAdd(&lh[mag_key(q[y].v[z]) >> 20], 1u);
     }
     __syncthreads();
     for (int t = threadIdx.x; t < kHistBins; t += 1024)
@@ -902,10 +912,10 @@ int enqueue_select(sams_ctx *ctx, hipStream_t stream, const SelScratch &sc, cons
     if (sc.shared) SAMS_TRY(enqueue_fill_u32_on(ctx, stream, reinterpret_cast<uint32_t *>(sc.st), kSelClearWords, 0u));
     if (!hist_done) {
         if (sel_hist_picks(len))
-            SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, k_sel_hist<true>, grid_for(len, 4096, kHistMaxGrid), 1024, keys, len,
+            SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, k_sel_hist<true>, hist_grid(len), 1024, keys, len,
                            (uint32_t)k, sc.st, sc.hist);
         else
-            SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, k_sel_hist<false>, grid_for(len, 4096, kHistMaxGrid), 1024, keys, len,
+            SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, k_sel_hist<false>, hist_grid(len), 1024, keys, len,
                            (uint32_t)k, sc.st, sc.hist);
     }
     if (small) {

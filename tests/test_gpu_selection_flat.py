@@ -53,3 +53,21 @@ def test_first_histogram_with_the_estimates(d, r, c, k):
             ctx.unsketch_topk(Sd, vd, idx, est)
             assert np.array_equal(idx.cpu().numpy(), ref)
             assert np.array_equal(est.cpu().numpy().view(np.uint32), e[ref].view(np.uint32))
+
+
+# the histogram pass: 128 workgroups of one, two and more turns of two tiles, then a workgroup per four tiles, 256 at most
+@pytest.mark.parametrize("k_in,k_out", [(131_073, 9_000), (524_287, 70_000), (524_293, 70_000), (1_048_577, 9_000), (2_097_149, 1_500_000),
+                                        (2_101_249, 300_001), (4_194_305, 100_000)])
+def test_histogram_pass(k_in, k_out):
+    from paper_2210_07454_amd import sams
+    rng = np.random.default_rng(k_in)
+    vals = (rng.standard_normal(k_in) / rng.random(k_in).clip(1e-6) ** 0.6).astype(np.float32)
+    vals[-1] = np.float32(3e38)                                      # the last key counts
+    cand = np.arange(k_in, dtype=np.int32)
+    idx, delta = Oracle("f32").refine(cand, vals, k_out)
+    io, do = torch.full((k_out,), -1, device="cuda", dtype=torch.int32), torch.full((k_out,), 7.0, device="cuda")
+    ci, vi = torch.from_numpy(cand).cuda(), torch.from_numpy(vals).cuda()
+    for _ in range(2):
+        sams.topk_refine_static(ci, vi, k_out, io, do)
+        assert np.array_equal(io.cpu().numpy(), idx)
+        assert np.array_equal(do.cpu().numpy().view(np.uint32), delta.view(np.uint32))
