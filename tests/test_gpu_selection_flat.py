@@ -71,3 +71,30 @@ def test_histogram_pass(k_in, k_out):
         sams.topk_refine_static(ci, vi, k_out, io, do)
         assert np.array_equal(io.cpu().numpy(), idx)
         assert np.array_equal(do.cpu().numpy().view(np.uint32), delta.view(np.uint32))
+
+
+# zeros of both signs and values below the first digit's range; fewer, as many and more keys that differ from zero than are kept
+@pytest.mark.parametrize("k_in,k_out", [(5_000, 1_000), (60_000, 8_192), (65_536, 7_500), (140_000, 2_999), (431_003, 3_000), (1 << 20, 2_500)])
+@pytest.mark.parametrize("nonzero", [0, 1, -1, -2, 0.5, 1.5, "front", "back"])
+def test_mostly_zeros(k_in, k_out, nonzero):
+    from paper_2210_07454_amd import sams
+    rng = np.random.default_rng(k_in)
+    vals = np.where(rng.random(k_in) < 0.5, np.float32(0.0), np.float32(-0.0)).astype(np.float32)
+    if nonzero == "front":
+        at = np.arange(k_out // 2)
+    elif nonzero == "back":
+        at = np.arange(k_in - k_out // 2, k_in)
+    else:
+        m = int(nonzero * k_out) if isinstance(nonzero, float) else (nonzero if nonzero >= 0 else k_out + 1 + nonzero)   # -1: k_out, -2: one fewer
+        at = rng.permutation(k_in)[:m]
+    vals[at] = rng.standard_normal(len(at)).astype(np.float32)
+    vals[at[::3]] = np.float32(1e-41)                                # subnormal: differs from zero, shares its first digit
+    vals[at[::5]] = np.float32(-3e-45)
+    cand = np.cumsum(rng.integers(1, 9, k_in)).astype(np.int32)
+    idx, delta = Oracle("f32").refine(cand, vals, k_out)
+    io, do = torch.full((k_out,), -1, device="cuda", dtype=torch.int32), torch.full((k_out,), 7.0, device="cuda")
+    ci, vi = torch.from_numpy(cand).cuda(), torch.from_numpy(vals).cuda()
+    for _ in range(2):
+        sams.topk_refine_static(ci, vi, k_out, io, do)
+        assert np.array_equal(io.cpu().numpy(), idx)
+        assert np.array_equal(do.cpu().numpy().view(np.uint32), delta.view(np.uint32))
