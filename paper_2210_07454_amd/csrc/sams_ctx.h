@@ -303,7 +303,7 @@ __device__ __forceinline__ bool last_workgroup(uint32_t *done, uint32_t nblk, ui
 }
 
 // The digit in which the k_rem-th largest key lies, from the histogram count(bin) of NB bins: exactly one thread calls
-// sink(digit, number of keys in higher bins), since k_rem <= the number of keys.  Thread t looks at NB / THREADS
+// sink(digit, number of keys in higher bins, in this one), since k_rem <= the number of keys.  Thread t looks at NB / THREADS
 // consecutive bins counted from the top.
 template <int THREADS, int NB, typename C, typename S>
 __device__ __forceinline__ void pick_digit(C count, uint32_t k_rem, S sink, uint32_t *part)
@@ -318,7 +318,7 @@ __device__ __forceinline__ void pick_digit(C count, uint32_t k_rem, S sink, uint
     uint32_t above = block_exclusive_scan<THREADS>(sum, part);
 #pragma unroll
     for (int z = 0; z < PER; ++z) {
-        if (above < k_rem && k_rem <= above + v[z]) sink((uint32_t)(top - z), above);
+        if (above < k_rem && k_rem <= above + v[z]) sink((uint32_t)(top - z), above, v[z]);
         above += v[z];
     }
 }
@@ -337,7 +337,7 @@ __device__ __forceinline__ void sel_pick(SelState *st, uint32_t *hist, int digit
         return x;
     };
     const int width = digit == 0 ? 11 : 10;
-    auto sink = [&](uint32_t b, uint32_t above) {
+    auto sink = [&](uint32_t b, uint32_t above, uint32_t) {
         const uint32_t prefix = (prefix_in << width) | b;
         st->prefix[digit] = picked[0] = prefix;
         st->k_rem[digit] = picked[1] = k_rem - above;

@@ -259,16 +259,32 @@ k_sel_hist_tiles(const float *__restrict__ keys, int64_t len, uint32_t *__restri
     tile_hist[blockIdx.x * (kHistBins / 2) + t] = lh[2 * t] | (lh[2 * t + 1] << 16);
 }
 
+// One more in h[bin] (LDS) for every lane with `in`.  Lanes that have the first one's bin are added up in registers: keys that are all
+// alike would queue up for one word.
+__device__ __forceinline__ void count_alike(uint32_t *h, bool in, uint32_t bin)
+{
+    const uint64_t all = __ballot(in);
+    if (!all) return;                                                // uniform
+    const int first = __ffsll((unsigned long long)all) - 1;
+    const uint32_t bin0 = (uint32_t)__builtin_amdgcn_readlane((int)bin, first);
+    const uint32_t same = (uint32_t)__popcll(__ballot(in && bin == bin0));
+    const bool leads = (int)(threadIdx.x & (kWave - 1)) == first;
+    if (leads || (in && bin != bin0)) atomicAdd(&h[bin], leads ? same : 1u);   // (one instruction: bin is the lane's)
+}
+
 // A tile of keys per workgroup: lists the keys whose first digit is at or above the k-th largest key's, in
 // coordinate order, at val / loc [tile * tile size], their number at cnt[tile].
 // PICK: the workgroup picks that digit from hist0 (the prefix and the number of keys to take among those that match it
 // are left in picked[2], LDS); otherwise it is *prefix_in.  AGENT: the list is read again in this launch, and zeros are not listed
 // (see flat_zeros).
 // TILES: hist0 is the tiles' histograms.
+// Where all tiles together list more than `crowd` keys, every tile adds the second digit of its keys that match the first to
+// hist1 (lh: 1024 bins in LDS) and leaves the smallest and the largest magnitude that it lists at ls.group[tile].
 template <bool PICK, bool AGENT, bool TILES = false>
 __device__ __forceinline__ void filter_tile(const float *__restrict__ keys, int64_t len, int64_t tile,
                                             const uint32_t *__restrict__ prefix_in, const uint32_t *__restrict__ hist0, uint32_t k,
-                                            const SelList &ls, uint32_t *picked)
+                                            const SelList &ls, uint32_t *picked, uint32_t crowd = 0,
+                                            uint32_t *__restrict__ hist1 = nullptr, uint32_t *lh = nullptr)
 {
     __shared__ uint32_t part[16], wsum[16];
     const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
@@ -289,9 +305,10 @@ __device__ __forceinline__ void filter_tile(const float *__restrict__ keys, int6
                     pair[1] += x[w] >> 16;
                 }
         }
-        pick_digit<1024, kHistBins>([&](int b) { return TILES ? pair[b & 1] : hist0[b]; }, k, [&](uint32_t b, uint32_t above) {
+        pick_digit<1024, kHistBins>([&](int b) { return TILES ? pair[b & 1] : hist0[b]; }, k, [&](uint32_t b, uint32_t above, uint32_t in) {
             picked[0] = b;
             picked[1] = k - above;
+            if (AGENT) picked[2] = above + in;                       // keys listed in all, and the zeros
         }, part);
         __syncthreads();
         prefix = picked[0];
@@ -315,17 +332,49 @@ __device__ __forceinline__ void filter_tile(const float *__restrict__ keys, int6
             ++pos;
         }
     if (t == 15) put<AGENT>(ls.cnt + tile, upto);
+    if (!hist1 || picked[2] <= crowd) return;                        // uniform over the workgroup
+    __shared__ uint32_t least[16], most[16];
+    uint32_t lo = UINT32_MAX, hi = 0;
+    lh[t] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int z = 0; z < 4; ++z) {
+        const uint32_t key = mag_key(q.v[z]);
+        const bool in = (keep >> z) & 1u;
+        count_alike(lh, in && (key >> 20) == prefix, (key >> 10) & 1023u);
+        lo = in && key < lo ? key : lo;
+        hi = in && key > hi ? key : hi;
+    }
+    for (int off = kWave / 2; off; off >>= 1) {
+        const uint32_t l = __shfl_xor(lo, off), h = __shfl_xor(hi, off);
+        lo = l < lo ? l : lo;
+        hi = h > hi ? h : hi;
+    }
+    if (lane == 0) {
+        least[wave] = lo;
+        most[wave] = hi;
+    }
+    __syncthreads();
+    if (lh[t]) atomicAdd(&hist1[t], lh[t]);
+    if (t == 0) {
+        for (int w = 1; w < 16; ++w) {
+            lo = least[w] < lo ? least[w] : lo;
+            hi = most[w] > hi ? most[w] : hi;
+        }
+        put<AGENT>(&ls.group[tile].x, lo);
+        put<AGENT>(&ls.group[tile].y, hi);
+    }
 }
 
 // The listed keys of at most TILES tiles as one sequence in coordinate order, for one workgroup of 1024 threads: entry e is
-// number e - start[tile] of its tile's list; the first kMax entries are copied to LDS.  Up to 16 tiles that is 64 KB in all; more
-// tiles (at most a workgroup per compute unit) list more keys for the same k, and the entries beyond kMax are fetched for every digit
-// again: with 7,168 and with 15,360 entries a step on 200,000 coordinates, k = 1,500 after 600 steps 54.3 and 52.0 us.
+// number e - start[tile] of its tile's list.  Up to kMax entries are copied to LDS, more than that stay in their lists (see
+// flat_crowded).  Up to 16 tiles that is 64 KB in all; more tiles (at most a workgroup per compute unit) list more keys for the same
+// k: with 7,168 and with 15,360 entries a step on 200,000 coordinates, k = 1,500 after 600 steps 54.3 and 52.0 us.
 template <int TILES>
 struct Flat {
-    static constexpr uint32_t kMax = TILES > kSelMaxTiles ? 15360 : 7168;
+    static constexpr uint32_t kMax = 15360;
     uint32_t start[2 * TILES];
-    uint32_t val[kMax], pos[kMax];
+    alignas(16) uint32_t val[kMax], pos[kMax];
     uint32_t part[16], picked[4], hist[1024];
 };
 
@@ -348,23 +397,28 @@ __device__ __forceinline__ void flat_fetch(const SelList &ls, const Flat<TILES> 
         x[z] = make_uint2(get<AGENT>(ls.val + at), base + get<AGENT>(ls.loc + at));
     }
 }
+
 // the number of entries; complete for all threads
 template <bool AGENT, int TILES>
-__device__ __forceinline__ uint32_t flat_load(const SelList &ls, Flat<TILES> &f, int ntile)
+__device__ __forceinline__ uint32_t flat_load(const SelList &ls, Flat<TILES> &f, int ntile, uint32_t len)
 {
     static_assert(2 * TILES <= 1024, "a thread per start");
     const int t = threadIdx.x;
-    const uint32_t before = block_exclusive_scan<1024>(t < ntile ? get<AGENT>(ls.cnt + t) : 0u, f.part);
+    // (a call on another stream with the same scratch may have put any count there: no list is longer than its tile)
+    const uint32_t rest = t < ntile ? len - ((uint32_t)t << kSelTileLog2) : 0u, tile = rest < 1u << kSelTileLog2 ? rest : 1u << kSelTileLog2;
+    const uint32_t cnt = t < ntile ? get<AGENT>(ls.cnt + t) : 0u;
+    const uint32_t before = block_exclusive_scan<1024>(cnt < tile ? cnt : tile, f.part);
     if (t < 2 * TILES) f.start[t] = before;                          // from ntile on: the number of entries
     f.hist[t] = 0;
     __syncthreads();
-    const uint32_t m = f.start[ntile], mm = m < Flat<TILES>::kMax ? m : Flat<TILES>::kMax;
+    const uint32_t m = f.start[ntile];
+    if (m > Flat<TILES>::kMax) return m;
 #pragma unroll 1
-    for (uint32_t e0 = t; e0 < mm; e0 += 4 * 1024) {
+    for (uint32_t e0 = t; e0 < m; e0 += 4 * 1024) {
         uint32_t e[4];
         uint2 x[4];
 #pragma unroll
-        for (int z = 0; z < 4; ++z) e[z] = e0 + z * 1024 < mm ? e0 + z * 1024 : mm - 1;
+        for (int z = 0; z < 4; ++z) e[z] = e0 + z * 1024 < m ? e0 + z * 1024 : m - 1;
         flat_fetch<AGENT, 4>(ls, f, e, x);
 #pragma unroll
         for (int z = 0; z < 4; ++z) {                                // (the last entry may be stored twice, alike)
@@ -376,69 +430,69 @@ __device__ __forceinline__ uint32_t flat_load(const SelList &ls, Flat<TILES> &f,
     return m;
 }
 
-// the last two digits: prefix (the first digit) and k_rem (keys to take among those that match it) become the threshold
-// and how many keys equal to it to take
-template <bool AGENT, int TILES>
-__device__ __forceinline__ void flat_digits(const SelList &ls, Flat<TILES> &f, uint32_t m, uint32_t &prefix, uint32_t &k_rem)
+// one digit of 10 bits from f.hist, which is zero again for the next one: prefix and k_rem (keys to take among those that match it)
+// go one digit on.  p: two words of LDS that no other digit has.  The histogram is complete (a barrier before)
+template <int TILES>
+__device__ __forceinline__ void flat_pick(Flat<TILES> &f, uint32_t *p, uint32_t &prefix, uint32_t &k_rem)
 {
-    const int t = threadIdx.x;
+    auto count = [&](int b) {                                        // (read by one thread)
+        const uint32_t x = f.hist[b];
+        f.hist[b] = 0;
+        return x;
+    };
+    pick_digit<1024, 1024>(count, k_rem, [&](uint32_t b, uint32_t above, uint32_t) {
+        p[0] = (prefix << 10) | b;
+        p[1] = k_rem - above;
+    }, f.part);
+    __syncthreads();
+    prefix = p[0];
+    k_rem = p[1];
+}
+
+// the last two digits of m entries in LDS: prefix (the first digit) and k_rem become the threshold and how many keys equal to it to take
+template <int TILES>
+__device__ __forceinline__ void flat_digits(Flat<TILES> &f, uint32_t m, uint32_t &prefix, uint32_t &k_rem)
+{
 #pragma unroll 1
     for (int digit = 1; digit <= 2; ++digit) {
-        uint32_t *h = f.hist, *p = f.picked + (digit - 1) * 2;
         const int up = 30 - 10 * digit;
-        const uint32_t near = m < Flat<TILES>::kMax ? m : Flat<TILES>::kMax;
-        auto see = [&](uint32_t bits) {
-            const uint32_t key = bits & 0x7fffffffu;
-            if ((key >> up) == prefix) atomicAdd(&h[(key >> (up - 10)) & 1023u], 1u);
-        };
-        for (uint32_t e = t; e < near; e += 1024) see(f.val[e]);
-#pragma unroll 1
-        for (uint32_t e0 = near; e0 < m; e0 += 4 * 1024) {           // (many equal keys: the lists hold most of them)
-            uint32_t e[4];
-            uint2 x[4];
-#pragma unroll
-            for (int z = 0; z < 4; ++z) e[z] = e0 + z * 1024 + t < m ? e0 + z * 1024 + t : m - 1;
-            flat_fetch<AGENT, 4>(ls, f, e, x);
-#pragma unroll
-            for (int z = 0; z < 4; ++z)
-                if (e0 + z * 1024 + t < m) see(x[z].x);
+        for (uint32_t e = threadIdx.x; e < m; e += 1024) {
+            const uint32_t key = f.val[e] & 0x7fffffffu;
+            if ((key >> up) == prefix) atomicAdd(&f.hist[(key >> (up - 10)) & 1023u], 1u);
         }
         __syncthreads();
-        auto count = [&](int b) {                                    // (read by one thread: zero again for the next digit)
-            const uint32_t x = h[b];
-            h[b] = 0;
-            return x;
-        };
-        pick_digit<1024, 1024>(count, k_rem, [&](uint32_t b, uint32_t above) {
-            p[0] = (prefix << 10) | b;
-            p[1] = k_rem - above;
-        }, f.part);
-        __syncthreads();
-        prefix = p[0];
-        k_rem = p[1];
+        flat_pick(f, f.picked + (digit - 1) * 2, prefix, k_rem);
     }
 }
 
-// writes the selected entries at their rank: key > tau, or key == tau and among the first k_eq such keys.  Of many entries in LDS
-// a thread has consecutive ones, so that one scan ranks them all; few, and those that LDS has no room for, come 1024 at a time.
+// where the selected entries go: an entry's rank follows from the keys above the threshold and at it before it.
 // map != null: the output is map[position] instead of the position, which a call on another stream with the same scratch may have
 // put there: it is held below len.
-template <bool AGENT, int TILES>
-__device__ __forceinline__ void flat_write(const SelList &ls, Flat<TILES> &f, uint32_t m, uint32_t tau, uint32_t k_eq, int64_t k,
-                                           int64_t len, const int32_t *__restrict__ map, int32_t *__restrict__ idx,
-                                           float *__restrict__ val_sel)
-{
-    auto out = [&](uint32_t bits, uint32_t at, uint32_t gtb, uint32_t eqb) {
+struct SelOut {
+    const int32_t *__restrict__ map;
+    int32_t *__restrict__ idx;
+    float *__restrict__ val_sel;
+    int64_t k, len;
+    uint32_t k_eq;   // how many keys equal to the threshold are taken
+    __device__ __forceinline__ uint32_t source(uint32_t at) const { return (uint32_t)map[at < (uint32_t)len ? at : (uint32_t)len - 1u]; }
+    __device__ __forceinline__ void put(uint32_t bits, uint32_t at, uint32_t gtb, uint32_t eqb) const
+    {
         const int64_t pos = (int64_t)gtb + (eqb < k_eq ? eqb : k_eq);
         if (pos >= k) return;
-        idx[pos] = map ? map[at < (uint32_t)len ? at : (uint32_t)len - 1u] : (int32_t)at;
+        idx[pos] = (int32_t)(map ? source(at) : at);
         if (val_sel) val_sel[pos] = __uint_as_float(bits);
-    };
-    uint32_t gt_run = 0, eq_run = 0, done = 0;
+    }
+};
+
+// writes the selected ones of m entries in LDS at their rank: key > tau, or key == tau and among the first k_eq such keys.  Of many
+// entries a thread has consecutive ones, so that one scan ranks them all; few come 1024 at a time.
+template <int TILES>
+__device__ __forceinline__ void flat_write(Flat<TILES> &f, uint32_t m, uint32_t tau, const SelOut &out)
+{
+    const uint32_t k_eq = out.k_eq;
     if (TILES > kSelMaxTiles && m > 3072) {                          // (up to 16 tiles the turns below are 0.6 us faster)
-        const uint32_t mm = m < Flat<TILES>::kMax ? m : Flat<TILES>::kMax;
-        const uint32_t per = ((mm + 1023u) / 1024u) | 1u;            // odd: the threads' first entries lie in different banks
-        const uint32_t e0 = threadIdx.x * per < mm ? threadIdx.x * per : mm, e1 = e0 + per < mm ? e0 + per : mm;
+        const uint32_t per = ((m + 1023u) / 1024u) | 1u;             // odd: the threads' first entries lie in different banks
+        const uint32_t e0 = threadIdx.x * per < m ? threadIdx.x * per : m, e1 = e0 + per < m ? e0 + per : m;
         uint32_t own = 0;                                            // above the threshold, and at it, in one scan
 #pragma unroll 1
         for (uint32_t e = e0; e < e1; ++e) {
@@ -447,60 +501,26 @@ __device__ __forceinline__ void flat_write(const SelList &ls, Flat<TILES> &f, ui
         }
         const uint32_t before = block_exclusive_scan<1024>(own, f.part);
         uint32_t gtb = before & 0xffffu, eqb = before >> 16;
-        if (threadIdx.x == 1023) f.picked[0] = before + own;
 #pragma unroll 1
         for (uint32_t e = e0; own && e < e1; ++e) {
             const uint32_t bits = f.val[e], key = bits & 0x7fffffffu;
-            if (key > tau || (key == tau && eqb < k_eq)) out(bits, f.pos[e], gtb, eqb);
+            if (key > tau || (key == tau && eqb < k_eq)) out.put(bits, f.pos[e], gtb, eqb);
             gtb += key > tau ? 1u : 0u;
             eqb += key == tau ? 1u : 0u;
         }
-        __syncthreads();
-        gt_run = f.picked[0] & 0xffffu;
-        eq_run = f.picked[0] >> 16;
-        done = mm;
-        __syncthreads();
+        return;
     }
-    const uint32_t near = m < Flat<TILES>::kMax ? m : Flat<TILES>::kMax;
+    uint32_t gt_run = 0, eq_run = 0;
 #pragma unroll 1
-    for (uint32_t e0 = done; e0 < near; e0 += 1024) {
+    for (uint32_t e0 = 0; e0 < m; e0 += 1024) {
         const uint32_t e = e0 + threadIdx.x;
-        const uint32_t bits = e < near ? f.val[e] : 0u, key = bits & 0x7fffffffu;
-        const bool gt = e < near && key > tau, eq = e < near && key == tau;
+        const uint32_t bits = e < m ? f.val[e] : 0u, key = bits & 0x7fffffffu;
+        const bool gt = e < m && key > tau, eq = e < m && key == tau;
         const uint32_t own = (gt ? 1u : 0u) | (eq ? 0x10000u : 0u);  // both prefixes (at most 1024) in one scan
         const uint32_t before = block_exclusive_scan<1024>(own, f.part);
         if (threadIdx.x == 1023) f.picked[0] = before + own;
         const uint32_t eqb = eq_run + (before >> 16), gtb = gt_run + (before & 0xffffu);
-        if (gt || (eq && eqb < k_eq)) out(bits, f.pos[e], gtb, eqb);
-        __syncthreads();
-        gt_run += f.picked[0] & 0xffffu;
-        eq_run += f.picked[0] >> 16;
-        __syncthreads();
-    }
-#pragma unroll 1
-    for (uint32_t e0 = near; e0 < m; e0 += 4 * 1024) {
-        uint32_t e[4], own = 0;
-        uint2 x[4];
-#pragma unroll
-        for (int z = 0; z < 4; ++z) e[z] = e0 + threadIdx.x * 4 + z < m ? e0 + threadIdx.x * 4 + z : m - 1;
-        flat_fetch<AGENT, 4>(ls, f, e, x);
-#pragma unroll
-        for (int z = 0; z < 4; ++z) {
-            const bool have = e0 + threadIdx.x * 4 + z < m;
-            const uint32_t key = x[z].x & 0x7fffffffu;
-            own += (have && key > tau ? 1u : 0u) + (have && key == tau ? 0x10000u : 0u);
-        }
-        const uint32_t before = block_exclusive_scan<1024>(own, f.part);
-        if (threadIdx.x == 1023) f.picked[0] = before + own;
-        uint32_t gtb = gt_run + (before & 0xffffu), eqb = eq_run + (before >> 16);
-#pragma unroll
-        for (int z = 0; z < 4; ++z) {
-            if (e0 + threadIdx.x * 4 + z >= m) break;
-            const uint32_t key = x[z].x & 0x7fffffffu;
-            if (key > tau || (key == tau && eqb < k_eq)) out(x[z].x, x[z].y, gtb, eqb);
-            gtb += key > tau ? 1u : 0u;
-            eqb += key == tau ? 1u : 0u;
-        }
+        if (gt || (eq && eqb < k_eq)) out.put(bits, f.pos[e], gtb, eqb);
         __syncthreads();
         gt_run += f.picked[0] & 0xffffu;
         eq_run += f.picked[0] >> 16;
@@ -508,11 +528,204 @@ __device__ __forceinline__ void flat_write(const SelList &ls, Flat<TILES> &f, ui
     }
 }
 
+// One wavefront walks nt lists in order, list q of length(q) entries from val[q 2^12] on: f(at, n, w) for every group of at most
+// 256 entries, val[at ... at + n), four consecutive ones per lane in w.  Four groups are under way, of one list or of several.  val is
+// 16-byte aligned, and has room for three words behind each list's last entry.  f is in the code four times, so what it does with
+// entries that matter is a loop over the four of a lane.
+template <int UNDER, typename L, typename F>
+__device__ __forceinline__ void each_group(const uint32_t *val, L length, int nt, F f)
+{
+    constexpr int kGroup = 4 * kWave;
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    int q = 0;
+    uint32_t e0 = 0, cnt = nt > 0 ? length(0) : 0u;
+    auto settle = [&] {                                              // to the next list with an entry; q == nt: no more
+        while (e0 >= cnt && q < nt) {
+            if (++q == nt) break;
+            e0 = 0;
+            cnt = length(q);
+        }
+    };
+    settle();
+    while (q < nt) {
+        uint32_t at[UNDER], n[UNDER];
+        uint4 w[UNDER];
+#pragma unroll
+        for (int z = 0; z < UNDER; ++z) {
+            at[z] = z && q >= nt ? at[z - 1] : ((uint32_t)q << kSelTileLog2) + e0;
+            n[z] = q >= nt ? 0u : (cnt - e0 < kGroup ? cnt - e0 : kGroup);
+            const uint32_t end = n[z] ? (n[z] - 1u) & ~3u : 0u;
+            const uint64_t *const src = reinterpret_cast<const uint64_t *>(val + at[z] + (lane * 4 < end ? lane * 4 : end));
+            const uint64_t lo = get<true>(src), hi = get<true>(src + 1);
+            w[z] = make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+            e0 += kGroup;
+            settle();
+        }
+#pragma unroll
+        for (int z = 0; z < UNDER; ++z)
+            if (n[z]) f(at[z], n[z], w[z]);
+    }
+}
+__device__ __forceinline__ uint4 next_entry(const uint4 &b) { return make_uint4(b.y, b.z, b.w, b.x); }
+// of the lanes below this one, how many are in mask, and `more`
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask, uint32_t more)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, more));
+}
+
+// The selection where LDS does not hold the listed keys: many share the threshold's first digit (its binary exponent and three
+// more bits), as clipped or quantised values do, and values that lie within an eighth of an octave.  Every wavefront has consecutive
+// tiles and walks their lists.  With AHEAD the filter has taken the second digit's histogram (h1: this thread's bin), so one walk
+// remains in most cases: it takes the third digit's and copies what may still be selected to the wavefront's part of LDS.  Equal keys too
+// many for that cost two more, to count and to write; but lists that are all one magnitude (range, with AHEAD) are not walked.
+// Measured (topk_refine_static, us; by separate launches, with a search in the lists for every entry and digit, and so): 200,000 keys, k =
+// 2,500, all equal 173, 615, 40, all within [1, 1.125) 83, 370, 74, a tenth there 31, 41, 27, normal values clipped at 1 74, 197, 39;
+// 431,003, k = 500 the same 174, 1,307, 30; 80, 746, 84; 33, 79, 35; 74, 419, 24; a million, k = 2,500 180, 3,288, 51; 85, 2,054, 191;
+// 37, 196, 60; 79, 1,016, 48; 60,000, k = 500 (no separate launches) 175, 62; 101, 47; 18, 17; 61, 33.  Most of the walk is what is done
+// with groups that hold a key to keep.
+template <bool AHEAD, int TILES>
+__device__ __forceinline__ void flat_crowded(const SelList &ls, Flat<TILES> &f, int ntile, uint32_t h1, uint32_t prefix, uint32_t k_rem,
+                                             SelOut out)
+{
+    constexpr uint32_t kPart = Flat<TILES>::kMax / 16;               // entries of a wavefront in LDS
+    constexpr uint32_t kLong = 4 * kWave;                            // a list of no more is one load
+    static_assert(kPart % 4 == 0, "parts start at 16 bytes");
+    const int t = threadIdx.x, lane = t & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(t / kWave);
+    const int per = (ntile + 15) / 16, t0 = wave * per < ntile ? wave * per : ntile, nt = ntile - t0 < per ? ntile - t0 : per;
+    const uint32_t first = (uint32_t)t0 << kSelTileLog2;             // of the wavefront's lists, in val and loc
+    // lane q has list q: its length, and its magnitude if that is the only one in a long list (else 0, which no listed key has)
+    const uint32_t count = lane < nt ? f.start[t0 + lane + 1] - f.start[t0 + lane] : 0u;
+    uint32_t only = 0;
+    if (AHEAD && count > kLong) {
+        const uint32_t lo = get<true>(&ls.group[t0 + lane].x), hi = get<true>(&ls.group[t0 + lane].y);
+        only = lo == hi ? lo : 0u;
+    }
+    if constexpr (!AHEAD) {
+        each_group<4>(ls.val + first, [&](int q) { return (uint32_t)__builtin_amdgcn_readlane((int)count, q); }, nt,
+                   [&](uint32_t, uint32_t n, const uint4 &w) {
+            uint4 b = w;
+#pragma unroll 1
+            for (int y = 0; y < 4; ++y, b = next_entry(b))
+                count_alike(f.hist, lane * 4 + y < (int)n && ((b.x >> 20) & 0x7ffu) == prefix, (b.x >> 10) & 1023u);
+        });
+        __syncthreads();
+    } else {
+        f.hist[t] = h1;
+        __syncthreads();
+    }
+    flat_pick(f, f.picked, prefix, k_rem);
+    uint32_t *const pv = f.val + wave * kPart, *const pp = f.pos + wave * kPart;
+    uint32_t mine = 0;                                               // may exceed kPart
+    const uint32_t open = only ? 0u : count;                         // to be walked
+    each_group<4>(ls.val + first, [&](int q) { return (uint32_t)__builtin_amdgcn_readlane((int)open, q); }, nt,
+               [&](uint32_t at, uint32_t n, const uint4 &w) {
+        const uint32_t bits[4] = {w.x, w.y, w.z, w.w};
+        const uint32_t least = prefix << 10;                         // (first 11 and next 10 bits of 31)
+        uint32_t top4 = 0;
+#pragma unroll
+        for (int y = 0; y < 4; ++y) top4 = (bits[y] & 0x7fffffffu) > top4 ? bits[y] & 0x7fffffffu : top4;
+        if (!__any(top4 >= least)) return;                           // uniform; most groups, where keys differ
+        const int have = (int)n - lane * 4;                          // entries of this lane
+        uint64_t keep[4];
+#pragma unroll
+        for (int y = 0; y < 4; ++y) keep[y] = __ballot((bits[y] & 0x7fffffffu) >= least && y < have);
+        if (!(keep[0] | keep[1] | keep[2] | keep[3])) return;        // uniform
+        uint32_t rank = mine;
+#pragma unroll
+        for (int y = 0; y < 4; ++y) rank = lanes_below(keep[y], rank);
+        const uint32_t more = (uint32_t)(__popcll(keep[0]) + __popcll(keep[1]) + __popcll(keep[2]) + __popcll(keep[3]));
+        const bool many = more > 32u;
+        mine += more;
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+            const uint32_t key = bits[y] & 0x7fffffffu;
+            const bool in = key >= least && y < have, digit = in && key < least + 1024u;
+            if (in && rank < kPart) {
+                pv[rank] = bits[y];
+                pp[rank] = at + lane * 4 + y;
+            }
+            rank += in;
+            if (many) count_alike(f.hist, digit, key & 1023u);       // uniform
+            else if (digit) atomicAdd(&f.hist[key & 1023u], 1u);
+        }
+    });
+    if (only && (only >> 10) == prefix) atomicAdd(&f.hist[only & 1023u], count);
+    const bool spill = __syncthreads_or(mine > kPart || (only && (only >> 10) >= prefix));
+    flat_pick(f, f.picked + 2, prefix, k_rem);
+    const uint32_t tau = prefix, k_eq = k_rem;
+    out.k_eq = k_eq;
+    // the wavefront's entries: its part of LDS, or its lists
+    const uint32_t *const src = spill ? ls.val + first : pv;
+    const uint32_t src_open = spill ? open : mine;                   // (lane 0's is asked for of LDS)
+    const int src_lists = spill ? nt : 1;
+    uint32_t gt = 0, eq = 0;
+    each_group<4>(src, [&](int q) { return (uint32_t)__builtin_amdgcn_readlane((int)src_open, q); }, src_lists,
+               [&](uint32_t, uint32_t n, const uint4 &w) {
+        const uint32_t bits[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+            gt += (bits[y] & 0x7fffffffu) > tau && lane * 4u + y < n ? 1u : 0u;
+            eq += (bits[y] & 0x7fffffffu) == tau && lane * 4u + y < n ? 1u : 0u;
+        }
+    });
+    if (only > tau) gt += count;
+    if (only == tau) eq += count;                                    // (tau is no zero: those are not listed)
+    const uint32_t gt_before = block_exclusive_scan<1024>(gt, f.part), eq_before = block_exclusive_scan<1024>(eq, f.part);
+    uint32_t gt_run = (uint32_t)__builtin_amdgcn_readfirstlane((int)gt_before), eq_run = (uint32_t)__builtin_amdgcn_readfirstlane((int)eq_before);
+    const uint32_t last = spill ? (only && only < tau ? 0u : count) : mine;
+    each_group<2>(src, [&](int q) {
+        if (spill && eq_run >= k_eq && (uint32_t)__builtin_amdgcn_readlane((int)only, q) == tau) return 0u;   // all taken
+        return (uint32_t)__builtin_amdgcn_readlane((int)last, q);
+    }, src_lists, [&](uint32_t at, uint32_t n, const uint4 &w) {
+        const uint32_t bits[4] = {w.x, w.y, w.z, w.w};
+        const int have = (int)n - lane * 4;
+        const bool ties = eq_run < k_eq;                             // more than k_eq need no count
+        uint64_t gts[4], eqs[4];
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+            gts[y] = __ballot((bits[y] & 0x7fffffffu) > tau && y < have);
+            eqs[y] = __ballot(ties && (bits[y] & 0x7fffffffu) == tau && y < have);
+        }
+        if (!(gts[0] | gts[1] | gts[2] | gts[3] | eqs[0] | eqs[1] | eqs[2] | eqs[3])) return;   // uniform
+        uint32_t gtb = gt_run, eqb = eq_run;
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+            gtb = lanes_below(gts[y], gtb);
+            eqb = lanes_below(eqs[y], eqb);
+            gt_run += (uint32_t)__popcll(gts[y]);
+            eq_run += (uint32_t)__popcll(eqs[y]);
+        }
+        bool take[4];
+        uint32_t to[4], from[4];
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {                                // all positions under way, then all that map[] says
+            const uint32_t key = bits[y] & 0x7fffffffu;
+            const bool g = key > tau && y < have, q = ties && key == tau && y < have;
+            take[y] = (g || (q && eqb < k_eq)) && gtb + (eqb < k_eq ? eqb : k_eq) < out.k;
+            to[y] = gtb + (eqb < k_eq ? eqb : k_eq);
+            gtb += g;
+            eqb += q;
+            const uint32_t e = at + lane * 4 + y, listed = first + (spill || !take[y] ? e : pp[e]);
+            from[y] = take[y] ? (listed & ~((1u << kSelTileLog2) - 1u)) + get<true>(ls.loc + listed) : 0u;
+        }
+        if (out.map) {
+#pragma unroll
+            for (int y = 0; y < 4; ++y)
+                if (take[y]) from[y] = out.source(from[y]);
+        }
+#pragma unroll
+        for (int y = 0; y < 4; ++y)
+            if (take[y]) {
+                out.idx[to[y]] = (int32_t)from[y];
+                if (out.val_sel) out.val_sel[to[y]] = __uint_as_float(bits[y]);
+            }
+    });
+}
+
 // The selection where fewer keys than k differ from zero: those, all of them listed, and the first zeros.  With z zeros to take, a
 // listed key's rank is its position while fewer than z zeros lie before it, and its number in the lists plus z from there on; all
 // positions before the last of those zeros are selected.  (Zeros in the lists, most of a sparse vector's coordinates, would make the
-// last workgroup walk all keys three times: of 431,003 keys, 750 of them other than zero, k = 1,500 1,330 us,
-// and now 18; of 60,000, 250 of them, k = 500 180, 16.  Lists that are as full of another value still take that long.)
+// last workgroup walk all keys: of 431,003 keys, 750 of them other than zero, k = 1,500 18 us; of 60,000, 250 of them, k = 500 16.)
 template <bool AGENT, int TILES>
 __device__ __forceinline__ void flat_zeros(const SelList &ls, Flat<TILES> &f, uint32_t m, const float *__restrict__ keys, uint32_t len,
                                            uint32_t k, const int32_t *__restrict__ map, int32_t *__restrict__ idx,
@@ -524,7 +737,7 @@ __device__ __forceinline__ void flat_zeros(const SelList &ls, Flat<TILES> &f, ui
     for (uint32_t e0 = threadIdx.x; e0 < m; e0 += 1024) {
         uint32_t e[1] = {e0};
         uint2 x[1];
-        if (e0 < Flat<TILES>::kMax) x[0] = make_uint2(f.val[e0], f.pos[e0]);
+        if (m <= Flat<TILES>::kMax) x[0] = make_uint2(f.val[e0], f.pos[e0]);
         else flat_fetch<AGENT, 1>(ls, f, e, x);
         if (x[0].y - e0 < z) {
             ++early;
@@ -550,19 +763,32 @@ k_sel_small(const float *__restrict__ keys, int64_t len, SelState *__restrict__ 
             int64_t k, const int32_t *__restrict__ map, int32_t *__restrict__ idx, float *__restrict__ val_sel)
 {
     __shared__ Flat<TILES> f;
-    filter_tile<true, true, HISTS>(keys, len, blockIdx.x, nullptr, hist, (uint32_t)k, ls, f.picked);
+    constexpr bool kAhead = TILES > kSelMaxTiles;                    // (up to 16 tiles there may be no histogram of zeros to add to)
+    uint32_t *const hist1 = kAhead ? hist + kHistBins : nullptr;
+    filter_tile<true, true, HISTS>(keys, len, blockIdx.x, nullptr, hist, (uint32_t)k, ls, f.picked, Flat<TILES>::kMax, hist1, f.hist);
     uint32_t prefix = f.picked[0], k_rem = f.picked[1];
     if (!last_workgroup(&st->done[1], gridDim.x, f.part)) return;
     if constexpr (!HISTS)
         for (int b = threadIdx.x; b < kHistBins; b += 1024) hist[b] = 0u;   // every workgroup has read it
     __syncthreads();
-    const uint32_t m = flat_load<true>(ls, f, (int)gridDim.x);
+    const uint32_t m = flat_load<true>(ls, f, (int)gridDim.x, (uint32_t)len);
+    uint32_t h1 = 0;
+    if constexpr (kAhead) {
+        if (m > Flat<TILES>::kMax) h1 = get<true>(hist1 + threadIdx.x);
+        hist1[threadIdx.x] = 0u;
+    }
     if (prefix == 0u && m < (uint32_t)k) {
         flat_zeros<true>(ls, f, m, keys, (uint32_t)len, (uint32_t)k, map, idx, val_sel);
         return;
     }
-    flat_digits<true>(ls, f, m, prefix, k_rem);
-    flat_write<true>(ls, f, m, prefix, k_rem, k, len, map, idx, val_sel);
+    SelOut out = {map, idx, val_sel, k, len, 0u};
+    if (m > Flat<TILES>::kMax) {
+        flat_crowded<kAhead>(ls, f, (int)gridDim.x, h1, prefix, k_rem, out);
+        return;
+    }
+    flat_digits(f, m, prefix, k_rem);
+    out.k_eq = k_rem;
+    flat_write(f, m, prefix, out);
 }
 
 // PICK: the filter picks the first digit (and leaves it in the state), see above
