@@ -414,7 +414,7 @@ static bool pull_shape(const sams_ctx *ctx, const Tunables &tun)
     if (tun.sketch_path != 0 || tun.estimate_path == 2 || tun.win_log2 || tun.tile_log2 || tun.chunk_log2 || tun.acc_threads ||
         tun.stage_rows)
         return false;                                                // the caller asks for the binned path or for a shape of it
-    if (ctx->c > kPullWide && ctx->d < kPullWideMinD) return false;
+    if (ctx->c > kPullWide && ctx->d < kPullWideMinD && !tun.pull_lists) return false;
     return ctx->c >= 128 && ctx->c <= kPullMaxC && ctx->d <= ((int64_t)1 << 26) && (int64_t)ctx->n * ctx->d >= 4;
 }
 
@@ -508,7 +508,7 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
     *done = false;
     PullPlan pp = {};
     const int32_t ntile = (int32_t)((ctx->d + kPullTile - 1) / kPullTile), nslice = (int32_t)((ctx->c + kWave - 1) / kWave);
-    if (!pull_shape(ctx, tun) || pull_declines(ctx, ntile)) return SAMS_OK;
+    if (!pull_shape(ctx, tun) || (!tun.pull_lists && pull_declines(ctx, ntile))) return SAMS_OK;
     const int64_t rows = (int64_t)ctx->r * ntile;                    // (row, tile) pairs
     uint16_t *cnt = nullptr, *len = nullptr;                         // build-time only
     uint32_t *off = nullptr;
@@ -545,7 +545,8 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
         PullOrder po = {};
         int64_t cost = INT64_MAX;
         double steps = 0;
-        for (int many = wide; many < 2; ++many) {
+        for (int many = 0; many < 2; ++many) {
+            if (tun.pull_lists ? (tun.pull_lists > 1) != many : wide && !many) continue;
             PullOrder x = {};
             x.ntile = ntile;
             x.nslice = nslice;
@@ -568,7 +569,7 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
                 steps = all;
             }
         }
-        if (wide && cost > 25000 + (int64_t)ctx->n * ctx->r * ctx->d * 7 / 4000) break;   // (see pull_declines)
+        if (wide && !tun.pull_lists && cost > 25000 + (int64_t)ctx->n * ctx->r * ctx->d * 7 / 4000) break;   // (see pull_declines)
         if (steps * kWave > 12.0 * ctx->r * (double)ctx->d + 8.0 * kWave * (double)rows * nslice) break;   // lists that are mostly padding
         if (counted > 1 && !count(1)) break;
         uint32_t longest = 0;
