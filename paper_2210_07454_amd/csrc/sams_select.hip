@@ -150,8 +150,8 @@ k_est_median(const float *__restrict__ rowest, const float *__restrict__ vhat, f
 // the selected ones and the candidates, about 1.5 k of them unless many keys are equal -- in coordinate order, every
 // tile of keys in a region of its own.  Everything after that works on the listed keys only (on all keys, without the filter,
 // where a context of more than 2^20 coordinates found no room for lists).
-//   up to 2^20 keys and small k (kSelSmallMaxK, kSelFlatMaxK, kSelFlatShortMaxK; but see sel_by_launches): k_sel_small filters, and its last
-//   workgroup finishes the selection
+//   up to 2^20 keys and small k (kSelSmallMaxK, kSelFlatMaxK, kSelFlatShortMaxK): k_sel_small filters, and its last workgroup finishes
+//   the selection
 //   else: k_sel_filter, two histograms of the listed keys, k_sel_count, k_sel_write
 // Up to 2^20 keys every filter workgroup picks the first digit from the histogram for itself (8 KiB, in every L2); above,
 // the last workgroup of the histogram does it once.
@@ -1007,10 +1007,6 @@ k_sel_write(const SelState *__restrict__ st, SelList ls, int64_t len, int64_t pi
     }
 }
 
-// Between 2^16 and 2^17 keys a selection is made of the separate launches, a histogram of the first digit among them, whatever k: a test
-// counts them (one workgroup would finish 100,000 keys, k = 800, in 12 us instead of 21).
-static bool sel_by_launches(int64_t len) { return len > kSelSmallMax && len <= 2 * kSelSmallMax; }
-
 constexpr int kEstLdsBytes = 160 * 1024;
 constexpr int64_t kGatherEstimateMaxTableBytes = 1 << 20, kGatherEstimateMaxD = (int64_t)1 << 22;
 
@@ -1108,7 +1104,7 @@ int enqueue_estimate(sams_ctx *ctx, const float *S_mean, const float *vhat, floa
         SAMS_HIP(hipGetLastError());
         return SAMS_OK;
     }
-    const bool with_hist = sc && !sel_by_launches(ctx->d);
+    const bool with_hist = sc != nullptr;
     SelState *const st = with_hist && sel_hist_picks(ctx->d) ? sc->st : nullptr;
     switch (ctx->r) {
 #define SAMS_CASE(R)                                                                                       \
@@ -1146,10 +1142,11 @@ SelScratch ctx_sel_scratch(const sams_ctx *ctx)
 // The largest k for which k_sel_small's last workgroup finishes by itself: it takes 2 us per thousand listed keys, where the other
 // kernels take 26 us (above 2^16 keys, without a first pass for tiles' histograms, 22) whatever the lists hold.  Both (topk_refine): 20,000
 // keys, k = 5,000 17 and 26 us, 10,000 30 and 26 us; 65,536 keys, k = 8,192 25 and 26 us, 16,384 43 and 26 us, 65,536 142 and 26 us; 431,003,
-// k = 500 16 and 30 us, 2,500 18 and 30 us, 4,311 22 and 30 us; a million, k = 3,000 23 and 32 us.  Above 2^16 keys the line lies lower
-// than these say: keys whose errors a training run has fed back for long are closer to each other, and three times k of them share
-// the first digits (whole steps after 600 to 1,000: 200,000 coordinates, k = 2,500 53 and 63 us; 300,000, 3,000 68.7 and 71; 431,003,
-// 3,000 76.3 and 78.3, 4,311 83.1 and 80.4; 800,000, 2,500 114 and 117; a million, 2,000 136 and 141, 3,000 141 and 137).
+// k = 500 16 and 30 us, 2,500 18 and 30 us, 4,311 22 and 30 us; 66,000, k = 3,000 17 and 25 us, 131,072 19 and 25; a million, k = 3,000 23
+// and 32 us.  Above 2^16 keys the line lies lower than these say: keys whose errors a training run has fed back for long are closer to
+// each other, and three times k of them share the first digits (whole steps after 600 to 1,000: 70,000 coordinates, k = 256 35 and
+// 50 us; 131,000, 3,000 48 and 57; 200,000, 2,500 53 and 63; 300,000, 3,000 68.7 and 71; 431,003, 3,000 76.3 and 78.3, 4,311 83.1 and
+// 80.4; 800,000, 2,500 114 and 117; a million, 2,000 136 and 141, 3,000 141 and 137).
 constexpr int64_t kSelSmallMaxK = 1 << 13, kSelFlatMaxK = 2500, kSelFlatShortMaxK = 3000, kSelFlatShort = (int64_t)1 << 19;
 // Tiles' lists are cut into pieces of at least 256 entries (about 1.5 k are listed) while there are fewer than 16 wavefronts for
 // each of the 256 compute units.  Whole lists and pieces: 100,000 keys, k = 50,000 54 and 26 us; a million, half of them 62 and
@@ -1164,7 +1161,7 @@ int enqueue_select(sams_ctx *ctx, hipStream_t stream, const SelScratch &sc, cons
     uint32_t *hist1 = sc.hist + kHistBins, *hist2 = hist1 + kHistBins / 2;
     const bool tiles = len <= kSelSmallMax;
     const int64_t small_k = tiles ? kSelSmallMaxK : len <= kSelFlatShort ? kSelFlatShortMaxK : kSelFlatMaxK;
-    const bool small = len <= kSelFlatMax && !sel_by_launches(len) && k <= small_k;
+    const bool small = len <= kSelFlatMax && k <= small_k;
     if (small && tiles && !hist_done) {
         const int grid = grid_for(len, 1 << kSelTileLog2);
         SAMS_LAUNCH_ON(ctx, stream, KID_SEL_HIST, k_sel_hist_tiles, grid, 1024, keys, len, sc.tile_hist, &sc.st->done[1]);

@@ -920,7 +920,7 @@ def test_step_on_a_side_stream_and_as_a_replayed_hip_graph(sams):
 def test_kernel_timing_counts_launches_and_changes_no_result(sams):
     """The optional per-kernel timing: every launch of the window is counted once, a filter restricts it to one
     kernel, durations are positive, and the outputs are the same bits as without it."""
-    d, n, r, c, k = 100_003, 3, 5, 1_000, 777
+    d, n, r, c, k = 100_003, 3, 5, 1_000, 7_777                      # a k that no one workgroup finishes: launches of every kind
     rng = np.random.default_rng(5)
     hp = inputs.hash_params(r, seed=5)
     u = dev(rng.standard_normal((n, d)).astype(np.float32))
@@ -942,7 +942,7 @@ def test_kernel_timing_counts_launches_and_changes_no_result(sams):
         prof = ctx.sams_profile_read()
         for got in timed:
             assert all(np.array_equal(a, b) for a, b in zip(got, plain))
-        assert prof["k_reduce"][1] == 3 and prof["k_sel_hist"][1] == 9 and prof["k_sel_write"][1] == 3
+        assert prof["k_reduce"][1] == 3 and prof["k_sel_hist"][1] == 6 and prof["k_sel_write"][1] == 3
         assert all(ms > 0.0 for ms, _ in prof.values())
         ctx.sams_profile_only("k_reduce")
         ctx.sams_profile_enable(True)

@@ -44,7 +44,7 @@ def crowd(kind, rng, n):
     raise ValueError(kind)
 
 
-@pytest.mark.parametrize("n,k", [(15_361, 1), (20_001, 8_192), (65_536, 777), (131_073, 3_000), (200_003, 2_999), (524_288, 1), (524_289, 2_500),
+@pytest.mark.parametrize("n,k", [(15_361, 1), (20_001, 8_192), (65_536, 777), (65_537, 3_000), (100_003, 777), (131_072, 2_999), (131_073, 3_000), (200_003, 2_999), (524_288, 1), (524_289, 2_500),
                                  (1_048_573, 2_499), (1 << 20, 17)])
 @pytest.mark.parametrize("kind", ["equal", "narrow", "clipped", "quantised", "clipped-and-above", "one-end", "ties-in-one-tile", "infinite", "subnormal"])
 def test_keys_that_share_the_first_digit(kind, n, k):
@@ -62,7 +62,7 @@ def test_keys_that_share_the_first_digit(kind, n, k):
 
 
 # without second moments a narrow table gives few magnitudes to many coordinates; a context's own lists and histograms, selection after selection
-@pytest.mark.parametrize("d,r,c,k", [(60_000, 1, 150, 700), (262_147, 1, 200, 2_000), (400_001, 2, 300, 2_900), (1_000_003, 3, 500, 2_500)])
+@pytest.mark.parametrize("d,r,c,k", [(60_000, 1, 150, 700), (65_537, 1, 200, 3_000), (131_071, 2, 300, 800), (262_147, 1, 200, 2_000), (400_001, 2, 300, 2_900), (1_000_003, 3, 500, 2_500)])
 def test_estimates_of_few_magnitudes(d, r, c, k):
     from paper_2210_07454_amd import sams
     rng = np.random.default_rng(d)
