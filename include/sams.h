@@ -136,9 +136,9 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
  *                 vector); LDS atomics for small tables with larger d.  A table of 128 to 16384 buckets under a vector of
  *                 up to 2^26 coordinates goes another way, by lists and without staging, which keeps the order up to d = 2^22
  *                 (above, the vector may be cut into parts whose sums are added up, always in the same way), unless "tile_log2", "win_log2",
- *                 "chunk_log2", "acc_threads", "stage_rows" or "estimate_path" 2 ask for the binned path, or (unless "pull_lists" is set) the shape is one that the
- *                 other path is faster for (few rows and workers, 2000 to 4096 buckets, d of a million or more; n*r of 160 or more,
- *                 long lists).  "fuse_head" then has nothing to stage and changes nothing; 1: one global atomic add per term
+ *                 "chunk_log2", "acc_threads", "stage_rows" or "estimate_path" 2 ask for the binned path, or (unless "pull_lists" is
+ *                 set) the shape is one that the other path is faster for (few rows and workers, up to 4096 buckets, d of a million
+ *                 or more).  "fuse_head" then has nothing to stage and changes nothing; 1: one global atomic add per term
  *                 (no plan and no staging); 2: the order-preserving path always; 3: LDS atomics whenever c fits one
  *                 window
  *   "pull_lists"  0 (default), 1 or 4: buckets that a lane of the path by lists (see "sketch_path") takes in turns from one list.  0:

@@ -408,7 +408,7 @@ k_pull_sum(const float *__restrict__ part, float *__restrict__ S, int64_t cells,
 // tile's 64 buckets are padding but for a tenth (13,308 coordinates and a step or two for each of 512 slices), and their making would
 // not fit in LDS; the lists of longer vectors take gigabytes.
 constexpr int64_t kPullLongD = 1000000;       // shorter vectors always pull: both paths are launches and latencies
-constexpr int64_t kPullWidePinned = 15000, kPullWide = 1 << 14, kPullMaxC = 1 << 15, kPullWideMinD = 1 << 18;
+constexpr int64_t kPullWide = 1 << 14, kPullMaxC = 1 << 15, kPullWideMinD = 1 << 18;
 static bool pull_shape(const sams_ctx *ctx, const Tunables &tun)
 {
     if (tun.sketch_path != 0 || tun.estimate_path == 2 || tun.win_log2 || tun.tile_log2 || tun.chunk_log2 || tun.acc_threads ||
@@ -486,9 +486,9 @@ static int64_t pull_share(const sams_ctx *ctx, PullOrder &po, const double *step
 // coordinates, 1 to 64 workers, 1 to 10 rows and 128 to 16,384 buckets the lists are the faster at 74, two to ten times so at most; not
 // where few pairs walk a long vector through few short streams: one row of 4,096 under four million coordinates, n = 1, 161 and
 // 106 us, three of 3,000, n = 2, 193 and 175 us.  In ns, as both were before the lists came in groups of four slices, and the line is
-// where it was: 820 per tile here, there a base, 0.67 per position of a window's stream and 1.6 per thousand terms.  Tables of
-// 15,000 to 2^14 buckets for many pairs stay binned too (tests pin that), although the lists have overtaken: 5 x 16,384, n = 50, four
-// million 1.9 ms, by lists 0.95 to 1.5 by the hash.
+// where it was: 820 per tile here, there a base, 0.67 per position of a window's stream and 1.6 per thousand terms.  Many pairs under
+// wide tables are no exception: of 16 shapes with 1 to 20 million coordinates, 160 to 600 pairs and 9,001 to 16,384 buckets, two hashes
+// each, lists are the faster at all, 1.03 to 2.7 times (5 x 16,384, n = 50, four million 1.27 and 1.48 by the hash, and 1.92 ms).
 // Above 2^14 buckets the line is the cost that pull_share returns against 1.75 ns per thousand terms by bins: of 66 shapes with 0.27 to
 // 21 million coordinates and 16,400 to 32,700 buckets the lists are the faster at 65, 1.0 to 2.5 times up to 2^22 coordinates (where
 // one of 40 others, 7 x 29,777 and n = 32 under 2.6 million, lost with 1,288 us to 1,005), two to 26 times above, where the others are
@@ -497,7 +497,6 @@ static bool pull_declines(const sams_ctx *ctx, int32_t ntile)
 {
     const int64_t pairs = (int64_t)ctx->n * ctx->r;
     if (ctx->d < kPullLongD) return false;
-    if (ctx->c > kPullWidePinned && ctx->c <= kPullWide && pairs >= 160) return true;
     if (ctx->d > kOrderedSingleBinMaxD || ctx->c > (1 << 12) || pairs * ((ctx->c + 127) / 128) >= 2048) return false;
     return 25000 + 86 * ctx->d / ctx->c + pairs * ctx->d * 16 / 10000 < ((int64_t)ntile + 12) * 820;
 }
