@@ -141,9 +141,9 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
  *                 or more).  "fuse_head" then has nothing to stage and changes nothing; 1: one global atomic add per term
  *                 (no plan and no staging); 2: the order-preserving path always; 3: LDS atomics whenever c fits one
  *                 window
- *   "pull_lists"  0 (default), 1 or 4: buckets that a lane of the path by lists (see "sketch_path") takes in turns from one list.  0:
- *                 chosen from the shape and the lengths of the lists; 1, 4: these, for every shape that lists can be made for.
- *                 Same results as by lists of the other kind
+ *   "pull_lists"  0 (default), 1, 2 or 4: what a wavefront of the path by lists (see "sketch_path") takes.  0: chosen from the shape and the
+ *                 lengths of the lists; 1: one list of 64 buckets; 2: one or two such lists; 4: one to four lists of 256 buckets; 1, 2 and
+ *                 4 for every shape that lists can be made for.  Same results with each up to d = 2^22
  * Returns SAMS_EINVAL for an unknown key or a value out of range.
  */
 int sams_configure(const char *key, int value);

@@ -258,7 +258,7 @@ int sams_configure(const char *key, int value)
         if (value < 0 || value > 1) return SAMS_EINVAL;
         g_tun.stage_spread = value;
     } else if (!strcmp(key, "pull_lists")) {
-        if (value != 0 && value != 1 && value != 4) return SAMS_EINVAL;
+        if (value != 0 && value != 1 && value != 2 && value != 4) return SAMS_EINVAL;
         g_tun.pull_lists = value;
     } else if (!strcmp(key, "acc_wide")) {
         if (value < 0 || value > 2) return SAMS_EINVAL;

@@ -121,7 +121,7 @@ struct Tunables {
     int run_pad;          // runs are padded to a multiple of this many stream positions (4, 8, 16 or 32)
     int stage_interleave; // 1 = the workers' staged copies are interleaved in pieces of 32 stream positions
     int stage_spread;     // 1 = a staging buffer of 2 GiB or more is mapped from 1 GiB chunks picked at even distances over all free device memory
-    int pull_lists;       // slices of a list of the pulling path: 0 = chosen; 1, 4 = these, wherever lists can be made
+    int pull_lists;       // lists of the pulling path: 0 = chosen; 1 = one of a slice per wavefront, 2 = up to two, 4 = up to four of four slices
     int acc_wide;         // accumulate kernel where its shape allows (1024 threads, 2048-position chunks): 1 = 16-byte loads,
                           // 2 = 16-byte loads and compact chunk records instead of meta words (falls back to 1 when a chunk has too many chains)
 };

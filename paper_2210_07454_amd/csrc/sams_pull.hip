@@ -7,9 +7,9 @@
 // lane of a wavefront owns one bucket of each of its slices -- one, or up to sixteen --, with the sum in a register.  Which
 // coordinates of a tile a bucket takes is worked out once, at context creation: lists of steps, each of 64 entries, one per lane -- the
 // coordinate inside the tile and its sign --, padded with an entry that points at a zero; the lists of a wavefront lie one after the
-// other, as one stream, which a lane reads 16 bytes at a time.  With one slice per wavefront a list is that of a (row, tile, slice);
-// with several it is that of four slices, a word (two steps) of each in every load: four sums that do not wait for each other, and one
-// test for the list's end in eight steps.  A lane takes its entries in ascending coordinate order, so the sums are those of a
+// other, as one stream, which a lane reads 16 bytes at a time.  With one or two slices per wavefront a list is that of a (row, tile,
+// slice); with more it is that of four slices, a word (two steps) of each in every load: four sums that do not wait for each other, and
+// one test for the list's end in eight steps.  A lane takes its entries in ascending coordinate order, so the sums are those of a
 // sequential loop over the coordinates, bit for bit (adding the padding's zero changes nothing: a sum that starts at +0 is never -0; a
 // value is added as fma(value, +-1, sum), which rounds once, like the addition).  No atomics, no exchange between lanes, one barrier
 // per tile.
@@ -58,6 +58,7 @@ constexpr int kPullDepth = 6;                 // such loads on their way ahead o
 constexpr int kPullSpare = 2 * kPullLoad * kPullDepth;   // words of a lane behind the last list: the adders' loop goes in turns of kPullDepth
                                               // loads, each refilled, so it reads up to 2 kPullDepth - 1 loads past its own
 constexpr int kPullMany = 4;                  // most lists of four slices per wavefront
+constexpr int kPullPair = 2;                  // most lists of one slice per wavefront
 constexpr int kPullMaxList = 512;             // longest list of one bucket in one tile
 // A word holds two consecutive steps of a lane: the first step's coordinate in bits 2-15 (so that it is a byte offset) and
 // its sign in bit 0, the second's in bits 17-30 and 31.  Bit 1 of the first word of a list's last unit, in every lane, ends the list.
@@ -71,6 +72,7 @@ constexpr int kPullMaxList = 512;             // longest list of one bucket in o
 struct PullOrder {
     int32_t ntile, nslice, nlist;
     int32_t per_list, group;          // slices of a list; words of a lane in a list's smallest unit
+    int32_t most;                     // lists that a wavefront may have: 1 or kPullPair of one slice, kPullMany of four
     int32_t parts, per_part, windows; // windows: of all rows
     PullRow row[SAMS_MAX_ROWS + 1];
 };
@@ -215,9 +217,10 @@ __device__ __forceinline__ void tile_barrier() { asm volatile("s_waitcnt lgkmcnt
 // their own loads only (a wavefront's loads come back in order: one that fetched both would wait for the whole next
 // tile before each list).  The adders' loop is a stream of words: a load is issued for every one used up, unconditionally and
 // straight into the registers that the loop carries, so that the compiler waits for exactly the oldest.
-// MANY = false: a slice per wavefront, lists of units of W words, whose values are read from LDS together and added in order.
-// MANY: lists of four slices, a word of each per load, and up to kPullMany such lists per wavefront, whose sums take turns.
-template <int W, bool MANY>
+// Up to MOST lists per wavefront, whose sums take turns.
+// MANY = false: lists of a slice, of units of W words, whose values are read from LDS together and added in order.
+// MANY: lists of four slices, a word of each per load.
+template <int W, bool MANY, int MOST>
 __global__ void __launch_bounds__(kPullThreads)
 k_sketch_pull(PullArgs a)
 {
@@ -303,9 +306,9 @@ k_sketch_pull(PullArgs a)
     }
     src += (int64_t)kPullDepth * kWave;
     constexpr int kPer = MANY ? kPullLoad : 1;                       // slices of a list
-    float x[MANY ? kPullMany * kPer : 1], sum[kPer];                 // sum: of the list that is being added, in place of its x
+    float x[MOST * kPer], sum[kPer];                                 // sum: of the list that is being added, in place of its x
 #pragma unroll
-    for (int p = 0; p < (MANY ? kPullMany * kPer : 1); ++p) x[p] = 0.f;
+    for (int p = 0; p < MOST * kPer; ++p) x[p] = 0.f;
 #pragma unroll
     for (int y = 0; y < kPer; ++y) sum[y] = 0.f;
     int32_t turn = 0;                                                // that list
@@ -363,7 +366,15 @@ k_sketch_pull(PullArgs a)
                     }
 #pragma unroll
                     for (int p = 0; p < W; ++p) add(sum[0], w[y * W + p], v[2 * p], v[2 * p + 1]);
-                    if (__builtin_amdgcn_readfirstlane((int)w[y * W]) & 2) tile_done(m + 1 < ng);
+                    if (__builtin_amdgcn_readfirstlane((int)w[y * W]) & 2) {     // the list ends
+                        if (MOST > 1 && lists > 1) {                 // x[1]: the sum of the one that waits
+                            const float other = x[1];
+                            x[1] = sum[0];
+                            sum[0] = other;
+                            turn ^= 1;
+                        }
+                        if (turn == 0) tile_done(m + 1 < ng);
+                    }
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -376,7 +387,7 @@ k_sketch_pull(PullArgs a)
     for (int y = 0; y < kPer; ++y) x[y] = sum[y];                    // the last tile's lists have ended
     float *out = a.S + (((int64_t)part * a.n + i) * a.r + j) * a.c;
 #pragma unroll
-    for (int p = 0; p < (MANY ? kPullMany * kPer : 1); ++p) {
+    for (int p = 0; p < MOST * kPer; ++p) {
         const int64_t b = (int64_t)(l0 * kPer + p) * kWave + lane;
         if (p < lists * kPer && b < a.c) out[b] = x[p];
     }
@@ -437,7 +448,7 @@ static int64_t pull_share(const sams_ctx *ctx, PullOrder &po, const double *step
 {
     const bool many = po.per_list > 1;
     const double kTileNs = 450, kStepNs = 3.0, kChainNs = many ? 20 : 30, kStartNs = ctx->d > kOrderedSingleBinMaxD ? 20000 : 5000;
-    const int32_t most_lists = kPullAdders * (many ? kPullMany : 1), least = (po.nlist + most_lists - 1) / most_lists;
+    const int32_t most_lists = kPullAdders * po.most, least = (po.nlist + most_lists - 1) / most_lists;
     const int32_t most_parts = ctx->d > kOrderedSingleBinMaxD ? (po.ntile < 128 ? po.ntile : 128) : 1;
     double best = 1e30;
     for (int32_t parts = 1; parts <= most_parts; ++parts) {
@@ -544,12 +555,20 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
         PullOrder po = {};
         int64_t cost = INT64_MAX;
         double steps = 0;
-        for (int many = 0; many < 2; ++many) {
-            if (tun.pull_lists ? (tun.pull_lists > 1) != many : wide && !many) continue;
+        // Two lists of a slice per wavefront save a round of workgroups where a row has 15 to 28 slices (45 x 5 pairs of 1,020 buckets, 77,028
+        // coordinates: 16.1 us with one, 11.8 with two, 14.4 with lists of four slices, of which four wavefronts of fourteen have one; 93 x 3
+        // of 971, 148,962: 44.5, 29.8, 41.7; 28 x 7 of 1,597, 347,459: 50, 39, 62).  Where lists are one unit, and most of it padding, they
+        // take longer than pull_share says: 3.3 million, 3 x 7 pairs of 16,000 buckets 209 us, lists of four slices 184.  Of 314
+        // shapes with 50,000 to 4 million coordinates and 400 to 16,000 buckets the choice is the fastest form or within 4 % of it at
+        // 285, 8 % at 306 and 37 % at all.
+        for (int form : {1, 2, 4}) {
+            if (tun.pull_lists ? tun.pull_lists != form : wide && form < 4) continue;
+            const bool many = form == 4;
             PullOrder x = {};
             x.ntile = ntile;
             x.nslice = nslice;
             x.per_list = many ? kPullLoad : 1;
+            x.most = many ? kPullMany : form;
             x.group = many ? kPullLoad : (ctx->c <= 1500 ? 4 : 2);
             x.nlist = (nslice + x.per_list - 1) / x.per_list;
             double per_tile[SAMS_MAX_ROWS], all = 0;
@@ -561,7 +580,8 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
                 per_tile[j] = (double)units * 2 * x.group / seen;
                 all += per_tile[j] * ntile;
             }
-            const int64_t c = pull_share(ctx, x, per_tile);
+            int64_t c = pull_share(ctx, x, per_tile);
+            if (form == 2 && x.group == 2 && !tun.pull_lists) c += c / 10;
             if (c < cost) {
                 cost = c;
                 po = x;
@@ -604,8 +624,9 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
                     }
         run = (run + per_load - 1) / per_load * per_load;
         if (run >= (1ull << 31)) break;
-        pp.kernel = po.per_list > 1 ? (const void *)k_sketch_pull<1, true>
-                                    : (po.group == 4 ? (const void *)k_sketch_pull<4, false> : (const void *)k_sketch_pull<2, false>);
+        if (po.per_list > 1) pp.kernel = (const void *)k_sketch_pull<1, true, kPullMany>;
+        else if (po.most > 1) pp.kernel = po.group == 4 ? (const void *)k_sketch_pull<4, false, kPullPair> : (const void *)k_sketch_pull<2, false, kPullPair>;
+        else pp.kernel = po.group == 4 ? (const void *)k_sketch_pull<4, false, 1> : (const void *)k_sketch_pull<2, false, 1>;
         e = hipFuncSetAttribute(pp.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
         if (e != hipSuccess) { g_last_hip_error = (int)e; rc = SAMS_EHIP; break; }
         pp.list_bytes = (int64_t)(run * (uint64_t)po.group + kPullSpare) * kWave * 4;
