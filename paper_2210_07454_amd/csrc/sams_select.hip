@@ -379,7 +379,7 @@ struct Flat {
 };
 
 // entries e[0..N), each below the number of entries: tile by bisection, N searches side by side
-template <bool AGENT, int N, int TILES>
+template <int N, int TILES>
 __device__ __forceinline__ void flat_fetch(const SelList &ls, const Flat<TILES> &f, const uint32_t (&e)[N], uint2 (&x)[N])
 {
     uint32_t tile[N];
@@ -394,19 +394,19 @@ __device__ __forceinline__ void flat_fetch(const SelList &ls, const Flat<TILES> 
 #pragma unroll
     for (int z = 0; z < N; ++z) {
         const uint32_t base = tile[z] << kSelTileLog2, at = base + e[z] - f.start[tile[z]];
-        x[z] = make_uint2(get<AGENT>(ls.val + at), base + get<AGENT>(ls.loc + at));
+        x[z] = make_uint2(get<true>(ls.val + at), base + get<true>(ls.loc + at));
     }
 }
 
 // the number of entries; complete for all threads
-template <bool AGENT, int TILES>
+template <int TILES>
 __device__ __forceinline__ uint32_t flat_load(const SelList &ls, Flat<TILES> &f, int ntile, uint32_t len)
 {
     static_assert(2 * TILES <= 1024, "a thread per start");
     const int t = threadIdx.x;
     // (a call on another stream with the same scratch may have put any count there: no list is longer than its tile)
     const uint32_t rest = t < ntile ? len - ((uint32_t)t << kSelTileLog2) : 0u, tile = rest < 1u << kSelTileLog2 ? rest : 1u << kSelTileLog2;
-    const uint32_t cnt = t < ntile ? get<AGENT>(ls.cnt + t) : 0u;
+    const uint32_t cnt = t < ntile ? get<true>(ls.cnt + t) : 0u;
     const uint32_t before = block_exclusive_scan<1024>(cnt < tile ? cnt : tile, f.part);
     if (t < 2 * TILES) f.start[t] = before;                          // from ntile on: the number of entries
     f.hist[t] = 0;
@@ -419,7 +419,7 @@ __device__ __forceinline__ uint32_t flat_load(const SelList &ls, Flat<TILES> &f,
         uint2 x[4];
 #pragma unroll
         for (int z = 0; z < 4; ++z) e[z] = e0 + z * 1024 < m ? e0 + z * 1024 : m - 1;
-        flat_fetch<AGENT, 4>(ls, f, e, x);
+        flat_fetch<4>(ls, f, e, x);
 #pragma unroll
         for (int z = 0; z < 4; ++z) {                                // (the last entry may be stored twice, alike)
             f.val[e[z]] = x[z].x;
@@ -579,10 +579,11 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask, uint32_t more)
 // remains in most cases: it takes the third digit's and copies what may still be selected to the wavefront's part of LDS.  Equal keys too
 // many for that cost two more, to count and to write; but lists that are all one magnitude (range, with AHEAD) are not walked.
 // Measured (topk_refine_static, us; by separate launches, with a search in the lists for every entry and digit, and so): 200,000 keys, k =
-// 2,500, all equal 173, 615, 40, all within [1, 1.125) 83, 370, 74, a tenth there 31, 41, 27, normal values clipped at 1 74, 197, 39;
-// 431,003, k = 500 the same 174, 1,307, 30; 80, 746, 84; 33, 79, 35; 74, 419, 24; a million, k = 2,500 180, 3,288, 51; 85, 2,054, 191;
-// 37, 196, 60; 79, 1,016, 48; 60,000, k = 500 (no separate launches) 175, 62; 101, 47; 18, 17; 61, 33.  Most of the walk is what is done
-// with groups that hold a key to keep.
+// 2,500, all equal 173, 615, 40, all within [1, 1.125) 83, 370, 54, a tenth there 31, 41, 27, normal values clipped at 1 74, 197, 39;
+// 431,003, k = 500 the same 174, 1,307, 30; 80, 746, 62; 33, 79, 29; 74, 419, 24; a million, k = 2,500 180, 3,288, 51; 85, 2,054, 130;
+// 37, 196, 48; 79, 1,016, 45; 60,000, k = 500 (no separate launches) 175, 62; 101, 42; 18, 17; 61, 33.  The walk is bound by instruction
+// issue: with eight groups under way in place of four it takes as long, with a case of its own for groups that hold a few keys to keep
+// 191 -> 130 us at a million.
 template <bool AHEAD, int TILES>
 __device__ __forceinline__ void flat_crowded(const SelList &ls, Flat<TILES> &f, int ntile, uint32_t h1, uint32_t prefix, uint32_t k_rem,
                                              SelOut out)
@@ -626,10 +627,29 @@ __device__ __forceinline__ void flat_crowded(const SelList &ls, Flat<TILES> &f, 
         for (int y = 0; y < 4; ++y) top4 = (bits[y] & 0x7fffffffu) > top4 ? bits[y] & 0x7fffffffu : top4;
         if (!__any(top4 >= least)) return;                           // uniform; most groups, where keys differ
         const int have = (int)n - lane * 4;                          // entries of this lane
+        uint32_t own = 0, bit = 0, which = 0;                        // how many are kept, the last one
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+            const bool in = (bits[y] & 0x7fffffffu) >= least && y < have;
+            own += in;
+            bit = in ? bits[y] : bit;
+            which = in ? y : which;
+        }
+        const uint64_t any = __ballot(own);
+        if (!any) return;                                            // uniform
+        if (__popcll(any) <= 32 && !__ballot(own > 1u)) {            // uniform; most of the rest: a third of the instructions
+            const uint32_t rank = lanes_below(any, mine), key = bit & 0x7fffffffu;
+            if (own && rank < kPart) {
+                pv[rank] = bit;
+                pp[rank] = at + lane * 4 + which;
+            }
+            if (own && key < least + 1024u) atomicAdd(&f.hist[key & 1023u], 1u);
+            mine += (uint32_t)__popcll(any);
+            return;
+        }
         uint64_t keep[4];
 #pragma unroll
         for (int y = 0; y < 4; ++y) keep[y] = __ballot((bits[y] & 0x7fffffffu) >= least && y < have);
-        if (!(keep[0] | keep[1] | keep[2] | keep[3])) return;        // uniform
         uint32_t rank = mine;
 #pragma unroll
         for (int y = 0; y < 4; ++y) rank = lanes_below(keep[y], rank);
@@ -726,7 +746,7 @@ __device__ __forceinline__ void flat_crowded(const SelList &ls, Flat<TILES> &f, 
 // listed key's rank is its position while fewer than z zeros lie before it, and its number in the lists plus z from there on; all
 // positions before the last of those zeros are selected.  (Zeros in the lists, most of a sparse vector's coordinates, would make the
 // last workgroup walk all keys: of 431,003 keys, 750 of them other than zero, k = 1,500 18 us; of 60,000, 250 of them, k = 500 16.)
-template <bool AGENT, int TILES>
+template <int TILES>
 __device__ __forceinline__ void flat_zeros(const SelList &ls, Flat<TILES> &f, uint32_t m, const float *__restrict__ keys, uint32_t len,
                                            uint32_t k, const int32_t *__restrict__ map, int32_t *__restrict__ idx,
                                            float *__restrict__ val_sel)
@@ -738,7 +758,7 @@ __device__ __forceinline__ void flat_zeros(const SelList &ls, Flat<TILES> &f, ui
         uint32_t e[1] = {e0};
         uint2 x[1];
         if (m <= Flat<TILES>::kMax) x[0] = make_uint2(f.val[e0], f.pos[e0]);
-        else flat_fetch<AGENT, 1>(ls, f, e, x);
+        else flat_fetch<1>(ls, f, e, x);
         if (x[0].y - e0 < z) {
             ++early;
         } else {
@@ -771,14 +791,14 @@ k_sel_small(const float *__restrict__ keys, int64_t len, SelState *__restrict__ 
     if constexpr (!HISTS)
         for (int b = threadIdx.x; b < kHistBins; b += 1024) hist[b] = 0u;   // every workgroup has read it
     __syncthreads();
-    const uint32_t m = flat_load<true>(ls, f, (int)gridDim.x, (uint32_t)len);
+    const uint32_t m = flat_load(ls, f, (int)gridDim.x, (uint32_t)len);
     uint32_t h1 = 0;
     if constexpr (kAhead) {
         if (m > Flat<TILES>::kMax) h1 = get<true>(hist1 + threadIdx.x);
         hist1[threadIdx.x] = 0u;
     }
     if (prefix == 0u && m < (uint32_t)k) {
-        flat_zeros<true>(ls, f, m, keys, (uint32_t)len, (uint32_t)k, map, idx, val_sel);
+        flat_zeros(ls, f, m, keys, (uint32_t)len, (uint32_t)k, map, idx, val_sel);
         return;
     }
     SelOut out = {map, idx, val_sel, k, len, 0u};

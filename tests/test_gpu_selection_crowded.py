@@ -61,6 +61,27 @@ def test_keys_that_share_the_first_digit(kind, n, k):
         assert np.array_equal(do.cpu().numpy().view(np.uint32), delta.view(np.uint32))
 
 
+# keys are compared as the bits of their magnitudes: a NaN is above infinity, by its payload; where the last workgroup finishes and by launches
+@pytest.mark.parametrize("n,k", [(20_001, 100), (65_537, 2_000), (100_003, 5_000), (300_001, 3_000), (1_300_001, 900)])
+@pytest.mark.parametrize("share", [0.0005, 0.5])
+def test_nan_and_infinite_keys(n, k, share):
+    from paper_2210_07454_amd import sams
+    rng = np.random.default_rng(n + k)
+    bits = rng.standard_normal(n).astype(np.float32).view(np.uint32)
+    bits[rng.random(n) < share] = np.uint32(0x7f800000)
+    bits[rng.random(n) < share] = np.uint32(0x7fc00000)
+    at = np.flatnonzero(rng.random(n) < share)
+    bits[at] = rng.integers(0x7f800001, 0x80000000, len(at)).astype(np.uint32)
+    bits ^= (rng.integers(0, 2, n) << 31).astype(np.uint32)
+    want = np.sort(np.lexsort((np.arange(n), -(bits & 0x7fffffff).astype(np.int64)))[:k])
+    io, do = torch.full((k,), -1, device="cuda", dtype=torch.int32), torch.full((k,), 7.0, device="cuda")
+    ci = torch.arange(n, device="cuda", dtype=torch.int32)
+    vi = torch.from_numpy(bits.view(np.int32)).cuda().view(torch.float32)
+    sams.topk_refine_static(ci, vi, k, io, do)
+    assert np.array_equal(io.cpu().numpy(), want)
+    assert np.array_equal(do.cpu().view(torch.int32).numpy().view(np.uint32), bits[want])
+
+
 # without second moments a narrow table gives few magnitudes to many coordinates; a context's own lists and histograms, selection after selection
 @pytest.mark.parametrize("d,r,c,k", [(60_000, 1, 150, 700), (65_537, 1, 200, 3_000), (131_071, 2, 300, 800), (262_147, 1, 200, 2_000), (400_001, 2, 300, 2_900), (1_000_003, 3, 500, 2_500)])
 def test_estimates_of_few_magnitudes(d, r, c, k):
