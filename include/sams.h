@@ -57,9 +57,9 @@ typedef struct sams_ctx sams_ctx;
  * Allocates the context's device scratch; sams_scratch_bytes reports the total:
  *   always            4d bytes for the estimates, d/8 for the index bitmap, small selection state
  *   c above one LDS window, or d <= 2^22: the sketch plan and its staging buffer, 4*r*d + 4*n*r*d bytes and their padding
- *   128 <= c <= 16384 and d <= 2^26, in their place: lists, 3 to 15 bytes per row and coordinate (24 at most: a hash that needs
- *                     more goes the other way), and above d = 2^22 up to 128 tables of n*r*c floats; where these find no
- *                     room, the context does without them (see "sketch_path")
+ *   128 <= c <= 32768 (16384 for d < 2^18) and d <= 2^26, in their place: lists, 2 to 15 bytes per row and coordinate by the
+ *                     hash (one that needs more than 24 + c/832 goes the other way), and above d = 2^22 up to 128 tables of
+ *                     n*r*c floats; where these find no room, the context does without them (see "sketch_path")
  *   no staging buffer of 6d bytes: that much for the lists of the selection ("sketch_path" 1 too), or, where it is not to be
  *                     had, 6 MiB (every pass of a selection from more than 2^20 keys is then over all of them)
  *   "fuse_head" 2, where it fuses: 4*n*k + d/8 bytes
@@ -133,12 +133,12 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
  *                 1: one gather per (row, coordinate) straight from the table; 2: through the plan whenever there is one
  *   "sketch_path" 0 (default): the order-preserving path whenever c exceeds one LDS window, and
  *                 also for smaller tables while d <= 2^22 (one bin; one workgroup per (worker, row) walks the
- *                 vector); LDS atomics for small tables with larger d.  A table of 128 to 16384 buckets under a vector of
- *                 up to 2^26 coordinates goes another way, by lists and without staging, which keeps the order up to d = 2^22
+ *                 vector); LDS atomics for small tables with larger d.  A table of 128 to 32768 buckets (16384
+ *                 for d below 2^18) under a vector of up to 2^26 coordinates goes another way, by lists and without staging, which keeps the order up to d = 2^22
  *                 (above, the vector may be cut into parts whose sums are added up, always in the same way), unless "tile_log2", "win_log2",
  *                 "chunk_log2", "acc_threads", "stage_rows" or "estimate_path" 2 ask for the binned path, or (unless "pull_lists" is
  *                 set) the shape is one that the other path is faster for (few rows and workers, up to 4096 buckets, d of a million
- *                 or more).  "fuse_head" then has nothing to stage and changes nothing; 1: one global atomic add per term
+ *                 or more; above 16384 buckets, lists so long that they are estimated to take longer).  "fuse_head" then has nothing to stage and changes nothing; 1: one global atomic add per term
  *                 (no plan and no staging); 2: the order-preserving path always; 3: LDS atomics whenever c fits one
  *                 window
  *   "pull_lists"  0 (default), 1, 2 or 4: what a wavefront of the path by lists (see "sketch_path") takes.  0: chosen from the shape and the

@@ -31,10 +31,10 @@
 // Measured on MI355X (us), lists with at most four slices per wavefront, one list per slice, 4- to 16-byte loads of their words and the
 // same number of windows for every row, and this kernel: 25.6 million, n = 4, 5 x 10,000 680 to 1,030 by the hash, now 340 to 530;
 // 12 million, n = 8, 5 x 16,384 757, 500; four million, n = 50, 5 x 12,000 1,290, 840; a million, n = 20, 5 x 12,000 172, 70; six
-// million, n = 8, 4 x 700 142, 84; 431,003, n = 5, 4 x 9,001 37.5, 25; 65,536, n = 4, 5 x 2,048 9.0, 6.8; 60,000, 5 x 400, n = 50 10.8, 10.2;
-// n = 100 20, 19.  The binned path: 98 and 130 us at the last two, 103 at 431,003, 8.5 ms at 25.6 million.
-// Making the lists takes half as long as the plan: 0.13 ms at 65,536, 0.35 at 431,003, 5.7 at 25.6 million; two waits for the stream and
-// the choice of windows on the host are in it.
+// million, n = 8, 4 x 700 142, 84; 431,003, n = 5, 4 x 9,001 37.5, 25 to 29 by the hash; 65,536, n = 4, 5 x 2,048 9.0, 7.6; 60,000, 5 x 400, n = 50
+// 10.8, 10.3; n = 100 20, 18.7.  The binned path: 98 and 130 us at the last two, 103 at 431,003, 8.5 ms at 25.6 million.
+// A context with lists is made in 0.10 ms at 65,536, 0.32 at 431,003, 2.9 at 25.6 million; two waits for the stream and the choice of
+// windows on the host are in it.
 #include <stdlib.h>
 
 #include "sams_ctx.h"
@@ -504,6 +504,10 @@ static int64_t pull_share(const sams_ctx *ctx, PullOrder &po, const double *step
 // 21 million coordinates and 16,400 to 32,700 buckets the lists are the faster at 65, 1.0 to 2.5 times up to 2^22 coordinates (where
 // one of 40 others, 7 x 29,777 and n = 32 under 2.6 million, lost with 1,288 us to 1,005), two to 26 times above, where the others are
 // LDS atomics.
+// Pulling also leaves the head and the recovery without the plan ("fuse_head" has nothing to stage, estimates are gathered).  Whole steps of 30
+// shapes up to 2^22 coordinates with 3 to 16 rows and 2 to 97 workers that pull, by lists and by bins: lists 1.03 to 1.9 times as
+// fast at 28, 24 of them with "fuse_head" 2 (10 x 27,000, n = 8, 2.5 million 570 and 712 us; 10 x 20,000, n = 8, a million 221 and 376), and 1.01 times
+// slower at two of those (10 x 19,102, n = 23, a million 628 and 622; 16 x 32,768, n = 10, four million 1,717 and 1,692).
 static bool pull_declines(const sams_ctx *ctx, int32_t ntile)
 {
     const int64_t pairs = (int64_t)ctx->n * ctx->r;
