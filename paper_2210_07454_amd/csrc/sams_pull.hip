@@ -558,7 +558,7 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
         // 29 and 25; 2,048: 7.1 and 6.8; 400: alike)
         PullOrder po = {};
         int64_t cost = INT64_MAX;
-        double steps = 0;
+        double steps = 0, per_tile[SAMS_MAX_ROWS], all = 0;
         // Two lists of a slice per wavefront save a round of workgroups where a row has 15 to 28 slices (45 x 5 pairs of 1,020 buckets, 77,028
         // coordinates: 16.1 us with one, 11.8 with two, 14.4 with lists of four slices, of which four wavefronts of fourteen have one; 93 x 3
         // of 971, 148,962: 44.5, 29.8, 41.7; 28 x 7 of 1,597, 347,459: 50, 39, 62).  Where lists are one unit, and most of it padding, they
@@ -575,9 +575,10 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
             x.most = many ? kPullMany : form;
             x.group = many ? kPullLoad : (ctx->c <= 1500 ? 4 : 2);
             x.nlist = (nslice + x.per_list - 1) / x.per_list;
-            double per_tile[SAMS_MAX_ROWS], all = 0;
             const int64_t tiles = (ntile + counted - 1) / counted, every = wide ? 1 : sample;
-            for (int j = 0; j < ctx->r; ++j) {
+            const bool count_steps = form != 2 || tun.pull_lists;    // (form 2 has the lists of form 1)
+            if (count_steps) all = 0;
+            for (int j = 0; count_steps && j < ctx->r; ++j) {
                 int64_t units = 0, seen = 0;
                 for (int64_t t = 0; t < tiles; t += every, ++seen)
                     for (int32_t l = 0; l < x.nlist; ++l) units += list_units(x, h_cnt + (j * tiles + t) * nslice, l);
