@@ -138,12 +138,13 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
  *                 (above, the vector may be cut into parts whose sums are added up, always in the same way), unless "tile_log2", "win_log2",
  *                 "chunk_log2", "acc_threads", "stage_rows" or "estimate_path" 2 ask for the binned path, or (unless "pull_lists" is
  *                 set) the shape is one that the other path is faster for (few rows and workers, up to 4096 buckets, d of a million
- *                 or more; above 16384 buckets, lists so long that they are estimated to take longer).  "fuse_head" then has nothing to stage and changes nothing; 1: one global atomic add per term
- *                 (no plan and no staging); 2: the order-preserving path always; 3: LDS atomics whenever c fits one
- *                 window
- *   "pull_lists"  0 (default), 1, 2 or 4: what a wavefront of the path by lists (see "sketch_path") takes.  0: chosen from the shape and the
- *                 lengths of the lists; 1: one list of 64 buckets; 2: one or two such lists; 4: one to four lists of 256 buckets; 1, 2 and
- *                 4 for every shape that lists can be made for.  Same results with each up to d = 2^22
+ *                 or more; above 16384 buckets, lists so long that they are estimated to take longer).  "fuse_head" then has
+ *                 nothing to stage and changes nothing; 1: one global atomic add per term (no plan and no staging); 2: the
+ *                 order-preserving path always; 3: LDS atomics whenever c fits one window
+ *   "pull_lists"  0 (default), 1, 2 or 4: what a wavefront of the path by lists (see "sketch_path") takes.  0: chosen from the shape
+ *                 and the lengths of the lists; 1: one list of 64 buckets; 2: one or two such lists (chosen up to d = 2^22 only);
+ *                 4: one to four lists of 256 buckets; 1, 2 and 4 for every shape that lists can be made for.  Same results with
+ *                 each up to d = 2^22
  * Returns SAMS_EINVAL for an unknown key or a value out of range.
  */
 int sams_configure(const char *key, int value);

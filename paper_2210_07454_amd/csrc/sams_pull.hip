@@ -565,8 +565,10 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
         // take longer than pull_share says: 3.3 million, 3 x 7 pairs of 16,000 buckets 209 us, lists of four slices 184.  Of 314
         // shapes with 50,000 to 4 million coordinates and 400 to 16,000 buckets the choice is the fastest form or within 4 % of it at
         // 285, 8 % at 306 and 37 % at all.
+        // Not where the vector may be cut into parts: two lists per wavefront are fewer parts, of longer sums (error against 64 bits, 2-norm:
+        // 11.4 million, n = 5, 5 x 955 7.0e-7, with one list 6.3e-7; nine million, 7, 5 x 1,459 5.7e-7 and 5.3e-7).
         for (int form : {1, 2, 4}) {
-            if (tun.pull_lists ? tun.pull_lists != form : wide && form < 4) continue;
+            if (tun.pull_lists ? tun.pull_lists != form : (wide && form < 4) || (form == 2 && ctx->d > kOrderedSingleBinMaxD)) continue;
             const bool many = form == 4;
             PullOrder x = {};
             x.ntile = ntile;
