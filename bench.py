@@ -45,6 +45,8 @@ def kernel_algorithmic_bytes(name, d, n, r, c, k, pa=False):
         "k_bin_scatter": 4 * n * d,             # reads u once; the staging it writes is not algorithmic
         "k_bin_accumulate": n * rc4,            # writes every table cell once; the staging it reads is not
         "k_sketch_lds": 4 * n * d + n * rc4,
+        "k_sketch_pull": 4 * n * d + n * rc4,
+        "k_sketch_push": 4 * n * d + n * rc4,
         "k_head_sparse_v": k * (4 * n + 4 + 16),  # idx, g of every worker, v and vhat read and written
         "k_head_pa": 36 * n * d,                # g, m, e, v, vhat read; m, u, v, vhat written
         # the head's own traffic; the staging it also writes is not

@@ -57,6 +57,8 @@ typedef struct sams_ctx sams_ctx;
  * Allocates the context's device scratch; sams_scratch_bytes reports the total:
  *   always            4d bytes for the estimates, d/8 for the index bitmap, small selection state
  *   c above one LDS window, or d <= 2^22: the sketch plan and its staging buffer, 4*r*d + 4*n*r*d bytes and their padding
+ *   10000 < c <= 652800 and 2^18 <= d <= 2^26, where it is the faster: lists, 4.4*r*d bytes (up to 8*r*d), and, in place of the staging
+ *                     buffer, one of 4*r*d bytes or of (4*n + 2)*d bytes for one to r sorted copies of the vectors
  *   128 <= c <= 32768 (16384 for d < 2^18) and d <= 2^26, in their place: lists, 2 to 15 bytes per row and coordinate by the
  *                     hash (one that needs more than 24 + c/832 goes the other way), and above d = 2^22 up to 128 tables of
  *                     n*r*c floats; where these find no room, the context does without them (see "sketch_path")
@@ -139,12 +141,19 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
  *                 "chunk_log2", "acc_threads", "stage_rows" or "estimate_path" 2 ask for the binned path, or (unless "pull_lists" is
  *                 set) the shape is one that the other path is faster for (few rows and workers, up to 4096 buckets, d of a million
  *                 or more; above 16384 buckets, lists so long that they are estimated to take longer).  "fuse_head" then has
- *                 nothing to stage and changes nothing; 1: one global atomic add per term (no plan and no staging); 2: the
+ *                 nothing to stage and changes nothing.  A table of more than 10000 buckets, up to 16 windows of 40800, under a vector of
+ *                 2^18 to 2^26 coordinates goes a third way, in the same order, where that is estimated to be the fastest (see
+ *                 "push_windows"): lists name the values of every (row, window), which are picked out of the vectors or out of sorted
+ *                 copies of them ("fuse_head" 2 then stages those), unless one of the settings above, "stage_interleave", "run_pad",
+ *                 "acc_wide" or "fuse_head" 1 ask for the binned path; 1: one global atomic add per term (no plan and no staging); 2: the
  *                 order-preserving path always; 3: LDS atomics whenever c fits one window
  *   "pull_lists"  0 (default), 1, 2 or 4: what a wavefront of the path by lists (see "sketch_path") takes.  0: chosen from the shape
  *                 and the lengths of the lists; 1: one list of 64 buckets; 2: one or two such lists (chosen up to d = 2^22 only);
  *                 4: one to four lists of 256 buckets; 1, 2 and 4 for every shape that lists can be made for.  Same results with
  *                 each up to d = 2^22
+ *   "push_windows" 0 (default), -1, 1 to 16 or 101 to 116: windows per row of the path that picks its values out of the vectors (1 to 16) or out
+ *                 of sorted copies (101 to 116); 0: whether it is taken, and how, is chosen from the shape and the hash; -1: it is not.  With a
+ *                 number of windows any shape takes it that lists can be made for.  Same results
  * Returns SAMS_EINVAL for an unknown key or a value out of range.
  */
 int sams_configure(const char *key, int value);
@@ -153,7 +162,7 @@ int sams_configure(const char *key, int value);
 int sams_destroy(sams_ctx *ctx);
 
 /* How this context carries out sketch_accumulate: 0 = one global atomic add per term, 1 = row by row in LDS
- * (c fits one window) or by lists for parts of a long vector, 2 = the order-preserving path (binned, or by lists for narrow tables).  -1 for a NULL context. */
+ * (c fits one window) or by lists for parts of a long vector, 2 = the order-preserving path (binned, or by lists).  -1 for a NULL context. */
 int sams_sketch_mode(const sams_ctx *ctx);
 
 /* How the second pass of the binned path reads its metadata in this context (see "acc_wide"): 2 = every row through

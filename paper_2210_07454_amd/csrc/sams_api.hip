@@ -10,7 +10,7 @@
 namespace sams {
 
 int g_last_hip_error = 0;
-Tunables g_tun = {0, 0, 0, 0, 0, 1024, 0, 0, 1, 0, 16, 0, 0, 0, 2};
+Tunables g_tun = {0, 0, 0, 0, 0, 1024, 0, 0, 1, 0, 16, 0, 0, 0, 0, 2};
 static std::mutex g_tun_mutex;      // sams_configure against the copy sams_create takes
 
 static const char *const kKernelNames[KID_COUNT] = {
@@ -18,7 +18,7 @@ static const char *const kKernelNames[KID_COUNT] = {
     "k_estimate", "k_sel_hist", "k_sel_filter", "k_sel_count", "k_sel_write",
     "k_gather", "k_plan_build", "k_bin_scatter", "k_bin_accumulate", "k_sketch_lds", "k_bin_lookup",
     "k_bin_collect", "k_est_median", "k_head_scatter", "k_head_pa", "k_head_sparse_v", "k_sel_small",
-    "k_sketch_pull", "k_pull_sum"};
+    "k_sketch_pull", "k_pull_sum", "k_sketch_push"};
 
 const char *kernel_name(int kid) { return (kid >= 0 && kid < KID_COUNT) ? kKernelNames[kid] : ""; }
 
@@ -154,9 +154,16 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
     int rc = static_scratch_ptr(&static_scratch);                    // resolved here so that topk_refine_static never has to
     if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, ctx->bitmap, words, 0u);
     if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, ctx->sel, kSelClearWords, 0u);
-    bool pulls = false;
-    if (rc == SAMS_OK) rc = pull_create(ctx, ctx->tun, &pulls);
-    if (rc == SAMS_OK && !pulls && ctx->tun.sketch_path != 1) rc = plan_create(ctx, ctx->tun);
+    bool pushes = false, pulls = false;
+    if (rc == SAMS_OK && ctx->c <= kPullMaxC) rc = push_create(ctx, ctx->tun, true, &pushes);
+    if (rc == SAMS_OK && !pushes) rc = pull_create(ctx, ctx->tun, &pulls);
+    if (rc == SAMS_OK && !pushes && !pulls) rc = push_create(ctx, ctx->tun, false, &pushes);
+    if (rc == SAMS_OK && !pulls && ctx->tun.sketch_path != 1 && (!pushes || (ctx->c > kPlanMinRecoveryC && estimate_wants_plan(ctx))))
+        rc = plan_create(ctx, ctx->tun);
+    if (rc == SAMS_OK && pushes) {
+        ctx->plan.mode = PLAN_BINNED;                                // to the caller: the order is the coordinates'
+        rc = plan_staging_alone(ctx);
+    }
     if (rc == SAMS_OK) rc = estimate_prepare(ctx);
     if (rc == SAMS_OK && ctx->tun.fuse_head == 2 && head_can_fuse(ctx, false)) {   // the per-worker fused head compacts g on I_{t-1}
         struct { void **p; int64_t bytes; } extra[] = {{(void **)&ctx->wordrank, words * 4}, {(void **)&ctx->gsel, (int64_t)n * k * 4}};
@@ -206,6 +213,7 @@ int sams_destroy(sams_ctx *ctx)
         if (p) (void)hipFree(p);
     plan_destroy(ctx);
     pull_destroy(ctx);
+    push_destroy(ctx);
     if (ctx->prof) {
         for (int s = 0; s < kProfPool; ++s) {
             if (ctx->prof[s].a) (void)hipEventDestroy(ctx->prof[s].a);
@@ -260,6 +268,9 @@ int sams_configure(const char *key, int value)
     } else if (!strcmp(key, "pull_lists")) {
         if (value != 0 && value != 1 && value != 2 && value != 4) return SAMS_EINVAL;
         g_tun.pull_lists = value;
+    } else if (!strcmp(key, "push_windows")) {
+        if (value < -1 || value > 116 || (value > 16 && value < 101)) return SAMS_EINVAL;
+        g_tun.push_windows = value;
     } else if (!strcmp(key, "acc_wide")) {
         if (value < 0 || value > 2) return SAMS_EINVAL;
         g_tun.acc_wide = value;
@@ -275,7 +286,7 @@ int sams_configure(const char *key, int value)
 int sams_sketch_mode(const sams_ctx *ctx) { return ctx ? ctx->plan.mode : -1; }
 
 // (a context that pulls has PLAN_BINNED or PLAN_LDS_ROW for the order of its additions, and no plan)
-static bool uses_plan(const sams_ctx *ctx) { return ctx && ctx->plan.mode == PLAN_BINNED && !ctx->pull.kernel; }
+static bool uses_plan(const sams_ctx *ctx) { return ctx && ctx->plan.mode == PLAN_BINNED && !ctx->pull.kernel && !ctx->push.words; }
 
 int sams_accumulate_variant(const sams_ctx *ctx) { return uses_plan(ctx) ? ctx->plan.acc_variant : -1; }
 

@@ -27,6 +27,8 @@ extern int g_last_hip_error;
     } while (0)
 
 constexpr int kWave = 64;
+constexpr int64_t kPullMaxC = 1 << 15;             // buckets up to which a context may pull
+constexpr int64_t kPlanMinRecoveryC = 1 << 15;   // buckets above which a context that pushes recovers through a plan
 constexpr int64_t kOrderedSingleBinMaxD = (int64_t)1 << 22;     // largest d sketched in order when c fits one window
 constexpr int kHistBins = 2048;     // first radix digit of the selection: 11 bits, then 10 and 10 (kHistBins / 2 bins)
 constexpr int kSelTileLog2 = 12;    // keys per tile of the filters: 1024 threads, 4 each
@@ -49,7 +51,7 @@ enum KernelId {
     KID_FILL = 0, KID_HASH_DUMP, KID_TAIL, KID_TAIL_ZERO_E, KID_HEAD, KID_SKETCH_ATOMIC, KID_REDUCE,
     KID_ESTIMATE, KID_SEL_HIST, KID_SEL_FILTER, KID_SEL_COUNT, KID_SEL_WRITE,
     KID_GATHER, KID_PLAN_BUILD, KID_BIN_SCATTER, KID_BIN_ACCUMULATE, KID_SKETCH_LDS, KID_BIN_LOOKUP,
-    KID_BIN_COLLECT, KID_EST_MEDIAN, KID_HEAD_SCATTER, KID_HEAD_PA, KID_HEAD_SPARSE_V, KID_SEL_SMALL, KID_SKETCH_PULL, KID_PULL_SUM, KID_COUNT
+    KID_BIN_COLLECT, KID_EST_MEDIAN, KID_HEAD_SCATTER, KID_HEAD_PA, KID_HEAD_SPARSE_V, KID_SEL_SMALL, KID_SKETCH_PULL, KID_PULL_SUM, KID_SKETCH_PUSH, KID_COUNT
 };
 const char *kernel_name(int kid);
 
@@ -73,6 +75,8 @@ struct Plan {
     uint32_t rec_mask;  // bit j set: row j reads chunk records in pass 2 (k_bin_accumulate_r)
     int win_log2, tile_log2, chunk_log2, acc_threads, run_pad, grp_log2, rows, stage_rows, stage_ilv, acc_wide;
     int64_t nbins, ntile, dpad, rowlen;
+    int64_t stg_words;  // floats of the staging buffer
+    int64_t stg_rows;   // rows of rowlen floats that the staging holds: n * stage_rows, or r where only the recovery goes through the plan
     uint16_t *srcp;     // [r][rowlen]      slot -> coordinate inside its tile (bits 0-14) and sign (bit 15), or padding
     uint32_t *dst16;    // [r][rowlen >> grp_log2]  stream position of each group of 2^grp_log2 slots (16, or the run padding if smaller)
     uint32_t *pbase;    // [r][ntile+1]     first slot of each tile
@@ -105,6 +109,19 @@ struct PullPlan {
     int64_t list_bytes, first_bytes;
 };
 
+// the lists of words of the path that picks its values out of the vector (see sams_push.hip); words == null: this context does not take it
+struct PushPlan {
+    int32_t nwin, win;            // windows of a row, buckets of a window
+    int32_t span, nph, nalloc;    // coordinates of a phase, phases, phases that a list has room for
+    uint32_t *words;              // [r * nwin][nalloc][2048]
+    int32_t ncopy;                // sorted copies of the vectors that the values are picked from (0: the vectors themselves)
+    int8_t copy_of[SAMS_MAX_ROWS], row[SAMS_MAX_ROWS];     // a row's copy; the order in which the rows are worked on
+    const void *kernel;
+    uint16_t *order;              // [ncopy][nph][span]  the coordinate, in its phase, that lies in a place of a copy
+    int64_t copy_words;           // floats of the copies, in the plan's staging buffer
+    int64_t word_bytes, order_bytes;
+};
+
 // tunables: sams_configure edits the process-wide set, sams_create copies it into the context, and every
 // later call on that context reads only its own copy
 struct Tunables {
@@ -122,6 +139,8 @@ struct Tunables {
     int stage_interleave; // 1 = the workers' staged copies are interleaved in pieces of 32 stream positions
     int stage_spread;     // 1 = a staging buffer of 2 GiB or more is mapped from 1 GiB chunks picked at even distances over all free device memory
     int pull_lists;       // lists of the pulling path: 0 = chosen; 1 = one of a slice per wavefront, 2 = up to two, 4 = up to four of four slices
+    int push_windows;     // windows of a row of the path that picks its values out of the vectors (sams_push.hip): 0 = chosen, -1 = not that path,
+                          // 1 to 16 = so many, 101 to 116 = so many, out of sorted copies
     int acc_wide;         // accumulate kernel where its shape allows (1024 threads, 2048-position chunks): 1 = 16-byte loads,
                           // 2 = 16-byte loads and compact chunk records instead of meta words (falls back to 1 when a chunk has too many chains)
 };
@@ -174,6 +193,7 @@ struct sams_ctx {
     int64_t scratch_bytes;
     sams::Plan plan;
     sams::PullPlan pull;
+    sams::PushPlan push;
     sams::Tunables tun;      // the tunables as they were when the context was created
     // per-kernel timing (host)
     int prof_on;
@@ -367,9 +387,17 @@ int enqueue_sketch(sams_ctx *ctx, const float *u, float *S_workers);
 int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done);
 void pull_destroy(sams_ctx *ctx);
 int enqueue_sketch_pull(sams_ctx *ctx, const float *u, float *S_workers);
+// sams_push.hip
+// first: whether one window, and the vectors themselves, are so much the fastest that no other path need be looked at
+int push_create(sams_ctx *ctx, const Tunables &tun, bool first, bool *done);
+void push_destroy(sams_ctx *ctx);
+int enqueue_sketch_push(sams_ctx *ctx, const float *u, float *S_workers);
 // sams_plan.hip
 int plan_create(sams_ctx *ctx, const Tunables &tun);
 void plan_destroy(sams_ctx *ctx);
+int copies_create();                                // the sorted copies of the path in sams_push.hip
+int enqueue_sort_copies(sams_ctx *ctx, const float *u);
+int plan_staging_alone(sams_ctx *ctx);              // the staging buffer, where there are copies but no plan
 int64_t plan_staging_words(const sams_ctx *ctx);     // size of the staging buffer in floats, 0 without one
 int enqueue_sketch_planned(sams_ctx *ctx, const float *u, float *S_workers);
 int enqueue_row_estimates_planned(sams_ctx *ctx, const float *S_mean, float *rowest);
@@ -386,6 +414,8 @@ int enqueue_head_scatter(sams_ctx *ctx, const float *g, float *m, float *e_u, fl
 // sams_select.hip
 // whether the kernel that takes the first digit's histogram over len keys also picks the digit (the filter does otherwise)
 bool sel_hist_picks(int64_t len);
+// whether stage 3 goes through the plan where there is one
+bool estimate_wants_plan(const sams_ctx *ctx);
 // at creation, once it is known whether there is a plan: what the kernels of enqueue_estimate need set
 int estimate_prepare(const sams_ctx *ctx);
 // sc != null: a selection of ctx->k from est follows with this scratch; *hist_done tells whether the estimate kernel has

@@ -277,7 +277,7 @@ k_plan_place(HashParams hp, int pad, int gl, int tile_log2, int win_log2, int64_
             if (s < len) {
                 sv = sj[a + s];
                 uint32_t wl = bucket_of(hp, j, (uint32_t)(l0 + (sv & 0x7fffu))) & wmask;
-                meta[(int64_t)j * rowlen + start + s] = wl;
+                if (meta) meta[(int64_t)j * rowlen + start + s] = wl;
                 wlow[(int64_t)j * rowlen + start + s] = (uint16_t)wl;
             }
             srcp[(int64_t)j * rowlen + po + s] = sv;
@@ -434,6 +434,31 @@ __device__ __forceinline__ void tile_and_worker(int64_t per, int32_t n, int32_t 
     *tile = (int64_t)(blockIdx.x % kNumXcd) + kNumXcd * (int64_t)(first + (in - w * size));
 }
 
+// Worker i's tile of u, coordinates [l0, l0 + L), to LDS; returns where coordinate l0 is.  The tile starts up to three floats past a 16-byte boundary (when
+// d is no multiple of 4) and is read from that boundary on; the values around it belong to its neighbours.
+template <bool STREAM>
+__device__ __forceinline__ const float *load_tile(const float *__restrict__ u, float *tilebuf, int32_t n, int32_t i, int64_t l0, int L, int64_t d)
+{
+    const int64_t flat = (int64_t)i * d + l0;
+    const int mis = (int)(flat & 3);
+    const float *src = u + (flat - mis);
+    const int64_t lim = (int64_t)n * d - (flat - mis);               // floats of u from src on
+    const int top = (int)(L < d - l0 ? L : d - l0) + mis;
+    for (int p = threadIdx.x * 4; p < top; p += blockDim.x * 4) {
+        float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (p + 4 <= lim) {
+            const float4 *at = reinterpret_cast<const float4 *>(src + p);
+            q = STREAM ? load_stream(at) : *at;
+        } else {                                                     // the last, partial group of u
+            q.x = src[p];
+            if (p + 1 < lim) q.y = src[p + 1];
+            if (p + 2 < lim) q.z = src[p + 2];
+        }
+        *reinterpret_cast<float4 *>(tilebuf + p) = q;
+    }
+    return tilebuf + mis;
+}
+
 // A thread owns 4 consecutive slots (always inside
 // one group of G >= 4 slots, hence one run): one 8-byte load of their sources, one 4-byte load of the group's
 // stream position, 4 LDS reads and one 16-byte store -- nothing depends on another global load.
@@ -453,27 +478,7 @@ k_bin_scatter(const float *__restrict__ u, const uint16_t *__restrict__ srcp, co
     if (tile >= ntile) return;
     const int64_t l0 = tile << tile_log2;
     {
-        // The worker's tile starts `mis` floats past a 16-byte boundary (not 0 when d is no multiple of 4): it is read from
-        // that boundary on, coordinate l0 + p to tile0[p].  The values around it belong to the tile's or the worker's
-        // neighbours; no slot names them.
-        const int64_t flat = (int64_t)i * d + l0;
-        const int mis = (int)(flat & 3);
-        const float *src = u + (flat - mis);
-        const int64_t lim = (int64_t)n * d - (flat - mis);           // floats of u from src on
-        const float *tile0 = tilebuf + mis;
-        const int top = (int)(L < d - l0 ? L : d - l0) + mis;
-        for (int p = threadIdx.x * 4; p < top; p += blockDim.x * 4) {
-            float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (p + 4 <= lim) {
-                const float4 *at = reinterpret_cast<const float4 *>(src + p);
-                q = STREAM ? load_stream(at) : *at;
-            } else {                                                 // the last, partial group of u
-                q.x = src[p];
-                if (p + 1 < lim) q.y = src[p + 1];
-                if (p + 2 < lim) q.z = src[p + 2];
-            }
-            *reinterpret_cast<float4 *>(tilebuf + p) = q;
-        }
+        const float *tile0 = load_tile<STREAM>(u, tilebuf, n, i, l0, L, d);   // no slot names the values around the tile
         __syncthreads();
         for (int32_t j = rg.j0; j < rg.j0 + rg.rj; ++j) {
             const uint32_t o0 = pbase[(int64_t)j * (ntile + 1) + tile], o1 = pbase[(int64_t)j * (ntile + 1) + tile + 1];
@@ -646,19 +651,8 @@ k_head_scatter(HeadArgs ha, const uint16_t *__restrict__ srcp, const uint32_t *_
 // VEC: 4 = 16-byte accesses (d a multiple of 4); 1 = 4-byte accesses, a thread's coordinates kFusedThreads apart (the workers'
 // vectors start at any alignment then), for Alg. 2 alone and long vectors (head_can_fuse).
 template <bool PA, int VEC>
-__global__ void __launch_bounds__(kFusedThreads)
-k_head_scatter_w(HeadArgs ha, const uint16_t *__restrict__ srcp, const uint32_t *__restrict__ dst16,
-                 const uint32_t *__restrict__ pbase, float *__restrict__ stg, int32_t n, RowGroup rg, int64_t d,
-                 int tile_log2, int64_t ntile, int64_t rowlen, int gl, int32_t group)
+__device__ __forceinline__ void head_tile(const HeadArgs &ha, float *tilebuf, int32_t i, int64_t l0, int L, int64_t d)
 {
-    extern __shared__ float tilebuf[];
-    const int L = 1 << tile_log2;
-    const int64_t per = (ntile + kNumXcd - 1) / kNumXcd;
-    int64_t tile;
-    int32_t i;
-    tile_and_worker(per, n, group, &tile, &i);
-    if (tile >= ntile) return;
-    const int64_t l0 = tile << tile_log2;
     const int64_t wbase = (int64_t)i * d + l0;
     if constexpr (VEC == 4) {
         float4 gkeep[kFusedIters];                                       // g and the bitmap word of the positions with a
@@ -800,6 +794,23 @@ k_head_scatter_w(HeadArgs ha, const uint16_t *__restrict__ srcp, const uint32_t 
                 }
         }
     }
+}
+
+template <bool PA, int VEC>
+__global__ void __launch_bounds__(kFusedThreads)
+k_head_scatter_w(HeadArgs ha, const uint16_t *__restrict__ srcp, const uint32_t *__restrict__ dst16,
+                 const uint32_t *__restrict__ pbase, float *__restrict__ stg, int32_t n, RowGroup rg, int64_t d,
+                 int tile_log2, int64_t ntile, int64_t rowlen, int gl, int32_t group)
+{
+    extern __shared__ float tilebuf[];
+    const int L = 1 << tile_log2;
+    const int64_t per = (ntile + kNumXcd - 1) / kNumXcd;
+    int64_t tile;
+    int32_t i;
+    tile_and_worker(per, n, group, &tile, &i);
+    if (tile >= ntile) return;
+    const int64_t l0 = tile << tile_log2;
+    head_tile<PA, VEC>(ha, tilebuf, i, l0, L, d);
     __syncthreads();
     for (int32_t j = rg.j0; j < rg.j0 + rg.rj; ++j) {
         const uint32_t o0 = pbase[(int64_t)j * (ntile + 1) + tile], o1 = pbase[(int64_t)j * (ntile + 1) + tile + 1];
@@ -818,6 +829,64 @@ k_head_scatter_w(HeadArgs ha, const uint16_t *__restrict__ srcp, const uint32_t 
             store_stream(reinterpret_cast<float4 *>(oj + at), v);
         }
     }
+}
+
+// Pass 1 of the path that picks its values out of sorted copies (sams_push.hip): per (tile, worker), the tile as it is to every copy, in that copy's order.
+// The copies are written from end to end, tile after tile; a thread owns 4 consecutive places.
+struct CopyArgs {
+    const uint16_t *order;            // [ncopy][ntile][L]  the coordinate that lies in a place
+    float *copies;                    // [ncopy][n][ntile][L]
+    int64_t ntile;
+    int32_t L, ncopy, n, group;
+};
+__device__ __forceinline__ void write_copies(const CopyArgs &ca, const float *tile0, int64_t tile, int32_t i)
+{
+    for (int32_t q = 0; q < ca.ncopy; ++q) {
+        const uint16_t *from = ca.order + (q * ca.ntile + tile) * ca.L;
+        float *to = ca.copies + (((int64_t)q * ca.n + i) * ca.ntile + tile) * ca.L;
+        uint2 packed[kFusedIters];
+#pragma unroll
+        for (int z = 0; z < kFusedIters; ++z) {
+            const int o = (z * kFusedThreads + (int)threadIdx.x) * 4;
+            packed[z] = *reinterpret_cast<const uint2 *>(from + (o < ca.L ? o : 0));
+        }
+#pragma unroll
+        for (int z = 0; z < kFusedIters; ++z) {
+            const int o = (z * kFusedThreads + (int)threadIdx.x) * 4;
+            if (o < ca.L)
+                store_stream(reinterpret_cast<float4 *>(to + o), make_float4(tile0[packed[z].x & 0xffffu], tile0[packed[z].x >> 16],
+                                                                              tile0[packed[z].y & 0xffffu], tile0[packed[z].y >> 16]));
+        }
+    }
+}
+
+template <bool STREAM>
+__global__ void __launch_bounds__(kFusedThreads)
+k_sort_copies(const float *__restrict__ u, CopyArgs ca, int64_t d)
+{
+    extern __shared__ float tilebuf[];
+    int64_t tile;
+    int32_t i;
+    tile_and_worker((ca.ntile + kNumXcd - 1) / kNumXcd, ca.n, ca.group, &tile, &i);
+    if (tile >= ca.ntile) return;
+    const float *tile0 = load_tile<STREAM>(u, tilebuf, ca.n, i, tile * ca.L, ca.L, d);
+    __syncthreads();
+    write_copies(ca, tile0, tile, i);
+}
+
+// fused with the head, like k_head_scatter_w
+template <bool PA, int VEC>
+__global__ void __launch_bounds__(kFusedThreads)
+k_head_copies(HeadArgs ha, CopyArgs ca, int64_t d)
+{
+    extern __shared__ float tilebuf[];
+    int64_t tile;
+    int32_t i;
+    tile_and_worker((ca.ntile + kNumXcd - 1) / kNumXcd, ca.n, ca.group, &tile, &i);
+    if (tile >= ca.ntile) return;
+    head_tile<PA, VEC>(ha, tilebuf, i, tile * ca.L, ca.L, d);
+    __syncthreads();
+    write_copies(ca, tilebuf, tile, i);
 }
 
 // v and vhat on I_{t-1} after k_head_scatter_w has decayed them: h = mean over the workers of g (summed in
@@ -1489,7 +1558,7 @@ int enqueue_row_estimates_planned(sams_ctx *ctx, const float *S_mean, float *row
     const int64_t L = (int64_t)1 << pl.tile_log2, W = (int64_t)1 << pl.win_log2;
     float *lk = pl.stg;                                              // the staging buffer is idle between two sketches
     pl.staged_u = nullptr;                                           // ... and whatever vector it held is overwritten
-    const int64_t cap = (int64_t)ctx->n * pl.stage_rows;             // rows of looked-up values it can hold
+    const int64_t cap = pl.stg_rows;                                 // rows of looked-up values it can hold
     for (int32_t j0 = 0; j0 < ctx->r; j0 += (int32_t)cap) {
         const int32_t rj = (ctx->r - j0) < cap ? (ctx->r - j0) : (int32_t)cap;
         {
@@ -1719,6 +1788,7 @@ static int dispatch_acc(sams_ctx *ctx, float *S_workers, RowGroup rg, bool set_a
 int plan_create(sams_ctx *ctx, const Tunables &tun)
 {
     Plan &pl = ctx->plan;
+    const bool recovery = ctx->push.words != nullptr;                // stage 1 does without the plan
     pl.win_log2 = tun.win_log2;
     pl.tile_log2 = tun.tile_log2;
     if (pl.tile_log2 == 0) {
@@ -1862,14 +1932,14 @@ int plan_create(sams_ctx *ctx, const Tunables &tun)
         if (rc != SAMS_OK) break;
         rc = dev_alloc(ctx, (void **)&pl.srcp, r * rowlen * 2);
         if (rc == SAMS_OK) rc = dev_alloc(ctx, (void **)&pl.dst16, r * (rowlen >> pl.grp_log2) * 4);
-        if (rc == SAMS_OK) rc = dev_alloc(ctx, (void **)&pl.meta, r * rowlen * 4);
+        if (rc == SAMS_OK && !recovery) rc = dev_alloc(ctx, (void **)&pl.meta, r * rowlen * 4);
         if (rc == SAMS_OK) rc = dev_alloc(ctx, (void **)&pl.wlow, r * rowlen * 2);
         if (rc != SAMS_OK) break;
         e = hipMemcpyAsync(pl.binbase, h_base, (size_t)(r * (NB + 1) * 4), hipMemcpyHostToDevice, ctx->stream);
         if (e == hipSuccess)
             e = hipMemcpyAsync(pl.pbase, h_tile, (size_t)(r * (pl.ntile + 1) * 4), hipMemcpyHostToDevice, ctx->stream);
         if (e != hipSuccess) { g_last_hip_error = (int)e; rc = SAMS_EHIP; break; }
-        rc = enqueue_fill_u32(ctx, pl.meta, r * rowlen, kMetaNotFirst | kMetaPad);
+        if (!recovery) rc = enqueue_fill_u32(ctx, pl.meta, r * rowlen, kMetaNotFirst | kMetaPad);
         if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, reinterpret_cast<uint32_t *>(pl.wlow), r * rowlen / 2, 0u);   // padding: bucket 0
         if (rc != SAMS_OK) break;
         {
@@ -1888,7 +1958,7 @@ int plan_create(sams_ctx *ctx, const Tunables &tun)
         // which accumulate kernel: the generic one, the one with 16-byte loads, or the one reading chunk records
         pl.acc_variant = (wide_shape && pl.acc_wide >= 1) ? 1 : 0;
         pl.rec_mask = 0;
-        if (wide_shape && pl.acc_wide >= 2) {
+        if (wide_shape && pl.acc_wide >= 2 && !recovery) {
             uint32_t *over = nullptr, h_over[SAMS_MAX_ROWS] = {0};
             if (hipMalloc((void **)&over, SAMS_MAX_ROWS * 4) != hipSuccess) { (void)hipGetLastError(); rc = SAMS_ENOMEM; break; }
             rc = dev_alloc(ctx, (void **)&pl.rec, r * (rowlen / kRecChunk) * kRecWords * 4);
@@ -1918,7 +1988,7 @@ int plan_create(sams_ctx *ctx, const Tunables &tun)
                 ctx->scratch_bytes -= r * (rowlen / kRecChunk) * kRecWords * 4;
             }
         }
-        if (pl.acc_variant != 2) {                                   // the kernels that read meta words need the chains
+        if (pl.acc_variant != 2 && !recovery) {                      // the kernels that read meta words need the chains
             ProfScope ps(ctx, KID_PLAN_BUILD);
             hipLaunchKernelGGL(k_plan_chain, dim3((unsigned)(rowlen / CH), (unsigned)r),
                                dim3(CH < kPlanThreads ? (unsigned)CH : kPlanThreads), (size_t)(CH * 4), ctx->stream,
@@ -1927,12 +1997,14 @@ int plan_create(sams_ctx *ctx, const Tunables &tun)
             if (e == hipSuccess) e = hipGetLastError();
             if (e != hipSuccess) { g_last_hip_error = (int)e; rc = SAMS_EHIP; break; }
         }
-        const int64_t stg_bytes = n * pl.stage_rows * rowlen * 4;
+        pl.stg_rows = recovery ? r : n * pl.stage_rows;
+        pl.stg_words = pl.stg_rows * rowlen > ctx->push.copy_words ? pl.stg_rows * rowlen : ctx->push.copy_words;
+        const int64_t stg_bytes = pl.stg_words * 4;
         rc = (tun.stage_spread && stg_bytes >= ((int64_t)2 << 30)) ? spread_alloc(ctx, stg_bytes) : SAMS_ENOMEM;
         if (rc != SAMS_OK) rc = dev_alloc(ctx, (void **)&pl.stg, stg_bytes);
         // the median is fused when a thread can hold the row estimates of its coordinates and the staging
         // buffer can hold the looked-up values of all r rows; otherwise they go through rowest
-        pl.fused_median = tun.fuse_median && fused_median_iters(ctx->r, pl.tile_log2) > 0 && n * pl.stage_rows >= r &&
+        pl.fused_median = tun.fuse_median && fused_median_iters(ctx->r, pl.tile_log2) > 0 && pl.stg_rows >= r &&
                           !((ctx->d & 3) != 0 && collect_apart(ctx->r, pl.tile_log2, pl.ntile));
         if (rc == SAMS_OK && !pl.fused_median) rc = dev_alloc(ctx, (void **)&pl.rowest, r * ctx->d * 4);
         if (rc != SAMS_OK) break;
@@ -1958,9 +2030,17 @@ void plan_destroy(sams_ctx *ctx)
     pl.stg = pl.rowest = nullptr;
 }
 
+int plan_staging_alone(sams_ctx *ctx)
+{
+    Plan &pl = ctx->plan;
+    if (!ctx->push.ncopy || pl.stg) return SAMS_OK;
+    pl.stg_words = ctx->push.copy_words;
+    return dev_alloc(ctx, (void **)&pl.stg, pl.stg_words * 4);
+}
+
 int64_t plan_staging_words(const sams_ctx *ctx)
 {
-    return ctx->plan.stg ? (int64_t)ctx->n * ctx->plan.stage_rows * ctx->plan.rowlen : 0;
+    return ctx->plan.stg ? ctx->plan.stg_words : 0;
 }
 
 static int64_t plan_metadata_bytes(const Plan &pl) { return (pl.rowlen * 2 + (pl.rowlen >> pl.grp_log2) * 4) * pl.rows; }
@@ -1992,6 +2072,33 @@ static bool scatter_streams(const sams_ctx *ctx)
     return (int64_t)ctx->n * ctx->d * 4 > ((int64_t)96 << 20) || plan_metadata_bytes(ctx->plan) > ((int64_t)12 << 20);
 }
 
+// the sorted copies lie in the staging buffer; tiles of an XCD are taken in groups as in pass 1 (scatter_group)
+static CopyArgs copy_args(const sams_ctx *ctx)
+{
+    const PushPlan &pp = ctx->push;
+    const int64_t per_tile = (int64_t)pp.span * 2 * pp.ncopy, want = 3000000 / per_tile;
+    return CopyArgs{pp.order, ctx->plan.stg, pp.nph, pp.span, pp.ncopy, ctx->n, (int32_t)(want < 1 ? 1 : (want > 16 ? 16 : want))};
+}
+static dim3 copy_grid(const CopyArgs &ca) { return dim3((unsigned)((ca.ntile + kNumXcd - 1) / kNumXcd * kNumXcd * ca.n)); }
+
+int copies_create()
+{
+    const void *kernels[] = {(const void *)k_sort_copies<true>, (const void *)k_sort_copies<false>, (const void *)k_head_copies<true, 4>,
+                             (const void *)k_head_copies<false, 4>, (const void *)k_head_copies<false, 1>};
+    for (const void *k : kernels) SAMS_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes));
+    return SAMS_OK;
+}
+
+int enqueue_sort_copies(sams_ctx *ctx, const float *u)
+{
+    const CopyArgs ca = copy_args(ctx);
+    const bool stream = (int64_t)ctx->n * ctx->d * 4 > ((int64_t)96 << 20);
+    ProfScope ps(ctx, KID_BIN_SCATTER);
+    hipLaunchKernelGGL((stream ? k_sort_copies<true> : k_sort_copies<false>), copy_grid(ca), dim3(kFusedThreads), (size_t)ca.L * 4 + 16, ctx->stream, u, ca, ctx->d);
+    SAMS_HIP(hipGetLastError());
+    return SAMS_OK;
+}
+
 bool head_compacts_g(const sams_ctx *ctx) { return ctx->wordrank != nullptr && ctx->gsel != nullptr; }
 
 // Where d is no multiple of four the workgroup per (tile, worker) has 4-byte accesses to pay for the copy of u that it saves.
@@ -2002,7 +2109,7 @@ bool head_compacts_g(const sams_ctx *ctx) { return ctx->wordrank != nullptr && c
 constexpr int64_t kFuseOddMinD = (int64_t)1 << 24;
 bool head_can_fuse(const sams_ctx *ctx, bool pa)
 {
-    if (!ctx->tun.fuse_head || ctx->plan.mode != PLAN_BINNED || ctx->pull.kernel) return false;
+    if (!ctx->tun.fuse_head || ctx->plan.mode != PLAN_BINNED || ctx->pull.kernel || (ctx->push.words && !ctx->push.ncopy)) return false;
     return (ctx->d & 3) == 0 || (ctx->tun.fuse_head == 2 && !pa && ctx->d >= kFuseOddMinD);
 }
 
@@ -2018,6 +2125,11 @@ int enqueue_head_scatter(sams_ctx *ctx, const float *g, float *m, float *e_u, fl
     {
         ProfScope ps(ctx, KID_HEAD_SCATTER);
         const dim3 grid((unsigned)(per * kNumXcd));
+        if (ctx->push.ncopy) {
+            const CopyArgs ca = copy_args(ctx);
+            const auto kernel = pa ? k_head_copies<true, 4> : ((ctx->d & 3) == 0 ? k_head_copies<false, 4> : k_head_copies<false, 1>);
+            hipLaunchKernelGGL(kernel, copy_grid(ca), dim3(kFusedThreads), (size_t)ca.L * 4, ctx->stream, ha, ca, ctx->d);
+        } else {
         const RowGroup rg = {0, pl.stage_rows, pl.stage_rows, ctx->r, pl.stage_ilv};
         if (ctx->tun.fuse_head == 2) {                                  // one workgroup per (tile, worker)
             const dim3 wgrid((unsigned)(per * kNumXcd * ctx->n));
@@ -2033,6 +2145,7 @@ int enqueue_head_scatter(sams_ctx *ctx, const float *g, float *m, float *e_u, fl
             hipLaunchKernelGGL(k_head_scatter<false>, grid, dim3(kFusedThreads), (size_t)(L * 4), ctx->stream, ha,
                                pl.srcp, pl.dst16, pl.pbase, pl.stg, ctx->n, rg, ctx->d, pl.tile_log2, pl.ntile,
                                pl.rowlen, pl.grp_log2);
+        }
     }
     if (compact) {
         if (ctx->n >= kWideMinWorkers)

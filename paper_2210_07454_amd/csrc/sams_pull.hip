@@ -419,7 +419,7 @@ k_pull_sum(const float *__restrict__ part, float *__restrict__ S, int64_t cells,
 // tile's 64 buckets are padding but for a tenth (13,308 coordinates and a step or two for each of 512 slices), and their making would
 // not fit in LDS; the lists of longer vectors take gigabytes.
 constexpr int64_t kPullLongD = 1000000;       // shorter vectors always pull: both paths are launches and latencies
-constexpr int64_t kPullWide = 1 << 14, kPullMaxC = 1 << 15, kPullWideMinD = 1 << 18;
+constexpr int64_t kPullWide = 1 << 14, kPullWideMinD = 1 << 18;
 static bool pull_shape(const sams_ctx *ctx, const Tunables &tun)
 {
     if (tun.sketch_path != 0 || tun.estimate_path == 2 || tun.win_log2 || tun.tile_log2 || tun.chunk_log2 || tun.acc_threads ||

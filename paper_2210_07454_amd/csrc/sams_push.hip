@@ -1,0 +1,636 @@
+// Order-preserving Count Sketch accumulation (stage 1 of sams.h; Sec. II-C update rule) for tables of a few LDS windows, without a staged copy per row.
+//
+// The binned path (sams_plan.hip) writes every signed value, once per row, to where its bucket's window will read it, and reads it back.  Where a row is only
+// a few windows wide, a workgroup can as well pick its values out of the worker's vector itself: it has one worker, one row and one window of up to 40,800
+// buckets in LDS, walks the vector in phases of `span` coordinates, and adds the ones that fall into its window.  Which those are is worked out once, at
+// context creation: a list of words per (row, window), shared by the workers, each word with a coordinate's place in its phase, its sign and the cell of its
+// bucket.
+//
+// A phase has at most kPushEntries words, kPushGroups groups of 64 (a word per lane) for each of 16 wavefronts; a lane reads its words, fetches the values
+// they name from memory, and adds each to its cell with a plain read-modify-write.  Wavefronts meet at one barrier per phase, and within a phase all
+// coordinates of a bucket are adjacent lanes of one group, in order: the first of them adds up what the others have.  So a bucket's terms are added in
+// coordinate order, bit for bit like a sequential loop; no atomics, every cell is written once.
+//
+// Out of the vectors themselves a group of 64 neighbouring coordinates of one of w windows touches 2 w lines, and that is what bounds it: a compute unit's L1
+// takes about two clocks for 16 lanes and a line, and the lines of all windows' workgroups come through it.  With more than a window or two (and where vectors
+// and lists do not fit the 256 MB cache together: 490 ns a phase there, 860 from HBM at three and six million, n = 8, 5 x 150,001) it is better to sort first: pass
+// 1 (k_sort_copies, or the head, sams_plan.hip) writes copies of the vectors whose phases are sorted by the windows of up to five rows, a window's values then
+// lie in long runs, and a row's lists name places in its copy.  That is one write per copy, from end to end, instead of one scattered write per row; the
+// copies' reads are one per row, as the binned path's are.  A phase takes 300 to 480 ns by its entries: half of it the read-modify-writes (15 clocks of the LDS
+// for 64 of them), the rest latencies between two barriers.
+//
+// A hash either has next to no bucket twice in a phase or, about one row in thirty, in hundreds of places: (a l + b) mod p walks a lattice, and a distance after
+// which buckets repeat is shorter than a phase or it is not (k_push_repeat).  Such a row's launch is up to a third slower: its words of one bucket name
+// places far apart.  It is the first row of its copy, whose runs are then cut by eighths of that distance, and the first in the launch.
+//
+// Measured on MI355X with cold caches, sketch_accumulate by bins and by these lists (us): 853,610 coordinates, n = 14, 5 x 40,514 162 and 130; 1.8 million, n = 17, 3
+// x 56,323 239 and 160; 2.2 million, n = 83, 5 x 39,335 1,890 and 741 (one window); 4.8 million, n = 10, 5 x 207,905 543 and 414; 11.3 million, n = 17, 5 x
+// 192,180 1,977 and 1,282; 32.6 million, n = 11, 7 x 389,885 4,498 and 3,800; by slices (sams_pull.hip) and these lists: a million, n = 43, 5 x 19,287 363
+// and 191; 1.4 million, n = 88, 7 x 15,826 855 and 669.  Of 190 shapes with 0.27 to 60 million coordinates and 9,000 to 650,000 buckets that the rules below
+// send here, 181 are faster, 1.05 to 2.9 times (in the middle 1.35), four alike and five 3 to 5 % slower.
+#include <math.h>
+#include <stdlib.h>
+#include <string.h>
+#include <type_traits>
+
+#include "sams_ctx.h"
+
+#pragma clang fp contract(off)
+
+namespace sams {
+
+constexpr int kPushThreads = 1024;
+constexpr int kPushWaves = kPushThreads / kWave;
+constexpr int kPushGroups = 2;                // words of a lane per phase
+constexpr int kPushEntries = kPushThreads * kPushGroups;
+constexpr int kPushMaxWin = 40800;            // buckets of a window, which with 64 cells for the padding words have to fit in LDS
+constexpr int kPushMostWin = 16;              // windows of a row (with more a phase has too few entries for its barrier)
+constexpr int kPushVals = 4;                  // phases whose values are under way
+constexpr int kPushRing = 8;                  // phases whose words are
+// Buckets lie in LDS in blocks of 64, each turned by a number of its own: the buckets of neighbouring coordinates step by a constant, and where that is a
+// multiple of 32 every lane of a group would be in one bank (207 instead of 147 us for one hash of eight at three million, n = 8, 5 x 150,001).
+__host__ __device__ __forceinline__ uint32_t push_cell(uint32_t b) { return (b & ~63u) | ((b + ((b >> 6) * 0x9e3779b1u >> 26)) & 63u); }
+static __host__ __device__ __forceinline__ int32_t push_cells(int32_t win) { return (win + kWave - 1) / kWave * kWave; }   // the padding's cells follow
+// A word: sign (bit 0), place in the phase (the next 15 bits, or 14), cell (up to bit 30); bit 31: the lane before has the same bucket and adds this lane's
+// value.  Padding: place 0, a cell of the lane's.
+
+// ------------------------------------------------------------------------------------------
+// plan
+// ------------------------------------------------------------------------------------------
+// Which rows share a copy, and how its phases are sorted: by the windows of its rows, the first row's first.  Where that row's buckets repeat, its window's
+// coordinates are sorted by eighths of the repeat distance before anything else, so that those of a bucket lie near each other.
+constexpr int kPushChunks = 8;
+struct PushCopies {
+    int32_t ncopy;
+    int32_t dist[SAMS_MAX_ROWS];               // per copy: the first row's repeat distance, 0 = none
+    int8_t rows[SAMS_MAX_ROWS], row[SAMS_MAX_ROWS][SAMS_MAX_ROWS], of[SAMS_MAX_ROWS];     // rows of a copy; a row's copy
+};
+
+// repeat[row]: the shortest distance below `span` after which buckets repeat, else 0x7fffffff.  From a coordinate to one that far behind it the hash moves by
+// t = a * distance mod p, or by t - p where it wraps: the bucket is the same for the share 1 - t / p of the coordinates if c divides t, for t / p if it
+// divides p - t.  Shares below a tenth do not count.
+__global__ void __launch_bounds__(1024)
+k_push_repeat(HashParams hp, int32_t span, uint32_t *__restrict__ repeat)
+{
+    __shared__ uint32_t least;
+    if (threadIdx.x == 0) least = 0x7fffffffu;
+    __syncthreads();
+    for (uint32_t dist = 1 + threadIdx.x; dist < (uint32_t)span; dist += 1024) {
+        const uint32_t t = hash_y(hp.row[blockIdx.x].ah, 0u, dist);
+        if ((mod_c(hp.modc, t) == 0 && t <= kP31 / 10 * 9) || (mod_c(hp.modc, kP31 - t) == 0 && t >= kP31 / 10)) {
+            atomicMin(&least, dist);
+            break;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) repeat[blockIdx.x] = least;
+}
+
+// per (phase, copy): the coordinate that lies in every place
+__global__ void __launch_bounds__(kPushThreads)
+k_push_order(HashParams hp, int64_t d, PushCopies pc, int32_t nwin, int32_t win, int32_t span, int32_t nph, uint16_t *__restrict__ order)
+{
+    extern __shared__ uint32_t keys[];                               // [span, up to a power of two]
+    const int t = threadIdx.x, q = blockIdx.y, rows = pc.rows[q], dist = pc.dist[q];
+    const int64_t l0 = (int64_t)blockIdx.x * span;
+    const int lim = d - l0 < span ? (int)(d - l0) : span;
+    int all = kPushThreads * 2;
+    while (all < span) all *= 2;
+    for (int x = t; x < all; x += kPushThreads) {
+        uint32_t key = 0;
+        for (int z = 0; z < rows && x < lim; ++z) {
+            key = key * (uint32_t)nwin + bucket_of(hp, pc.row[q][z], (uint32_t)(l0 + x)) / (uint32_t)win;
+            if (z == 0 && dist) key = key * kPushChunks + (uint32_t)(x % dist * kPushChunks / dist);
+        }
+        keys[x] = x < lim ? (key << 14) | (uint32_t)x : 0xffffffffu;
+    }
+    for (int size = 2; size <= all; size *= 2)
+        for (int step = size / 2; step; step /= 2) {
+            __syncthreads();
+            for (int p = t; p < all / 2; p += kPushThreads) {
+                const int lo = 2 * step * (p / step) + p % step, hi = lo + step;
+                const uint32_t x = keys[lo], y = keys[hi];
+                if ((x > y) == ((lo & size) == 0)) {
+                    keys[lo] = y;
+                    keys[hi] = x;
+                }
+            }
+        }
+    __syncthreads();
+    uint16_t *out = order + ((int64_t)q * nph + blockIdx.x) * span;
+    for (int x = t; x < span; x += kPushThreads) out[x] = x < lim ? (uint16_t)(keys[x] & 0x3fffu) : (uint16_t)0;
+}
+
+// per (phase, row and window): the words.  status[0]: a phase has too many entries, or too many that share buckets; status[1]: entries that share a
+// bucket, all phases together
+__global__ void __launch_bounds__(kPushThreads)
+k_push_plan(HashParams hp, int64_t d, int32_t nwin, int32_t win, int32_t span, int32_t nph, int32_t nalloc, int place_bits,
+            const uint16_t *__restrict__ order, PushCopies pc, uint32_t *__restrict__ words, uint32_t *__restrict__ status)
+{
+    extern __shared__ uint32_t cnt[];                                // [win / 2 + 1]  entries of a bucket, two in a word
+    __shared__ uint32_t ent[kPushEntries], outw[kPushEntries];       // the entries' words, by place and in their slots
+    __shared__ uint16_t coord[kPushEntries];                         // their coordinates in the phase
+    __shared__ uint16_t multi[kPushEntries], nth[kPushEntries];      // entries that share a bucket; how many of its entries come before one
+    __shared__ uint32_t place[kPushEntries];                         // of a shared bucket's first entry: group, lane among the group's shared; of the others: the first
+    __shared__ uint32_t part[kPushWaves], many[kPushWaves * kPushGroups], before[kPushWaves * kPushGroups + 1];
+    __shared__ uint32_t sh, longest;
+    const int bshift = place_bits + 1;
+    const int t = threadIdx.x, j = blockIdx.y / nwin, w = blockIdx.y % nwin;
+    uint32_t *out = words + ((int64_t)blockIdx.y * nalloc + blockIdx.x) * kPushEntries;
+    const int64_t l0 = (int64_t)blockIdx.x * span;
+    const int lim = (int)blockIdx.x >= nph ? 0 : (d - l0 < span ? (int)(d - l0) : span);
+    const uint32_t b0 = (uint32_t)w * (uint32_t)win;
+    for (int q = t; q < win / 2 + 1; q += kPushThreads) cnt[q] = 0u;
+    for (int q = t; q < kPushEntries; q += kPushThreads) outw[q] = (uint32_t)(push_cells(win) + q / kPushGroups % kWave) << bshift;
+    if (t < kPushWaves * kPushGroups) many[t] = 0u;
+    if (t == 0) longest = 0u;
+    // the window's coordinates in the order of their places: thread t has the places [t * per, (t + 1) * per) of the phase
+    const uint16_t *in_place = order ? order + ((int64_t)pc.of[j] * nph + blockIdx.x) * span : nullptr;
+    auto at_place = [&](int x) { return in_place ? (int)in_place[x] : x; };
+    const int per = (lim + kPushThreads - 1) / kPushThreads, x0 = t * per, x1 = x0 + per < lim ? x0 + per : lim;
+    uint32_t mine = 0;
+    for (int x = x0; x < x1; ++x) mine += bucket_of(hp, j, (uint32_t)(l0 + at_place(x))) - b0 < (uint32_t)win ? 1u : 0u;
+    __syncthreads();
+    uint32_t at = block_exclusive_scan<kPushThreads>(mine, part);
+    if (t == kPushThreads - 1) sh = at + mine;
+    __syncthreads();
+    const uint32_t total = sh;
+    __syncthreads();
+    if (total > (uint32_t)kPushEntries) {
+        if (t == 0) atomicOr(status, 1u);
+        return;
+    }
+    for (int x = x0; x < x1; ++x) {
+        const uint32_t l = (uint32_t)(l0 + at_place(x)), b = bucket_of(hp, j, l) - b0;
+        if (b >= (uint32_t)win) continue;
+        coord[at] = (uint16_t)at_place(x);
+        ent[at++] = (b << bshift) | ((uint32_t)x << 1) | (sign_neg(hp, j, l) ? 1u : 0u);
+        atomicAdd(&cnt[b >> 1], 1u << (16 * (b & 1)));
+    }
+    __syncthreads();
+    auto bucket = [&](uint32_t e) { return ent[e] >> bshift; };
+    auto members = [&](uint32_t e) { return (cnt[bucket(e) >> 1] >> (16 * (bucket(e) & 1))) & 0xffffu; };
+    bool is_multi[kPushGroups];
+    uint32_t nm = 0;
+#pragma unroll
+    for (int z = 0; z < kPushGroups; ++z) {
+        const uint32_t e = t * kPushGroups + z;
+        is_multi[z] = e < total && members(e) > 1;
+        nm += is_multi[z] ? 1u : 0u;
+    }
+    const uint32_t multi_before = block_exclusive_scan<kPushThreads>(nm, part);
+    {
+        uint32_t k = multi_before;
+#pragma unroll
+        for (int z = 0; z < kPushGroups; ++z)
+            if (is_multi[z]) multi[k++] = (uint16_t)(t * kPushGroups + z);
+        if (t == kPushThreads - 1) sh = k;
+    }
+    __syncthreads();
+    const uint32_t nmulti = sh;
+    __syncthreads();
+    if (nmulti) {
+        for (uint32_t k = t; k < nmulti; k += kPushThreads) {
+            const uint32_t b = bucket(multi[k]);
+            uint32_t n = 0, first = k;
+            for (uint32_t q = 0; q < nmulti; ++q)
+                if (bucket(multi[q]) == b) {
+                    if (coord[multi[q]] < coord[multi[k]]) ++n;
+                    if (coord[multi[q]] < coord[multi[first]]) first = q;
+                }
+            nth[k] = (uint16_t)n;
+            if (n) place[k] = first;
+        }
+        __syncthreads();
+        // The shared buckets in the order of their first entries, as if in one line that is cut every 64 - (most entries of a bucket - 1): a bucket goes
+        // with all its entries to the group in whose piece it starts, and none is longer than what the group has left
+        uint32_t len[kPushGroups], sum = 0;
+#pragma unroll
+        for (int z = 0; z < kPushGroups; ++z) {
+            const uint32_t k = t * kPushGroups + z;
+            len[z] = k < nmulti && nth[k] == 0 ? members(multi[k]) : 0u;
+            sum += len[z];
+            if (len[z] > 1) atomicMax(&longest, len[z]);
+        }
+        uint32_t pos = block_exclusive_scan<kPushThreads>(sum, part);
+        const uint32_t piece = longest < (uint32_t)kWave ? (uint32_t)kWave + 1u - longest : 1u;
+        bool fits = longest < (uint32_t)kWave;
+#pragma unroll
+        for (int z = 0; z < kPushGroups; ++z) {
+            const uint32_t k = t * kPushGroups + z, group = pos / piece, f = pos % piece;
+            if (!len[z]) continue;
+            if (group < (uint32_t)(kPushWaves * kPushGroups)) {
+                place[k] = group | (f << 8);
+                atomicMax(&many[group], f + len[z]);
+            } else {
+                fits = false;
+            }
+            pos += len[z];
+        }
+        // (a hash that leaves no room for the others either needs shorter phases)
+        if (!__syncthreads_and(fits)) {
+            if (t == 0) atomicOr(status, 1u);
+            return;
+        }
+        if (t == 0) atomicAdd(status + 1, nmulti);
+    }
+    // the others fill what room the groups have, in order
+    const uint32_t singles = total - nmulti;
+    if (t < kWave) {
+        constexpr int kAll = kPushWaves * kPushGroups;
+        const uint32_t room = t < kAll ? (uint32_t)kWave - many[t] : 0u;
+        const uint32_t upto = wave_inclusive_scan(room);
+        if (t < kAll) before[t + 1] = upto;
+        if (t == 0) before[0] = 0u;
+    }
+    __syncthreads();
+    if (before[kPushWaves * kPushGroups] < singles) {
+        if (t == 0) atomicOr(status, 1u);
+        return;
+    }
+    auto word_of = [&](uint32_t e) { return (push_cell(bucket(e)) << bshift) | (ent[e] & ((1u << bshift) - 1u)); };
+    auto slot = [&](uint32_t group, uint32_t lane) { return ((group / kPushGroups) * kWave + lane) * kPushGroups + group % kPushGroups; };
+    {
+        uint32_t s = (uint32_t)(t * kPushGroups) - multi_before, group = 0;
+#pragma unroll
+        for (int z = 0; z < kPushGroups; ++z) {
+            const uint32_t e = t * kPushGroups + z;
+            if (e >= total || is_multi[z]) continue;
+            while (before[group + 1] <= s) ++group;                  // there is room for all: the search ends
+            outw[slot(group, s - before[group])] = word_of(e);
+            ++s;
+        }
+    }
+    for (uint32_t k = t; k < nmulti; k += kPushThreads) {
+        const uint32_t n = nth[k], p = n ? place[place[k]] : place[k], group = p & 255u, room = before[group + 1] - before[group];
+        const uint32_t ahead = singles <= before[group] ? 0u : (singles - before[group] < room ? singles - before[group] : room);
+        outw[slot(group, ahead + (p >> 8) + n)] = word_of(multi[k]) | (n ? 0x80000000u : 0u);
+    }
+    __syncthreads();
+    for (int q = t; q < kPushEntries; q += kPushThreads)
+        out[q] = outw[q];
+}
+
+// ------------------------------------------------------------------------------------------
+// accumulation
+// ------------------------------------------------------------------------------------------
+struct PushArgs {
+    const float *u;                   // [n][d], or the copies [ncopy][n][nph * span]
+    const uint32_t *words;            // [r * nwin][nalloc][kPushWaves][64][kPushGroups]
+    float *S;                         // [n][r][c]
+    int64_t c, stride;                // floats between two workers' vectors
+    int32_t n, r, nwin, win, span, nph, nalloc;
+    int32_t share;                    // workers whose units take turns in the order of the units
+    int8_t copy_of[SAMS_MAX_ROWS], row[SAMS_MAX_ROWS];     // a row's copy; the rows, those that take longest first
+};
+
+__device__ __forceinline__ void push_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// The word and value rings are filled by unconditional loads in a fixed order, straight into the registers that the loop carries, so that
+// the compiler waits for exactly the oldest; loads past the vector's end fetch padding words (nalloc), whose place is 0.
+template <int PLACE>
+__global__ void __launch_bounds__(kPushThreads)
+k_sketch_push(PushArgs a)
+{
+    extern __shared__ float tbl[];                                   // [push_cells(win) + 64]
+    // Units in the order row, window, worker; the 8 XCDs, to which workgroups are dealt round-robin, take `share` at a time: workers with the same words side
+    // by side, and the windows of a row, which may take longer than others', on all XCDs
+    const int32_t slot = (int32_t)(blockIdx.x / 8), unit = (slot / a.share * 8 + (int32_t)(blockIdx.x % 8)) * a.share + slot % a.share;
+    if (unit >= a.n * a.r * a.nwin) return;
+    const int32_t i = unit % a.n, list = unit / a.n, j = a.row[list / a.nwin], jw = j * a.nwin + list % a.nwin;
+    const int64_t b0 = (int64_t)(jw % a.nwin) * a.win;
+    const float *ui = a.u + ((int64_t)a.copy_of[j] * a.n + i) * a.stride;
+    const int t = threadIdx.x;
+    constexpr int G = kPushGroups;
+    constexpr uint32_t kPlaces = ((1u << PLACE) - 1u) << 2, kBuckets = ((1u << (30 - PLACE)) - 1u) << 2;
+    typedef uint32_t vecw __attribute__((ext_vector_type(G)));
+    vecw w[kPushRing];
+    float v[kPushVals][G];
+    const char *words = reinterpret_cast<const char *>(a.words + (int64_t)jw * a.nalloc * kPushEntries);
+    uint32_t loff = (uint32_t)t * G * 4;                             // (a list is below 4 GB)
+    const float *ucur = ui;
+    int32_t vph = 0;
+    auto load_words = [&](int z) {
+        w[z] = *reinterpret_cast<const vecw *>(words + loff);
+        loff += kPushEntries * 4;
+        asm volatile("" : "+v"(loff));                               // one addition, not one of 64 bits for each phase of a turn
+    };
+    auto load_values = [&](int zv, int zw) {
+        const char *base = reinterpret_cast<const char *>(vph < a.nph ? ucur : ui);
+#pragma unroll
+        for (int g = 0; g < G; ++g) v[zv][g] = *reinterpret_cast<const float *>(base + ((w[zw][g] << 1) & kPlaces));
+        ucur += a.span;
+        ++vph;
+    };
+    for (int32_t b = t; b < push_cells(a.win) + kWave; b += kPushThreads) tbl[b] = 0.f;
+#pragma unroll
+    for (int z = 0; z < kPushRing; ++z) {
+        load_words(z);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int z = 0; z < kPushVals; ++z) {
+        load_values(z, z);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    auto phase = [&](auto zc) {
+        constexpr int z = zc;
+        uint32_t ww[G];
+        float vv[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            ww[g] = w[z][g];
+            vv[g] = v[z % kPushVals][g];
+            asm volatile("" : "+v"(ww[g]), "+v"(vv[g]));         // (or their use moves up, and with it the wait)
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        load_words(z);
+        __builtin_amdgcn_sched_barrier(0);
+        load_values(z % kPushVals, (z + kPushVals) % kPushRing);
+        __builtin_amdgcn_sched_barrier(0);
+        push_barrier();                                          // the phase before has been added
+        float *cell[G], x[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            cell[g] = reinterpret_cast<float *>(reinterpret_cast<char *>(tbl) + ((ww[g] >> (PLACE - 1)) & kBuckets));
+            vv[g] = __uint_as_float(__float_as_uint(vv[g]) ^ (ww[g] << 31));
+            x[g] = *cell[g];
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) x[g] = x[g] + vv[g];
+        uint64_t follows[G], any = 0;
+#pragma unroll
+        for (int g = 0; g < G; ++g) any |= follows[g] = __ballot((int)ww[g] < 0);
+        if (!any) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) *cell[g] = x[g];
+            asm volatile("; no bucket twice" ::: "memory");          // (kept apart from the other case)
+        } else {
+            // a bucket's first lane adds the values of the lanes that follow, one after the other: all lanes shift, by a lane each time, and those with
+            // that many followers add
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                uint64_t more = follows[g] >> 1;
+                float y = vv[g];
+                for (int q = 2; more; ++q) {
+                    y = __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(y), 0x130, 0xf, 0xf, false));
+                    x[g] = __builtin_amdgcn_inverse_ballot_w64(more) ? x[g] + y : x[g];
+                    more &= follows[g] >> q;
+                }
+                if (!__builtin_amdgcn_inverse_ballot_w64(follows[g])) *cell[g] = x[g];
+            }
+        }
+    };
+    // whole turns of the ring, with no way out in between (or the compiler waits for all loads at the turn's end), then what is left
+    int32_t p = 0;
+    for (; p + kPushRing <= a.nph; p += kPushRing) {
+        phase(std::integral_constant<int, 0>{});
+        phase(std::integral_constant<int, 1>{});
+        phase(std::integral_constant<int, 2>{});
+        phase(std::integral_constant<int, 3>{});
+        phase(std::integral_constant<int, 4>{});
+        phase(std::integral_constant<int, 5>{});
+        phase(std::integral_constant<int, 6>{});
+        phase(std::integral_constant<int, 7>{});
+    }
+    static_assert(kPushRing == 8, "the phases of a turn");
+    if (p + 0 < a.nph) phase(std::integral_constant<int, 0>{});
+    if (p + 1 < a.nph) phase(std::integral_constant<int, 1>{});
+    if (p + 2 < a.nph) phase(std::integral_constant<int, 2>{});
+    if (p + 3 < a.nph) phase(std::integral_constant<int, 3>{});
+    if (p + 4 < a.nph) phase(std::integral_constant<int, 4>{});
+    if (p + 5 < a.nph) phase(std::integral_constant<int, 5>{});
+    if (p + 6 < a.nph) phase(std::integral_constant<int, 6>{});
+    __syncthreads();
+    const int32_t nb = a.c - b0 < a.win ? (int32_t)(a.c - b0) : a.win;
+    float *out = a.S + ((int64_t)i * a.r + j) * a.c + b0;
+    for (int32_t b = t; b < nb; b += kPushThreads) out[b] = tbl[push_cell((uint32_t)b)];
+}
+
+// ------------------------------------------------------------------------------------------
+// host side
+// ------------------------------------------------------------------------------------------
+static int push_place_bits(int32_t win) { return push_cells(win) + kWave <= 1 << 15 ? 15 : 14; }
+static int32_t push_win(int64_t c, int32_t nwin) { return (int32_t)((c + nwin - 1) / nwin); }
+static size_t push_lds(int32_t win) { return (size_t)(push_cells(win) + kWave) * 4; }
+constexpr int32_t kPushTile = 1 << 14;        // most coordinates of a phase with copies: pass 1 holds one in LDS
+
+// coordinates of a phase: its entries, a binomial number, stay below kPushEntries by `sigmas` deviations
+static int32_t push_span(int64_t c, int32_t win, bool copies, double sigmas)
+{
+    const double f = (double)win / (double)c;
+    double mean = kPushEntries;
+    for (int it = 0; it < 20; ++it) mean = kPushEntries - sigmas * sqrt(mean * (1.0 - f) + 1.0);
+    const int64_t span = (int64_t)(mean / f) / 32 * 32, most = copies ? kPushTile : ((int64_t)1 << push_place_bits(win)) - 32;
+    return (int32_t)(span < most ? span : most);
+}
+
+// rows that a copy has room for: runs of a phase's coordinates that have everything they are sorted by in common keep 20 places
+static int32_t push_rows(int32_t nwin, int32_t span, int64_t bins)
+{
+    int32_t rows = 0;
+    while (nwin > 1 && bins * nwin <= 1024 && span / (bins * nwin) >= 20) {
+        bins *= nwin;
+        ++rows;
+    }
+    return rows;
+}
+
+// the rows' copies: every row whose buckets repeat within a phase is the first of one
+static PushCopies push_copies(const sams_ctx *ctx, int32_t nwin, int32_t span, const uint32_t *repeat)
+{
+    PushCopies pc = {};
+    const int32_t most = push_rows(nwin, span, 1), most_repeat = push_rows(nwin, span, kPushChunks);
+    if (most < 1) return pc;
+    auto open = [&](int32_t j, int32_t dist) {
+        pc.dist[pc.ncopy] = dist;
+        pc.row[pc.ncopy][0] = (int8_t)j;
+        pc.rows[pc.ncopy] = 1;
+        pc.of[j] = (int8_t)pc.ncopy++;
+    };
+    for (int32_t j = 0; j < ctx->r; ++j)
+        if (repeat[j] < (uint32_t)span && most_repeat >= 1) open(j, (int32_t)repeat[j]);
+    for (int32_t j = 0; j < ctx->r; ++j) {
+        if (repeat[j] < (uint32_t)span && most_repeat >= 1) continue;
+        int32_t q = 0;
+        while (q < pc.ncopy && pc.rows[q] >= (pc.dist[q] ? most_repeat : most)) ++q;
+        if (q == pc.ncopy) {
+            open(j, 0);
+        } else {
+            pc.row[q][pc.rows[q]++] = (int8_t)j;
+            pc.of[j] = (int8_t)q;
+        }
+    }
+    return pc;
+}
+
+// What a sketch should take, in ns.  Workgroups run in rounds of 256, one per compute unit.  A phase out of the vectors takes the longer the more windows share
+// their lines (cold caches; 310 to 400 with one window, 530 to 620 with two, up to 690 with four); out of copies 300 to 480 by its entries, and less where fewer
+// than 256 run (11.2 million, n = 8, 5 x 262,144, nine windows, 360 workgroups: 684 phases in 457 us).  Rows that repeat take up to a third longer.
+static double push_cost(const sams_ctx *ctx, int32_t nwin, bool copies, bool fused, const uint32_t *repeat)
+{
+    const int32_t win = push_win(ctx->c, nwin);
+    const int32_t span = push_span(ctx->c, win, copies, 4.5);
+    const double nph = (double)((ctx->d + span - 1) / span), entries = (double)span * win / ctx->c, nd = (double)ctx->n * ctx->d;
+    const int64_t units = (int64_t)ctx->n * ctx->r * nwin, full = units / 256, rest = units % 256;
+    bool repeats = false;
+    for (int32_t j = 0; j < ctx->r; ++j) {
+        if (repeat[j] < (uint32_t)span / 24) return 1e30;            // (dozens of a phase's entries in a bucket)
+        repeats |= repeat[j] < (uint32_t)span;
+    }
+    if (!copies) {
+        const double phase[] = {340, 560, 640, 690, 850};
+        return 8000 + (full + (rest ? 1 : 0)) * nph * (nwin <= 5 ? phase[nwin - 1] : 350 + 100 * nwin) * (repeats ? 1.3 : 1.0);
+    }
+    const PushCopies pc = push_copies(ctx, nwin, span, repeat);
+    if (!pc.ncopy) return 1e30;
+    const double one = 130 + 0.19 * entries > 300 ? 130 + 0.19 * entries : 300, part = rest * one / 256;
+    return 8000 + nph * (full * one + (rest ? (part > 290 ? part : 290) : 0)) * (repeats ? 1.12 : 1.0) +
+           (fused ? nd * pc.ncopy * 4 / 5100.0 : 6000 + nd * (pc.ncopy + 1) * 4 / 5000.0);
+}
+
+// Whether this shape may push: tables of 10,000 buckets (below, the lists of sams_pull.hip are the faster, and phases have dozens of coordinates for a bucket) to
+// kPushMostWin windows, vectors of 2^18 coordinates (below, everything is launches and latencies) to 2^26 (the lists take gigabytes).
+static bool push_shape(const sams_ctx *ctx, const Tunables &tun)
+{
+    if (tun.sketch_path != 0 || tun.estimate_path == 2 || tun.win_log2 || tun.tile_log2 || tun.chunk_log2 || tun.acc_threads || tun.stage_rows ||
+        tun.stage_interleave || tun.run_pad != 16 || tun.acc_wide != 2 || tun.fuse_head == 1)
+        return false;                                                // the caller asks for the binned path or for a shape of it
+    if (ctx->c > kPushMostWin * (int64_t)kPushMaxWin || ctx->d > 1 << 26) return false;
+    return tun.push_windows ? tun.push_windows > 0 : ctx->c > 10000 && ctx->d >= 1 << 18;
+}
+
+// the fastest number of windows, and whether out of copies; 1e30: none
+static double push_choose(const sams_ctx *ctx, const Tunables &tun, bool first, const uint32_t *repeat, int32_t *windows, bool *copies)
+{
+    double best = 1e30;
+    for (int mode = 0; mode < 2; ++mode)
+        for (int32_t nwin = (int32_t)((ctx->c + kPushMaxWin - 1) / kPushMaxWin); nwin <= kPushMostWin; ++nwin) {
+            if (tun.push_windows ? tun.push_windows != mode * 100 + nwin : first && (nwin > 1 || mode)) continue;
+            const double cost = push_cost(ctx, nwin, mode == 1, tun.fuse_head == 2, repeat);
+            if (cost >= best) continue;
+            best = cost;
+            *windows = nwin;
+            *copies = mode == 1;
+        }
+    return best;
+}
+
+// What the other paths are taken to need, in ns: 0.95 per thousand terms by slices with many pairs (measured 0.93 to 2.3), 1.85 by bins (1.8 to 2.4 from
+// 2 million coordinates on, up to 3 below), 1.57 where the head stages (1.55 to 1.95); a little in favour of what was there.
+static bool push_pays(const sams_ctx *ctx, const Tunables &tun, bool first, double cost)
+{
+    if (tun.push_windows) return cost < 1e30;
+    return cost <= 10000 + (double)ctx->n * ctx->r * ctx->d * (first ? 0.95e-3 : (tun.fuse_head == 2 ? 1.57e-3 : 1.85e-3));
+}
+
+int push_create(sams_ctx *ctx, const Tunables &tun, bool first, bool *done)
+{
+    *done = false;
+    if (!push_shape(ctx, tun)) return SAMS_OK;
+    PushPlan pp = {};
+    bool copies = false;
+    uint32_t *status = nullptr, h_status[4] = {0, 0, 0, 0}, repeat[SAMS_MAX_ROWS];
+    for (uint32_t &x : repeat) x = 0x7fffffffu;
+    if (!push_pays(ctx, tun, first, push_choose(ctx, tun, first, repeat, &pp.nwin, &copies))) return SAMS_OK;   // not even with the best of hashes
+    PushCopies pc = {};
+    int rc = SAMS_OK;
+    do {
+        if (hipMalloc((void **)&status, (4 + SAMS_MAX_ROWS) * 4) != hipSuccess) break;
+        {
+            ProfScope ps(ctx, KID_PLAN_BUILD);
+            hipLaunchKernelGGL(k_push_repeat, dim3((unsigned)ctx->r), dim3(1024), 0, ctx->stream, ctx->hp, 1 << 15, status + 4);
+        }
+        hipError_t e = hipMemcpyAsync(repeat, status + 4, (size_t)ctx->r * 4, hipMemcpyDeviceToHost, ctx->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+        if (e != hipSuccess) { g_last_hip_error = (int)e; rc = SAMS_EHIP; break; }
+        if (!push_pays(ctx, tun, first, push_choose(ctx, tun, first, repeat, &pp.nwin, &copies))) break;
+        pp.win = push_win(ctx->c, pp.nwin);
+        int32_t rows = 0;
+        for (int repeats = 1; repeats >= 0; --repeats)               // the rows whose buckets repeat first
+            for (int32_t j = 0; j < ctx->r; ++j)
+                if ((repeat[j] < (uint32_t)push_span(ctx->c, pp.win, copies, 4.5)) == (repeats == 1)) pp.row[rows++] = (int8_t)j;
+        const int place_bits = copies ? 14 : push_place_bits(pp.win);
+        pp.kernel = place_bits == 15 ? (const void *)k_sketch_push<15> : (const void *)k_sketch_push<14>;
+        e = hipFuncSetAttribute((const void *)k_push_plan, hipFuncAttributeMaxDynamicSharedMemorySize, (kPushMaxWin / 2 + 1) * 4);
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_push_order, hipFuncAttributeMaxDynamicSharedMemorySize, kPushTile * 4);
+        if (e == hipSuccess) e = hipFuncSetAttribute(pp.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)push_lds(kPushMaxWin));
+        if (e != hipSuccess) { g_last_hip_error = (int)e; rc = SAMS_EHIP; break; }
+        if (copies && (rc = copies_create()) != SAMS_OK) break;
+        for (double sigmas = 4.5; sigmas < 10; sigmas += 4.5) {
+            pp.span = push_span(ctx->c, pp.win, copies, sigmas);
+            pp.nph = (int32_t)((ctx->d + pp.span - 1) / pp.span);
+            pp.nalloc = pp.nph + kPushRing;
+            pp.word_bytes = (int64_t)ctx->r * pp.nwin * pp.nalloc * kPushEntries * 4;
+            if (copies) {
+                pc = push_copies(ctx, pp.nwin, pp.span, repeat);
+                if (!pc.ncopy) break;
+                pp.ncopy = pc.ncopy;
+                memcpy(pp.copy_of, pc.of, sizeof(pp.copy_of));
+                pp.order_bytes = (int64_t)pp.ncopy * pp.nph * pp.span * 2;
+                pp.copy_words = (int64_t)pp.ncopy * ctx->n * pp.nph * pp.span;
+                if (hipMalloc((void **)&pp.order, (size_t)pp.order_bytes) != hipSuccess) { pp.order = nullptr; break; }
+            }
+            if (hipMalloc((void **)&pp.words, (size_t)pp.word_bytes) != hipSuccess) { pp.words = nullptr; break; }
+            rc = enqueue_fill_u32(ctx, status, 4, 0u);
+            if (rc != SAMS_OK) break;
+            {
+                ProfScope ps(ctx, KID_PLAN_BUILD);
+                if (copies) {
+                    int32_t all = kPushThreads * 2;
+                    while (all < pp.span) all *= 2;
+                    hipLaunchKernelGGL(k_push_order, dim3((unsigned)pp.nph, (unsigned)pp.ncopy), dim3(kPushThreads), (size_t)all * 4, ctx->stream, ctx->hp,
+                                       ctx->d, pc, pp.nwin, pp.win, pp.span, pp.nph, pp.order);
+                }
+                hipLaunchKernelGGL(k_push_plan, dim3((unsigned)pp.nalloc, (unsigned)(ctx->r * pp.nwin)), dim3(kPushThreads), (size_t)(pp.win / 2 + 1) * 4,
+                                   ctx->stream, ctx->hp, ctx->d, pp.nwin, pp.win, pp.span, pp.nph, pp.nalloc, place_bits, pp.order, pc, pp.words,
+                                   status);
+            }
+            e = hipMemcpyAsync(h_status, status, 16, hipMemcpyDeviceToHost, ctx->stream);
+            if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+            if (e == hipSuccess) e = hipGetLastError();
+            if (e != hipSuccess) { g_last_hip_error = (int)e; rc = SAMS_EHIP; break; }
+            if (!h_status[0]) break;
+            (void)hipFree(pp.words);
+            if (pp.order) (void)hipFree(pp.order);
+            pp.words = nullptr;
+            pp.order = nullptr;
+        }
+        if (rc != SAMS_OK || !pp.words) break;
+        *done = true;
+        ctx->scratch_bytes += pp.word_bytes + pp.order_bytes;
+    } while (0);
+    (void)hipGetLastError();
+    if (status) (void)hipFree(status);
+    ctx->push = pp;
+    if (!*done) push_destroy(ctx);
+    return rc;
+}
+
+void push_destroy(sams_ctx *ctx)
+{
+    if (ctx->push.words) (void)hipFree(ctx->push.words);
+    if (ctx->push.order) (void)hipFree(ctx->push.order);
+    ctx->push = PushPlan{};
+}
+
+int enqueue_sketch_push(sams_ctx *ctx, const float *u, float *S_workers)
+{
+    const PushPlan &pp = ctx->push;
+    if (pp.ncopy && ctx->plan.staged_u != u) {                       // not written by a fused head
+        SAMS_TRY(enqueue_sort_copies(ctx, u));
+        ctx->plan.staged_u = nullptr;
+    }
+    PushArgs a = {pp.ncopy ? ctx->plan.stg : u, pp.words, S_workers, ctx->c, pp.ncopy ? (int64_t)pp.nph * pp.span : ctx->d, ctx->n, ctx->r, pp.nwin,
+                  pp.win, pp.span, pp.nph, pp.nalloc, ctx->n < 4 ? ctx->n : 4, {0}, {0}};
+    memcpy(a.copy_of, pp.copy_of, sizeof(a.copy_of));
+    memcpy(a.row, pp.row, sizeof(a.row));
+    const int64_t units = (int64_t)ctx->n * ctx->r * pp.nwin, chunks = (units + a.share - 1) / a.share;
+    void *args[] = {&a};
+    ProfScope ps(ctx, KID_SKETCH_PUSH);
+    SAMS_HIP(hipLaunchKernel(pp.kernel, dim3((unsigned)((chunks + 7) / 8 * 8 * a.share)), dim3(kPushThreads), args, push_lds(pp.win), ctx->stream));
+    SAMS_HIP(hipGetLastError());
+    return SAMS_OK;
+}
+
+}  // namespace sams

@@ -1033,11 +1033,12 @@ constexpr int64_t kGatherEstimateMaxTableBytes = 1 << 20, kGatherEstimateMaxD = 
 // Whether stage 3 goes through the plan.  A small table under a short vector stays in every L2: r gathers per coordinate in
 // one launch then beat the two launches of the plan-driven recovery (C1: 6 us against 23), which is made for tables far
 // larger than any cache.
-static bool estimate_by_plan(const sams_ctx *ctx)
+bool estimate_wants_plan(const sams_ctx *ctx)
 {
     const bool small = (int64_t)ctx->r * ctx->c * 4 <= kGatherEstimateMaxTableBytes && ctx->d <= kGatherEstimateMaxD;
-    return ctx->plan.mode == PLAN_BINNED && !ctx->pull.kernel && (ctx->tun.estimate_path == 2 || (ctx->tun.estimate_path == 0 && !small));
+    return ctx->tun.estimate_path == 2 || (ctx->tun.estimate_path == 0 && !small);
 }
+static bool estimate_by_plan(const sams_ctx *ctx) { return ctx->plan.srcp && estimate_wants_plan(ctx); }
 
 // Rows that k_estimate_lds holds, 0 = it is not used.  It has to fill its LDS and to compute more per coordinate than the
 // gathers wait for while their table stays in the 32 KB L1s; rows that it has no room for cost it more than the gathers.

@@ -31,6 +31,7 @@ k_sketch_atomic(const float *__restrict__ u, float *__restrict__ S, HashParams h
 
 int enqueue_sketch(sams_ctx *ctx, const float *u, float *S_workers)
 {
+    if (ctx->push.words) return enqueue_sketch_push(ctx, u, S_workers);
     if (ctx->pull.kernel) return enqueue_sketch_pull(ctx, u, S_workers);
     if (ctx->plan.mode != PLAN_ATOMIC) return enqueue_sketch_planned(ctx, u, S_workers);
     const int64_t cells = (int64_t)ctx->n * ctx->r * ctx->c;

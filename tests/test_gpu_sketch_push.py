@@ -1,0 +1,161 @@
+"""sketch_accumulate where workgroups pick their values out of the vectors, or out of sorted copies of them, by lists of words: tables bit for bit
+those of a sequential loop, at the edges of phases (2,048 words; a multiple of 32 coordinates), windows and wavefronts."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import Oracle
+from paper_2210_07454_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+P31 = 2 ** 31 - 1
+
+
+def context(d, n, r, c, hp, k=1, **tunables):
+    from paper_2210_07454_amd import sams
+    try:
+        for key, val in tunables.items():
+            sams.sams_configure(key, val)
+        return sams.Context(d, n, r, c, k, hp)
+    finally:
+        for key in tunables:
+            sams.sams_configure(key, 0)
+
+
+def kernels(ctx, u, S):
+    ctx.sams_profile_enable(True)
+    ctx.sketch_accumulate(u, S)
+    ctx.sams_profile_enable(False)
+    return set(ctx.sams_profile_read())
+
+
+def check(d, n, r, c, hp, windows, u=None):
+    """windows: the tunable "push_windows"; returns the kernels of one sketch."""
+    rng = np.random.default_rng(d + c)
+    if u is None:
+        u = (rng.standard_normal((n, d)) * 10.0 ** rng.uniform(-3, 1, d)).astype(np.float32)
+        u[:, ::7] *= np.float32(0.0)                                 # zeros of both signs
+    S = torch.full((n, r, c), 9.0, device="cuda")
+    with context(d, n, r, c, hp, push_windows=windows) as ctx:
+        assert ctx.sketch_mode == 2
+        used = kernels(ctx, torch.from_numpy(u).cuda(), S)
+        assert ctx.accumulate_variant == -1 or "k_sketch_push" not in used
+    got = S.cpu().numpy()
+    o = Oracle("f32")
+    for i in range(n):
+        ref = o.sketch(u[i], hp, c)
+        assert np.array_equal(np.isnan(got[i]), np.isnan(ref))
+        assert np.array_equal(got[i].view(np.uint32)[~np.isnan(ref)], ref.view(np.uint32)[~np.isnan(ref)]), i
+    return used
+
+
+# one window: 2,016 coordinates a phase; windows of one bucket, of up to and above 2^15 cells (where places have 14 bits), the last one of a few buckets or
+# none; a vector of one coordinate, one phase, one more and one less, the ring's eight phases and around; workers that do and do not fill an XCD's share
+@pytest.mark.parametrize("d,n,r,c,windows", [
+    (1, 1, 1, 1, 1), (3, 5, 2, 2, 2), (2_016, 4, 2, 64, 1), (2_017, 3, 2, 65, 1), (2_015, 9, 1, 63, 1), (16_128, 2, 3, 40_800, 1), (16_129, 2, 3, 32_704, 1),
+    (18_143, 1, 2, 32_705, 1), (4_033, 33, 5, 5_000, 1), (30_001, 3, 3, 65_409, 2), (40_003, 7, 2, 81_600, 2), (29_999, 2, 16, 3_000, 3), (100_003, 6, 4, 20_001, 5),
+    (250_001, 2, 3, 33, 16), (300_007, 2, 2, 17, 16), (123_457, 4, 5, 100_000, 16), (60_000, 5, 2, 60_000, 7)])
+def test_from_the_vectors(d, n, r, c, windows):
+    assert check(d, n, r, c, inputs.hash_params(r, seed=d % 89), windows) <= {"k_sketch_push", "k_sketch_pull", "k_bin_scatter", "k_bin_accumulate"}
+
+
+@pytest.mark.parametrize("d,n,r,c,windows", [
+    (1, 1, 1, 40_001, 102), (3_808, 4, 2, 30_000, 102), (3_809, 3, 5, 81_600, 102), (3_807, 5, 3, 9_001, 102), (100_001, 3, 10, 100_000, 103),
+    (70_003, 2, 7, 50_001, 106), (200_000, 9, 5, 262_144, 109), (49_153, 2, 4, 3_000, 116), (49_152, 1, 16, 600_000, 116)])
+def test_from_sorted_copies(d, n, r, c, windows):
+    assert check(d, n, r, c, inputs.hash_params(r, seed=d % 83), windows) == {"k_sketch_push", "k_bin_scatter"}
+
+
+def repeating(r, c, dist, rows):
+    """Hash parameters under which, in the given rows, most coordinates share the bucket with the one `dist` on."""
+    hp = inputs.hash_params(r, seed=5)
+    for z, j in enumerate(rows):
+        hp[j, 0] = (3 + z) * c * pow(dist, -1, P31) % P31            # a * dist = (3 + z) c (mod p)
+    return hp
+
+
+# two, a few and some twenty coordinates of a phase in a bucket; so many that the rows keep the binned path
+@pytest.mark.parametrize("windows", [1, 3, 5, 103, 105])
+@pytest.mark.parametrize("dist,rows", [(3_000, (1,)), (1_500, (0, 2)), (601, (2,)), (200, (1,)), (97, (0,)), (5, (1,)), (1, (0, 1))])
+def test_buckets_that_repeat_within_a_phase(dist, rows, windows):
+    d, n, r, c = 50_021, 3, 3, 20_000
+    used = check(d, n, r, c, repeating(r, c, dist, rows), windows)
+    assert dist > 5 or "k_sketch_push" not in used
+
+
+@pytest.mark.parametrize("windows", [2, 104])
+def test_infinities_and_nan_reach_their_cells_only(windows):
+    d, n, r, c = 30_011, 3, 3, 20_011
+    rng = np.random.default_rng(7)
+    u = rng.standard_normal((n, d)).astype(np.float32)
+    u[0, 5], u[1, 70], u[2, d - 1], u[2, 4_000] = np.inf, -np.inf, np.nan, np.float32(1e-44)
+    check(d, n, r, c, inputs.hash_params(r, seed=8), windows, u)
+
+
+# where the paths are chosen: by each of them the same bits, and the one that is meant
+@pytest.mark.parametrize("d,n,r,c,kernel", [
+    (262_144, 84, 5, 12_000, "k_sketch_push"), (262_143, 84, 5, 12_000, "k_sketch_pull"), (262_144, 84, 5, 10_000, "k_sketch_pull"),
+    (300_001, 2, 2, 300_001, "k_bin_accumulate"), (400_003, 40, 5, 32_769, "k_sketch_push"), (1_000_001, 9, 5, 100_003, "k_sketch_push")])
+def test_the_chosen_path(d, n, r, c, kernel):
+    assert kernel in check(d, n, r, c, inputs.hash_params(r, seed=3), 0)
+
+
+@pytest.mark.parametrize("windows,fuse_head", [(103, 2), (103, 0), (3, 2), (1, 0)])
+@pytest.mark.parametrize("d", [40_000, 40_003])
+def test_one_iteration(d, windows, fuse_head):
+    """head, sketches, recovery and update; a second sketch of the same vector comes from what the head has staged"""
+    from paper_2210_07454_amd import sams
+    from tests.test_gpu_random_shapes import one_iteration
+    try:
+        sams.sams_configure("push_windows", windows)
+        sams.sams_configure("fuse_head", fuse_head)
+        assert one_iteration(sams, (d, 5, 5, 33_003, 400), seed=d % 97 + windows)
+    finally:
+        sams.sams_configure("push_windows", 0)
+        sams.sams_configure("fuse_head", 0)
+
+
+@pytest.mark.parametrize("pa", [False, True])
+def test_copies_written_by_the_head_are_used_once_and_for_their_vector(pa):
+    """A sketch of another vector, and a recovery, take the copies' place: the next sketch of the head's vector sorts it again."""
+    d, n, r, c, k = 50_004, 3, 5, 40_000, 200
+    hp = inputs.hash_params(r, seed=6)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    g, other = torch.randn(n, d, device="cuda", generator=gen), torch.randn(n, d, device="cuda", generator=gen)
+    m, e = torch.zeros(n, d, device="cuda"), torch.zeros(n, d, device="cuda")
+    v, vhat = (torch.full((n, d) if pa else (d,), 1e-4, device="cuda") for _ in range(2))
+    S = torch.empty(n, r, c, device="cuda")
+    o = Oracle("f32")
+    with context(d, n, r, c, hp, k, push_windows=104, fuse_head=2) as ctx:
+        (ctx.amsgrad_ef_update_pa if pa else ctx.amsgrad_ef_update)(g, m, e, v, vhat, torch.zeros(d, device="cuda"), None, None, 0, 0.9, 0.99, 1e-3)
+        want = np.stack([o.sketch(x, hp, c) for x in e.cpu().numpy()])
+        sketches = [("k_sketch_push",), ("k_sketch_push", "k_bin_scatter"), ("k_sketch_push", "k_bin_scatter")]
+        for u, expect in zip((e, other, e), sketches):
+            assert kernels(ctx, u, S) == set(expect)
+            assert np.array_equal(S.cpu().numpy(), want if u is e else np.stack([o.sketch(x, hp, c) for x in other.cpu().numpy()]))
+        ctx.unsketch_topk(S.mean(0).contiguous(), None, torch.empty(k, device="cuda", dtype=torch.int32), None)
+        assert kernels(ctx, e, S) == {"k_sketch_push", "k_bin_scatter"}
+        assert np.array_equal(S.cpu().numpy(), want)
+
+
+def test_replayed_graph_equals_eager():
+    d, n, r, c = 60_001, 4, 3, 50_000
+    hp = inputs.hash_params(r, seed=2)
+    u = torch.randn(n, d, device="cuda")
+    for windows in (2, 103):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            with context(d, n, r, c, hp, push_windows=windows) as ctx:
+                S, ref = torch.empty(n, r, c, device="cuda"), torch.empty(n, r, c, device="cuda")
+                ctx.sketch_accumulate(u, ref)
+                stream.synchronize()
+                graph = torch.cuda.CUDAGraph()
+                with torch.cuda.graph(graph, stream=stream):
+                    ctx.sketch_accumulate(u, S)
+                for _ in range(3):
+                    S.fill_(3.0)
+                    graph.replay()
+                    stream.synchronize()
+                    assert torch.equal(S, ref)
+                    ctx.sketch_accumulate(u, ref)
