@@ -2188,6 +2188,7 @@ int enqueue_sketch_planned(sams_ctx *ctx, const float *u, float *S_workers)
     }
     const int64_t L = (int64_t)1 << pl.tile_log2;
     const int64_t per = (pl.ntile + kNumXcd - 1) / kNumXcd;
+    if (pl.staged_u != u) pl.staged_u = nullptr;                     // pass 1 overwrites the vector that a fused head staged
     for (int32_t j0 = 0; j0 < ctx->r; j0 += pl.stage_rows) {
         const RowGroup rg = {j0, (ctx->r - j0) < pl.stage_rows ? (ctx->r - j0) : pl.stage_rows, pl.stage_rows, ctx->r, pl.stage_ilv};
         if (j0 > 0 || pl.staged_u != u) {                            // not staged by a fused head: pass 1 now

@@ -117,8 +117,9 @@ def test_one_iteration(d, windows, fuse_head):
 
 
 @pytest.mark.parametrize("pa", [False, True])
-def test_copies_written_by_the_head_are_used_once_and_for_their_vector(pa):
-    """A sketch of another vector, and a recovery, take the copies' place: the next sketch of the head's vector sorts it again."""
+@pytest.mark.parametrize("tunables,kernel", [(dict(push_windows=104), "k_sketch_push"), (dict(sketch_path=2), "k_bin_accumulate")])
+def test_copies_written_by_the_head_are_used_once_and_for_their_vector(tunables, kernel, pa):
+    """A sketch of another vector, and a recovery, take the place of what the head staged: the next sketch of the head's vector sorts it again."""
     d, n, r, c, k = 50_004, 3, 5, 40_000, 200
     hp = inputs.hash_params(r, seed=6)
     gen = torch.Generator(device="cuda").manual_seed(1)
@@ -127,15 +128,15 @@ def test_copies_written_by_the_head_are_used_once_and_for_their_vector(pa):
     v, vhat = (torch.full((n, d) if pa else (d,), 1e-4, device="cuda") for _ in range(2))
     S = torch.empty(n, r, c, device="cuda")
     o = Oracle("f32")
-    with context(d, n, r, c, hp, k, push_windows=104, fuse_head=2) as ctx:
+    with context(d, n, r, c, hp, k, fuse_head=2, **tunables) as ctx:
         (ctx.amsgrad_ef_update_pa if pa else ctx.amsgrad_ef_update)(g, m, e, v, vhat, torch.zeros(d, device="cuda"), None, None, 0, 0.9, 0.99, 1e-3)
         want = np.stack([o.sketch(x, hp, c) for x in e.cpu().numpy()])
-        sketches = [("k_sketch_push",), ("k_sketch_push", "k_bin_scatter"), ("k_sketch_push", "k_bin_scatter")]
+        sketches = [(kernel,), (kernel, "k_bin_scatter"), (kernel, "k_bin_scatter")]
         for u, expect in zip((e, other, e), sketches):
             assert kernels(ctx, u, S) == set(expect)
             assert np.array_equal(S.cpu().numpy(), want if u is e else np.stack([o.sketch(x, hp, c) for x in other.cpu().numpy()]))
         ctx.unsketch_topk(S.mean(0).contiguous(), None, torch.empty(k, device="cuda", dtype=torch.int32), None)
-        assert kernels(ctx, e, S) == {"k_sketch_push", "k_bin_scatter"}
+        assert kernels(ctx, e, S) == {kernel, "k_bin_scatter"}
         assert np.array_equal(S.cpu().numpy(), want)
 
 
