@@ -8,26 +8,30 @@
 //
 // A phase has at most kPushEntries words, kPushGroups groups of 64 (a word per lane) for each of 16 wavefronts; a lane reads its words, fetches the values
 // they name from memory, and adds each to its cell with a plain read-modify-write.  Wavefronts meet at one barrier per phase, and within a phase all
-// coordinates of a bucket are adjacent lanes of one group, in order: the first of them adds up what the others have.  So a bucket's terms are added in
-// coordinate order, bit for bit like a sequential loop; no atomics, every cell is written once.
+// coordinates of a bucket are one lane's two words, or words of adjacent lanes, in order, each of which adds to the sum of the one before.  So a bucket's terms are
+// added in coordinate order, bit for bit like a sequential loop; no atomics, every cell is written once.
 //
 // Out of the vectors themselves a group of 64 neighbouring coordinates of one of w windows touches 2 w lines, and that is what bounds it: a compute unit's L1
 // takes about two clocks for 16 lanes and a line, and the lines of all windows' workgroups come through it.  With more than a window or two (and where vectors
 // and lists do not fit the 256 MB cache together: 490 ns a phase there, 860 from HBM at three and six million, n = 8, 5 x 150,001) it is better to sort first: pass
 // 1 (k_sort_copies, or the head, sams_plan.hip) writes copies of the vectors whose phases are sorted by the windows of up to five rows, a window's values then
 // lie in long runs, and a row's lists name places in its copy.  That is one write per copy, from end to end, instead of one scattered write per row; the
-// copies' reads are one per row, as the binned path's are.  A phase takes 300 to 480 ns by its entries: half of it the read-modify-writes (15 clocks of the LDS
-// for 64 of them), the rest latencies between two barriers.
+// copies' reads are one per row, as the binned path's are.  A phase of 1,870 entries takes 340 to 430 ns.  No one thing bounds it: without
+// the read-modify-writes, or with every second barrier, it takes as long; with all values from the caches (the same phase again and again) 8 to 16 % less, with the
+// words too 20 %, and without any values 30 to 38 % less (11.2 million, n = 8, 5 x 262,001 477, 441, 385 and 341 us; 25 million, n = 16, 10 x 100,000 3,573, 3,008,
+// 2,915 and 2,275): addresses of gathers, which the vector memory unit works at two thirds of the time, then instructions and the LDS.
 //
 // A hash either has next to no bucket twice in a phase or, about one row in thirty, in hundreds of places: (a l + b) mod p walks a lattice, and a distance after
-// which buckets repeat is shorter than a phase or it is not (k_push_repeat).  Such a row's launch is up to a third slower: its words of one bucket name
-// places far apart.  It is the first row of its copy, whose runs are then cut by eighths of that distance, and the first in the launch.
+// which buckets repeat is shorter than a phase or it is not (k_push_repeat).  Such a row's words of a bucket name places far apart, and its workgroups take up to
+// half as long again; they come first.  (That a bucket's words are a lane's two and not two lanes' matters here: with the first lane collecting the others' values by
+// shifts, in copies sorted for such rows, 11.2 million, n = 8, 5 x 262,001 with one took 588 to 663 us; now 515 to 575, and 480 without such a row.  Copies of their
+// own for such rows, sorted so that a bucket's values lie side by side, cost more than they gave.)
 //
 // Measured on MI355X with cold caches, sketch_accumulate by bins and by these lists (us): 853,610 coordinates, n = 14, 5 x 40,514 162 and 130; 1.8 million, n = 17, 3
-// x 56,323 239 and 160; 2.2 million, n = 83, 5 x 39,335 1,890 and 741 (one window); 4.8 million, n = 10, 5 x 207,905 543 and 414; 11.3 million, n = 17, 5 x
-// 192,180 1,977 and 1,282; 32.6 million, n = 11, 7 x 389,885 4,498 and 3,800; by slices (sams_pull.hip) and these lists: a million, n = 43, 5 x 19,287 363
-// and 191; 1.4 million, n = 88, 7 x 15,826 855 and 669.  Of 190 shapes with 0.27 to 60 million coordinates and 9,000 to 650,000 buckets that the rules below
-// send here, 181 are faster, 1.05 to 2.9 times (in the middle 1.35), four alike and five 3 to 5 % slower.
+// x 56,323 239 and 160; 2.2 million, n = 83, 5 x 39,335 1,890 and 741 (one window); 4.3 million, n = 21, 5 x 134,908 930 and 606; 13.6 million, n = 19, 10 x
+// 110,245 4,423 and 3,005; 46 million, n = 8, 5 x 446,747 3,386 and 2,948; by slices (sams_pull.hip) and these lists: a million, n = 43, 5 x 19,287 363
+// and 191; 0.8 million, n = 70, 10 x 11,957 687 and 455.  Of 220 shapes with 0.27 to 60 million coordinates and 9,000 to 650,000 buckets that the rules below
+// send here, 209 are faster, 1.05 to 2.9 times (in the middle 1.35), and of the rest one is 11 % slower (0.29 million) and none of the others more than 5 %.
 #include <math.h>
 #include <stdlib.h>
 #include <string.h>
@@ -51,18 +55,15 @@ constexpr int kPushRing = 8;                  // phases whose words are
 // multiple of 32 every lane of a group would be in one bank (207 instead of 147 us for one hash of eight at three million, n = 8, 5 x 150,001).
 __host__ __device__ __forceinline__ uint32_t push_cell(uint32_t b) { return (b & ~63u) | ((b + ((b >> 6) * 0x9e3779b1u >> 26)) & 63u); }
 static __host__ __device__ __forceinline__ int32_t push_cells(int32_t win) { return (win + kWave - 1) / kWave * kWave; }   // the padding's cells follow
-// A word: sign (bit 0), place in the phase (the next 15 bits, or 14), cell (up to bit 30); bit 31: the lane before has the same bucket and adds this lane's
-// value.  Padding: place 0, a cell of the lane's.
+// A word: sign (bit 0), place in the phase (the next 15 bits, or 14), cell (up to bit 30); bit 31: the word before, the lane's first or the second
+// of the lane before, has the same bucket.  Padding: place 0, a cell of the lane's.
 
 // ------------------------------------------------------------------------------------------
 // plan
 // ------------------------------------------------------------------------------------------
-// Which rows share a copy, and how its phases are sorted: by the windows of its rows, the first row's first.  Where that row's buckets repeat, its window's
-// coordinates are sorted by eighths of the repeat distance before anything else, so that those of a bucket lie near each other.
-constexpr int kPushChunks = 8;
+// Which rows share a copy, and how its phases are sorted: by the windows of its rows, the first row's first.
 struct PushCopies {
     int32_t ncopy;
-    int32_t dist[SAMS_MAX_ROWS];               // per copy: the first row's repeat distance, 0 = none
     int8_t rows[SAMS_MAX_ROWS], row[SAMS_MAX_ROWS][SAMS_MAX_ROWS], of[SAMS_MAX_ROWS];     // rows of a copy; a row's copy
 };
 
@@ -91,7 +92,7 @@ __global__ void __launch_bounds__(kPushThreads)
 k_push_order(HashParams hp, int64_t d, PushCopies pc, int32_t nwin, int32_t win, int32_t span, int32_t nph, uint16_t *__restrict__ order)
 {
     extern __shared__ uint32_t keys[];                               // [span, up to a power of two]
-    const int t = threadIdx.x, q = blockIdx.y, rows = pc.rows[q], dist = pc.dist[q];
+    const int t = threadIdx.x, q = blockIdx.y, rows = pc.rows[q];
     const int64_t l0 = (int64_t)blockIdx.x * span;
     const int lim = d - l0 < span ? (int)(d - l0) : span;
     int all = kPushThreads * 2;
@@ -100,7 +101,6 @@ k_push_order(HashParams hp, int64_t d, PushCopies pc, int32_t nwin, int32_t win,
         uint32_t key = 0;
         for (int z = 0; z < rows && x < lim; ++z) {
             key = key * (uint32_t)nwin + bucket_of(hp, pc.row[q][z], (uint32_t)(l0 + x)) / (uint32_t)win;
-            if (z == 0 && dist) key = key * kPushChunks + (uint32_t)(x % dist * kPushChunks / dist);
         }
         keys[x] = x < lim ? (key << 14) | (uint32_t)x : 0xffffffffu;
     }
@@ -131,8 +131,8 @@ k_push_plan(HashParams hp, int64_t d, int32_t nwin, int32_t win, int32_t span, i
     __shared__ uint32_t ent[kPushEntries], outw[kPushEntries];       // the entries' words, by place and in their slots
     __shared__ uint16_t coord[kPushEntries];                         // their coordinates in the phase
     __shared__ uint16_t multi[kPushEntries], nth[kPushEntries];      // entries that share a bucket; how many of its entries come before one
-    __shared__ uint32_t place[kPushEntries];                         // of a shared bucket's first entry: group, lane among the group's shared; of the others: the first
-    __shared__ uint32_t part[kPushWaves], many[kPushWaves * kPushGroups], before[kPushWaves * kPushGroups + 1];
+    __shared__ uint32_t place[kPushEntries];                         // of a shared bucket's first entry: wavefront, place among its words; of the others: the first
+    __shared__ uint32_t part[kPushWaves], many[kPushWaves], before[kPushWaves * kPushGroups + 1];
     __shared__ uint32_t sh, longest;
     const int bshift = place_bits + 1;
     const int t = threadIdx.x, j = blockIdx.y / nwin, w = blockIdx.y % nwin;
@@ -142,7 +142,7 @@ k_push_plan(HashParams hp, int64_t d, int32_t nwin, int32_t win, int32_t span, i
     const uint32_t b0 = (uint32_t)w * (uint32_t)win;
     for (int q = t; q < win / 2 + 1; q += kPushThreads) cnt[q] = 0u;
     for (int q = t; q < kPushEntries; q += kPushThreads) outw[q] = (uint32_t)(push_cells(win) + q / kPushGroups % kWave) << bshift;
-    if (t < kPushWaves * kPushGroups) many[t] = 0u;
+    if (t < kPushWaves) many[t] = 0u;
     if (t == 0) longest = 0u;
     // the window's coordinates in the order of their places: thread t has the places [t * per, (t + 1) * per) of the phase
     const uint16_t *in_place = order ? order + ((int64_t)pc.of[j] * nph + blockIdx.x) * span : nullptr;
@@ -202,30 +202,39 @@ k_push_plan(HashParams hp, int64_t d, int32_t nwin, int32_t win, int32_t span, i
             if (n) place[k] = first;
         }
         __syncthreads();
-        // The shared buckets in the order of their first entries, as if in one line that is cut every 64 - (most entries of a bucket - 1): a bucket goes
-        // with all its entries to the group in whose piece it starts, and none is longer than what the group has left
+        // The shared buckets in the order of their first entries, as if in one line that is cut every 128 - (most entries of a bucket - 1): a bucket
+        // goes with all its entries to the wavefront in whose piece it starts, and none is longer than what is left of the 128 words.  Where there is
+        // room, each starts with a lane's first word.
         uint32_t len[kPushGroups], sum = 0;
 #pragma unroll
         for (int z = 0; z < kPushGroups; ++z) {
             const uint32_t k = t * kPushGroups + z;
             len[z] = k < nmulti && nth[k] == 0 ? members(multi[k]) : 0u;
-            sum += len[z];
+            sum += (len[z] + 1) & ~1u;
             if (len[z] > 1) atomicMax(&longest, len[z]);
         }
         uint32_t pos = block_exclusive_scan<kPushThreads>(sum, part);
-        const uint32_t piece = longest < (uint32_t)kWave ? (uint32_t)kWave + 1u - longest : 1u;
-        bool fits = longest < (uint32_t)kWave;
+        if (t == kPushThreads - 1) sh = pos + sum;
+        __syncthreads();
+        const bool even = sh + (total - nmulti) + kPushWaves * longest <= (uint32_t)kPushEntries;
+        if (!even) {
+            sum = 0;
+            for (int z = 0; z < kPushGroups; ++z) sum += len[z];
+            pos = block_exclusive_scan<kPushThreads>(sum, part);
+        }
+        const uint32_t span_of = kWave * kPushGroups, piece = longest < span_of ? (span_of + 1 + even - longest) & ~1u : 2u;
+        bool fits = longest < span_of;
 #pragma unroll
         for (int z = 0; z < kPushGroups; ++z) {
-            const uint32_t k = t * kPushGroups + z, group = pos / piece, f = pos % piece;
+            const uint32_t k = t * kPushGroups + z, wave = pos / piece, f = pos % piece;
             if (!len[z]) continue;
-            if (group < (uint32_t)(kPushWaves * kPushGroups)) {
-                place[k] = group | (f << 8);
-                atomicMax(&many[group], f + len[z]);
+            if (wave < (uint32_t)kPushWaves) {
+                place[k] = wave | (f << 8);
+                atomicMax(&many[wave], f + len[z]);
             } else {
                 fits = false;
             }
-            pos += len[z];
+            pos += even ? (len[z] + 1) & ~1u : len[z];
         }
         // (a hash that leaves no room for the others either needs shorter phases)
         if (!__syncthreads_and(fits)) {
@@ -234,11 +243,11 @@ k_push_plan(HashParams hp, int64_t d, int32_t nwin, int32_t win, int32_t span, i
         }
         if (t == 0) atomicAdd(status + 1, nmulti);
     }
-    // the others fill what room the groups have, in order
+    // the others fill the lanes that the shared buckets leave, in order, a wavefront's first words before its second
     const uint32_t singles = total - nmulti;
     if (t < kWave) {
         constexpr int kAll = kPushWaves * kPushGroups;
-        const uint32_t room = t < kAll ? (uint32_t)kWave - many[t] : 0u;
+        const uint32_t room = t < kAll ? (uint32_t)kWave - (many[t / kPushGroups] + 1) / 2 : 0u;
         const uint32_t upto = wave_inclusive_scan(room);
         if (t < kAll) before[t + 1] = upto;
         if (t == 0) before[0] = 0u;
@@ -249,7 +258,6 @@ k_push_plan(HashParams hp, int64_t d, int32_t nwin, int32_t win, int32_t span, i
         return;
     }
     auto word_of = [&](uint32_t e) { return (push_cell(bucket(e)) << bshift) | (ent[e] & ((1u << bshift) - 1u)); };
-    auto slot = [&](uint32_t group, uint32_t lane) { return ((group / kPushGroups) * kWave + lane) * kPushGroups + group % kPushGroups; };
     {
         uint32_t s = (uint32_t)(t * kPushGroups) - multi_before, group = 0;
 #pragma unroll
@@ -257,14 +265,14 @@ k_push_plan(HashParams hp, int64_t d, int32_t nwin, int32_t win, int32_t span, i
             const uint32_t e = t * kPushGroups + z;
             if (e >= total || is_multi[z]) continue;
             while (before[group + 1] <= s) ++group;                  // there is room for all: the search ends
-            outw[slot(group, s - before[group])] = word_of(e);
+            const uint32_t wave = group / kPushGroups, lane = (many[wave] + 1) / 2 + s - before[group];
+            outw[(wave * kWave + lane) * kPushGroups + group % kPushGroups] = word_of(e);
             ++s;
         }
     }
     for (uint32_t k = t; k < nmulti; k += kPushThreads) {
-        const uint32_t n = nth[k], p = n ? place[place[k]] : place[k], group = p & 255u, room = before[group + 1] - before[group];
-        const uint32_t ahead = singles <= before[group] ? 0u : (singles - before[group] < room ? singles - before[group] : room);
-        outw[slot(group, ahead + (p >> 8) + n)] = word_of(multi[k]) | (n ? 0x80000000u : 0u);
+        const uint32_t n = nth[k], p = n ? place[place[k]] : place[k];
+        outw[(p & 255u) * (kWave * kPushGroups) + (p >> 8) + n] = word_of(multi[k]) | (n ? 0x80000000u : 0u);
     }
     __syncthreads();
     for (int q = t; q < kPushEntries; q += kPushThreads)
@@ -286,6 +294,11 @@ struct PushArgs {
 
 __device__ __forceinline__ void push_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+__device__ __forceinline__ float from_lane_before(float y)
+{
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(y), 0x138, 0xf, 0xf, false));
+}
+
 // The word and value rings are filled by unconditional loads in a fixed order, straight into the registers that the loop carries, so that
 // the compiler waits for exactly the oldest; loads past the vector's end fetch padding words (nalloc), whose place is 0.
 template <int PLACE>
@@ -294,7 +307,9 @@ k_sketch_push(PushArgs a)
 {
     extern __shared__ float tbl[];                                   // [push_cells(win) + 64]
     // Units in the order row, window, worker; the 8 XCDs, to which workgroups are dealt round-robin, take `share` at a time: workers with the same words side
-    // by side, and the windows of a row, which may take longer than others', on all XCDs
+    // by side, and the windows of a row, which may take longer than others', on all XCDs.  Out of copies by 16 (25 million, n = 16, 10 x 100,000 with 1, 4 and
+    // 16: 3,882, 3,907 and 3,539 us); out of the vectors, where the windows' workgroups read the same lines, by 4 (2.2 million, n = 83: with 8 and 16 up to 940
+    // instead of 755).
     const int32_t slot = (int32_t)(blockIdx.x / 8), unit = (slot / a.share * 8 + (int32_t)(blockIdx.x % 8)) * a.share + slot % a.share;
     if (unit >= a.n * a.r * a.nwin) return;
     const int32_t i = unit % a.n, list = unit / a.n, j = a.row[list / a.nwin], jw = j * a.nwin + list % a.nwin;
@@ -323,14 +338,12 @@ k_sketch_push(PushArgs a)
         ++vph;
     };
     for (int32_t b = t; b < push_cells(a.win) + kWave; b += kPushThreads) tbl[b] = 0.f;
+    // in the order in which the phases go on (or the first phases of a turn wait for values that are not theirs)
 #pragma unroll
     for (int z = 0; z < kPushRing; ++z) {
         load_words(z);
         __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int z = 0; z < kPushVals; ++z) {
-        load_values(z, z);
+        if (z >= kPushRing - kPushVals) load_values(z - (kPushRing - kPushVals), z - (kPushRing - kPushVals));
         __builtin_amdgcn_sched_barrier(0);
     }
     auto phase = [&](auto zc) {
@@ -356,29 +369,28 @@ k_sketch_push(PushArgs a)
             vv[g] = __uint_as_float(__float_as_uint(vv[g]) ^ (ww[g] << 31));
             x[g] = *cell[g];
         }
-#pragma unroll
-        for (int g = 0; g < G; ++g) x[g] = x[g] + vv[g];
-        uint64_t follows[G], any = 0;
-#pragma unroll
-        for (int g = 0; g < G; ++g) any |= follows[g] = __ballot((int)ww[g] < 0);
-        if (!any) {
-#pragma unroll
-            for (int g = 0; g < G; ++g) *cell[g] = x[g];
-            asm volatile("; no bucket twice" ::: "memory");          // (kept apart from the other case)
+        // a word that follows takes its bucket's sum from the word before: its lane's first word, or the second of the lane before
+        static_assert(G == 2, "a lane's two words");
+        const uint64_t first = __ballot((int)ww[0] < 0);
+        const bool second = (int)ww[1] < 0;
+        x[0] = x[0] + vv[0];
+        const float x1 = second ? x[0] : x[1];
+        if (!first) {
+            *cell[0] = x[0];
+            *cell[1] = x1 + vv[1];
+            asm volatile("; in one lane" ::: "memory");              // (kept apart from the other case)
         } else {
-            // a bucket's first lane adds the values of the lanes that follow, one after the other: all lanes shift, by a lane each time, and those with
-            // that many followers add
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                uint64_t more = follows[g] >> 1;
-                float y = vv[g];
-                for (int q = 2; more; ++q) {
-                    y = __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(y), 0x130, 0xf, 0xf, false));
-                    x[g] = __builtin_amdgcn_inverse_ballot_w64(more) ? x[g] + y : x[g];
-                    more &= follows[g] >> q;
-                }
-                if (!__builtin_amdgcn_inverse_ballot_w64(follows[g])) *cell[g] = x[g];
+            const uint64_t on = __ballot(second);
+            const float r1 = x[1];
+            x[1] = x1 + vv[1];
+            // by one lane more each time; those that are there do the same again
+            for (uint64_t far = first; far; far = first & (far & on) << 1) {
+                const float y = from_lane_before(x[1]);
+                x[0] = __builtin_amdgcn_inverse_ballot_w64(first) ? y + vv[0] : x[0];
+                x[1] = (second ? x[0] : r1) + vv[1];
             }
+            if (!second) *cell[0] = x[0];
+            if (!__builtin_amdgcn_inverse_ballot_w64(first >> 1)) *cell[1] = x[1];
         }
     };
     // whole turns of the ring, with no way out in between (or the compiler waits for all loads at the turn's end), then what is left
@@ -426,8 +438,9 @@ static int32_t push_span(int64_t c, int32_t win, bool copies, double sigmas)
 }
 
 // rows that a copy has room for: runs of a phase's coordinates that have everything they are sorted by in common keep 20 places
-static int32_t push_rows(int32_t nwin, int32_t span, int64_t bins)
+static int32_t push_rows(int32_t nwin, int32_t span)
 {
+    int64_t bins = 1;
     int32_t rows = 0;
     while (nwin > 1 && bins * nwin <= 1024 && span / (bins * nwin) >= 20) {
         bins *= nwin;
@@ -436,37 +449,31 @@ static int32_t push_rows(int32_t nwin, int32_t span, int64_t bins)
     return rows;
 }
 
-// the rows' copies: every row whose buckets repeat within a phase is the first of one
-static PushCopies push_copies(const sams_ctx *ctx, int32_t nwin, int32_t span, const uint32_t *repeat)
+// The rows in the order of their workgroups, and in what copies: those whose buckets repeat first (they take longer), and a copy's rows side by side, so that
+// what they read of it at about the same time comes from memory once.
+static PushCopies push_copies(const sams_ctx *ctx, int32_t nwin, int32_t span, const uint32_t *repeat, int8_t *order)
 {
     PushCopies pc = {};
-    const int32_t most = push_rows(nwin, span, 1), most_repeat = push_rows(nwin, span, kPushChunks);
-    if (most < 1) return pc;
-    auto open = [&](int32_t j, int32_t dist) {
-        pc.dist[pc.ncopy] = dist;
-        pc.row[pc.ncopy][0] = (int8_t)j;
-        pc.rows[pc.ncopy] = 1;
-        pc.of[j] = (int8_t)pc.ncopy++;
-    };
-    for (int32_t j = 0; j < ctx->r; ++j)
-        if (repeat[j] < (uint32_t)span && most_repeat >= 1) open(j, (int32_t)repeat[j]);
-    for (int32_t j = 0; j < ctx->r; ++j) {
-        if (repeat[j] < (uint32_t)span && most_repeat >= 1) continue;
-        int32_t q = 0;
-        while (q < pc.ncopy && pc.rows[q] >= (pc.dist[q] ? most_repeat : most)) ++q;
-        if (q == pc.ncopy) {
-            open(j, 0);
-        } else {
-            pc.row[q][pc.rows[q]++] = (int8_t)j;
-            pc.of[j] = (int8_t)q;
+    const int32_t most = push_rows(nwin, span);
+    int32_t at = 0;
+    if (most >= 1) pc.ncopy = (ctx->r + most - 1) / most;
+    for (int repeats = 1; repeats >= 0; --repeats)
+        for (int32_t j = 0; j < ctx->r; ++j) {
+            if ((repeat[j] < (uint32_t)span) != (repeats == 1)) continue;
+            const int32_t q = at * pc.ncopy / ctx->r;                // (as many rows in each, or one less)
+            order[at++] = (int8_t)j;
+            if (pc.ncopy) {
+                pc.row[q][pc.rows[q]++] = (int8_t)j;
+                pc.of[j] = (int8_t)q;
+            }
         }
-    }
     return pc;
 }
 
 // What a sketch should take, in ns.  Workgroups run in rounds of 256, one per compute unit.  A phase out of the vectors takes the longer the more windows share
-// their lines (cold caches; 310 to 400 with one window, 530 to 620 with two, up to 690 with four); out of copies 300 to 480 by its entries, and less where fewer
-// than 256 run (11.2 million, n = 8, 5 x 262,144, nine windows, 360 workgroups: 684 phases in 457 us).  Rows that repeat take up to a third longer.
+// their lines (cold caches; 310 to 400 with one window, 530 to 620 with two, up to 690 with four).  Out of copies it takes 300 at least and 340 to 430 with
+// 1,870 entries where all units are busy, less where few are (of 60 timings, 0.6 to 5 rounds, 9 in 10 within 15 %), and up to 500 where a copy has more than four
+// rows, whose last ones read runs of 23 values; with rows that repeat 1.05 to 1.3 times that.  Copies are written at 5 TB/s, by the head at 4.0 to 5.
 static double push_cost(const sams_ctx *ctx, int32_t nwin, bool copies, bool fused, const uint32_t *repeat)
 {
     const int32_t win = push_win(ctx->c, nwin);
@@ -482,11 +489,12 @@ static double push_cost(const sams_ctx *ctx, int32_t nwin, bool copies, bool fus
         const double phase[] = {340, 560, 640, 690, 850};
         return 8000 + (full + (rest ? 1 : 0)) * nph * (nwin <= 5 ? phase[nwin - 1] : 350 + 100 * nwin) * (repeats ? 1.3 : 1.0);
     }
-    const PushCopies pc = push_copies(ctx, nwin, span, repeat);
-    if (!pc.ncopy) return 1e30;
-    const double one = 130 + 0.19 * entries > 300 ? 130 + 0.19 * entries : 300, part = rest * one / 256;
-    return 8000 + nph * (full * one + (rest ? (part > 290 ? part : 290) : 0)) * (repeats ? 1.12 : 1.0) +
-           (fused ? nd * pc.ncopy * 4 / 5100.0 : 6000 + nd * (pc.ncopy + 1) * 4 / 5000.0);
+    const int32_t most = push_rows(nwin, span);
+    if (most < 1) return 1e30;
+    const int32_t ncopy = (ctx->r + most - 1) / most;
+    const double one = 110 + 0.15 * entries > 300 ? 110 + 0.15 * entries : 300, last = rest ? 290 + 0.075 * entries * rest / 256 : 0;
+    return 8000 + nph * (full * one + last + (most > 4 ? 80 * (full + 1) : 0)) * (repeats ? 1.2 : 1.0) +
+           (fused ? nd * ncopy * 4 / 4300.0 : 6000 + nd * (ncopy + 1) * 4 / 5000.0);
 }
 
 // Whether this shape may push: tables of 10,000 buckets (below, the lists of sams_pull.hip are the faster, and phases have dozens of coordinates for a bucket) to
@@ -546,10 +554,6 @@ int push_create(sams_ctx *ctx, const Tunables &tun, bool first, bool *done)
         if (e != hipSuccess) { g_last_hip_error = (int)e; rc = SAMS_EHIP; break; }
         if (!push_pays(ctx, tun, first, push_choose(ctx, tun, first, repeat, &pp.nwin, &copies))) break;
         pp.win = push_win(ctx->c, pp.nwin);
-        int32_t rows = 0;
-        for (int repeats = 1; repeats >= 0; --repeats)               // the rows whose buckets repeat first
-            for (int32_t j = 0; j < ctx->r; ++j)
-                if ((repeat[j] < (uint32_t)push_span(ctx->c, pp.win, copies, 4.5)) == (repeats == 1)) pp.row[rows++] = (int8_t)j;
         const int place_bits = copies ? 14 : push_place_bits(pp.win);
         pp.kernel = place_bits == 15 ? (const void *)k_sketch_push<15> : (const void *)k_sketch_push<14>;
         e = hipFuncSetAttribute((const void *)k_push_plan, hipFuncAttributeMaxDynamicSharedMemorySize, (kPushMaxWin / 2 + 1) * 4);
@@ -562,8 +566,8 @@ int push_create(sams_ctx *ctx, const Tunables &tun, bool first, bool *done)
             pp.nph = (int32_t)((ctx->d + pp.span - 1) / pp.span);
             pp.nalloc = pp.nph + kPushRing;
             pp.word_bytes = (int64_t)ctx->r * pp.nwin * pp.nalloc * kPushEntries * 4;
+            pc = push_copies(ctx, pp.nwin, pp.span, repeat, pp.row);
             if (copies) {
-                pc = push_copies(ctx, pp.nwin, pp.span, repeat);
                 if (!pc.ncopy) break;
                 pp.ncopy = pc.ncopy;
                 memcpy(pp.copy_of, pc.of, sizeof(pp.copy_of));
@@ -622,7 +626,9 @@ int enqueue_sketch_push(sams_ctx *ctx, const float *u, float *S_workers)
         ctx->plan.staged_u = nullptr;
     }
     PushArgs a = {pp.ncopy ? ctx->plan.stg : u, pp.words, S_workers, ctx->c, pp.ncopy ? (int64_t)pp.nph * pp.span : ctx->d, ctx->n, ctx->r, pp.nwin,
-                  pp.win, pp.span, pp.nph, pp.nalloc, ctx->n < 4 ? ctx->n : 4, {0}, {0}};
+                  pp.win, pp.span, pp.nph, pp.nalloc, 0, {0}, {0}};
+    const int32_t share = pp.ncopy ? 16 : 4;                         // (see the kernel)
+    a.share = ctx->n < share ? ctx->n : share;
     memcpy(a.copy_of, pp.copy_of, sizeof(a.copy_of));
     memcpy(a.row, pp.row, sizeof(a.row));
     const int64_t units = (int64_t)ctx->n * ctx->r * pp.nwin, chunks = (units + a.share - 1) / a.share;
