@@ -471,7 +471,7 @@ static PushCopies push_copies(const sams_ctx *ctx, int32_t nwin, int32_t span, c
 }
 
 // What a sketch should take, in ns.  Workgroups run in rounds of 256, one per compute unit.  A phase out of the vectors takes the longer the more windows share
-// their lines (cold caches; 310 to 400 with one window, 530 to 620 with two, up to 690 with four).  Out of copies it takes 300 at least and 340 to 430 with
+// their lines (cold caches; 310 to 400 with one window, 530 to 620 with two, up to 690 with four).  Out of copies it takes 320 at least and 340 to 430 with
 // 1,870 entries where all units are busy, less where few are (of 60 timings, 0.6 to 5 rounds, 9 in 10 within 15 %), and up to 500 where a copy has more than four
 // rows, whose last ones read runs of 23 values; with rows that repeat 1.05 to 1.3 times that.  Copies are written at 5 TB/s, by the head at 4.0 to 5.
 static double push_cost(const sams_ctx *ctx, int32_t nwin, bool copies, bool fused, const uint32_t *repeat)
@@ -492,7 +492,7 @@ static double push_cost(const sams_ctx *ctx, int32_t nwin, bool copies, bool fus
     const int32_t most = push_rows(nwin, span);
     if (most < 1) return 1e30;
     const int32_t ncopy = (ctx->r + most - 1) / most;
-    const double one = 110 + 0.15 * entries > 300 ? 110 + 0.15 * entries : 300, last = rest ? 290 + 0.075 * entries * rest / 256 : 0;
+    const double one = 110 + 0.15 * entries > 320 ? 110 + 0.15 * entries : 320, last = rest ? 290 + 0.075 * entries * rest / 256 : 0;
     return 8000 + nph * (full * one + last + (most > 4 ? 80 * (full + 1) : 0)) * (repeats ? 1.2 : 1.0) +
            (fused ? nd * ncopy * 4 / 4300.0 : 6000 + nd * (ncopy + 1) * 4 / 5000.0);
 }
@@ -524,12 +524,13 @@ static double push_choose(const sams_ctx *ctx, const Tunables &tun, bool first, 
     return best;
 }
 
-// What the other paths are taken to need, in ns: 0.95 per thousand terms by slices with many pairs (measured 0.93 to 2.3), 1.85 by bins (1.8 to 2.4 from
-// 2 million coordinates on, up to 3 below), 1.57 where the head stages (1.55 to 1.95); a little in favour of what was there.
+// What the other paths are taken to need, in ns: 0.95 per thousand terms by slices with many pairs (measured 0.93 to 2.3), 1.85 by bins: against whole steps by bins
+// the break-even lies at 2.0 to 2.2 of the cost below, with the head fused or not (60 shapes of 0.5 to 43 million coordinates, two hashes each), and up to 3 below
+// two million; a little in favour of what was there.
 static bool push_pays(const sams_ctx *ctx, const Tunables &tun, bool first, double cost)
 {
     if (tun.push_windows) return cost < 1e30;
-    return cost <= 10000 + (double)ctx->n * ctx->r * ctx->d * (first ? 0.95e-3 : (tun.fuse_head == 2 ? 1.57e-3 : 1.85e-3));
+    return cost <= 10000 + (double)ctx->n * ctx->r * ctx->d * (first ? 0.95e-3 : 1.85e-3);
 }
 
 int push_create(sams_ctx *ctx, const Tunables &tun, bool first, bool *done)
