@@ -1359,8 +1359,6 @@ k_bin_collect(const float *__restrict__ lk, const uint16_t *__restrict__ srcp, c
 // k_bin_collect with the median of Sec. II-C and the 1/sqrt(vhat) scaling of Alg. 3 fused in: each thread
 // keeps the R row estimates of its 4 * ITERS coordinates in registers (tiles of at most 4096 * ITERS
 // coordinates), so the per-row estimates never go to memory.
-constexpr int kCollectAhead = 4;
-
 template <int R, int ITERS>
 __global__ void __launch_bounds__(kFusedThreads)
 k_bin_collect_median(const float *__restrict__ lk, const uint16_t *__restrict__ srcp,
@@ -1369,29 +1367,48 @@ k_bin_collect_median(const float *__restrict__ lk, const uint16_t *__restrict__ 
                      int64_t ntile, int64_t rowlen, int gl, uint32_t k, SelState *__restrict__ st,
                      uint32_t *__restrict__ hist)
 {
+    constexpr int AHEAD = R * ITERS < 24 ? ITERS + 1 : ITERS;        // sweeps of a row that are under way at once: its slots, and the runs' padding
+    constexpr bool EARLY = R * ITERS <= 20;                          // (above, there are not enough registers)
     extern __shared__ float rowbuf[];                                // [2][L], at least kHistBins words in all
     const int L = 1 << tile_log2;
     const int64_t tile = blockIdx.x;
     const int64_t l0 = tile << tile_log2;
     float a[R][ITERS][4];
-    // The loads of a row's first kCollectAhead sweeps are issued before the barrier of the row before it, so that
+    // The loads of a row's first AHEAD sweeps are issued before the barrier of the row before it, so that
     // they are in flight while the workgroup (the only one on its compute unit) waits and empties the LDS buffer.
-    // Past the tile's last slot group they read that group again (in bounds; not used).
-    uint2 pk[kCollectAhead];
-    float4 pv[kCollectAhead];
-    uint32_t o0 = 0, o1 = 0;
-    auto issue = [&](int j) {
-        o0 = pbase[(int64_t)j * (ntile + 1) + tile];
-        o1 = pbase[(int64_t)j * (ntile + 1) + tile + 1];
+    // Past the tile's last slot group they read that group again (in bounds; not used).  What says where the values are
+    // is asked for a row earlier (EARLY), and all rows' slots at the start: a row then waits for one load and not for three
+    // in turn (25.6 million, 7 x 1,048,576 440 -> 306 us; 25 million, 10 rows 590 -> 422; 11.2 million, 5 rows 125 -> 108;
+    // 124 million, 5 rows 1,150 -> 1,045; now 4 to 4.5 TB/s).
+    uint2 pk[AHEAD], pk_next[AHEAD];
+    uint32_t at[AHEAD];
+    float4 pv[AHEAD];
+    uint32_t o0[R], o1[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        o0[j] = pbase[(int64_t)j * (ntile + 1) + tile];
+        o1[j] = pbase[(int64_t)j * (ntile + 1) + tile + 1];
+    }
+    auto slot = [&](int j, int s) {
+        const uint32_t o = o0[j] + (uint32_t)(s * kFusedThreads + (int)threadIdx.x) * 4u;
+        return o < o1[j] ? o : o1[j] - 4u;                           // a tile has at least one group of 4 slots
+    };
+    auto find = [&](int j) {
         const uint16_t *sj = srcp + (int64_t)j * rowlen;
         const uint32_t *dj = dst16 + (int64_t)j * (rowlen >> gl);
+#pragma unroll
+        for (int s = 0; s < AHEAD; ++s) {
+            const uint32_t oc = slot(j, s);
+            pk_next[s] = load_stream2(reinterpret_cast<const uint2 *>(sj + oc));
+            at[s] = dj[oc >> gl];
+        }
+    };
+    auto issue = [&](int j) {
         const float *lj = lk + (int64_t)j * rowlen;
 #pragma unroll
-        for (int s = 0; s < kCollectAhead; ++s) {
-            const uint32_t o = o0 + (uint32_t)(s * kFusedThreads + (int)threadIdx.x) * 4u;
-            const uint32_t oc = o < o1 ? o : o1 - 4u;                // a tile has at least one group of 4 slots
-            pk[s] = load_stream2(reinterpret_cast<const uint2 *>(sj + oc));
-            pv[s] = load_stream(reinterpret_cast<const float4 *>(lj + dj[oc >> gl] + (oc & ((1u << gl) - 1u))));
+        for (int s = 0; s < AHEAD; ++s) {
+            pk[s] = pk_next[s];
+            pv[s] = load_stream(reinterpret_cast<const float4 *>(lj + at[s] + (slot(j, s) & ((1u << gl) - 1u))));
         }
     };
     auto place = [&](float *buf, const uint2 packed, const float4 v) {
@@ -1401,26 +1418,33 @@ k_bin_collect_median(const float *__restrict__ lk, const uint16_t *__restrict__ 
         if (s2 != kSrcPad) buf[s2 & 0x7fffu] = (s2 & 0x8000u) ? -v.z : v.z;
         if (s3 != kSrcPad) buf[s3 & 0x7fffu] = (s3 & 0x8000u) ? -v.w : v.w;
     };
+    find(0);
     issue(0);
 #pragma unroll
     for (int j = 0; j < R; ++j) {
         float *buf = rowbuf + (j & 1) * L;
-        const uint32_t b0 = o0, b1 = o1;
+        if (EARLY && j + 1 < R) {
+            find(j + 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
-        for (int s = 0; s < kCollectAhead; ++s)
-            if (b0 + (uint32_t)(s * kFusedThreads + (int)threadIdx.x) * 4u < b1) place(buf, pk[s], pv[s]);
+        for (int s = 0; s < AHEAD; ++s)
+            if (o0[j] + (uint32_t)(s * kFusedThreads + (int)threadIdx.x) * 4u < o1[j]) place(buf, pk[s], pv[s]);
         {
             const uint16_t *sj = srcp + (int64_t)j * rowlen;
             const uint32_t *dj = dst16 + (int64_t)j * (rowlen >> gl);
             const float *lj = lk + (int64_t)j * rowlen;
-            for (uint32_t o = b0 + (uint32_t)(kCollectAhead * kFusedThreads + (int)threadIdx.x) * 4u; o < b1;
+            for (uint32_t o = o0[j] + (uint32_t)(AHEAD * kFusedThreads + (int)threadIdx.x) * 4u; o < o1[j];
                  o += kFusedThreads * 4) {
                 const uint2 packed = load_stream2(reinterpret_cast<const uint2 *>(sj + o));
-                const uint32_t at = dj[o >> gl] + (o & ((1u << gl) - 1u));
-                place(buf, packed, load_stream(reinterpret_cast<const float4 *>(lj + at)));
+                const uint32_t to = dj[o >> gl] + (o & ((1u << gl) - 1u));
+                place(buf, packed, load_stream(reinterpret_cast<const float4 *>(lj + to)));
             }
         }
-        if (j + 1 < R) issue(j + 1);
+        if (j + 1 < R) {
+            if (!EARLY) find(j + 1);
+            issue(j + 1);
+        }
         __syncthreads();   // the other buffer is free again once every thread has passed this barrier
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) {
