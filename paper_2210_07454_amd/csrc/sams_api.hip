@@ -155,9 +155,11 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
     if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, ctx->bitmap, words, 0u);
     if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, ctx->sel, kSelClearWords, 0u);
     bool pushes = false, pulls = false;
-    if (rc == SAMS_OK && ctx->c <= kPullMaxC) rc = push_create(ctx, ctx->tun, true, &pushes);
-    if (rc == SAMS_OK && !pushes) rc = pull_create(ctx, ctx->tun, &pulls);
-    if (rc == SAMS_OK && !pushes && !pulls) rc = push_create(ctx, ctx->tun, false, &pushes);
+    double push_ns = 1e30;
+    if (rc == SAMS_OK) rc = push_estimate(ctx, ctx->tun, &push_ns);
+    if (rc == SAMS_OK) rc = pull_create(ctx, ctx->tun, push_ns, &pulls);
+    if (rc == SAMS_OK && !pulls && push_ns < 1e30) rc = push_create(ctx, ctx->tun, &pushes);
+    if (rc == SAMS_OK && !pulls && !pushes && push_ns < 1e30) rc = pull_create(ctx, ctx->tun, 1e30, &pulls);
     if (rc == SAMS_OK && !pulls && ctx->tun.sketch_path != 1 && (!pushes || (ctx->c > kPlanMinRecoveryC && estimate_wants_plan(ctx))))
         rc = plan_create(ctx, ctx->tun);
     if (rc == SAMS_OK && pushes) {

@@ -27,7 +27,6 @@ extern int g_last_hip_error;
     } while (0)
 
 constexpr int kWave = 64;
-constexpr int64_t kPullMaxC = 1 << 15;             // buckets up to which a context may pull
 constexpr int64_t kPlanMinRecoveryC = 1 << 15;   // buckets above which a context that pushes recovers through a plan
 constexpr int64_t kOrderedSingleBinMaxD = (int64_t)1 << 22;     // largest d sketched in order when c fits one window
 constexpr int kHistBins = 2048;     // first radix digit of the selection: 11 bits, then 10 and 10 (kHistBins / 2 bins)
@@ -384,12 +383,13 @@ int enqueue_gather(sams_ctx *ctx, const float *u, const float *vhat, const int32
 // sams_sketch.hip
 int enqueue_sketch(sams_ctx *ctx, const float *u, float *S_workers);
 // sams_pull.hip
-int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done);
+int pull_create(sams_ctx *ctx, const Tunables &tun, double limit, bool *done);
 void pull_destroy(sams_ctx *ctx);
 int enqueue_sketch_pull(sams_ctx *ctx, const float *u, float *S_workers);
 // sams_push.hip
 // first: whether one window, and the vectors themselves, are so much the fastest that no other path need be looked at
-int push_create(sams_ctx *ctx, const Tunables &tun, bool first, bool *done);
+int push_estimate(sams_ctx *ctx, const Tunables &tun, double *ns);
+int push_create(sams_ctx *ctx, const Tunables &tun, bool *done);
 void push_destroy(sams_ctx *ctx);
 int enqueue_sketch_push(sams_ctx *ctx, const float *u, float *S_workers);
 // sams_plan.hip

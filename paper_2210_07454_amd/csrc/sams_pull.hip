@@ -419,7 +419,7 @@ k_pull_sum(const float *__restrict__ part, float *__restrict__ S, int64_t cells,
 // tile's 64 buckets are padding but for a tenth (13,308 coordinates and a step or two for each of 512 slices), and their making would
 // not fit in LDS; the lists of longer vectors take gigabytes.
 constexpr int64_t kPullLongD = 1000000;       // shorter vectors always pull: both paths are launches and latencies
-constexpr int64_t kPullWide = 1 << 14, kPullWideMinD = 1 << 18;
+constexpr int64_t kPullWide = 1 << 14, kPullMaxC = 1 << 15, kPullWideMinD = 1 << 18;
 static bool pull_shape(const sams_ctx *ctx, const Tunables &tun)
 {
     if (tun.sketch_path != 0 || tun.estimate_path == 2 || tun.win_log2 || tun.tile_log2 || tun.chunk_log2 || tun.acc_threads ||
@@ -516,8 +516,8 @@ static bool pull_declines(const sams_ctx *ctx, int32_t ntile)
     return 25000 + 86 * ctx->d / ctx->c + pairs * ctx->d * 16 / 10000 < ((int64_t)ntile + 12) * 820;
 }
 
-// SAMS_OK with *done saying whether the context pulls; device memory that cannot be had means it does not
-int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
+// SAMS_OK with *done saying whether the context pulls; device memory that cannot be had means it does not.  limit: what another path is taken to need, in ns
+int pull_create(sams_ctx *ctx, const Tunables &tun, double limit, bool *done)
 {
     *done = false;
     PullPlan pp = {};
@@ -595,6 +595,7 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, bool *done)
                 steps = all;
             }
         }
+        if (!tun.pull_lists && (double)cost > limit) break;
         if (wide && !tun.pull_lists && cost > 25000 + (int64_t)ctx->n * ctx->r * ctx->d * 7 / 4000) break;   // (see pull_declines)
         if (steps * kWave > 12.0 * ctx->r * (double)ctx->d + 8.0 * kWave * (double)rows * nslice) break;   // lists that are mostly padding
         if (counted > 1 && !count(1)) break;

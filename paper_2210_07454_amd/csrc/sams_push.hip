@@ -473,27 +473,30 @@ static PushCopies push_copies(const sams_ctx *ctx, int32_t nwin, int32_t span, c
 // What a sketch should take, in ns.  Workgroups run in rounds of 256, one per compute unit.  A phase out of the vectors takes the longer the more windows share
 // their lines (cold caches; 310 to 400 with one window, 530 to 620 with two, up to 690 with four).  Out of copies it takes 320 at least and 340 to 430 with
 // 1,870 entries where all units are busy, less where few are (of 60 timings, 0.6 to 5 rounds, 9 in 10 within 15 %), and up to 500 where a copy has more than four
-// rows, whose last ones read runs of 23 values; with rows that repeat 1.05 to 1.3 times that.  Copies are written at 5 TB/s, by the head at 4.0 to 5.
+// rows, whose last ones read runs of 23 values; with rows that repeat 1.05 to 1.3 times that, also where a phase has dozens of entries for a bucket (0.94
+// million, n = 54, 10 x 31,212 with a distance of 82 in phases of 2,016 469 us, by bins 1,016; 25 million, n = 16, 10 x 100,000 with 202 in 7,488 5.3 ms, by
+// bins 7.5).  Copies are written at 5 TB/s, by the head at 4.0 to 5.
 static double push_cost(const sams_ctx *ctx, int32_t nwin, bool copies, bool fused, const uint32_t *repeat)
 {
     const int32_t win = push_win(ctx->c, nwin);
     const int32_t span = push_span(ctx->c, win, copies, 4.5);
     const double nph = (double)((ctx->d + span - 1) / span), entries = (double)span * win / ctx->c, nd = (double)ctx->n * ctx->d;
     const int64_t units = (int64_t)ctx->n * ctx->r * nwin, full = units / 256, rest = units % 256;
-    bool repeats = false;
+    double longer = 1.0;
     for (int32_t j = 0; j < ctx->r; ++j) {
-        if (repeat[j] < (uint32_t)span / 24) return 1e30;            // (dozens of a phase's entries in a bucket)
-        repeats |= repeat[j] < (uint32_t)span;
+        if (repeat[j] < (uint32_t)span / 64) return 1e30;            // (more of a phase's entries in a bucket than a wavefront has room for)
+        if (repeat[j] < (uint32_t)span && longer < 1.2) longer = 1.2;
+        if (repeat[j] < (uint32_t)span / 24) longer = 1.35;
     }
     if (!copies) {
         const double phase[] = {340, 560, 640, 690, 850};
-        return 8000 + (full + (rest ? 1 : 0)) * nph * (nwin <= 5 ? phase[nwin - 1] : 350 + 100 * nwin) * (repeats ? 1.3 : 1.0);
+        return 8000 + (full + (rest ? 1 : 0)) * nph * (nwin <= 5 ? phase[nwin - 1] : 350 + 100 * nwin) * longer;
     }
     const int32_t most = push_rows(nwin, span);
     if (most < 1) return 1e30;
     const int32_t ncopy = (ctx->r + most - 1) / most;
     const double one = 110 + 0.15 * entries > 320 ? 110 + 0.15 * entries : 320, last = rest ? 290 + 0.075 * entries * rest / 256 : 0;
-    return 8000 + nph * (full * one + last + (most > 4 ? 80 * (full + 1) : 0)) * (repeats ? 1.2 : 1.0) +
+    return 8000 + nph * (full * one + last + (most > 4 ? 80 * (full + 1) : 0)) * longer +
            (fused ? nd * ncopy * 4 / 4300.0 : 6000 + nd * (ncopy + 1) * 4 / 5000.0);
 }
 
@@ -509,12 +512,12 @@ static bool push_shape(const sams_ctx *ctx, const Tunables &tun)
 }
 
 // the fastest number of windows, and whether out of copies; 1e30: none
-static double push_choose(const sams_ctx *ctx, const Tunables &tun, bool first, const uint32_t *repeat, int32_t *windows, bool *copies)
+static double push_choose(const sams_ctx *ctx, const Tunables &tun, const uint32_t *repeat, int32_t *windows, bool *copies)
 {
     double best = 1e30;
     for (int mode = 0; mode < 2; ++mode)
         for (int32_t nwin = (int32_t)((ctx->c + kPushMaxWin - 1) / kPushMaxWin); nwin <= kPushMostWin; ++nwin) {
-            if (tun.push_windows ? tun.push_windows != mode * 100 + nwin : first && (nwin > 1 || mode)) continue;
+            if (tun.push_windows && tun.push_windows != mode * 100 + nwin) continue;
             const double cost = push_cost(ctx, nwin, mode == 1, tun.fuse_head == 2, repeat);
             if (cost >= best) continue;
             best = cost;
@@ -524,36 +527,70 @@ static double push_choose(const sams_ctx *ctx, const Tunables &tun, bool first, 
     return best;
 }
 
-// What the other paths are taken to need, in ns: 0.95 per thousand terms by slices with many pairs (measured 0.93 to 2.3), 1.85 by bins: against whole steps by bins
-// the break-even lies at 2.0 to 2.2 of the cost below, with the head fused or not (60 shapes of 0.5 to 43 million coordinates, two hashes each), and up to 3 below
-// two million; a little in favour of what was there.
-static bool push_pays(const sams_ctx *ctx, const Tunables &tun, bool first, double cost)
+// Whether bins are taken to need more: 1.85 ns per thousand terms.  Against whole steps by bins the break-even lies at 2.0 to 2.2 of the cost above, with the head
+// fused or not (60 shapes of 0.5 to 43 million coordinates, two hashes each), and up to 3 below two million.
+static bool push_pays(const sams_ctx *ctx, const Tunables &tun, double cost)
 {
-    if (tun.push_windows) return cost < 1e30;
-    return cost <= 10000 + (double)ctx->n * ctx->r * ctx->d * (first ? 0.95e-3 : 1.85e-3);
+    return tun.push_windows ? cost < 1e30 : cost <= 10000 + (double)ctx->n * ctx->r * ctx->d * 1.85e-3;
 }
 
-int push_create(sams_ctx *ctx, const Tunables &tun, bool first, bool *done)
+// every row's repeat distance below 2^15, from the device
+static int push_repeats(sams_ctx *ctx, uint32_t *repeat)
+{
+    uint32_t *d_repeat = nullptr;
+    if (hipMalloc((void **)&d_repeat, SAMS_MAX_ROWS * 4) != hipSuccess) {
+        (void)hipGetLastError();
+        return SAMS_ENOMEM;
+    }
+    {
+        ProfScope ps(ctx, KID_PLAN_BUILD);
+        hipLaunchKernelGGL(k_push_repeat, dim3((unsigned)ctx->r), dim3(1024), 0, ctx->stream, ctx->hp, 1 << 15, d_repeat);
+    }
+    hipError_t e = hipMemcpyAsync(repeat, d_repeat, (size_t)ctx->r * 4, hipMemcpyDeviceToHost, ctx->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+    (void)hipFree(d_repeat);
+    if (e == hipSuccess) return SAMS_OK;
+    g_last_hip_error = (int)e;
+    return SAMS_EHIP;
+}
+
+// *ns: what a sketch should take this way (out of copies a little more: slices gain more from warm caches), 1e30 where bins are taken to need less or the shape
+// cannot.  Slices (sams_pull.hip) go first where they are taken to
+// need less.  Of 45 shapes of 10,000 to 32,768 buckets and 0.3 to 4.3 million coordinates, 13 change from slices to this: two take 2 to 3 % longer and eleven
+// less, 1.05 to 2.2 times (us, cold caches: 2.1 million, n = 25, 7 x 29,263 770 and 353; 1.6 million, n = 6, 5 x 14,952 157 and 118; 0.57 million, n = 69, 3 x
+// 21,015 159 and 127); of the 18 others that could, the slices are faster at 14, up to 2 times, and at the rest this is by 1 to 4 %.
+int push_estimate(sams_ctx *ctx, const Tunables &tun, double *ns)
+{
+    *ns = 1e30;
+    if (!push_shape(ctx, tun)) return SAMS_OK;
+    int32_t windows;
+    bool copies;
+    uint32_t repeat[SAMS_MAX_ROWS];
+    for (uint32_t &x : repeat) x = 0x7fffffffu;
+    if (!push_pays(ctx, tun, push_choose(ctx, tun, repeat, &windows, &copies))) return SAMS_OK;   // not even with the best of hashes
+    const int rc = push_repeats(ctx, repeat);
+    if (rc == SAMS_ENOMEM) return SAMS_OK;
+    const double cost = push_choose(ctx, tun, repeat, &windows, &copies);
+    if (rc == SAMS_OK && push_pays(ctx, tun, cost)) *ns = tun.push_windows ? 0 : (copies ? cost * 1.3 : cost);
+    return rc;
+}
+
+int push_create(sams_ctx *ctx, const Tunables &tun, bool *done)
 {
     *done = false;
-    if (!push_shape(ctx, tun)) return SAMS_OK;
     PushPlan pp = {};
+    PushCopies pc = {};
     bool copies = false;
     uint32_t *status = nullptr, h_status[4] = {0, 0, 0, 0}, repeat[SAMS_MAX_ROWS];
-    for (uint32_t &x : repeat) x = 0x7fffffffu;
-    if (!push_pays(ctx, tun, first, push_choose(ctx, tun, first, repeat, &pp.nwin, &copies))) return SAMS_OK;   // not even with the best of hashes
-    PushCopies pc = {};
     int rc = SAMS_OK;
     do {
-        if (hipMalloc((void **)&status, (4 + SAMS_MAX_ROWS) * 4) != hipSuccess) break;
-        {
-            ProfScope ps(ctx, KID_PLAN_BUILD);
-            hipLaunchKernelGGL(k_push_repeat, dim3((unsigned)ctx->r), dim3(1024), 0, ctx->stream, ctx->hp, 1 << 15, status + 4);
+        hipError_t e;
+        rc = push_repeats(ctx, repeat);
+        if (rc != SAMS_OK) {
+            if (rc == SAMS_ENOMEM) rc = SAMS_OK;
+            break;
         }
-        hipError_t e = hipMemcpyAsync(repeat, status + 4, (size_t)ctx->r * 4, hipMemcpyDeviceToHost, ctx->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-        if (e != hipSuccess) { g_last_hip_error = (int)e; rc = SAMS_EHIP; break; }
-        if (!push_pays(ctx, tun, first, push_choose(ctx, tun, first, repeat, &pp.nwin, &copies))) break;
+        if (push_choose(ctx, tun, repeat, &pp.nwin, &copies) >= 1e30 || hipMalloc((void **)&status, 4 * 4) != hipSuccess) break;
         pp.win = push_win(ctx->c, pp.nwin);
         const int place_bits = copies ? 14 : push_place_bits(pp.win);
         pp.kernel = place_bits == 15 ? (const void *)k_sketch_push<15> : (const void *)k_sketch_push<14>;

@@ -75,9 +75,9 @@ def repeating(r, c, dist, rows):
     return hp
 
 
-# two, a few and some twenty coordinates of a phase in a bucket; so many that the rows keep the binned path
+# two, a few and dozens of coordinates of a phase in a bucket; so many that the rows keep the binned path
 @pytest.mark.parametrize("windows", [1, 3, 5, 103, 105])
-@pytest.mark.parametrize("dist,rows", [(3_000, (1,)), (1_500, (0, 2)), (601, (2,)), (200, (1,)), (97, (0,)), (5, (1,)), (1, (0, 1))])
+@pytest.mark.parametrize("dist,rows", [(3_000, (1,)), (1_500, (0, 2)), (601, (2,)), (200, (1,)), (97, (0,)), (40, (1,)), (5, (1,)), (1, (0, 1))])
 def test_buckets_that_repeat_within_a_phase(dist, rows, windows):
     d, n, r, c = 50_021, 3, 3, 20_000
     used = check(d, n, r, c, repeating(r, c, dist, rows), windows)
@@ -96,7 +96,7 @@ def test_infinities_and_nan_reach_their_cells_only(windows):
 # where the paths are chosen: by each of them the same bits, and the one that is meant
 @pytest.mark.parametrize("d,n,r,c,kernel", [
     (262_144, 84, 5, 12_000, "k_sketch_push"), (262_143, 84, 5, 12_000, "k_sketch_pull"), (262_144, 84, 5, 10_000, "k_sketch_pull"),
-    (300_001, 2, 2, 300_001, "k_bin_accumulate"), (400_003, 40, 5, 32_769, "k_sketch_push"), (1_000_001, 9, 5, 100_003, "k_sketch_push")])
+    (400_009, 6, 3, 20_000, "k_sketch_pull"), (300_001, 2, 2, 300_001, "k_bin_accumulate"), (400_003, 40, 5, 32_769, "k_sketch_push"), (1_000_001, 9, 5, 100_003, "k_sketch_push")])
 def test_the_chosen_path(d, n, r, c, kernel):
     assert kernel in check(d, n, r, c, inputs.hash_params(r, seed=3), 0)
 
