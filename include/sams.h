@@ -57,7 +57,7 @@ typedef struct sams_ctx sams_ctx;
  * Allocates the context's device scratch; sams_scratch_bytes reports the total:
  *   always            4d bytes for the estimates, d/8 for the index bitmap, small selection state
  *   c above one LDS window, or d <= 2^22: the sketch plan and its staging buffer, 4*r*d + 4*n*r*d bytes and their padding
- *   10000 < c <= 652800 and 2^18 <= d <= 2^26, where it is the faster: lists, 4.4*r*d bytes (up to 8*r*d), and, in place of the staging
+ *   10000 < c <= 652800 and 2^18 <= d <= 2^26 (2^22 for c <= 2^15), where it is the faster: lists, 4.4*r*d bytes (up to 8*r*d), and, in place of the staging
  *                     buffer, one of 4*r*d bytes or of (4*n + 2)*d bytes for one to r sorted copies of the vectors
  *   128 <= c <= 32768 (16384 for d < 2^18) and d <= 2^26, in their place: lists, 2 to 15 bytes per row and coordinate by the
  *                     hash (one that needs more than 24 + c/832 goes the other way), and above d = 2^22 up to 128 tables of
@@ -142,7 +142,7 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
  *                 set) the shape is one that the other path is faster for (few rows and workers, up to 4096 buckets, d of a million
  *                 or more; above 16384 buckets, lists so long that they are estimated to take longer).  "fuse_head" then has
  *                 nothing to stage and changes nothing.  A table of more than 10000 buckets, up to 16 windows of 40800, under a vector of
- *                 2^18 to 2^26 coordinates goes a third way, in the same order, where that is estimated to be the fastest (see
+ *                 2^18 to 2^26 coordinates (2^22 up to 2^15 buckets) goes a third way, in the same order, where that is estimated to be the fastest (see
  *                 "push_windows"): lists name the values of every (row, window), which are picked out of the vectors or out of sorted
  *                 copies of them ("fuse_head" 2 then stages those), unless one of the settings above, "stage_interleave", "run_pad",
  *                 "acc_wide" or "fuse_head" 1 ask for the binned path; 1: one global atomic add per term (no plan and no staging); 2: the

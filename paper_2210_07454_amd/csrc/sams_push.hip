@@ -508,6 +508,7 @@ static bool push_shape(const sams_ctx *ctx, const Tunables &tun)
         tun.stage_interleave || tun.run_pad != 16 || tun.acc_wide != 2 || tun.fuse_head == 1)
         return false;                                                // the caller asks for the binned path or for a shape of it
     if (ctx->c > kPushMostWin * (int64_t)kPushMaxWin || ctx->d > 1 << 26) return false;
+    if (!tun.push_windows && ctx->c <= 1 << 15 && ctx->d > kOrderedSingleBinMaxD) return false;   // sums in parts, which the others give there, are more precise
     return tun.push_windows ? tun.push_windows > 0 : ctx->c > 10000 && ctx->d >= 1 << 18;
 }
 

@@ -96,7 +96,7 @@ def test_infinities_and_nan_reach_their_cells_only(windows):
 # where the paths are chosen: by each of them the same bits, and the one that is meant
 @pytest.mark.parametrize("d,n,r,c,kernel", [
     (262_144, 84, 5, 12_000, "k_sketch_push"), (262_143, 84, 5, 12_000, "k_sketch_pull"), (262_144, 84, 5, 10_000, "k_sketch_pull"),
-    (400_009, 6, 3, 20_000, "k_sketch_pull"), (300_001, 2, 2, 300_001, "k_bin_accumulate"), (400_003, 40, 5, 32_769, "k_sketch_push"), (1_000_001, 9, 5, 100_003, "k_sketch_push")])
+    (400_009, 6, 3, 20_000, "k_sketch_pull"), (2 ** 22, 20, 5, 32_768, "k_sketch_push"), (300_001, 2, 2, 300_001, "k_bin_accumulate"), (400_003, 40, 5, 32_769, "k_sketch_push"), (1_000_001, 9, 5, 100_003, "k_sketch_push")])
 def test_the_chosen_path(d, n, r, c, kernel):
     assert kernel in check(d, n, r, c, inputs.hash_params(r, seed=3), 0)
 
@@ -160,3 +160,12 @@ def test_replayed_graph_equals_eager():
                     stream.synchronize()
                     assert torch.equal(S, ref)
                     ctx.sketch_accumulate(u, ref)
+
+
+def test_sums_in_parts_stay_in_parts():
+    """above 2^22 coordinates a table of one LDS window is summed in parts, nearer to the exact sums than one after the other"""
+    d, n, r, c = 2 ** 22 + 7, 9, 3, 32_768
+    hp = inputs.hash_params(r, seed=4)
+    u, S = torch.randn(n, d, device="cuda"), torch.empty(n, r, c, device="cuda")
+    with context(d, n, r, c, hp) as ctx:
+        assert ctx.sketch_mode == 1 and "k_sketch_push" not in kernels(ctx, u, S)
