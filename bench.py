@@ -69,7 +69,9 @@ def kernel_algorithmic_bytes(name, d, n, r, c, k, pa=False):
 def load_traffic(kernel, workload):
     """HBM bytes per launch measured with rocprofv3 --pmc (FETCH_SIZE, WRITE_SIZE), if a summary for this
     workload has been recorded under profiles/ (rows: kernel, launches, fetched raw, fetched scaled, written,
-    total scaled, in GB; a timing slot such as k_head_scatter covers the variants whose names start with it)."""
+    total scaled, in GB; a timing slot such as k_head_scatter covers the variants whose names start with it, and the
+    kernels that write sorted copies in its place)."""
+    names = (kernel, {"k_head_scatter": "k_head_copies", "k_bin_scatter": "k_sort_copies"}.get(kernel, kernel))
     path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles", f"step_{workload}_hbm_traffic.txt")
     try:
         with open(path) as f:
@@ -77,7 +79,7 @@ def load_traffic(kernel, workload):
                 cols = line.strip().split(",")
                 if line.startswith("#") or len(cols) < 6 or cols[0] == "kernel":
                     continue
-                if cols[0].split("::")[-1].split("<")[0].startswith(kernel):
+                if cols[0].split("::")[-1].split("<")[0].startswith(names):
                     return round(float(cols[-1]) * 1e9), (f"profiles/step_{workload}_hbm_traffic.txt: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE "
                                                           "runs of this command recorded earlier, not counters of this run")
     except (OSError, ValueError):
