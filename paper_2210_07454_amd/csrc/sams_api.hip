@@ -158,14 +158,23 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
     double push_ns = 1e30;
     if (rc == SAMS_OK) rc = push_estimate(ctx, ctx->tun, &push_ns);
     if (rc == SAMS_OK) rc = pull_create(ctx, ctx->tun, push_ns, &pulls);
+    const int64_t scratch_before = ctx->scratch_bytes;
     if (rc == SAMS_OK && !pulls && push_ns < 1e30) rc = push_create(ctx, ctx->tun, &pushes);
-    if (rc == SAMS_OK && !pulls && !pushes && push_ns < 1e30) rc = pull_create(ctx, ctx->tun, 1e30, &pulls);
-    if (rc == SAMS_OK && !pulls && ctx->tun.sketch_path != 1 && (!pushes || (ctx->c > kPlanMinRecoveryC && estimate_wants_plan(ctx))))
-        rc = plan_create(ctx, ctx->tun);
     if (rc == SAMS_OK && pushes) {
+        if (ctx->c > kPlanMinRecoveryC && estimate_wants_plan(ctx)) rc = plan_create(ctx, ctx->tun);
+        if (rc == SAMS_OK) rc = plan_staging_alone(ctx);
         ctx->plan.mode = PLAN_BINNED;                                // to the caller: the order is the coordinates'
-        rc = plan_staging_alone(ctx);
+        if (rc == SAMS_ENOMEM) {                                     // what the others need may be had
+            push_destroy(ctx);
+            plan_destroy(ctx);
+            ctx->plan = Plan{};
+            ctx->scratch_bytes = scratch_before;
+            pushes = false;
+            rc = SAMS_OK;
+        }
     }
+    if (rc == SAMS_OK && !pulls && !pushes && push_ns < 1e30) rc = pull_create(ctx, ctx->tun, 1e30, &pulls);
+    if (rc == SAMS_OK && !pulls && !pushes && ctx->tun.sketch_path != 1) rc = plan_create(ctx, ctx->tun);
     if (rc == SAMS_OK) rc = estimate_prepare(ctx);
     if (rc == SAMS_OK && ctx->tun.fuse_head == 2 && head_can_fuse(ctx, false)) {   // the per-worker fused head compacts g on I_{t-1}
         struct { void **p; int64_t bytes; } extra[] = {{(void **)&ctx->wordrank, words * 4}, {(void **)&ctx->gsel, (int64_t)n * k * 4}};

@@ -169,3 +169,23 @@ def test_sums_in_parts_stay_in_parts():
     u, S = torch.randn(n, d, device="cuda"), torch.empty(n, r, c, device="cuda")
     with context(d, n, r, c, hp) as ctx:
         assert ctx.sketch_mode == 1 and "k_sketch_push" not in kernels(ctx, u, S)
+
+
+def test_without_room_for_the_copies():
+    """the context sums lists of slices instead, as if the copies had not been asked for"""
+    from tests.test_gpu_short_memory import hold_all_but
+    d, n, r, c = 4_000_000, 30, 5, 32_000                               # copies of 960 MB
+    hp = inputs.hash_params(r, seed=3)
+    u, S, ref = torch.randn(n, d, device="cuda"), torch.empty(n, r, c, device="cuda"), torch.empty(n, r, c, device="cuda")
+    with context(d, n, r, c, hp, push_windows=104) as ctx:
+        assert kernels(ctx, u, ref) == {"k_sketch_push", "k_bin_scatter"}
+    torch.cuda.empty_cache()
+    held = hold_all_but(700 << 20)
+    try:
+        with context(d, n, r, c, hp, push_windows=104) as ctx:
+            assert kernels(ctx, u, S) == {"k_sketch_pull"} and ctx.scratch_bytes < 700 << 20
+            torch.cuda.synchronize()
+    finally:
+        del held
+        torch.cuda.empty_cache()
+    assert torch.equal(S, ref)
