@@ -2059,7 +2059,9 @@ int plan_staging_alone(sams_ctx *ctx)
     Plan &pl = ctx->plan;
     if (!ctx->push.ncopy || pl.stg) return SAMS_OK;
     pl.stg_words = ctx->push.copy_words;
-    return dev_alloc(ctx, (void **)&pl.stg, pl.stg_words * 4);
+    const int64_t bytes = pl.stg_words * 4;
+    if (ctx->tun.stage_spread && bytes >= ((int64_t)2 << 30) && spread_alloc(ctx, bytes) == SAMS_OK) return SAMS_OK;
+    return dev_alloc(ctx, (void **)&pl.stg, bytes);
 }
 
 int64_t plan_staging_words(const sams_ctx *ctx)
