@@ -661,8 +661,8 @@ int enqueue_sketch_push(sams_ctx *ctx, const float *u, float *S_workers)
 {
     const PushPlan &pp = ctx->push;
     if (pp.ncopy && ctx->plan.staged_u != u) {                       // not written by a fused head
+        ctx->plan.staged_u = nullptr;                                // what it wrote is overwritten, also if an error follows
         SAMS_TRY(enqueue_sort_copies(ctx, u));
-        ctx->plan.staged_u = nullptr;
     }
     PushArgs a = {pp.ncopy ? ctx->plan.stg : u, pp.words, S_workers, ctx->c, pp.ncopy ? (int64_t)pp.nph * pp.span : ctx->d, ctx->n, ctx->r, pp.nwin,
                   pp.win, pp.span, pp.nph, pp.nalloc, 0, {0}, {0}};

@@ -140,6 +140,32 @@ def test_copies_written_by_the_head_are_used_once_and_for_their_vector(tunables,
         assert np.array_equal(S.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("tunables", [dict(push_windows=104), dict(sketch_path=2)], ids=["copies", "bins"])
+def test_a_sketch_that_fails_forgets_what_the_head_staged(tunables):
+    """An error that an earlier HIP call of the thread has left behind is reported once pass 1 for another vector has been enqueued: what it
+    overwrote is not taken for the head's vector afterwards."""
+    from paper_2210_07454_amd import sams
+    from tests.test_gpu_selection_recovers import hip
+    d, n, r, c = 50_004, 3, 5, 40_000
+    hp = inputs.hash_params(r, seed=6)
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    g, other = torch.randn(n, d, device="cuda", generator=gen), torch.randn(n, d, device="cuda", generator=gen)
+    m, e = torch.zeros(n, d, device="cuda"), torch.zeros(n, d, device="cuda")
+    v, vhat = (torch.full((d,), 1e-4, device="cuda") for _ in range(2))
+    S = torch.empty(n, r, c, device="cuda")
+    o = Oracle("f32")
+    lib = hip()
+    with context(d, n, r, c, hp, fuse_head=2, **tunables) as ctx:
+        ctx.amsgrad_ef_update(g, m, e, v, vhat, torch.zeros(d, device="cuda"), None, None, 0, 0.9, 0.99, 1e-3)
+        torch.cuda.synchronize()
+        assert lib.hipSetDevice(4096) != 0                               # no such device: leaves its error behind
+        with pytest.raises(sams.SamsError):
+            ctx.sketch_accumulate(other, S)
+        lib.hipGetLastError()
+        ctx.sketch_accumulate(e, S)
+        assert np.array_equal(S.cpu().numpy(), np.stack([o.sketch(x, hp, c) for x in e.cpu().numpy()]))
+
+
 def test_replayed_graph_equals_eager():
     d, n, r, c = 60_001, 4, 3, 50_000
     hp = inputs.hash_params(r, seed=2)
