@@ -404,6 +404,8 @@ int enqueue_row_estimates_planned(sams_ctx *ctx, const float *S_mean, float *row
 // whole recovery through the plan when the fused collect+median kernel applies; *done says whether it ran
 int enqueue_estimates_planned_fused(sams_ctx *ctx, const float *S_mean, const float *vhat, float *est, bool *done,
                                     const SelScratch *sc);   // see enqueue_estimate; *done implies the histogram
+// whether the tunables and the vector's length let the head write what the first sketch pass would, and whether this context has that to write
+bool head_form_fuses(const Tunables &tun, int64_t d, bool pa);
 bool head_can_fuse(const sams_ctx *ctx, bool pa);
 // wordrank and gsel exist for this context (sams_create decides): the per-worker fused head then leaves the
 // gradients of the selected coordinates in gsel and the second moments on I_{t-1} need no gathers

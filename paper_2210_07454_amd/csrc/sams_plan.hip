@@ -2134,10 +2134,15 @@ bool head_compacts_g(const sams_ctx *ctx) { return ctx->wordrank != nullptr && c
 // with n = 4, 53 and 58 us but a step of 119 and 113 us, with the tail and the second moments on I_{t-1} in launches of their
 // own.  Alg. 1: 1.44 and 1.12 ms at 11.2 million, 6.0 and 5.7 at 60 million, 4.6 and 4.3 at 100 million (three rows).
 constexpr int64_t kFuseOddMinD = (int64_t)1 << 24;
+bool head_form_fuses(const Tunables &tun, int64_t d, bool pa)
+{
+    return tun.fuse_head && ((d & 3) == 0 || (tun.fuse_head == 2 && !pa && d >= kFuseOddMinD));
+}
+
 bool head_can_fuse(const sams_ctx *ctx, bool pa)
 {
-    if (!ctx->tun.fuse_head || ctx->plan.mode != PLAN_BINNED || ctx->pull.kernel || (ctx->push.words && !ctx->push.ncopy)) return false;
-    return (ctx->d & 3) == 0 || (ctx->tun.fuse_head == 2 && !pa && ctx->d >= kFuseOddMinD);
+    if (ctx->plan.mode != PLAN_BINNED || ctx->pull.kernel || (ctx->push.words && !ctx->push.ncopy)) return false;
+    return head_form_fuses(ctx->tun, ctx->d, pa);
 }
 
 int enqueue_head_scatter(sams_ctx *ctx, const float *g, float *m, float *e_u, float *v, float *vhat,

@@ -512,14 +512,16 @@ static bool push_shape(const sams_ctx *ctx, const Tunables &tun)
     return tun.push_windows ? tun.push_windows > 0 : ctx->c > 10000 && ctx->d >= 1 << 18;
 }
 
-// the fastest number of windows, and whether out of copies; 1e30: none
+// the fastest number of windows, and whether out of copies; 1e30: none.  (Copies that only the head of Alg. 2 can write, as of a long vector whose length is
+// no multiple of four, count as the head's: which update the context will have is not known yet.)
 static double push_choose(const sams_ctx *ctx, const Tunables &tun, const uint32_t *repeat, int32_t *windows, bool *copies)
 {
+    const bool fused = head_form_fuses(tun, ctx->d, false);
     double best = 1e30;
     for (int mode = 0; mode < 2; ++mode)
         for (int32_t nwin = (int32_t)((ctx->c + kPushMaxWin - 1) / kPushMaxWin); nwin <= kPushMostWin; ++nwin) {
             if (tun.push_windows && tun.push_windows != mode * 100 + nwin) continue;
-            const double cost = push_cost(ctx, nwin, mode == 1, tun.fuse_head == 2, repeat);
+            const double cost = push_cost(ctx, nwin, mode == 1, fused, repeat);
             if (cost >= best) continue;
             best = cost;
             *windows = nwin;

@@ -101,6 +101,18 @@ def test_the_chosen_path(d, n, r, c, kernel):
     assert kernel in check(d, n, r, c, inputs.hash_params(r, seed=3), 0)
 
 
+@pytest.mark.parametrize("d,n,r,c", [(997_358, 42, 3, 36_492), (538_297, 17, 5, 42_700), (609_463, 9, 3, 125_447), (886_797, 4, 4, 281_664)])
+def test_a_head_that_does_not_fuse_changes_no_choice(d, n, r, c):
+    """d no multiple of four: pass 1 writes the copies whatever "fuse_head" says, so the path and its windows are those of "fuse_head" 0"""
+    hp = inputs.hash_params(r, seed=1)
+    u, S = torch.randn(n, d, device="cuda"), torch.empty(n, r, c, device="cuda")
+    seen = []
+    for fuse_head in (0, 2):
+        with context(d, n, r, c, hp, fuse_head=fuse_head) as ctx:
+            seen.append((kernels(ctx, u, S), ctx.scratch_bytes, S.clone()))
+    assert seen[0][:2] == seen[1][:2] and torch.equal(seen[0][2], seen[1][2])
+
+
 @pytest.mark.parametrize("windows,fuse_head", [(103, 2), (103, 0), (3, 2), (1, 0)])
 @pytest.mark.parametrize("d", [40_000, 40_003])
 def test_one_iteration(d, windows, fuse_head):
