@@ -92,6 +92,75 @@ static int selection(sams_ctx *ctx, F body)
     return SAMS_OK;
 }
 
+// What stage 1 (and a recovery through the plan) goes by: slices, lists of values where they are taken to need less than those
+// (push_ns, 1e30: not at all), or the plan.
+static int create_paths(sams_ctx *ctx, double push_ns)
+{
+    bool pushes = false, pulls = false;
+    SAMS_TRY(pull_create(ctx, ctx->tun, push_ns, &pulls));
+    if (!pulls && push_ns < 1e30) SAMS_TRY(push_create(ctx, ctx->tun, &pushes));
+    if (pushes) {
+        if (ctx->c > kPlanMinRecoveryC && estimate_wants_plan(ctx)) SAMS_TRY(plan_create(ctx, ctx->tun));
+        SAMS_TRY(plan_staging_alone(ctx));
+        ctx->plan.mode = PLAN_BINNED;                                // to the caller: the order is the coordinates'
+        return SAMS_OK;
+    }
+    if (!pulls && push_ns < 1e30) SAMS_TRY(pull_create(ctx, ctx->tun, 1e30, &pulls));
+    if (!pulls && ctx->tun.sketch_path != 1) SAMS_TRY(plan_create(ctx, ctx->tun));
+    return SAMS_OK;
+}
+
+// What else depends on the path taken: g compacted on I_{t-1} for a per-worker fused head, and lists for the selection where
+// the staging buffer has no room for them.
+static int create_rest(sams_ctx *ctx)
+{
+    const int64_t words = (ctx->d + 31) / 32;
+    SAMS_TRY(estimate_prepare(ctx));
+    if (ctx->tun.fuse_head == 2 && head_can_fuse(ctx, false)) {
+        struct { void **p; int64_t bytes; } extra[] = {{(void **)&ctx->wordrank, words * 4}, {(void **)&ctx->gsel, (int64_t)ctx->n * ctx->k * 4}};
+        for (auto &a : extra) {
+            hipError_t e = hipMalloc(a.p, (size_t)a.bytes);
+            if (e != hipSuccess) {
+                g_last_hip_error = (int)e;
+                (void)hipGetLastError();
+                *a.p = nullptr;
+                return SAMS_ENOMEM;
+            }
+            ctx->scratch_bytes += a.bytes;
+        }
+    }
+    if (plan_staging_words(ctx) < sel_list_words(ctx->d)) {
+        hipError_t e = hipMalloc((void **)&ctx->sel_list, (size_t)sel_list_words(ctx->d) * 4);
+        if (e != hipSuccess && ctx->d > kSelHistPickMin) {           // longer selections work on the keys themselves
+            (void)hipGetLastError();
+            ctx->sel_cap = kSelHistPickMin;
+            e = hipMalloc((void **)&ctx->sel_list, (size_t)sel_list_words(ctx->sel_cap) * 4);
+        }
+        if (e != hipSuccess) {
+            g_last_hip_error = (int)e;
+            (void)hipGetLastError();
+            ctx->sel_list = nullptr;
+            return SAMS_ENOMEM;
+        }
+        ctx->scratch_bytes += sel_list_words(ctx->sel_cap) * 4;
+    }
+    return SAMS_OK;
+}
+
+// back to before create_paths (a context that pushes)
+static void destroy_paths(sams_ctx *ctx)
+{
+    push_destroy(ctx);
+    plan_destroy(ctx);
+    ctx->plan = Plan{};
+    void **rest[] = {(void **)&ctx->wordrank, (void **)&ctx->gsel, (void **)&ctx->sel_list};
+    for (void **p : rest) {
+        if (*p) (void)hipFree(*p);
+        *p = nullptr;
+    }
+    ctx->sel_cap = ctx->d;
+}
+
 }  // namespace sams
 
 using namespace sams;
@@ -154,56 +223,16 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
     int rc = static_scratch_ptr(&static_scratch);                    // resolved here so that topk_refine_static never has to
     if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, ctx->bitmap, words, 0u);
     if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, ctx->sel, kSelClearWords, 0u);
-    bool pushes = false, pulls = false;
     double push_ns = 1e30;
     if (rc == SAMS_OK) rc = push_estimate(ctx, ctx->tun, &push_ns);
-    if (rc == SAMS_OK) rc = pull_create(ctx, ctx->tun, push_ns, &pulls);
     const int64_t scratch_before = ctx->scratch_bytes;
-    if (rc == SAMS_OK && !pulls && push_ns < 1e30) rc = push_create(ctx, ctx->tun, &pushes);
-    if (rc == SAMS_OK && pushes) {
-        if (ctx->c > kPlanMinRecoveryC && estimate_wants_plan(ctx)) rc = plan_create(ctx, ctx->tun);
-        if (rc == SAMS_OK) rc = plan_staging_alone(ctx);
-        ctx->plan.mode = PLAN_BINNED;                                // to the caller: the order is the coordinates'
-        if (rc == SAMS_ENOMEM) {                                     // what the others need may be had
-            push_destroy(ctx);
-            plan_destroy(ctx);
-            ctx->plan = Plan{};
-            ctx->scratch_bytes = scratch_before;
-            pushes = false;
-            rc = SAMS_OK;
-        }
-    }
-    if (rc == SAMS_OK && !pulls && !pushes && push_ns < 1e30) rc = pull_create(ctx, ctx->tun, 1e30, &pulls);
-    if (rc == SAMS_OK && !pulls && !pushes && ctx->tun.sketch_path != 1) rc = plan_create(ctx, ctx->tun);
-    if (rc == SAMS_OK) rc = estimate_prepare(ctx);
-    if (rc == SAMS_OK && ctx->tun.fuse_head == 2 && head_can_fuse(ctx, false)) {   // the per-worker fused head compacts g on I_{t-1}
-        struct { void **p; int64_t bytes; } extra[] = {{(void **)&ctx->wordrank, words * 4}, {(void **)&ctx->gsel, (int64_t)n * k * 4}};
-        for (auto &a : extra) {
-            hipError_t e = hipMalloc(a.p, (size_t)a.bytes);
-            if (e != hipSuccess) {
-                g_last_hip_error = (int)e;
-                (void)hipGetLastError();
-                sams_destroy(ctx);
-                return SAMS_ENOMEM;
-            }
-            ctx->scratch_bytes += a.bytes;
-        }
-    }
-    if (rc == SAMS_OK && plan_staging_words(ctx) < sel_list_words(d)) {
-        hipError_t e = hipMalloc((void **)&ctx->sel_list, (size_t)sel_list_words(d) * 4);
-        if (e != hipSuccess && d > kSelHistPickMin) {                // longer selections work on the keys themselves
-            (void)hipGetLastError();
-            ctx->sel_list = nullptr;
-            ctx->sel_cap = kSelHistPickMin;
-            e = hipMalloc((void **)&ctx->sel_list, (size_t)sel_list_words(ctx->sel_cap) * 4);
-        }
-        if (e != hipSuccess) {
-            g_last_hip_error = (int)e;
-            (void)hipGetLastError();
-            rc = SAMS_ENOMEM;
-        } else {
-            ctx->scratch_bytes += sel_list_words(ctx->sel_cap) * 4;
-        }
+    if (rc == SAMS_OK) rc = create_paths(ctx, push_ns);
+    if (rc == SAMS_OK) rc = create_rest(ctx);
+    if (rc == SAMS_ENOMEM && ctx->push.words) {                      // what the others need may be had
+        destroy_paths(ctx);
+        ctx->scratch_bytes = scratch_before;
+        rc = create_paths(ctx, 1e30);
+        if (rc == SAMS_OK) rc = create_rest(ctx);
     }
     if (rc != SAMS_OK) {
         sams_destroy(ctx);

@@ -227,3 +227,23 @@ def test_without_room_for_the_copies():
         del held
         torch.cuda.empty_cache()
     assert torch.equal(S, ref)
+
+
+def test_without_room_for_what_the_head_compacts():
+    """the copies find room, the gradients of the selected coordinates beside them do not: the context sums lists of slices, whose head compacts nothing"""
+    from tests.test_gpu_short_memory import hold_all_but
+    d, n, r, c, k = 4_000_000, 30, 5, 32_000, 2_000_000                 # lists and copies 1,081 MB, gradients 240 MB
+    hp = inputs.hash_params(r, seed=3)
+    u, S, ref = torch.randn(n, d, device="cuda"), torch.empty(n, r, c, device="cuda"), torch.empty(n, r, c, device="cuda")
+    with context(d, n, r, c, hp, k, push_windows=104, fuse_head=2) as ctx:
+        assert kernels(ctx, u, ref) == {"k_sketch_push", "k_bin_scatter"} and 1_310e6 < ctx.scratch_bytes < 1_340e6
+    torch.cuda.empty_cache()
+    held = hold_all_but(1150 << 20)
+    try:
+        with context(d, n, r, c, hp, k, push_windows=104, fuse_head=2) as ctx:
+            assert kernels(ctx, u, S) == {"k_sketch_pull"} and ctx.scratch_bytes < 1_000e6
+            torch.cuda.synchronize()
+    finally:
+        del held
+        torch.cuda.empty_cache()
+    assert torch.equal(S, ref)
