@@ -93,19 +93,19 @@ static int selection(sams_ctx *ctx, F body)
 }
 
 // What stage 1 (and a recovery through the plan) goes by: slices, lists of values where they are taken to need less than those
-// (push_ns, 1e30: not at all), or the plan.
-static int create_paths(sams_ctx *ctx, double push_ns)
+// (push.ns), or the plan.
+static int create_paths(sams_ctx *ctx, const PushChoice &push)
 {
     bool pushes = false, pulls = false;
-    SAMS_TRY(pull_create(ctx, ctx->tun, push_ns, &pulls));
-    if (!pulls && push_ns < 1e30) SAMS_TRY(push_create(ctx, ctx->tun, &pushes));
+    SAMS_TRY(pull_create(ctx, ctx->tun, push.ns, &pulls));
+    if (!pulls && push.ns < 1e30) SAMS_TRY(push_create(ctx, push, &pushes));
     if (pushes) {
         if (ctx->c > kPlanMinRecoveryC && estimate_wants_plan(ctx)) SAMS_TRY(plan_create(ctx, ctx->tun));
         SAMS_TRY(plan_staging_alone(ctx));
         ctx->plan.mode = PLAN_BINNED;                                // to the caller: the order is the coordinates'
         return SAMS_OK;
     }
-    if (!pulls && push_ns < 1e30) SAMS_TRY(pull_create(ctx, ctx->tun, 1e30, &pulls));
+    if (!pulls && push.ns < 1e30) SAMS_TRY(pull_create(ctx, ctx->tun, 1e30, &pulls));
     if (!pulls && ctx->tun.sketch_path != 1) SAMS_TRY(plan_create(ctx, ctx->tun));
     return SAMS_OK;
 }
@@ -223,15 +223,16 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
     int rc = static_scratch_ptr(&static_scratch);                    // resolved here so that topk_refine_static never has to
     if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, ctx->bitmap, words, 0u);
     if (rc == SAMS_OK) rc = enqueue_fill_u32(ctx, ctx->sel, kSelClearWords, 0u);
-    double push_ns = 1e30;
-    if (rc == SAMS_OK) rc = push_estimate(ctx, ctx->tun, &push_ns);
+    PushChoice push = {};
+    if (rc == SAMS_OK) rc = push_estimate(ctx, ctx->tun, &push);
     const int64_t scratch_before = ctx->scratch_bytes;
-    if (rc == SAMS_OK) rc = create_paths(ctx, push_ns);
+    if (rc == SAMS_OK) rc = create_paths(ctx, push);
     if (rc == SAMS_OK) rc = create_rest(ctx);
     if (rc == SAMS_ENOMEM && ctx->push.words) {                      // what the others need may be had
         destroy_paths(ctx);
         ctx->scratch_bytes = scratch_before;
-        rc = create_paths(ctx, 1e30);
+        push.ns = 1e30;
+        rc = create_paths(ctx, push);
         if (rc == SAMS_OK) rc = create_rest(ctx);
     }
     if (rc != SAMS_OK) {

@@ -121,6 +121,14 @@ struct PushPlan {
     int64_t word_bytes, order_bytes;
 };
 
+// what a context that pushes would take (push_estimate)
+struct PushChoice {
+    double ns;                    // time of a sketch; 1e30: it does not push
+    int32_t windows;              // of a row
+    bool copies;
+    uint32_t repeat[SAMS_MAX_ROWS];       // rows' shortest distances after which buckets repeat
+};
+
 // tunables: sams_configure edits the process-wide set, sams_create copies it into the context, and every
 // later call on that context reads only its own copy
 struct Tunables {
@@ -387,9 +395,9 @@ int pull_create(sams_ctx *ctx, const Tunables &tun, double limit, bool *done);
 void pull_destroy(sams_ctx *ctx);
 int enqueue_sketch_pull(sams_ctx *ctx, const float *u, float *S_workers);
 // sams_push.hip
-// first: whether one window, and the vectors themselves, are so much the fastest that no other path need be looked at
-int push_estimate(sams_ctx *ctx, const Tunables &tun, double *ns);
-int push_create(sams_ctx *ctx, const Tunables &tun, bool *done);
+// Before push_create: whether this path is taken to pay, and how.  Allocates nothing.
+int push_estimate(sams_ctx *ctx, const Tunables &tun, PushChoice *choice);
+int push_create(sams_ctx *ctx, const PushChoice &choice, bool *done);
 void push_destroy(sams_ctx *ctx);
 int enqueue_sketch_push(sams_ctx *ctx, const float *u, float *S_workers);
 // sams_plan.hip

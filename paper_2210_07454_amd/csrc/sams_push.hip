@@ -55,6 +55,7 @@ constexpr int kPushRing = 8;                  // phases whose words are
 // multiple of 32 every lane of a group would be in one bank (207 instead of 147 us for one hash of eight at three million, n = 8, 5 x 150,001).
 __host__ __device__ __forceinline__ uint32_t push_cell(uint32_t b) { return (b & ~63u) | ((b + ((b >> 6) * 0x9e3779b1u >> 26)) & 63u); }
 static __host__ __device__ __forceinline__ int32_t push_cells(int32_t win) { return (win + kWave - 1) / kWave * kWave; }   // the padding's cells follow
+static __host__ __device__ __forceinline__ int32_t push_bit_words(int32_t win) { return (win + 31) / 32; }
 // A word: sign (bit 0), place in the phase (the next 15 bits, or 14), cell (up to bit 30); bit 31: the word before, the lane's first or the second
 // of the lane before, has the same bucket.  Padding: place 0, a cell of the lane's.
 
@@ -121,13 +122,17 @@ k_push_order(HashParams hp, int64_t d, PushCopies pc, int32_t nwin, int32_t win,
     for (int x = t; x < span; x += kPushThreads) out[x] = x < lim ? (uint16_t)(keys[x] & 0x3fffu) : (uint16_t)0;
 }
 
-// per (phase, row and window): the words.  status[0]: a phase has too many entries, or too many that share buckets; status[1]: entries that share a
-// bucket, all phases together
-__global__ void __launch_bounds__(kPushThreads)
+// per (phase, row and window): the words.  *status: a phase has too many entries, or too many that share buckets
+//
+// Bound by hashing and barriers: every window's workgroup hashes the whole phase, in sweeps of a coordinate per thread, and then only the places that it found,
+// two per thread.  Which buckets are shared is two bits per bucket, and the entries that share one are sorted, so that a workgroup takes 46 KB of LDS and two
+// fit a unit (with 16-bit counters 118 KB, a second hash of everything and all pairs of shared entries compared: 11.2 million, 5 x 262,144 2.65 ms, now 0.80;
+// 25 million, 10 x 100,000 12.5, with a row that repeats 25.4, now 4.3 and 5.9).
+__global__ void __launch_bounds__(kPushThreads, 8)
 k_push_plan(HashParams hp, int64_t d, int32_t nwin, int32_t win, int32_t span, int32_t nph, int32_t nalloc, int place_bits,
             const uint16_t *__restrict__ order, PushCopies pc, uint32_t *__restrict__ words, uint32_t *__restrict__ status)
 {
-    extern __shared__ uint32_t cnt[];                                // [win / 2 + 1]  entries of a bucket, two in a word
+    extern __shared__ uint32_t seen[];                               // [2][push_bit_words(win)]  bit per bucket: has an entry, has several
     __shared__ uint32_t ent[kPushEntries], outw[kPushEntries];       // the entries' words, by place and in their slots
     __shared__ uint16_t coord[kPushEntries];                         // their coordinates in the phase
     __shared__ uint16_t multi[kPushEntries], nth[kPushEntries];      // entries that share a bucket; how many of its entries come before one
@@ -135,47 +140,72 @@ k_push_plan(HashParams hp, int64_t d, int32_t nwin, int32_t win, int32_t span, i
     __shared__ uint32_t part[kPushWaves], many[kPushWaves], before[kPushWaves * kPushGroups + 1];
     __shared__ uint32_t sh, longest;
     const int bshift = place_bits + 1;
-    const int t = threadIdx.x, j = blockIdx.y / nwin, w = blockIdx.y % nwin;
+    const int t = threadIdx.x, my_lane = t & (kWave - 1), my_wave = t / kWave, j = blockIdx.y / nwin, w = blockIdx.y % nwin;
     uint32_t *out = words + ((int64_t)blockIdx.y * nalloc + blockIdx.x) * kPushEntries;
     const int64_t l0 = (int64_t)blockIdx.x * span;
     const int lim = (int)blockIdx.x >= nph ? 0 : (d - l0 < span ? (int)(d - l0) : span);
     const uint32_t b0 = (uint32_t)w * (uint32_t)win;
-    for (int q = t; q < win / 2 + 1; q += kPushThreads) cnt[q] = 0u;
-    for (int q = t; q < kPushEntries; q += kPushThreads) outw[q] = (uint32_t)(push_cells(win) + q / kPushGroups % kWave) << bshift;
+    uint32_t *several = seen + push_bit_words(win);
+    for (int q = t; q < 2 * push_bit_words(win); q += kPushThreads) seen[q] = 0u;
     if (t < kPushWaves) many[t] = 0u;
     if (t == 0) longest = 0u;
-    // the window's coordinates in the order of their places: thread t has the places [t * per, (t + 1) * per) of the phase
+    // the window's places, in order: in a sweep every thread looks at one of 1,024 neighbours
     const uint16_t *in_place = order ? order + ((int64_t)pc.of[j] * nph + blockIdx.x) * span : nullptr;
     auto at_place = [&](int x) { return in_place ? (int)in_place[x] : x; };
-    const int per = (lim + kPushThreads - 1) / kPushThreads, x0 = t * per, x1 = x0 + per < lim ? x0 + per : lim;
+    const int sweeps = (lim + kPushThreads - 1) / kPushThreads;      // at most 32: a place has 15 bits
+    uint32_t *found = ent;                                           // [sweeps][kPushWaves]  places of a wavefront's 64, then of all before
+    uint16_t *places = nth;                                          // (neither is in use yet)
     uint32_t mine = 0;
-    for (int x = x0; x < x1; ++x) mine += bucket_of(hp, j, (uint32_t)(l0 + at_place(x))) - b0 < (uint32_t)win ? 1u : 0u;
+    for (int z0 = 0; z0 < sweeps; z0 += 4) {
+        uint32_t l[4];
+#pragma unroll
+        for (int z = 0; z < 4; ++z) {
+            const int x = (z0 + z) * kPushThreads + t;
+            l[z] = (uint32_t)(l0 + at_place(x < lim ? x : 0));
+        }
+#pragma unroll
+        for (int z = 0; z < 4; ++z) {
+            const bool in = (z0 + z) * kPushThreads + t < lim && bucket_of(hp, j, l[z]) - b0 < (uint32_t)win;
+            const uint64_t all = __ballot(in);
+            if (my_lane == 0) found[(z0 + z) * kPushWaves + my_wave] = (uint32_t)__popcll(all);
+            mine |= (in ? 1u : 0u) << (z0 + z);
+        }
+    }
     __syncthreads();
-    uint32_t at = block_exclusive_scan<kPushThreads>(mine, part);
-    if (t == kPushThreads - 1) sh = at + mine;
+    {
+        const uint32_t n = t < sweeps * kPushWaves ? found[t] : 0u, upto = block_exclusive_scan<kPushThreads>(n, part);
+        if (t < sweeps * kPushWaves) found[t] = upto;
+        if (t == kPushThreads - 1) sh = upto + n;
+    }
     __syncthreads();
     const uint32_t total = sh;
-    __syncthreads();
     if (total > (uint32_t)kPushEntries) {
         if (t == 0) atomicOr(status, 1u);
         return;
     }
-    for (int x = x0; x < x1; ++x) {
-        const uint32_t l = (uint32_t)(l0 + at_place(x)), b = bucket_of(hp, j, l) - b0;
-        if (b >= (uint32_t)win) continue;
-        coord[at] = (uint16_t)at_place(x);
-        ent[at++] = (b << bshift) | ((uint32_t)x << 1) | (sign_neg(hp, j, l) ? 1u : 0u);
-        atomicAdd(&cnt[b >> 1], 1u << (16 * (b & 1)));
+    for (int z = 0; z < sweeps; ++z) {
+        const uint64_t all = __ballot((mine >> z) & 1u);
+        if ((mine >> z) & 1u) places[found[z * kPushWaves + my_wave] + __popcll(all & (((uint64_t)1 << my_lane) - 1))] = (uint16_t)(z * kPushThreads + t);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int z = 0; z < kPushGroups; ++z) {
+        const uint32_t e = t * kPushGroups + z;
+        if (e >= total) continue;
+        const uint32_t x = places[e], q = (uint32_t)at_place((int)x), l = (uint32_t)l0 + q, b = bucket_of(hp, j, l) - b0;
+        coord[e] = (uint16_t)q;
+        ent[e] = (b << bshift) | (x << 1) | (sign_neg(hp, j, l) ? 1u : 0u);
+        const uint32_t bit = 1u << (b & 31);
+        if (atomicOr(&seen[b >> 5], bit) & bit) atomicOr(&several[b >> 5], bit);
     }
     __syncthreads();
     auto bucket = [&](uint32_t e) { return ent[e] >> bshift; };
-    auto members = [&](uint32_t e) { return (cnt[bucket(e) >> 1] >> (16 * (bucket(e) & 1))) & 0xffffu; };
     bool is_multi[kPushGroups];
     uint32_t nm = 0;
 #pragma unroll
     for (int z = 0; z < kPushGroups; ++z) {
         const uint32_t e = t * kPushGroups + z;
-        is_multi[z] = e < total && members(e) > 1;
+        is_multi[z] = e < total && ((several[bucket(e) >> 5] >> (bucket(e) & 31)) & 1u);
         nm += is_multi[z] ? 1u : 0u;
     }
     const uint32_t multi_before = block_exclusive_scan<kPushThreads>(nm, part);
@@ -190,26 +220,58 @@ k_push_plan(HashParams hp, int64_t d, int32_t nwin, int32_t win, int32_t span, i
     const uint32_t nmulti = sh;
     __syncthreads();
     if (nmulti) {
-        for (uint32_t k = t; k < nmulti; k += kPushThreads) {
-            const uint32_t b = bucket(multi[k]);
-            uint32_t n = 0, first = k;
-            for (uint32_t q = 0; q < nmulti; ++q)
-                if (bucket(multi[q]) == b) {
-                    if (coord[multi[q]] < coord[multi[k]]) ++n;
-                    if (coord[multi[q]] < coord[multi[first]]) first = q;
-                }
-            nth[k] = (uint16_t)n;
-            if (n) place[k] = first;
-        }
-        __syncthreads();
-        // The shared buckets in the order of their first entries, as if in one line that is cut every 128 - (most entries of a bucket - 1): a bucket
-        // goes with all its entries to the wavefront in whose piece it starts, and none is longer than what is left of the 128 words.  Where there is
-        // room, each starts with a lane's first word.
-        uint32_t len[kPushGroups], sum = 0;
+        // sorted by bucket and coordinate, a bucket's entries lie side by side, the first one first
+        uint32_t key[kPushGroups], first[kPushGroups], len[kPushGroups], sum = 0;
+        uint32_t *keys = outw;
+        uint32_t all = 2;
+        while (all < nmulti) all *= 2;
 #pragma unroll
         for (int z = 0; z < kPushGroups; ++z) {
             const uint32_t k = t * kPushGroups + z;
-            len[z] = k < nmulti && nth[k] == 0 ? members(multi[k]) : 0u;
+            key[z] = k < nmulti ? (bucket(multi[k]) << 15) | coord[multi[k]] : 0xffffffffu;
+            if (k < all) keys[k] = key[z];
+        }
+        for (uint32_t size = 2; size <= all; size *= 2)
+            for (uint32_t step = size / 2; step; step /= 2) {
+                __syncthreads();
+                if ((uint32_t)t < all / 2) {
+                    const uint32_t lo = 2 * step * (t / step) + t % step, hi = lo + step, x = keys[lo], y = keys[hi];
+                    if ((x > y) == ((lo & size) == 0)) {
+                        keys[lo] = y;
+                        keys[hi] = x;
+                    }
+                }
+            }
+        __syncthreads();
+        auto below = [&](uint32_t v) {                               // keys below v
+            uint32_t n = 0;
+            for (uint32_t s = all; s; s /= 2)
+                if (n + s <= all && keys[n + s - 1] < v) n += s;
+            return n;
+        };
+        uint16_t *sorted = coord;                                    // (no longer needed)
+#pragma unroll
+        for (int z = 0; z < kPushGroups; ++z) {
+            const uint32_t k = t * kPushGroups + z;
+            len[z] = first[z] = 0u;
+            if (k >= nmulti) continue;
+            const uint32_t at = below(key[z]);
+            first[z] = below(key[z] & ~0x7fffu);
+            nth[k] = (uint16_t)(at - first[z]);
+            sorted[at] = (uint16_t)k;
+            if (at == first[z]) len[z] = below((key[z] | 0x7fffu) + 1u) - at;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int z = 0; z < kPushGroups; ++z) {
+            const uint32_t k = t * kPushGroups + z;
+            if (k < nmulti && !len[z]) place[k] = sorted[first[z]];
+        }
+        // The shared buckets in the order of their first entries, as if in one line that is cut every 128 - (most entries of a bucket - 1): a bucket
+        // goes with all its entries to the wavefront in whose piece it starts, and none is longer than what is left of the 128 words.  Where there is
+        // room, each starts with a lane's first word.
+#pragma unroll
+        for (int z = 0; z < kPushGroups; ++z) {
             sum += (len[z] + 1) & ~1u;
             if (len[z] > 1) atomicMax(&longest, len[z]);
         }
@@ -241,8 +303,8 @@ k_push_plan(HashParams hp, int64_t d, int32_t nwin, int32_t win, int32_t span, i
             if (t == 0) atomicOr(status, 1u);
             return;
         }
-        if (t == 0) atomicAdd(status + 1, nmulti);
     }
+    for (int q = t; q < kPushEntries; q += kPushThreads) outw[q] = (uint32_t)(push_cells(win) + q / kPushGroups % kWave) << bshift;
     // the others fill the lanes that the shared buckets leave, in order, a wavefront's first words before its second
     const uint32_t singles = total - nmulti;
     if (t < kWave) {
@@ -514,18 +576,18 @@ static bool push_shape(const sams_ctx *ctx, const Tunables &tun)
 
 // the fastest number of windows, and whether out of copies; 1e30: none.  (Copies that only the head of Alg. 2 can write, as of a long vector whose length is
 // no multiple of four, count as the head's: which update the context will have is not known yet.)
-static double push_choose(const sams_ctx *ctx, const Tunables &tun, const uint32_t *repeat, int32_t *windows, bool *copies)
+static double push_choose(const sams_ctx *ctx, const Tunables &tun, PushChoice *choice)
 {
     const bool fused = head_form_fuses(tun, ctx->d, false);
     double best = 1e30;
     for (int mode = 0; mode < 2; ++mode)
         for (int32_t nwin = (int32_t)((ctx->c + kPushMaxWin - 1) / kPushMaxWin); nwin <= kPushMostWin; ++nwin) {
             if (tun.push_windows && tun.push_windows != mode * 100 + nwin) continue;
-            const double cost = push_cost(ctx, nwin, mode == 1, fused, repeat);
+            const double cost = push_cost(ctx, nwin, mode == 1, fused, choice->repeat);
             if (cost >= best) continue;
             best = cost;
-            *windows = nwin;
-            *copies = mode == 1;
+            choice->windows = nwin;
+            choice->copies = mode == 1;
         }
     return best;
 }
@@ -537,67 +599,51 @@ static bool push_pays(const sams_ctx *ctx, const Tunables &tun, double cost)
     return tun.push_windows ? cost < 1e30 : cost <= 10000 + (double)ctx->n * ctx->r * ctx->d * 1.85e-3;
 }
 
-// every row's repeat distance below 2^15, from the device
+// every row's repeat distance below 2^15, from the device (by way of the selection's scratch, which nothing uses yet)
 static int push_repeats(sams_ctx *ctx, uint32_t *repeat)
 {
-    uint32_t *d_repeat = nullptr;
-    if (hipMalloc((void **)&d_repeat, SAMS_MAX_ROWS * 4) != hipSuccess) {
-        (void)hipGetLastError();
-        return SAMS_ENOMEM;
-    }
     {
         ProfScope ps(ctx, KID_PLAN_BUILD);
-        hipLaunchKernelGGL(k_push_repeat, dim3((unsigned)ctx->r), dim3(1024), 0, ctx->stream, ctx->hp, 1 << 15, d_repeat);
+        hipLaunchKernelGGL(k_push_repeat, dim3((unsigned)ctx->r), dim3(1024), 0, ctx->stream, ctx->hp, 1 << 15, ctx->sel_tile);
     }
-    hipError_t e = hipMemcpyAsync(repeat, d_repeat, (size_t)ctx->r * 4, hipMemcpyDeviceToHost, ctx->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    (void)hipFree(d_repeat);
-    if (e == hipSuccess) return SAMS_OK;
-    g_last_hip_error = (int)e;
-    return SAMS_EHIP;
+    SAMS_HIP(hipGetLastError());
+    SAMS_HIP(hipMemcpyAsync(repeat, ctx->sel_tile, (size_t)ctx->r * 4, hipMemcpyDeviceToHost, ctx->stream));
+    SAMS_HIP(hipStreamSynchronize(ctx->stream));
+    return SAMS_OK;
 }
 
-// *ns: what a sketch should take this way (out of copies a little more: slices gain more from warm caches), 1e30 where bins are taken to need less or the shape
-// cannot.  Slices (sams_pull.hip) go first where they are taken to
+// choice->ns: what a sketch should take this way (out of copies a little more: slices gain more from warm caches), 1e30 where bins are taken to need less or the
+// shape cannot.  Slices (sams_pull.hip) go first where they are taken to
 // need less.  Of 45 shapes of 10,000 to 32,768 buckets and 0.3 to 4.3 million coordinates, 13 change from slices to this: two take 2 to 3 % longer and eleven
 // less, 1.05 to 2.2 times (us, cold caches: 2.1 million, n = 25, 7 x 29,263 770 and 353; 1.6 million, n = 6, 5 x 14,952 157 and 118; 0.57 million, n = 69, 3 x
 // 21,015 159 and 127); of the 18 others that could, the slices are faster at 14, up to 2 times, and at the rest this is by 1 to 4 %.
-int push_estimate(sams_ctx *ctx, const Tunables &tun, double *ns)
+int push_estimate(sams_ctx *ctx, const Tunables &tun, PushChoice *choice)
 {
-    *ns = 1e30;
+    choice->ns = 1e30;
     if (!push_shape(ctx, tun)) return SAMS_OK;
-    int32_t windows;
-    bool copies;
-    uint32_t repeat[SAMS_MAX_ROWS];
-    for (uint32_t &x : repeat) x = 0x7fffffffu;
-    if (!push_pays(ctx, tun, push_choose(ctx, tun, repeat, &windows, &copies))) return SAMS_OK;   // not even with the best of hashes
-    const int rc = push_repeats(ctx, repeat);
-    if (rc == SAMS_ENOMEM) return SAMS_OK;
-    const double cost = push_choose(ctx, tun, repeat, &windows, &copies);
-    if (rc == SAMS_OK && push_pays(ctx, tun, cost)) *ns = tun.push_windows ? 0 : (copies ? cost * 1.3 : cost);
-    return rc;
+    for (uint32_t &x : choice->repeat) x = 0x7fffffffu;
+    if (!push_pays(ctx, tun, push_choose(ctx, tun, choice))) return SAMS_OK;   // not even with the best of hashes
+    SAMS_TRY(push_repeats(ctx, choice->repeat));
+    const double cost = push_choose(ctx, tun, choice);
+    if (push_pays(ctx, tun, cost)) choice->ns = tun.push_windows ? 0 : (choice->copies ? cost * 1.3 : cost);
+    return SAMS_OK;
 }
 
-int push_create(sams_ctx *ctx, const Tunables &tun, bool *done)
+int push_create(sams_ctx *ctx, const PushChoice &choice, bool *done)
 {
     *done = false;
     PushPlan pp = {};
     PushCopies pc = {};
-    bool copies = false;
-    uint32_t *status = nullptr, h_status[4] = {0, 0, 0, 0}, repeat[SAMS_MAX_ROWS];
+    const bool copies = choice.copies;
+    uint32_t *status = ctx->sel_tile, h_status = 0;                  // (see push_repeats)
     int rc = SAMS_OK;
+    pp.nwin = choice.windows;
     do {
         hipError_t e;
-        rc = push_repeats(ctx, repeat);
-        if (rc != SAMS_OK) {
-            if (rc == SAMS_ENOMEM) rc = SAMS_OK;
-            break;
-        }
-        if (push_choose(ctx, tun, repeat, &pp.nwin, &copies) >= 1e30 || hipMalloc((void **)&status, 4 * 4) != hipSuccess) break;
         pp.win = push_win(ctx->c, pp.nwin);
         const int place_bits = copies ? 14 : push_place_bits(pp.win);
         pp.kernel = place_bits == 15 ? (const void *)k_sketch_push<15> : (const void *)k_sketch_push<14>;
-        e = hipFuncSetAttribute((const void *)k_push_plan, hipFuncAttributeMaxDynamicSharedMemorySize, (kPushMaxWin / 2 + 1) * 4);
+        e = hipFuncSetAttribute((const void *)k_push_plan, hipFuncAttributeMaxDynamicSharedMemorySize, 8 * push_bit_words(kPushMaxWin));
         if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_push_order, hipFuncAttributeMaxDynamicSharedMemorySize, kPushTile * 4);
         if (e == hipSuccess) e = hipFuncSetAttribute(pp.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)push_lds(kPushMaxWin));
         if (e != hipSuccess) { g_last_hip_error = (int)e; rc = SAMS_EHIP; break; }
@@ -607,7 +653,7 @@ int push_create(sams_ctx *ctx, const Tunables &tun, bool *done)
             pp.nph = (int32_t)((ctx->d + pp.span - 1) / pp.span);
             pp.nalloc = pp.nph + kPushRing;
             pp.word_bytes = (int64_t)ctx->r * pp.nwin * pp.nalloc * kPushEntries * 4;
-            pc = push_copies(ctx, pp.nwin, pp.span, repeat, pp.row);
+            pc = push_copies(ctx, pp.nwin, pp.span, choice.repeat, pp.row);
             if (copies) {
                 if (!pc.ncopy) break;
                 pp.ncopy = pc.ncopy;
@@ -617,7 +663,7 @@ int push_create(sams_ctx *ctx, const Tunables &tun, bool *done)
                 if (hipMalloc((void **)&pp.order, (size_t)pp.order_bytes) != hipSuccess) { pp.order = nullptr; break; }
             }
             if (hipMalloc((void **)&pp.words, (size_t)pp.word_bytes) != hipSuccess) { pp.words = nullptr; break; }
-            rc = enqueue_fill_u32(ctx, status, 4, 0u);
+            rc = enqueue_fill_u32(ctx, status, 1, 0u);
             if (rc != SAMS_OK) break;
             {
                 ProfScope ps(ctx, KID_PLAN_BUILD);
@@ -627,15 +673,15 @@ int push_create(sams_ctx *ctx, const Tunables &tun, bool *done)
                     hipLaunchKernelGGL(k_push_order, dim3((unsigned)pp.nph, (unsigned)pp.ncopy), dim3(kPushThreads), (size_t)all * 4, ctx->stream, ctx->hp,
                                        ctx->d, pc, pp.nwin, pp.win, pp.span, pp.nph, pp.order);
                 }
-                hipLaunchKernelGGL(k_push_plan, dim3((unsigned)pp.nalloc, (unsigned)(ctx->r * pp.nwin)), dim3(kPushThreads), (size_t)(pp.win / 2 + 1) * 4,
+                hipLaunchKernelGGL(k_push_plan, dim3((unsigned)pp.nalloc, (unsigned)(ctx->r * pp.nwin)), dim3(kPushThreads), (size_t)8 * push_bit_words(pp.win),
                                    ctx->stream, ctx->hp, ctx->d, pp.nwin, pp.win, pp.span, pp.nph, pp.nalloc, place_bits, pp.order, pc, pp.words,
                                    status);
             }
-            e = hipMemcpyAsync(h_status, status, 16, hipMemcpyDeviceToHost, ctx->stream);
+            e = hipMemcpyAsync(&h_status, status, 4, hipMemcpyDeviceToHost, ctx->stream);
             if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
             if (e == hipSuccess) e = hipGetLastError();
             if (e != hipSuccess) { g_last_hip_error = (int)e; rc = SAMS_EHIP; break; }
-            if (!h_status[0]) break;
+            if (!h_status) break;
             (void)hipFree(pp.words);
             if (pp.order) (void)hipFree(pp.order);
             pp.words = nullptr;
@@ -646,7 +692,6 @@ int push_create(sams_ctx *ctx, const Tunables &tun, bool *done)
         ctx->scratch_bytes += pp.word_bytes + pp.order_bytes;
     } while (0);
     (void)hipGetLastError();
-    if (status) (void)hipFree(status);
     ctx->push = pp;
     if (!*done) push_destroy(ctx);
     return rc;
