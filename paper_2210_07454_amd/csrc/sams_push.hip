@@ -625,7 +625,9 @@ int push_estimate(sams_ctx *ctx, const Tunables &tun, PushChoice *choice)
     if (!push_pays(ctx, tun, push_choose(ctx, tun, choice))) return SAMS_OK;   // not even with the best of hashes
     SAMS_TRY(push_repeats(ctx, choice->repeat));
     const double cost = push_choose(ctx, tun, choice);
-    if (push_pays(ctx, tun, cost)) choice->ns = tun.push_windows ? 0 : (choice->copies ? cost * 1.3 : cost);
+    // (a head that writes copies is three launches, with the tail and the second moments on I_{t-1}; a context that pulls has one)
+    const double launches = choice->copies && head_form_fuses(tun, ctx->d, false) ? 10000 : 0;
+    if (push_pays(ctx, tun, cost)) choice->ns = tun.push_windows ? 0 : (choice->copies ? cost * 1.3 + launches : cost);
     return SAMS_OK;
 }
 

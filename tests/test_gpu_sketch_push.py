@@ -113,6 +113,14 @@ def test_a_head_that_does_not_fuse_changes_no_choice(d, n, r, c):
     assert seen[0][:2] == seen[1][:2] and torch.equal(seen[0][2], seen[1][2])
 
 
+def test_launches_of_a_fused_head_count_against_slices():
+    """two workers of half a million coordinates: tail, head and second moments in launches of their own cost more than the sketch saves"""
+    d, n, r, c = 531_384, 2, 10, 10_329
+    u, S = torch.randn(n, d, device="cuda"), torch.empty(n, r, c, device="cuda")
+    with context(d, n, r, c, inputs.hash_params(r, seed=26), fuse_head=2) as ctx:
+        assert kernels(ctx, u, S) == {"k_sketch_pull"}
+
+
 @pytest.mark.parametrize("windows,fuse_head", [(103, 2), (103, 0), (3, 2), (1, 0)])
 @pytest.mark.parametrize("d", [40_000, 40_003])
 def test_one_iteration(d, windows, fuse_head):
