@@ -151,6 +151,35 @@ def test_random_shapes_and_launch_configurations(block, capfd):
     assert ran >= 12                                  # most samples are configurations the library accepts
 
 
+@pytest.mark.parametrize("block", range(4))
+def test_random_shapes_by_lists_of_values(block, capfd):
+    """The same with "push_windows" drawn: contexts that pick their values out of the vectors or out of sorted copies, which short
+    vectors do not become by themselves."""
+    from paper_2210_07454_amd import sams
+    rng = np.random.default_rng(5000 + block)
+    pushed = 0
+    try:
+        for q in range(25):
+            (d, n, r, c, k), _ = sample(rng)
+            c = max(c, int(rng.integers(500, 30_000)))               # (narrower tables have no room for their lists)
+            tun = dict(DEFAULTS, push_windows=int(rng.choice([-1, 0, *range(1, 17), *range(101, 117)])), fuse_head=int(rng.choice([0, 2])),
+                       estimate_path=int(rng.choice([0, 1])), fuse_median=int(rng.integers(0, 2)), scatter_threads=int(rng.choice([256, 1024])))
+            for key, val in tun.items():
+                sams.sams_configure(key, val)
+            with capfd.disabled():
+                print(f"[lists-of-values] sample {block}.{q}: d,n,r,c,k={(d, n, r, c, k)} {tun}", flush=True)
+            assert one_iteration(sams, (d, n, r, c, k), seed=100 * block + q)
+            with sams.Context(d, n, r, c, k, inputs.hash_params(r, seed=100 * block + q)) as ctx:
+                ctx.sams_profile_enable(True)
+                ctx.sketch_accumulate(torch.zeros(n, d, device="cuda"), torch.empty(n, r, c, device="cuda"))
+                ctx.sams_profile_enable(False)
+                pushed += "k_sketch_push" in ctx.sams_profile_read()
+    finally:
+        for key, val in dict(DEFAULTS, push_windows=0).items():
+            sams.sams_configure(key, val)
+    assert pushed >= 10
+
+
 LIMIT_SHAPES = {
     "most-workers-most-rows": (2048, 1024, 16, 300, 64),
     "most-workers-one-bucket": (4, 1024, 1, 1, 4),

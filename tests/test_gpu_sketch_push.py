@@ -50,14 +50,22 @@ def check(d, n, r, c, hp, windows, u=None):
     return used
 
 
-# one window: 2,016 coordinates a phase; windows of one bucket, of up to and above 2^15 cells (where places have 14 bits), the last one of a few buckets or
-# none; a vector of one coordinate, one phase, one more and one less, the ring's eight phases and around; workers that do and do not fill an XCD's share
+# one window: 2,016 coordinates a phase; windows of up to and above 2^15 cells (where places have 14 bits); a vector of one coordinate, of one phase, one more
+# and one less, the ring's eight phases and around; workers that do and do not fill an XCD's share
 @pytest.mark.parametrize("d,n,r,c,windows", [
-    (1, 1, 1, 1, 1), (3, 5, 2, 2, 2), (2_016, 4, 2, 64, 1), (2_017, 3, 2, 65, 1), (2_015, 9, 1, 63, 1), (16_128, 2, 3, 40_800, 1), (16_129, 2, 3, 32_704, 1),
+    (1, 2, 2, 40_800, 1), (2_016, 4, 2, 5_000, 1), (2_017, 3, 2, 4_999, 1), (2_015, 9, 1, 6_000, 1), (16_128, 2, 3, 40_800, 1), (16_129, 2, 3, 32_704, 1),
     (18_143, 1, 2, 32_705, 1), (4_033, 33, 5, 5_000, 1), (30_001, 3, 3, 65_409, 2), (40_003, 7, 2, 81_600, 2), (29_999, 2, 16, 3_000, 3), (100_003, 6, 4, 20_001, 5),
-    (250_001, 2, 3, 33, 16), (300_007, 2, 2, 17, 16), (123_457, 4, 5, 100_000, 16), (60_000, 5, 2, 60_000, 7)])
+    (123_457, 4, 5, 100_000, 16), (60_000, 5, 2, 60_000, 7)])
 def test_from_the_vectors(d, n, r, c, windows):
-    assert check(d, n, r, c, inputs.hash_params(r, seed=d % 89), windows) <= {"k_sketch_push", "k_sketch_pull", "k_bin_scatter", "k_bin_accumulate"}
+    assert check(d, n, r, c, inputs.hash_params(r, seed=d % 89), windows) == {"k_sketch_push"}
+
+
+# tables so narrow that a phase has dozens of coordinates for a bucket (windows of a few buckets or none are all of this kind): the paths that they had
+@pytest.mark.parametrize("d,n,r,c,windows", [
+    (1, 1, 1, 1, 1), (3, 5, 2, 2, 2), (2_016, 4, 2, 64, 1), (2_017, 3, 2, 65, 1), (2_015, 9, 1, 63, 1), (250_001, 2, 3, 33, 16), (300_007, 2, 2, 17, 16),
+    (5_000, 3, 2, 225, 16), (5_001, 2, 3, 241, 16)])
+def test_lists_that_cannot_be_made(d, n, r, c, windows):
+    assert "k_sketch_push" not in check(d, n, r, c, inputs.hash_params(r, seed=d % 89), windows)
 
 
 @pytest.mark.parametrize("d,n,r,c,windows", [
@@ -75,13 +83,23 @@ def repeating(r, c, dist, rows):
     return hp
 
 
-# two, a few and dozens of coordinates of a phase in a bucket; so many that the rows keep the binned path
+# two to six coordinates of a phase in a bucket, for most of its buckets: with the windows for which a phase's shared buckets still find room (a bucket's
+# words lie in one wavefront) by the lists, with the others by the paths that they had
 @pytest.mark.parametrize("windows", [1, 3, 5, 103, 105])
-@pytest.mark.parametrize("dist,rows", [(3_000, (1,)), (1_500, (0, 2)), (601, (2,)), (200, (1,)), (97, (0,)), (40, (1,)), (5, (1,)), (1, (0, 1))])
-def test_buckets_that_repeat_within_a_phase(dist, rows, windows):
+@pytest.mark.parametrize("dist,rows,pushes", [
+    (3_000, (1,), {1, 3, 5, 103, 105}), (1_500, (0, 2), {3, 103}), (601, (2,), {3, 5, 103, 105}), (200, (1,), set()), (97, (0,), set()), (40, (1,), set()),
+    (5, (1,), set()), (1, (0, 1), set())])
+def test_buckets_that_repeat_within_a_phase(dist, rows, pushes, windows):
     d, n, r, c = 50_021, 3, 3, 20_000
     used = check(d, n, r, c, repeating(r, c, dist, rows), windows)
-    assert dist > 5 or "k_sketch_push" not in used
+    assert used == ({"k_sketch_push"} | ({"k_bin_scatter"} if windows > 100 else set()) if windows in pushes else {"k_bin_accumulate", "k_bin_scatter"})
+
+
+@pytest.mark.parametrize("d,dist,windows", [(1_000, 97, 1), (1_000, 37, 1), (2_000, 101, 2), (3_000, 97, 3), (3_001, 97, 103), (5_000, 151, 105)])
+def test_dozens_of_coordinates_of_a_phase_in_a_bucket(d, dist, windows):
+    """half a phase, so that there is room: chains of 10 to 30 words that go on from lane to lane"""
+    used = check(d, 3, 3, 20_000, repeating(3, 20_000, dist, (1,)), windows)
+    assert used == {"k_sketch_push"} | ({"k_bin_scatter"} if windows > 100 else set())
 
 
 @pytest.mark.parametrize("windows", [2, 104])
@@ -121,19 +139,50 @@ def test_launches_of_a_fused_head_count_against_slices():
         assert kernels(ctx, u, S) == {"k_sketch_pull"}
 
 
+def kernels_of_an_iteration(d, n, r, c, k, seed, **tunables):
+    """the kernels of a head and of the two sketches after it, of its vector and of another one"""
+    g, m, e, other = (torch.zeros(n, d, device="cuda") for _ in range(4))
+    v, vhat = (torch.ones(d, device="cuda") for _ in range(2))
+    S = torch.empty(n, r, c, device="cuda")
+    with context(d, n, r, c, inputs.hash_params(r, seed=seed), k, **tunables) as ctx:
+        ctx.sams_profile_enable(True)
+        ctx.amsgrad_ef_update(g, m, e, v, vhat, torch.zeros(d, device="cuda"), None, None, 0, 0.9, 0.99, 1e-3)
+        ctx.sams_profile_enable(False)
+        return set(ctx.sams_profile_read()), kernels(ctx, e, S), kernels(ctx, other, S)
+
+
+def one_iteration_with(shape, seed, **tunables):
+    from paper_2210_07454_amd import sams
+    from tests.test_gpu_random_shapes import one_iteration
+    try:
+        for key, val in tunables.items():
+            sams.sams_configure(key, val)
+        assert one_iteration(sams, shape, seed=seed)
+    finally:
+        for key in tunables:
+            sams.sams_configure(key, 0)
+
+
 @pytest.mark.parametrize("windows,fuse_head", [(103, 2), (103, 0), (3, 2), (1, 0)])
 @pytest.mark.parametrize("d", [40_000, 40_003])
 def test_one_iteration(d, windows, fuse_head):
     """head, sketches, recovery and update; a second sketch of the same vector comes from what the head has staged"""
-    from paper_2210_07454_amd import sams
-    from tests.test_gpu_random_shapes import one_iteration
-    try:
-        sams.sams_configure("push_windows", windows)
-        sams.sams_configure("fuse_head", fuse_head)
-        assert one_iteration(sams, (d, 5, 5, 33_003, 400), seed=d % 97 + windows)
-    finally:
-        sams.sams_configure("push_windows", 0)
-        sams.sams_configure("fuse_head", 0)
+    shape, seed, tunables = (d, 5, 5, 33_003, 400), d % 97 + windows, dict(push_windows=windows, fuse_head=fuse_head)
+    one_iteration_with(shape, seed, **tunables)
+    head, sketch, another = kernels_of_an_iteration(*shape, seed, **tunables)
+    fused = fuse_head == 2 and windows > 100 and d % 4 == 0
+    assert ("k_head_scatter" in head) == fused
+    assert sketch == {"k_sketch_push"} | ({"k_bin_scatter"} if windows > 100 and not fused else set())
+    assert another == {"k_sketch_push"} | ({"k_bin_scatter"} if windows > 100 else set())
+
+
+@pytest.mark.parametrize("d,windows", [((1 << 24) + 1, 103), ((1 << 24) + 3, 116)])
+def test_copies_of_long_ragged_vectors_by_the_head(d, windows):
+    """4-byte accesses: tiles that are no power of two, the last of a few coordinates; g compacted on the index set of the iteration before"""
+    shape, seed, tunables = (d, 2, 2, 70_001, 20_000), 11, dict(push_windows=windows, fuse_head=2)
+    one_iteration_with(shape, seed, **tunables)
+    head, sketch, another = kernels_of_an_iteration(*shape, seed, **tunables)
+    assert "k_head_scatter" in head and sketch == {"k_sketch_push"} and another == {"k_sketch_push", "k_bin_scatter"}
 
 
 @pytest.mark.parametrize("pa", [False, True])
