@@ -113,6 +113,7 @@ struct PushPlan {
     int32_t nwin, win;            // windows of a row, buckets of a window
     int32_t span, nph, nalloc;    // coordinates of a phase, phases, phases that a list has room for
     uint32_t *words;              // [r * nwin][nalloc][2048]
+    int32_t share;                // units of an XCD's turn
     int32_t ncopy;                // sorted copies of the vectors that the values are picked from (0: the vectors themselves)
     int8_t copy_of[SAMS_MAX_ROWS], row[SAMS_MAX_ROWS];     // a row's copy; the order in which the rows are worked on
     const void *kernel;

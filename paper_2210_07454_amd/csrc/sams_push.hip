@@ -612,6 +612,19 @@ static int push_repeats(sams_ctx *ctx, uint32_t *repeat)
     return SAMS_OK;
 }
 
+// Units that take turns (see the kernel): up to 16 workers' out of copies, 4 out of the vectors, but not so many that the XCD that has one turn more than others
+// (32 of the 256 compute units) needs a round of workgroups more for it than units dealt one by one would.  Five workers, 50 lists: turns of five are 35 units
+// for two of the XCDs (us, in turns of all workers and now: 11.2 million, n = 7, 5 x 55,872 753 and 429; 45 million, n = 6, 7 x 56,659 3,237 and 2,097; 2.4 million, n = 6,
+// 7 x 150,527 148 and 98; bins need 884, about 4,000 and 211).
+static int32_t push_share(int32_t n, int64_t units, bool copies)
+{
+    auto rounds = [&](int32_t share) { return (((units + share - 1) / share + 7) / 8 * share + 31) / 32; };
+    const int32_t most = copies ? 16 : 4;
+    int32_t share = n < most ? n : most;
+    while (rounds(share) > rounds(1)) --share;
+    return share;
+}
+
 // choice->ns: what a sketch should take this way (out of copies a little more: slices gain more from warm caches), 1e30 where bins are taken to need less or the
 // shape cannot.  Slices (sams_pull.hip) go first where they are taken to
 // need less.  Of 45 shapes of 10,000 to 32,768 buckets and 0.3 to 4.3 million coordinates, 13 change from slices to this: two take 2 to 3 % longer and eleven
@@ -640,6 +653,7 @@ int push_create(sams_ctx *ctx, const PushChoice &choice, bool *done)
     uint32_t *status = ctx->sel_tile, h_status = 0;                  // (see push_repeats)
     int rc = SAMS_OK;
     pp.nwin = choice.windows;
+    pp.share = push_share(ctx->n, (int64_t)ctx->n * ctx->r * pp.nwin, copies);
     do {
         hipError_t e;
         pp.win = push_win(ctx->c, pp.nwin);
@@ -715,8 +729,7 @@ int enqueue_sketch_push(sams_ctx *ctx, const float *u, float *S_workers)
     }
     PushArgs a = {pp.ncopy ? ctx->plan.stg : u, pp.words, S_workers, ctx->c, pp.ncopy ? (int64_t)pp.nph * pp.span : ctx->d, ctx->n, ctx->r, pp.nwin,
                   pp.win, pp.span, pp.nph, pp.nalloc, 0, {0}, {0}};
-    const int32_t share = pp.ncopy ? 16 : 4;                         // (see the kernel)
-    a.share = ctx->n < share ? ctx->n : share;
+    a.share = pp.share;
     memcpy(a.copy_of, pp.copy_of, sizeof(a.copy_of));
     memcpy(a.row, pp.row, sizeof(a.row));
     const int64_t units = (int64_t)ctx->n * ctx->r * pp.nwin, chunks = (units + a.share - 1) / a.share;

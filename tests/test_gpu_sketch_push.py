@@ -75,6 +75,32 @@ def test_from_sorted_copies(d, n, r, c, windows):
     assert check(d, n, r, c, inputs.hash_params(r, seed=d % 83), windows) == {"k_sketch_push", "k_bin_scatter"}
 
 
+# workers whose turns on an XCD are cut so that no compute unit has a workgroup more than it need have: 250, 245, 252, 243 and 510 workgroups
+@pytest.mark.parametrize("d,n,r,c,windows,seed", [
+    (40_003, 5, 10, 20_000, 5, 4), (40_003, 5, 10, 20_000, 105, 4), (50_001, 7, 5, 55_872, 107, 2), (45_001, 6, 14, 30_001, 3, 2), (45_002, 3, 9, 39_001, 9, 3),
+    (30_001, 17, 15, 60_001, 102, 0)])
+def test_workgroups_dealt_to_the_xcds(d, n, r, c, windows, seed):
+    assert "k_sketch_push" in check(d, n, r, c, inputs.hash_params(r, seed=seed), windows)
+
+
+def test_a_worker_more_takes_no_second_round():
+    """245 workgroups fit the 256 compute units as 210 do: 1.8 times as long means that some units had two"""
+    d, r, c, ms = 11_214_720, 5, 55_872, {}
+    hp = inputs.hash_params(r, seed=46)
+    for n in (6, 7):
+        u, S = torch.randn(n, d, device="cuda"), torch.empty(n, r, c, device="cuda")
+        with context(d, n, r, c, hp, push_windows=107) as ctx:
+            ctx.sketch_accumulate(u, S)
+            times = []
+            for _ in range(7):
+                ctx.sams_profile_enable(True)
+                ctx.sketch_accumulate(u, S)
+                ctx.sams_profile_enable(False)
+                times.append(ctx.sams_profile_read()["k_sketch_push"][0])
+            ms[n] = min(times)
+    assert ms[7] < 1.4 * ms[6], ms
+
+
 def repeating(r, c, dist, rows):
     """Hash parameters under which, in the given rows, most coordinates share the bucket with the one `dist` on."""
     hp = inputs.hash_params(r, seed=5)
