@@ -58,7 +58,7 @@ typedef struct sams_ctx sams_ctx;
  *   always            4d bytes for the estimates, d/8 for the index bitmap, small selection state
  *   c above one LDS window, or d <= 2^22: the sketch plan and its staging buffer, 4*r*d + 4*n*r*d bytes and their padding
  *   10000 < c <= 652800 and 2^18 <= d <= 2^26 (2^22 for c <= 2^15), where it is the faster: lists, 4.4*r*d bytes (up to 8*r*d), and, in place of the staging
- *                     buffer, one of 4*r*d bytes or of (4*n + 2)*d bytes for one to r sorted copies of the vectors
+ *                     buffer, one of 4*r*d bytes, or of 4*n*d, and 2*d more, for each of one to r sorted copies of the vectors
  *   128 <= c <= 32768 (16384 for d < 2^18) and d <= 2^26, in their place: lists, 2 to 15 bytes per row and coordinate by the
  *                     hash (one that needs more than 24 + c/832 goes the other way), and above d = 2^22 up to 128 tables of
  *                     n*r*c floats; where these find no room, the context does without them (see "sketch_path")
@@ -93,11 +93,11 @@ int sams_create(sams_ctx **out, int64_t d, int32_t n, int32_t r, int64_t c, int6
  *                 fewer staged bytes, but runs that share a memory line with their neighbours)
  *   "scatter_threads" 256, 512 or 1024 (default 1024): workgroup size of the binned scatter pass
  *   "fuse_head"   0 (default), 1 or 2: with 1 or 2, amsgrad_ef_update or amsgrad_ef_update_pa (when it runs the head and the context uses
- *                 the binned path) also writes the sorted copy of e_u that sketch_accumulate needs, and a
+ *                 the binned path, or, with 2, sorted copies: see "sketch_path") also writes the sorted copy of e_u that sketch_accumulate needs, and a
  *                 following sketch_accumulate called with that same e_u pointer skips its first pass.
  *                 The caller must then not write to e_u between the two calls (the algorithm never does).
  *                 The sorted copy lives in the context's staging buffer and is forgotten as soon as anything else
- *                 uses that buffer (unsketch_topk, unsketch_estimates, topk_refine, a sketch_accumulate that stages row groups)
+ *                 uses that buffer (unsketch_topk, unsketch_estimates, topk_refine, a sketch_accumulate of another vector or in row groups)
  *                 or e_u changes through this library (any amsgrad_ef_update*): a later sketch_accumulate of the
  *                 same pointer then runs both passes again.
  *                 1: one workgroup per tile loops over the workers; 2: one workgroup per (tile, worker), the

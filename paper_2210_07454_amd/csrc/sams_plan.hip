@@ -2098,8 +2098,9 @@ static bool scatter_streams(const sams_ctx *ctx)
     return (int64_t)ctx->n * ctx->d * 4 > ((int64_t)96 << 20) || plan_metadata_bytes(ctx->plan) > ((int64_t)12 << 20);
 }
 
-// the sorted copies lie in the staging buffer; tiles of an XCD are taken in groups as in pass 1 (scatter_group), with short tiles in larger ones (25 million,
-// n = 16, three copies, tiles of 7,488, fused with the head: groups of 4, 16, 64 and 1,000 tiles 2.56, 2.47, 2.40 and 2.44 ms)
+// The sorted copies lie in the staging buffer; tiles of an XCD are taken in groups as in pass 1 (scatter_group), whose orders come to 3 MB.  Fused with the head
+// in groups of 1, 16, 64 and 1,000 tiles (us): 25 million, n = 16, four copies, tiles of 14,912 2,855, 2,825, 2,825 and 2,855 (25 now: 2,815); 11.2 million, n = 8,
+// two copies, tiles of 16,384 513, 502, 487 and 487 (45 now: 487); apart, three million, n = 8, two, 11,200 68, 52, 51 and 51 (64 now: 51).
 static CopyArgs copy_args(const sams_ctx *ctx)
 {
     const PushPlan &pp = ctx->push;

@@ -14,8 +14,8 @@
 // Out of the vectors themselves a group of 64 neighbouring coordinates of one of w windows touches 2 w lines, and that is what bounds it: a compute unit's L1
 // takes about two clocks for 16 lanes and a line, and the lines of all windows' workgroups come through it.  With more than a window or two (and where vectors
 // and lists do not fit the 256 MB cache together: 490 ns a phase there, 860 from HBM at three and six million, n = 8, 5 x 150,001) it is better to sort first: pass
-// 1 (k_sort_copies, or the head, sams_plan.hip) writes copies of the vectors whose phases are sorted by the windows of up to five rows, a window's values then
-// lie in long runs, and a row's lists name places in its copy.  That is one write per copy, from end to end, instead of one scattered write per row; the
+// 1 (k_sort_copies, or the head, sams_plan.hip) writes copies of the vectors whose phases are sorted by the windows of two to seven rows (push_rows), a window's values
+// then lie in long runs, and a row's lists name places in its copy.  That is one write per copy, from end to end, instead of one scattered write per row; the
 // copies' reads are one per row, as the binned path's are.  A phase of 1,870 entries takes 340 to 430 ns.  No one thing bounds it: without
 // the read-modify-writes, or with every second barrier, it takes as long; with all values from the caches (the same phase again and again) 8 to 16 % less, with the
 // words too 20 %, and without any values 30 to 38 % less (11.2 million, n = 8, 5 x 262,001 477, 441, 385 and 341 us; 25 million, n = 16, 10 x 100,000 3,573, 3,008,
@@ -30,8 +30,9 @@
 // Measured on MI355X with cold caches, sketch_accumulate by bins and by these lists (us): 853,610 coordinates, n = 14, 5 x 40,514 162 and 130; 1.8 million, n = 17, 3
 // x 56,323 239 and 160; 2.2 million, n = 83, 5 x 39,335 1,890 and 741 (one window); 4.3 million, n = 21, 5 x 134,908 930 and 606; 13.6 million, n = 19, 10 x
 // 110,245 4,423 and 3,005; 46 million, n = 8, 5 x 446,747 3,386 and 2,948; by slices (sams_pull.hip) and these lists: a million, n = 43, 5 x 19,287 363
-// and 191; 0.8 million, n = 70, 10 x 11,957 687 and 455.  Of 220 shapes with 0.27 to 60 million coordinates and 9,000 to 650,000 buckets that the rules below
-// send here, 209 are faster, 1.05 to 2.9 times (in the middle 1.35), and of the rest one is 11 % slower (0.29 million) and none of the others more than 5 %.
+// and 191; 0.8 million, n = 70, 10 x 11,957 687 and 455.  Of 290 shapes drawn at random (0.26 to 60 million coordinates, 10,000 to 650,000 buckets; all in
+// profiles/sketch_paths_us.txt) the rules below send 114 here: whole steps are 1.02 to 1.9 times as fast as by bins (93, in the middle 1.22) and 0.97 to 1.67 times
+// as fast as by slices (21, in the middle 1.23; three below 1).
 #include <math.h>
 #include <stdlib.h>
 #include <string.h>
@@ -534,7 +535,8 @@ static PushCopies push_copies(const sams_ctx *ctx, int32_t nwin, int32_t span, c
 
 // What a sketch should take, in ns.  Workgroups run in rounds of 256, one per compute unit.  A phase out of the vectors takes the longer the more windows share
 // their lines (cold caches; 310 to 400 with one window, 530 to 620 with two, up to 690 with four).  Out of copies it takes 320 at least and 340 to 430 with
-// 1,870 entries where all units are busy, less where few are (of 60 timings, 0.6 to 5 rounds, 9 in 10 within 15 %), and up to 500 where a copy has more than four
+// 1,870 entries where all units are busy, less where few are (of 51 timings 8 in 10 lie between 0.85 and 1.15 of what this says, the others
+// between 0.81 and 1.35; out of the vectors of 29 between 0.73 and 1.10, and 0.70 and 1.31), and up to 500 where a copy has more than four
 // rows, whose last ones read runs of 23 values; with rows that repeat 1.05 to 1.3 times that, also where a phase has dozens of entries for a bucket (0.94
 // million, n = 54, 10 x 31,212 with a distance of 82 in phases of 2,016 469 us, by bins 1,016; 25 million, n = 16, 10 x 100,000 with 202 in 7,488 5.3 ms, by
 // bins 7.5).  Copies are written at 5 TB/s, by the head at 4.0 to 5.
@@ -592,8 +594,8 @@ static double push_choose(const sams_ctx *ctx, const Tunables &tun, PushChoice *
     return best;
 }
 
-// Whether bins are taken to need more: 1.85 ns per thousand terms.  Against whole steps by bins the break-even lies at 2.0 to 2.2 of the cost above, with the head
-// fused or not (60 shapes of 0.5 to 43 million coordinates, two hashes each), and up to 3 below two million.
+// Whether bins are taken to need more: 1.85 ns per thousand terms, which errs towards the bins: of 160 drawn shapes that could go either way (see above) all 93 on
+// this side of the line take less by the lists, and of the 67 beyond it 50 would (1.02 to 1.74 times), six are alike and eleven take 1.01 to 1.32 times as long.
 static bool push_pays(const sams_ctx *ctx, const Tunables &tun, double cost)
 {
     return tun.push_windows ? cost < 1e30 : cost <= 10000 + (double)ctx->n * ctx->r * ctx->d * 1.85e-3;
@@ -627,9 +629,9 @@ static int32_t push_share(int32_t n, int64_t units, bool copies)
 
 // choice->ns: what a sketch should take this way (out of copies a little more: slices gain more from warm caches), 1e30 where bins are taken to need less or the
 // shape cannot.  Slices (sams_pull.hip) go first where they are taken to
-// need less.  Of 45 shapes of 10,000 to 32,768 buckets and 0.3 to 4.3 million coordinates, 13 change from slices to this: two take 2 to 3 % longer and eleven
-// less, 1.05 to 2.2 times (us, cold caches: 2.1 million, n = 25, 7 x 29,263 770 and 353; 1.6 million, n = 6, 5 x 14,952 157 and 118; 0.57 million, n = 69, 3 x
-// 21,015 159 and 127); of the 18 others that could, the slices are faster at 14, up to 2 times, and at the rest this is by 1 to 4 %.
+// need less.  Of 130 drawn shapes that could go by slices or this (see above) 21 take this: whole steps are 1.05 to 1.67 times as fast at 18, alike at one, and 1 and
+// 2.5 % slower at two; of the 109 that keep the slices those are the faster at 74, up to 2.6 times, and at 31 this would be by 1.02 to 1.3 (us, sketches with cold
+// caches: 2.1 million, n = 25, 7 x 29,263 770 and 353; 1.6 million, n = 6, 5 x 14,952 157 and 118; 0.57 million, n = 69, 3 x 21,015 159 and 127).
 int push_estimate(sams_ctx *ctx, const Tunables &tun, PushChoice *choice)
 {
     choice->ns = 1e30;
