@@ -58,7 +58,8 @@ typedef struct sams_ctx sams_ctx;
  *   always            4d bytes for the estimates, d/8 for the index bitmap, small selection state
  *   c above one LDS window, or d <= 2^22: the sketch plan and its staging buffer, 4*r*d + 4*n*r*d bytes and their padding
  *   10000 < c <= 652800 and 2^18 <= d <= 2^26 (2^22 for c <= 2^15), where it is the faster: lists, 4.4*r*d bytes (up to 8*r*d), and, in place of the staging
- *                     buffer, one of 4*r*d bytes, or of 4*n*d, and 2*d more, for each of one to r sorted copies of the vectors
+ *                     buffer, one of 4*r*d bytes, or of 4*n*d, and 2*d more, for each of one to r sorted copies of the vectors;
+ *                     where these, or what "fuse_head" 2 takes beside them, find no room, the context goes one of the other ways
  *   128 <= c <= 32768 (16384 for d < 2^18) and d <= 2^26, in their place: lists, 2 to 15 bytes per row and coordinate by the
  *                     hash (one that needs more than 24 + c/832 goes the other way), and above d = 2^22 up to 128 tables of
  *                     n*r*c floats; where these find no room, the context does without them (see "sketch_path")
